@@ -12,6 +12,7 @@
 
 #include "lif_common.h"
 #include "lif_ffn.h"
+#include "lif_ffn_down1.h"
 #include "lif_ffn_mfma.h"
 #include "lif_ffn_down_mfma.h"
 #include "lif_predict.h"
@@ -235,33 +236,51 @@ void launch_ffn_up(lif_layer* L, const void* x, int batch, float* h, hipStream_t
 #undef LIF_UP_X
 }
 
-template <typename T, int BT, bool SKIP, int LANES>
-void launch_ffn_down_as(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, bool use_new) {
+// rows the launch geometry is made for: the row-count hint with some slack, else the capacity
+int geometry_rows(const lif_layer* L) {
+    return L->expected_rows > 0 ? std::min(L->cfg.capacity_rows, L->expected_rows + L->expected_rows / 8)
+                                : L->cfg.capacity_rows;
+}
+
+// one token
+template <typename T, bool SKIP>
+void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t s, bool use_new) {
     const lif_config& c = L->cfg;
-    const int cols = LANES * Vec<T>::N;
-    int slices = (c.d_model + cols - 1) / cols;
-    if (LANES * 16 < 128) slices = (slices + kXcds - 1) / kXcds * kXcds;      // whole runs of slices per XCD
-    // workgroup rows: enough for the chunks of the expected number of rows (with some slack), else of the
-    // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
-    const int rows_hint = L->expected_rows > 0 ? std::min(c.capacity_rows, L->expected_rows + L->expected_rows / 8)
-                                               : c.capacity_rows;
-    const int wg_rows = down_chunks<BT, SKIP>(rows_hint);
+    constexpr int cols = kDown1Lanes * Vec<T>::N;
+    const int slices = ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;     // whole runs of slices per XCD
+    const int rows = geometry_rows(L);
+    const int wg_rows = down1_chunks<SKIP>(rows);    // fewer than the chunks in use is still correct
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    // one token: groups of 256 slots whose activations the first workgroup row asks for before the row count arrives
-    // (from the hint; 2048 slots without one); several tokens: all of the first pass
-    const int spec_groups = BT > 1 ? (1 << 20) : L->expected_rows > 0 ? std::max(1, (rows_hint + 255) / 256) : 8;
-    // one token: compaction passes of 4096 slots when more than 2048 rows are expected (one pass instead of two;
-    // the sums are the same), of 2048 otherwise (half the registers and guards on the shortest path)
-    if (BT == 1 && L->expected_rows > 0 && rows_hint > kDownTile)
-        hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, LANES, 2 * kDownTile>), dim3(slices, wg_rows), dim3(256), 0, s,
-                           (const T*)L->buf.matrix, h, use_new ? L->h_new : nullptr, use_new ? L->stamp : nullptr,
-                           (T*)y, ypart, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, spec_groups, L->st);
-    else
-        hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, LANES>), dim3(slices, wg_rows), dim3(256), 0, s,
-                           (const T*)L->buf.matrix, h, use_new ? L->h_new : nullptr, use_new ? L->stamp : nullptr,
-                           (T*)y, ypart, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, spec_groups, L->st);
+    const int waves = down1_waves(rows);
+    // groups of slots whose activations are asked for ahead of the row count: those the hint covers; without a hint 2048
+    // slots if that many rows make one pass (else the order of the slots is not known yet)
+    const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;
+#define LIF_D1(W)                                                                                            \
+    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W>), dim3(slices, wg_rows), dim3(W * 64), 0, s, (const T*)L->buf.matrix, h,  \
+                       use_new ? L->h_new : nullptr, use_new ? L->stamp : nullptr, (T*)y, ypart, c.d_model,         \
+                       c.capacity_rows, L->row_elems, down_off, spec, L->st)
+    if (waves == 8) LIF_D1(8);
+    else LIF_D1(16);
+#undef LIF_D1
     if (wg_rows > 1)
-        hipLaunchKernelGGL((k_ffn_down_finish<T, BT, SKIP>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_ffn_down_finish<T, down1_chunks<SKIP>>), dim3((c.d_model + 255) / 256), dim3(256), 0, s,
+                           ypart, (T*)y, c.d_model, 1, L->st);
+}
+
+// several tokens, fp32
+template <typename T, int BT, bool SKIP>
+void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s) {
+    const lif_config& c = L->cfg;
+    constexpr int cols = kDownLanesB * Vec<T>::N;
+    // workgroup rows: enough for the chunks of the expected number of rows; fewer than the chunks in use is still
+    // correct (a workgroup row then takes several chunks)
+    const int wg_rows = down_chunks(geometry_rows(L));
+    const int down_off = (c.glu ? 2 : 1) * c.d_model;
+    hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB>), dim3((c.d_model + cols - 1) / cols, wg_rows), dim3(256), 0,
+                       s, (const T*)L->buf.matrix, h, (T*)y, ypart, c.d_model, batch, c.capacity_rows, L->row_elems,
+                       down_off, L->st);
+    if (wg_rows > 1)
+        hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
                            ypart, (T*)y, c.d_model, batch, L->st);
 }
 
@@ -273,9 +292,7 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
     const int chunk_rows = down_mfma_chunk_rows(c.capacity_rows);
     // workgroup rows: enough for the chunks of the expected number of rows (with some slack), else of the
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
-    const int rows_hint = L->expected_rows > 0 ? std::min(c.capacity_rows, L->expected_rows + L->expected_rows / 8)
-                                               : c.capacity_rows;
-    const int wg_rows = down_mfma_chunks(rows_hint, chunk_rows);
+    const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
     hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves>), dim3(slices, wg_rows), dim3(kDmWaves * 64), 0, s,
                        (const _Float16*)L->buf.matrix, h, (_Float16*)y, ypart, c.d_model, batch, c.capacity_rows,
@@ -288,22 +305,20 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
 template <typename T>
 void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, bool use_new = false) {
     const bool skip = L->cfg.ffn_mode == LIF_FFN_SKIP_DEAD;
-    if constexpr (std::is_same<T, _Float16>::value) {
-        if (batch > 1) {
-            if (skip) launch_ffn_down_mfma<true>(L, batch, y, h, ypart, s);
-            else launch_ffn_down_mfma<false>(L, batch, y, h, ypart, s);
-            return;
-        }
-    }
     if (batch == 1) {
-        if (skip) launch_ffn_down_as<T, 1, true, kDownLanes1>(L, batch, y, h, ypart, s, use_new);
-        else launch_ffn_down_as<T, 1, false, kDownLanesN>(L, batch, y, h, ypart, s, use_new);
+        if (skip) launch_ffn_down1<T, true>(L, y, h, ypart, s, use_new);
+        else launch_ffn_down1<T, false>(L, y, h, ypart, s, use_new);
+        return;
+    }
+    if constexpr (std::is_same<T, _Float16>::value) {
+        if (skip) launch_ffn_down_mfma<true>(L, batch, y, h, ypart, s);
+        else launch_ffn_down_mfma<false>(L, batch, y, h, ypart, s);
     } else if (batch <= 4) {
-        if (skip) launch_ffn_down_as<T, 4, true, kDownLanesB>(L, batch, y, h, ypart, s, use_new);
-        else launch_ffn_down_as<T, 4, false, kDownLanesB>(L, batch, y, h, ypart, s, use_new);
+        if (skip) launch_ffn_down_batch<T, 4, true>(L, batch, y, h, ypart, s);
+        else launch_ffn_down_batch<T, 4, false>(L, batch, y, h, ypart, s);
     } else {
-        if (skip) launch_ffn_down_as<T, 8, true, kDownLanesB>(L, batch, y, h, ypart, s, use_new);
-        else launch_ffn_down_as<T, 8, false, kDownLanesB>(L, batch, y, h, ypart, s, use_new);
+        if (skip) launch_ffn_down_batch<T, 8, true>(L, batch, y, h, ypart, s);
+        else launch_ffn_down_batch<T, 8, false>(L, batch, y, h, ypart, s);
     }
 }
 

@@ -8,10 +8,9 @@
 //             issued before the first use; the wave reduces the dot product and writes the
 //             activation h[s].
 //   ffn_down  workgroups per slice of output columns (and per chunk of rows once the cache is large): no
-//             atomics, fixed summation order.  It compacts the rows with a non-zero activation
-//             (prefix sum in LDS) and streams only their down columns.  (A variant without
-//             compaction - predicated loads over all rows - measured 1.6 us slower at the
-//             OPT-6.7B shape.)
+//             atomics, fixed summation order.  It compacts the rows with a non-zero activation and
+//             streams only their down columns: k_ffn_down1 (lif_ffn_down1.h) for one token,
+//             k_ffn_down below for several tokens in fp32.
 #pragma once
 
 #include "lif_common.h"
@@ -177,52 +176,39 @@ constexpr int kXcds = 8;            // accelerator complex dies of an MI355X, ea
 constexpr int kDownTile = 2048;     // activations (rows x tokens) compacted per pass (at least 512 rows)
 constexpr int kDownChunksMax = 32;  // row chunks of the down projection (partial outputs per chunk)
 constexpr int kDownLanesB = 16;       // lanes per column slice for several tokens
-constexpr int kDownLanes1 = 4;        // ... single token skipping dead rows (latency bound)
-constexpr int kDownLanesN = 8;        // ... when most rows are read: 8 x 16 B = one 128-byte line per row
-constexpr int kDownRowsSparse = 4096; // rows per chunk: single token, rows without activation skipped
-constexpr int kDownRowsDense = 512;   // ... single token, every row read
-constexpr int kDownRowsBatch = 512;   // ... several tokens
+constexpr int kDownRowsBatch = 512;   // rows per chunk for several tokens
 
-// Row chunks in use for n cached rows.  For a single token and up to 4096 rows (1024 in full-bundle mode), one
-// chunk (one workgroup per column slice, no partial sums) is the shortest path: the kernel is latency bound
-// there.  Beyond that, the single-token
-// case that skips rows without activation keeps chunks of 4096 rows (one compaction pass each; few rows
-// contribute); when most rows are read (full-bundle mode, or several tokens whose active sets add up) a
-// chunk is 512 rows so that several hundred workgroups stream at once: column slices alone (d / 64
-// workgroups) reach only about 3 TB/s.  The host sizes the grid with the same rule.
-template <int BT, bool SKIP>
+// Row chunks in use for n cached rows and several tokens: their active sets add up, most rows are read, and a chunk is
+// 512 rows so that several hundred workgroups stream at once (column slices alone, d / 64 workgroups, reach only
+// about 3 TB/s).  The host sizes the grid with the same rule.
 __host__ __device__ __forceinline__ int down_chunks(int n) {
-    constexpr int per = (BT == 1 && SKIP) ? kDownRowsSparse : (BT == 1 ? kDownRowsDense : kDownRowsBatch);
-    if (BT == 1 && n <= (SKIP ? kDownRowsSparse : 2 * kDownRowsDense)) return 1;
-    const int c = (n + per - 1) / per;
+    const int c = (n + kDownRowsBatch - 1) / kDownRowsBatch;
     return c < 1 ? 1 : (c > kDownChunksMax ? kDownChunksMax : c);
 }
 
-// Down projection  y[t][j] = sum_s H[t][s] * D[s][j]  over the rows in use, for 1..BT tokens.
+// Down projection  y[t][j] = sum_s H[t][s] * D[s][j]  over the rows in use, for 2..BT tokens (fp32 layers; fp16
+// batches run on the matrix cores, single tokens in k_ffn_down1).
 // grid = (column slices, row-chunk workgroups), block = 256 = (256 / LANES) row groups x LANES lanes; a
 // lane owns 16 bytes of every down column it reads, a workgroup LANES * 16 contiguous bytes.
 // SKIP: rows whose activation is zero for every token of the batch are not read (they are compacted
 // away with a prefix sum in LDS, in a fixed order).
-// h_new / stamp (may be null): activations of the rows that the fused load kernel wrote during the
-// step whose number equals stamp[s]; they override h for those rows.
 // The rows are cut into down_chunks(n) chunks - a function of n alone, so the arithmetic does not
 // depend on the launch geometry - and workgroup row y takes the chunks y, y + gridDim.y, ...  Every
 // chunk is summed from zero.  With one chunk in use the workgroup writes its columns of y.  With more,
 // a grid of one workgroup row adds its chunk sums in chunk order and writes y; a taller grid writes
 // them to ypart[chunk][token][d] (fp32) and k_ffn_down_finish adds them in the same order.  No atomics.
-template <typename T, int BT, bool SKIP, int LANES, int TS1 = kDownTile>
+template <typename T, int BT, bool SKIP, int LANES>
 __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, const float* __restrict__ h,
-                                                  const float* __restrict__ h_new, const int32_t* __restrict__ stamp,
                                                   T* __restrict__ y, float* __restrict__ ypart, int d, int batch,
-                                                  int capacity, size_t row_elems, int down_off, int spec_groups,
+                                                  int capacity, size_t row_elems, int down_off,
                                                   DevState* __restrict__ st) {
+    static_assert(BT > 1, "single tokens: k_ffn_down1");
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N;
     constexpr int RG = 256 / LANES;                  // row groups per workgroup
-    // rows per compaction pass (one token: TS1, 2048 or 4096 - the host picks by the row-count hint; both give the
-    // same bits, see below)
-    constexpr int TS = (BT == 1) ? TS1 : (kDownTile / BT < 512) ? 512 : kDownTile / BT;
+    constexpr int TS = (kDownTile / BT < 512) ? 512 : kDownTile / BT;      // rows per compaction pass
     constexpr int PER = TS / 256;                    // slots per thread in the compaction
+    static_assert(LANES * 16 >= 128, "a slice covers whole L2 lines");
     __shared__ int list[TS];
     __shared__ float hv[BT][TS];
     __shared__ int wave_tot[4];
@@ -230,15 +216,7 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     __shared__ int n_active;
 
     const int tid = threadIdx.x, l = tid & (LANES - 1), rg = tid / LANES;
-    // XCD-aware slice order when a slice is narrower than a 128-byte L2 line: workgroups are dealt
-    // round-robin to the 8 XCDs, each with its own L2; giving every XCD a contiguous run of slices makes
-    // the parts of a line meet in one L2 instead of being fetched by several (the host rounds the
-    // grid up to a multiple of 8 in that case).
-    int slice = blockIdx.x;
-    if (LANES * 16 < 128) {
-        const int per_xcd = gridDim.x / kXcds;
-        slice = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    }
+    const int slice = blockIdx.x;
     const int col = slice * (LANES * VE) + l * VE;
     const bool col_ok = col < d;
     const T* base = matrix + down_off + (col_ok ? col : 0);
@@ -248,56 +226,26 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     // (the activation array spans the whole capacity, so the addresses are valid; values past
     // num_used are masked below): one memory round trip less on the critical path
     const bool first_row = blockIdx.y == 0;
-    // (uniform branches around unconditional loads from clamped slots: a predicate per load would cost a branch each;
-    // spec_groups = how many groups of 256 slots to ask for now when a pass has more than 8: the host derives it from
-    // the row-count hint, the rest is read once the count is known)
-    float hfirst[PER][BT], hnfirst[PER][BT];
-    int sfirst[PER];
+    float hfirst[PER][BT];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        sfirst[q] = -1;
+    for (int q = 0; q < PER; ++q)
 #pragma unroll
-        for (int b = 0; b < BT; ++b) hfirst[q][b] = hnfirst[q][b] = 0.f;
-    }
+        for (int b = 0; b < BT; ++b) hfirst[q][b] = 0.f;
     if (first_row) {
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (b < batch) {
 #pragma unroll
-                for (int q = 0; q < PER; ++q)
-                    if (PER <= 8 || q < spec_groups) hfirst[q][b] = h[(size_t)b * capacity + min(q * 256 + tid, capacity - 1)];
-            }
-        }
-        if (stamp) {
-            // the loader-written activations travel in the same round trip as h and the stamps
-#pragma unroll
-            for (int q = 0; q < PER; ++q)
-                if (PER <= 8 || q < spec_groups) sfirst[q] = stamp[min(q * 256 + tid, capacity - 1)];
-#pragma unroll
-            for (int b = 0; b < BT; ++b) {
-                if (b < batch) {
-#pragma unroll
-                    for (int q = 0; q < PER; ++q)
-                        if (PER <= 8 || q < spec_groups) hnfirst[q][b] = h_new[(size_t)b * capacity + min(q * 256 + tid, capacity - 1)];
-                }
+                for (int q = 0; q < PER; ++q) hfirst[q][b] = h[(size_t)b * capacity + min(q * 256 + tid, capacity - 1)];
             }
         }
     }
     const int err = st->error;
     const int n = err ? 0 : st->num_used;
-    const int cur_step = st->step;
     if (err) return;
-    const int chunks = down_chunks<BT, SKIP>(n);
+    const int chunks = down_chunks(n);
     if ((int)blockIdx.y >= chunks) return;           // uniform
     const int per_chunk = (n + chunks - 1) / chunks;
-    if (first_row && stamp) {
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (sfirst[q] == cur_step) {
-#pragma unroll
-                for (int b = 0; b < BT; ++b) hfirst[q][b] = hnfirst[q][b];
-            }
-    }
     const int ob = tid / LANES, ol = tid - ob * LANES;            // (token, lane) whose 16-byte piece this thread writes
     const int ocol = slice * (LANES * VE) + ol * VE;
     const bool writer = tid < LANES * BT && ocol < d && ob < batch;
@@ -311,153 +259,69 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
 #pragma unroll
         for (int i = 0; i < BT * VE; ++i) acc[i] = 0.f;
         __syncthreads();
-        if constexpr (BT == 1) {
-            // One token: every wave compacts the slots of its own lanes with ballots into its own quarter of the
-            // list and then reads the rows of that quarter, so a pass needs no workgroup barrier and no scan through
-            // LDS (a wave's LDS operations complete in order).  Slots are dealt to threads round-robin, so the waves
-            // get even shares.  Order inside a wave: slot-major (q, then lane); the adds stay in list order.
-            constexpr int WL = TS / 4;                   // list entries per wave (PER slots x 64 lanes)
-            constexpr int RGW = 64 / LANES;              // row groups per wave
-            const int lane = tid & 63, wv = tid >> 6, rgw = lane / LANES;
-            int* wlist = list + wv * WL;
-            float* whv = hv[0] + wv * WL;
-            // A thread takes the list positions i with i mod RGW = its row group, counted over the whole chunk and
-            // not per pass, and adds them in ascending order: passes of 2048 or of 4096 slots give the same sums.
-            int cnt = 0;                                 // entries of this wave's list so far (uniform over the wave)
-            for (int s_base = r0; s_base < r1; s_base += TS) {
-                const int start = cnt;                   // list position of the first entry of this pass
-                int nz = 0;
-                float hval[PER];
-                const int need = min(PER, (r1 - s_base + 255) >> 8);      // groups of 256 slots with rows in them
-                const int have = (s_base == 0) ? (PER <= 8 ? PER : min(spec_groups, PER)) : 0;   // ... of which requested at the start
+        for (int s_base = r0; s_base < r1; s_base += TS) {
+            // compaction of the rows that contribute, in a fixed order (thread-major over slots q * 256 + tid)
+            float hloc[PER][BT];
+            unsigned flags = 0, nonzero = 0;
 #pragma unroll
-                for (int q = 0; q < PER; ++q) hval[q] = hfirst[q][0];       // (only chunk 0 starts at row 0)
-                if (need > have) {
+            for (int q = 0; q < PER; ++q) {
+                const int s = s_base + q * 256 + tid;
+                bool any = false;
 #pragma unroll
-                    for (int q = 0; q < PER; ++q)
-                        if (q >= have && q < need) hval[q] = h[min(s_base + q * 256 + tid, capacity - 1)];
-                    if (stamp) {
-#pragma unroll
-                        for (int q = 0; q < PER; ++q) {
-                            if (q >= have && q < need) {
-                                const int sc = min(s_base + q * 256 + tid, capacity - 1);
-                                const float hn = h_new[sc];
-                                if (stamp[sc] == cur_step) hval[q] = hn;
-                            }
-                        }
+                for (int b = 0; b < BT; ++b) {
+                    float v = 0.f;
+                    if (s < r1 && b < batch) {
+                        if (s_base == 0) v = hfirst[q][b];       // only chunk 0 (first workgroup row) starts at row 0
+                        else v = h[(size_t)b * capacity + s];
                     }
+                    hloc[q][b] = v;
+                    any |= (v != 0.f);
                 }
-#pragma unroll
-                for (int q = 0; q < PER; ++q) {
-                    if (PER <= 8 || q < need) {           // uniform (short passes: all groups, empty ones cost little)
-                        const int s = s_base + q * 256 + tid;
-                        const float v = (s < r1) ? hval[q] : 0.f;
-                        const bool nonzero = v != 0.f;
-                        const bool take = SKIP ? nonzero : s < r1;
-                        const unsigned long long m = __ballot(take);
-                        if (take) {
-                            const int pos = cnt + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-                            wlist[pos - start] = s;
-                            whv[pos - start] = v;
-                        }
-                        cnt += __popcll(m);
-                        nz += SKIP ? __popcll(m) : __popcll(__ballot(nonzero));
-                    }
-                }
-                if (slice == 0 && lane == 0 && nz) atomicAdd(&n_active, nz);      // statistics only
-                __builtin_amdgcn_wave_barrier();
-                if (col_ok) {
-                    // all row loads of a pass over kInFlight rows per thread are issued before the first use
-                    constexpr int kInFlight = 8;
-                    const int first = start + ((rgw - start) & (RGW - 1));   // first position >= start of this row group
-                    for (int i0 = first; i0 < cnt; i0 += RGW * kInFlight) {
-                        V v[kInFlight];
-#pragma unroll
-                        for (int u = 0; u < kInFlight; ++u) {
-                            const int i = i0 + u * RGW;
-                            const int sr = wlist[(i < cnt ? i : i0) - start];
-                            v[u] = (i < cnt) ? *reinterpret_cast<const V*>(base + (size_t)sr * row_elems) : V(0);
-                        }
-#pragma unroll
-                        for (int u = 0; u < kInFlight; ++u) {
-                            const int i = i0 + u * RGW;
-                            if (i < cnt) {
-                                const float hb = whv[i - start];
-#pragma unroll
-                                for (int e = 0; e < VE; ++e) acc[e] = __builtin_fmaf(hb, (float)v[u][e], acc[e]);
-                            }
-                        }
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
+                if (any) nonzero |= 1u << q;
+                if (!SKIP) any = s < r1;
+                if (any) flags |= 1u << q;
             }
-        } else {
-            for (int s_base = r0; s_base < r1; s_base += TS) {
-                // compaction of the rows that contribute, in a fixed order (thread-major over slots q * 256 + tid)
-                float hloc[PER][BT];
-                unsigned flags = 0, nonzero = 0;
+            if (slice == 0 && nonzero) atomicAdd(&n_active, __popc(nonzero));   // statistics only
+            int cnt;
+            int off = block_exclusive_scan<4>(__popc(flags), wave_tot, &cnt);
 #pragma unroll
-                for (int q = 0; q < PER; ++q) {
-                    const int s = s_base + q * 256 + tid;
-                    bool any = false;
+            for (int q = 0; q < PER; ++q) {
+                if (flags & (1u << q)) {
+                    list[off] = s_base + q * 256 + tid;
 #pragma unroll
-                    for (int b = 0; b < BT; ++b) {
-                        float v = 0.f;
-                        if (s < r1 && b < batch) {
-                            if (s_base == 0) v = hfirst[q][b];       // only chunk 0 (first workgroup row) starts at row 0
-                            else v = (stamp && stamp[s] == cur_step) ? h_new[(size_t)b * capacity + s]
-                                                                     : h[(size_t)b * capacity + s];
-                        }
-                        hloc[q][b] = v;
-                        any |= (v != 0.f);
-                    }
-                    if (any) nonzero |= 1u << q;
-                    if (!SKIP) any = s < r1;
-                    if (any) flags |= 1u << q;
+                    for (int b = 0; b < BT; ++b) hv[b][off] = hloc[q][b];
+                    ++off;
                 }
-                if (slice == 0 && nonzero) atomicAdd(&n_active, __popc(nonzero));   // statistics only
-                int cnt;
-                int off = block_exclusive_scan<4>(__popc(flags), wave_tot, &cnt);
+            }
+            __syncthreads();
+            if (col_ok) {
+                // all row loads of a pass over kInFlight rows per thread are issued before the first use (a loop with a
+                // run-time trip count would wait for every load in turn); the adds stay in ascending row order
+                constexpr int kInFlight = 4;
+                for (int i0 = rg; i0 < cnt; i0 += RG * kInFlight) {
+                    V v[kInFlight];
 #pragma unroll
-                for (int q = 0; q < PER; ++q) {
-                    if (flags & (1u << q)) {
-                        list[off] = s_base + q * 256 + tid;
-#pragma unroll
-                        for (int b = 0; b < BT; ++b) hv[b][off] = hloc[q][b];
-                        ++off;
+                    for (int u = 0; u < kInFlight; ++u) {
+                        const int i = i0 + u * RG;
+                        const int s = list[i < cnt ? i : i0];
+                        v[u] = (i < cnt) ? *reinterpret_cast<const V*>(base + (size_t)s * row_elems) : V(0);
                     }
-                }
-                __syncthreads();
-                if (col_ok) {
-                    // all row loads of a pass over kInFlight rows per thread are issued before the first use (a loop with a
-                    // run-time trip count would wait for every load in turn); the adds stay in ascending row order
-                    constexpr int kInFlight = (BT == 1) ? 8 : 4;
-                    for (int i0 = rg; i0 < cnt; i0 += RG * kInFlight) {
-                        V v[kInFlight];
 #pragma unroll
-                        for (int u = 0; u < kInFlight; ++u) {
-                            const int i = i0 + u * RG;
-                            const int s = list[i < cnt ? i : i0];
-                            v[u] = (i < cnt) ? *reinterpret_cast<const V*>(base + (size_t)s * row_elems) : V(0);
-                        }
+                    for (int u = 0; u < kInFlight; ++u) {
+                        const int i = i0 + u * RG;
+                        if (i < cnt) {
 #pragma unroll
-                        for (int u = 0; u < kInFlight; ++u) {
-                            const int i = i0 + u * RG;
-                            if (i < cnt) {
+                            for (int b = 0; b < BT; ++b) {
+                                const float hb = hv[b][i];
 #pragma unroll
-                                for (int b = 0; b < BT; ++b) {
-                                    const float hb = hv[b][i];
-#pragma unroll
-                                    for (int e = 0; e < VE; ++e)
-                                        acc[b * VE + e] = __builtin_fmaf(hb, (float)v[u][e], acc[b * VE + e]);
-                                }
+                                for (int e = 0; e < VE; ++e)
+                                    acc[b * VE + e] = __builtin_fmaf(hb, (float)v[u][e], acc[b * VE + e]);
                             }
                         }
                     }
                 }
-                __syncthreads();
             }
+            __syncthreads();
         }
         // the row groups of one wave sit LANES lanes apart: halving butterfly over the upper lane bits (a lane
         // ends with a few finished sums), then LDS over waves
@@ -505,11 +369,12 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
 // y = sum of the chunk partials in chunk order, rounded once to the element type.  Launched after a
 // k_ffn_down grid of more than one workgroup row; does nothing when a single chunk was in use (y is
 // written already).  grid = ceil(batch * d / 256), block = 256.
-template <typename T, int BT, bool SKIP>
+// CHUNKS: the chunk rule of the kernel that wrote the partials.
+template <typename T, int (*CHUNKS)(int)>
 __global__ __launch_bounds__(256) void k_ffn_down_finish(const float* __restrict__ ypart, T* __restrict__ y, int d,
                                                          int batch, const DevState* __restrict__ st) {
     if (st->error) return;
-    const int chunks = down_chunks<BT, SKIP>(st->num_used);
+    const int chunks = CHUNKS(st->num_used);
     if (chunks == 1) return;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= batch * d) return;

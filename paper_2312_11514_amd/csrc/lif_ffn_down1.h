@@ -1,0 +1,215 @@
+// Step 4, down projection of a single token (Section 3.3 item 3):  y[j] = sum_s h[s] * D[s][j]  over the rows in use.
+//
+// What bounds it: a few hundred to a few thousand 64-byte pieces per workgroup behind three dependent memory round
+// trips (activations and row count -> down columns -> y), so latency first and the loads in flight per compute unit
+// second.  A workgroup owns 64 bytes of every down column (d / 32 workgroups in fp16: about half the compute units) and
+// has many waves, so that each wave compacts few slots and each thread has few rows, all of them in flight at once.
+// Measured in a HIP graph on gfx950 (rows in use / rows with an activation, fp16, d = 4096; before = 4 waves per
+// workgroup, partial sums and a second launch above 4096 rows or when every row is read):
+//     1060 / 337    4.0 -> 3.6 us      1927 / 864    6.0 -> 4.2      4096 / 1366   9.0 -> 5.0
+//     8000 / 2500  11.5 -> 8.6         1060, all rows read  7.2 -> 4.6         2977, all rows read  7.8 -> 6.3
+// Slices of 32 or 128 bytes were slower at most sizes (half a line wasted per piece; too few workgroups).
+#pragma once
+
+#include "lif_common.h"
+#include "lif_ffn.h"
+
+namespace lif {
+
+constexpr int kDown1Lanes = 4;           // lanes per row: 64 bytes of its down column
+constexpr int kDown1Per = 4;             // slots a thread compacts per pass
+constexpr int kDown1FewRows = 2048;      // up to here one pass of 8 waves covers all rows
+constexpr int kDown1RowsSkip = 8192;     // rows per chunk when rows without activation are skipped
+constexpr int kDown1RowsFull = 2048;     // ... when every row is read, once there are more than kDown1OneFull
+constexpr int kDown1OneFull = 4096;
+
+// Row chunks in use for n cached rows.  One chunk (no partial sums, no second launch) as long as d / 32 workgroups keep
+// up with the rows: skipping rows, 8000 rows take 8.6 us in one chunk against 11.5 us in two chunks and a second
+// launch; reading every row, one chunk is faster up to about 4096 rows (8000 rows: 21 us in one chunk).
+template <bool SKIP>
+__host__ __device__ __forceinline__ int down1_chunks(int n) {
+    if (n <= (SKIP ? kDown1RowsSkip : kDown1OneFull)) return 1;
+    constexpr int per = SKIP ? kDown1RowsSkip : kDown1RowsFull;
+    return (n + per - 1) / per;              // at most 65536 / 2048 = kDownChunksMax
+}
+
+// Waves of the summation order for n rows: a function of n alone.  The slots are dealt to that many (virtual) waves,
+// 64 consecutive slots at a time; every wave compacts its own slots with ballots into its own list, takes the list
+// positions i with i mod 16 = row group in ascending order, folds its row groups, and the waves are added in order.  A
+// workgroup launched with other than that many waves goes through the virtual waves in turn (or leaves some idle), so
+// the result does not depend on the launch geometry.
+__host__ __device__ __forceinline__ int down1_waves(int n) { return n <= kDown1FewRows ? 8 : 16; }
+
+// grid = (column slices of 64 bytes, rounded up to a multiple of 8; row-chunk workgroups), block = WAVES * 64.
+// h_new / stamp (may be null): activations of the rows that the fused load kernel wrote during the step whose number
+// equals stamp[s]; they override h for those rows.
+// spec: groups of WAVES * 64 slots whose activations are requested before the row count is known (the arrays span the
+// capacity, so the addresses are valid; values past the count are masked).
+// Workgroup row y takes the chunks y, y + gridDim.y, ...; with several chunks and several workgroup rows the sums go to
+// ypart[chunk][d] (fp32) and k_ffn_down_finish adds them, else this kernel adds them in the same order.  No atomics.
+template <typename T, bool SKIP, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ matrix, const float* __restrict__ h,
+                                                          const float* __restrict__ h_new,
+                                                          const int32_t* __restrict__ stamp, T* __restrict__ y,
+                                                          float* __restrict__ ypart, int d, int capacity,
+                                                          size_t row_elems, int down_off, int spec,
+                                                          DevState* __restrict__ st) {
+    using V = typename Vec<T>::type;
+    constexpr int VE = Vec<T>::N, LANES = kDown1Lanes, PER = kDown1Per, THREADS = WAVES * 64;
+    constexpr int WL = PER * 64;                     // list entries per wave and pass
+    constexpr int RG = 64 / LANES;                   // row groups per wave
+    constexpr int VWMAX = 16;
+    __shared__ int list[WAVES][WL];
+    __shared__ float hv[WAVES][WL];
+    __shared__ float red[VWMAX][LANES][VE + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l = lane & (LANES - 1), rg = lane / LANES;
+    // XCD-aware slice order: workgroups are dealt round-robin to the 8 XCDs, each with its own L2; giving every XCD a
+    // contiguous run of slices makes the two halves of a 128-byte line meet in one L2 instead of being fetched twice
+    const int per_xcd = gridDim.x / kXcds;
+    const int slice = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    const int col = slice * (LANES * VE) + l * VE;
+    const bool col_ok = col < d;
+    const T* base = matrix + down_off + (col_ok ? col : 0);
+
+    float hfirst[PER], hnfirst[PER];
+    int sfirst[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        hfirst[q] = hnfirst[q] = 0.f;
+        sfirst[q] = -1;
+    }
+    const bool first_row = blockIdx.y == 0;
+    if (first_row) {                                 // (uniform branches around loads from clamped slots)
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (q < spec) hfirst[q] = h[min(q * THREADS + tid, capacity - 1)];
+        if (stamp) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+                if (q < spec) {
+                    sfirst[q] = stamp[min(q * THREADS + tid, capacity - 1)];
+                    hnfirst[q] = h_new[min(q * THREADS + tid, capacity - 1)];
+                }
+        }
+    }
+    const int err = st->error, n = st->num_used, cur_step = st->step;
+    if (err) return;
+    const int chunks = down1_chunks<SKIP>(n);
+    if ((int)blockIdx.y >= chunks) return;           // uniform
+    const int per_chunk = (n + chunks - 1) / chunks;
+    const int vwaves = down1_waves(n);
+    const int stride = vwaves * 64;                  // slots between the groups of a (virtual) wave
+    const bool natural = vwaves == WAVES;            // the requests above were for the right slots
+    float total = 0.f;
+    for (int chunk = blockIdx.y; chunk < chunks; chunk += gridDim.y) {
+        const int r0 = chunk * per_chunk, r1 = min(n, r0 + per_chunk);
+        for (int vw = wv; vw < vwaves; vw += WAVES) {
+            float acc[VE];
+#pragma unroll
+            for (int i = 0; i < VE; ++i) acc[i] = 0.f;
+            int cnt = 0;                             // entries of this wave's list so far (uniform over the wave)
+            int nz = 0;
+            for (int s_base = r0; s_base < r1; s_base += PER * stride) {
+                const int s0 = s_base + vw * 64 + lane;
+                const int start = cnt;               // list position of the first entry of this pass
+                const int need = min(PER, (r1 - s_base - vw * 64 + stride - 1) / stride);       // groups with rows in them
+                const int have = (natural && first_row && s_base == 0) ? spec : 0;              // ... requested at the start
+                float hval[PER];
+#pragma unroll
+                for (int q = 0; q < PER; ++q) hval[q] = (sfirst[q] == cur_step) ? hnfirst[q] : hfirst[q];
+                if (need > have) {
+#pragma unroll
+                    for (int q = 0; q < PER; ++q)
+                        if (q >= have && q < need) hval[q] = h[min(s0 + q * stride, capacity - 1)];
+                    if (stamp) {
+#pragma unroll
+                        for (int q = 0; q < PER; ++q) {
+                            if (q >= have && q < need) {
+                                const int sc = min(s0 + q * stride, capacity - 1);
+                                const float hn = h_new[sc];
+                                if (stamp[sc] == cur_step) hval[q] = hn;
+                            }
+                        }
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    if (q < need) {                  // uniform over the wave
+                        const int s = s0 + q * stride;
+                        const float v = (s < r1) ? hval[q] : 0.f;
+                        const bool nonzero = v != 0.f;
+                        const bool take = SKIP ? nonzero : s < r1;
+                        const unsigned long long m = __ballot(take);
+                        if (take) {
+                            const int pos = cnt + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+                            list[wv][pos - start] = s;
+                            hv[wv][pos - start] = v;
+                        }
+                        cnt += __popcll(m);
+                        nz += SKIP ? __popcll(m) : __popcll(__ballot(nonzero));
+                    }
+                }
+                // (the list is this wave's alone and a wave's LDS operations complete in order: no barrier instruction)
+                __builtin_amdgcn_wave_barrier();
+                if (col_ok) {
+                    // all row loads of a pass over kInFlight rows per thread are issued before the first use; a thread
+                    // takes the list positions i with i mod RG = its row group, counted over the whole chunk
+                    constexpr int kInFlight = 8;
+                    const int first = start + ((rg - start) & (RG - 1));
+                    for (int i0 = first; i0 < cnt; i0 += RG * kInFlight) {
+                        V v[kInFlight];
+#pragma unroll
+                        for (int u = 0; u < kInFlight; ++u) {
+                            const int i = i0 + u * RG;
+                            const int sr = list[wv][(i < cnt ? i : i0) - start];
+                            v[u] = (i < cnt) ? *reinterpret_cast<const V*>(base + (size_t)sr * row_elems) : V(0);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kInFlight; ++u) {
+                            const int i = i0 + u * RG;
+                            if (i < cnt) {
+                                const float hb = hv[wv][i - start];
+#pragma unroll
+                                for (int e = 0; e < VE; ++e) acc[e] = __builtin_fmaf(hb, (float)v[u][e], acc[e]);
+                            }
+                        }
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (slice == 0 && lane == 0 && nz) atomicAdd(&st->c_ffn_active, (unsigned long long)nz);     // statistics only
+            constexpr int held = wave_fold_held<VE, LANES>();
+            constexpr int dup = wave_fold_dup_mask<VE, LANES>();
+            const int first = wave_fold<VE, LANES>(acc, lane);
+            if ((lane & dup) == 0) {
+#pragma unroll
+                for (int i = 0; i < held; ++i) red[vw][l][first + i] = acc[i];
+            }
+        }
+        __syncthreads();
+        if (tid < LANES * VE) {                      // one column per thread, waves in order
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < VWMAX; ++w)
+                if (w < vwaves) sum += red[w][tid / VE][tid % VE];
+            const int oc = slice * (LANES * VE) + tid;
+            if (chunks > 1 && gridDim.y > 1) {
+                if (oc < d) ypart[(size_t)chunk * d + oc] = sum;
+            } else {
+                total += sum;                        // chunk order; 0 + first sum is exact
+            }
+        }
+        __syncthreads();                             // red is written again by the next chunk
+    }
+    if (slice == 0 && tid == 0 && first_row) {
+        atomicAdd(&st->c_ffn_calls, 1ull);
+        atomicAdd(&st->c_ffn_rows, (unsigned long long)n);
+    }
+    if (chunks == 1 || gridDim.y == 1) {
+        const int oc = slice * (LANES * VE) + tid;
+        if (tid < LANES * VE && oc < d) y[oc] = (T)total;
+    }
+}
+
+}  // namespace lif
