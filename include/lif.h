@@ -273,8 +273,9 @@ size_t lif_static_scratch_bytes(void);
  * four calls in sequence.  The cache update and the activation stage of the FFN share one
  * launch: the host-link gather keeps few compute units busy, the others compute the
  * activations of the resident rows meanwhile (Section 3.3 items 2 and 3 overlapped).  For
- * batch == 1 the loaders compute the activations of the rows they write, with the same
- * summation order; for fp16 batches a short second pass covers those rows.  y, masks, ids,
+ * batch == 1 the predictor and the window update are part of that launch too, and the loaders
+ * compute the activations of the rows they write, with the same summation order; for fp16
+ * batches a short second pass covers those rows.  y, masks, ids,
  * counts and the cache are bit-identical to the four-call sequence.
  */
 int lif_step(lif_layer* layer, const void* x_dev, int32_t batch, void* y_dev, uint8_t* masks_dev,
@@ -301,10 +302,17 @@ int lif_set_expected_rows(lif_layer* layer, int32_t rows);
 
 /*
  * Performance knob of lif_step's bundle gather (Section 3.3 item 2): the number of loader wave pairs (one bundle in
- * flight per pair), 1..64; 0 restores the default, which is chosen from the bundle size (256 KiB of reads
+ * flight per pair), 1..64; 0 restores the default, which is chosen from the bundle size (320 KiB of reads
  * outstanding, within 5..32 pairs).  Results never depend on it.
  */
 int lif_set_loader_pairs(lif_layer* layer, int32_t pairs);
+
+/*
+ * Performance knob of the single-token lif_step: workgroups of one launch hand values over to each other, and a
+ * workgroup that has polled for a value this often without success computes it itself (0: it never waits).  Results
+ * never depend on it.
+ */
+int lif_set_handoff_polls(lif_layer* layer, int32_t polls);
 
 /* Synchronises `stream`, then copies the device-side state / counters to the host. */
 int lif_get_state(lif_layer* layer, lif_state* out, void* stream);

@@ -62,6 +62,7 @@ EXPORTS = {
                         [C.c_void_p]),
     "lif_set_expected_rows": (C.c_int, [C.c_void_p, C.c_int32]),
     "lif_set_loader_pairs": (C.c_int, [C.c_void_p, C.c_int32]),
+    "lif_set_handoff_polls": (C.c_int, [C.c_void_p, C.c_int32]),
     "lif_get_state": (C.c_int, [C.c_void_p, C.POINTER(LifState), C.c_void_p]),
     "lif_get_counters": (C.c_int, [C.c_void_p, C.POINTER(LifCounters), C.c_void_p]),
     "lif_profile_read": (C.c_int, [C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]),
@@ -249,6 +250,9 @@ class Layer:
 
     def set_loader_pairs(self, pairs: int):
         _check(self.lib.lif_set_loader_pairs(self.handle, int(pairs)))
+
+    def set_handoff_polls(self, polls: int):
+        _check(self.lib.lif_set_handoff_polls(self.handle, int(polls)))
 
     # ---- introspection ---------------------------------------------------------------
     def state(self) -> dict:

@@ -17,6 +17,7 @@
 #include "lif_ffn_down_mfma.h"
 #include "lif_predict.h"
 #include "lif_step.h"
+#include "lif_step1.h"
 #include "lif_window.h"
 
 using namespace lif;
@@ -41,10 +42,19 @@ int fail(int code, const char* fmt, const char* detail = "") {
         if (e_ != hipSuccess) return fail(LIF_HIP_ERROR, #call ": %s", hipGetErrorString(e_)); \
     } while (0)
 
+// Bytes of host reads that lif_step keeps outstanding: pairs of loader workgroups (one bundle in flight per pair) =
+// kStepInflightBytes / bundle bytes, within 5..32.  The link needs about 128 KiB (56 GB/s at 1.5 to 2.4 us); the rest covers
+// the time in which a loader writes a bundle out and asks for the next.  One token with 144 / 192 / 256 / 320 / 384 KiB:
+// OPT shape 60.4 / 59.4 / 58.2 / 58.4 / 60.0 us, Falcon shape 188 / 159 / 143 / 141 / 140 us, gated Llama-2 shape 147 / 138 /
+// 137 / 138 / 143 us.
+constexpr size_t kStepInflightBytes = 320 * 1024;
+constexpr int kDefaultPolls = 4096;      // a failed poll takes about 0.7 us: 3 ms before a workgroup helps itself
+
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Layout {
-    size_t state, ring, tpart, move_dst, hole_list, h, ypart, h_new, stamp, gact, total;
+    size_t state, words, ring, tpart, move_dst, hole_list, h, ypart, h_new, stamp, ptr_new, bias_new, gact, total;
+    int reset_words;                   // 64-bit words from `words` on that a reset clears
 };
 
 int elem_bytes(const lif_config& c) { return c.dtype == LIF_F32 ? 4 : 2; }
@@ -79,9 +89,12 @@ Layout make_layout(const lif_config& c) {
     size_t off = 0;
     L.state = off;
     off = align_up(off + sizeof(DevState), 256);
+    L.words = off;                     // words handed over inside a fused step: t = x A, then the mask words
+    off = off + sizeof(uint64_t) * kWordReps * ((size_t)words_pitch(2 * std::max(c.rank, 0)) + words_pitch(2 * ring_words(c)));
     L.ring = off;                      // window_k step masks, each padded to whole 64-bit words
-    off = off + (size_t)c.window_k * ring_words(c) * 8;     // ... directly followed by the bitmap of the cached set
-    off = align_up(off + (size_t)ring_words(c) * 8, 256);
+    off = off + (size_t)(c.window_k + 2) * ring_words(c) * 8;     // ... directly followed by the two bitmaps of the cached set
+    L.reset_words = (int)((off - L.words) / 8);
+    off = align_up(off, 256);
     L.tpart = off;
     off = align_up(off + sizeof(double) * c.max_batch * std::max(c.rank, 0), 256);
     L.move_dst = off;
@@ -96,6 +109,10 @@ Layout make_layout(const lif_config& c) {
     off = align_up(off + sizeof(float) * c.capacity_rows, 256);
     L.stamp = off;                     // step number at which h_new[slot] was written
     off = align_up(off + sizeof(int32_t) * c.capacity_rows, 256);
+    L.ptr_new = off;                   // slot owners and biases written by the fused step
+    off = align_up(off + sizeof(int32_t) * c.capacity_rows, 256);
+    L.bias_new = off;
+    off = align_up(off + sizeof(float) * c.capacity_rows, 256);
     L.gact = off;                      // gate predictor: relu(gate_i . x_t + b_i) per token and original neuron
     off = align_up(off + (c.predictor == LIF_PRED_GATE ? sizeof(float) * c.max_batch * c.d_ffn : 0), 256);
     L.total = off;
@@ -119,6 +136,10 @@ struct lif_layer {
     float* ypart;
     float* h_new;
     int32_t* stamp;
+    int32_t* ptr_new;
+    float* bias_new;
+    unsigned long long* words;
+    int polls;                  // failed polls of a hand-over word before a workgroup computes the value itself
     float* gact;                // null unless the gate projection is the predictor
     size_t row_elems, row_bytes;
     bool window_pending;
@@ -244,7 +265,7 @@ int geometry_rows(const lif_layer* L) {
 
 // one token
 template <typename T, bool SKIP>
-void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t s, bool use_new) {
+void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t s, bool fused_step) {
     const lif_config& c = L->cfg;
     constexpr int cols = kDown1Lanes * Vec<T>::N;
     const int slices = ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;     // whole runs of slices per XCD
@@ -255,10 +276,12 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     // groups of slots whose activations are asked for ahead of the row count: those the hint covers; without a hint 2048
     // slots if that many rows make one pass (else the order of the slots is not known yet)
     const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;
+    FusedRows f = {};
+    if (fused_step) f = FusedRows{L->h_new, L->stamp, L->ptr_new, L->bias_new, L->buf.pointers, L->buf.bias};
 #define LIF_D1(W)                                                                                            \
-    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W>), dim3(slices, wg_rows), dim3(W * 64), 0, s, (const T*)L->buf.matrix, h,  \
-                       use_new ? L->h_new : nullptr, use_new ? L->stamp : nullptr, (T*)y, ypart, c.d_model,         \
-                       c.capacity_rows, L->row_elems, down_off, spec, L->st)
+    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W>), dim3(slices + (fused_step ? 1 : 0), wg_rows), dim3(W * 64), 0, s,     \
+                       (const T*)L->buf.matrix, h, f, (T*)y, ypart, c.d_model, c.capacity_rows, L->row_elems,        \
+                       down_off, spec, slices, L->buf.pointers, L->gact, c.d_ffn, L->st)
     if (waves == 8) LIF_D1(8);
     else LIF_D1(16);
 #undef LIF_D1
@@ -303,11 +326,11 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
 }
 
 template <typename T>
-void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, bool use_new = false) {
+void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, bool fused_step = false) {
     const bool skip = L->cfg.ffn_mode == LIF_FFN_SKIP_DEAD;
     if (batch == 1) {
-        if (skip) launch_ffn_down1<T, true>(L, y, h, ypart, s, use_new);
-        else launch_ffn_down1<T, false>(L, y, h, ypart, s, use_new);
+        if (skip) launch_ffn_down1<T, true>(L, y, h, ypart, s, fused_step);
+        else launch_ffn_down1<T, false>(L, y, h, ypart, s, fused_step);
         return;
     }
     if constexpr (std::is_same<T, _Float16>::value) {
@@ -322,31 +345,37 @@ void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, h
     }
 }
 
-template <typename T, bool GLU>
-void launch_load_up(lif_layer* L, const void* x, const int32_t* added, hipStream_t s) {
+// one token: everything up to the down projection
+void launch_step1(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_mask, int32_t* added, int32_t* n_added,
+                  int32_t* removed, int32_t* n_removed, hipStream_t s) {
     const lif_config& c = L->cfg;
-    const int nvec = c.d_model / Vec<T>::N;
-    const int ni = (nvec + 63) / 64;
-    const int spec = L->expected_rows > 0 ? 1 : 0;
-    const int up_blocks = spec ? std::min(kUpMaxWgs, std::max(1, std::min(L->expected_rows, c.capacity_rows) / 4))
-                               : std::min((c.capacity_rows + 3) / 4, 512);
-    // loader waves come in pairs (activation vectors | down vector of one bundle), one wave per workgroup
-    const int load_wgs = 2 * (L->loader_pairs > 0 ? L->loader_pairs
-                                                   : (int)std::min<size_t>(32, std::max<size_t>(5, kStepInflightBytes / L->row_bytes)));
-#define LIF_LU(NI)                                                                                            \
-    hipLaunchKernelGGL((k_load_up<T, NI, GLU>), dim3(load_wgs + up_blocks), dim3(256), 0, s,                      \
-                       (T*)L->buf.matrix, L->buf.pointers, L->buf.bias, L->host, L->buf.b, added, \
-                       L->move_dst, L->row_elems, c.d_ffn, c.d_model, c.capacity_rows, (const T*)x, L->h,         \
-                       L->h_new, L->stamp, spec, load_wgs, L->gact, L->st)
-    if (ni <= 1) LIF_LU(1);
-    else if (ni <= 2) LIF_LU(2);
-    else if (ni <= 4) LIF_LU(4);
-    else if (ni <= 6) LIF_LU(6);
-    else if (ni <= 8) LIF_LU(8);
-    else if (ni <= 9) LIF_LU(9);
-    else if (ni <= 12) LIF_LU(12);
-    else LIF_LU(16);
-#undef LIF_LU
+    const bool gate = c.predictor == LIF_PRED_GATE, f32 = c.dtype == LIF_F32;
+    const int words = ring_words(c);
+    Step1Args a = {};
+    a.A = L->buf.A; a.B = L->buf.B; a.c = L->buf.c; a.rank = c.rank; a.theta = c.threshold;
+    a.t_pitch = words_pitch(2 * std::max(c.rank, 0)); a.m_pitch = words_pitch(2 * words);
+    a.t_words = L->words; a.m_words = L->words + (size_t)kWordReps * a.t_pitch;
+    a.masks = masks; a.step_mask = step_mask; a.gact = L->gact;
+    a.ring = L->ring; a.cur_set = L->ring + (size_t)c.window_k * words; a.ring_words = words;
+    a.k = c.window_k; a.shrink = c.shrink_window;
+    a.added = added; a.n_added = n_added; a.removed = removed; a.n_removed = n_removed; a.hole_list = L->hole_list;
+    a.matrix = L->buf.matrix; a.pointers = L->buf.pointers; a.bias = L->buf.bias; a.host = L->host; a.b = L->buf.b;
+    a.row_elems = L->row_elems; a.F = c.d_ffn; a.d = c.d_model; a.capacity = c.capacity_rows;
+    a.x = x; a.h = L->h; a.h_new = L->h_new; a.stamp = L->stamp; a.ptr_new = L->ptr_new; a.bias_new = L->bias_new;
+    a.polls = L->polls; a.st = L->st;
+    // predictor workgroups: one per 64 neurons (32 with the gate predictor), and enough for the columns of A
+    a.n_pred = gate ? 2 * words : std::max(words, (c.rank + 3) / 4);
+    // loader waves: two per bundle in flight
+    const int pairs = L->loader_pairs > 0 ? L->loader_pairs
+                                          : (int)std::min<size_t>(32, std::max<size_t>(5, kStepInflightBytes / L->row_bytes));
+    a.n_load = 2 * pairs;
+    // activation role: one wave per row; with a row-count hint the grid is sized to it
+    a.spec = L->expected_rows > 0 ? 1 : 0;
+    const int up = a.spec ? std::min(kUpMaxWgs, std::max(1, std::min(L->expected_rows, c.capacity_rows) / 4))
+                          : std::min((c.capacity_rows + 3) / 4, 512);
+    const int grid = a.n_pred + 1 + a.n_load + up;
+    if (f32) (gate ? launch_step1_f32_gate : c.glu ? launch_step1_f32_glu : launch_step1_f32_plain)(a, grid, s);
+    else (gate ? launch_step1_f16_gate : c.glu ? launch_step1_f16_glu : launch_step1_f16_plain)(a, grid, s);
 }
 
 constexpr int kFuseBatchedMinRows = 2048;
@@ -590,6 +619,10 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
     L->ypart = (float*)(ws + lay.ypart);
     L->h_new = (float*)(ws + lay.h_new);
     L->stamp = (int32_t*)(ws + lay.stamp);
+    L->ptr_new = (int32_t*)(ws + lay.ptr_new);
+    L->bias_new = (float*)(ws + lay.bias_new);
+    L->words = (unsigned long long*)(ws + lay.words);
+    L->polls = kDefaultPolls;
     L->gact = cfg->predictor == LIF_PRED_GATE ? (float*)(ws + lay.gact) : nullptr;
     L->row_elems = (size_t)(cfg->glu ? 3 : 2) * cfg->d_model;
     L->row_bytes = L->row_elems * elem_bytes(*cfg);
@@ -634,9 +667,8 @@ int lif_destroy(lif_layer* layer) {
 int lif_reset(lif_layer* L, void* stream) {
     if (!L) return fail(LIF_INVALID_ARG, "layer is null");
     hipStream_t s = (hipStream_t)stream;
-    const int total_words = (L->cfg.window_k + 1) * ring_words(L->cfg);      // ring + cached-set bitmap
-    const int grid = std::min((total_words + 255) / 256, 256);
-    hipLaunchKernelGGL(k_reset, dim3(grid), dim3(256), 0, s, L->ring, total_words, L->stamp, L->cfg.capacity_rows,
+    const int grid = std::min((L->lay.reset_words + 255) / 256, 256);
+    hipLaunchKernelGGL(k_reset, dim3(grid), dim3(256), 0, s, L->words, L->lay.reset_words, L->stamp, L->cfg.capacity_rows,
                        L->st);
     L->window_pending = false;
     return check_launch();
@@ -804,52 +836,43 @@ static int step_impl(lif_layer* L, const void* x_dev, int32_t batch, int32_t kee
     if (keep >= 0 && (rc = check_window_tokens(L, batch, keep))) return rc;
     rc = check_update_window(L, keep < 0 ? step_mask_dev : masks_dev, added_dev, n_added_dev, removed_dev, n_removed_dev);
     if (rc) return rc;
+    hipStream_t s = (hipStream_t)stream;
+    const lif_config& c = L->cfg;
+    if (batch == 1 && keep != 0) {
+        {
+            Timed t(L, LIF_K_LOAD, s);
+            launch_step1(L, x_dev, masks_dev, step_mask_dev, added_dev, n_added_dev, removed_dev, n_removed_dev, s);
+        }
+        Timed t(L, LIF_K_FFN_DOWN, s);
+        if (c.dtype == LIF_F32) launch_ffn_down<float>(L, 1, y_dev, L->h, L->ypart, s, true);
+        else launch_ffn_down<_Float16>(L, 1, y_dev, L->h, L->ypart, s, true);
+        return check_launch();
+    }
     rc = lif_predict(L, x_dev, batch, masks_dev, step_mask_dev, stream);
     if (rc) return rc;
     rc = keep < 0 ? lif_update_window(L, step_mask_dev, added_dev, n_added_dev, removed_dev, n_removed_dev, stream)
                   : lif_update_window_tokens(L, masks_dev, batch, keep, added_dev, n_added_dev, removed_dev,
                                              n_removed_dev, stream);
     if (rc) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    const lif_config& c = L->cfg;
-    // batch > 1: sharing a launch between the load and the activation stage pays once the activation stage over
+    // sharing a launch between the load and the activation stage pays once the activation stage over
     // all rows takes longer than the second pass over the rows the load wrote (about 2000 rows in use)
     const int rows_hint = L->expected_rows > 0 ? L->expected_rows : c.capacity_rows;
-    if (batch > 1 && (!mfma_path(c, batch) || rows_hint < kFuseBatchedMinRows)) {
+    if (!mfma_path(c, batch) || rows_hint < kFuseBatchedMinRows) {
         rc = lif_load_bundles(L, added_dev, n_added_dev, removed_dev, n_removed_dev, stream);
         if (rc) return rc;
         return lif_sparse_ffn(L, x_dev, batch, y_dev, stream);
     }
-    if (batch > 1) {
-        {
-            Timed t(L, LIF_K_LOAD, s);
-            launch_load_up_mfma(L, x_dev, batch, added_dev, s);
-        }
-        L->window_pending = false;
-        {
-            Timed t(L, LIF_K_FFN_UP, s);
-            launch_ffn_up_mfma<kRowsChanged>(L, x_dev, batch, L->h, s);
-        }
-        Timed t(L, LIF_K_FFN_DOWN, s);
-        launch_ffn_down<_Float16>(L, batch, y_dev, L->h, L->ypart, s);
-        return check_launch();
-    }
     {
         Timed t(L, LIF_K_LOAD, s);
-        if (c.dtype == LIF_F32) {
-            if (c.glu) launch_load_up<float, true>(L, x_dev, added_dev, s);
-            else launch_load_up<float, false>(L, x_dev, added_dev, s);
-        } else {
-            if (c.glu) launch_load_up<_Float16, true>(L, x_dev, added_dev, s);
-            else launch_load_up<_Float16, false>(L, x_dev, added_dev, s);
-        }
+        launch_load_up_mfma(L, x_dev, batch, added_dev, s);
     }
     L->window_pending = false;
     {
-        Timed t(L, LIF_K_FFN_DOWN, s);
-        if (c.dtype == LIF_F32) launch_ffn_down<float>(L, 1, y_dev, L->h, L->ypart, s, true);
-        else launch_ffn_down<_Float16>(L, 1, y_dev, L->h, L->ypart, s, true);
+        Timed t(L, LIF_K_FFN_UP, s);
+        launch_ffn_up_mfma<kRowsChanged>(L, x_dev, batch, L->h, s);
     }
+    Timed t(L, LIF_K_FFN_DOWN, s);
+    launch_ffn_down<_Float16>(L, batch, y_dev, L->h, L->ypart, s);
     return check_launch();
 }
 
@@ -874,6 +897,12 @@ int lif_set_loader_pairs(lif_layer* L, int32_t pairs) {
     return LIF_OK;
 }
 
+int lif_set_handoff_polls(lif_layer* L, int32_t polls) {
+    if (!L || polls < 0) return fail(LIF_INVALID_ARG, "polls must be at least 0");
+    L->polls = polls;
+    return LIF_OK;
+}
+
 int lif_set_expected_rows(lif_layer* L, int32_t rows) {
     if (!L || rows < 0) return fail(LIF_INVALID_ARG, "bad row hint");
     L->expected_rows = rows;
@@ -892,13 +921,13 @@ int lif_get_state(lif_layer* L, lif_state* out, void* stream) {
     DevState h;
     int rc = read_state(L, &h, stream);
     if (rc) return rc;
-    out->num_used = h.num_used;
-    out->step = h.step;
-    out->error = h.error;
-    out->last_added = h.n_added;
-    out->last_removed = h.n_removed;
-    out->last_moved = h.n_moved;
-    out->window_len = h.window_len;
+    out->num_used = h.cur.num_used;
+    out->step = h.cur.step;
+    out->error = h.cur.error;
+    out->last_added = h.cur.n_added;
+    out->last_removed = h.cur.n_removed;
+    out->last_moved = h.cur.n_moved;
+    out->window_len = h.cur.window_len;
     return LIF_OK;
 }
 

@@ -8,9 +8,8 @@ namespace lif {
 
 constexpr int kWave = 64;
 
-// Device-resident state of one layer.  Lives at the start of the caller's workspace so
-// that the hot calls chain on a stream without the host ever knowing a count.
-struct DevState {
+// Counts of one layer.
+struct StepCounts {
     int32_t num_used;     // rows of the cache in use (Section 3.3 "num_used")
     int32_t n_base;       // rows kept after the pending deletion (n' = num_used - c)
     int32_t step;         // completed window updates
@@ -20,7 +19,16 @@ struct DevState {
     int32_t n_moved;      // rows moved by the last deletion
     int32_t window_len;   // step masks currently in the window (<= k; smaller after a dynamic shrink)
     int32_t ring_pos;     // ring entry the next mask goes to
-    int32_t pad;
+    int32_t set_par;      // which of the two bitmaps of the cached set is current
+};
+
+// Device-resident state of one layer.  Lives at the start of the caller's workspace so
+// that the hot calls chain on a stream without the host ever knowing a count.
+// `next`: a fused step (k_step1) decides the new counts while all its workgroups still read the old ones, so it leaves
+// them here and the down projection of the same step, whose workgroups read only `next`, copies them into `cur`.
+struct DevState {
+    StepCounts cur;
+    StepCounts next;
     // counters: only ever updated with atomic adds whose result is not used (a load-add-store at the end of a kernel
     // would keep its last wave waiting for a memory round trip)
     unsigned long long c_steps, c_added, c_removed, c_rows_moved, c_h2d_bytes;

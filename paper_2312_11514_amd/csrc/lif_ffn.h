@@ -31,7 +31,8 @@ namespace lif {
 // `gact` (may be null, plain bundles only): per-neuron gate activations relu(gate_i . x + b_i) written by the
 // gate predictor (Appendix, Llama 2, "Alternative approaches": the resident gate projection is the predictor);
 // the activation of slot s for token t is then gact[t][pointers[s]] * (up_s . x_t), gact [batch x gact_n];
-// gact_n = d_ffn bounds the lookup.
+// gact_n = d_ffn bounds the lookup.  A single token (XREG) leaves up_s . x and k_ffn_down1 multiplies: a fused step
+// computes both in the same launch.
 template <typename T, int NI, bool GLU, bool XREG>
 __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const float* __restrict__ bias,
                                             const T* __restrict__ x, float* __restrict__ h, int d, int batch,
@@ -73,9 +74,9 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
                 u[it] = in ? row[idx] : V(0);
             }
         }
-        if (ok) bs = gact ? gact[min(max(pointers[gw], 0), gact_n - 1)] : bias[gw];     // token 0 (the only one if XREG)
+        if (ok) bs = !gact ? bias[gw] : XREG ? 0.f : gact[min(max(pointers[gw], 0), gact_n - 1)];      // of token 0
     }
-    const int err = st->error;
+    const int err = st->cur.error;
     const int n = *n_ptr;
     if (err || block * 4 >= n) return;               // whole workgroup has no row (uniform)
 
@@ -97,7 +98,7 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
                 u[it] = in ? row[idx] : V(0);
             }
         }
-        bs = gact ? gact[min(max(pointers[gw], 0), gact_n - 1)] : bias[gw];
+        bs = !gact ? bias[gw] : XREG ? 0.f : gact[min(max(pointers[gw], 0), gact_n - 1)];
     }
     for (int s = gw; s < n; s += nw) {
         // the next row of this wave is requested before the current one is reduced (when the grid is
@@ -118,7 +119,7 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
                     un[it] = in ? row[idx] : V(0);
                 }
             }
-            bsn = gact ? gact[min(max(pointers[sn], 0), gact_n - 1)] : bias[sn];
+            bsn = !gact ? bias[sn] : XREG ? 0.f : gact[min(max(pointers[sn], 0), gact_n - 1)];
         }
         for (int b = 0; b < (XREG ? 1 : batch); ++b) {
             float du = 0.f, dg = 0.f;
@@ -141,9 +142,8 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
                 act = fmaxf(dg + bs, 0.f) * du;
             } else if (gact) {
                 // resident gate: relu(gate . x_b + bias) from the predictor (bs holds token 0's)
-                const float gb = (XREG || b == 0) ? bs
-                                                  : gact[(size_t)b * gact_n + min(max(pointers[s], 0), gact_n - 1)];
-                act = gb * du;
+                const float gb = b == 0 ? bs : gact[(size_t)b * gact_n + min(max(pointers[s], 0), gact_n - 1)];
+                act = XREG ? du : gb * du;
             } else {
                 act = fmaxf(du + bs, 0.f);
             }
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void k_ffn_up(const T* __restrict__ matrix, co
                                                 const int32_t* __restrict__ pointers, const float* __restrict__ gact,
                                                 int gact_n, const DevState* __restrict__ st) {
     ffn_up_role<T, NI, GLU, XREG>(matrix, bias, x, h, d, batch, capacity, row_elems, spec, blockIdx.x, gridDim.x,
-                                  &st->num_used, pointers, gact, gact_n, st);
+                                  &st->cur.num_used, pointers, gact, gact_n, st);
 }
 
 constexpr int kUpMaxWgs = 1024;   // workgroups of the activation stage: beyond this, waves loop over rows (x stays in registers)
@@ -240,8 +240,8 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
             }
         }
     }
-    const int err = st->error;
-    const int n = err ? 0 : st->num_used;
+    const int err = st->cur.error;
+    const int n = err ? 0 : st->cur.num_used;
     if (err) return;
     const int chunks = down_chunks(n);
     if ((int)blockIdx.y >= chunks) return;           // uniform
@@ -373,8 +373,8 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
 template <typename T, int (*CHUNKS)(int)>
 __global__ __launch_bounds__(256) void k_ffn_down_finish(const float* __restrict__ ypart, T* __restrict__ y, int d,
                                                          int batch, const DevState* __restrict__ st) {
-    if (st->error) return;
-    const int chunks = CHUNKS(st->num_used);
+    if (st->cur.error) return;
+    const int chunks = CHUNKS(st->cur.num_used);
     if (chunks == 1) return;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= batch * d) return;

@@ -40,19 +40,61 @@ __host__ __device__ __forceinline__ int down1_chunks(int n) {
 // the result does not depend on the launch geometry.
 __host__ __device__ __forceinline__ int down1_waves(int n) { return n <= kDown1FewRows ? 8 : 16; }
 
-// grid = (column slices of 64 bytes, rounded up to a multiple of 8; row-chunk workgroups), block = WAVES * 64.
-// h_new / stamp (may be null): activations of the rows that the fused load kernel wrote during the step whose number
-// equals stamp[s]; they override h for those rows.
+// After a fused step (k_step1): the activations, slot owners and biases of the rows that it wrote, valid for the slots
+// whose stamp is the number of that step.  All null otherwise.
+struct FusedRows {
+    const float* h_new;
+    const int32_t* stamp;
+    const int32_t* ptr_new;
+    const float* bias_new;
+    int32_t* pointers;               // where they are committed to
+    float* bias;
+};
+
+// The end of a fused step, by one workgroup: counts, slot owners and biases.  The other workgroups of the launch read
+// st->next and not what is written here.
+template <int THREADS>
+__device__ __forceinline__ void commit_step(const FusedRows& f, int capacity, DevState* st) {
+    constexpr int PER = 4;
+    const StepCounts nx = st->next;
+    if (threadIdx.x == 0) st->cur = nx;
+    if (nx.error) return;
+    for (int s0 = threadIdx.x; s0 < nx.num_used; s0 += PER * THREADS) {
+        int stamp[PER], p[PER];
+        float b[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int s = min(s0 + q * THREADS, capacity - 1);
+            stamp[q] = f.stamp[s];
+            p[q] = f.ptr_new[s];
+            b[q] = f.bias_new[s];
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int s = s0 + q * THREADS;
+            if (s < nx.num_used && stamp[q] == nx.step) {
+                f.pointers[s] = p[q];
+                f.bias[s] = b[q];
+            }
+        }
+    }
+}
+
+// grid = (column slices of 64 bytes, rounded up to a multiple of 8, + 1 after a fused step: the workgroup that commits
+// it; row-chunk workgroups), block = WAVES * 64.
+// gact (may be null): the activations in h and h_new are up . x alone and are multiplied with the gate activation of the
+// slot's neuron here (gate predictor; gact_n = number of neurons).
 // spec: groups of WAVES * 64 slots whose activations are requested before the row count is known (the arrays span the
 // capacity, so the addresses are valid; values past the count are masked).
 // Workgroup row y takes the chunks y, y + gridDim.y, ...; with several chunks and several workgroup rows the sums go to
 // ypart[chunk][d] (fp32) and k_ffn_down_finish adds them, else this kernel adds them in the same order.  No atomics.
 template <typename T, bool SKIP, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ matrix, const float* __restrict__ h,
-                                                          const float* __restrict__ h_new,
-                                                          const int32_t* __restrict__ stamp, T* __restrict__ y,
+                                                          const FusedRows fused, T* __restrict__ y,
                                                           float* __restrict__ ypart, int d, int capacity,
-                                                          size_t row_elems, int down_off, int spec,
+                                                          size_t row_elems, int down_off, int spec, int slices,
+                                                          const int32_t* __restrict__ pointers,
+                                                          const float* __restrict__ gact, int gact_n,
                                                           DevState* __restrict__ st) {
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N, LANES = kDown1Lanes, PER = kDown1Per, THREADS = WAVES * 64;
@@ -65,18 +107,25 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l = lane & (LANES - 1), rg = lane / LANES;
     // XCD-aware slice order: workgroups are dealt round-robin to the 8 XCDs, each with its own L2; giving every XCD a
     // contiguous run of slices makes the two halves of a 128-byte line meet in one L2 instead of being fetched twice
-    const int per_xcd = gridDim.x / kXcds;
+    if ((int)blockIdx.x == slices) {                 // (only after a fused step)
+        if (blockIdx.y == 0) commit_step<THREADS>(fused, capacity, st);
+        return;
+    }
+    const float* __restrict__ h_new = fused.h_new;
+    const int32_t* __restrict__ stamp = fused.stamp;
+    const int per_xcd = slices / kXcds;
     const int slice = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     const int col = slice * (LANES * VE) + l * VE;
     const bool col_ok = col < d;
     const T* base = matrix + down_off + (col_ok ? col : 0);
 
     float hfirst[PER], hnfirst[PER];
-    int sfirst[PER];
+    int sfirst[PER], ofirst[PER], onfirst[PER];      // o..: slot owners, only with gact
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         hfirst[q] = hnfirst[q] = 0.f;
         sfirst[q] = -1;
+        ofirst[q] = onfirst[q] = 0;
     }
     const bool first_row = blockIdx.y == 0;
     if (first_row) {                                 // (uniform branches around loads from clamped slots)
@@ -91,8 +140,17 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
                     hnfirst[q] = h_new[min(q * THREADS + tid, capacity - 1)];
                 }
         }
+        if (gact) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+                if (q < spec) {
+                    ofirst[q] = pointers[min(q * THREADS + tid, capacity - 1)];
+                    if (stamp) onfirst[q] = fused.ptr_new[min(q * THREADS + tid, capacity - 1)];
+                }
+        }
     }
-    const int err = st->error, n = st->num_used, cur_step = st->step;
+    const StepCounts* counts = stamp ? &st->next : &st->cur;
+    const int err = counts->error, n = counts->num_used, cur_step = counts->step;
     if (err) return;
     const int chunks = down1_chunks<SKIP>(n);
     if ((int)blockIdx.y >= chunks) return;           // uniform
@@ -115,22 +173,42 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
                 const int need = min(PER, (r1 - s_base - vw * 64 + stride - 1) / stride);       // groups with rows in them
                 const int have = (natural && first_row && s_base == 0) ? spec : 0;              // ... requested at the start
                 float hval[PER];
+                int owner[PER];
 #pragma unroll
-                for (int q = 0; q < PER; ++q) hval[q] = (sfirst[q] == cur_step) ? hnfirst[q] : hfirst[q];
+                for (int q = 0; q < PER; ++q) {
+                    const bool fresh = stamp && sfirst[q] == cur_step;
+                    hval[q] = fresh ? hnfirst[q] : hfirst[q];
+                    owner[q] = fresh ? onfirst[q] : ofirst[q];
+                }
                 if (need > have) {
 #pragma unroll
                     for (int q = 0; q < PER; ++q)
-                        if (q >= have && q < need) hval[q] = h[min(s0 + q * stride, capacity - 1)];
+                        if (q >= have && q < need) {
+                            const int sc = min(s0 + q * stride, capacity - 1);
+                            hval[q] = h[sc];
+                            if (gact) owner[q] = pointers[sc];
+                        }
                     if (stamp) {
 #pragma unroll
                         for (int q = 0; q < PER; ++q) {
                             if (q >= have && q < need) {
                                 const int sc = min(s0 + q * stride, capacity - 1);
                                 const float hn = h_new[sc];
-                                if (stamp[sc] == cur_step) hval[q] = hn;
+                                const int on = gact ? fused.ptr_new[sc] : 0;
+                                if (stamp[sc] == cur_step) {
+                                    hval[q] = hn;
+                                    owner[q] = on;
+                                }
                             }
                         }
                     }
+                }
+                if (gact) {
+                    float g[PER];
+#pragma unroll
+                    for (int q = 0; q < PER; ++q) g[q] = (q < need) ? gact[min(max(owner[q], 0), gact_n - 1)] : 0.f;
+#pragma unroll
+                    for (int q = 0; q < PER; ++q) hval[q] = g[q] * hval[q];
                 }
 #pragma unroll
                 for (int q = 0; q < PER; ++q) {

@@ -83,8 +83,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
 #pragma unroll
         for (int b = 0; b < BT; ++b) hfirst[p][b] = (s < capacity && b < batch) ? h[(size_t)b * capacity + s] : 0.f;
     }
-    const int err = st->error;
-    const int n = err ? 0 : st->num_used;
+    const int err = st->cur.error;
+    const int n = err ? 0 : st->cur.num_used;
     if (err) return;
     const int chunks = down_mfma_chunks(n, chunk_rows);
     if ((int)blockIdx.y >= chunks) return;           // uniform
@@ -243,8 +243,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
 __global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* __restrict__ ypart, _Float16* __restrict__ y,
                                                               int d, int batch, int chunk_rows,
                                                               const DevState* __restrict__ st) {
-    if (st->error) return;
-    const int chunks = down_mfma_chunks(st->num_used, chunk_rows);
+    if (st->cur.error) return;
+    const int chunks = down_mfma_chunks(st->cur.num_used, chunk_rows);
     if (chunks == 1) return;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= batch * d) return;

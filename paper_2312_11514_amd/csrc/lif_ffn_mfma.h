@@ -77,9 +77,9 @@ __device__ __forceinline__ bool ffn_up_mfma_tile(const _Float16* __restrict__ ma
     // requested together with the state (the list spans the capacity, so the address is valid; masked below)
     int moved_to = -1;
     if (MODE == kRowsChanged && s0 + i < capacity) moved_to = move_dst[s0 + i];
-    const int err = st->error;
-    const int n_removed = st->n_removed, n_base = st->n_base;
-    const int n = (MODE == kRowsAll) ? st->num_used : (MODE == kRowsKept) ? n_base : n_removed + st->n_added;
+    const int err = st->cur.error;
+    const int n_removed = st->cur.n_removed, n_base = st->cur.n_base;
+    const int n = (MODE == kRowsAll) ? st->cur.num_used : (MODE == kRowsKept) ? n_base : n_removed + st->cur.n_added;
     if (err || s0 >= n) return false;                             // uniform
 
     int srow = s0 + i;                                            // slot of list entry s0 + i (-1: none)
@@ -239,8 +239,8 @@ __device__ __forceinline__ bool ffn_up_mfma_tile_staged(const _Float16* __restri
         }
     };
     if (spec) issue(w * PPW, 0);
-    const int err = st->error;
-    const int n = (MODE == kRowsAll) ? st->num_used : st->n_base;
+    const int err = st->cur.error;
+    const int n = (MODE == kRowsAll) ? st->cur.num_used : st->cur.n_base;
     if (err || s0 >= n) return false;                             // uniform
     if (!spec) issue(w * PPW, 0);
 

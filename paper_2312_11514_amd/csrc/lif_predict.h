@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void k_predict_xa(const T* __restrict__ x, con
         a[it] = (idx < nvec) ? row[idx] : V(0);
         xr[it] = (idx < nvec) ? xv[idx] : V(0);
     }
-    const int err = st->error;
+    const int err = st->cur.error;
     double acc = 0.0;
 #pragma unroll
     for (int it = 0; it < NI; ++it) acc = dot_f64(a[it], xr[it], acc);
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void k_predict_mask(const T* __restrict__ B, c
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) tr[u] = t[min(jg + u * kMaskJg, r - 1)];
     }
-    const int err = st->error;
+    const int err = st->cur.error;
 
     for (int b0 = 0; b0 < batch; b0 += BT) {
         if (BT == 1 && r <= kMaskRows * kMaskJg && b0 > 0) __syncthreads();   // red is still read from the pass before
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void k_predict_gate(const T* __restrict__ Wg, 
         for (int i = tid; i < batch * nvec; i += 256) xs[i] = xv[i];
         __syncthreads();
     }
-    if (st->error) return;
+    if (st->cur.error) return;
     const double th = (double)theta;
     const int mask_stride = F >> 3;
     for (int grp = gw; grp * 8 < F; grp += nw) {

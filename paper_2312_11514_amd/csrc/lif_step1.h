@@ -1,0 +1,997 @@
+// One decode step of a single token, up to the down projection, in one launch (lif_step, batch 1).
+//
+// A step is a chain of small dependent stages in front of one long one, the host-link gather of the new bundles
+// (Section 3.3 item 2).  As separate launches every short stage costs 4 to 6 us on gfx950: 1.6 us of launch, a memory
+// round trip for the state, another one for what the previous kernel wrote.  Here the workgroups of one launch take
+// different roles and hand over inside it:
+//   workgroups [0, n_pred)        predictor: the first ceil(rank / 4) of them compute t = x A (one column per wave) and
+//                                 publish it; each of the first ceil(F / 64) waits for t and decides the 64 mask bits of
+//                                 its neurons (their weights are requested before the wait).  Gate predictor: 32 neurons
+//                                 per workgroup, nothing to wait for.
+//   workgroup n_pred              bookkeeping: waits for the masks, writes the window state, id lists and counts
+//   the next n_load workgroups    loaders: wait for the masks, work out the added ids and the deletion plan (every
+//                                 workgroup for itself: cheaper than waiting for one that does), move rows, gather
+//                                 bundles from pinned host memory and compute the activations of the rows they write
+//                                 (h_new, stamped with the step)
+//   the rest                      activations of the rows that were already in use; waits for nothing
+// A value handed over is a 64-bit word: 32 bits of payload and the number of the step as a stamp, written by a relaxed
+// device-scope atomic store and polled with relaxed device-scope atomic loads, so no fence (a device-scope release
+// writes back the L2: 6 us) and no clearing is needed.  Stamps are unique between two resets, which clear the words.
+// A workgroup waits only for workgroups with smaller numbers, and never without bound: after `polls` failed polls it
+// computes what it is missing itself, with the same arithmetic (polls = 0: never waits at all).
+// What other workgroups may still read is not overwritten: the new counts are left in st->next and the slot owners and
+// biases of the rows a loader writes in ptr_new / bias_new; the down projection, which runs after all of them, commits
+// them.  A matrix row that the activation role reads while a loader overwrites it gives a value that is never used: the
+// loader's stamped activation takes precedence for that slot.
+// Every sum is formed in the order of the separate kernels, so the step is bit-identical to the four calls.
+//
+// What bounds it: the host link, at 56 GB/s (a copy of 256 MiB by the runtime reaches 57), behind a chain of about 8 us
+// (x A 3, masks 3, window and first ids 2) and in front of the down projection.  Measured on gfx950, one decode token,
+// before (five launches) -> now (this kernel and the down projection): fp32 d = 256, F = 1024: 22 -> 15 us; OPT-6.7B
+// shape 65 -> 58; Falcon-7B shape 151 -> 141; Llama-2 shape gated 149 -> 137, with the gate resident 113 -> 110.
+#pragma once
+
+#include "lif_ffn.h"
+#include "lif_predict.h"
+#include "lif_window_bits.h"
+
+namespace lif {
+
+constexpr int kWordReps = 8;         // copies of every word: hundreds of workgroups polling the same lines would queue up
+// words of one copy, padded so that the copies do not fall on the same memory channels
+__host__ __device__ __forceinline__ int words_pitch(int n) { return (n + 31) / 32 * 32 + 32; }
+constexpr int kListItems = 2048;     // work items listed at a time
+
+struct Step1Args {
+    // predictor
+    const void* A;                   // [rank x d], or the gate projection [F x d]
+    const void* B;
+    const float* c;
+    int rank;
+    float theta;
+    unsigned long long* t_words;     // [kWordReps][t_pitch] stamped halves of t (doubles)
+    unsigned long long* m_words;     // [kWordReps][m_pitch] stamped 32-bit halves of the mask words
+    int t_pitch, m_pitch;
+    uint8_t* masks;
+    uint8_t* step_mask;
+    float* gact;                     // gate predictor: relu(gate_i . x + b_i) per neuron
+    // window
+    unsigned long long* ring;
+    unsigned long long* cur_set;     // [2][ring_words]
+    int ring_words, k, shrink;
+    int32_t *added, *n_added, *removed, *n_removed;
+    int32_t* hole_list;
+    // cache
+    void* matrix;
+    const int32_t* pointers;
+    const float* bias;
+    HostStore host;
+    const float* b;
+    size_t row_elems;
+    int F, d, capacity;
+    const void* x;
+    float* h;
+    float* h_new;
+    int32_t* stamp;                  // step in which h_new, ptr_new and bias_new of a slot were written
+    int32_t* ptr_new;
+    float* bias_new;
+    int spec;                        // the activation role requests its first rows ahead of the row count
+    int n_pred, n_load;
+    int polls;
+    DevState* st;
+};
+
+__device__ __forceinline__ unsigned long long word_load(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void word_store(unsigned long long* p, unsigned stamp, unsigned payload) {
+    __hip_atomic_store(p, ((unsigned long long)stamp << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Reads N words p[i * step] (i < n) of this stamp: all are requested before the first is looked at, the missing ones
+// again until they arrive or `polls` more reads have failed.  Returns whether all have arrived.
+template <int N>
+__device__ __forceinline__ bool poll_words(const unsigned long long* p, int step, int n, unsigned stamp, int polls,
+                                           unsigned (&out)[N]) {
+    unsigned long long w[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = (i < n) ? word_load(p + (size_t)i * step) : 0ull;
+    bool all = true;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (i < n) {
+            for (int tries = 0; (unsigned)(w[i] >> 32) != stamp && tries < polls; ++tries) w[i] = word_load(p + (size_t)i * step);
+            all = all && (unsigned)(w[i] >> 32) == stamp;
+        }
+        out[i] = (unsigned)w[i];
+    }
+    return all;
+}
+
+// ---- predictor -------------------------------------------------------------------------------------------------
+
+struct PredictLds {
+    double t[2048];                  // t = x A
+    double red[4][kMaskCols][8];
+};
+
+// x . row j of A (the whole wave; every lane returns the sum), in the order of k_predict_xa
+template <typename T, int NI>
+__device__ __forceinline__ double column_dot(const typename Vec<T>::type (&a)[NI], const typename Vec<T>::type (&xr)[NI]) {
+    double acc = 0.0;
+#pragma unroll
+    for (int it = 0; it < NI; ++it) acc = dot_f64(a[it], xr[it], acc);
+    return wave_sum(acc);
+}
+template <typename T, int NI>
+__device__ __forceinline__ void load_vec(typename Vec<T>::type (&v)[NI], const T* p, int nvec, int lane) {
+    using V = typename Vec<T>::type;
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const int idx = it * 64 + lane;
+        v[it] = (idx < nvec) ? reinterpret_cast<const V*>(p)[idx] : V(0);
+    }
+}
+
+// The same sum straight from memory, for the rare case that a wait ran out: few registers instead of loads in flight
+template <typename T>
+__device__ __forceinline__ double column_dot_slow(const T* col, const T* x, int nvec, int lane) {
+    using V = typename Vec<T>::type;
+    double acc = 0.0;
+#pragma unroll 1
+    for (int idx = lane; idx < nvec; idx += 64)
+        acc = dot_f64(reinterpret_cast<const V*>(col)[idx], reinterpret_cast<const V*>(x)[idx], acc);
+    return wave_sum(acc);
+}
+// t computed by this workgroup alone (a wait that ran out)
+template <typename T>
+__device__ __forceinline__ void own_t(const Step1Args& a, PredictLds& L) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll 1
+    for (int j = threadIdx.x >> 6; j < a.rank; j += 4) {
+        const double v = column_dot_slow((const T*)a.A + (size_t)j * a.d, (const T*)a.x, a.d / Vec<T>::N, lane);
+        if (lane == 0) L.t[j] = v;
+    }
+    __syncthreads();
+}
+
+// The 64 mask bits of a tile of neurons: as k_predict_mask for one token.  The weights and offsets are requested by
+// the constructor, before t is there.
+template <typename T>
+struct MaskTile {
+    using V = typename Vec<T>::type;
+    static constexpr int VE = Vec<T>::N, LPB = 8 / VE;
+    V bv[kMaskRows][LPB];
+    double bd[kMaskRows][8];
+    float cv[8];
+    int n0;
+    __device__ __forceinline__ void request(const Step1Args& a, int tile) {
+        const int tid = threadIdx.x, cl = tid & (kMaskCols - 1), jg = tid >> 3;
+        n0 = (tile * kMaskCols + cl) * 8;
+        const T* B = (const T*)a.B;
+#pragma unroll
+        for (int u = 0; u < kMaskRows; ++u) {
+            const int j = jg + u * kMaskJg;
+#pragma unroll
+            for (int q = 0; q < LPB; ++q)
+                bv[u][q] = (n0 < a.F && j < a.rank) ? reinterpret_cast<const V*>(B + (size_t)j * a.F + n0)[q] : V(0);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) cv[e] = (a.c && tid < kMaskCols && n0 < a.F) ? a.c[n0 + e] : 0.f;
+    }
+    // widening takes longer than the multiply-adds (64 values per thread, quarter-rate conversions: 0.6 us), so it is done
+    // while t is still on its way
+    __device__ __forceinline__ void widen() {
+#pragma unroll
+        for (int u = 0; u < kMaskRows; ++u)
+#pragma unroll
+            for (int q = 0; q < LPB; ++q)
+#pragma unroll
+                for (int e = 0; e < VE; ++e) bd[u][q * VE + e] = (double)bv[u][q][e];
+    }
+    // mask byte of neurons n0 .. n0 + 7 in the threads tid < kMaskCols (0 past the last neuron); one barrier
+    template <bool WIDE>
+    __device__ __forceinline__ unsigned finish(const Step1Args& a, PredictLds& L) {
+        const int tid = threadIdx.x, wave = tid >> 6, cl = tid & (kMaskCols - 1), jg = tid >> 3;
+        const T* B = (const T*)a.B;
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = 0.0;
+#pragma unroll
+        for (int u = 0; u < kMaskRows; ++u) {
+            const double tj = L.t[min(jg + u * kMaskJg, a.rank - 1)];            // bd[u] is 0 past the end
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tj, WIDE ? bd[u][e] : (double)bv[u][e / VE][e % VE], v[e]);
+        }
+        if (n0 < a.F) {
+            for (int j = jg + kMaskRows * kMaskJg; j < a.rank; j += kMaskJg) {   // only when rank > 256
+                const double tj = L.t[j];
+                const V* bp = reinterpret_cast<const V*>(B + (size_t)j * a.F + n0);
+#pragma unroll
+                for (int q = 0; q < LPB; ++q) {
+                    const V bw = bp[q];
+#pragma unroll
+                    for (int e = 0; e < VE; ++e) v[q * VE + e] = __builtin_fma(tj, (double)bw[e], v[q * VE + e]);
+                }
+            }
+        }
+        // rank groups of a wave sit 8 lanes apart: halving folds, lanes 8 apart first (a DPP rotation)
+        int owner = 0;
+        auto halve = [&](auto half_c, int m) {
+            constexpr int half = decltype(half_c)::value;
+            const bool up = (tid & m) != 0;
+#pragma unroll
+            for (int i = 0; i < half; ++i) {
+                const double send = up ? v[i] : v[i + half], keep = up ? v[i + half] : v[i];
+                v[i] = keep + (m == 8 ? dpp_from<0x128, 0xf>(send) : __shfl_xor(send, m, kWave));
+            }
+            owner = owner * 2 + (up ? 1 : 0);
+        };
+        halve(std::integral_constant<int, 4>{}, 8);
+        halve(std::integral_constant<int, 2>{}, 16);
+        halve(std::integral_constant<int, 1>{}, 32);
+        L.red[wave][cl][owner] = v[0];
+        __syncthreads();
+        unsigned byte = 0;
+        if (tid < kMaskCols && n0 < a.F) {
+            const double th = (double)a.theta;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                double z = ((L.red[0][cl][e] + L.red[1][cl][e]) + L.red[2][cl][e]) + L.red[3][cl][e];
+                z += (double)cv[e];
+                if (z > th) byte |= 1u << e;
+            }
+        }
+        return byte;
+    }
+};
+
+template <typename T, int NI>
+__device__ __forceinline__ void lowrank_role(const Step1Args& a, int block, PredictLds& L) {
+    using V = typename Vec<T>::type;
+    const int tid = threadIdx.x, lane = tid & 63, nvec = a.d / Vec<T>::N;
+    const int j = block * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool producer = j < a.rank;                // uniform over the wave
+    const bool has_tile = block * kMaskCols * 8 < a.F;
+    V col[NI], xr[NI];
+    if (producer) {
+        load_vec<T, NI>(xr, (const T*)a.x, nvec, lane);
+        load_vec<T, NI>(col, (const T*)a.A + (size_t)j * a.d, nvec, lane);
+    }
+    MaskTile<T> tile;
+    if (has_tile) tile.request(a, block);
+    const int err = a.st->cur.error;
+    const unsigned now = (unsigned)a.st->cur.step + 1u;
+    if (err) return;
+    if (producer) {
+        const double v = column_dot<T, NI>(col, xr);
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        if (lane < 2 * kWordReps)
+            word_store(a.t_words + (size_t)(lane >> 1) * a.t_pitch + 2 * j + (lane & 1), now,
+                       (lane & 1) ? (unsigned)(u >> 32) : (unsigned)u);
+    }
+    if (!has_tile) return;
+    tile.widen();
+    unsigned* t32 = reinterpret_cast<unsigned*>(L.t);
+    const unsigned long long* src = a.t_words + (size_t)(block & (kWordReps - 1)) * a.t_pitch;
+    bool ok = true;
+    for (int i0 = tid; i0 < 2 * a.rank; i0 += 4 * 256) {
+        unsigned p[4];
+        const int n = min(4, (2 * a.rank - i0 + 255) >> 8);
+        ok = poll_words<4>(src + i0, 256, n, now, a.polls, p) && ok;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < n) t32[i0 + i * 256] = p[i];
+    }
+    if (__syncthreads_or(!ok)) own_t<T>(a, L);
+    const unsigned byte = tile.template finish<true>(a, L);
+    if (tid < 64) {
+        unsigned w = byte << (8 * (tid & 3));        // lanes 0..3 and 4..7: the halves of the 64-bit mask word
+        w |= __shfl_xor(w, 1, kWave);
+        w |= __shfl_xor(w, 2, kWave);
+        w = __shfl(w, (tid & 1) * 4, kWave);
+        if (tid < 2 * kWordReps) word_store(a.m_words + (size_t)(tid >> 1) * a.m_pitch + 2 * block + (tid & 1), now, w);
+        if (tid < kMaskCols && tile.n0 < a.F) {
+            a.masks[tile.n0 >> 3] = (uint8_t)byte;
+            a.step_mask[tile.n0 >> 3] = (uint8_t)byte;
+        }
+    }
+}
+
+// Gate predictor: relu(gate_i . x + b_i) and the mask bit of 8 neurons per wave, as k_predict_gate for one token.
+template <typename T, int NI>
+__device__ __forceinline__ unsigned gate_byte(const Step1Args& a, int grp, const typename Vec<T>::type (&xr)[NI]) {
+    using V = typename Vec<T>::type;
+    const int lane = threadIdx.x & 63, nvec = a.d / Vec<T>::N;
+    const double th = (double)a.theta;
+    unsigned bits = 0;
+#pragma unroll 2
+    for (int e = 0; e < 8; ++e) {
+        const int i = grp * 8 + e;
+        V g[NI];
+        load_vec<T, NI>(g, (const T*)a.A + (size_t)i * a.d, nvec, lane);
+        const double v = column_dot<T, NI>(g, xr) + (double)a.b[i];
+        if (v > th) bits |= 1u << e;
+        if (lane == 0) a.gact[i] = (float)(v > 0.0 ? v : 0.0);
+    }
+    return bits;
+}
+template <typename T, int NI>
+__device__ __forceinline__ void gate_role(const Step1Args& a, int block, unsigned* lds) {
+    using V = typename Vec<T>::type;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    V xr[NI];
+    load_vec<T, NI>(xr, (const T*)a.x, a.d / Vec<T>::N, lane);
+    const int err = a.st->cur.error;
+    const unsigned now = (unsigned)a.st->cur.step + 1u;
+    if (err) return;
+    const int grp = block * 4 + wave;
+    unsigned byte = 0;
+    if (grp * 8 < a.F) {
+        byte = gate_byte<T, NI>(a, grp, xr);
+        if (lane == 0) {
+            a.masks[grp] = (uint8_t)byte;
+            a.step_mask[grp] = (uint8_t)byte;
+        }
+    }
+    if (lane == 0) lds[wave] = byte << (8 * wave);
+    __syncthreads();
+    if (tid < kWordReps) word_store(a.m_words + (size_t)tid * a.m_pitch + block, now, lds[0] | lds[1] | lds[2] | lds[3]);
+}
+
+// pieces of 1 KiB that every vector served by this NI has in full (launch_step1_as)
+constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ? 2 : ni <= 6 ? 4 : ni <= 8 ? 6 : ni <= 9 ? 8 : ni <= 12 ? 9 : 12; }
+
+// ---- window, deletion plan, loaders ----------------------------------------------------------------------------
+
+constexpr int kPtrLds = 4096;        // slot owners staged in LDS
+constexpr int kHoleFew = 2048;       // holes kept in LDS; longer lists go to the global scratch list
+struct PlanLds {
+    unsigned long long rem[1024], add[1024]; // removed and added neurons, one bit each
+    union {
+        PredictLds predict;                  // only when a wait ran out
+        struct {
+            int ids[kListItems], dst[kListItems];    // work items: new neuron, destination of the tail row
+            int hole[kHoleFew];
+            uint16_t blk_h[1024], blk_f[1024];       // per 64-slot block: counts, then exclusive prefixes
+        };
+    };
+    int ptr[kPtrLds];
+    unsigned long long wave_tot[4];
+    int cnt_age[264];
+    unsigned byte[4];
+    unsigned long long flag_h[64], flag_f[64];       // per block: which slots are holes, fillers (plan_alone)
+    int classified;                          // waves that have written their share of those
+    int planned;                             // wave 1 has written dst
+};
+
+// All mask words computed by this workgroup alone (a wait that ran out): m[i] of the words this thread owns
+template <typename T, bool GATE>
+__device__ __forceinline__ void own_masks(const Step1Args& a, PlanLds& L, int wpt, unsigned long long (&m)[4]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nwords = (a.F + 63) >> 6;
+    if constexpr (!GATE) own_t<T>(a, L.predict);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m[i] = 0ull;
+#pragma unroll 1
+    for (int w = 0; w < nwords; ++w) {
+        unsigned half[2];
+        if constexpr (GATE) {
+            for (int hf = 0; hf < 2; ++hf) {
+                const int grp = w * 8 + hf * 4 + wave;
+                unsigned byte = 0;
+#pragma unroll 1
+                for (int e = 0; e < 8 && grp * 8 < a.F; ++e) {
+                    const int i = grp * 8 + e;
+                    const double v = column_dot_slow((const T*)a.A + (size_t)i * a.d, (const T*)a.x, a.d / Vec<T>::N, lane);
+                    if (v + (double)a.b[i] > (double)a.theta) byte |= 1u << e;
+                }
+                __syncthreads();
+                if (lane == 0) L.byte[wave] = byte << (8 * wave);
+                __syncthreads();
+                half[hf] = L.byte[0] | L.byte[1] | L.byte[2] | L.byte[3];
+            }
+        } else {
+            MaskTile<T> tile;
+            tile.request(a, w);
+            __syncthreads();
+            const unsigned byte = tile.template finish<false>(a, L.predict);
+            unsigned v = byte << (8 * (tid & 3));
+            v |= __shfl_xor(v, 1, kWave);
+            v |= __shfl_xor(v, 2, kWave);
+            if (tid < kMaskCols && (tid & 3) == 0) L.byte[tid >> 2] = v;
+            __syncthreads();
+            half[0] = L.byte[0];
+            half[1] = L.byte[1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < wpt && w == tid * wpt + i) m[i] = ((unsigned long long)half[1] << 32) | half[0];
+    }
+    __syncthreads();
+}
+
+// wg = 0: bookkeeping; wg >= 1: loader workgroup wg - 1.
+// Work item q covers tail slot s = n' + q (see k_load).  Rows of more than 2 KiB per vector are handled in two units,
+// the vectors the activation needs (gate | up) with the bookkeeping of the slot, and the down vector; shorter rows
+// are one unit.  Within a loader workgroup
+//   wave 0      loads: requests its part of the host bundle, moves its part of the live tail row in slot s to its hole,
+//               writes the bundle part to slot s, and requests the next unit before it finishes the current one.  The L1
+//               of a compute unit returns loads in order over all its waves, so a load of device memory behind host
+//               reads takes as long as they do (2 to 5 us): the tail row is requested just behind the bundle (ahead of
+//               it, it would hold back the host read), and the loaders are spread over compute units (four loading waves per workgroup moved 35 GB/s where one
+//               moves 50).  The units of a round are dealt to the workgroups one place further each round, so that all
+//               get as many activation parts as down parts (a counter drawn from by atomics balanced no better, and the
+//               wait for its answer cost 1.5 us per unit; with all activation parts first, rows of 16 KiB loaded a
+//               quarter slower, all reads falling on the same half of every row);
+//   waves 1..3  make the deletion plan meanwhile (LDS only), then move the tail rows that nothing overwrites (more neurons removed than added).
+// Lane l holds the same 16-byte pieces of every vector as in the activation role and sums in the same order.
+template <typename T, int NI, bool GLU, bool GATE>
+__device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& L) {
+    using V = typename Vec<T>::type;
+    constexpr int VE = Vec<T>::N;
+    constexpr bool PAIRED = NI > 2;
+    constexpr int GA = PAIRED ? (GLU ? 2 : 1) : (GLU ? 3 : 2);   // vectors of a unit at most
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    const int F = a.F, d = a.d, capacity = a.capacity, k = a.k;
+    const int nwords = (F + 63) >> 6, wpt = (nwords + 255) >> 8;   // mask words per thread (1..4)
+    DevState* st = a.st;
+
+    // ---- everything that does not depend on this step's masks: slot owners, window, x ----
+    auto stage_owners = [&]() {
+        int id[kPtrLds / 256];
+#pragma unroll
+        for (int q = 0; q < kPtrLds / 256; ++q) id[q] = (q * 256 + tid < capacity) ? a.pointers[q * 256 + tid] : -1;
+#pragma unroll
+        for (int q = 0; q < kPtrLds / 256; ++q) L.ptr[q * 256 + tid] = id[q];
+    };
+    stage_owners();
+    const StepCounts cur = st->cur;
+    if (cur.error) {
+        if (wg == 0 && tid == 0) {
+            *a.n_added = 0;
+            *a.n_removed = 0;
+            StepCounts nx = cur;
+            nx.n_added = nx.n_removed = 0;
+            st->next = nx;
+        }
+        return;
+    }
+    const unsigned stamp_now = (unsigned)cur.step + 1u;
+    const int n = cur.num_used, slot_now = cur.ring_pos % k, oldest = min(cur.window_len, k - 1);
+    unsigned long long prev[4], keep[4], m[4], now[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) prev[i] = keep[i] = m[i] = 0ull;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int w = tid * wpt + i;
+        if (i < wpt && w < nwords) {
+            prev[i] = a.cur_set[(size_t)cur.set_par * a.ring_words + w];
+            for (int j0 = 0; j0 < k; j0 += kRingRegs) {
+                unsigned long long v[kRingRegs];
+#pragma unroll
+                for (int j = 0; j < kRingRegs; ++j)
+                    v[j] = (j0 + j < k && ring_age(j0 + j, slot_now, k) <= oldest) ? a.ring[(size_t)(j0 + j) * a.ring_words + w] : 0ull;
+#pragma unroll
+                for (int j = 0; j < kRingRegs; ++j) keep[i] |= v[j];
+            }
+        }
+    }
+    const int lw = wg - 1;                                        // loader wave
+    const bool loads = wg > 0 && wave == 0;
+    const int nvec = d / VE;
+    const size_t row_bytes = a.row_elems * sizeof(T);
+    T* matrix = (T*)a.matrix;
+    V hv[GA][NI], mv[GA][NI];                                    // the vectors of a unit: host bundle, tail row
+    int k_eff = k, off_a = 0, off_r = 0, tot_a = 0, tot_r = 0, n2 = 0, items = 0;
+    auto diff = [&]() {
+        int pa = 0, pr = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            pa += __popcll(now[i] & ~prev[i]);
+            pr += __popcll(prev[i] & ~now[i]);
+        }
+        block_exclusive_scan2<4, true>(pa, pr, L.wave_tot, &off_a, &off_r, &tot_a, &tot_r);
+    };
+    // the added neurons q of [c0, c0 + kListItems) (the words come back from LDS: in registers they would be live through
+    // the load loop)
+    auto fill_ids = [&](int c0) {
+        int q = off_a - c0;
+#pragma unroll 1
+        for (int i = 0; i < wpt; ++i) {
+            unsigned long long bits = L.add[tid * wpt + i];
+            while (bits) {
+                if ((unsigned)q < (unsigned)kListItems) L.ids[q] = (tid * wpt + i) * 64 + __ffsll((long long)bits) - 1;
+                bits &= bits - 1;
+                ++q;
+            }
+        }
+    };
+    // Addresses are kept uniform over the wave (one base per vector, the lane's 16 bytes as offset): a 64-bit address per
+    // lane and piece cost more registers than the data, and spilled registers queue up behind the host reads.
+    const size_t vec_bytes = (size_t)d * sizeof(T);
+    auto host_vec = [&](int nid, int v) -> const char* {          // vector v (gate | up | down) of the bundle of neuron nid
+        const size_t off = (size_t)v * vec_bytes;
+        if (a.host.down && off >= a.host.act_bytes) return a.host.down + (size_t)nid * vec_bytes + (off - a.host.act_bytes);
+        return a.host.rows + (size_t)nid * (a.host.down ? a.host.act_bytes : row_bytes) + off;
+    };
+    auto row_vec = [&](int s, int v) -> char* { return reinterpret_cast<char*>(matrix) + (size_t)s * row_bytes + (size_t)v * vec_bytes; };
+    auto lane_bytes = [&]() {                                    // (opaque: keeps address arithmetic where it is used)
+        unsigned off = (unsigned)lane * 16u;
+        asm volatile("" : "+v"(off));
+        return off;
+    };
+    // (no branch around a load: a conditional load makes the compiler keep a second copy of its registers.  Lanes past the
+    // end of the vector read its last 16 bytes and keep 0.)
+    auto load_pieces = [&](V (&dst)[NI], const char* p) {
+        const unsigned off = lane_bytes(), end = (unsigned)vec_bytes;
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            if (it < full_pieces(NI)) {
+                dst[it] = *reinterpret_cast<const V*>(p + (off + it * 1024u));
+            } else {
+                const V v = *reinterpret_cast<const V*>(p + min(off + it * 1024u, end - 16u));
+                dst[it] = (off + it * 1024u < end) ? v : V(0);
+            }
+        }
+    };
+    auto store_pieces = [&](char* p, const V (&v)[NI]) {
+        const unsigned off = lane_bytes();
+#pragma unroll
+        for (int it = 0; it < NI; ++it)
+            if (it < full_pieces(NI) || off + it * 1024u < (unsigned)vec_bytes) *reinterpret_cast<V*>(p + (off + it * 1024u)) = v[it];
+    };
+    // (the second vector of a unit exists only in its activation part, a third one only in unsplit gated bundles)
+    auto in_part = [&](int g, int part) { return part ? g == 0 : true; };
+    auto request_host = [&](int nid, int part) {
+#pragma unroll
+        for (int g = 0; g < GA; ++g)
+            if (in_part(g, part)) load_pieces(hv[g], host_vec(nid, part * GA + g));
+    };
+    auto request_row = [&](int s, int part) {
+#pragma unroll
+        for (int g = 0; g < GA; ++g)
+            if (in_part(g, part)) load_pieces(mv[g], row_vec(s, part * GA + g));
+    };
+    auto store_row = [&](int s, int part, const V (&v)[GA][NI]) {
+#pragma unroll
+        for (int g = 0; g < GA; ++g)
+            if (in_part(g, part)) store_pieces(row_vec(s, part * GA + g), v[g]);
+    };
+    const int nblk = (n + kWave - 1) >> 6;
+    // slot owner of this lane in block b; blocks past the staged ones are read again
+    auto owner = [&](int b) {
+        const int s = b * kWave + lane;
+        int id = L.ptr[min(s, kPtrLds - 1)];
+        if (b >= kPtrLds / kWave) id = s < n ? a.pointers[s] : -1;
+        return id;
+    };
+    auto flags_of = [&](int b, int id, bool& hole, bool& fill) {
+        const int s = b * kWave + lane;
+        const bool dead = (unsigned)id >= (unsigned)F || ((L.rem[id >> 6] >> (id & 63)) & 1ull);
+        hole = s < n2 && dead;
+        fill = s >= n2 && s < n && !dead;
+    };
+    auto count_block = [&](int b, int id) {
+        bool hole, fill;
+        flags_of(b, id, hole, fill);
+        const int ch = __popcll(__ballot(hole)), cf = __popcll(__ballot(fill));
+        if (lane == 0) {
+            L.blk_h[b] = (uint16_t)ch;
+            L.blk_f[b] = (uint16_t)cf;
+        }
+    };
+
+    // ---- masks -> window -> id list -> first host read ----
+    {
+        unsigned p[8];
+        const int w0 = tid * wpt, nw = max(0, min(wpt, nwords - w0));
+        const bool ok = poll_words<8>(a.m_words + (size_t)(wg & (kWordReps - 1)) * a.m_pitch + 2 * w0, 1, 2 * nw, stamp_now,
+                                      a.polls, p);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < nw) m[i] = ((unsigned long long)p[2 * i + 1] << 32) | p[2 * i];
+        if (__syncthreads_or(!ok)) own_masks<T, GATE>(a, L, wpt, m);        // (does not touch the staged owners)
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) now[i] = keep[i] | m[i];
+    diff();
+    bool over = n - tot_r < 0 || n - tot_r + tot_a > capacity;
+    if (over && a.shrink) {
+        // Dynamic window (see k_window_plan): U_a = union of the newest a masks; keep the largest a whose union fits.
+        auto age_word = [&](int age, int w) -> unsigned long long {
+            return a.ring[(size_t)((slot_now - age + k) % k) * a.ring_words + w];
+        };
+        for (int i = tid; i < k; i += 256) L.cnt_age[i] = 0;
+        lds_barrier();
+        unsigned long long u[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] = m[i];
+        for (int a0 = 1; a0 <= k; a0 += kRingRegs) {          // counts of U_a, a = a0 .. a0 + 7
+            int pc[kRingRegs];
+#pragma unroll
+            for (int j = 0; j < kRingRegs; ++j) pc[j] = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int w = tid * wpt + i;
+                if (i < wpt) {                                // uniform: one word after the other, few registers
+                    unsigned long long e[kRingRegs];
+#pragma unroll
+                    for (int j = 0; j < kRingRegs; ++j) {
+                        const int age = a0 + j - 1;
+                        e[j] = (w < nwords && age >= 1 && age <= oldest) ? age_word(age, w) : 0ull;
+                    }
+#pragma unroll
+                    for (int j = 0; j < kRingRegs; ++j) {
+                        u[i] |= e[j];
+                        pc[j] += __popcll(u[i]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kRingRegs; ++j) {
+                const int tot = __builtin_amdgcn_readlane(wave_inclusive_scan(pc[j], lane), kWave - 1);
+                if (lane == 0 && tot && a0 + j <= k) atomicAdd(&L.cnt_age[a0 + j - 1], tot);
+            }
+        }
+        lds_barrier();
+        k_eff = 0;
+        for (int i = 1; i <= k; ++i)
+            if (L.cnt_age[i - 1] <= capacity) k_eff = i;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            now[i] = m[i];
+            const int w = tid * wpt + i;
+            if (i < wpt && w < nwords)
+                for (int a0 = 1; a0 < k_eff && a0 <= oldest; ++a0) now[i] |= age_word(a0, w);
+        }
+        diff();
+        over = k_eff == 0 || n - tot_r < 0 || n - tot_r + tot_a > capacity;
+    }
+    if (over) {                                      // uniform: leave everything untouched
+        if (wg == 0 && tid == 0) {
+            *a.n_added = 0;
+            *a.n_removed = 0;
+            StepCounts nx = cur;
+            nx.error = 3;                                    // LIF_CAPACITY
+            nx.n_added = nx.n_removed = 0;
+            st->next = nx;
+        }
+        return;
+    }
+    n2 = n - tot_r;
+    items = max(tot_a, tot_r);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (i < wpt) {
+            L.rem[tid * wpt + i] = prev[i] & ~now[i];
+            L.add[tid * wpt + i] = now[i] & ~prev[i];
+        }
+    fill_ids(0);                                                 // (reads only what this thread has just written)
+    if (tid == 0) L.planned = L.classified = 0;
+    lds_barrier();
+
+    // ---- deletion plan (see k_window_plan): holes = dead slots below n', fillers = live slots at or above it ----
+    // Up to 4096 rows waves 1..3 make it while the first host read of wave 0 is on its way (plan_alone).  More rows, and
+    // the bookkeeping workgroup (which needs the number of moves): all waves together, ahead of the host reads.
+    const bool alone = wg > 0 && nblk <= kWave;
+    int H = 0;
+    if (tot_r > 0 && !alone) {                                   // uniform
+        for (int b0 = wave; b0 < nblk; b0 += 4 * 8) {
+            int id[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) id[q] = (b0 + q * 4 < nblk) ? owner(b0 + q * 4) : -1;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (b0 + q * 4 < nblk) count_block(b0 + q * 4, id[q]);
+        }
+        lds_barrier();
+        {                                                        // prefix over the blocks, bpt consecutive ones per thread
+            const int bpt = (nblk + 255) >> 8;
+            int vh = 0, vf = 0, fillers;
+#pragma unroll 1
+            for (int b = tid * bpt; b < min(nblk, tid * bpt + bpt); ++b) {
+                vh += L.blk_h[b];
+                vf += L.blk_f[b];
+            }
+            int ph, pf;
+            block_exclusive_scan2<4, true>(vh, vf, L.wave_tot, &ph, &pf, &H, &fillers);
+#pragma unroll 1
+            for (int b = tid * bpt; b < min(nblk, tid * bpt + bpt); ++b) {
+                const int ch = L.blk_h[b], cf = L.blk_f[b];
+                L.blk_h[b] = (uint16_t)ph;
+                L.blk_f[b] = (uint16_t)pf;
+                ph += ch;
+                pf += cf;
+            }
+        }
+        lds_barrier();
+        if (wg > 0) {
+            const bool in_lds = H <= kHoleFew;                   // longer lists: every workgroup writes the same values to global
+            const int hblk = (n2 + kWave - 1) >> 6;              // blocks with slots below the tail
+#pragma unroll 1
+            for (int b = wave; b < hblk; b += 4) {
+                bool hole, fill;
+                flags_of(b, owner(b), hole, fill);
+                const unsigned long long bh = __ballot(hole);
+                if (hole) {
+                    const int pos = L.blk_h[b] + __popcll(bh & lt);
+                    if (in_lds) L.hole[pos] = b * kWave + lane;
+                    else a.hole_list[pos] = b * kWave + lane;
+                }
+            }
+            if (in_lds) lds_barrier();
+            else __syncthreads();
+        }
+    }
+    auto fill_dst = [&](int c0) {                                // destinations of the tail slots of items [c0, ...) (-1: dead)
+        const bool in_lds = H <= kHoleFew;
+        const int tail = (n2 + c0) >> 6;                         // first block with slots of these items
+#pragma unroll 1
+        for (int b = tail + ((wave - tail) & 3); b < nblk; b += 4) {
+            bool hole, fill;
+            flags_of(b, owner(b), hole, fill);
+            const unsigned long long bf = __ballot(fill);
+            const int q = b * kWave + lane - n2;
+            if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
+                const int r = H - 1 - (L.blk_f[b] + __popcll(bf & lt));
+                L.dst[q - c0] = (fill && r >= 0 && r < H) ? (in_lds ? L.hole[r] : a.hole_list[r]) : -1;
+            }
+        }
+    };
+    // The plan for at most 64 blocks, all of them staged, by waves 1..3: they share the classification, wave 1 does the rest.
+    auto plan_alone = [&](int c0) {
+        for (int b0 = (wave - 1) * 4; b0 < nblk; b0 += 12) {
+            int id[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) id[q] = L.ptr[min(b0 + q, kPtrLds / kWave - 1) * kWave + lane];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {                        // (blocks past the last one have no slots in use)
+                bool hole, fill;
+                flags_of(b0 + q, id[q], hole, fill);
+                const unsigned long long bh = __ballot(hole), bf = __ballot(fill);
+                if (lane == 0 && b0 + q < kWave) {
+                    L.flag_h[b0 + q] = bh;
+                    L.flag_f[b0 + q] = bf;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) __hip_atomic_fetch_add(&L.classified, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (wave != 1) return;
+        while (__hip_atomic_load(&L.classified, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < 3) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        // lane b keeps the flags of block b, and lists its holes
+        unsigned long long mh = lane < nblk ? L.flag_h[lane] : 0ull;
+        const unsigned long long mf = lane < nblk ? L.flag_f[lane] : 0ull;
+        const int v = __popcll(mh) | (__popcll(mf) << 16), inc = wave_inclusive_scan(v, lane), ex = inc - v;
+        const int holes = __builtin_amdgcn_readlane(inc, kWave - 1) & 0xffff;
+        for (int pos = ex & 0xffff; __any(mh != 0ull); ++pos) {
+            if (mh) L.hole[min(pos, kHoleFew - 1)] = lane * kWave + __ffsll((long long)mh) - 1;
+            mh &= mh - 1;
+        }
+        // (at most half of 4096 rows can be holes: kHoleFew)
+        __builtin_amdgcn_wave_barrier();
+        for (int b = (n2 + c0) >> 6; b < nblk; ++b) {
+            const unsigned long long bf = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(mf >> 32), b) << 32) |
+                                          (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mf, b);
+            const int q = b * kWave + lane - n2;
+            if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
+                const int r = holes - 1 - ((int)((unsigned)__builtin_amdgcn_readlane(ex, b) >> 16) + __popcll(bf & lt));
+                L.dst[q - c0] = (((bf >> lane) & 1ull) && r >= 0) ? L.hole[r] : -1;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) __hip_atomic_store(&L.planned, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    if (wg > 0 && !alone) {
+        if (tot_r > 0) fill_dst(0);
+        lds_barrier();
+    }
+    if (loads && lw < (PAIRED ? 2 * tot_a : tot_a))              // unit lw (below kListItems)
+        request_host(__builtin_amdgcn_readfirstlane(L.ids[PAIRED ? lw >> 1 : lw]), PAIRED ? lw & 1 : 0);
+
+    if (wg == 0) {
+        // ---- bookkeeping: window state, id lists, counts ----
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int w = tid * wpt + i;
+            if (i < wpt && w < nwords) {
+                a.cur_set[(size_t)(cur.set_par ^ 1) * a.ring_words + w] = now[i];
+                a.ring[(size_t)slot_now * a.ring_words + w] = m[i];
+            }
+        }
+        for (int i = 0; i < wpt; ++i) {
+            unsigned long long ab = L.add[tid * wpt + i], rb = L.rem[tid * wpt + i];
+            while (ab) {
+                a.added[off_a++] = (tid * wpt + i) * 64 + __ffsll((long long)ab) - 1;
+                ab &= ab - 1;
+            }
+            while (rb) {
+                a.removed[off_r++] = (tid * wpt + i) * 64 + __ffsll((long long)rb) - 1;
+                rb &= rb - 1;
+            }
+        }
+        if (tid == 0) {
+            *a.n_added = tot_a;
+            *a.n_removed = tot_r;
+            StepCounts nx;
+            nx.num_used = n2 + tot_a;
+            nx.n_base = n2;
+            nx.step = cur.step + 1;
+            nx.error = 0;
+            nx.n_added = tot_a;
+            nx.n_removed = tot_r;
+            nx.n_moved = H;
+            nx.window_len = min(min(cur.window_len + 1, k), k_eff);
+            nx.ring_pos = (cur.ring_pos + 1) % k;
+            nx.set_par = cur.set_par ^ 1;
+            st->next = nx;
+            atomicAdd(&st->c_steps, 1ull);
+            atomicAdd(&st->c_added, (unsigned long long)tot_a);
+            atomicAdd(&st->c_removed, (unsigned long long)tot_r);
+            atomicAdd(&st->c_rows_moved, (unsigned long long)H);
+            atomicAdd(&st->c_h2d_bytes, (unsigned long long)tot_a * row_bytes);
+        }
+        return;
+    }
+
+    // ---- load and move ----
+    const int new_step = cur.step + 1, nw = a.n_load;
+    V xr[NI];                                                    // (behind the first host read: needed once that has arrived)
+    if (wave == 0 || !alone) load_pieces(xr, (const char*)a.x);  // (the others have a plan to make first)
+    // What a slot becomes: the activation of a row, in the order of operations of the activation role
+    auto partial_dots = [&](const V (&v)[GA][NI], float& pu, float& pg) {
+        pu = pg = 0.f;
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            pu = dot_acc(v[GLU ? 1 : 0][it], xr[it], pu);
+            if (GLU) pg = dot_acc(v[0][it], xr[it], pg);
+        }
+    };
+    auto finish_slot = [&](int s, int id, float bs, float pu, float pg) {
+        const float du = wave_sum(pu);
+        float act;
+        if (GLU) act = fmaxf(wave_sum(pg) + bs, 0.f) * du;
+        else if (GATE) act = du;                                 // the down projection multiplies with the gate activation
+        else act = fmaxf(du + bs, 0.f);
+        if (lane == 0) {
+            a.ptr_new[s] = id;
+            a.bias_new[s] = bs;
+            a.h_new[s] = act;
+            a.stamp[s] = new_step;
+        }
+    };
+    auto await_plan = [&]() {
+        while (!__hip_atomic_load(&L.planned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    // Lists longer than kListItems are gone through piece by piece.
+    for (int c0 = 0; c0 < items; c0 += kListItems) {
+        if (c0 > 0) {
+            lds_barrier();
+            fill_ids(c0);
+            if (tid == 0) L.planned = L.classified = 0;
+            if (tot_r > 0 && !alone) fill_dst(c0);
+            lds_barrier();
+        }
+        const int n_a = min(max(tot_a - c0, 0), kListItems), n_r = min(max(tot_r - c0, 0), kListItems);     // of this piece
+        const int units = PAIRED ? 2 * n_a : n_a;
+        if (alone && wave > 0) {
+            if (tot_r > c0) plan_alone(c0);
+            load_pieces(xr, (const char*)a.x);
+        }
+        if (wave == 0) {
+            struct Unit {
+                int i, part, nid, dst, old_id;                   // item c0 + i
+                float old_bias, new_bias;
+            };
+            auto make_unit = [&](int u, bool ask) {              // its numbers and its requests
+                Unit r;
+                r.part = PAIRED ? u & 1 : 0;
+                r.i = PAIRED ? u >> 1 : u;
+                const int s = n2 + c0 + r.i;
+                r.nid = __builtin_amdgcn_readfirstlane(L.ids[r.i]);
+                r.dst = r.i < n_r ? __builtin_amdgcn_readfirstlane(L.dst[r.i]) : -1;
+                r.old_id = a.pointers[s];
+                r.old_bias = a.bias[s];
+                r.new_bias = a.b[r.nid];
+                if (ask) request_host(r.nid, r.part);
+                request_row(s, r.part);                          // (also where nothing is moved: no branch around loads)
+                return r;
+            };
+            int place = lw, round = 0;
+            if (lw < units) {
+                if (alone && n_r > 0) await_plan();
+                Unit cu = make_unit(lw, c0 > 0);                 // (the bundle of the first piece was requested above)
+                for (;;) {
+                    const int s = n2 + c0 + cu.i;
+                    float mdu = 0.f, mdg = 0.f, hdu = 0.f, hdg = 0.f;
+                    if (cu.dst >= 0) {                           // uniform over the wave
+                        store_row(cu.dst, cu.part, mv);
+                        if (cu.part == 0) partial_dots(mv, mdu, mdg);
+                    }
+                    store_row(s, cu.part, hv);
+                    if (cu.part == 0) partial_dots(hv, hdu, hdg);
+                    place = place + 1 < nw ? place + 1 : 0;
+                    round += nw;
+                    const bool more = round + place < units;
+                    Unit nu = cu;
+                    if (more) {
+                        nu = make_unit(round + place, true);
+                    }
+                    if (cu.part == 0) {
+                        if (cu.dst >= 0) finish_slot(cu.dst, cu.old_id, cu.old_bias, mdu, mdg);
+                        finish_slot(s, cu.nid, cu.new_bias, hdu, hdg);
+                    }
+                    if (!more) break;
+                    cu = nu;
+                }
+            }
+        } else {
+            const int only = max(n_r - n_a, 0);                  // rows that nothing overwrites
+            if (alone && wave > 1 && only > 0) await_plan();
+            for (int v = lw * 3 + wave - 1; v < (PAIRED ? 2 * only : only); v += 3 * nw) {
+                const int part = (PAIRED && v >= only) ? 1 : 0, i = n_a + v - part * only;
+                const int dst = __builtin_amdgcn_readfirstlane(L.dst[i]), s = n2 + c0 + i;
+                if (dst < 0) continue;
+                request_row(s, part);
+                const int id = a.pointers[s];
+                const float bs = a.bias[s];
+                store_row(dst, part, mv);
+                if (part == 0) {
+                    float pu, pg;
+                    partial_dots(mv, pu, pg);
+                    finish_slot(dst, id, bs, pu, pg);
+                }
+            }
+        }
+    }
+}
+
+// Two workgroups per compute unit as long as a loader's bundle piece, row piece and x fit the registers of half a SIMD.
+template <int NI, bool GLU>
+constexpr int step1_wgs_per_cu() {
+    constexpr int vectors = NI > 2 ? (GLU ? 2 : 1) : (GLU ? 3 : 2);
+    return (2 * vectors + 1) * NI * 4 <= 120 ? 2 : 1;
+}
+template <typename T, int NI, bool GLU, bool GATE>
+__global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(const Step1Args a) {
+    __shared__ __align__(16) unsigned char lds[sizeof(PlanLds) > sizeof(PredictLds) ? sizeof(PlanLds) : sizeof(PredictLds)];
+    const int block = blockIdx.x;
+    if (block < a.n_pred) {
+        if constexpr (GATE) gate_role<T, NI>(a, block, reinterpret_cast<unsigned*>(lds));
+        else lowrank_role<T, NI>(a, block, *reinterpret_cast<PredictLds*>(lds));
+    } else if (block <= a.n_pred + a.n_load) {
+        cache_role<T, NI, GLU, GATE>(a, block - a.n_pred, *reinterpret_cast<PlanLds*>(lds));
+    } else {
+        const int first = a.n_pred + a.n_load + 1;
+        ffn_up_role<T, NI, GLU, true>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, 1, a.capacity, a.row_elems, a.spec,
+                                      block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers, a.gact, a.F, a.st);
+    }
+}
+
+// Launches k_step1 for one element type and bundle form (NI by the row width).  Every combination is compiled in a
+// source file of its own (step1_*.hip), side by side: together they are most of the library's compile time.
+template <typename T, bool GLU, bool GATE>
+inline void launch_step1_as(const Step1Args& a, int grid, hipStream_t s) {
+    const int ni = (a.d / Vec<T>::N + 63) / 64;
+#define LIF_S1(NI) hipLaunchKernelGGL((k_step1<T, NI, GLU, GATE>), dim3(grid), dim3(256), 0, s, a)
+    if (ni <= 1) LIF_S1(1);
+    else if (ni <= 2) LIF_S1(2);
+    else if (ni <= 4) LIF_S1(4);
+    else if (ni <= 6) LIF_S1(6);
+    else if (ni <= 8) LIF_S1(8);
+    else if (ni <= 9) LIF_S1(9);
+    else if (ni <= 12) LIF_S1(12);
+    else LIF_S1(16);
+#undef LIF_S1
+}
+void launch_step1_f16_plain(const Step1Args& a, int grid, hipStream_t s);
+void launch_step1_f16_glu(const Step1Args& a, int grid, hipStream_t s);
+void launch_step1_f16_gate(const Step1Args& a, int grid, hipStream_t s);
+void launch_step1_f32_plain(const Step1Args& a, int grid, hipStream_t s);
+void launch_step1_f32_glu(const Step1Args& a, int grid, hipStream_t s);
+void launch_step1_f32_gate(const Step1Args& a, int grid, hipStream_t s);
+
+}  // namespace lif

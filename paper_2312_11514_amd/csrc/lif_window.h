@@ -6,57 +6,17 @@
 // Everything is integer work: results are exact.
 #pragma once
 
-#include "lif_common.h"
+#include "lif_window_bits.h"
 
 namespace lif {
-
-constexpr int kScanThreads = 1024;   // single-workgroup kernels: 16 waves; one 64-neuron word or one 64-slot block per lane
-constexpr int kMaxSpan = 64;         // d_ffn <= 1024 * 64; capacity <= 1024 * 64
-constexpr int kHoleLds = 4096;       // holes kept in LDS; longer lists spill to the global scratch list
-constexpr int kRingRegs = 8;         // window masks a lane keeps in registers (larger k takes a second pass)
-
-// 64 mask bits starting at neuron 64 * w; the mask has nbytes bytes (a multiple of 8 bits, maybe not of 64)
-__device__ __forceinline__ unsigned long long load_mask_word(const uint8_t* __restrict__ m, int w, int nbytes) {
-    const int b0 = w * 8;
-    if (b0 + 8 <= nbytes) return *reinterpret_cast<const unsigned long long*>(m + b0);
-    unsigned long long v = 0;
-    for (int i = 0; i < 8; ++i)
-        if (b0 + i < nbytes) v |= (unsigned long long)m[b0 + i] << (8 * i);
-    return v;
-}
-
-// Exclusive prefix sums of two counts per thread (each at most 64) in one pass over a workgroup of NW waves.
-// Inside a wave both counts travel in one 32-bit value (a wave sums to at most 4096 per count); the totals of
-// the waves are kept as two 32-bit halves of a 64-bit LDS word.  One barrier, two with GUARD (needed when
-// wave_tot may still be read from an earlier scan that no barrier separates from this one).
-template <int NW, bool GUARD>
-__device__ __forceinline__ void block_exclusive_scan2(int va, int vb, unsigned long long* wave_tot, int* off_a,
-                                                      int* off_b, int* tot_a, int* tot_b) {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
-    const int v = (vb << 16) | va;
-    const int inc = wave_inclusive_scan(v, lane);
-    if (GUARD) lds_barrier();
-    if (lane == kWave - 1) wave_tot[w] = ((unsigned long long)(unsigned)(inc >> 16) << 32) | (unsigned)(inc & 0xffff);
-    lds_barrier();
-    unsigned long long before = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        const unsigned long long t = wave_tot[i];
-        if (i < w) before += t;
-        all += t;
-    }
-    const int ex = inc - v;                                  // exclusive inside the wave, both halves at once
-    *off_a = (int)(unsigned)(before & 0xffffffffull) + (ex & 0xffff);
-    *off_b = (int)(unsigned)(before >> 32) + (ex >> 16);
-    *tot_a = (int)(unsigned)(all & 0xffffffffull);
-    *tot_b = (int)(unsigned)(all >> 32);
-}
 
 // One workgroup does the window update and the deletion plan back to back.
 //
 // Window (Section 3.1): ring[j] holds the step masks of the last k steps; step t overwrites
-// ring[t mod k].  Lane w owns the 64 neurons of word w:
-//   prev = OR of all ring words (S_{t-1});  keep = OR of all but ring[t mod k];  S_t = keep | m
+// ring[t mod k].  The entry written a steps ago has age a; entries older than window_len left the window (or were
+// never written) and are not read.  The bitmap of the cached set is double-buffered (set_par): a fused step writes the
+// new one while others still read the old one.  Lane w owns the 64 neurons of word w:
+//   prev = cached set (S_{t-1});  keep = OR of the ring entries of ages 1 .. k - 1;  S_t = keep | m
 //   added = m & ~prev;  removed = prev & ~(keep | m)
 // A workgroup-wide prefix sum over the popcounts puts the ids out in ascending order.
 //
@@ -92,7 +52,8 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
 
     // ---- issue the state-independent loads ----
     unsigned long long m = have ? load_mask_word(step_mask, tid, nbytes) : 0ull;   // first (or only) mask of the step
-    const unsigned long long cur = have ? cur_set[tid] : 0ull;                       // what the cache holds now
+    unsigned long long cur = have ? cur_set[tid] : 0ull;                             // what the cache holds now
+    const unsigned long long cur1 = have ? cur_set[ring_words + tid] : 0ull;
     unsigned long long rv[kRingRegs];
 #pragma unroll
     for (int j = 0; j < kRingRegs; ++j) rv[j] = (have && j < k) ? ring[(size_t)j * ring_words + tid] : 0ull;
@@ -105,18 +66,20 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
         const int s = (w + it * NW) * kWave + lane;
         idpre[it] = (s < capacity) ? pointers[s] : -1;
     }
-    const int err = st->error;
-    const int t = st->step;
-    const int n = st->num_used;
-    const int wl_prev = st->window_len;
-    const int pos = st->ring_pos;
+    const int err = st->cur.error;
+    const int t = st->cur.step;
+    const int n = st->cur.num_used;
+    const int wl_prev = st->cur.window_len;
+    const int pos = st->cur.ring_pos;
+    const int par = st->cur.set_par;
+    if (par) cur = cur1;
 
     if (err) {
         if (tid == 0) {
             *n_added = 0;
             *n_removed = 0;
-            st->n_added = 0;
-            st->n_removed = 0;
+            st->cur.n_added = 0;
+            st->cur.n_removed = 0;
         }
         return;
     }
@@ -125,13 +88,14 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
     const int slot = pos % k;                            // ring entry that this step's (first) mask replaces
     const unsigned long long prev = cur;
     unsigned long long keep = 0;
+    const int oldest = min(wl_prev, k - 1);              // largest age that stays in the window
 #pragma unroll
     for (int j = 0; j < kRingRegs; ++j)
-        if (j != slot) keep |= rv[j];
+        if (ring_age(j, slot, k) <= oldest) keep |= rv[j];
     if (have) {
         for (int j = kRingRegs; j < k; ++j) {                 // only for windows longer than kRingRegs steps
             const unsigned long long v = ring[(size_t)j * ring_words + tid];
-            if (j != slot) keep |= v;
+            if (ring_age(j, slot, k) <= oldest) keep |= v;
         }
     }
     unsigned long long now = keep | m;                   // S_t with the full window
@@ -147,8 +111,8 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
         if (have) {
             for (int i = 0; i < ntok; ++i) now |= load_mask_word(step_mask + (size_t)i * row_bytes, tid, nbytes);
             for (int j = 0; j < k; ++j) {
-                const int since = j - pos + (j < pos ? k : 0);   // (j - pos) mod k: this entry is overwritten by kept token `since`
-                if (since >= keep_tok) now |= ring[(size_t)j * ring_words + tid];
+                const int age = ring_age(j, slot, k);        // the kept tokens overwrite the ages above k - keep_tok
+                if (age <= min(wl_prev, k - keep_tok)) now |= ring[(size_t)j * ring_words + tid];
             }
         }
     }
@@ -161,6 +125,7 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
         auto age_mask = [&](int a) -> unsigned long long {        // mask of age a (1 <= a <= k), word of this lane
             if (a <= keep_tok) return load_mask_word(step_mask + (size_t)(keep_tok - a) * nbytes, tid, nbytes);
             const int m_old = a - keep_tok;                        // m_old-th most recent entry written before this pass
+            if (m_old > wl_prev) return 0ull;
             return ring[(size_t)(((pos - m_old) % k + k) % k) * ring_words + tid];
         };
         for (int a = tid; a <= k; a += THREADS) cnt_age[a] = 0;
@@ -180,11 +145,11 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
             if (cnt_age[a] <= capacity) k_eff = a;
         if (k_eff < 0) {                                     // uniform: the masks of the pass alone do not fit
             if (tid == 0) {
-                st->error = 3;                               // LIF_CAPACITY
+                st->cur.error = 3;                               // LIF_CAPACITY
                 *n_added = 0;
                 *n_removed = 0;
-                st->n_added = 0;
-                st->n_removed = 0;
+                st->cur.n_added = 0;
+                st->cur.n_removed = 0;
             }
             return;
         }
@@ -217,7 +182,7 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
 #pragma unroll
                 for (int j = 0; j < kRingRegs; ++j)
                     if (j == idx) v = rv[j];
-                e[a] = (a < k) ? v : 0ull;
+                e[a] = (a <= oldest) ? v : 0ull;
             }
             unsigned long long u = m;
             ua[0] = u;
@@ -238,7 +203,7 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
         } else {
             unsigned long long u = m;
             for (int a = 1; a <= k; ++a) {
-                if (a > 1 && have) u |= ring[(size_t)((slot - (a - 1) + k) % k) * ring_words + tid];
+                if (a > 1 && a - 1 <= oldest && have) u |= ring[(size_t)((slot - (a - 1) + k) % k) * ring_words + tid];
                 const int pc = __popcll(u);
                 if (pc) atomicAdd(&cnt_age[a - 1], pc);
             }
@@ -255,11 +220,11 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
         }
         if (k_eff == 0) {                                    // uniform: this step's mask alone does not fit
             if (tid == 0) {
-                st->error = 3;                               // LIF_CAPACITY
+                st->cur.error = 3;                               // LIF_CAPACITY
                 *n_added = 0;
                 *n_removed = 0;
-                st->n_added = 0;
-                st->n_removed = 0;
+                st->cur.n_added = 0;
+                st->cur.n_removed = 0;
             }
             return;
         }
@@ -269,7 +234,7 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
             for (int a = 1; a < kRingRegs; ++a)
                 if (a < k_eff) now = ua[a];                  // U_a grows with a: the last one taken is U_{k_eff}
         } else if (have) {
-            for (int a = 2; a <= k_eff; ++a) now |= ring[(size_t)((slot - (a - 1) + k) % k) * ring_words + tid];
+            for (int a = 2; a <= k_eff && a - 1 <= oldest; ++a) now |= ring[(size_t)((slot - (a - 1) + k) % k) * ring_words + tid];
         }
     }
     unsigned long long abits = now & ~prev;
@@ -280,11 +245,11 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
     const int n2 = n - tot_r;
     if (n2 < 0 || n2 + tot_a > capacity) {          // uniform: leave the window untouched
         if (tid == 0) {
-            st->error = 3;                           // LIF_CAPACITY
+            st->cur.error = 3;                           // LIF_CAPACITY
             *n_added = 0;
             *n_removed = 0;
-            st->n_added = 0;
-            st->n_removed = 0;
+            st->cur.n_added = 0;
+            st->cur.n_removed = 0;
         }
         return;
     }
@@ -374,18 +339,14 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
     // ---- the new window and the id lists go out last: nothing in this kernel reads them back, and the plan above
     // does not wait for them ----
     if (have) {
-        cur_set[tid] = now;
+        cur_set[par * ring_words + tid] = now;
+        // (masks that the dynamic window dropped are older than window_len from now on)
         if (!multi) {
             ring[(size_t)slot * ring_words + tid] = m;
-            for (int a = k_eff + 1; a <= k; ++a)             // masks dropped by the dynamic window leave it for good
-                ring[(size_t)((slot - (a - 1) + k) % k) * ring_words + tid] = 0ull;
         } else {
             for (int i = max(0, keep_tok - k); i < keep_tok; ++i)
                 ring[(size_t)((pos + i) % k) * ring_words + tid] =
                     load_mask_word(step_mask + (size_t)i * nbytes, tid, nbytes);
-            // entries written before this pass that the dynamic window dropped (ages above k_eff) leave for good
-            for (int m_old = max(k_eff - keep_tok, 0) + 1; m_old <= k - keep_tok; ++m_old)
-                ring[(size_t)(((pos - m_old) % k + k) % k) * ring_words + tid] = 0ull;
         }
     }
     while (abits) {
@@ -399,13 +360,13 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
     if (tid == 0) {
         *n_added = tot_a;
         *n_removed = tot_r;
-        st->n_added = tot_a;
-        st->n_removed = tot_r;
-        st->n_base = n2;
-        st->n_moved = H;
-        st->window_len = multi ? min(min(wl_prev + keep_tok, k), k_eff) : min(min(wl_prev + 1, k), k_eff);
-        st->ring_pos = (pos + (multi ? keep_tok : 1)) % k;
-        st->step = t + 1;
+        st->cur.n_added = tot_a;
+        st->cur.n_removed = tot_r;
+        st->cur.n_base = n2;
+        st->cur.n_moved = H;
+        st->cur.window_len = multi ? min(min(wl_prev + keep_tok, k), k_eff) : min(min(wl_prev + 1, k), k_eff);
+        st->cur.ring_pos = (pos + (multi ? keep_tok : 1)) % k;
+        st->cur.step = t + 1;
         atomicAdd(&st->c_steps, 1ull);
         atomicAdd(&st->c_added, (unsigned long long)tot_a);
         atomicAdd(&st->c_removed, (unsigned long long)tot_r);
@@ -433,8 +394,8 @@ __device__ __forceinline__ void load_rows_role(char* __restrict__ matrix, int32_
                                                const float* __restrict__ b, const int32_t* __restrict__ added,
                                                const int32_t* __restrict__ move_dst, size_t row_bytes, int F,
                                                int block, int nblocks, DevState* st) {
-    if (st->error) return;
-    const int n2 = st->n_base, c = st->n_removed, a = st->n_added;
+    if (st->cur.error) return;
+    const int n2 = st->cur.n_base, c = st->cur.n_removed, a = st->cur.n_added;
     const int items = max(c, a);
     const int cpr = (int)((row_bytes + kLoadChunk - 1) / kLoadChunk);
     const long long total = (long long)items * cpr;
@@ -484,7 +445,7 @@ __device__ __forceinline__ void load_rows_role(char* __restrict__ matrix, int32_
         }
     }
     if (block == 0 && tid == 0) {
-        st->num_used = n2 + a;
+        st->cur.num_used = n2 + a;
         atomicAdd(&st->c_h2d_bytes, (unsigned long long)a * row_bytes);
     }
 }
@@ -497,12 +458,12 @@ __global__ __launch_bounds__(256) void k_load(char* __restrict__ matrix, int32_t
     load_rows_role(matrix, pointers, bias, host, b, added, move_dst, row_bytes, F, blockIdx.x, gridDim.x, st);
 }
 
-// Empty cache: no mask in the window, state and counters zero.
-// (ring_total_words covers the ring and the current-set bitmap that follows it)
-__global__ void k_reset(unsigned long long* __restrict__ ring, int ring_total_words, int32_t* __restrict__ stamp,
+// Empty cache: no mask in the window, state and counters zero, no word handed over yet (the stamps start again).
+// `words`: the hand-over words of the fused step, then the window ring and the two bitmaps of the cached set.
+__global__ void k_reset(unsigned long long* __restrict__ words, int total_words, int32_t* __restrict__ stamp,
                         int capacity, DevState* st) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    for (int j = i; j < ring_total_words; j += gridDim.x * blockDim.x) ring[j] = 0ull;
+    for (int j = i; j < total_words; j += gridDim.x * blockDim.x) words[j] = 0ull;
     for (int j = i; j < capacity; j += gridDim.x * blockDim.x) stamp[j] = -1;   // no activation from a fused step
     if (i == 0) {
         DevState z = {};

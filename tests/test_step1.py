@@ -1,0 +1,111 @@
+"""The single-launch step of one token (lif_step, batch 1) against the four separate calls, bit for bit, where its
+hand-overs, lists and loops can go wrong: edges of the 64-neuron tiles, slots of more than 512 work items, more than
+4096 holes, more than 256 blocks of slots, long windows, the dynamic window, overflow - each waiting for the values that
+other workgroups publish, and (polls = 0) never waiting, so that every workgroup computes them itself."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # name: (dtype, glu, gate, d, F, rank, k, p, capacity, shrink, pairs)
+    "one-tile": ("f32", False, False, 8, 8, 4, 2, 0.4, 8, False, 0),
+    "partial-tile": ("f16", False, False, 264, 1096, 40, 3, 0.08, 700, False, 0),
+    "more-columns-than-tiles": ("f16", False, False, 128, 192, 320, 4, 0.1, 192, False, 0),
+    "glu": ("f16", True, False, 1544, 712, 24, 5, 0.1, 500, False, 3),
+    "gate": ("f16", False, True, 1032, 1096, 8, 3, 0.1, 900, False, 0),
+    "gate-f32": ("f32", False, True, 260, 136, 8, 2, 0.2, 136, False, 1),
+    "long-window": ("f32", False, False, 64, 4104, 16, 11, 0.02, 3000, False, 0),
+    "dynamic-window": ("f16", False, False, 64, 4160, 16, 9, 0.1, 900, True, 0),
+    "dynamic-window-two-words": ("f16", False, False, 64, 17000, 64, 4, 0.1, 4500, True, 0),
+    "slot-of-many-items": ("f16", False, False, 520, 6000, 32, 2, 0.35, 6000, False, 1),
+    "many-holes": ("f16", False, False, 16, 40000, 64, 1, 0.5, 40000, False, 0),
+}
+
+
+def _make(name, seed=5):
+    dtype, glu, gate, d, F, rank, k, p, cap, shrink, pairs = CASES[name]
+    w = wl.scaled(wl.WORKLOADS["C1"], name=name, d_model=d, d_ffn=F, rank=rank, window_k=k, p_active=p, dtype=dtype,
+                  glu=glu or gate, gate_resident=gate, capacity_rows=cap, shrink=shrink)
+    rng = np.random.default_rng(seed)
+    dt = w.np_dtype
+    g = lambda *s: rng.standard_normal(s, dtype=np.float32)
+    mats = [(g(F, d) / np.sqrt(d)).astype(dt) for _ in range(3 if w.glu else 2)]
+    act = mats[0]
+    z = float(wl.norm.ppf(1 - p))
+    b = (-z * np.linalg.norm(act.astype(np.float64), axis=1)).astype(np.float32)
+    A, B = (g(d, rank) / np.sqrt(d)).astype(dt), (g(rank, F) / np.sqrt(rank)).astype(dt)
+    c = (-z * np.linalg.norm(B.astype(np.float64), axis=0)).astype(np.float32)
+    w_gate, w_up, w_down = (mats if w.glu else [None] + mats)
+    parts = ([w_gate] if (w.glu and not gate) else []) + [w_up, w_down]
+    L = wl.LayerData(w_up, w_down, w_gate, b, A, B, c, 0.0, np.ascontiguousarray(np.concatenate(parts, axis=1)))
+    return w, L, wl.make_inputs(w, tokens=16), pairs
+
+
+def _snapshot(gpu):
+    lay = gpu.layer
+    st = lay.state()
+    n, na, nr = st["num_used"], int(lay.n_added.item()), int(lay.n_removed.item())
+    return (st, gpu.y.cpu().numpy().tobytes(), lay.masks.cpu().numpy().tobytes(), lay.step_mask.cpu().numpy().tobytes(),
+            lay.added[:na].cpu().numpy().tobytes(), lay.removed[:nr].cpu().numpy().tobytes(),
+            lay.pointers[:n].cpu().numpy().tobytes(), lay.bias[:n].cpu().numpy().tobytes(),
+            lay.matrix[:n].cpu().numpy().tobytes(), lay.counters())
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_single_launch_step_equals_four_calls(name):
+    from tests.harness import GpuLayer
+    w, L, X, pairs = _make(name)
+    ref = GpuLayer(w, L)
+    runs = []
+    for polls in (None, 0):
+        g = GpuLayer(w, L, share=ref)
+        if polls is not None:
+            g.layer.set_handoff_polls(polls)
+        if pairs:
+            g.layer.set_loader_pairs(pairs)
+        runs.append((polls, g))
+    xd = ref.upload_x(X)
+    for again in range(2):                          # the second time after a reset: the stamps start again
+        for g in [ref] + [g for _, g in runs]:
+            g.layer.reset()
+        for t in range(len(X)):
+            ref.layer.step_calls(xd[t], ref.y)
+            want = _snapshot(ref)
+            assert want[0]["error"] == 0
+            for polls, g in runs:
+                print(f"{name}: token {t} polls {polls}", flush=True)
+                g.layer.step(xd[t], g.y)
+                got = _snapshot(g)
+                for i, (a, b) in enumerate(zip(got, want)):
+                    assert a == b, f"{name}: token {t}, polls {polls}, item {i}"
+    moved = ref.layer.counters()["rows_moved"]
+    assert moved > 0 or name in ("one-tile", "more-columns-than-tiles")
+
+
+@pytest.mark.parametrize("shrink", [False, True])
+def test_single_launch_step_overflow(shrink):
+    """A step whose mask does not fit: the sticky error, nothing loaded, and mixed use with the four calls before it."""
+    from tests.harness import GpuLayer
+    w, L, X, _ = _make("partial-tile")
+    ref = GpuLayer(w, L, capacity=150, shrink=shrink)
+    g = GpuLayer(w, L, capacity=150, shrink=shrink, share=ref)
+    L_all = np.full(w.d_ffn, 10.0, np.float32)
+    xd = ref.upload_x(X)
+    for t in range(3):
+        ref.layer.step_calls(xd[t], ref.y)
+        (g.layer.step if t % 2 == 0 else g.layer.step_calls)(xd[t], g.y)
+        assert _snapshot(g) == _snapshot(ref)
+    for lay in (ref.layer, g.layer):                # every neuron is predicted from here on
+        lay.c.copy_(torch.from_numpy(L_all))
+    ref.layer.step_calls(xd[3], ref.y)
+    g.layer.step(xd[3], g.y)
+    want, got = _snapshot(ref), _snapshot(g)
+    assert got[0]["error"] != 0 and got == want
+    g.layer.step(xd[4], g.y)
+    ref.layer.step_calls(xd[4], ref.y)
+    want, got = _snapshot(ref), _snapshot(g)
+    assert got[0] == want[0] and got[4:] == want[4:]
