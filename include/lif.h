@@ -273,9 +273,8 @@ size_t lif_static_scratch_bytes(void);
  * four calls in sequence.  The cache update and the activation stage of the FFN share one
  * launch: the host-link gather keeps few compute units busy, the others compute the
  * activations of the resident rows meanwhile (Section 3.3 items 2 and 3 overlapped).  For
- * batch == 1 the predictor and the window update are part of that launch too, and the loaders
- * compute the activations of the rows they write, with the same summation order; for fp16
- * batches a short second pass covers those rows.  y, masks, ids,
+ * batch == 1 the predictor is part of that launch too; the loaders compute the activations of
+ * the rows they write, with the same summation order.  y, masks, ids,
  * counts and the cache are bit-identical to the four-call sequence.
  */
 int lif_step(lif_layer* layer, const void* x_dev, int32_t batch, void* y_dev, uint8_t* masks_dev,

@@ -16,7 +16,6 @@
 #include "lif_ffn_mfma.h"
 #include "lif_ffn_down_mfma.h"
 #include "lif_predict.h"
-#include "lif_step.h"
 #include "lif_step1.h"
 #include "lif_window.h"
 
@@ -43,11 +42,15 @@ int fail(int code, const char* fmt, const char* detail = "") {
     } while (0)
 
 // Bytes of host reads that lif_step keeps outstanding: pairs of loader workgroups (one bundle in flight per pair) =
-// kStepInflightBytes / bundle bytes, within 5..32.  The link needs about 128 KiB (56 GB/s at 1.5 to 2.4 us); the rest covers
+// kStepInflightBytes / bundle bytes, within 5..kStepPairs.  The link needs about 128 KiB (56 GB/s at 1.5 to 2.4 us); the rest covers
 // the time in which a loader writes a bundle out and asks for the next.  One token with 144 / 192 / 256 / 320 / 384 KiB:
 // OPT shape 60.4 / 59.4 / 58.2 / 58.4 / 60.0 us, Falcon shape 188 / 159 / 143 / 141 / 140 us, gated Llama-2 shape 147 / 138 /
 // 137 / 138 / 143 us.
-constexpr size_t kStepInflightBytes = 320 * 1024;
+// For rows of at most 10 KiB the number of loaders is what limits (kStepPairs).  Several tokens: more loaders, a bundle takes
+// longer to deal with; 20 / 32 / 48 / 64 pairs of 16 KiB rows: 205 / 207 / 200 / 200 us a pass, of 24 KiB: 262 / 252 / 249 / 250;
+// but every loader workgroup costs a compute unit of the activation stage (11 KiB rows, 60 loaded: 52 / 52 / 53 / 56).
+constexpr size_t kStepInflightBytes = 320 * 1024, kStepInflightBytesB = 768 * 1024;
+constexpr int kStepPairs = 32, kStepPairsB = 48;
 constexpr int kDefaultPolls = 4096;      // a failed poll takes about 0.7 us: 3 ms before a workgroup helps itself
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -105,8 +108,8 @@ Layout make_layout(const lif_config& c) {
     off = align_up(off + sizeof(float) * c.max_batch * c.capacity_rows, 256);
     L.ypart = off;                     // per-chunk partial outputs of the down projection
     off = align_up(off + sizeof(float) * kDownChunksMax * c.max_batch * c.d_model, 256);
-    L.h_new = off;                     // activations written by the fused load kernel (single-token steps)
-    off = align_up(off + sizeof(float) * c.capacity_rows, 256);
+    L.h_new = off;                     // activations written by the loaders of a fused step
+    off = align_up(off + sizeof(float) * c.max_batch * c.capacity_rows, 256);
     L.stamp = off;                     // step number at which h_new[slot] was written
     off = align_up(off + sizeof(int32_t) * c.capacity_rows, 256);
     L.ptr_new = off;                   // slot owners and biases written by the fused step
@@ -263,9 +266,28 @@ int geometry_rows(const lif_layer* L) {
                                 : L->cfg.capacity_rows;
 }
 
+// what the down projection of a fused step commits (`pass`: token-granular window update; the masks enter the ring here)
+struct FusedCall {
+    bool on = false;
+    const uint8_t* masks = nullptr;
+    int keep = 1;
+    bool pass = false;
+};
+FusedRows fused_rows(const lif_layer* L, const FusedCall& f) {
+    FusedRows r = {};
+    if (!f.on) return r;
+    r.h_new = L->h_new; r.stamp = L->stamp; r.ptr_new = L->ptr_new; r.bias_new = L->bias_new;
+    r.pointers = L->buf.pointers; r.bias = L->buf.bias;
+    if (f.pass) {
+        r.masks = f.masks; r.ring = L->ring; r.ring_words = ring_words(L->cfg); r.nbytes = L->cfg.d_ffn / 8;
+        r.k = L->cfg.window_k; r.keep = f.keep;
+    }
+    return r;
+}
+
 // one token
 template <typename T, bool SKIP>
-void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t s, bool fused_step) {
+void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
     const lif_config& c = L->cfg;
     constexpr int cols = kDown1Lanes * Vec<T>::N;
     const int slices = ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;     // whole runs of slices per XCD
@@ -276,10 +298,9 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     // groups of slots whose activations are asked for ahead of the row count: those the hint covers; without a hint 2048
     // slots if that many rows make one pass (else the order of the slots is not known yet)
     const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;
-    FusedRows f = {};
-    if (fused_step) f = FusedRows{L->h_new, L->stamp, L->ptr_new, L->bias_new, L->buf.pointers, L->buf.bias};
+    const FusedRows f = fused_rows(L, fc);
 #define LIF_D1(W)                                                                                            \
-    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W>), dim3(slices + (fused_step ? 1 : 0), wg_rows), dim3(W * 64), 0, s,     \
+    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(W * 64), 0, s,     \
                        (const T*)L->buf.matrix, h, f, (T*)y, ypart, c.d_model, c.capacity_rows, L->row_elems,        \
                        down_off, spec, slices, L->buf.pointers, L->gact, c.d_ffn, L->st)
     if (waves == 8) LIF_D1(8);
@@ -292,16 +313,17 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
 
 // several tokens, fp32
 template <typename T, int BT, bool SKIP>
-void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s) {
+void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
     const lif_config& c = L->cfg;
     constexpr int cols = kDownLanesB * Vec<T>::N;
     // workgroup rows: enough for the chunks of the expected number of rows; fewer than the chunks in use is still
     // correct (a workgroup row then takes several chunks)
     const int wg_rows = down_chunks(geometry_rows(L));
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB>), dim3((c.d_model + cols - 1) / cols, wg_rows), dim3(256), 0,
-                       s, (const T*)L->buf.matrix, h, (T*)y, ypart, c.d_model, batch, c.capacity_rows, L->row_elems,
-                       down_off, L->st);
+    const int slices = (c.d_model + cols - 1) / cols;
+    hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(256), 0, s,
+                       (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, c.d_model, batch, c.capacity_rows,
+                       L->row_elems, down_off, slices, L->st);
     if (wg_rows > 1)
         hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
                            ypart, (T*)y, c.d_model, batch, L->st);
@@ -309,7 +331,7 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
 
 // several tokens, fp16: the down projection on the matrix cores
 template <bool SKIP>
-void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s) {
+void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
     const lif_config& c = L->cfg;
     const int slices = (c.d_model + kDmCols - 1) / kDmCols;
     const int chunk_rows = down_mfma_chunk_rows(c.capacity_rows);
@@ -317,41 +339,40 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves>), dim3(slices, wg_rows), dim3(kDmWaves * 64), 0, s,
-                       (const _Float16*)L->buf.matrix, h, (_Float16*)y, ypart, c.d_model, batch, c.capacity_rows,
-                       L->row_elems, down_off, chunk_rows, L->st);
+    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(kDmWaves * 64), 0, s,
+                       (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y, ypart, c.d_model, batch,
+                       c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st);
     if (wg_rows > 1)
         hipLaunchKernelGGL(k_ffn_down_mfma_finish, dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart,
                            (_Float16*)y, c.d_model, batch, chunk_rows, L->st);
 }
 
 template <typename T>
-void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, bool fused_step = false) {
+void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc = FusedCall()) {
     const bool skip = L->cfg.ffn_mode == LIF_FFN_SKIP_DEAD;
     if (batch == 1) {
-        if (skip) launch_ffn_down1<T, true>(L, y, h, ypart, s, fused_step);
-        else launch_ffn_down1<T, false>(L, y, h, ypart, s, fused_step);
+        if (skip) launch_ffn_down1<T, true>(L, y, h, ypart, s, fc);
+        else launch_ffn_down1<T, false>(L, y, h, ypart, s, fc);
         return;
     }
     if constexpr (std::is_same<T, _Float16>::value) {
-        if (skip) launch_ffn_down_mfma<true>(L, batch, y, h, ypart, s);
-        else launch_ffn_down_mfma<false>(L, batch, y, h, ypart, s);
+        if (skip) launch_ffn_down_mfma<true>(L, batch, y, h, ypart, s, fc);
+        else launch_ffn_down_mfma<false>(L, batch, y, h, ypart, s, fc);
     } else if (batch <= 4) {
-        if (skip) launch_ffn_down_batch<T, 4, true>(L, batch, y, h, ypart, s);
-        else launch_ffn_down_batch<T, 4, false>(L, batch, y, h, ypart, s);
+        if (skip) launch_ffn_down_batch<T, 4, true>(L, batch, y, h, ypart, s, fc);
+        else launch_ffn_down_batch<T, 4, false>(L, batch, y, h, ypart, s, fc);
     } else {
-        if (skip) launch_ffn_down_batch<T, 8, true>(L, batch, y, h, ypart, s);
-        else launch_ffn_down_batch<T, 8, false>(L, batch, y, h, ypart, s);
+        if (skip) launch_ffn_down_batch<T, 8, true>(L, batch, y, h, ypart, s, fc);
+        else launch_ffn_down_batch<T, 8, false>(L, batch, y, h, ypart, s, fc);
     }
 }
 
-// one token: everything up to the down projection
-void launch_step1(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_mask, int32_t* added, int32_t* n_added,
-                  int32_t* removed, int32_t* n_removed, hipStream_t s) {
+// arguments that both forms of a fused step take
+StepArgs step_args(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_mask, int32_t* added, int32_t* n_added,
+                   int32_t* removed, int32_t* n_removed, int batch) {
     const lif_config& c = L->cfg;
-    const bool gate = c.predictor == LIF_PRED_GATE, f32 = c.dtype == LIF_F32;
     const int words = ring_words(c);
-    Step1Args a = {};
+    StepArgs a = {};
     a.A = L->buf.A; a.B = L->buf.B; a.c = L->buf.c; a.rank = c.rank; a.theta = c.threshold;
     a.t_pitch = words_pitch(2 * std::max(c.rank, 0)); a.m_pitch = words_pitch(2 * words);
     a.t_words = L->words; a.m_words = L->words + (size_t)kWordReps * a.t_pitch;
@@ -362,23 +383,32 @@ void launch_step1(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_mas
     a.matrix = L->buf.matrix; a.pointers = L->buf.pointers; a.bias = L->buf.bias; a.host = L->host; a.b = L->buf.b;
     a.row_elems = L->row_elems; a.F = c.d_ffn; a.d = c.d_model; a.capacity = c.capacity_rows;
     a.x = x; a.h = L->h; a.h_new = L->h_new; a.stamp = L->stamp; a.ptr_new = L->ptr_new; a.bias_new = L->bias_new;
-    a.polls = L->polls; a.st = L->st;
-    // predictor workgroups: one per 64 neurons (32 with the gate predictor), and enough for the columns of A
-    a.n_pred = gate ? 2 * words : std::max(words, (c.rank + 3) / 4);
+    a.batch = batch; a.keep = 1; a.polls = L->polls; a.st = L->st;
     // loader waves: two per bundle in flight
+    const size_t inflight = batch > 1 ? kStepInflightBytesB : kStepInflightBytes;
+    const int most = batch > 1 ? kStepPairsB : kStepPairs;
     const int pairs = L->loader_pairs > 0 ? L->loader_pairs
-                                          : (int)std::min<size_t>(32, std::max<size_t>(5, kStepInflightBytes / L->row_bytes));
+                                          : std::min(most, std::max(5, (int)std::min<size_t>(inflight / L->row_bytes, most)));
     a.n_load = 2 * pairs;
-    // activation role: one wave per row; with a row-count hint the grid is sized to it
-    a.spec = L->expected_rows > 0 ? 1 : 0;
-    const int up = a.spec ? std::min(kUpMaxWgs, std::max(1, std::min(L->expected_rows, c.capacity_rows) / 4))
-                          : std::min((c.capacity_rows + 3) / 4, 512);
-    const int grid = a.n_pred + 1 + a.n_load + up;
-    if (f32) (gate ? launch_step1_f32_gate : c.glu ? launch_step1_f32_glu : launch_step1_f32_plain)(a, grid, s);
-    else (gate ? launch_step1_f16_gate : c.glu ? launch_step1_f16_glu : launch_step1_f16_plain)(a, grid, s);
+    return a;
+}
+// workgroups of the activation role with one wave per row; with a row-count hint the grid is sized to it
+int up_blocks(const lif_layer* L) {
+    return L->expected_rows > 0 ? std::min(kUpMaxWgs, std::max(1, std::min(L->expected_rows, L->cfg.capacity_rows) / 4))
+                                : std::min((L->cfg.capacity_rows + 3) / 4, 512);
 }
 
-constexpr int kFuseBatchedMinRows = 2048;
+// one token: everything up to the down projection
+void launch_step1(lif_layer* L, StepArgs a, hipStream_t s) {
+    const lif_config& c = L->cfg;
+    const bool gate = c.predictor == LIF_PRED_GATE;
+    // predictor workgroups: one per 64 neurons (32 with the gate predictor), and enough for the columns of A
+    a.n_pred = gate ? 2 * a.ring_words : std::max(a.ring_words, (c.rank + 3) / 4);
+    a.spec = L->expected_rows > 0 ? 1 : 0;
+    const int grid = a.n_pred + 1 + a.n_load + up_blocks(L);
+    if (c.dtype == LIF_F32) (gate ? launch_step1_f32_gate : c.glu ? launch_step1_f32_glu : launch_step1_f32_plain)(a, grid, s);
+    else (gate ? launch_step1_f16_gate : c.glu ? launch_step1_f16_glu : launch_step1_f16_plain)(a, grid, s);
+}
 
 bool mfma_path(const lif_config& c, int batch) {
     return c.dtype == LIF_F16 && batch > 1 && c.d_model % 32 == 0;
@@ -390,42 +420,46 @@ int mfma_hint_tiles(const lif_layer* L) {
     return std::max(1, std::min(tiles, (L->expected_rows + 15) / 16));
 }
 
-template <int MODE>
-void launch_ffn_up_mfma(lif_layer* L, const void* x, int batch, float* h, hipStream_t s) {
+// several tokens, the predictor's launches done: window, load and activations (allow: see launch_step_batch_as)
+hipError_t launch_step_batch(lif_layer* L, StepArgs a, bool allow, hipStream_t s) {
     const lif_config& c = L->cfg;
-    constexpr int W = (MODE == kRowsChanged) ? kMfmaWavesFix : kMfmaWavesAll;
-    // the rows a load wrote are few: a small grid strides over their tiles
-    const int tiles = (c.capacity_rows + 15) / 16;
-    // all rows: with a row-count hint the grid is sized to it (a workgroup strides on if more rows are in use)
-    // and every workgroup asks for its first rows before the count arrives
-    const int spec = (MODE == kRowsAll && L->expected_rows > 0) ? 1 : 0;
-    const int grid = (MODE == kRowsChanged) ? std::min(tiles, 64) : spec ? mfma_hint_tiles(L) : tiles;
-    if (c.glu)
-        hipLaunchKernelGGL((k_ffn_up_mfma<true, MODE, W>), dim3(grid), dim3(W * 64), 0, s,
-                           (const _Float16*)L->buf.matrix, L->buf.bias, (const _Float16*)x, h, c.d_model, batch,
-                           c.capacity_rows, L->row_elems, L->move_dst, L->buf.pointers, L->gact, c.d_ffn, spec, L->st);
-    else
-        hipLaunchKernelGGL((k_ffn_up_mfma<false, MODE, W>), dim3(grid), dim3(W * 64), 0, s,
-                           (const _Float16*)L->buf.matrix, L->buf.bias, (const _Float16*)x, h, c.d_model, batch,
-                           c.capacity_rows, L->row_elems, L->move_dst, L->buf.pointers, L->gact, c.d_ffn, spec, L->st);
+    const bool mfma = mfma_path(c, 2);
+    a.x_pitch = step_x_pitch(c.d_model, elem_bytes(c));
+    // (one row always fits)
+    a.stage_rows = 2;
+    size_t lds = step_batch_lds(a.batch, c.d_model, elem_bytes(c), c.glu, mfma, 2);
+    if (lds > kStepLdsLimit) {
+        a.stage_rows = 1;
+        lds = step_batch_lds(a.batch, c.d_model, elem_bytes(c), c.glu, mfma, 1);
+    }
+    int up;
+    if (mfma) {
+        up = (c.capacity_rows + 15) / 16;
+        a.spec = L->expected_rows > 0 ? mfma_hint_tiles(L) : 0;
+    } else {
+        up = up_blocks(L);
+        a.spec = L->expected_rows > 0 ? 1 : 0;
+    }
+    const int grid = 1 + a.n_load + up;
+    if (c.dtype == LIF_F32) return (c.glu ? launch_step_batch_f32_glu : launch_step_batch_f32)(a, grid, lds, allow, s);
+    if (mfma) return (c.glu ? launch_step_batch_f16_mfma_glu : launch_step_batch_f16_mfma)(a, grid, lds, allow, s);
+    return (c.glu ? launch_step_batch_f16_glu : launch_step_batch_f16)(a, grid, lds, allow, s);
 }
 
-// batch > 1, fp16: bundle load next to the activation stage of the surviving rows, then the rows the load wrote
-void launch_load_up_mfma(lif_layer* L, const void* x, int batch, const int32_t* added, hipStream_t s) {
+void launch_ffn_up_mfma(lif_layer* L, const void* x, int batch, float* h, hipStream_t s) {
     const lif_config& c = L->cfg;
-    const int tiles = (c.capacity_rows + 15) / 16;
-    static_assert(kMfmaWaves == 4, "the fused kernel runs both roles with 256 threads");
-    const int spec_tiles = L->expected_rows > 0 ? mfma_hint_tiles(L) : 0;
-    if (c.glu)
-        hipLaunchKernelGGL((k_load_up_mfma<true>), dim3(kLoadGrid + tiles), dim3(256), 0, s, (_Float16*)L->buf.matrix,
-                           L->buf.pointers, L->buf.bias, L->host, L->buf.b, added, L->move_dst, L->row_bytes,
-                           c.d_ffn, (const _Float16*)x, L->h, c.d_model, batch, c.capacity_rows, kLoadGrid, spec_tiles,
-                           L->gact, L->st);
-    else
-        hipLaunchKernelGGL((k_load_up_mfma<false>), dim3(kLoadGrid + tiles), dim3(256), 0, s, (_Float16*)L->buf.matrix,
-                           L->buf.pointers, L->buf.bias, L->host, L->buf.b, added, L->move_dst, L->row_bytes,
-                           c.d_ffn, (const _Float16*)x, L->h, c.d_model, batch, c.capacity_rows, kLoadGrid, spec_tiles,
-                           L->gact, L->st);
+    constexpr int W = kMfmaWavesAll;
+    // with a row-count hint the grid is sized to it (a workgroup strides on if more rows are in use) and every
+    // workgroup asks for its first rows before the count arrives
+    const int spec = L->expected_rows > 0 ? 1 : 0;
+    const int grid = spec ? mfma_hint_tiles(L) : (c.capacity_rows + 15) / 16;
+#define LIF_UM(GLU)                                                                                          \
+    hipLaunchKernelGGL((k_ffn_up_mfma<GLU, W>), dim3(grid), dim3(W * 64), 0, s, (const _Float16*)L->buf.matrix,  \
+                       L->buf.bias, (const _Float16*)x, h, c.d_model, batch, c.capacity_rows, L->row_elems,        \
+                       L->buf.pointers, L->gact, c.d_ffn, spec, L->st)
+    if (c.glu) LIF_UM(true);
+    else LIF_UM(false);
+#undef LIF_UM
 }
 
 // LDS a workgroup of k_predict_mask<T, BT> needs for a predictor of rank r: its static arrays plus BT * r doubles.
@@ -653,6 +687,13 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
             return rc;
         }
     }
+    if (cfg->max_batch > 1) {
+        hipError_t e = launch_step_batch(L, StepArgs{}, true, nullptr);
+        if (e != hipSuccess) {
+            delete L;
+            return fail(LIF_HIP_ERROR, "LDS of the batched step: %s", hipGetErrorString(e));
+        }
+    }
     *out = L;
     return LIF_OK;
 }
@@ -780,7 +821,7 @@ static int ffn_launches(lif_layer* L, const void* x_dev, int32_t batch, void* y_
     if (mfma_path(c, batch)) {
         // batched tokens: the activation stage is a dense contraction -> matrix cores
         Timed t(L, LIF_K_FFN_UP, s);
-        launch_ffn_up_mfma<kRowsAll>(L, x_dev, batch, h, s);
+        launch_ffn_up_mfma(L, x_dev, batch, h, s);
     } else {
         Timed t(L, LIF_K_FFN_UP, s);
         if (c.dtype == LIF_F32) {
@@ -838,41 +879,33 @@ static int step_impl(lif_layer* L, const void* x_dev, int32_t batch, int32_t kee
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     const lif_config& c = L->cfg;
-    if (batch == 1 && keep != 0) {
-        {
-            Timed t(L, LIF_K_LOAD, s);
-            launch_step1(L, x_dev, masks_dev, step_mask_dev, added_dev, n_added_dev, removed_dev, n_removed_dev, s);
-        }
-        Timed t(L, LIF_K_FFN_DOWN, s);
-        if (c.dtype == LIF_F32) launch_ffn_down<float>(L, 1, y_dev, L->h, L->ypart, s, true);
-        else launch_ffn_down<_Float16>(L, 1, y_dev, L->h, L->ypart, s, true);
-        return check_launch();
+    // (a pass of one token that is not kept: the token-granular update by itself)
+    if (batch == 1 && keep == 0) {
+        rc = lif_predict(L, x_dev, batch, masks_dev, step_mask_dev, stream);
+        if (!rc) rc = lif_update_window_tokens(L, masks_dev, batch, keep, added_dev, n_added_dev, removed_dev, n_removed_dev, stream);
+        if (!rc) rc = lif_load_bundles(L, added_dev, n_added_dev, removed_dev, n_removed_dev, stream);
+        return rc ? rc : lif_sparse_ffn(L, x_dev, batch, y_dev, stream);
     }
-    rc = lif_predict(L, x_dev, batch, masks_dev, step_mask_dev, stream);
-    if (rc) return rc;
-    rc = keep < 0 ? lif_update_window(L, step_mask_dev, added_dev, n_added_dev, removed_dev, n_removed_dev, stream)
-                  : lif_update_window_tokens(L, masks_dev, batch, keep, added_dev, n_added_dev, removed_dev,
-                                             n_removed_dev, stream);
-    if (rc) return rc;
-    // sharing a launch between the load and the activation stage pays once the activation stage over
-    // all rows takes longer than the second pass over the rows the load wrote (about 2000 rows in use)
-    const int rows_hint = L->expected_rows > 0 ? L->expected_rows : c.capacity_rows;
-    if (!mfma_path(c, batch) || rows_hint < kFuseBatchedMinRows) {
-        rc = lif_load_bundles(L, added_dev, n_added_dev, removed_dev, n_removed_dev, stream);
+    StepArgs a = step_args(L, x_dev, masks_dev, step_mask_dev, added_dev, n_added_dev, removed_dev, n_removed_dev, batch);
+    FusedCall fc;
+    fc.on = true;
+    if (batch > 1) {
+        if (keep >= 0) {
+            a.multi = fc.pass = true;
+            a.keep = fc.keep = keep;
+            fc.masks = masks_dev;
+        }
+        rc = lif_predict(L, x_dev, batch, masks_dev, step_mask_dev, stream);
         if (rc) return rc;
-        return lif_sparse_ffn(L, x_dev, batch, y_dev, stream);
     }
     {
         Timed t(L, LIF_K_LOAD, s);
-        launch_load_up_mfma(L, x_dev, batch, added_dev, s);
-    }
-    L->window_pending = false;
-    {
-        Timed t(L, LIF_K_FFN_UP, s);
-        launch_ffn_up_mfma<kRowsChanged>(L, x_dev, batch, L->h, s);
+        if (batch == 1) launch_step1(L, a, s);
+        else LIF_HIP(launch_step_batch(L, a, false, s));
     }
     Timed t(L, LIF_K_FFN_DOWN, s);
-    launch_ffn_down<_Float16>(L, batch, y_dev, L->h, L->ypart, s);
+    if (c.dtype == LIF_F32) launch_ffn_down<float>(L, batch, y_dev, L->h, L->ypart, s, fc);
+    else launch_ffn_down<_Float16>(L, batch, y_dev, L->h, L->ypart, s, fc);
     return check_launch();
 }
 

@@ -14,6 +14,7 @@
 #pragma once
 
 #include "lif_common.h"
+#include "lif_window_bits.h"
 
 namespace lif {
 
@@ -170,6 +171,57 @@ __global__ __launch_bounds__(256) void k_ffn_up(const T* __restrict__ matrix, co
                                   &st->cur.num_used, pointers, gact, gact_n, st);
 }
 
+// After a fused step (k_step1, k_step_batch): the activations, slot owners and biases of the rows that it wrote, valid for the slots
+// whose stamp is the number of that step.  All null otherwise.
+struct FusedRows {
+    const float* h_new;
+    const int32_t* stamp;
+    const int32_t* ptr_new;
+    const float* bias_new;
+    int32_t* pointers;               // where they are committed to
+    float* bias;
+    // a pass of several tokens: the masks of the first `keep` go into the ring
+    const uint8_t* masks;            // [tokens x F / 8], null: the ring is up to date
+    unsigned long long* ring;
+    int ring_words, nbytes, k, keep;
+};
+
+// The end of a fused step, by one workgroup: counts, slot owners and biases.  The other workgroups of the launch read
+// st->next and not what is written here.
+template <int THREADS>
+__device__ __forceinline__ void commit_step(const FusedRows& f, int capacity, DevState* st) {
+    constexpr int PER = 4;
+    const StepCounts nx = st->next;
+    if (threadIdx.x == 0) st->cur = nx;
+    if (nx.error) return;
+    if (f.masks) {
+        const int pos = nx.ring_pos - f.keep;                    // entry of the first kept token, modulo k
+        for (int i = max(0, f.keep - f.k); i < f.keep; ++i) {
+            unsigned long long* to = f.ring + (size_t)((((pos + i) % f.k) + f.k) % f.k) * f.ring_words;
+            for (int w = threadIdx.x; w * 8 < f.nbytes; w += THREADS) to[w] = load_mask_word(f.masks + (size_t)i * f.nbytes, w, f.nbytes);
+        }
+    }
+    for (int s0 = threadIdx.x; s0 < nx.num_used; s0 += PER * THREADS) {
+        int stamp[PER], p[PER];
+        float b[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int s = min(s0 + q * THREADS, capacity - 1);
+            stamp[q] = f.stamp[s];
+            p[q] = f.ptr_new[s];
+            b[q] = f.bias_new[s];
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int s = s0 + q * THREADS;
+            if (s < nx.num_used && stamp[q] == nx.step) {
+                f.pointers[s] = p[q];
+                f.bias[s] = b[q];
+            }
+        }
+    }
+}
+
 constexpr int kUpMaxWgs = 1024;   // workgroups of the activation stage: beyond this, waves loop over rows (x stays in registers)
 
 constexpr int kXcds = 8;            // accelerator complex dies of an MI355X, each with a private L2
@@ -199,9 +251,9 @@ __host__ __device__ __forceinline__ int down_chunks(int n) {
 // them to ypart[chunk][token][d] (fp32) and k_ffn_down_finish adds them in the same order.  No atomics.
 template <typename T, int BT, bool SKIP, int LANES>
 __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, const float* __restrict__ h,
-                                                  T* __restrict__ y, float* __restrict__ ypart, int d, int batch,
-                                                  int capacity, size_t row_elems, int down_off,
-                                                  DevState* __restrict__ st) {
+                                                  const FusedRows fused, T* __restrict__ y,
+                                                  float* __restrict__ ypart, int d, int batch, int capacity,
+                                                  size_t row_elems, int down_off, int slices, DevState* __restrict__ st) {
     static_assert(BT > 1, "single tokens: k_ffn_down1");
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N;
@@ -215,6 +267,12 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     __shared__ float red[4][LANES][BT * VE];
     __shared__ int n_active;
 
+    if ((int)blockIdx.x == slices) {                 // (only after a fused step)
+        if (blockIdx.y == 0) commit_step<256>(fused, capacity, st);
+        return;
+    }
+    const float* __restrict__ h_new = fused.h_new;
+    const int32_t* __restrict__ stamp = fused.stamp;
     const int tid = threadIdx.x, l = tid & (LANES - 1), rg = tid / LANES;
     const int slice = blockIdx.x;
     const int col = slice * (LANES * VE) + l * VE;
@@ -226,22 +284,31 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     // (the activation array spans the whole capacity, so the addresses are valid; values past
     // num_used are masked below): one memory round trip less on the critical path
     const bool first_row = blockIdx.y == 0;
-    float hfirst[PER][BT];
+    float hfirst[PER][BT], hnfirst[PER][BT];
+    int sfirst[PER];
 #pragma unroll
-    for (int q = 0; q < PER; ++q)
+    for (int q = 0; q < PER; ++q) {
+        sfirst[q] = -1;
 #pragma unroll
-        for (int b = 0; b < BT; ++b) hfirst[q][b] = 0.f;
+        for (int b = 0; b < BT; ++b) hfirst[q][b] = hnfirst[q][b] = 0.f;
+    }
     if (first_row) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (stamp) sfirst[q] = stamp[min(q * 256 + tid, capacity - 1)];
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (b < batch) {
 #pragma unroll
-                for (int q = 0; q < PER; ++q) hfirst[q][b] = h[(size_t)b * capacity + min(q * 256 + tid, capacity - 1)];
+                for (int q = 0; q < PER; ++q) {
+                    hfirst[q][b] = h[(size_t)b * capacity + min(q * 256 + tid, capacity - 1)];
+                    if (stamp) hnfirst[q][b] = h_new[(size_t)b * capacity + min(q * 256 + tid, capacity - 1)];
+                }
             }
         }
     }
-    const int err = st->cur.error;
-    const int n = err ? 0 : st->cur.num_used;
+    const StepCounts* counts = stamp ? &st->next : &st->cur;
+    const int err = counts->error, n = counts->num_used, cur_step = counts->step;
     if (err) return;
     const int chunks = down_chunks(n);
     if ((int)blockIdx.y >= chunks) return;           // uniform
@@ -267,12 +334,15 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
             for (int q = 0; q < PER; ++q) {
                 const int s = s_base + q * 256 + tid;
                 bool any = false;
+                const bool ahead = s_base == 0;              // only chunk 0 (first workgroup row) starts at row 0
+                const bool fresh = stamp && (ahead ? sfirst[q] : s < r1 ? stamp[s] : -1) == cur_step;
+                const float* from = fresh ? h_new : h;
 #pragma unroll
                 for (int b = 0; b < BT; ++b) {
                     float v = 0.f;
                     if (s < r1 && b < batch) {
-                        if (s_base == 0) v = hfirst[q][b];       // only chunk 0 (first workgroup row) starts at row 0
-                        else v = h[(size_t)b * capacity + s];
+                        if (ahead) v = fresh ? hnfirst[q][b] : hfirst[q][b];
+                        else v = from[(size_t)b * capacity + s];
                     }
                     hloc[q][b] = v;
                     any |= (v != 0.f);

@@ -40,46 +40,6 @@ __host__ __device__ __forceinline__ int down1_chunks(int n) {
 // the result does not depend on the launch geometry.
 __host__ __device__ __forceinline__ int down1_waves(int n) { return n <= kDown1FewRows ? 8 : 16; }
 
-// After a fused step (k_step1): the activations, slot owners and biases of the rows that it wrote, valid for the slots
-// whose stamp is the number of that step.  All null otherwise.
-struct FusedRows {
-    const float* h_new;
-    const int32_t* stamp;
-    const int32_t* ptr_new;
-    const float* bias_new;
-    int32_t* pointers;               // where they are committed to
-    float* bias;
-};
-
-// The end of a fused step, by one workgroup: counts, slot owners and biases.  The other workgroups of the launch read
-// st->next and not what is written here.
-template <int THREADS>
-__device__ __forceinline__ void commit_step(const FusedRows& f, int capacity, DevState* st) {
-    constexpr int PER = 4;
-    const StepCounts nx = st->next;
-    if (threadIdx.x == 0) st->cur = nx;
-    if (nx.error) return;
-    for (int s0 = threadIdx.x; s0 < nx.num_used; s0 += PER * THREADS) {
-        int stamp[PER], p[PER];
-        float b[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int s = min(s0 + q * THREADS, capacity - 1);
-            stamp[q] = f.stamp[s];
-            p[q] = f.ptr_new[s];
-            b[q] = f.bias_new[s];
-        }
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int s = s0 + q * THREADS;
-            if (s < nx.num_used && stamp[q] == nx.step) {
-                f.pointers[s] = p[q];
-                f.bias[s] = b[q];
-            }
-        }
-    }
-}
-
 // grid = (column slices of 64 bytes, rounded up to a multiple of 8, + 1 after a fused step: the workgroup that commits
 // it; row-chunk workgroups), block = WAVES * 64.
 // gact (may be null): the activations in h and h_new are up . x alone and are multiplied with the gate activation of the

@@ -53,10 +53,10 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // the launch geometry.
 template <bool SKIP, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __restrict__ matrix,
-                                                              const float* __restrict__ h, _Float16* __restrict__ y,
-                                                              float* __restrict__ ypart, int d, int batch, int capacity,
-                                                              size_t row_elems, int down_off, int chunk_rows,
-                                                              DevState* __restrict__ st) {
+                                                              const float* __restrict__ h, const FusedRows fused,
+                                                              _Float16* __restrict__ y, float* __restrict__ ypart, int d,
+                                                              int batch, int capacity, size_t row_elems, int down_off,
+                                                              int chunk_rows, int slices, DevState* __restrict__ st) {
     constexpr int BT = 8, T = WAVES * 64;
     constexpr int PER = kDmRows / T;                 // slots per thread in the compaction
     constexpr int OUTS = BT * kDmCols / T;           // outputs per thread
@@ -68,6 +68,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
     __shared__ float red[WAVES][32][33];             // per wave and lane with q < 2: 32 sums, padded
     __shared__ int n_active;
 
+    if ((int)blockIdx.x == slices) {                 // (only after a fused step)
+        if (blockIdx.y == 0) commit_step<WAVES * 64>(fused, capacity, st);
+        return;
+    }
+    const float* __restrict__ h_new = fused.h_new;
+    const int32_t* __restrict__ stamp = fused.stamp;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, q = lane >> 4;
     const int col = blockIdx.x * kDmCols + n16 * 8;
@@ -76,15 +82,20 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
 
     if (tid == 0) n_active = 0;
     // the activations of the first pass are requested before the row count is known (the array spans the capacity)
-    float hfirst[PER][BT];
+    float hfirst[PER][BT], hnfirst[PER][BT];
+    int sfirst[PER];
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
         const int s = blockIdx.y * chunk_rows + p * T + tid;
+        sfirst[p] = (stamp && s < capacity) ? stamp[s] : -1;
 #pragma unroll
-        for (int b = 0; b < BT; ++b) hfirst[p][b] = (s < capacity && b < batch) ? h[(size_t)b * capacity + s] : 0.f;
+        for (int b = 0; b < BT; ++b) {
+            hfirst[p][b] = (s < capacity && b < batch) ? h[(size_t)b * capacity + s] : 0.f;
+            hnfirst[p][b] = (stamp && s < capacity && b < batch) ? h_new[(size_t)b * capacity + s] : 0.f;
+        }
     }
-    const int err = st->cur.error;
-    const int n = err ? 0 : st->cur.num_used;
+    const StepCounts* counts = stamp ? &st->next : &st->cur;
+    const int err = counts->error, n = counts->num_used, cur_step = counts->step;
     if (err) return;
     const int chunks = down_mfma_chunks(n, chunk_rows);
     if ((int)blockIdx.y >= chunks) return;           // uniform
@@ -110,10 +121,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
             for (int p = 0; p < PER; ++p) {
                 const int s = s_base + p * T + tid;
                 bool any = false;
+                const bool fresh = stamp && (spec ? sfirst[p] : s < r1 ? stamp[s] : -1) == cur_step;
+                const float* from = fresh ? h_new : h;
 #pragma unroll
                 for (int b = 0; b < BT; ++b) {
                     float v = 0.f;
-                    if (s < r1 && b < batch) v = spec ? hfirst[p][b] : h[(size_t)b * capacity + s];
+                    if (s < r1 && b < batch) v = !spec ? from[(size_t)b * capacity + s] : fresh ? hnfirst[p][b] : hfirst[p][b];
                     hloc[p][b] = v;
                     any |= (v != 0.f);
                     amax = fmaxf(amax, fabsf(v));

@@ -32,6 +32,7 @@
 #pragma once
 
 #include "lif_ffn.h"
+#include "lif_ffn_mfma.h"
 #include "lif_predict.h"
 #include "lif_window_bits.h"
 
@@ -42,7 +43,7 @@ constexpr int kWordReps = 8;         // copies of every word: hundreds of workgr
 __host__ __device__ __forceinline__ int words_pitch(int n) { return (n + 31) / 32 * 32 + 32; }
 constexpr int kListItems = 2048;     // work items listed at a time
 
-struct Step1Args {
+struct StepArgs {
     // predictor
     const void* A;                   // [rank x d], or the gate projection [F x d]
     const void* B;
@@ -75,6 +76,10 @@ struct Step1Args {
     int32_t* stamp;                  // step in which h_new, ptr_new and bias_new of a slot were written
     int32_t* ptr_new;
     float* bias_new;
+    int batch;                       // tokens of the step; with several of them:
+    int keep, multi;                 // ring entries the step fills; 1: a pass of tokens, whose masks the commit writes there
+    int x_pitch;                     // bytes between the tokens' x in LDS
+    int stage_rows;                  // rows of activation vectors a loader workgroup has room for in LDS (1, 2)
     int spec;                        // the activation role requests its first rows ahead of the row count
     int n_pred, n_load;
     int polls;
@@ -144,7 +149,7 @@ __device__ __forceinline__ double column_dot_slow(const T* col, const T* x, int 
 }
 // t computed by this workgroup alone (a wait that ran out)
 template <typename T>
-__device__ __forceinline__ void own_t(const Step1Args& a, PredictLds& L) {
+__device__ __forceinline__ void own_t(const StepArgs& a, PredictLds& L) {
     const int lane = threadIdx.x & 63;
 #pragma unroll 1
     for (int j = threadIdx.x >> 6; j < a.rank; j += 4) {
@@ -164,7 +169,7 @@ struct MaskTile {
     double bd[kMaskRows][8];
     float cv[8];
     int n0;
-    __device__ __forceinline__ void request(const Step1Args& a, int tile) {
+    __device__ __forceinline__ void request(const StepArgs& a, int tile) {
         const int tid = threadIdx.x, cl = tid & (kMaskCols - 1), jg = tid >> 3;
         n0 = (tile * kMaskCols + cl) * 8;
         const T* B = (const T*)a.B;
@@ -190,7 +195,7 @@ struct MaskTile {
     }
     // mask byte of neurons n0 .. n0 + 7 in the threads tid < kMaskCols (0 past the last neuron); one barrier
     template <bool WIDE>
-    __device__ __forceinline__ unsigned finish(const Step1Args& a, PredictLds& L) {
+    __device__ __forceinline__ unsigned finish(const StepArgs& a, PredictLds& L) {
         const int tid = threadIdx.x, wave = tid >> 6, cl = tid & (kMaskCols - 1), jg = tid >> 3;
         const T* B = (const T*)a.B;
         double v[8];
@@ -246,7 +251,7 @@ struct MaskTile {
 };
 
 template <typename T, int NI>
-__device__ __forceinline__ void lowrank_role(const Step1Args& a, int block, PredictLds& L) {
+__device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, PredictLds& L) {
     using V = typename Vec<T>::type;
     const int tid = threadIdx.x, lane = tid & 63, nvec = a.d / Vec<T>::N;
     const int j = block * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -299,7 +304,7 @@ __device__ __forceinline__ void lowrank_role(const Step1Args& a, int block, Pred
 
 // Gate predictor: relu(gate_i . x + b_i) and the mask bit of 8 neurons per wave, as k_predict_gate for one token.
 template <typename T, int NI>
-__device__ __forceinline__ unsigned gate_byte(const Step1Args& a, int grp, const typename Vec<T>::type (&xr)[NI]) {
+__device__ __forceinline__ unsigned gate_byte(const StepArgs& a, int grp, const typename Vec<T>::type (&xr)[NI]) {
     using V = typename Vec<T>::type;
     const int lane = threadIdx.x & 63, nvec = a.d / Vec<T>::N;
     const double th = (double)a.theta;
@@ -316,7 +321,7 @@ __device__ __forceinline__ unsigned gate_byte(const Step1Args& a, int grp, const
     return bits;
 }
 template <typename T, int NI>
-__device__ __forceinline__ void gate_role(const Step1Args& a, int block, unsigned* lds) {
+__device__ __forceinline__ void gate_role(const StepArgs& a, int block, unsigned* lds) {
     using V = typename Vec<T>::type;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     V xr[NI];
@@ -344,18 +349,19 @@ constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ?
 // ---- window, deletion plan, loaders ----------------------------------------------------------------------------
 
 constexpr int kPtrLds = 4096;        // slot owners staged in LDS
+constexpr int kNoDst = 0xffff;       // dead tail slot (a hole lies below n' <= 65535, so it is never slot 65535)
 constexpr int kHoleFew = 2048;       // holes kept in LDS; longer lists go to the global scratch list
 struct PlanLds {
     unsigned long long rem[1024], add[1024]; // removed and added neurons, one bit each
     union {
         PredictLds predict;                  // only when a wait ran out
         struct {
-            int ids[kListItems], dst[kListItems];    // work items: new neuron, destination of the tail row
-            int hole[kHoleFew];
+            uint16_t ids[kListItems], dst[kListItems];       // work items: new neuron, destination of the tail row (kNoDst)
+            uint16_t hole[kHoleFew];
             uint16_t blk_h[1024], blk_f[1024];       // per 64-slot block: counts, then exclusive prefixes
         };
     };
-    int ptr[kPtrLds];
+    uint16_t ptr[kPtrLds];                   // (of the slots in use: neurons are numbers below 65536)
     unsigned long long wave_tot[4];
     int cnt_age[264];
     unsigned byte[4];
@@ -366,7 +372,7 @@ struct PlanLds {
 
 // All mask words computed by this workgroup alone (a wait that ran out): m[i] of the words this thread owns
 template <typename T, bool GATE>
-__device__ __forceinline__ void own_masks(const Step1Args& a, PlanLds& L, int wpt, unsigned long long (&m)[4]) {
+__device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt, unsigned long long (&m)[4]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nwords = (a.F + 63) >> 6;
     if constexpr (!GATE) own_t<T>(a, L.predict);
@@ -418,15 +424,39 @@ __device__ __forceinline__ void own_masks(const Step1Args& a, PlanLds& L, int wp
 //               writes the bundle part to slot s, and requests the next unit before it finishes the current one.  The L1
 //               of a compute unit returns loads in order over all its waves, so a load of device memory behind host
 //               reads takes as long as they do (2 to 5 us): the tail row is requested just behind the bundle (ahead of
-//               it, it would hold back the host read), and the loaders are spread over compute units (four loading waves per workgroup moved 35 GB/s where one
-//               moves 50).  The units of a round are dealt to the workgroups one place further each round, so that all
+//               it, it would hold back the host read), and the loaders are spread over compute units (four
+//               loading waves per workgroup moved 35 GB/s where one moves 50).  The units of a round are dealt to the workgroups one place further each round, so that all
 //               get as many activation parts as down parts (a counter drawn from by atomics balanced no better, and the
 //               wait for its answer cost 1.5 us per unit; with all activation parts first, rows of 16 KiB loaded a
 //               quarter slower, all reads falling on the same half of every row);
-//   waves 1..3  make the deletion plan meanwhile (LDS only), then move the tail rows that nothing overwrites (more neurons removed than added).
+//   waves 1..3  make the deletion plan meanwhile (LDS only), then move the tail rows that nothing overwrites (more
+//               neurons removed than added; with several tokens one wave does).
 // Lane l holds the same 16-byte pieces of every vector as in the activation role and sums in the same order.
-template <typename T, int NI, bool GLU, bool GATE>
-__device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& L) {
+//
+// Several tokens (MODE kDots, kMfma): the masks were written by the launch before this one and x lies in LDS.  Wave 0 puts the
+// activation vectors of the rows it writes (new, moved) into LDS and posts them there; waves 1..3 compute the activations
+// while its next bundle is on its way, kDots as in ffn_up_role with the tokens dealt to the waves, kMfma with the matrix
+// instruction and the order of ffn_up_mfma_tile_staged (the vectors of both rows are rows of one operand; the parts of the k
+// range are dealt to the waves).  One wave alone took 6 us per bundle of 24 KiB and 8 tokens, as long as the link.
+enum StepMode { kOneToken = 0, kDots = 1, kMfma = 2 };
+
+// LDS behind PlanLds: PostLds, x of the tokens, the activation vectors of `stage_rows` rows
+struct Slot {                                                // a row that was written
+    int s, id;
+    float bias;
+};
+struct PostLds {
+    int seq, done, arrived;                                  // posts so far; waves that have finished, delivered their sums
+    int rows;                                                // of this post (0: the last one)
+    Slot slot[2];
+    float gate[2][8];                                        // resident gate activations, per token
+    alignas(16) float sums[8][16][4];                        // kMfma: sums of parts 2 g and 2 g + 1, per token and vector
+};
+constexpr int kStepXOff = (int)((sizeof(PlanLds) + 15) / 16 * 16 + (sizeof(PostLds) + 15) / 16 * 16);
+__host__ __device__ __forceinline__ int step_x_pitch(int d, int elem) { return d * elem + 16; }     // (16: the reads of 16 tokens
+                                                                                                     //  fall on different banks)
+template <typename T, int NI, bool GLU, bool GATE, int MODE>
+__device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L, PostLds* post, unsigned char* lds_x) {
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N;
     constexpr bool PAIRED = NI > 2;
@@ -443,7 +473,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
 #pragma unroll
         for (int q = 0; q < kPtrLds / 256; ++q) id[q] = (q * 256 + tid < capacity) ? a.pointers[q * 256 + tid] : -1;
 #pragma unroll
-        for (int q = 0; q < kPtrLds / 256; ++q) L.ptr[q * 256 + tid] = id[q];
+        for (int q = 0; q < kPtrLds / 256; ++q) L.ptr[q * 256 + tid] = (uint16_t)id[q];
     };
     stage_owners();
     const StepCounts cur = st->cur;
@@ -458,7 +488,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
         return;
     }
     const unsigned stamp_now = (unsigned)cur.step + 1u;
-    const int n = cur.num_used, slot_now = cur.ring_pos % k, oldest = min(cur.window_len, k - 1);
+    const int n = cur.num_used, slot_now = cur.ring_pos % k, oldest = min(cur.window_len, k - a.keep);      // largest age that stays in the window
     unsigned long long prev[4], keep[4], m[4], now[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) prev[i] = keep[i] = m[i] = 0ull;
@@ -501,7 +531,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
         for (int i = 0; i < wpt; ++i) {
             unsigned long long bits = L.add[tid * wpt + i];
             while (bits) {
-                if ((unsigned)q < (unsigned)kListItems) L.ids[q] = (tid * wpt + i) * 64 + __ffsll((long long)bits) - 1;
+                if ((unsigned)q < (unsigned)kListItems) L.ids[q] = (uint16_t)((tid * wpt + i) * 64 + __ffsll((long long)bits) - 1);
                 bits &= bits - 1;
                 ++q;
             }
@@ -583,7 +613,24 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
     };
 
     // ---- masks -> window -> id list -> first host read ----
-    {
+    const int x_pieces = nvec * a.batch;
+    V xs[MODE == kOneToken ? 1 : 16];
+    if constexpr (MODE != kOneToken) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int w = tid * wpt + i;
+            if (i < wpt && w < nwords) m[i] = load_mask_word(a.step_mask, w, F >> 3);
+        }
+        // x of the tokens (at most 64 KiB) is requested here and stored behind the first host read
+        if (wg > 0) {
+#pragma unroll
+            for (int g = 0; g < 16; g += 4)
+                if (g * 256 < x_pieces) {
+#pragma unroll
+                    for (int i = g; i < g + 4; ++i) xs[i] = reinterpret_cast<const V*>(a.x)[min(i * 256 + tid, x_pieces - 1)];
+                }
+        }
+    } else {
         unsigned p[8];
         const int w0 = tid * wpt, nw = max(0, min(wpt, nwords - w0));
         const bool ok = poll_words<8>(a.m_words + (size_t)(wg & (kWordReps - 1)) * a.m_pitch + 2 * w0, 1, 2 * nw, stamp_now,
@@ -598,16 +645,18 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
     diff();
     bool over = n - tot_r < 0 || n - tot_r + tot_a > capacity;
     if (over && a.shrink) {
-        // Dynamic window (see k_window_plan): U_a = union of the newest a masks; keep the largest a whose union fits.
+        // Dynamic window (see k_window_plan): what this step needs in any case (m) and the ring entries of ages 1 .. j, for the
+        // largest j for which they fit.
         auto age_word = [&](int age, int w) -> unsigned long long {
             return a.ring[(size_t)((slot_now - age + k) % k) * a.ring_words + w];
         };
-        for (int i = tid; i < k; i += 256) L.cnt_age[i] = 0;
+        const int ages = max(k - a.keep, 0);                      // L.cnt_age[j], j = 0 .. ages
+        for (int i = tid; i <= ages; i += 256) L.cnt_age[i] = 0;
         lds_barrier();
         unsigned long long u[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) u[i] = m[i];
-        for (int a0 = 1; a0 <= k; a0 += kRingRegs) {          // counts of U_a, a = a0 .. a0 + 7
+        for (int a0 = 0; a0 <= ages; a0 += kRingRegs) {           // counts for j = a0 .. a0 + 7
             int pc[kRingRegs];
 #pragma unroll
             for (int j = 0; j < kRingRegs; ++j) pc[j] = 0;
@@ -618,7 +667,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
                     unsigned long long e[kRingRegs];
 #pragma unroll
                     for (int j = 0; j < kRingRegs; ++j) {
-                        const int age = a0 + j - 1;
+                        const int age = a0 + j;
                         e[j] = (w < nwords && age >= 1 && age <= oldest) ? age_word(age, w) : 0ull;
                     }
 #pragma unroll
@@ -631,22 +680,23 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
 #pragma unroll
             for (int j = 0; j < kRingRegs; ++j) {
                 const int tot = __builtin_amdgcn_readlane(wave_inclusive_scan(pc[j], lane), kWave - 1);
-                if (lane == 0 && tot && a0 + j <= k) atomicAdd(&L.cnt_age[a0 + j - 1], tot);
+                if (lane == 0 && tot && a0 + j <= ages) atomicAdd(&L.cnt_age[a0 + j], tot);
             }
         }
         lds_barrier();
-        k_eff = 0;
-        for (int i = 1; i <= k; ++i)
-            if (L.cnt_age[i - 1] <= capacity) k_eff = i;
+        int fit = -1;
+        for (int j = 0; j <= ages; ++j)
+            if (L.cnt_age[j] <= capacity) fit = j;                // (the counts grow with j)
+        k_eff = a.keep + fit;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             now[i] = m[i];
             const int w = tid * wpt + i;
             if (i < wpt && w < nwords)
-                for (int a0 = 1; a0 < k_eff && a0 <= oldest; ++a0) now[i] |= age_word(a0, w);
+                for (int age = 1; age <= min(fit, oldest); ++age) now[i] |= age_word(age, w);
         }
         diff();
-        over = k_eff == 0 || n - tot_r < 0 || n - tot_r + tot_a > capacity;
+        over = fit < 0 || n - tot_r < 0 || n - tot_r + tot_a > capacity;
     }
     if (over) {                                      // uniform: leave everything untouched
         if (wg == 0 && tid == 0) {
@@ -669,6 +719,8 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
         }
     fill_ids(0);                                                 // (reads only what this thread has just written)
     if (tid == 0) L.planned = L.classified = 0;
+    if constexpr (MODE != kOneToken)
+        if (tid == 0) post->seq = post->done = post->arrived = 0;
     lds_barrier();
 
     // ---- deletion plan (see k_window_plan): holes = dead slots below n', fillers = live slots at or above it ----
@@ -716,7 +768,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
                 const unsigned long long bh = __ballot(hole);
                 if (hole) {
                     const int pos = L.blk_h[b] + __popcll(bh & lt);
-                    if (in_lds) L.hole[pos] = b * kWave + lane;
+                    if (in_lds) L.hole[pos] = (uint16_t)(b * kWave + lane);
                     else a.hole_list[pos] = b * kWave + lane;
                 }
             }
@@ -735,7 +787,12 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
             const int q = b * kWave + lane - n2;
             if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
                 const int r = H - 1 - (L.blk_f[b] + __popcll(bf & lt));
-                L.dst[q - c0] = (fill && r >= 0 && r < H) ? (in_lds ? L.hole[r] : a.hole_list[r]) : -1;
+                int dst = kNoDst;
+                if (fill && r >= 0 && r < H) {
+                    if (in_lds) dst = L.hole[r];
+                    else dst = a.hole_list[r];
+                }
+                L.dst[q - c0] = (uint16_t)dst;
             }
         }
     };
@@ -767,7 +824,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
         const int v = __popcll(mh) | (__popcll(mf) << 16), inc = wave_inclusive_scan(v, lane), ex = inc - v;
         const int holes = __builtin_amdgcn_readlane(inc, kWave - 1) & 0xffff;
         for (int pos = ex & 0xffff; __any(mh != 0ull); ++pos) {
-            if (mh) L.hole[min(pos, kHoleFew - 1)] = lane * kWave + __ffsll((long long)mh) - 1;
+            if (mh) L.hole[min(pos, kHoleFew - 1)] = (uint16_t)(lane * kWave + __ffsll((long long)mh) - 1);
             mh &= mh - 1;
         }
         // (at most half of 4096 rows can be holes: kHoleFew)
@@ -778,7 +835,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
             const int q = b * kWave + lane - n2;
             if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
                 const int r = holes - 1 - ((int)((unsigned)__builtin_amdgcn_readlane(ex, b) >> 16) + __popcll(bf & lt));
-                L.dst[q - c0] = (((bf >> lane) & 1ull) && r >= 0) ? L.hole[r] : -1;
+                L.dst[q - c0] = (((bf >> lane) & 1ull) && r >= 0) ? L.hole[r] : (uint16_t)kNoDst;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -789,7 +846,29 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
         lds_barrier();
     }
     if (loads && lw < (PAIRED ? 2 * tot_a : tot_a))              // unit lw (below kListItems)
-        request_host(__builtin_amdgcn_readfirstlane(L.ids[PAIRED ? lw >> 1 : lw]), PAIRED ? lw & 1 : 0);
+        request_host(__builtin_amdgcn_readfirstlane((int)L.ids[PAIRED ? lw >> 1 : lw]), PAIRED ? lw & 1 : 0);
+
+    if constexpr (MODE != kOneToken) {
+        if (wg > 0) {
+            int t = tid / nvec, p = tid - t * nvec;
+            const int dt = 256 / nvec, dp = 256 - dt * nvec;
+#pragma unroll
+            for (int g = 0; g < 16; g += 4)
+                if (g * 256 < x_pieces) {
+#pragma unroll
+                    for (int i = g; i < g + 4; ++i) {
+                        if (i * 256 + tid < x_pieces) reinterpret_cast<V*>(lds_x + t * a.x_pitch)[p] = xs[i];
+                        t += dt;
+                        p += dp;
+                        if (p >= nvec) {
+                            p -= nvec;
+                            ++t;
+                        }
+                    }
+                }
+            lds_barrier();
+        }
+    }
 
     if (wg == 0) {
         // ---- bookkeeping: window state, id lists, counts ----
@@ -798,7 +877,7 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
             const int w = tid * wpt + i;
             if (i < wpt && w < nwords) {
                 a.cur_set[(size_t)(cur.set_par ^ 1) * a.ring_words + w] = now[i];
-                a.ring[(size_t)slot_now * a.ring_words + w] = m[i];
+                if (!a.multi) a.ring[(size_t)slot_now * a.ring_words + w] = m[i];
             }
         }
         for (int i = 0; i < wpt; ++i) {
@@ -823,8 +902,8 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
             nx.n_added = tot_a;
             nx.n_removed = tot_r;
             nx.n_moved = H;
-            nx.window_len = min(min(cur.window_len + 1, k), k_eff);
-            nx.ring_pos = (cur.ring_pos + 1) % k;
+            nx.window_len = min(min(cur.window_len + a.keep, k), k_eff);
+            nx.ring_pos = (cur.ring_pos + a.keep) % k;
             nx.set_par = cur.set_par ^ 1;
             st->next = nx;
             atomicAdd(&st->c_steps, 1ull);
@@ -838,15 +917,21 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
 
     // ---- load and move ----
     const int new_step = cur.step + 1, nw = a.n_load;
-    V xr[NI];                                                    // (behind the first host read: needed once that has arrived)
-    if (wave == 0 || !alone) load_pieces(xr, (const char*)a.x);  // (the others have a plan to make first)
+    V xr[MODE == kOneToken ? NI : 1];                            // (behind the first host read: needed once that has arrived)
+    auto load_x = [&]() {
+        if constexpr (MODE == kOneToken) load_pieces(xr, (const char*)a.x);
+    };
+    if (wave == 0 || !alone) load_x();                           // (the others have a plan to make first)
     // What a slot becomes: the activation of a row, in the order of operations of the activation role
+    constexpr int GV = GLU ? 2 : 1;                              // vectors it needs
     auto partial_dots = [&](const V (&v)[GA][NI], float& pu, float& pg) {
         pu = pg = 0.f;
+        if constexpr (MODE == kOneToken) {
 #pragma unroll
-        for (int it = 0; it < NI; ++it) {
-            pu = dot_acc(v[GLU ? 1 : 0][it], xr[it], pu);
-            if (GLU) pg = dot_acc(v[0][it], xr[it], pg);
+            for (int it = 0; it < NI; ++it) {
+                pu = dot_acc(v[GLU ? 1 : 0][it], xr[it], pu);
+                if (GLU) pg = dot_acc(v[0][it], xr[it], pg);
+            }
         }
     };
     auto finish_slot = [&](int s, int id, float bs, float pu, float pg) {
@@ -861,6 +946,161 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
             a.h_new[s] = act;
             a.stamp[s] = new_step;
         }
+    };
+    // several tokens: wave 0 stages the rows of a unit and posts them, waves 1..3 compute
+    const int row_pitch = step_x_pitch(d, (int)sizeof(T));
+    const int in_lds = a.stage_rows;                             // rows there is room for: 2, or one after the other
+    unsigned char* lds_row = lds_x + a.batch * a.x_pitch;
+    int seq = 0;                                                 // posts so far
+    auto stage_row = [&](const V (&v)[GA][NI], int place) {
+        if constexpr (MODE != kOneToken) {
+            const unsigned off = lane_bytes();
+#pragma unroll
+            for (int g = 0; g < GV; ++g)
+#pragma unroll
+                for (int it = 0; it < NI; ++it)
+                    if (it < full_pieces(NI) || off + it * 1024u < (unsigned)vec_bytes)
+                        *reinterpret_cast<V*>(lds_row + (place * GV + g) * row_pitch + (off + it * 1024u)) = v[g][it];
+        }
+    };
+    auto await_done = [&]() {                                    // the rows of the post before have been used
+        if constexpr (MODE != kOneToken) {
+            while (__hip_atomic_load(&post->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < 3 * seq) __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        }
+    };
+    auto post_rows = [&](int rows, const Slot& r0, float g0, const Slot& r1, float g1) {        // g: lane t: of token t
+        if constexpr (MODE != kOneToken) {
+            if (lane == 0) {
+                post->rows = rows;
+                post->slot[0] = r0;
+                post->slot[1] = r1;
+            }
+            if (GATE && lane < 8) {
+                post->gate[0][lane] = g0;
+                post->gate[1][lane] = g1;
+            }
+            ++seq;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            if (lane == 0) __hip_atomic_store(&post->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
+    auto put = [&](int row, int t, float sg, float su) {         // activation of one row for token t
+        if constexpr (MODE != kOneToken) {
+            const Slot r = post->slot[row];
+            float act;
+            if (GLU) act = fmaxf(sg + r.bias, 0.f) * su;
+            else if (GATE) act = post->gate[row][t] * su;
+            else act = fmaxf(su + r.bias, 0.f);
+            a.h_new[(size_t)t * capacity + r.s] = act;
+            if (t == 0) {
+                a.ptr_new[r.s] = r.id;
+                a.bias_new[r.s] = r.bias;
+                a.stamp[r.s] = new_step;
+            }
+        }
+    };
+    // kMfma: parts 2 g and 2 g + 1 for the NG groups g = first, first + 3, ..., independent chains side by side
+    auto group_sums = [&](auto ng_c, int first, int rows) {
+        if constexpr (MODE == kMfma) {
+            constexpr int NP = 2 * decltype(ng_c)::value;
+            const int i16 = lane & 15, q = lane >> 4, nks = d >> 5, per = (nks + kMfmaParts - 1) / kMfmaParts;
+            const unsigned char* xl = lds_x + min(i16, a.batch - 1) * a.x_pitch + q * 16;       // (columns past the batch are not used)
+            const unsigned char* rl = lds_row + (i16 & (GV * rows - 1)) * row_pitch + q * 16;   // (nor rows past the vectors)
+            f32x4 acc[NP];
+            int k0[NP], cnt[NP];
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int part = 2 * (first + 3 * (p >> 1)) + (p & 1);
+                acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+                k0[p] = part * per;
+                cnt[p] = min(max(nks - part * per, 0), per);     // (does not grow with p)
+            }
+            auto step = [&](int ks, f32x4 v) {
+                return __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const f16x8*>(rl + ks * 64),
+                                                              *reinterpret_cast<const f16x8*>(xl + ks * 64), v, 0, 0, 0);
+            };
+#pragma unroll 1
+            for (int j = 0; j < cnt[NP - 1]; ++j)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) acc[p] = step(k0[p] + j, acc[p]);
+#pragma unroll
+            for (int p = 0; p < NP - 1; ++p)
+#pragma unroll 1
+                for (int j = cnt[NP - 1]; j < cnt[p]; ++j) acc[p] = step(k0[p] + j, acc[p]);
+#pragma unroll
+            for (int p = 0; p < NP; p += 2)
+                if (lane < 16) *reinterpret_cast<f32x4*>(post->sums[first + 3 * (p >> 1)][lane]) = acc[p] + acc[p + 1];   // D[v][t], v = 0..3
+        }
+    };
+    auto work = [&]() {                                          // waves 1..3, until wave 0 has posted its last rows
+        if constexpr (MODE != kOneToken) {
+            for (;;) {
+                ++seq;
+                while (__hip_atomic_load(&post->seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < seq) __builtin_amdgcn_s_sleep(1);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                const int rows = __builtin_amdgcn_readfirstlane(post->rows);
+                if constexpr (MODE == kMfma) {
+                    if (rows > 0) {
+                        if (wave < 3) group_sums(std::integral_constant<int, 3>{}, wave - 1, rows);
+                        else group_sums(std::integral_constant<int, 2>{}, 2, rows);
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                        int before = 0;
+                        if (lane == 0) before = __hip_atomic_fetch_add(&post->arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (__builtin_amdgcn_readfirstlane(before) % 3 == 2) {   // the last of the three
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                            // lane = 8 * vector + token; the tree over the groups as tree_push and tree_sum
+                            const int t = lane & 7, v = (lane >> 3) & (2 * GV - 1);
+                            float g8[8];
+#pragma unroll
+                            for (int g = 0; g < 8; ++g) g8[g] = post->sums[g][t][v];
+                            const float su = tree_sum<8>(g8), sg = GLU ? __shfl(su, lane - 8, kWave) : 0.f;
+                            if (lane < 16 * GV && t < a.batch && v % GV == GV - 1 && v / GV < rows) put(v / GV, t, sg, su);
+                        }
+                    }
+                } else if (rows > 0) {
+                    constexpr int TT = 3;                        // tokens of a wave, at most 8 in all
+                    float acc[TT][2 * GV];
+#pragma unroll
+                    for (int t = 0; t < TT; ++t)
+#pragma unroll
+                        for (int v = 0; v < 2 * GV; ++v) acc[t][v] = 0.f;
+#pragma unroll 1
+                    for (int idx = lane; idx < nvec; idx += 64) {
+                        V row[2 * GV];
+#pragma unroll
+                        for (int v = 0; v < 2 * GV; ++v)
+                            row[v] = reinterpret_cast<const V*>(lds_row + min(v, GV * rows - 1) * row_pitch)[idx];
+#pragma unroll
+                        for (int t = 0; t < TT; ++t) {
+                            const V xv = reinterpret_cast<const V*>(lds_x + min(wave - 1 + 3 * t, a.batch - 1) * a.x_pitch)[idx];
+#pragma unroll
+                            for (int v = 0; v < 2 * GV; ++v) acc[t][v] = dot_acc(row[v], xv, acc[t][v]);
+                        }
+                    }
+#pragma unroll
+                    for (int t = 0; t < TT; ++t)
+#pragma unroll
+                        for (int v = 0; v < 2 * GV; ++v) acc[t][v] = wave_sum(acc[t][v]);
+#pragma unroll
+                    for (int t = 0; t < TT; ++t)
+                        if (wave - 1 + 3 * t < a.batch && lane < rows)
+                            put(lane, wave - 1 + 3 * t, lane ? acc[t][GV] : acc[t][0], lane ? acc[t][2 * GV - 1] : acc[t][GV - 1]);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                if (lane == 0) __hip_atomic_fetch_add(&post->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (rows == 0) break;
+            }
+        }
+    };
+    auto gate_of = [&](int id) -> float {                        // lane t: resident gate activation of neuron id for token t
+        if constexpr (MODE != kOneToken && GATE) return a.gact[(size_t)min(lane, a.batch - 1) * F + min(max(id, 0), F - 1)];
+        return 0.f;
+    };
+    auto old_owner = [&](int s) -> int {
+        int id = L.ptr[min(s, kPtrLds - 1)];
+        if (s >= kPtrLds) id = a.pointers[s];
+        return id;
     };
     auto await_plan = [&]() {
         while (!__hip_atomic_load(&L.planned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) __builtin_amdgcn_s_sleep(1);
@@ -879,72 +1119,114 @@ __device__ __forceinline__ void cache_role(const Step1Args& a, int wg, PlanLds& 
         const int units = PAIRED ? 2 * n_a : n_a;
         if (alone && wave > 0) {
             if (tot_r > c0) plan_alone(c0);
-            load_pieces(xr, (const char*)a.x);
+            load_x();
         }
+        const int only = max(n_r - n_a, 0);                      // rows that nothing overwrites
+        if (MODE != kOneToken && wave > 0) work();
         if (wave == 0) {
             struct Unit {
                 int i, part, nid, dst, old_id;                   // item c0 + i
-                float old_bias, new_bias;
+                float old_bias, new_bias, old_gate, new_gate;
             };
-            auto make_unit = [&](int u, bool ask) {              // its numbers and its requests
+            auto make_unit = [&](int u, bool ask) {              // its numbers, and the requests for its bundle
                 Unit r;
                 r.part = PAIRED ? u & 1 : 0;
                 r.i = PAIRED ? u >> 1 : u;
                 const int s = n2 + c0 + r.i;
-                r.nid = __builtin_amdgcn_readfirstlane(L.ids[r.i]);
-                r.dst = r.i < n_r ? __builtin_amdgcn_readfirstlane(L.dst[r.i]) : -1;
-                r.old_id = a.pointers[s];
+                r.nid = __builtin_amdgcn_readfirstlane((int)L.ids[r.i]);
+                r.dst = r.i < n_r ? __builtin_amdgcn_readfirstlane((int)L.dst[r.i]) : kNoDst;
+                if constexpr (MODE == kOneToken) r.old_id = a.pointers[s];
+                else r.old_id = old_owner(s);
                 r.old_bias = a.bias[s];
                 r.new_bias = a.b[r.nid];
+                r.old_gate = gate_of(r.old_id);
+                r.new_gate = gate_of(r.nid);
                 if (ask) request_host(r.nid, r.part);
-                request_row(s, r.part);                          // (also where nothing is moved: no branch around loads)
                 return r;
             };
             int place = lw, round = 0;
             if (lw < units) {
                 if (alone && n_r > 0) await_plan();
                 Unit cu = make_unit(lw, c0 > 0);                 // (the bundle of the first piece was requested above)
+                request_row(n2 + c0 + cu.i, cu.part);            // (also where nothing is moved: no branch around loads)
                 for (;;) {
                     const int s = n2 + c0 + cu.i;
+                    const bool act = cu.part == 0, moves = cu.dst != kNoDst;      // uniform over the wave
                     float mdu = 0.f, mdg = 0.f, hdu = 0.f, hdg = 0.f;
-                    if (cu.dst >= 0) {                           // uniform over the wave
+                    if (moves) {
                         store_row(cu.dst, cu.part, mv);
-                        if (cu.part == 0) partial_dots(mv, mdu, mdg);
+                        if (act) partial_dots(mv, mdu, mdg);
                     }
                     store_row(s, cu.part, hv);
-                    if (cu.part == 0) partial_dots(hv, hdu, hdg);
+                    const Slot fresh = {s, cu.nid, cu.new_bias}, moved = {cu.dst, cu.old_id, cu.old_bias};
+                    if (act) {
+                        partial_dots(hv, hdu, hdg);
+                        if (MODE != kOneToken) {
+                            await_done();
+                            stage_row(hv, 0);
+                            if (moves && in_lds > 1) stage_row(mv, 1);
+                            post_rows(moves && in_lds > 1 ? 2 : 1, fresh, cu.new_gate, moved, cu.old_gate);
+                            if (moves && in_lds < 2) {
+                                await_done();
+                                stage_row(mv, 0);
+                                post_rows(1, moved, cu.old_gate, moved, cu.old_gate);
+                            }
+                        }
+                    }
                     place = place + 1 < nw ? place + 1 : 0;
                     round += nw;
                     const bool more = round + place < units;
                     Unit nu = cu;
                     if (more) {
                         nu = make_unit(round + place, true);
+                        request_row(n2 + c0 + nu.i, nu.part);
                     }
-                    if (cu.part == 0) {
-                        if (cu.dst >= 0) finish_slot(cu.dst, cu.old_id, cu.old_bias, mdu, mdg);
+                    if (MODE == kOneToken && act) {
+                        if (moves) finish_slot(cu.dst, cu.old_id, cu.old_bias, mdu, mdg);
                         finish_slot(s, cu.nid, cu.new_bias, hdu, hdg);
                     }
                     if (!more) break;
                     cu = nu;
                 }
             }
-        } else {
-            const int only = max(n_r - n_a, 0);                  // rows that nothing overwrites
-            if (alone && wave > 1 && only > 0) await_plan();
-            for (int v = lw * 3 + wave - 1; v < (PAIRED ? 2 * only : only); v += 3 * nw) {
-                const int part = (PAIRED && v >= only) ? 1 : 0, i = n_a + v - part * only;
-                const int dst = __builtin_amdgcn_readfirstlane(L.dst[i]), s = n2 + c0 + i;
-                if (dst < 0) continue;
-                request_row(s, part);
-                const int id = a.pointers[s];
-                const float bs = a.bias[s];
-                store_row(dst, part, mv);
-                if (part == 0) {
-                    float pu, pg;
-                    partial_dots(mv, pu, pg);
-                    finish_slot(dst, id, bs, pu, pg);
+        }
+        // rows that nothing overwrites: by the waves that do not load, with several tokens by the one that does (whole rows)
+        if constexpr (MODE == kOneToken) {
+            if (wave > 0 && only > 0) {
+                if (alone) await_plan();
+                for (int v = lw * 3 + wave - 1; v < (PAIRED ? 2 * only : only); v += 3 * nw) {
+                    const int part = (PAIRED && v >= only) ? 1 : 0, i = n_a + v - part * only;
+                    const int dst = __builtin_amdgcn_readfirstlane((int)L.dst[i]), s = n2 + c0 + i;
+                    if (dst == kNoDst) continue;
+                    request_row(s, part);
+                    const int id = a.pointers[s];
+                    const float bs = a.bias[s];
+                    store_row(dst, part, mv);
+                    if (part == 0) {
+                        float pu, pg;
+                        partial_dots(mv, pu, pg);
+                        finish_slot(dst, id, bs, pu, pg);
+                    }
                 }
             }
+        } else if (wave == 0) {
+            if (only > 0 && alone) await_plan();
+            for (int i = n_a + (nw - 1 - lw); i < n_a + only; i += nw) {         // (the last ones have had the fewest units)
+                const int dst = __builtin_amdgcn_readfirstlane((int)L.dst[i]), s = n2 + c0 + i;
+                if (dst == kNoDst) continue;
+                request_row(s, 0);
+                if (PAIRED) load_pieces(hv[0], row_vec(s, GA));
+                const int id = old_owner(s);
+                const Slot r = {dst, id, a.bias[s]};
+                const float gb = gate_of(id);
+                store_row(dst, 0, mv);
+                if (PAIRED) store_pieces(row_vec(dst, GA), hv[0]);
+                await_done();
+                stage_row(mv, 0);
+                post_rows(1, r, gb, r, gb);
+            }
+            await_done();
+            post_rows(0, Slot{}, 0.f, Slot{}, 0.f);
         }
     }
 }
@@ -956,14 +1238,14 @@ constexpr int step1_wgs_per_cu() {
     return (2 * vectors + 1) * NI * 4 <= 120 ? 2 : 1;
 }
 template <typename T, int NI, bool GLU, bool GATE>
-__global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(const Step1Args a) {
+__global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(const StepArgs a) {
     __shared__ __align__(16) unsigned char lds[sizeof(PlanLds) > sizeof(PredictLds) ? sizeof(PlanLds) : sizeof(PredictLds)];
     const int block = blockIdx.x;
     if (block < a.n_pred) {
         if constexpr (GATE) gate_role<T, NI>(a, block, reinterpret_cast<unsigned*>(lds));
         else lowrank_role<T, NI>(a, block, *reinterpret_cast<PredictLds*>(lds));
     } else if (block <= a.n_pred + a.n_load) {
-        cache_role<T, NI, GLU, GATE>(a, block - a.n_pred, *reinterpret_cast<PlanLds*>(lds));
+        cache_role<T, NI, GLU, GATE, kOneToken>(a, block - a.n_pred, *reinterpret_cast<PlanLds*>(lds), nullptr, nullptr);
     } else {
         const int first = a.n_pred + a.n_load + 1;
         ffn_up_role<T, NI, GLU, true>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, 1, a.capacity, a.row_elems, a.spec,
@@ -971,10 +1253,43 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
     }
 }
 
-// Launches k_step1 for one element type and bundle form (NI by the row width).  Every combination is compiled in a
-// source file of its own (step1_*.hip), side by side: together they are most of the library's compile time.
+// The same for a batch of tokens or a pass of several, behind the launches of the predictor: bookkeeping (workgroup 0),
+// loaders, and the activation stage over the rows in use - on the matrix cores (MFMA: fp16, d a multiple of 32), else one
+// wave per row.  Dynamic LDS: step_batch_lds bytes.
+template <typename T, int NI, bool GLU, bool MFMA>
+__global__ __launch_bounds__(256, 1) void k_step_batch(const StepArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_step[];
+    const int block = blockIdx.x;
+    constexpr int MODE = MFMA ? kMfma : kDots;
+    if (block <= a.n_load) {
+        PlanLds& plan = *reinterpret_cast<PlanLds*>(smem_step);
+        PostLds* post = reinterpret_cast<PostLds*>(smem_step + (sizeof(PlanLds) + 15) / 16 * 16);
+        if (!GLU && a.gact) cache_role<T, NI, GLU, true, MODE>(a, block, plan, post, smem_step + kStepXOff);
+        else cache_role<T, NI, GLU, false, MODE>(a, block, plan, post, smem_step + kStepXOff);
+    } else if constexpr (MFMA) {
+        const int tile = block - a.n_load - 1;
+        ffn_up_mfma_tile_staged<GLU, kMfmaWaves>(
+            (const _Float16*)a.matrix, a.bias, (const _Float16*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems, tile,
+            tile < a.spec, a.pointers, a.gact, a.F, a.st, smem_step);
+    } else {
+        const int first = a.n_load + 1;
+        ffn_up_role<T, NI, GLU, false>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems,
+                                       a.spec, block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers, a.gact, a.F,
+                                       a.st);
+    }
+}
+// LDS of a workgroup of k_step_batch
+inline size_t step_batch_lds(int batch, int d, int elem, bool glu, bool mfma, int rows) {
+    const size_t loader = kStepXOff + (size_t)batch * step_x_pitch(d, elem) + (size_t)rows * (glu ? 2 : 1) * step_x_pitch(d, elem);
+    const size_t up = mfma ? (size_t)mfma_staged_lds(glu, kMfmaWaves) : (size_t)batch * d * elem;
+    return loader > up ? loader : up;
+}
+constexpr size_t kStepLdsLimit = 160 * 1024;
+
+// Launches for one element type and bundle form (NI by the row width).  Every combination is compiled in a source file of
+// its own (step*.hip), side by side: together they are most of the library's compile time.
 template <typename T, bool GLU, bool GATE>
-inline void launch_step1_as(const Step1Args& a, int grid, hipStream_t s) {
+inline void launch_step1_as(const StepArgs& a, int grid, hipStream_t s) {
     const int ni = (a.d / Vec<T>::N + 63) / 64;
 #define LIF_S1(NI) hipLaunchKernelGGL((k_step1<T, NI, GLU, GATE>), dim3(grid), dim3(256), 0, s, a)
     if (ni <= 1) LIF_S1(1);
@@ -987,11 +1302,39 @@ inline void launch_step1_as(const Step1Args& a, int grid, hipStream_t s) {
     else LIF_S1(16);
 #undef LIF_S1
 }
-void launch_step1_f16_plain(const Step1Args& a, int grid, hipStream_t s);
-void launch_step1_f16_glu(const Step1Args& a, int grid, hipStream_t s);
-void launch_step1_f16_gate(const Step1Args& a, int grid, hipStream_t s);
-void launch_step1_f32_plain(const Step1Args& a, int grid, hipStream_t s);
-void launch_step1_f32_glu(const Step1Args& a, int grid, hipStream_t s);
-void launch_step1_f32_gate(const Step1Args& a, int grid, hipStream_t s);
+// (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that)
+template <typename T, bool GLU, bool MFMA>
+inline hipError_t launch_step_batch_as(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s) {
+    const int ni = (a.d / Vec<T>::N + 63) / 64;
+#define LIF_SB(NI)                                                                                                      \
+    do {                                                                                                                 \
+        if (allow)                                                                                                       \
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_step_batch<T, NI, GLU, MFMA>),                   \
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepLdsLimit);                  \
+        hipLaunchKernelGGL((k_step_batch<T, NI, GLU, MFMA>), dim3(grid), dim3(256), lds, s, a);                          \
+        return hipSuccess;                                                                                               \
+    } while (0)
+    if (ni <= 1) LIF_SB(1);
+    else if (ni <= 2) LIF_SB(2);
+    else if (ni <= 4) LIF_SB(4);
+    else if (ni <= 6) LIF_SB(6);
+    else if (ni <= 8) LIF_SB(8);
+    else if (ni <= 9) LIF_SB(9);
+    else if (ni <= 12) LIF_SB(12);
+    else LIF_SB(16);
+#undef LIF_SB
+}
+void launch_step1_f16_plain(const StepArgs& a, int grid, hipStream_t s);
+void launch_step1_f16_glu(const StepArgs& a, int grid, hipStream_t s);
+void launch_step1_f16_gate(const StepArgs& a, int grid, hipStream_t s);
+void launch_step1_f32_plain(const StepArgs& a, int grid, hipStream_t s);
+void launch_step1_f32_glu(const StepArgs& a, int grid, hipStream_t s);
+void launch_step1_f32_gate(const StepArgs& a, int grid, hipStream_t s);
+hipError_t launch_step_batch_f16_mfma(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16_mfma_glu(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16_glu(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f32(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f32_glu(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
 
 }  // namespace lif

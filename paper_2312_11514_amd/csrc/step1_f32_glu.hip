@@ -1,5 +1,5 @@
 #include "lif_step1.h"
 
 namespace lif {
-void launch_step1_f32_glu(const Step1Args& a, int grid, hipStream_t s) { launch_step1_as<float, true, false>(a, grid, s); }
+void launch_step1_f32_glu(const StepArgs& a, int grid, hipStream_t s) { launch_step1_as<float, true, false>(a, grid, s); }
 }  // namespace lif

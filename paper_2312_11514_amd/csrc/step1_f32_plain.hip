@@ -1,5 +1,5 @@
 #include "lif_step1.h"
 
 namespace lif {
-void launch_step1_f32_plain(const Step1Args& a, int grid, hipStream_t s) { launch_step1_as<float, false, false>(a, grid, s); }
+void launch_step1_f32_plain(const StepArgs& a, int grid, hipStream_t s) { launch_step1_as<float, false, false>(a, grid, s); }
 }  // namespace lif

@@ -109,3 +109,55 @@ def test_single_launch_step_overflow(shrink):
     ref.layer.step_calls(xd[4], ref.y)
     want, got = _snapshot(ref), _snapshot(g)
     assert got[0] == want[0] and got[4:] == want[4:]
+
+
+BATCH_CASES = {
+    # name: (dtype, glu, gate, d, F, rank, k, p, capacity, shrink, pairs), then the batch
+    "mfma": (("f16", False, False, 1056, 1096, 40, 3, 0.06, 900, False, 0), 3),
+    "mfma-glu": (("f16", True, False, 544, 2048, 24, 5, 0.04, 1700, False, 3), 8),
+    "mfma-gate": (("f16", False, True, 96, 1088, 8, 3, 0.05, 900, False, 0), 5),
+    "mfma-dynamic": (("f16", False, False, 64, 4160, 16, 9, 0.03, 1100, True, 0), 4),
+    "mfma-many-rows": (("f16", True, False, 32, 20032, 64, 2, 0.1, 18000, False, 0), 6),
+    "mfma-widest-glu": (("f16", True, False, 8192, 384, 16, 2, 0.1, 300, False, 2), 4),
+    "dots": (("f16", False, False, 1032, 1088, 40, 3, 0.06, 900, False, 0), 3),
+    "dots-glu": (("f16", True, False, 264, 704, 24, 2, 0.05, 600, False, 1), 8),
+    "dots-gate": (("f32", False, True, 260, 192, 8, 2, 0.05, 192, False, 0), 2),
+    "dots-f32-dynamic": (("f32", True, False, 516, 4160, 16, 4, 0.05, 900, True, 0), 2),
+}
+
+
+@pytest.mark.parametrize("name", list(BATCH_CASES))
+def test_single_launch_batch_equals_calls(name):
+    """Batches (lif_step) and passes of several tokens (lif_step_tokens, every number of kept tokens) the same way."""
+    from tests.harness import GpuLayer
+    case, batch = BATCH_CASES[name]
+    CASES[name] = case
+    w, L, _, pairs = _make(name)
+    del CASES[name]
+    X = wl.make_inputs(w, tokens=12 * batch)
+    ref = GpuLayer(w, L, max_batch=batch)
+    g = GpuLayer(w, L, max_batch=batch, share=ref)
+    for lay in (ref.layer, g.layer):                # (fewer tokens than max_batch leave the rest of these alone)
+        lay.masks.zero_()
+    if pairs:
+        g.layer.set_loader_pairs(pairs)
+    xd = ref.upload_x(X)
+    for t in range(12):
+        x = xd[t * batch:(t + 1) * batch]
+        tokens = batch if t % 4 else 1 + t % batch
+        keep = t % (tokens + 1)
+        print(f"{name}: step {t} tokens {tokens}", flush=True)
+        if t % 3 == 0 or w.d_ffn % 64:
+            ref.layer.step_calls(x, ref.y, batch=tokens)
+            g.layer.step(x, g.y, batch=tokens)
+        else:
+            ref.layer.predict(x, batch=tokens)
+            ref.layer.update_window_tokens(tokens, keep)
+            ref.layer.load_bundles()
+            ref.layer.sparse_ffn(x, ref.y, batch=tokens)
+            g.layer.step_tokens(x, g.y, tokens, keep)
+        want, got = _snapshot(ref), _snapshot(g)
+        assert want[0]["error"] == 0
+        for i, (a, b) in enumerate(zip(got, want)):
+            assert a == b, f"{name}: step {t}, tokens {tokens}, keep {keep}, item {i}"
+    assert ref.layer.counters()["rows_moved"] > 0
