@@ -51,6 +51,8 @@ int fail(int code, const char* fmt, const char* detail = "") {
 // but every loader workgroup costs a compute unit of the activation stage (11 KiB rows, 60 loaded: 52 / 52 / 53 / 56).
 constexpr size_t kStepInflightBytes = 320 * 1024, kStepInflightBytesB = 768 * 1024;
 constexpr int kStepPairs = 32, kStepPairsB = 48;
+// lif_load_bundles by itself: with 320 / 640 KiB rows of 25 and 30 KiB took 121 / 117 and 110 / 105 us (all four calls).
+constexpr size_t kLoadInflightBytes = 640 * 1024;
 constexpr int kDefaultPolls = 4096;      // a failed poll takes about 0.7 us: 3 ms before a workgroup helps itself
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -367,6 +369,12 @@ void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, h
     }
 }
 
+// bundles of host reads kept in flight
+int loader_pairs(const lif_layer* L, size_t inflight, int most) {
+    if (L->loader_pairs > 0) return L->loader_pairs;
+    return std::min(most, std::max(5, (int)std::min<size_t>(inflight / L->row_bytes, most)));
+}
+
 // arguments that both forms of a fused step take
 StepArgs step_args(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_mask, int32_t* added, int32_t* n_added,
                    int32_t* removed, int32_t* n_removed, int batch) {
@@ -385,11 +393,7 @@ StepArgs step_args(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_ma
     a.x = x; a.h = L->h; a.h_new = L->h_new; a.stamp = L->stamp; a.ptr_new = L->ptr_new; a.bias_new = L->bias_new;
     a.batch = batch; a.keep = 1; a.polls = L->polls; a.st = L->st;
     // loader waves: two per bundle in flight
-    const size_t inflight = batch > 1 ? kStepInflightBytesB : kStepInflightBytes;
-    const int most = batch > 1 ? kStepPairsB : kStepPairs;
-    const int pairs = L->loader_pairs > 0 ? L->loader_pairs
-                                          : std::min(most, std::max(5, (int)std::min<size_t>(inflight / L->row_bytes, most)));
-    a.n_load = 2 * pairs;
+    a.n_load = 2 * (batch > 1 ? loader_pairs(L, kStepInflightBytesB, kStepPairsB) : loader_pairs(L, kStepInflightBytes, kStepPairs));
     return a;
 }
 // workgroups of the activation role with one wave per row; with a row-count hint the grid is sized to it
@@ -796,12 +800,20 @@ int lif_load_bundles(lif_layer* L, const int32_t* added_dev, const int32_t* n_ad
     hipStream_t s = (hipStream_t)stream;
     const lif_config& c = L->cfg;
     {
-        const int cpr = (int)((L->row_bytes + kLoadChunk - 1) / kLoadChunk);
-        const long long worst = (long long)c.capacity_rows * cpr;
-        const int grid = (int)std::min<long long>(worst, kLoadGrid);
+        const int chunks = load_chunks(L->row_bytes);
+        const int chunk_bytes = (int)align_up((L->row_bytes + chunks - 1) / chunks, 16);
+        const int grid = (int)std::min<long long>((long long)c.capacity_rows * chunks, 2 * loader_pairs(L, kLoadInflightBytes, kStepPairs));
         Timed t(L, LIF_K_LOAD, s);
-        hipLaunchKernelGGL(k_load, dim3(grid), dim3(256), 0, s, (char*)L->buf.matrix, L->buf.pointers, L->buf.bias,
-                           L->host, L->buf.b, added_dev, L->move_dst, L->row_bytes, c.d_ffn, L->st);
+#define LIF_LD(NP)                                                                                                       \
+    case NP:                                                                                                             \
+        hipLaunchKernelGGL(k_load<NP>, dim3(grid), dim3(64), 0, s, (char*)L->buf.matrix, L->buf.pointers, L->buf.bias,     \
+                           L->host, L->buf.b, added_dev, L->move_dst, L->row_bytes, chunks, chunk_bytes, c.d_ffn,          \
+                           c.capacity_rows, L->st);                                                                        \
+        break
+        switch ((chunk_bytes + 1023) / 1024) {
+            LIF_LD(1); LIF_LD(2); LIF_LD(3); LIF_LD(4); LIF_LD(5); LIF_LD(6); LIF_LD(7); LIF_LD(8);
+        }
+#undef LIF_LD
     }
     L->window_pending = false;
     return check_launch();

@@ -374,88 +374,128 @@ __global__ __launch_bounds__(kScanThreads) void k_window_plan(
     }
 }
 
-// Row moves of the deletion plan fused with the host-to-device append (Section 3.3 item 2;
-// one contiguous bundle per neuron, Section 3.2).  Work item q covers tail slot s = n' + q:
-//   (1) if slot s is a live tail row, copy it to its hole;  (2) if q < |added|, read the
-//   bundle of added[q] from pinned host memory and write it to slot s.
-// Every 16-byte piece of slot s is read (1) and overwritten (2) by the same thread in
-// program order, holes lie below n' and appends at or above it, so no two work items
-// touch the same bytes.  grid-stride over (item, 16 KiB chunk); block = 256, four 16-byte
-// loads per thread in flight.
-// The host link wants FEW requests in flight: measured on MI355X / PCIe Gen5, 146 bundles of
-// 16 KiB take 45 us with 32-64 workgroups (128-256 KiB in flight) and 58 us with 146 or more.
-constexpr int kLoadPer = 4;
-constexpr size_t kLoadChunk = 256 * 16 * kLoadPer;
-constexpr int kLoadGrid = 32;
+// Row moves of the deletion plan fused with the host-to-device append (Section 3.3 item 2; one contiguous bundle per neuron,
+// Section 3.2).  Work item q covers tail slot s = n' + q:
+//   (1) if slot s is a live tail row, copy it to its hole;  (2) if q < |added|, read the bundle of added[q] from pinned host
+//   memory and write it to slot s.
+// Every 16-byte piece of slot s is read (1) and overwritten (2) by the same thread in program order, holes lie below n' and
+// appends at or above it, so no two work items touch the same bytes.
+//
+// Bound by the host link, which wants few requests in flight but never fewer than about 128 KiB.  A bundle is cut into equal
+// chunks of at most kLoadChunk bytes; a unit is one chunk of one item, and every workgroup is a single wave that takes one
+// unit after the other (the L1 of a compute unit returns loads in order: several waves on one would wait for each other).
+// All numbers of a wave's units (ids, destinations, owners, biases: lane i those of its i-th unit) are read at once ahead
+// of the first host read, and each host read is requested as soon as the stores of the unit before it have been issued.
+// The units of a round are dealt one place further each round, so that the chunks read at a time fall on different parts of
+// the rows.  With 32 workgroups of four waves, a bundle at a time
+// each: bundles of 10 KiB, all four calls 75 -> 72 us; 2.4 KiB, 134 -> 106 us a step.
+constexpr int kLoadPieces = 8;                           // pieces of 1 KiB per chunk at most
+constexpr size_t kLoadChunk = kLoadPieces * 1024;
+inline int load_chunks(size_t row_bytes) { return (int)((row_bytes + kLoadChunk - 1) / kLoadChunk); }
 
-// `block` / `nblocks`: index and count of the workgroups that share this role.
-__device__ __forceinline__ void load_rows_role(char* __restrict__ matrix, int32_t* __restrict__ pointers,
-                                               float* __restrict__ bias, const HostStore host,
-                                               const float* __restrict__ b, const int32_t* __restrict__ added,
-                                               const int32_t* __restrict__ move_dst, size_t row_bytes, int F,
-                                               int block, int nblocks, DevState* st) {
+template <int NP>
+__global__ __launch_bounds__(64) void k_load(char* __restrict__ matrix, int32_t* __restrict__ pointers,
+                                             float* __restrict__ bias, const HostStore host,
+                                             const float* __restrict__ b, const int32_t* __restrict__ added,
+                                             const int32_t* __restrict__ move_dst, size_t row_bytes, int chunks,
+                                             int chunk_bytes, int F, int capacity, DevState* st) {
+    const int lane = threadIdx.x, nw = gridDim.x, lw = blockIdx.x;
+    // unit i of this wave is number i * nw + (lw + i) mod nw; lane l reads the numbers of unit first + l
+    auto unit_of = [&](int i) { return i * nw + (lw + i) % nw; };        // (below 65536 items of 6 chunks)
+    int l_id = 0, l_dst = 0, l_owner = 0;
+    float l_bias = 0.f, l_new = 0.f;
+    auto request_lists = [&](int first) {                // (entries past the counts are read and not used)
+        const int q = min(unit_of(first + lane) / chunks, min(F, capacity) - 1);
+        l_id = added[q];
+        l_dst = move_dst[q];
+    };
+    request_lists(0);
     if (st->cur.error) return;
     const int n2 = st->cur.n_base, c = st->cur.n_removed, a = st->cur.n_added;
-    const int items = max(c, a);
-    const int cpr = (int)((row_bytes + kLoadChunk - 1) / kLoadChunk);
-    const long long total = (long long)items * cpr;
-    const int tid = threadIdx.x;
-    for (long long it = block; it < total; it += nblocks) {
-        const int q = (int)(it / cpr), ch = (int)(it - (long long)q * cpr);
-        const int s = n2 + q;
-        const int dst = (q < c) ? move_dst[q] : -1;
-        int nid = (q < a) ? added[q] : -1;
-        if (nid >= F) nid = -1;
-        const size_t off0 = (size_t)ch * kLoadChunk + (size_t)tid * 16;
-        const char* msrc = matrix + (size_t)s * row_bytes + off0;
-        char* mdst = matrix + (size_t)max(dst, 0) * row_bytes + off0;
-        char* adst = matrix + (size_t)s * row_bytes + off0;
-        uint4 hv[kLoadPer], mv[kLoadPer];
-        bool ok[kLoadPer];
+    const int loads = a * chunks, total = max(c, a) * chunks;
+    const unsigned lane_off = lane * 16u;
+    f32x4 hv[NP], mv[NP];
+    struct Unit {
+        int s, dst, nid, off, len;
+    };
+    // (no branch around a load, which would make the compiler keep a second copy of its registers: a row that nothing is
+    // moved from is read all the same.  Lanes past the end of the chunk read its last 16 bytes.)
+    auto ask_host = [&](const Unit& r) {
 #pragma unroll
-        for (int p = 0; p < kLoadPer; ++p) {
-            ok[p] = off0 + (size_t)p * 4096 < row_bytes;
-            hv[p] = make_uint4(0, 0, 0, 0);
-            mv[p] = make_uint4(0, 0, 0, 0);
+        for (int p = 0; p < NP; ++p)
+            hv[p] = *reinterpret_cast<const f32x4*>(host_piece(host, max(r.nid, 0), r.off + min(p * 1024u + lane_off, r.len - 16u), row_bytes));
+    };
+    auto ask_row = [&](const Unit& r) {
+        const char* row = matrix + (size_t)r.s * row_bytes + r.off;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) mv[p] = *reinterpret_cast<const f32x4*>(row + min(p * 1024u + lane_off, r.len - 16u));
+    };
+    auto store = [&](const f32x4 (&v)[NP], const Unit& r, int slot) {
+        char* row = matrix + (size_t)slot * row_bytes + r.off;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (p * 1024u + lane_off < (unsigned)r.len) *reinterpret_cast<f32x4*>(row + (p * 1024u + lane_off)) = v[p];
+    };
+    for (int first = 0; unit_of(first) < total; first += 64) {
+        if (first > 0) request_lists(first);
+        {
+            const int s = min(n2 + unit_of(first + lane) / chunks, capacity - 1);
+            l_owner = pointers[s];
+            l_bias = bias[s];
+            if ((unsigned)l_id >= (unsigned)F) l_id = -1;        // (not a neuron: its slot is left alone)
+            l_new = b[max(l_id, 0)];
         }
-#pragma unroll
-        for (int p = 0; p < kLoadPer; ++p)
-            if (ok[p] && nid >= 0)
-                hv[p] = *reinterpret_cast<const uint4*>(host_piece(host, nid, off0 + (size_t)p * 4096, row_bytes));
-#pragma unroll
-        for (int p = 0; p < kLoadPer; ++p)
-            if (ok[p] && dst >= 0) mv[p] = *reinterpret_cast<const uint4*>(msrc + (size_t)p * 4096);
-#pragma unroll
-        for (int p = 0; p < kLoadPer; ++p)
-            if (ok[p] && dst >= 0) *reinterpret_cast<uint4*>(mdst + (size_t)p * 4096) = mv[p];
-#pragma unroll
-        for (int p = 0; p < kLoadPer; ++p)
-            if (ok[p] && nid >= 0) *reinterpret_cast<uint4*>(adst + (size_t)p * 4096) = hv[p];
-        if (ch == 0 && tid == 0) {
-            const int32_t old_ptr = pointers[s];
-            const float old_bias = bias[s];
-            if (dst >= 0) {
-                pointers[dst] = old_ptr;
-                bias[dst] = old_bias;
+        auto unit = [&](int i) {                         // i-th one from `first`
+            const int u = unit_of(first + i), q = u / chunks, ch = u - q * chunks;
+            Unit r;
+            r.s = n2 + q;
+            r.dst = __builtin_amdgcn_readlane(l_dst, i);
+            if (q >= c) r.dst = -1;
+            r.nid = __builtin_amdgcn_readlane(l_id, i);
+            r.off = ch * chunk_bytes;
+            r.len = min(chunk_bytes, (int)row_bytes - r.off);
+            return r;
+        };
+        auto owner = [&](const Unit& r, int i, bool fresh) {
+            if (r.off == 0 && lane == i) {
+                if (r.dst >= 0) {
+                    pointers[r.dst] = l_owner;
+                    bias[r.dst] = l_bias;
+                }
+                if (fresh) {
+                    pointers[r.s] = r.nid;
+                    bias[r.s] = l_new;
+                }
             }
-            if (nid >= 0) {
-                pointers[s] = nid;
-                bias[s] = b[nid];
+        };
+        int i = 0;
+        if (unit_of(first) < loads) {
+            Unit cu = unit(0);
+            ask_host(cu);
+            ask_row(cu);
+            for (;;) {
+                if (cu.dst >= 0) store(mv, cu, cu.dst);
+                if (cu.nid >= 0) store(hv, cu, cu.s);
+                owner(cu, i, cu.nid >= 0);
+                ++i;
+                if (i == 64 || unit_of(first + i) >= loads) break;
+                cu = unit(i);
+                ask_host(cu);
+                ask_row(cu);
             }
+        }
+        for (; i < 64 && unit_of(first + i) < total; ++i) {      // more neurons removed than added: moves only
+            const Unit r = unit(i);
+            if (r.dst < 0) continue;
+            ask_row(r);
+            store(mv, r, r.dst);
+            owner(r, i, false);
         }
     }
-    if (block == 0 && tid == 0) {
+    if (lw == 0 && lane == 0) {
         st->cur.num_used = n2 + a;
         atomicAdd(&st->c_h2d_bytes, (unsigned long long)a * row_bytes);
     }
-}
-
-__global__ __launch_bounds__(256) void k_load(char* __restrict__ matrix, int32_t* __restrict__ pointers,
-                                              float* __restrict__ bias, const HostStore host,
-                                              const float* __restrict__ b, const int32_t* __restrict__ added,
-                                              const int32_t* __restrict__ move_dst, size_t row_bytes, int F,
-                                              DevState* st) {
-    load_rows_role(matrix, pointers, bias, host, b, added, move_dst, row_bytes, F, blockIdx.x, gridDim.x, st);
 }
 
 // Empty cache: no mask in the window, state and counters zero, no word handed over yet (the stamps start again).

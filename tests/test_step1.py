@@ -161,3 +161,34 @@ def test_single_launch_batch_equals_calls(name):
         for i, (a, b) in enumerate(zip(got, want)):
             assert a == b, f"{name}: step {t}, tokens {tokens}, keep {keep}, item {i}"
     assert ref.layer.counters()["rows_moved"] > 0
+
+
+LOAD_CASES = {
+    # name: ((dtype, glu, gate, d, F, rank, k, p, capacity, shrink, pairs), bundles in two parts)
+    "32-byte-rows": (("f32", False, False, 4, 264, 4, 2, 0.2, 264, False, 0), False),
+    "one-chunk": (("f16", False, False, 1288, 800, 16, 2, 0.1, 800, False, 0), False),
+    "short-last-chunk": (("f32", True, False, 2052, 320, 16, 3, 0.1, 320, False, 0), False),
+    "six-chunks": (("f16", True, False, 8192, 200, 16, 2, 0.1, 200, False, 0), False),
+    "two-parts": (("f16", True, False, 2072, 640, 16, 2, 0.1, 640, False, 0), True),
+    "many-units-a-wave": (("f16", False, False, 264, 4096, 16, 1, 0.3, 4096, False, 1), False),
+}
+
+
+@pytest.mark.parametrize("name", list(LOAD_CASES))
+def test_load_bundles_chunks_and_lists(name):
+    """lif_load_bundles where its units can go wrong: the cache rows, owners and biases against the oracle."""
+    from oracle import lif_oracle as O
+    from tests.harness import GpuLayer, compare_step
+    case, unbundled = LOAD_CASES[name]
+    CASES[name] = case
+    w, L, X, pairs = _make(name)
+    del CASES[name]
+    gpu = GpuLayer(w, L, unbundled=unbundled)
+    if pairs:
+        gpu.layer.set_loader_pairs(pairs)
+    ora = O.OracleLayer(w.d_model, w.d_ffn, w.window_k, w.capacity_rows, w.glu, L.A, L.B, L.c, L.theta, L.b, L.bundles)
+    moved = 0
+    for t in range(5):
+        print(f"{name}: token {t}", flush=True)
+        moved += compare_step(gpu, ora, X[t], w, t)["moved"]
+    assert moved > 0
