@@ -341,7 +341,10 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(kDmWaves * 64), 0, s,
+    if (fc.on) hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, true>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(kDmWaves * 64), 0, s,
+                       (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y, ypart, c.d_model, batch,
+                       c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st);
+    else hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, false>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(kDmWaves * 64), 0, s,
                        (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y, ypart, c.d_model, batch,
                        c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st);
     if (wg_rows > 1)

@@ -22,8 +22,9 @@ constexpr int kDmRows = 512;             // rows compacted per pass
 constexpr int kDmPitch = kDmRows + 8;    // fp16 values per token slot in LDS (16 bytes of padding: lanes of one
                                          // row block read 16 different slots at the same offset)
 constexpr int kDmCols = 128;             // columns per workgroup: 16 lanes x 16 bytes
-constexpr int kDmWaves = 4;              // waves per workgroup: 8 are faster below 4000 rows (9 against 12 us) but their
-                                         // registers leave one workgroup per compute unit (27 against 16 us at 8700 rows)
+constexpr int kDmWaves = 4;              // waves per workgroup: 8 are a little faster below 5000 rows (196 against 197 us for a
+                                         // step of 4 tokens at 1250 rows) but leave two workgroups per compute unit and so a
+                                         // second, nearly empty round of them above (24 against 19 us at 8600 rows)
 
 // Rows per chunk (one partial output per chunk): a multiple of kDmRows that depends on the capacity alone, so a
 // workgroup row knows where its first chunk starts before the row count arrives, and at most kDownChunksMax
@@ -44,6 +45,10 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
     return high ? __builtin_amdgcn_perm(second, first, 0x07060302u) : __builtin_amdgcn_perm(second, first, 0x05040100u);
 }
 
+// What bounds it: HBM, about 5.5 TB/s for this access pattern, between a prologue of 5 us (activations, compaction) and the
+// reductions.  All workgroups are resident at once (three per compute unit need at most 168 registers, which the launch
+// bound asks for), so the prologue is not hidden by other workgroups; where every row is read it overlaps with the first
+// quarter of the rows: 10976 rows, 8 tokens, d = 4096, gated, activations and down projection 63.3 -> 60.2 us.
 // grid = (ceil(d / 128) column slices, row-chunk workgroups), block = WAVES waves; lane l of a wave: column
 // group n16 = l mod 16 (8 columns) and token slot n16, row block q = l div 16 (8 of the 32 rows of an instruction).
 // A pass compacts the contributing rows of 512 slots (SKIP: rows with some activation; else all rows in use) in a
@@ -51,8 +56,8 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // A chunk's passes are added in order, the waves in wave order, the chunks in chunk order (by this kernel when
 // one workgroup row is launched, else by k_ffn_down_mfma_finish from ypart[chunk][token][d]).  Nothing depends on
 // the launch geometry.
-template <bool SKIP, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __restrict__ matrix,
+template <bool SKIP, int WAVES, bool FUSED>
+__global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16* __restrict__ matrix,
                                                               const float* __restrict__ h, const FusedRows fused,
                                                               _Float16* __restrict__ y, float* __restrict__ ypart, int d,
                                                               int batch, int capacity, size_t row_elems, int down_off,
@@ -68,32 +73,49 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
     __shared__ float red[WAVES][32][33];             // per wave and lane with q < 2: 32 sums, padded
     __shared__ int n_active;
 
-    if ((int)blockIdx.x == slices) {                 // (only after a fused step)
+    if (FUSED && (int)blockIdx.x == slices) {                 // (only after a fused step)
         if (blockIdx.y == 0) commit_step<WAVES * 64>(fused, capacity, st);
         return;
     }
     const float* __restrict__ h_new = fused.h_new;
-    const int32_t* __restrict__ stamp = fused.stamp;
+    const int32_t* __restrict__ stamp = FUSED ? fused.stamp : nullptr;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, q = lane >> 4;
     const int col = blockIdx.x * kDmCols + n16 * 8;
     const bool col_ok = col < d;
-    const _Float16* base = matrix + down_off + (col_ok ? col : 0);
+    // (offsets in bytes from the uniform base: 65536 rows of 48 KiB stay below 4 GiB)
+    const unsigned row_bytes = (unsigned)row_elems * 2u, col_bytes = (unsigned)(down_off + (col_ok ? col : 0)) * 2u;
 
     if (tid == 0) n_active = 0;
-    // the activations of the first pass are requested before the row count is known (the array spans the capacity)
-    float hfirst[PER][BT], hnfirst[PER][BT];
-    int sfirst[PER];
+    // What a pass begins with is requested at the end of the one before, for the first one before the row count is known (the
+    // arrays span the capacity; values past the rows in use are masked): its activations and, where every row is read, the
+    // rows of the first group of each wave.
+    float ha[PER][BT], hb[PER][BT];
+    int fresh_at[PER];
+    f16x8 v[8];
+    // the rows of a group: 8 loads of 16 bytes per lane
+    auto load = [&](int g, int cnt, auto slot) {
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int s = blockIdx.y * chunk_rows + p * T + tid;
-        sfirst[p] = (stamp && s < capacity) ? stamp[s] : -1;
-#pragma unroll
-        for (int b = 0; b < BT; ++b) {
-            hfirst[p][b] = (s < capacity && b < batch) ? h[(size_t)b * capacity + s] : 0.f;
-            hnfirst[p][b] = (stamp && s < capacity && b < batch) ? h_new[(size_t)b * capacity + s] : 0.f;
+        for (int r = 0; r < 8; ++r) {
+            const int i = g * 32 + q * 8 + r;
+            v[r] = *reinterpret_cast<const f16x8*>(reinterpret_cast<const char*>(matrix) + ((unsigned)slot(i < cnt ? i : 0) * row_bytes + col_bytes));
         }
-    }
+    };
+    auto request = [&](int s_base) {
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const unsigned s = min(s_base + p * T + tid, capacity - 1);
+            fresh_at[p] = stamp ? stamp[s] : -1;
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                ha[p][b] = b < batch ? (h + (size_t)b * capacity)[s] : 0.f;
+                hb[p][b] = stamp && b < batch ? (h_new + (size_t)b * capacity)[s] : 0.f;
+            }
+        }
+        asm volatile("" ::: "memory");       // (behind the activations: loads return in order)
+        if constexpr (!SKIP) load(w, kDmRows, [&](int i) { return min(s_base + i, capacity - 1); });
+    };
+    request(blockIdx.y * chunk_rows);
     const StepCounts* counts = stamp ? &st->next : &st->cur;
     const int err = counts->error, n = counts->num_used, cur_step = counts->step;
     if (err) return;
@@ -113,23 +135,19 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
         }
         for (int s_base = r0; s_base < r1; s_base += kDmRows) {
             // compaction of the rows that contribute and the largest |activation| of the pass
-            const bool spec = chunk == (int)blockIdx.y && s_base == r0;
-            float hloc[PER][BT];
             unsigned flags = 0, nonzero = 0;
             float amax = 0.f;
 #pragma unroll
             for (int p = 0; p < PER; ++p) {
                 const int s = s_base + p * T + tid;
                 bool any = false;
-                const bool fresh = stamp && (spec ? sfirst[p] : s < r1 ? stamp[s] : -1) == cur_step;
-                const float* from = fresh ? h_new : h;
+                const bool fresh = stamp && fresh_at[p] == cur_step;
 #pragma unroll
                 for (int b = 0; b < BT; ++b) {
-                    float v = 0.f;
-                    if (s < r1 && b < batch) v = !spec ? from[(size_t)b * capacity + s] : fresh ? hnfirst[p][b] : hfirst[p][b];
-                    hloc[p][b] = v;
-                    any |= (v != 0.f);
-                    amax = fmaxf(amax, fabsf(v));
+                    const float a = s >= r1 ? 0.f : fresh ? hb[p][b] : ha[p][b];
+                    ha[p][b] = a;
+                    any |= (a != 0.f);
+                    amax = fmaxf(amax, fabsf(a));
                 }
                 if (any) nonzero |= 1u << p;
                 if (SKIP ? any : s < r1) flags |= 1u << p;
@@ -139,8 +157,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
             for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, kWave));
             if (lane == 0) wave_max[w] = amax;       // (the barriers of the scan order this write and the reads below,
                                                      //  and keep the previous pass's readers of list / hv ahead of the writes)
-            int cnt;
-            int off = block_exclusive_scan<WAVES>(__popc(flags), wave_tot, &cnt);
+            int cnt = min(r1 - s_base, kDmRows), off = 0;
+            if constexpr (SKIP) off = block_exclusive_scan<WAVES>(__popc(flags), wave_tot, &cnt);
+            else __syncthreads();
             float smax = wave_max[0];
 #pragma unroll
             for (int i = 1; i < WAVES; ++i) smax = fmaxf(smax, wave_max[i]);
@@ -150,11 +169,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
             const float scale = ldexpf(1.f, 14 - ex), inv_scale = ldexpf(1.f, ex - 14);
 #pragma unroll
             for (int p = 0; p < PER; ++p) {
+                if (!SKIP) off = p * T + tid;
                 if (flags & (1u << p)) {
-                    list[off] = s_base + p * T + tid;
+                    if (SKIP) list[off] = s_base + p * T + tid;
 #pragma unroll
                     for (int b = 0; b < BT; ++b) {
-                        const float hs = hloc[p][b] * scale;
+                        const float hs = ha[p][b] * scale;
                         const _Float16 hi = (_Float16)hs;
                         hv[b][off] = hi;
                         hv[BT + b][off] = (_Float16)(hs - (float)hi);
@@ -172,16 +192,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
                 f32x4 acc[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-                // the rows of a group: 8 loads of 16 bytes per lane
-                auto load = [&](f16x8 (&v)[8], int g) {
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const int i = g * 32 + q * 8 + r;
-                        const int sr = list[i < cnt ? i : 0];
-                        v[r] = (i < cnt && col_ok) ? *reinterpret_cast<const f16x8*>(base + (size_t)sr * row_elems) : f16x8(0);
-                    }
-                };
-                auto compute = [&](const f16x8 (&v)[8], int g) {
+                auto compute = [&](int g) {
                     // this lane's token slot: activations of rows i0 .. i0 + 7
                     const f16x8 a = *reinterpret_cast<const f16x8*>(&hv[n16][g * 32 + q * 8]);
 #pragma unroll
@@ -196,12 +207,20 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
                         acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, __builtin_bit_cast(f16x8, bj), acc[j], 0, 0, 0);
                     }
                 };
-                // (a second register set that requests the wave's next group ahead of the arithmetic was measured:
-                // no faster at 1400 rows, and the registers cost a third of the resident waves at 8700)
-                for (int g = w; g * 32 < cnt; g += WAVES) {
-                    f16x8 v[8];
-                    load(v, g);
-                    compute(v, g);
+                // (rows past the last one are read as the first one, against activations of 0; a second register set that
+                // requests the wave's next group ahead of the arithmetic was no faster at 1400 rows)
+                auto row = [&](int i) { return SKIP ? list[i] : s_base + i; };
+                if constexpr (SKIP) {
+                    if (w * 32 < cnt) load(w, cnt, row);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r)
+                        if (w * 32 + q * 8 + r >= cnt) v[r] = f16x8(0);      // (slots not in use hold anything)
+                }
+                for (int g = w; g * 32 < cnt;) {
+                    compute(g);
+                    g += WAVES;
+                    if (g * 32 < cnt) load(g, cnt, row);
                 }
                 // token slots 8..15 (lanes with q >= 2) hold the low-part products of tokens 0..7: add them; the
                 // passes of a chunk add up in the wave's own LDS entries (0 + first pass is exact)
@@ -213,6 +232,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down_mfma(const _Float16* __
                         if (q < 2) red[w][lane][j * 4 + r] += (acc[j][r] + lo) * inv_scale;
                     }
             }
+            const int next = s_base + kDmRows < r1 ? s_base + kDmRows
+                                                   : chunk + (int)gridDim.y < chunks ? (chunk + (int)gridDim.y) * chunk_rows : -1;
+            if (next >= 0) request(next);
         }
         // the waves took different rows: add in wave order
         __syncthreads();

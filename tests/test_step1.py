@@ -192,3 +192,22 @@ def test_load_bundles_chunks_and_lists(name):
         print(f"{name}: token {t}", flush=True)
         moved += compare_step(gpu, ora, X[t], w, t)["moved"]
     assert moved > 0
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 128, 511, 513, 1030])
+def test_batched_down_projection_reading_every_row(n):
+    """fp16 batch, every row read: rows are requested ahead of the row count, so slots not in use may hold anything."""
+    import paper_2312_11514_amd as lif
+    from tests.harness import REL_L2_TOL, GpuLayer, rel_l2
+    w = wl.scaled(wl.WORKLOADS["C1"], name="full", d_model=136, d_ffn=1096, rank=16, capacity_rows=1030, dtype="f16", p_active=0.4)
+    L = wl.make_layer(w)
+    gpu = GpuLayer(w, L, ffn_mode=lif.FFN_FULL_BUNDLE, max_batch=3)
+    ids = np.random.default_rng(n).permutation(w.d_ffn)[:n]
+    gpu.layer.matrix.fill_(float("nan"))
+    gpu.fill_cache(ids, L)
+    x = wl.make_inputs(w, tokens=3)
+    gpu.layer.sparse_ffn(gpu.upload_x(x), gpu.y, batch=3)
+    bun = L.bundles[ids].astype(np.float64)
+    d = w.d_model
+    h = np.maximum(x.astype(np.float64) @ bun[:, :d].T + L.b[ids], 0.0)
+    assert rel_l2(gpu.y.cpu().numpy().astype(np.float64), h @ bun[:, d:]) <= REL_L2_TOL
