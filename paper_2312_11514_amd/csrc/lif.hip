@@ -301,12 +301,14 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     // slots if that many rows make one pass (else the order of the slots is not known yet)
     const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;
     const FusedRows f = fused_rows(L, fc);
-#define LIF_D1(W)                                                                                            \
-    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(W * 64), 0, s,     \
+#define LIF_D1(W, FUSED)                                                                                     \
+    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W, FUSED>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(W * 64), 0, s,     \
                        (const T*)L->buf.matrix, h, f, (T*)y, ypart, c.d_model, c.capacity_rows, L->row_elems,        \
                        down_off, spec, slices, L->buf.pointers, L->gact, c.d_ffn, L->st)
-    if (waves == 8) LIF_D1(8);
-    else LIF_D1(16);
+    if (waves == 8 && fc.on) LIF_D1(8, true);
+    else if (waves == 8) LIF_D1(8, false);
+    else if (fc.on) LIF_D1(16, true);
+    else LIF_D1(16, false);
 #undef LIF_D1
     if (wg_rows > 1)
         hipLaunchKernelGGL((k_ffn_down_finish<T, down1_chunks<SKIP>>), dim3((c.d_model + 255) / 256), dim3(256), 0, s,
@@ -323,9 +325,13 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
     const int wg_rows = down_chunks(geometry_rows(L));
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
     const int slices = (c.d_model + cols - 1) / cols;
-    hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(256), 0, s,
-                       (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, c.d_model, batch, c.capacity_rows,
-                       L->row_elems, down_off, slices, L->st);
+#define LIF_DB(FUSED)                                                                                        \
+    hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(256),  \
+                       0, s, (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, c.d_model, batch,          \
+                       c.capacity_rows, L->row_elems, down_off, slices, L->st)
+    if (fc.on) LIF_DB(true);
+    else LIF_DB(false);
+#undef LIF_DB
     if (wg_rows > 1)
         hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
                            ypart, (T*)y, c.d_model, batch, L->st);
@@ -341,12 +347,13 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    if (fc.on) hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, true>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(kDmWaves * 64), 0, s,
-                       (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y, ypart, c.d_model, batch,
-                       c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st);
-    else hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, false>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(kDmWaves * 64), 0, s,
-                       (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y, ypart, c.d_model, batch,
-                       c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st);
+#define LIF_DM(FUSED)                                                                                        \
+    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),             \
+                       dim3(kDmWaves * 64), 0, s, (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y,  \
+                       ypart, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
+    if (fc.on) LIF_DM(true);
+    else LIF_DM(false);
+#undef LIF_DM
     if (wg_rows > 1)
         hipLaunchKernelGGL(k_ffn_down_mfma_finish, dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart,
                            (_Float16*)y, c.d_model, batch, chunk_rows, L->st);

@@ -244,12 +244,14 @@ __host__ __device__ __forceinline__ int down_chunks(int n) {
 // lane owns 16 bytes of every down column it reads, a workgroup LANES * 16 contiguous bytes.
 // SKIP: rows whose activation is zero for every token of the batch are not read (they are compacted
 // away with a prefix sum in LDS, in a fixed order).
+// FUSED: the launch after k_step_batch.  One more workgroup commits the step and the activations of fresh rows are picked
+// up; a form of its own because the run-time test cost the plain call 0.2 to 0.6 us of 17 (2 to 5 tokens, d 400 to 2800).
 // The rows are cut into down_chunks(n) chunks - a function of n alone, so the arithmetic does not
 // depend on the launch geometry - and workgroup row y takes the chunks y, y + gridDim.y, ...  Every
 // chunk is summed from zero.  With one chunk in use the workgroup writes its columns of y.  With more,
 // a grid of one workgroup row adds its chunk sums in chunk order and writes y; a taller grid writes
 // them to ypart[chunk][token][d] (fp32) and k_ffn_down_finish adds them in the same order.  No atomics.
-template <typename T, int BT, bool SKIP, int LANES>
+template <typename T, int BT, bool SKIP, int LANES, bool FUSED>
 __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, const float* __restrict__ h,
                                                   const FusedRows fused, T* __restrict__ y,
                                                   float* __restrict__ ypart, int d, int batch, int capacity,
@@ -267,12 +269,12 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     __shared__ float red[4][LANES][BT * VE];
     __shared__ int n_active;
 
-    if ((int)blockIdx.x == slices) {                 // (only after a fused step)
+    if (FUSED && (int)blockIdx.x == slices) {
         if (blockIdx.y == 0) commit_step<256>(fused, capacity, st);
         return;
     }
     const float* __restrict__ h_new = fused.h_new;
-    const int32_t* __restrict__ stamp = fused.stamp;
+    const int32_t* __restrict__ stamp = FUSED ? fused.stamp : nullptr;
     const int tid = threadIdx.x, l = tid & (LANES - 1), rg = tid / LANES;
     const int slice = blockIdx.x;
     const int col = slice * (LANES * VE) + l * VE;

@@ -40,7 +40,7 @@ __host__ __device__ __forceinline__ int down1_chunks(int n) {
 // the result does not depend on the launch geometry.
 __host__ __device__ __forceinline__ int down1_waves(int n) { return n <= kDown1FewRows ? 8 : 16; }
 
-// grid = (column slices of 64 bytes, rounded up to a multiple of 8, + 1 after a fused step: the workgroup that commits
+// grid = (column slices of 64 bytes, rounded up to a multiple of 8, + 1 after a fused step (FUSED): the workgroup that commits
 // it; row-chunk workgroups), block = WAVES * 64.
 // gact (may be null): the activations in h and h_new are up . x alone and are multiplied with the gate activation of the
 // slot's neuron here (gate predictor; gact_n = number of neurons).
@@ -48,7 +48,7 @@ __host__ __device__ __forceinline__ int down1_waves(int n) { return n <= kDown1F
 // capacity, so the addresses are valid; values past the count are masked).
 // Workgroup row y takes the chunks y, y + gridDim.y, ...; with several chunks and several workgroup rows the sums go to
 // ypart[chunk][d] (fp32) and k_ffn_down_finish adds them, else this kernel adds them in the same order.  No atomics.
-template <typename T, bool SKIP, int WAVES>
+template <typename T, bool SKIP, int WAVES, bool FUSED>
 __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ matrix, const float* __restrict__ h,
                                                           const FusedRows fused, T* __restrict__ y,
                                                           float* __restrict__ ypart, int d, int capacity,
@@ -67,12 +67,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l = lane & (LANES - 1), rg = lane / LANES;
     // XCD-aware slice order: workgroups are dealt round-robin to the 8 XCDs, each with its own L2; giving every XCD a
     // contiguous run of slices makes the two halves of a 128-byte line meet in one L2 instead of being fetched twice
-    if ((int)blockIdx.x == slices) {                 // (only after a fused step)
+    if (FUSED && (int)blockIdx.x == slices) {
         if (blockIdx.y == 0) commit_step<THREADS>(fused, capacity, st);
         return;
     }
     const float* __restrict__ h_new = fused.h_new;
-    const int32_t* __restrict__ stamp = fused.stamp;
+    const int32_t* __restrict__ stamp = FUSED ? fused.stamp : nullptr;
     const int per_xcd = slices / kXcds;
     const int slice = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     const int col = slice * (LANES * VE) + l * VE;

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
     __shared__ float red[WAVES][32][33];             // per wave and lane with q < 2: 32 sums, padded
     __shared__ int n_active;
 
-    if (FUSED && (int)blockIdx.x == slices) {                 // (only after a fused step)
+    if (FUSED && (int)blockIdx.x == slices) {
         if (blockIdx.y == 0) commit_step<WAVES * 64>(fused, capacity, st);
         return;
     }
