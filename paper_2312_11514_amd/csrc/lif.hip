@@ -693,7 +693,7 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
         if (e != hipSuccess) rc = fail(LIF_HIP_ERROR, "device LDS limit: %s", hipGetErrorString(e));
-        lds_limit = std::min(lds_limit, 64 * 1024);      // no launch of this library asks for more than 64 KiB
+        lds_limit = std::min(lds_limit, 64 * 1024);      // (more would have to be allowed for the kernel first)
         if (!rc) rc = cfg->dtype == LIF_F32 ? choose_mask_tiles<float>(L, (size_t)lds_limit)
                                             : choose_mask_tiles<_Float16>(L, (size_t)lds_limit);
         if (rc) {
@@ -702,7 +702,10 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
         }
     }
     if (cfg->max_batch > 1) {
-        hipError_t e = launch_step_batch(L, StepArgs{}, true, nullptr);
+        StepArgs a = {};                                     // (the row width names the kernel form)
+        a.d = cfg->d_model;
+        a.batch = cfg->max_batch;
+        hipError_t e = launch_step_batch(L, a, true, nullptr);
         if (e != hipSuccess) {
             delete L;
             return fail(LIF_HIP_ERROR, "LDS of the batched step: %s", hipGetErrorString(e));

@@ -1302,7 +1302,7 @@ inline void launch_step1_as(const StepArgs& a, int grid, hipStream_t s) {
     else LIF_S1(16);
 #undef LIF_S1
 }
-// (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that)
+// (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that, for the kernel of a.d)
 template <typename T, bool GLU, bool MFMA>
 inline hipError_t launch_step_batch_as(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s) {
     const int ni = (a.d / Vec<T>::N + 63) / 64;

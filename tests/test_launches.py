@@ -1,0 +1,106 @@
+"""What the host side of liblif.so launches, looked at without a GPU: the library is loaded behind a stand-in for the HIP
+runtime (hip_host_stub.cpp) that runs nothing and writes every launch down.  In a process of its own, because the stand-in
+takes the place of the runtime."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+LDS_DEFAULT, LDS_MOST = 64 * 1024, 160 * 1024      # of a workgroup: without asking, and in all
+
+
+class Library:
+    """liblif.so over the stand-in (in the child process)."""
+
+    def __init__(self, stub):
+        self.stub = C.CDLL(stub, mode=C.RTLD_GLOBAL)
+        self.stub.stub_kernel.restype = C.c_char_p
+        sys.path.insert(0, ROOT)
+        from paper_2312_11514_amd import binding
+        self.b = binding
+        self.lib = C.CDLL(binding.LIB_PATH)
+        for name, (res, args) in binding.EXPORTS.items():
+            getattr(self.lib, name).restype, getattr(self.lib, name).argtypes = res, args
+        self.p = 1 << 32                           # a device address: 256-byte aligned, never read
+
+    def layer(self, d, F=1024, rank=16, k=3, capacity=512, max_batch=1, glu=0, f16=True, gate=False, full=False):
+        b, p = self.b, self.p
+        cfg = b.LifConfig(d, F, rank, k, capacity, max_batch, int(glu), b.LIF_F16 if f16 else b.LIF_F32, int(full), 0, int(gate), 0.0)
+        buf = b.LifBuffers(p, None if gate else p, None, p, p, p, p, p, p, self.lib.lif_workspace_bytes(C.byref(cfg)), None)
+        assert buf.workspace_bytes, (d, F, rank, max_batch, glu, f16)
+        h = C.c_void_p()
+        assert self.lib.lif_create(C.byref(cfg), C.byref(buf), C.byref(h)) == 0, self.lib.lif_last_error_string()
+        return h
+
+    def launches(self, call):
+        """[kernel, grid, block, dynamic LDS, LDS allowed] of every launch of a call, and what it returned"""
+        self.stub.stub_clear()
+        rc = call()
+        got = []
+        for i in range(self.stub.stub_launches()):
+            grid, block, lds, allowed = C.c_uint32(), C.c_uint32(), C.c_size_t(), C.c_int()
+            self.stub.stub_geometry(i, C.byref(grid), C.byref(block), C.byref(lds), C.byref(allowed))
+            got.append([self.stub.stub_kernel(i).decode(), grid.value, block.value, lds.value, allowed.value])
+        return rc, got
+
+    def step(self, h, batch, step_mask=None):
+        p = self.p
+        return self.launches(lambda: self.lib.lif_step(h, p, batch, p, p, step_mask or p + 4096, p, p, p, p, None))
+
+
+def _every_width():
+    """One row width for every kernel form: 64-lane loads per vector 1, 2, 4, 6, 8, 9, 12, 16, whole and ragged"""
+    for f16 in (True, False):
+        ve = 8 if f16 else 4
+        for ni in (1, 2, 3, 5, 7, 9, 11, 16):
+            for d in (64 * ni * ve, 64 * ni * ve - 3 * ve):
+                yield f16, d
+
+
+def child_lds(lib):
+    seen = 0
+    for f16, d in _every_width():
+        for glu, gate in ((0, False), (1, False), (0, True)):
+            most = min(8, 64 * 1024 // (d * (2 if f16 else 4)))
+            h = lib.layer(d, max_batch=most, glu=glu, f16=f16, gate=gate)
+            for batch in range(1, most + 1):
+                rc, got = lib.step(h, batch)
+                assert rc == 0 and got, (f16, d, glu, gate, batch)
+                for kernel, grid, block, lds, allowed in got:
+                    assert lds <= max(LDS_DEFAULT, allowed) and lds <= LDS_MOST, (f16, d, glu, gate, batch, kernel, lds, allowed)
+                    assert grid > 0 and block % 64 == 0
+                    seen += lds > LDS_DEFAULT
+            lib.lib.lif_destroy(h)
+    return seen
+
+
+def _run(tmp_path_factory, what):
+    stub = str(tmp_path_factory.getbasetemp() / "hip_host_stub.so")
+    if not os.path.exists(stub):
+        subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", stub, os.path.join(HERE, "hip_host_stub.cpp")], check=True)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, what], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+@pytest.fixture
+def child(tmp_path_factory):
+    from paper_2312_11514_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2312_11514_amd.build import build_library
+        build_library()
+    return lambda what: _run(tmp_path_factory, what)
+
+
+def test_lds_of_every_launch_is_allowed(child):
+    """A launch with more than 64 KiB of LDS needs the limit of its own kernel form raised (lif_create)."""
+    assert child("lds") > 0
+
+
+if __name__ == "__main__":
+    print(json.dumps(globals()["child_" + sys.argv[2]](Library(sys.argv[1]))))
