@@ -904,8 +904,9 @@ static int step_impl(lif_layer* L, const void* x_dev, int32_t batch, int32_t kee
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     const lif_config& c = L->cfg;
-    // (a pass of one token that is not kept: the token-granular update by itself)
-    if (batch == 1 && keep == 0) {
+    // Passes of tokens that go through the separate kernels: one token that is not kept, and a step mask that k_step_batch
+    // cannot read by 64-bit words.
+    if (keep >= 0 && ((batch == 1 && keep == 0) || (batch > 1 && (uintptr_t)step_mask_dev % 8))) {
         rc = lif_predict(L, x_dev, batch, masks_dev, step_mask_dev, stream);
         if (!rc) rc = lif_update_window_tokens(L, masks_dev, batch, keep, added_dev, n_added_dev, removed_dev, n_removed_dev, stream);
         if (!rc) rc = lif_load_bundles(L, added_dev, n_added_dev, removed_dev, n_removed_dev, stream);

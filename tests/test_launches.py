@@ -79,6 +79,20 @@ def child_lds(lib):
     return seen
 
 
+def child_step_mask(lib):
+    """Kernels launched for a pass of tokens, by the address of the step mask"""
+    p, got = lib.p, {}
+    for gate in (False, True):
+        h = lib.layer(512, max_batch=4, gate=gate)
+        for offset in (0, 8, 1, 2, 4, 7):
+            rc, seen = lib.launches(lambda: lib.lib.lif_step_tokens(h, p, 3, 2, p, p, p + 4096 + offset, p, p, p, p, None))
+            assert rc == 0, offset
+            got["%d%s" % (offset, " gate" if gate else "")] = [k[0] for k in seen]
+        assert lib.step(h, 3, p + 4096 + 4)[0] == lib.b.LIF_INVALID_ARG
+        lib.lib.lif_destroy(h)
+    return got
+
+
 def _run(tmp_path_factory, what):
     stub = str(tmp_path_factory.getbasetemp() / "hip_host_stub.so")
     if not os.path.exists(stub):
@@ -100,6 +114,15 @@ def child(tmp_path_factory):
 def test_lds_of_every_launch_is_allowed(child):
     """A launch with more than 64 KiB of LDS needs the limit of its own kernel form raised (lif_create)."""
     assert child("lds") > 0
+
+
+def test_step_mask_of_a_pass_may_have_any_address(child):
+    """The batched step reads the step mask by 64-bit words; a pass of tokens whose step mask is not aligned to them goes
+    through the separate kernels, which write it byte by byte and read the tokens' masks (lif_step refuses such a mask)."""
+    for case, kernels in child("step_mask").items():
+        by_words = any("k_step_batch" in k for k in kernels)
+        assert by_words == (int(case.split()[0]) % 8 == 0), (case, kernels)
+        assert by_words or [n for n in ("window_plan", "k_load", "ffn_up", "ffn_down") if not any(n in k for k in kernels)] == []
 
 
 if __name__ == "__main__":

@@ -163,6 +163,25 @@ def test_single_launch_batch_equals_calls(name):
     assert ref.layer.counters()["rows_moved"] > 0
 
 
+def test_pass_of_tokens_with_a_step_mask_at_an_odd_address():
+    """lif_step_tokens takes a step mask of any alignment (it then runs the separate kernels)."""
+    from tests.harness import GpuLayer
+    w, L, X, _ = _make("dynamic-window")
+    ref = GpuLayer(w, L, max_batch=4)
+    g = GpuLayer(w, L, max_batch=4, share=ref)
+    room = torch.zeros(w.d_ffn // 8 + 8, dtype=torch.uint8, device=g.dev)
+    g.layer.step_mask = room[3:3 + w.d_ffn // 8]
+    for lay in (ref.layer, g.layer):
+        lay.masks.zero_()
+    xd = ref.upload_x(X)
+    for t in range(5):
+        x = xd[2 * t:2 * t + 4]
+        ref.layer.step_tokens(x, ref.y, 4, 2)
+        g.layer.step_tokens(x, g.y, 4, 2)
+        assert _snapshot(g) == _snapshot(ref), f"pass {t}"
+    assert int(room[:3].sum()) == 0 and int(room[3 + w.d_ffn // 8:].sum()) == 0
+
+
 LOAD_CASES = {
     # name: ((dtype, glu, gate, d, F, rank, k, p, capacity, shrink, pairs), bundles in two parts)
     "32-byte-rows": (("f32", False, False, 4, 264, 4, 2, 0.2, 264, False, 0), False),
