@@ -455,9 +455,12 @@ hipError_t launch_step_batch(lif_layer* L, StepArgs a, bool allow, hipStream_t s
         a.spec = L->expected_rows > 0 ? 1 : 0;
     }
     const int grid = 1 + a.n_load + up;
-    if (c.dtype == LIF_F32) return (c.glu ? launch_step_batch_f32_glu : launch_step_batch_f32)(a, grid, lds, allow, s);
-    if (mfma) return (c.glu ? launch_step_batch_f16_mfma_glu : launch_step_batch_f16_mfma)(a, grid, lds, allow, s);
-    return (c.glu ? launch_step_batch_f16_glu : launch_step_batch_f16)(a, grid, lds, allow, s);
+    const bool gate = c.predictor == LIF_PRED_GATE;
+#define LIF_FORM(NAME) (gate ? launch_step_batch_##NAME##_gate : c.glu ? launch_step_batch_##NAME##_glu : launch_step_batch_##NAME##_plain)
+    if (c.dtype == LIF_F32) return LIF_FORM(f32)(a, grid, lds, allow, s);
+    if (mfma) return LIF_FORM(f16_mfma)(a, grid, lds, allow, s);
+    return LIF_FORM(f16)(a, grid, lds, allow, s);
+#undef LIF_FORM
 }
 
 void launch_ffn_up_mfma(lif_layer* L, const void* x, int batch, float* h, hipStream_t s) {

@@ -1256,26 +1256,28 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
 // The same for a batch of tokens or a pass of several, behind the launches of the predictor: bookkeeping (workgroup 0),
 // loaders, and the activation stage over the rows in use - on the matrix cores (MFMA: fp16, d a multiple of 32), else one
 // wave per row.  Dynamic LDS: step_batch_lds bytes.
-template <typename T, int NI, bool GLU, bool MFMA>
+// Registers (gfx950, as the compiler reports them): the loader role has more uniform values than the 106 scalar registers hold,
+// 97 to 148 of them live in lanes of vector registers (k_step1: 75 to 124).  None goes to memory, which would queue up behind the
+// host reads.  The predictor is a template parameter for that reason: a kernel with both forms of the role spilled 169 to 246
+// scalar registers and was 82 to 106 KB of code (41 to 60 KB each by itself), more than the 64 KB instruction cache of two compute units.
+template <typename T, int NI, bool GLU, bool GATE, bool MFMA>
 __global__ __launch_bounds__(256, 1) void k_step_batch(const StepArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_step[];
     const int block = blockIdx.x;
-    constexpr int MODE = MFMA ? kMfma : kDots;
     if (block <= a.n_load) {
         PlanLds& plan = *reinterpret_cast<PlanLds*>(smem_step);
         PostLds* post = reinterpret_cast<PostLds*>(smem_step + (sizeof(PlanLds) + 15) / 16 * 16);
-        if (!GLU && a.gact) cache_role<T, NI, GLU, true, MODE>(a, block, plan, post, smem_step + kStepXOff);
-        else cache_role<T, NI, GLU, false, MODE>(a, block, plan, post, smem_step + kStepXOff);
+        cache_role<T, NI, GLU, GATE, MFMA ? kMfma : kDots>(a, block, plan, post, smem_step + kStepXOff);
     } else if constexpr (MFMA) {
         const int tile = block - a.n_load - 1;
         ffn_up_mfma_tile_staged<GLU, kMfmaWaves>(
             (const _Float16*)a.matrix, a.bias, (const _Float16*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems, tile,
-            tile < a.spec, a.pointers, a.gact, a.F, a.st, smem_step);
+            tile < a.spec, a.pointers, GATE ? a.gact : nullptr, a.F, a.st, smem_step);
     } else {
         const int first = a.n_load + 1;
         ffn_up_role<T, NI, GLU, false>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems,
-                                       a.spec, block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers, a.gact, a.F,
-                                       a.st);
+                                       a.spec, block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers,
+                                       GATE ? a.gact : nullptr, a.F, a.st);
     }
 }
 // LDS of a workgroup of k_step_batch
@@ -1303,15 +1305,15 @@ inline void launch_step1_as(const StepArgs& a, int grid, hipStream_t s) {
 #undef LIF_S1
 }
 // (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that, for the kernel of a.d)
-template <typename T, bool GLU, bool MFMA>
+template <typename T, bool GLU, bool GATE, bool MFMA>
 inline hipError_t launch_step_batch_as(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s) {
     const int ni = (a.d / Vec<T>::N + 63) / 64;
 #define LIF_SB(NI)                                                                                                      \
     do {                                                                                                                 \
         if (allow)                                                                                                       \
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_step_batch<T, NI, GLU, MFMA>),                   \
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_step_batch<T, NI, GLU, GATE, MFMA>),             \
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepLdsLimit);                  \
-        hipLaunchKernelGGL((k_step_batch<T, NI, GLU, MFMA>), dim3(grid), dim3(256), lds, s, a);                          \
+        hipLaunchKernelGGL((k_step_batch<T, NI, GLU, GATE, MFMA>), dim3(grid), dim3(256), lds, s, a);                    \
         return hipSuccess;                                                                                               \
     } while (0)
     if (ni <= 1) LIF_SB(1);
@@ -1330,11 +1332,14 @@ void launch_step1_f16_gate(const StepArgs& a, int grid, hipStream_t s);
 void launch_step1_f32_plain(const StepArgs& a, int grid, hipStream_t s);
 void launch_step1_f32_glu(const StepArgs& a, int grid, hipStream_t s);
 void launch_step1_f32_gate(const StepArgs& a, int grid, hipStream_t s);
-hipError_t launch_step_batch_f16_mfma(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
-hipError_t launch_step_batch_f16_mfma_glu(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
-hipError_t launch_step_batch_f16(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16_plain(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
 hipError_t launch_step_batch_f16_glu(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
-hipError_t launch_step_batch_f32(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16_gate(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16_mfma_plain(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16_mfma_glu(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f16_mfma_gate(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f32_plain(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
 hipError_t launch_step_batch_f32_glu(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
+hipError_t launch_step_batch_f32_gate(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s);
 
 }  // namespace lif

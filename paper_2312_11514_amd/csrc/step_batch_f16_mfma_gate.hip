@@ -1,0 +1,7 @@
+#include "lif_step1.h"
+
+namespace lif {
+hipError_t launch_step_batch_f16_mfma_gate(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s) {
+    return launch_step_batch_as<_Float16, false, true, true>(a, grid, lds, allow, s);
+}
+}  // namespace lif

@@ -1,0 +1,7 @@
+#include "lif_step1.h"
+
+namespace lif {
+hipError_t launch_step_batch_f32_gate(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s) {
+    return launch_step_batch_as<float, false, true, false>(a, grid, lds, allow, s);
+}
+}  // namespace lif
