@@ -602,14 +602,26 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         hole = s < n2 && dead;
         fill = s >= n2 && s < n && !dead;
     };
-    auto count_block = [&](int b, int id) {
-        bool hole, fill;
-        flags_of(b, id, hole, fill);
-        const int ch = __popcll(__ballot(hole)), cf = __popcll(__ballot(fill));
-        if (lane == 0) {
+    // The dead slots of block b are kept by the wave that classifies it (number i = b / 4 of its blocks) in lane i mod 64 of
+    // dead[i / 64]: looked up again in every pass, the owners past the staged ones cost a memory round trip per block (OPT shape, 4
+    // tokens: 140 -> 125 us a step at 15700 rows, 124 -> 111 at 14300; one token 91 -> 88 at 6600; up to 4096 rows the same).
+    unsigned long long dead[4] = {0ull, 0ull, 0ull, 0ull};
+    auto classify = [&](int b, int id, unsigned long long removed) {         // removed: word id / 64 of L.rem
+        const int i = b >> 2, s = b * kWave + lane;
+        const unsigned long long m = __ballot((unsigned)id >= (unsigned)F || ((removed >> (id & 63)) & 1ull));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dead[r] = (i == r * kWave + lane) ? m : dead[r];
+        const int ch = __popcll(__ballot(s < n2) & m), cf = __popcll(__ballot(s >= n2 && s < n) & ~m);
+        if (lane == 0 && b < nblk) {
             L.blk_h[b] = (uint16_t)ch;
             L.blk_f[b] = (uint16_t)cf;
         }
+    };
+    auto dead_of = [&](int b) -> unsigned long long {            // uniform; never under a condition that differs between lanes
+        const int i = b >> 2;
+        const unsigned long long v = i < 64 ? dead[0] : i < 128 ? dead[1] : i < 192 ? dead[2] : dead[3];
+        return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), i & 63) << 32) |
+               (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, i & 63);
     };
 
     // ---- masks -> window -> id list -> first host read ----
@@ -729,13 +741,26 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     const bool alone = wg > 0 && nblk <= kWave;
     int H = 0;
     if (tot_r > 0 && !alone) {                                   // uniform
+        static_assert(kPtrLds / kWave % 32 == 0, "a round is staged as a whole or not at all");
+#pragma unroll 1
         for (int b0 = wave; b0 < nblk; b0 += 4 * 8) {
             int id[8];
+            if (b0 < kPtrLds / kWave) {                          // uniform
 #pragma unroll
-            for (int q = 0; q < 8; ++q) id[q] = (b0 + q * 4 < nblk) ? owner(b0 + q * 4) : -1;
+                for (int q = 0; q < 8; ++q) id[q] = L.ptr[(b0 + q * 4) * kWave + lane];
+            } else {
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (b0 + q * 4 < nblk) count_block(b0 + q * 4, id[q]);
+                for (int q = 0; q < 8; ++q) id[q] = a.pointers[min((b0 + q * 4) * kWave + lane, capacity - 1)];
+            }
+#pragma unroll
+            for (int g = 0; g < 8; g += 4) {
+                unsigned long long w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w[q] = L.rem[min((unsigned)id[g + q] >> 6, 1023u)];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)                      // (one token: 0.7 us faster with the branch, a batch 0.6 without)
+                    if (MODE != kOneToken || b0 + (g + q) * 4 < nblk) classify(b0 + (g + q) * 4, id[g + q], w[q]);
+            }
         }
         lds_barrier();
         {                                                        // prefix over the blocks, bpt consecutive ones per thread
@@ -763,26 +788,31 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             const int hblk = (n2 + kWave - 1) >> 6;              // blocks with slots below the tail
 #pragma unroll 1
             for (int b = wave; b < hblk; b += 4) {
-                bool hole, fill;
-                flags_of(b, owner(b), hole, fill);
-                const unsigned long long bh = __ballot(hole);
-                if (hole) {
+                const int s = b * kWave + lane;
+                const unsigned long long bh = dead_of(b) & __ballot(s < n2);
+                if ((bh >> lane) & 1ull) {
                     const int pos = L.blk_h[b] + __popcll(bh & lt);
-                    if (in_lds) L.hole[pos] = (uint16_t)(b * kWave + lane);
-                    else a.hole_list[pos] = b * kWave + lane;
+                    if (in_lds) L.hole[pos] = (uint16_t)s;
+                    else a.hole_list[pos] = s;
                 }
             }
             if (in_lds) lds_barrier();
             else __syncthreads();
         }
     }
-    auto fill_dst = [&](int c0) {                                // destinations of the tail slots of items [c0, ...) (-1: dead)
+    auto fill_dst = [&](int c0, auto again_c) {                  // destinations of the tail slots of items [c0, ...) (kNoDst: dead)
         const bool in_lds = H <= kHoleFew;
         const int tail = (n2 + c0) >> 6;                         // first block with slots of these items
 #pragma unroll 1
         for (int b = tail + ((wave - tail) & 3); b < nblk; b += 4) {
             bool hole, fill;
-            flags_of(b, owner(b), hole, fill);
+            if constexpr (decltype(again_c)::value) {            // (later pieces: `dead` is not kept through the load loop)
+                flags_of(b, owner(b), hole, fill);
+            } else {
+                const int s = b * kWave + lane;
+                const unsigned long long m = dead_of(b);         // (by the whole wave)
+                fill = s >= n2 && s < n && !((m >> lane) & 1ull);
+            }
             const unsigned long long bf = __ballot(fill);
             const int q = b * kWave + lane - n2;
             if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
@@ -842,7 +872,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         if (lane == 0) __hip_atomic_store(&L.planned, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     if (wg > 0 && !alone) {
-        if (tot_r > 0) fill_dst(0);
+        if (tot_r > 0) fill_dst(0, std::false_type{});
         lds_barrier();
     }
     if (loads && lw < (PAIRED ? 2 * tot_a : tot_a))              // unit lw (below kListItems)
@@ -1112,7 +1142,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             lds_barrier();
             fill_ids(c0);
             if (tid == 0) L.planned = L.classified = 0;
-            if (tot_r > 0 && !alone) fill_dst(c0);
+            if (tot_r > 0 && !alone) fill_dst(c0, std::true_type{});
             lds_barrier();
         }
         const int n_a = min(max(tot_a - c0, 0), kListItems), n_r = min(max(tot_r - c0, 0), kListItems);     // of this piece

@@ -22,6 +22,7 @@ CASES = {
     "dynamic-window": ("f16", False, False, 64, 4160, 16, 9, 0.1, 900, True, 0),
     "dynamic-window-two-words": ("f16", False, False, 64, 17000, 64, 4, 0.1, 4500, True, 0),
     "slot-of-many-items": ("f16", False, False, 520, 6000, 32, 2, 0.35, 6000, False, 1),
+    "most-rows": ("f16", False, False, 16, 65536, 16, 1, 0.85, 65536, False, 0),
     "many-holes": ("f16", False, False, 16, 40000, 64, 1, 0.5, 40000, False, 0),
 }
 
@@ -119,6 +120,8 @@ BATCH_CASES = {
     "mfma-dynamic": (("f16", False, False, 64, 4160, 16, 9, 0.03, 1100, True, 0), 4),
     "mfma-many-rows": (("f16", True, False, 32, 20032, 64, 2, 0.1, 18000, False, 0), 6),
     "mfma-widest-glu": (("f16", True, False, 8192, 384, 16, 2, 0.1, 300, False, 2), 4),
+    "mfma-most-rows": (("f16", False, False, 32, 65536, 16, 2, 0.35, 65536, False, 0), 4),
+    "dots-many-rows": (("f16", False, False, 24, 20032, 16, 2, 0.2, 20032, False, 0), 3),
     "dots": (("f16", False, False, 1032, 1088, 40, 3, 0.06, 900, False, 0), 3),
     "dots-glu": (("f16", True, False, 264, 704, 24, 2, 0.05, 600, False, 1), 8),
     "dots-gate": (("f32", False, True, 260, 192, 8, 2, 0.05, 192, False, 0), 2),
