@@ -451,7 +451,8 @@ hipError_t launch_step_batch(lif_layer* L, StepArgs a, bool allow, hipStream_t s
         up = (c.capacity_rows + 15) / 16;
         a.spec = L->expected_rows > 0 ? mfma_hint_tiles(L) : 0;
     } else {
-        up = up_blocks(L);
+        const int waves = step_batch_waves((c.d_model / vec_elems(c) + 63) / 64, c.glu, mfma, lds);
+        up = (4 * up_blocks(L) + waves - 1) / waves;
         a.spec = L->expected_rows > 0 ? 1 : 0;
     }
     const int grid = 1 + a.n_load + up;

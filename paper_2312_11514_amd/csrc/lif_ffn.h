@@ -34,7 +34,7 @@ namespace lif {
 // the activation of slot s for token t is then gact[t][pointers[s]] * (up_s . x_t), gact [batch x gact_n];
 // gact_n = d_ffn bounds the lookup.  A single token (XREG) leaves up_s . x and k_ffn_down1 multiplies: a fused step
 // computes both in the same launch.
-template <typename T, int NI, bool GLU, bool XREG>
+template <typename T, int NI, bool GLU, bool XREG, int WAVES = 4>
 __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const float* __restrict__ bias,
                                             const T* __restrict__ x, float* __restrict__ h, int d, int batch,
                                             int capacity, size_t row_elems, int spec, int block, int nblocks,
@@ -47,7 +47,7 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
     V* xs = reinterpret_cast<V*>(smem_raw);
     const int tid = threadIdx.x, lane = tid & 63;
     const int nvec = d / VE;
-    const int gw = block * 4 + (tid >> 6), nw = nblocks * 4;
+    const int gw = block * WAVES + (tid >> 6), nw = nblocks * WAVES;
     const V* xv = reinterpret_cast<const V*>(x);
 
     V xr[XREG ? NI : 1];
@@ -79,10 +79,10 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
     }
     const int err = st->cur.error;
     const int n = *n_ptr;
-    if (err || block * 4 >= n) return;               // whole workgroup has no row (uniform)
+    if (err || block * WAVES >= n) return;           // whole workgroup has no row (uniform)
 
     if (!XREG) {
-        for (int i = tid; i < batch * nvec; i += 256) xs[i] = xv[i];
+        for (int i = tid; i < batch * nvec; i += WAVES * 64) xs[i] = xv[i];
         __syncthreads();
     }
 

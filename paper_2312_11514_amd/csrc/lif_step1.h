@@ -1290,24 +1290,25 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
 // 97 to 148 of them live in lanes of vector registers (k_step1: 75 to 124).  None goes to memory, which would queue up behind the
 // host reads.  The predictor is a template parameter for that reason: a kernel with both forms of the role spilled 169 to 246
 // scalar registers and was 82 to 106 KB of code (41 to 60 KB each by itself), more than the 64 KB instruction cache of two compute units.
-template <typename T, int NI, bool GLU, bool GATE, bool MFMA>
-__global__ __launch_bounds__(256, 1) void k_step_batch(const StepArgs a) {
+template <typename T, int NI, bool GLU, bool GATE, bool MFMA, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 1) void k_step_batch(const StepArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_step[];
     const int block = blockIdx.x;
     if (block <= a.n_load) {
+        if (WAVES > 4 && threadIdx.x >= 256) return;             // (a barrier waits for the waves that are left)
         PlanLds& plan = *reinterpret_cast<PlanLds*>(smem_step);
         PostLds* post = reinterpret_cast<PostLds*>(smem_step + (sizeof(PlanLds) + 15) / 16 * 16);
         cache_role<T, NI, GLU, GATE, MFMA ? kMfma : kDots>(a, block, plan, post, smem_step + kStepXOff);
     } else if constexpr (MFMA) {
         const int tile = block - a.n_load - 1;
-        ffn_up_mfma_tile_staged<GLU, kMfmaWaves>(
+        ffn_up_mfma_tile_staged<GLU, WAVES>(
             (const _Float16*)a.matrix, a.bias, (const _Float16*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems, tile,
             tile < a.spec, a.pointers, GATE ? a.gact : nullptr, a.F, a.st, smem_step);
     } else {
         const int first = a.n_load + 1;
-        ffn_up_role<T, NI, GLU, false>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems,
-                                       a.spec, block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers,
-                                       GATE ? a.gact : nullptr, a.F, a.st);
+        ffn_up_role<T, NI, GLU, false, WAVES>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems,
+                                              a.spec, block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers,
+                                              GATE ? a.gact : nullptr, a.F, a.st);
     }
 }
 // LDS of a workgroup of k_step_batch
@@ -1334,16 +1335,33 @@ inline void launch_step1_as(const StepArgs& a, int grid, hipStream_t s) {
     else LIF_S1(16);
 #undef LIF_S1
 }
-// (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that, for the kernel of a.d)
+// Waves of a workgroup of k_step_batch: 4, or 8 where the LDS of a loader (x of the tokens and staged rows) leaves room for one
+// workgroup per compute unit.  The activation workgroups of the launch carry the same LDS, and four waves that read a row each
+// reach a fraction of the bandwidth, which shows where few rows are added and the load does not cover them.  fp32 rows, us a
+// step with 4 -> 8 waves (rows in use, rows added): d = 1288, 8 tokens: (9277, 0) 77.7 -> 57.0, (9578, 47) 88.3 -> 71.2, (13408,
+// 477) 157.8 -> 156.9; d = 2048, gated, 8 tokens: (4699, 0) 71.8 -> 55.1, (6444, 304) 187.8 -> 187.1; d = 2048, 4 tokens: (6221,
+// 0) 51.9 -> 43.2.  With room for two workgroups four waves are better (d = 1288, 3 tokens, (929, 0): 25.7 against 26.6).
+// The matrix-core stage keeps 4: it is at least as fast as in a launch of its own.  Gated rows of more than 12 KiB a vector
+// would spill registers at 8 waves.
+constexpr int step_batch_most_waves(int ni, bool glu, bool mfma) { return mfma || ni <= 2 || (glu && ni > 12) ? 4 : 8; }
+inline int step_batch_waves(int ni, bool glu, bool mfma, size_t lds) { return lds > kStepLdsLimit / 2 ? step_batch_most_waves(ni, glu, mfma) : 4; }
+
+// (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that, for the kernels of a.d)
 template <typename T, bool GLU, bool GATE, bool MFMA>
 inline hipError_t launch_step_batch_as(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s) {
     const int ni = (a.d / Vec<T>::N + 63) / 64;
 #define LIF_SB(NI)                                                                                                      \
     do {                                                                                                                 \
-        if (allow)                                                                                                       \
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_step_batch<T, NI, GLU, GATE, MFMA>),             \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepLdsLimit);                  \
-        hipLaunchKernelGGL((k_step_batch<T, NI, GLU, GATE, MFMA>), dim3(grid), dim3(256), lds, s, a);                    \
+        constexpr int kMost = step_batch_most_waves(NI, GLU, MFMA);                                                      \
+        const auto few = &k_step_batch<T, NI, GLU, GATE, MFMA, 4>, many = &k_step_batch<T, NI, GLU, GATE, MFMA, kMost>;  \
+        if (allow) {                                                                                                     \
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(few),                                 \
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepLdsLimit);    \
+            return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(many),                        \
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepLdsLimit); \
+        }                                                                                                                \
+        const int waves = step_batch_waves(NI, GLU, MFMA, lds);                                                          \
+        hipLaunchKernelGGL(waves == 4 ? few : many, dim3(grid), dim3(waves * 64), lds, s, a);                            \
         return hipSuccess;                                                                                               \
     } while (0)
     if (ni <= 1) LIF_SB(1);

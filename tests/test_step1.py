@@ -122,6 +122,10 @@ BATCH_CASES = {
     "mfma-widest-glu": (("f16", True, False, 8192, 384, 16, 2, 0.1, 300, False, 2), 4),
     "mfma-most-rows": (("f16", False, False, 32, 65536, 16, 2, 0.35, 65536, False, 0), 4),
     "dots-many-rows": (("f16", False, False, 24, 20032, 16, 2, 0.2, 20032, False, 0), 3),
+    "dots-eight-waves": (("f32", False, False, 1288, 704, 16, 2, 0.05, 600, False, 0), 8),
+    "dots-eight-waves-gate": (("f32", False, True, 2564, 192, 8, 2, 0.1, 192, False, 0), 6),
+    "dots-eight-waves-glu": (("f16", True, False, 6152, 256, 16, 2, 0.1, 256, False, 0), 4),
+    "dots-widest-glu": (("f32", True, False, 4096, 256, 16, 2, 0.1, 256, False, 0), 4),
     "dots": (("f16", False, False, 1032, 1088, 40, 3, 0.06, 900, False, 0), 3),
     "dots-glu": (("f16", True, False, 264, 704, 24, 2, 0.05, 600, False, 1), 8),
     "dots-gate": (("f32", False, True, 260, 192, 8, 2, 0.05, 192, False, 0), 2),
