@@ -110,15 +110,17 @@ def _ptr(t):
     return t.data_ptr() if t is not None else None
 
 
-def _stream():
-    return _raw_stream(_current_device())
-
-
 def _bind_torch():
-    """torch is imported when the library is loaded, not when this module is (argument checks need no GPU)."""
-    global _raw_stream, _current_device
+    """torch is imported when the library is loaded, not when this module is (argument checks need no GPU).  The two
+    functions behind torch.cuda.current_stream() are private: a torch without them takes the public way."""
+    global _stream
     import torch
-    _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw_stream and device:
+        _stream = lambda: raw_stream(device())
+    else:
+        _stream = lambda: torch.cuda.current_stream().cuda_stream
 
 
 def profile_read(src, nbytes, sink):

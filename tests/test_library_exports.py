@@ -54,3 +54,18 @@ def test_workspace_size_and_config_validation_without_gpu():
     h = ctypes.c_void_p()
     assert lib.lif_create(ctypes.byref(ok), None, ctypes.byref(h)) == b.LIF_INVALID_ARG
     assert b"null" in lib.lif_last_error_string()
+
+
+def test_loads_with_a_torch_that_lacks_the_private_stream_functions(monkeypatch):
+    """The stream handle is read through private functions of torch where there are such, else the public way."""
+    import types
+    import torch
+    from paper_2312_11514_amd import binding as b
+    b.load_library()
+    monkeypatch.setattr(b, "_lib", None)
+    monkeypatch.setattr(b, "_stream", b._stream)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    b.load_library()
+    assert b._stream() == 1234
