@@ -27,8 +27,8 @@ CASES = {
 }
 
 
-def _make(name, seed=5):
-    dtype, glu, gate, d, F, rank, k, p, cap, shrink, pairs = CASES[name]
+def _make(name, case=None, seed=5):
+    dtype, glu, gate, d, F, rank, k, p, cap, shrink, pairs = case or CASES[name]
     w = wl.scaled(wl.WORKLOADS["C1"], name=name, d_model=d, d_ffn=F, rank=rank, window_k=k, p_active=p, dtype=dtype,
                   glu=glu or gate, gate_resident=gate, capacity_rows=cap, shrink=shrink)
     rng = np.random.default_rng(seed)
@@ -62,13 +62,14 @@ def test_single_launch_step_equals_four_calls(name):
     w, L, X, pairs = _make(name)
     ref = GpuLayer(w, L)
     runs = []
-    for polls in (None, 0):
+    for polls, hint in ((None, 0), (0, 0), (None, 1), (None, w.capacity_rows)):     # (a hint: rows requested ahead of the count)
         g = GpuLayer(w, L, share=ref)
         if polls is not None:
             g.layer.set_handoff_polls(polls)
         if pairs:
             g.layer.set_loader_pairs(pairs)
-        runs.append((polls, g))
+        g.layer.set_expected_rows(hint)
+        runs.append(((polls, hint), g))
     xd = ref.upload_x(X)
     for again in range(2):                          # the second time after a reset: the stamps start again
         for g in [ref] + [g for _, g in runs]:
@@ -82,7 +83,7 @@ def test_single_launch_step_equals_four_calls(name):
                 g.layer.step(xd[t], g.y)
                 got = _snapshot(g)
                 for i, (a, b) in enumerate(zip(got, want)):
-                    assert a == b, f"{name}: token {t}, polls {polls}, item {i}"
+                    assert a == b, f"{name}: token {t}, polls and hint {polls}, item {i}"
     moved = ref.layer.counters()["rows_moved"]
     assert moved > 0 or name in ("one-tile", "more-columns-than-tiles")
 
@@ -138,36 +139,102 @@ def test_single_launch_batch_equals_calls(name):
     """Batches (lif_step) and passes of several tokens (lif_step_tokens, every number of kept tokens) the same way."""
     from tests.harness import GpuLayer
     case, batch = BATCH_CASES[name]
-    CASES[name] = case
-    w, L, _, pairs = _make(name)
-    del CASES[name]
+    w, L, _, pairs = _make(name, case)
     X = wl.make_inputs(w, tokens=12 * batch)
     ref = GpuLayer(w, L, max_batch=batch)
-    g = GpuLayer(w, L, max_batch=batch, share=ref)
-    for lay in (ref.layer, g.layer):                # (fewer tokens than max_batch leave the rest of these alone)
+    runs = []
+    for hint in (0, 1, w.capacity_rows):            # (a hint: rows requested ahead of the count)
+        g = GpuLayer(w, L, max_batch=batch, share=ref)
+        if pairs:
+            g.layer.set_loader_pairs(pairs)
+        g.layer.set_expected_rows(hint)
+        runs.append((hint, g))
+    for lay in [ref.layer] + [g.layer for _, g in runs]:        # (fewer tokens than max_batch leave the rest of these alone)
         lay.masks.zero_()
-    if pairs:
-        g.layer.set_loader_pairs(pairs)
     xd = ref.upload_x(X)
     for t in range(12):
         x = xd[t * batch:(t + 1) * batch]
         tokens = batch if t % 4 else 1 + t % batch
         keep = t % (tokens + 1)
         print(f"{name}: step {t} tokens {tokens}", flush=True)
-        if t % 3 == 0 or w.d_ffn % 64:
+        whole = t % 3 == 0 or w.d_ffn % 64
+        if whole:
             ref.layer.step_calls(x, ref.y, batch=tokens)
-            g.layer.step(x, g.y, batch=tokens)
         else:
             ref.layer.predict(x, batch=tokens)
             ref.layer.update_window_tokens(tokens, keep)
             ref.layer.load_bundles()
             ref.layer.sparse_ffn(x, ref.y, batch=tokens)
-            g.layer.step_tokens(x, g.y, tokens, keep)
-        want, got = _snapshot(ref), _snapshot(g)
+        want = _snapshot(ref)
         assert want[0]["error"] == 0
-        for i, (a, b) in enumerate(zip(got, want)):
-            assert a == b, f"{name}: step {t}, tokens {tokens}, keep {keep}, item {i}"
+        for hint, g in runs:
+            if whole:
+                g.layer.step(x, g.y, batch=tokens)
+            else:
+                g.layer.step_tokens(x, g.y, tokens, keep)
+            for i, (a, b) in enumerate(zip(_snapshot(g), want)):
+                assert a == b, f"{name}: step {t}, tokens {tokens}, keep {keep}, hint {hint}, item {i}"
     assert ref.layer.counters()["rows_moved"] > 0
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+def test_two_layers_step_on_two_streams(batch):
+    """Layers share nothing: steps of two of them in flight at once leave what each leaves by itself."""
+    from tests.harness import GpuLayer
+    w, L, X, _ = _make("dots", BATCH_CASES["dots"][0])
+    X = wl.make_inputs(w, tokens=20 * batch)
+    alone = GpuLayer(w, L, max_batch=batch)
+    pair = [GpuLayer(w, L, max_batch=batch, share=alone) for _ in range(2)]
+    xd = alone.upload_x(X)
+    ys = [[torch.zeros_like(alone.y) for _ in range(20)] for _ in range(3)]
+    streams = [torch.cuda.Stream() for _ in pair]
+    torch.cuda.synchronize()
+    print(f"two streams, batch {batch}", flush=True)
+    for t in range(20):                             # the second layer goes through the tokens the other way round
+        for i, (g, s) in enumerate(zip(pair, streams)):
+            at = t if i == 0 else 19 - t
+            with torch.cuda.stream(s):
+                g.layer.step(xd[at * batch:(at + 1) * batch], ys[i][t], batch=batch)
+    torch.cuda.synchronize()
+    got = [_snapshot(g) for g in pair]
+    for i in range(2):
+        alone.layer.reset()
+        for t in range(20):
+            at = t if i == 0 else 19 - t
+            alone.layer.step_calls(xd[at * batch:(at + 1) * batch], ys[2][t], batch=batch)
+        want = _snapshot(alone)
+        assert got[i][0] == want[0] and got[i][2:] == want[2:]
+        assert all(torch.equal(a, b) for a, b in zip(ys[i], ys[2]))
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+def test_graph_replay_across_resets(batch):
+    """A captured step replayed with eager steps and resets in between: the stamps of what workgroups hand over come from
+    device state, not from what was captured."""
+    from tests.harness import GpuLayer
+    w, L, X, _ = _make("dots", BATCH_CASES["dots"][0])
+    X = wl.make_inputs(w, tokens=8 * batch)
+    ref = GpuLayer(w, L, max_batch=batch)
+    g = GpuLayer(w, L, max_batch=batch, share=ref)
+    xd = ref.upload_x(X).view(8, batch, -1)
+    stage = xd[0].clone()
+    g.layer.step(stage, g.y, batch=batch)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.layer.step(stage, g.y, batch=batch)
+    for again in range(3):
+        for lay in (ref.layer, g.layer):
+            lay.reset()
+        for t in range(8):
+            print(f"graph, batch {batch}: sequence {again} token {t}", flush=True)
+            ref.layer.step_calls(xd[t], ref.y, batch=batch)
+            if (t + again) % 3 == 2:
+                g.layer.step(xd[t], g.y, batch=batch)
+            else:
+                stage.copy_(xd[t])
+                graph.replay()
+            assert _snapshot(g) == _snapshot(ref), f"sequence {again} token {t}"
 
 
 def test_pass_of_tokens_with_a_step_mask_at_an_odd_address():
@@ -206,9 +273,7 @@ def test_load_bundles_chunks_and_lists(name):
     from oracle import lif_oracle as O
     from tests.harness import GpuLayer, compare_step
     case, unbundled = LOAD_CASES[name]
-    CASES[name] = case
-    w, L, X, pairs = _make(name)
-    del CASES[name]
+    w, L, X, pairs = _make(name, case)
     gpu = GpuLayer(w, L, unbundled=unbundled)
     if pairs:
         gpu.layer.set_loader_pairs(pairs)
