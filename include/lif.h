@@ -293,16 +293,20 @@ int lif_step_tokens(lif_layer* layer, const void* x_dev, int32_t n_tokens, int32
 
 /*
  * Performance hint: the number of rows the cache
- * typically holds (for example the mean num_used of an earlier run).  lif_sparse_ffn then
- * launches that many waves and lets each request its first row before the device-side row
+ * typically holds (for example the mean num_used of an earlier run).  lif_sparse_ffn and the fused steps then
+ * launch that many waves and let each request its first row before the device-side row
  * count has arrived.  0 removes the hint.  Results never depend on it.
  */
 int lif_set_expected_rows(lif_layer* layer, int32_t rows);
 
 /*
- * Performance knob of lif_step's bundle gather (Section 3.3 item 2): the number of loader wave pairs (one bundle in
- * flight per pair), 1..64; 0 restores the default, which is chosen from the bundle size (320 KiB of reads
- * outstanding, within 5..32 pairs).  Results never depend on it.
+ * Performance knob of the bundle gather (Section 3.3 item 2) in lif_step, lif_step_tokens and lif_load_bundles: pairs of
+ * loader waves, one bundle in flight per pair, 1..64; 0 restores the default.  The default comes from the bundle size,
+ * as many pairs as keep so many bytes of host reads outstanding, and at least 5:
+ *   a step of one token            320 KiB, at most 32 pairs
+ *   a step or pass of several      768 KiB, at most 48 pairs
+ *   lif_load_bundles               640 KiB, at most 32 pairs
+ * Results never depend on it.
  */
 int lif_set_loader_pairs(lif_layer* layer, int32_t pairs);
 

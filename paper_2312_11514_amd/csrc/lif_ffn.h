@@ -18,7 +18,7 @@
 
 namespace lif {
 
-// grid-stride over rows, block = 256 (4 waves, one row per wave at a time).
+// grid-stride over rows, one row per wave at a time; block = 256 by itself, 256 or 512 in k_step_batch.
 // NI = 16-byte loads per lane and vector (ceil(d / (64 * VE))).
 // XREG (batch 1): every lane keeps its fragments of x in registers, loaded straight from
 // global memory.  Otherwise x is staged once per workgroup in LDS (dynamic LDS: batch * d
@@ -27,8 +27,7 @@ namespace lif {
 // capacity is always valid memory; the result is dropped if the slot is not in use), so the
 // state, x and the first rows travel in one round trip.  The host only asks for this when it
 // was told how many rows to expect and has sized the grid to that many waves.
-// `block` / `nblocks`: index and count of the workgroups that share this role; `n_ptr`: device
-// address of the number of rows to cover (num_used, or the rows kept by a pending deletion).
+// `block` / `nblocks`: index and count of the workgroups (of WAVES waves) that share this role.
 // `gact` (may be null, plain bundles only): per-neuron gate activations relu(gate_i . x + b_i) written by the
 // gate predictor (Appendix, Llama 2, "Alternative approaches": the resident gate projection is the predictor);
 // the activation of slot s for token t is then gact[t][pointers[s]] * (up_s . x_t), gact [batch x gact_n];
@@ -38,7 +37,7 @@ template <typename T, int NI, bool GLU, bool XREG, int WAVES = 4>
 __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const float* __restrict__ bias,
                                             const T* __restrict__ x, float* __restrict__ h, int d, int batch,
                                             int capacity, size_t row_elems, int spec, int block, int nblocks,
-                                            const int32_t* __restrict__ n_ptr, const int32_t* __restrict__ pointers,
+                                            const int32_t* __restrict__ pointers,
                                             const float* __restrict__ gact, int gact_n,
                                             const DevState* __restrict__ st) {
     using V = typename Vec<T>::type;
@@ -78,7 +77,7 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
         if (ok) bs = !gact ? bias[gw] : XREG ? 0.f : gact[min(max(pointers[gw], 0), gact_n - 1)];      // of token 0
     }
     const int err = st->cur.error;
-    const int n = *n_ptr;
+    const int n = st->cur.num_used;
     if (err || block * WAVES >= n) return;           // whole workgroup has no row (uniform)
 
     if (!XREG) {
@@ -168,7 +167,7 @@ __global__ __launch_bounds__(256) void k_ffn_up(const T* __restrict__ matrix, co
                                                 const int32_t* __restrict__ pointers, const float* __restrict__ gact,
                                                 int gact_n, const DevState* __restrict__ st) {
     ffn_up_role<T, NI, GLU, XREG>(matrix, bias, x, h, d, batch, capacity, row_elems, spec, blockIdx.x, gridDim.x,
-                                  &st->cur.num_used, pointers, gact, gact_n, st);
+                                  pointers, gact, gact_n, st);
 }
 
 // After a fused step (k_step1, k_step_batch): the activations, slot owners and biases of the rows that it wrote, valid for the slots

@@ -1,4 +1,5 @@
-// One decode step of a single token, up to the down projection, in one launch (lif_step, batch 1).
+// One step up to the down projection: of a single token in one launch (k_step1: lif_step and lif_step_tokens, batch 1), of a
+// batch or a pass of several tokens in one launch behind the two of the predictor (k_step_batch).
 //
 // A step is a chain of small dependent stages in front of one long one, the host-link gather of the new bundles
 // (Section 3.3 item 2).  As separate launches every short stage costs 4 to 6 us on gfx950: 1.6 us of launch, a memory
@@ -27,8 +28,9 @@
 //
 // What bounds it: the host link, at 56 GB/s (a copy of 256 MiB by the runtime reaches 57), behind a chain of about 8 us
 // (x A 3, masks 3, window and first ids 2) and in front of the down projection.  Measured on gfx950, one decode token,
-// before (five launches) -> now (this kernel and the down projection): fp32 d = 256, F = 1024: 22 -> 15 us; OPT-6.7B
-// shape 65 -> 58; Falcon-7B shape 151 -> 141; Llama-2 shape gated 149 -> 137, with the gate resident 113 -> 110.
+// with five launches -> with this kernel and the down projection, side by side in one run (runs on other machines differ by up
+// to 4 %): fp32 d = 256, F = 1024: 23.4 -> 14.4 us; OPT-6.7B shape 65.3 -> 59.1; Falcon-7B shape 149.5 -> 139.4; Llama-2 shape
+// gated, from a graph, 148.7 -> 136.6, with the gate resident 112.8 -> 109.1.  Eight tokens, Llama-2 shape gated: 276.8 -> 253.6.
 #pragma once
 
 #include "lif_ffn.h"
@@ -1279,7 +1281,7 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
     } else {
         const int first = a.n_pred + a.n_load + 1;
         ffn_up_role<T, NI, GLU, true>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, 1, a.capacity, a.row_elems, a.spec,
-                                      block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers, a.gact, a.F, a.st);
+                                      block - first, gridDim.x - first, a.pointers, a.gact, a.F, a.st);
     }
 }
 
@@ -1307,7 +1309,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_step_batch(const StepArgs a) 
     } else {
         const int first = a.n_load + 1;
         ffn_up_role<T, NI, GLU, false, WAVES>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, a.batch, a.capacity, a.row_elems,
-                                              a.spec, block - first, gridDim.x - first, &a.st->cur.num_used, a.pointers,
+                                              a.spec, block - first, gridDim.x - first, a.pointers,
                                               GATE ? a.gact : nullptr, a.F, a.st);
     }
 }
