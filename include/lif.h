@@ -303,7 +303,8 @@ int lif_set_expected_rows(lif_layer* layer, int32_t rows);
  * Performance knob of the bundle gather (Section 3.3 item 2) in lif_step, lif_step_tokens and lif_load_bundles: pairs of
  * loader waves, one bundle in flight per pair, 1..64; 0 restores the default.  The default comes from the bundle size,
  * as many pairs as keep so many bytes of host reads outstanding, and at least 5:
- *   a step of one token            320 KiB, at most 32 pairs
+ *   a step of one token            320 KiB, at most 32 pairs; vectors of at most 2 KiB (a pair then has two bundles in
+ *                                  flight): 256 KiB, at most 64 pairs
  *   a step or pass of several      768 KiB, at most 48 pairs
  *   lif_load_bundles               640 KiB, at most 32 pairs
  * Results never depend on it.

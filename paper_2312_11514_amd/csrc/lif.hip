@@ -46,11 +46,16 @@ int fail(int code, const char* fmt, const char* detail = "") {
 // the time in which a loader writes a bundle out and asks for the next.  One token with 144 / 192 / 256 / 320 / 384 KiB:
 // OPT shape 60.4 / 59.4 / 58.2 / 58.4 / 60.0 us, Falcon shape 188 / 159 / 143 / 141 / 140 us, gated Llama-2 shape 147 / 138 /
 // 137 / 138 / 143 us.
-// For rows of at most 10 KiB the number of loaders is what limits (kStepPairs).  Several tokens: more loaders, a bundle takes
-// longer to deal with; 20 / 32 / 48 / 64 pairs of 16 KiB rows: 205 / 207 / 200 / 200 us a pass, of 24 KiB: 262 / 252 / 249 / 250;
-// but every loader workgroup costs a compute unit of the activation stage (11 KiB rows, 60 loaded: 52 / 52 / 53 / 56).
-constexpr size_t kStepInflightBytes = 320 * 1024, kStepInflightBytesB = 768 * 1024;
-constexpr int kStepPairs = 32, kStepPairsB = 48;
+// For rows of at most 10 KiB the number of loaders is what limits (kStepPairs).
+// Where a vector is at most 2 KiB a loader takes whole bundles, a pair has two in flight, and 256 KiB of them are asked for by
+// at most kStepPairsWhole pairs: bundles of 1 KiB, 1278 and 395 added, with 32 / 48 / 64 pairs 77.1 / 65.1 / 62.1 and 43.8 / 40.5 /
+// 39.5 us (five separate launches: 70.2 and 43.6); of 2 KiB, 783 and 198 added, 57.0 / 55.7 / 55.3 and 28.9 / 27.6 / 26.8; of
+// 4 KiB, 455 and 136 added, with 32 / 40 / 64 54.0 / 53.5 / 54.3 and 29.3 / 29.4 / 30.1.
+// Several tokens: more loaders, a bundle takes longer to deal with; 20 / 32 / 48 / 64 pairs of 16 KiB rows: 205 / 207 / 200 / 200 us a
+// pass, of 24 KiB: 262 / 252 / 249 / 250; but every loader workgroup costs a compute unit of the activation stage (11 KiB rows, 60
+// loaded: 52 / 52 / 53 / 56).
+constexpr size_t kStepInflightBytes = 320 * 1024, kStepInflightBytesWhole = 256 * 1024, kStepInflightBytesB = 768 * 1024;
+constexpr int kStepPairs = 32, kStepPairsWhole = 64, kStepPairsB = 48;
 // lif_load_bundles by itself: with 320 / 640 KiB rows of 25 and 30 KiB took 121 / 117 and 110 / 105 us (all four calls).
 constexpr size_t kLoadInflightBytes = 640 * 1024;
 constexpr int kDefaultPolls = 4096;      // a failed poll takes about 0.7 us: 3 ms before a workgroup helps itself
@@ -403,7 +408,10 @@ StepArgs step_args(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_ma
     a.x = x; a.h = L->h; a.h_new = L->h_new; a.stamp = L->stamp; a.ptr_new = L->ptr_new; a.bias_new = L->bias_new;
     a.batch = batch; a.keep = 1; a.polls = L->polls; a.st = L->st;
     // loader waves: two per bundle in flight
-    a.n_load = 2 * (batch > 1 ? loader_pairs(L, kStepInflightBytesB, kStepPairsB) : loader_pairs(L, kStepInflightBytes, kStepPairs));
+    const bool whole = (size_t)c.d_model * elem_bytes(c) <= 2048;
+    a.n_load = 2 * (batch > 1 ? loader_pairs(L, kStepInflightBytesB, kStepPairsB)
+                    : whole   ? loader_pairs(L, kStepInflightBytesWhole / 2, kStepPairsWhole)
+                              : loader_pairs(L, kStepInflightBytes, kStepPairs));
     return a;
 }
 // workgroups of the activation role with one wave per row; with a row-count hint the grid is sized to it
