@@ -604,27 +604,6 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         hole = s < n2 && dead;
         fill = s >= n2 && s < n && !dead;
     };
-    // The dead slots of block b are kept by the wave that classifies it (number i = b / 4 of its blocks) in lane i mod 64 of
-    // dead[i / 64]: looked up again in every pass, the owners past the staged ones cost a memory round trip per block (OPT shape, 4
-    // tokens: 140 -> 125 us a step at 15700 rows, 124 -> 111 at 14300; one token 91 -> 88 at 6600; up to 4096 rows the same).
-    unsigned long long dead[4] = {0ull, 0ull, 0ull, 0ull};
-    auto classify = [&](int b, int id, unsigned long long removed) {         // removed: word id / 64 of L.rem
-        const int i = b >> 2, s = b * kWave + lane;
-        const unsigned long long m = __ballot((unsigned)id >= (unsigned)F || ((removed >> (id & 63)) & 1ull));
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dead[r] = (i == r * kWave + lane) ? m : dead[r];
-        const int ch = __popcll(__ballot(s < n2) & m), cf = __popcll(__ballot(s >= n2 && s < n) & ~m);
-        if (lane == 0 && b < nblk) {
-            L.blk_h[b] = (uint16_t)ch;
-            L.blk_f[b] = (uint16_t)cf;
-        }
-    };
-    auto dead_of = [&](int b) -> unsigned long long {            // uniform; never under a condition that differs between lanes
-        const int i = b >> 2;
-        const unsigned long long v = i < 64 ? dead[0] : i < 128 ? dead[1] : i < 192 ? dead[2] : dead[3];
-        return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), i & 63) << 32) |
-               (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, i & 63);
-    };
 
     // ---- masks -> window -> id list -> first host read ----
     const int x_pieces = nvec * a.batch;
@@ -742,7 +721,42 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     // the bookkeeping workgroup (which needs the number of moves): all waves together, ahead of the host reads.
     const bool alone = wg > 0 && nblk <= kWave;
     int H = 0;
+    // destination of the tail slot of this lane in block b (kNoDst: dead) for the items [c0, ...)
+    auto put_dst = [&](int b, bool fill, int c0) {
+        const unsigned long long bf = __ballot(fill);
+        const int q = b * kWave + lane - n2;
+        if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
+            const int r = H - 1 - (L.blk_f[b] + __popcll(bf & lt));
+            int dst = kNoDst;
+            if (fill && r >= 0 && r < H) {
+                if (H <= kHoleFew) dst = L.hole[r];
+                else dst = a.hole_list[r];
+            }
+            L.dst[q - c0] = (uint16_t)dst;
+        }
+    };
     if (tot_r > 0 && !alone) {                                   // uniform
+        // The dead slots of block b are kept by the wave that classifies it (number i = b / 4 of its blocks) in lane i mod 64 of
+        // dead[i / 64]: looked up again in every pass, the owners past the staged ones cost a memory round trip per block (OPT shape, 4
+        // tokens: 140 -> 125 us a step at 15700 rows, 124 -> 111 at 14300; one token 91 -> 88 at 6600; up to 4096 rows the same).
+        unsigned long long dead[4] = {0ull, 0ull, 0ull, 0ull};
+        auto classify = [&](int b, int id, unsigned long long removed) {         // removed: word id / 64 of L.rem
+            const int i = b >> 2, s = b * kWave + lane;
+            const unsigned long long m = __ballot((unsigned)id >= (unsigned)F || ((removed >> (id & 63)) & 1ull));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dead[r] = (i == r * kWave + lane) ? m : dead[r];
+            const int ch = __popcll(__ballot(s < n2) & m), cf = __popcll(__ballot(s >= n2 && s < n) & ~m);
+            if (lane == 0 && b < nblk) {
+                L.blk_h[b] = (uint16_t)ch;
+                L.blk_f[b] = (uint16_t)cf;
+            }
+        };
+        auto dead_of = [&](int b) -> unsigned long long {            // uniform; never under a condition that differs between lanes
+            const int i = b >> 2;
+            const unsigned long long v = i < 64 ? dead[0] : i < 128 ? dead[1] : i < 192 ? dead[2] : dead[3];
+            return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), i & 63) << 32) |
+                   (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, i & 63);
+        };
         static_assert(kPtrLds / kWave % 32 == 0, "a round is staged as a whole or not at all");
 #pragma unroll 1
         for (int b0 = wave; b0 < nblk; b0 += 4 * 8) {
@@ -800,32 +814,22 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             }
             if (in_lds) lds_barrier();
             else __syncthreads();
+            const int tail = n2 >> 6;                            // first block with slots of the first items
+#pragma unroll 1
+            for (int b = tail + ((wave - tail) & 3); b < nblk; b += 4) {
+                const int s = b * kWave + lane;
+                const unsigned long long m = dead_of(b);         // (by the whole wave)
+                put_dst(b, s >= n2 && s < n && !((m >> lane) & 1ull), 0);
+            }
         }
     }
-    auto fill_dst = [&](int c0, auto again_c) {                  // destinations of the tail slots of items [c0, ...) (kNoDst: dead)
-        const bool in_lds = H <= kHoleFew;
-        const int tail = (n2 + c0) >> 6;                         // first block with slots of these items
+    auto fill_dst = [&](int c0) {                                // later pieces of the list (`dead` is not kept through the load loop)
+        const int tail = (n2 + c0) >> 6;
 #pragma unroll 1
         for (int b = tail + ((wave - tail) & 3); b < nblk; b += 4) {
             bool hole, fill;
-            if constexpr (decltype(again_c)::value) {            // (later pieces: `dead` is not kept through the load loop)
-                flags_of(b, owner(b), hole, fill);
-            } else {
-                const int s = b * kWave + lane;
-                const unsigned long long m = dead_of(b);         // (by the whole wave)
-                fill = s >= n2 && s < n && !((m >> lane) & 1ull);
-            }
-            const unsigned long long bf = __ballot(fill);
-            const int q = b * kWave + lane - n2;
-            if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
-                const int r = H - 1 - (L.blk_f[b] + __popcll(bf & lt));
-                int dst = kNoDst;
-                if (fill && r >= 0 && r < H) {
-                    if (in_lds) dst = L.hole[r];
-                    else dst = a.hole_list[r];
-                }
-                L.dst[q - c0] = (uint16_t)dst;
-            }
+            flags_of(b, owner(b), hole, fill);
+            put_dst(b, fill, c0);
         }
     };
     // The plan for at most 64 blocks, all of them staged, by waves 1..3: they share the classification, wave 1 does the rest.
@@ -873,10 +877,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         if (lane == 0) __hip_atomic_store(&L.planned, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
-    if (wg > 0 && !alone) {
-        if (tot_r > 0) fill_dst(0, std::false_type{});
-        lds_barrier();
-    }
+    if (wg > 0 && !alone) lds_barrier();
     if (loads && lw < (PAIRED ? 2 * tot_a : tot_a))              // unit lw (below kListItems)
         request_host(__builtin_amdgcn_readfirstlane((int)L.ids[PAIRED ? lw >> 1 : lw]), PAIRED ? lw & 1 : 0);
 
@@ -1144,7 +1145,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             lds_barrier();
             fill_ids(c0);
             if (tid == 0) L.planned = L.classified = 0;
-            if (tot_r > 0 && !alone) fill_dst(c0, std::true_type{});
+            if (tot_r > 0 && !alone) fill_dst(c0);
             lds_barrier();
         }
         const int n_a = min(max(tot_a - c0, 0), kListItems), n_r = min(max(tot_r - c0, 0), kListItems);     // of this piece
