@@ -299,9 +299,16 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     constexpr int cols = kDown1Lanes * Vec<T>::N;
     const int slices = ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;     // whole runs of slices per XCD
     const int rows = geometry_rows(L);
-    const int wg_rows = down1_chunks<SKIP>(rows);    // fewer than the chunks in use is still correct
+    // fewer workgroup rows than chunks are still correct; one, and no second launch, where the hint itself needs one chunk
+    const bool one = L->expected_rows > 0 && down1_chunks<SKIP>(std::min(L->expected_rows, c.capacity_rows), slices) == 1;
+    const int wg_rows = one ? 1 : down1_chunks<SKIP>(rows, slices);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    const int waves = down1_waves(rows);
+    // Waves of a workgroup: what the rows likely in use need, a little less than the hint says.  Any choice is correct, but a
+    // workgroup of 8 goes twice through the work of 16 (Falcon shape, 5120 rows, skipping: 16.9 -> 19.3 us), while one of 16 leaves
+    // half of its waves idle where 8 are in use, so without a hint 8 are taken only where every row is read and most layers of
+    // this capacity hold more than one chunk (OPT shape, 8192 rows: 29.9 -> 28.3 us).
+    const int likely = L->expected_rows > 0 ? L->expected_rows / 6 * 5 : SKIP ? kDown1OneSkip : c.capacity_rows / 2;
+    const int waves = rows <= kDown1FewRows ? 8 : down1_waves<SKIP>(std::max(kDown1FewRows + 1, likely), slices);
     // groups of slots whose activations are asked for ahead of the row count: those the hint covers; without a hint 2048
     // slots if that many rows make one pass (else the order of the slots is not known yet)
     const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;
@@ -317,7 +324,7 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
 #undef LIF_D1
     if (wg_rows > 1)
         hipLaunchKernelGGL((k_ffn_down_finish<T, down1_chunks<SKIP>>), dim3((c.d_model + 255) / 256), dim3(256), 0, s,
-                           ypart, (T*)y, c.d_model, 1, L->st);
+                           ypart, (T*)y, c.d_model, 1, slices, L->st);
 }
 
 // several tokens, fp32
@@ -339,7 +346,7 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
 #undef LIF_DB
     if (wg_rows > 1)
         hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
-                           ypart, (T*)y, c.d_model, batch, L->st);
+                           ypart, (T*)y, c.d_model, batch, slices, L->st);
 }
 
 // several tokens, fp16: the down projection on the matrix cores

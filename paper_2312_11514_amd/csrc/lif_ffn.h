@@ -232,7 +232,7 @@ constexpr int kDownRowsBatch = 512;   // rows per chunk for several tokens
 // Row chunks in use for n cached rows and several tokens: their active sets add up, most rows are read, and a chunk is
 // 512 rows so that several hundred workgroups stream at once (column slices alone, d / 64 workgroups, reach only
 // about 3 TB/s).  The host sizes the grid with the same rule.
-__host__ __device__ __forceinline__ int down_chunks(int n) {
+__host__ __device__ __forceinline__ int down_chunks(int n, int = 0) {
     const int c = (n + kDownRowsBatch - 1) / kDownRowsBatch;
     return c < 1 ? 1 : (c > kDownChunksMax ? kDownChunksMax : c);
 }
@@ -440,12 +440,12 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
 // y = sum of the chunk partials in chunk order, rounded once to the element type.  Launched after a
 // k_ffn_down grid of more than one workgroup row; does nothing when a single chunk was in use (y is
 // written already).  grid = ceil(batch * d / 256), block = 256.
-// CHUNKS: the chunk rule of the kernel that wrote the partials.
-template <typename T, int (*CHUNKS)(int)>
+// CHUNKS: the chunk rule of the kernel that wrote the partials, for its number of column slices.
+template <typename T, int (*CHUNKS)(int, int)>
 __global__ __launch_bounds__(256) void k_ffn_down_finish(const float* __restrict__ ypart, T* __restrict__ y, int d,
-                                                         int batch, const DevState* __restrict__ st) {
+                                                         int batch, int slices, const DevState* __restrict__ st) {
     if (st->cur.error) return;
-    const int chunks = CHUNKS(st->cur.num_used);
+    const int chunks = CHUNKS(st->cur.num_used, slices);
     if (chunks == 1) return;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= batch * d) return;

@@ -19,26 +19,40 @@ namespace lif {
 constexpr int kDown1Lanes = 4;           // lanes per row: 64 bytes of its down column
 constexpr int kDown1Per = 4;             // slots a thread compacts per pass
 constexpr int kDown1FewRows = 2048;      // up to here one pass of 8 waves covers all rows
-constexpr int kDown1RowsSkip = 8192;     // rows per chunk when rows without activation are skipped
-constexpr int kDown1RowsFull = 2048;     // ... when every row is read, once there are more than kDown1OneFull
-constexpr int kDown1OneFull = 4096;
+constexpr int kDown1OneSkip = 8192;      // one chunk up to here when rows without activation are skipped
+constexpr int kDown1OneFull = 3584;      // ... when every row is read
+constexpr int kDown1RowsSkip = 4096;     // rows per chunk beyond, for workgroups of 8 waves
+constexpr int kDown1RowsFull = 1024;
 
-// Row chunks in use for n cached rows.  One chunk (no partial sums, no second launch) as long as d / 32 workgroups keep
-// up with the rows: skipping rows, 8000 rows take 8.6 us in one chunk against 11.5 us in two chunks and a second
-// launch; reading every row, one chunk is faster up to about 4096 rows (8000 rows: 21 us in one chunk).
+// Row chunks in use for n cached rows and `slices` column slices.  One chunk (no partial sums, no second launch) as long as
+// d / 32 workgroups of 16 waves keep up with the rows: skipping rows, 8000 rows take 8.6 us in one chunk against 11.5 us in two
+// chunks and a second launch; reading every row (one whole call, OPT shape) 3072 rows 15.7 against 16.8, 3584 rows 17.3 either
+// way, 4096 rows 18.7 in four chunks.
+// Beyond, workgroups of 8 waves, several to a compute unit (with 16 waves one workgroup fills it, and what is left of the
+// workgroups after 256 of them runs almost alone): us a call, 16 waves -> 8 waves, every row read: OPT shape 5120 rows 23.1 -> 21.7,
+// 10240 rows 36.0 -> 32.7; Falcon shape 16384 rows 64.8 -> 56.7; skipping rows, Falcon shape, 10240 rows 27.5 -> 24.1.  Skipping
+// rows in two chunks, where workgroups of 16 waves just fill the compute units (down1_two16), they are better: OPT shape, half of
+// 10240 rows active, 27.5 against 28.7.
+__host__ __device__ __forceinline__ bool down1_two16(int n, int slices) { return n <= 2 * kDown1OneSkip && slices > 96 && slices <= 128; }
 template <bool SKIP>
-__host__ __device__ __forceinline__ int down1_chunks(int n) {
-    if (n <= (SKIP ? kDown1RowsSkip : kDown1OneFull)) return 1;
+__host__ __device__ __forceinline__ int down1_chunks(int n, int slices) {
+    if (n <= (SKIP ? kDown1OneSkip : kDown1OneFull)) return 1;
+    if (SKIP && down1_two16(n, slices)) return 2;
     constexpr int per = SKIP ? kDown1RowsSkip : kDown1RowsFull;
-    return (n + per - 1) / per;              // at most 65536 / 2048 = kDownChunksMax
+    const int c = (n + per - 1) / per;
+    return c < kDownChunksMax ? c : kDownChunksMax;
 }
 
-// Waves of the summation order for n rows: a function of n alone.  The slots are dealt to that many (virtual) waves,
+// Waves of the summation order for n rows: a function of n and the width alone.  The slots are dealt to that many (virtual) waves,
 // 64 consecutive slots at a time; every wave compacts its own slots with ballots into its own list, takes the list
 // positions i with i mod 16 = row group in ascending order, folds its row groups, and the waves are added in order.  A
 // workgroup launched with other than that many waves goes through the virtual waves in turn (or leaves some idle), so
 // the result does not depend on the launch geometry.
-__host__ __device__ __forceinline__ int down1_waves(int n) { return n <= kDown1FewRows ? 8 : 16; }
+template <bool SKIP>
+__host__ __device__ __forceinline__ int down1_waves(int n, int slices) {
+    if (n <= kDown1FewRows) return 8;
+    return n <= (SKIP ? kDown1OneSkip : kDown1OneFull) || (SKIP && down1_two16(n, slices)) ? 16 : 8;
+}
 
 // grid = (column slices of 64 bytes, rounded up to a multiple of 8, + 1 after a fused step (FUSED): the workgroup that commits
 // it; row-chunk workgroups), block = WAVES * 64.
@@ -112,10 +126,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
     const StepCounts* counts = stamp ? &st->next : &st->cur;
     const int err = counts->error, n = counts->num_used, cur_step = counts->step;
     if (err) return;
-    const int chunks = down1_chunks<SKIP>(n);
+    const int chunks = down1_chunks<SKIP>(n, slices);
     if ((int)blockIdx.y >= chunks) return;           // uniform
     const int per_chunk = (n + chunks - 1) / chunks;
-    const int vwaves = down1_waves(n);
+    const int vwaves = down1_waves<SKIP>(n, slices);
     const int stride = vwaves * 64;                  // slots between the groups of a (virtual) wave
     const bool natural = vwaves == WAVES;            // the requests above were for the right slots
     float total = 0.f;

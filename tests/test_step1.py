@@ -302,3 +302,36 @@ def test_batched_down_projection_reading_every_row(n):
     d = w.d_model
     h = np.maximum(x.astype(np.float64) @ bun[:, :d].T + L.b[ids], 0.0)
     assert rel_l2(gpu.y.cpu().numpy().astype(np.float64), h @ bun[:, d:]) <= REL_L2_TOL
+
+
+@pytest.mark.parametrize("d,F,rows", [(96, 33000, (2048, 2049, 3584, 3585, 4097, 8192, 8193, 16385, 33000)),
+                                      (4096, 16384, (3585, 8193, 16384)), (4544, 10240, (3584, 8193, 10240))])
+@pytest.mark.parametrize("full", [False, True])
+def test_down_projection_of_one_token_by_row_chunks(d, F, rows, full):
+    """The chunks and waves of the down projection follow from the rows in use, whatever launch the hint leads to: the same
+    bytes with every hint, and the sum itself, around the row counts where the rule changes."""
+    import paper_2312_11514_amd as lif
+    from tests.harness import REL_L2_TOL, rel_l2, require_gpu
+    require_gpu()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + full)
+    zeros = lambda *s, dt=torch.float16: torch.zeros(s, dtype=dt, device="cuda")
+    lay = lif.Layer(d_model=d, d_ffn=F, rank=8, window_k=2, capacity_rows=F, dtype="f16",
+                    ffn_mode=lif.FFN_FULL_BUNDLE if full else lif.FFN_SKIP_DEAD, A=zeros(8, d), B=zeros(8, F), c=None,
+                    b=zeros(F, dt=torch.float32), host_bundles=torch.zeros((F, 2 * d), dtype=torch.float16).pin_memory())
+    lay.matrix.copy_(torch.randn((F, 2 * d), generator=g, device="cuda").div_(d ** 0.5))
+    lay.bias.fill_(-0.7)
+    x = torch.randn((1, d), generator=g, device="cuda").half()
+    h = torch.relu(lay.matrix[:, :d].double() @ x[0].double() - 0.7)
+    for n in rows:
+        lay.workspace[:4] = torch.tensor([n], dtype=torch.int32).view(torch.uint8).cuda()
+        got = []
+        for hint in (0, 1, n // 2, n, n + n // 7, F):
+            print(f"one token, d {d}, full {full}: {n} rows, hint {hint}", flush=True)
+            lay.set_expected_rows(hint)
+            y = torch.full_like(x, 9.0)
+            lay.sparse_ffn(x, y)
+            got.append(y)
+        assert all(torch.equal(y, got[0]) for y in got[1:]), n
+        want = h[:n] @ lay.matrix[:n, d:].double()
+        assert rel_l2(got[0].double().cpu().numpy(), want.cpu().numpy()) <= REL_L2_TOL, n
