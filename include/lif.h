@@ -304,7 +304,7 @@ int lif_set_expected_rows(lif_layer* layer, int32_t rows);
  * loader waves, one bundle in flight per pair, 1..64; 0 restores the default.  The default comes from the bundle size,
  * as many pairs as keep so many bytes of host reads outstanding, and at least 5:
  *   a step of one token            320 KiB, at most 32 pairs; vectors of at most 2 KiB (a pair then has two bundles in
- *                                  flight): 256 KiB, at most 64 pairs
+ *                                  flight): 256 KiB, at most 64 pairs; vectors of more than 12 KiB: 20 pairs
  *   a step or pass of several      768 KiB, at most 48 pairs
  *   lif_load_bundles               640 KiB, at most 32 pairs
  * Results never depend on it.

@@ -51,11 +51,14 @@ int fail(int code, const char* fmt, const char* detail = "") {
 // at most kStepPairsWhole pairs: bundles of 1 KiB, 1278 and 395 added, with 32 / 48 / 64 pairs 77.1 / 65.1 / 62.1 and 43.8 / 40.5 /
 // 39.5 us (five separate launches: 70.2 and 43.6); of 2 KiB, 783 and 198 added, 57.0 / 55.7 / 55.3 and 28.9 / 27.6 / 26.8; of
 // 4 KiB, 455 and 136 added, with 32 / 40 / 64 54.0 / 53.5 / 54.3 and 29.3 / 29.4 / 30.1.
+// Vectors of more than 12 KiB: a loader takes so long with each (16 pieces a lane) that kStepPairsWide pairs are needed; d = 8192,
+// with 10 / 14 / 20 / 32 pairs: plain 75.0 / 63.3 / 60.2 / 61.6 us (five separate launches: 67.1), gated 92.1 / 87.5 / 83.9 / 84.7, with
+// the gate resident 91.1 / 79.6 / 76.0 / 78.0; d = 7168 59.4 / 53.8 / 53.0 / 55.1; but d = 6144 44.0 / 44.6 / 45.9 / 46.2.
 // Several tokens: more loaders, a bundle takes longer to deal with; 20 / 32 / 48 / 64 pairs of 16 KiB rows: 205 / 207 / 200 / 200 us a
 // pass, of 24 KiB: 262 / 252 / 249 / 250; but every loader workgroup costs a compute unit of the activation stage (11 KiB rows, 60
 // loaded: 52 / 52 / 53 / 56).
 constexpr size_t kStepInflightBytes = 320 * 1024, kStepInflightBytesWhole = 256 * 1024, kStepInflightBytesB = 768 * 1024;
-constexpr int kStepPairs = 32, kStepPairsWhole = 64, kStepPairsB = 48;
+constexpr int kStepPairs = 32, kStepPairsWhole = 64, kStepPairsWide = 20, kStepPairsB = 48;
 // lif_load_bundles by itself: with 320 / 640 KiB rows of 25 and 30 KiB took 121 / 117 and 110 / 105 us (all four calls).
 constexpr size_t kLoadInflightBytes = 640 * 1024;
 constexpr int kDefaultPolls = 4096;      // a failed poll takes about 0.7 us: 3 ms before a workgroup helps itself
@@ -415,10 +418,11 @@ StepArgs step_args(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_ma
     a.x = x; a.h = L->h; a.h_new = L->h_new; a.stamp = L->stamp; a.ptr_new = L->ptr_new; a.bias_new = L->bias_new;
     a.batch = batch; a.keep = 1; a.polls = L->polls; a.st = L->st;
     // loader waves: two per bundle in flight
-    const bool whole = (size_t)c.d_model * elem_bytes(c) <= 2048;
-    a.n_load = 2 * (batch > 1 ? loader_pairs(L, kStepInflightBytesB, kStepPairsB)
-                    : whole   ? loader_pairs(L, kStepInflightBytesWhole / 2, kStepPairsWhole)
-                              : loader_pairs(L, kStepInflightBytes, kStepPairs));
+    const size_t vector = (size_t)c.d_model * elem_bytes(c);
+    a.n_load = 2 * (batch > 1              ? loader_pairs(L, kStepInflightBytesB, kStepPairsB)
+                    : vector <= 2 * 1024   ? loader_pairs(L, kStepInflightBytesWhole / 2, kStepPairsWhole)
+                    : vector <= 12 * 1024  ? loader_pairs(L, kStepInflightBytes, kStepPairs)
+                                           : loader_pairs(L, kStepPairsWide * L->row_bytes, kStepPairsWide));
     return a;
 }
 // workgroups of the activation role with one wave per row; with a row-count hint the grid is sized to it
