@@ -31,13 +31,17 @@ constexpr int kDown1RowsFull = 1024;
 // Beyond, workgroups of 8 waves, several to a compute unit (with 16 waves one workgroup fills it, and what is left of the
 // workgroups after 256 of them runs almost alone): us a call, 16 waves -> 8 waves, every row read: OPT shape 5120 rows 23.1 -> 21.7,
 // 10240 rows 36.0 -> 32.7; Falcon shape 16384 rows 64.8 -> 56.7; skipping rows, Falcon shape, 10240 rows 27.5 -> 24.1.  Skipping
-// rows in two chunks, where workgroups of 16 waves just fill the compute units (down1_two16), they are better: OPT shape, half of
+// rows in two chunks, where workgroups of 16 waves just fill the compute units (down1_rows16), they are better: OPT shape, half of
 // 10240 rows active, 27.5 against 28.7.
-__host__ __device__ __forceinline__ bool down1_two16(int n, int slices) { return n <= 2 * kDown1OneSkip && slices > 96 && slices <= 128; }
+// rows up to which workgroups have 16 waves (from kDown1FewRows on): known before the row count is
+template <bool SKIP>
+__host__ __device__ __forceinline__ int down1_rows16(int slices) {
+    return !SKIP ? kDown1OneFull : slices > 96 && slices <= 128 ? 2 * kDown1OneSkip : kDown1OneSkip;
+}
 template <bool SKIP>
 __host__ __device__ __forceinline__ int down1_chunks(int n, int slices) {
     if (n <= (SKIP ? kDown1OneSkip : kDown1OneFull)) return 1;
-    if (SKIP && down1_two16(n, slices)) return 2;
+    if (n <= down1_rows16<SKIP>(slices)) return 2;
     constexpr int per = SKIP ? kDown1RowsSkip : kDown1RowsFull;
     const int c = (n + per - 1) / per;
     return c < kDownChunksMax ? c : kDownChunksMax;
@@ -50,8 +54,7 @@ __host__ __device__ __forceinline__ int down1_chunks(int n, int slices) {
 // the result does not depend on the launch geometry.
 template <bool SKIP>
 __host__ __device__ __forceinline__ int down1_waves(int n, int slices) {
-    if (n <= kDown1FewRows) return 8;
-    return n <= (SKIP ? kDown1OneSkip : kDown1OneFull) || (SKIP && down1_two16(n, slices)) ? 16 : 8;
+    return n > kDown1FewRows && n <= down1_rows16<SKIP>(slices) ? 16 : 8;
 }
 
 // grid = (column slices of 64 bytes, rounded up to a multiple of 8, + 1 after a fused step (FUSED): the workgroup that commits
@@ -128,7 +131,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
     if (err) return;
     const int chunks = down1_chunks<SKIP>(n, slices);
     if ((int)blockIdx.y >= chunks) return;           // uniform
-    const int per_chunk = (n + chunks - 1) / chunks;
+    const int per_chunk = chunks == 1 ? n : (n + chunks - 1) / chunks;      // (no division on the shortest path)
     const int vwaves = down1_waves<SKIP>(n, slices);
     const int stride = vwaves * 64;                  // slots between the groups of a (virtual) wave
     const bool natural = vwaves == WAVES;            // the requests above were for the right slots
