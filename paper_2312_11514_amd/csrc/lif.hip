@@ -102,8 +102,9 @@ Layout make_layout(const lif_config& c) {
     size_t off = 0;
     L.state = off;
     off = align_up(off + sizeof(DevState), 256);
-    L.words = off;                     // words handed over inside a fused step: t = x A, then the mask words
+    L.words = off;                     // words handed over inside a fused step: t = x A, the mask words
     off = off + sizeof(uint64_t) * kWordReps * ((size_t)words_pitch(2 * std::max(c.rank, 0)) + words_pitch(2 * ring_words(c)));
+    off = off + sizeof(uint64_t) * c.capacity_rows;               // ... and the deletion plan
     L.ring = off;                      // window_k step masks, each padded to whole 64-bit words
     off = off + (size_t)(c.window_k + 2) * ring_words(c) * 8;     // ... directly followed by the two bitmaps of the cached set
     L.reset_words = (int)((off - L.words) / 8);
@@ -191,7 +192,7 @@ int launch_predict(lif_layer* L, const void* x, int batch, uint8_t* masks, uint8
         Timed t(L, LIF_K_PREDICT_XA, s);
         const int ni = (c.d_model / Vec<T>::N + 63) / 64;
 #define LIF_XA(NI)                                                                                          \
-    hipLaunchKernelGGL((k_predict_xa<T, NI>), dim3((c.rank + 3) / 4, batch), dim3(256), 0, s, (const T*)x,       \
+    hipLaunchKernelGGL((k_predict_xa<T, NI>), dim3(c.rank, batch), dim3(256), 0, s, (const T*)x,       \
                        (const T*)L->buf.A, L->tpart, c.d_model, c.rank, L->st)
         if (ni <= 1) LIF_XA(1);
         else if (ni <= 2) LIF_XA(2);
@@ -409,6 +410,7 @@ StepArgs step_args(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_ma
     a.A = L->buf.A; a.B = L->buf.B; a.c = L->buf.c; a.rank = c.rank; a.theta = c.threshold;
     a.t_pitch = words_pitch(2 * std::max(c.rank, 0)); a.m_pitch = words_pitch(2 * words);
     a.t_words = L->words; a.m_words = L->words + (size_t)kWordReps * a.t_pitch;
+    a.plan_words = a.m_words + (size_t)kWordReps * a.m_pitch;
     a.masks = masks; a.step_mask = step_mask; a.gact = L->gact;
     a.ring = L->ring; a.cur_set = L->ring + (size_t)c.window_k * words; a.ring_words = words;
     a.k = c.window_k; a.shrink = c.shrink_window;
@@ -435,8 +437,8 @@ int up_blocks(const lif_layer* L) {
 void launch_step1(lif_layer* L, StepArgs a, hipStream_t s) {
     const lif_config& c = L->cfg;
     const bool gate = c.predictor == LIF_PRED_GATE;
-    // predictor workgroups: one per 64 neurons (32 with the gate predictor), and enough for the columns of A
-    a.n_pred = gate ? 2 * a.ring_words : std::max(a.ring_words, (c.rank + 3) / 4);
+    // predictor workgroups: one per 64 neurons (32 with the gate predictor), and one per column of A as far as kStepColumns
+    a.n_pred = gate ? 2 * a.ring_words : std::max(a.ring_words, std::min(c.rank, kStepColumns));
     a.spec = L->expected_rows > 0 ? 1 : 0;
     const int grid = a.n_pred + 1 + a.n_load + up_blocks(L);
     if (c.dtype == LIF_F32) (gate ? launch_step1_f32_gate : c.glu ? launch_step1_f32_glu : launch_step1_f32_plain)(a, grid, s);

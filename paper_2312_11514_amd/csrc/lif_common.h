@@ -97,6 +97,20 @@ __device__ __forceinline__ double dpp_from(double v) {
     const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
+// a + b where lanes M apart (16 or 32) trade first: the lane whose bit M is clear gets its own and its partner's a, the other one
+// both b.
+template <int M>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    static_assert(M == 16 || M == 32, "rows or halves of the wave");
+    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a), ub = __builtin_bit_cast(unsigned long long, b);
+    auto trade = [](unsigned x, unsigned y) {
+        if constexpr (M == 16) return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        else return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    };
+    const auto lo = trade((unsigned)ua, (unsigned)ub), hi = trade((unsigned)(ua >> 32), (unsigned)(ub >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
 __device__ __forceinline__ float wave_sum(float v) {
     v += dpp_from<0x111, 0xf>(v);   // row_shr:1
     v += dpp_from<0x112, 0xf>(v);   // row_shr:2
@@ -117,6 +131,16 @@ __device__ __forceinline__ double wave_sum(double v) {
     const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, 63);
     const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), 63);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// *p at an address that is the same for the whole wave, through the scalar cache: of memory that nothing writes during the launch
+template <typename U>
+__device__ __forceinline__ U uniform_load(const U* p) {
+    static_assert(sizeof(U) == 4, "one dword");
+    const unsigned long long u = reinterpret_cast<unsigned long long>(p);
+    const unsigned long long q = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32)) << 32) |
+                                 (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+    return *reinterpret_cast<const __attribute__((address_space(4))) U*>(q);
 }
 
 // Workgroup barrier that orders LDS accesses only: unlike __syncthreads() it does not wait for the global

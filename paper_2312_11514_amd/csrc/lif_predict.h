@@ -34,35 +34,50 @@ constexpr int kMaskCols = 8;       // mask bytes (groups of 8 neurons) per workg
 constexpr int kMaskJg = 32;        // rank groups per workgroup of predict_mask
 constexpr int kMaskRows = 8;       // rows of B a thread keeps in flight
 
-// t[b][j] = sum_i x[b][i] * At[j][i]   (At = the first predictor matrix with the contraction dimension
-// contiguous, [r x d]).  One wave per (j, b): 16-byte loads along the row, fp64 accumulation, wave
-// reduction - every t[b][j] is complete after this kernel, so the mask kernel needs no partial sums.
-// grid = (ceil(r / 4), batch), block = 256.  NI = ceil(d / (64 * VE)) loads per lane.
+// t[j] = x . row j of At (the first predictor matrix with the contraction dimension contiguous, [r x d]) by a workgroup of four waves:
+// wave w takes the 1 KiB pieces [w * P, w * P + P), P = ceil(NI / 4) of NI = ceil(d / (64 * VE)), in fp64, and the four sums are
+// added in wave order.  A whole row per wave took 1.8 us from the last load to the sum at d = 4096 in fp16: a conversion and a
+// dependent fp64 add for each of 64 products, one wave to a SIMD (k_step1, x A known after 3.1 us instead of 2.3).
+template <typename T, int NI>
+struct ColumnPart {
+    using V = typename Vec<T>::type;
+    static constexpr int P = (NI + 3) / 4;
+    V a[P], x[P];
+    static __device__ __forceinline__ int piece(int it) { return (threadIdx.x >> 6) * P + it; }
+    static __device__ __forceinline__ void load(V (&v)[P], const T* p, int nvec) {
+#pragma unroll
+        for (int it = 0; it < P; ++it) {
+            const int idx = piece(it) * 64 + (threadIdx.x & 63);
+            v[it] = (piece(it) < NI && idx < nvec) ? reinterpret_cast<const V*>(p)[idx] : V(0);
+        }
+    }
+    // this wave's part of the sum, in every lane
+    __device__ __forceinline__ double sum() const {
+        double acc = 0.0;
+#pragma unroll
+        for (int it = 0; it < P; ++it) acc = dot_f64(a[it], x[it], acc);
+        return wave_sum(acc);
+    }
+};
+// the parts of the four waves
+__device__ __forceinline__ double column_total(const double (&part)[4]) { return ((part[0] + part[1]) + part[2]) + part[3]; }
+
+// t[b][j] for every token and column: complete after this kernel, so the mask kernel needs no partial sums.
+// grid = (r, batch), block = 256.
 template <typename T, int NI>
 __global__ __launch_bounds__(256) void k_predict_xa(const T* __restrict__ x, const T* __restrict__ At,
                                                     double* __restrict__ t, int d, int r,
                                                     const DevState* __restrict__ st) {
-    using V = typename Vec<T>::type;
-    constexpr int VE = Vec<T>::N;
-    const int lane = threadIdx.x & 63;
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
-    if (j >= r) return;                              // wave-uniform; the kernel has no barrier
-    const int nvec = d / VE;
-    const V* xv = reinterpret_cast<const V*>(x + (size_t)b * d);
-    const V* row = reinterpret_cast<const V*>(At + (size_t)j * d);
-    V a[NI], xr[NI];
-#pragma unroll
-    for (int it = 0; it < NI; ++it) {
-        const int idx = it * 64 + lane;
-        a[it] = (idx < nvec) ? row[idx] : V(0);
-        xr[it] = (idx < nvec) ? xv[idx] : V(0);
-    }
+    __shared__ double part[4];
+    const int j = blockIdx.x, b = blockIdx.y, nvec = d / Vec<T>::N;
+    ColumnPart<T, NI> c;
+    c.load(c.a, At + (size_t)j * d, nvec);
+    c.load(c.x, x + (size_t)b * d, nvec);
     const int err = st->cur.error;
-    double acc = 0.0;
-#pragma unroll
-    for (int it = 0; it < NI; ++it) acc = dot_f64(a[it], xr[it], acc);
-    acc = wave_sum(acc);
-    if (lane == 0 && !err) t[(size_t)b * r + j] = acc;
+    const double v = c.sum();
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0 && !err) t[(size_t)b * r + j] = column_total(part);
 }
 
 // logits = t B + c, threshold, pack 8 neurons per byte; step mask = OR over the batch.

@@ -5,16 +5,16 @@
 // (Section 3.3 item 2).  As separate launches every short stage costs 4 to 6 us on gfx950: 1.6 us of launch, a memory
 // round trip for the state, another one for what the previous kernel wrote.  Here the workgroups of one launch take
 // different roles and hand over inside it:
-//   workgroups [0, n_pred)        predictor: the first ceil(rank / 4) of them compute t = x A (one column per wave) and
-//                                 publish it; each of the first ceil(F / 64) waits for t and decides the 64 mask bits of
-//                                 its neurons (their weights are requested before the wait).  Gate predictor: 32 neurons
-//                                 per workgroup, nothing to wait for.
-//   workgroup n_pred              bookkeeping: waits for the masks, writes the window state, id lists and counts
-//   the next n_load workgroups    loaders: wait for the masks, work out the added ids and the deletion plan (every
-//                                 workgroup for itself: cheaper than waiting for one that does), move rows, gather
-//                                 bundles from pinned host memory and compute the activations of the rows they write
-//                                 (h_new, stamped with the step)
-//   the rest                      activations of the rows that were already in use; waits for nothing
+//   workgroups [0, n_pred)        predictor: the first ones compute t = x A (a column each, 256 at a time) and publish it; each of
+//                                 the first ceil(F / 64) waits for t and decides the 64 mask bits of its neurons (their weights
+//                                 are requested before the wait).  Gate predictor: 32 neurons per workgroup, nothing to wait for.
+//   workgroup n_pred              bookkeeping: waits for the masks, makes the deletion plan and publishes it, writes the window
+//                                 state, id lists and counts
+//   the next n_load workgroups    loaders: wait for the masks, work out the added ids (every workgroup for itself: cheaper than
+//                                 waiting for one that does), gather bundles from pinned host memory, move the rows they
+//                                 overwrite where the plan says and compute the activations of the rows they write (h_new,
+//                                 stamped with the step)
+//   the rest                      activations of the rows that were already in use; they begin when the predictor is done
 // A value handed over is a 64-bit word: 32 bits of payload and the number of the step as a stamp, written by a relaxed
 // device-scope atomic store and polled with relaxed device-scope atomic loads, so no fence (a device-scope release
 // writes back the L2: 6 us) and no clearing is needed.  Stamps are unique between two resets, which clear the words.
@@ -26,11 +26,14 @@
 // loader's stamped activation takes precedence for that slot.
 // Every sum is formed in the order of the separate kernels, so the step is bit-identical to the four calls.
 //
-// What bounds it: the host link, at 56 GB/s (a copy of 256 MiB by the runtime reaches 57), behind a chain of about 8 us
-// (x A 3, masks 3, window and first ids 2) and in front of the down projection.  Measured on gfx950, one decode token,
-// with five launches -> with this kernel and the down projection, side by side in one run (runs on other machines differ by up
-// to 4 %): fp32 d = 256, F = 1024: 23.4 -> 14.4 us; OPT-6.7B shape 65.3 -> 59.1; Falcon-7B shape 149.5 -> 139.4; Llama-2 shape
-// gated, from a graph, 148.7 -> 136.6, with the gate resident 112.8 -> 109.1.  Eight tokens, Llama-2 shape gated: 276.8 -> 253.6.
+// What bounds it: the host link.  From the first request to the last bundle it moves 55 to 57 GB/s (a copy of 256 MiB by the
+// runtime: 57.5).  In front of the first request are a launch and two hand-overs, OPT-6.7B shape (Falcon-7B shape), us from the
+// start of the first workgroup: x A published 2.4 (2.5), masks published 4.7 (5.0), known to the loaders 6.2 (6.6), first request 7
+// (7.5); behind the last bundle is the down projection.  A compute unit has about 5 KiB of host reads under way, whatever its
+// waves ask for, so some 30 loaders fill the link.
+// Measured on gfx950, one decode token, with five launches -> with this kernel and the down projection: fp32 d = 256, F = 1024:
+// 23.4 -> 14.1 us; OPT-6.7B shape 65.3 -> 57; Falcon-7B shape 149.5 -> 136; Llama-2 shape gated, from a graph, 148.7 -> 132, with the
+// gate resident 112.8 -> 108.5.
 #pragma once
 
 #include "lif_ffn.h"
@@ -44,6 +47,7 @@ constexpr int kWordReps = 8;         // copies of every word: hundreds of workgr
 // words of one copy, padded so that the copies do not fall on the same memory channels
 __host__ __device__ __forceinline__ int words_pitch(int n) { return (n + 31) / 32 * 32 + 32; }
 constexpr int kListItems = 2048;     // work items listed at a time
+constexpr int kStepColumns = 256;    // predictor workgroups that only compute columns of x A: at most as many as there are compute units
 
 struct StepArgs {
     // predictor
@@ -55,6 +59,7 @@ struct StepArgs {
     unsigned long long* t_words;     // [kWordReps][t_pitch] stamped halves of t (doubles)
     unsigned long long* m_words;     // [kWordReps][m_pitch] stamped 32-bit halves of the mask words
     int t_pitch, m_pitch;
+    unsigned long long* plan_words;  // [capacity] stamped destinations of the tail slots (kNoDst: dead), in the order of the slots
     uint8_t* masks;
     uint8_t* step_mask;
     float* gact;                     // gate predictor: relu(gate_i . x + b_i) per neuron
@@ -94,22 +99,24 @@ __device__ __forceinline__ unsigned long long word_load(const unsigned long long
 __device__ __forceinline__ void word_store(unsigned long long* p, unsigned stamp, unsigned payload) {
     __hip_atomic_store(p, ((unsigned long long)stamp << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Reads N words p[i * step] (i < n) of this stamp: all are requested before the first is looked at, the missing ones
-// again until they arrive or `polls` more reads have failed.  Returns whether all have arrived.
+// Reads N words p[i * step] (i < n) of this stamp by the whole wave: all are requested before the first is looked at, and
+// again as a whole until every lane has its words or `polls` more reads have failed (read again one after the other, a
+// lane's second word cost a round trip of its own).  Returns whether all words of this lane have arrived.
 template <int N>
 __device__ __forceinline__ bool poll_words(const unsigned long long* p, int step, int n, unsigned stamp, int polls,
                                            unsigned (&out)[N]) {
-    unsigned long long w[N];
+    bool all;
+    for (int tries = 0;; ++tries) {
+        unsigned long long w[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) w[i] = (i < n) ? word_load(p + (size_t)i * step) : 0ull;
-    bool all = true;
+        for (int i = 0; i < N; ++i) w[i] = (i < n) ? word_load(p + (size_t)i * step) : 0ull;
+        all = true;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        if (i < n) {
-            for (int tries = 0; (unsigned)(w[i] >> 32) != stamp && tries < polls; ++tries) w[i] = word_load(p + (size_t)i * step);
-            all = all && (unsigned)(w[i] >> 32) == stamp;
+        for (int i = 0; i < N; ++i) {
+            all = all && (i >= n || (unsigned)(w[i] >> 32) == stamp);
+            out[i] = (unsigned)w[i];
         }
-        out[i] = (unsigned)w[i];
+        if (!__any(!all) || tries >= polls) break;
     }
     return all;
 }
@@ -118,10 +125,12 @@ __device__ __forceinline__ bool poll_words(const unsigned long long* p, int step
 
 struct PredictLds {
     double t[2048];                  // t = x A
-    double red[4][kMaskCols][8];
+    double red[4][64];               // per wave and neuron of the tile
+    double part[4];                  // parts of a column
+    int missing[4];                  // per wave: a word did not arrive
 };
 
-// x . row j of A (the whole wave; every lane returns the sum), in the order of k_predict_xa
+// x . row of the gate projection (the whole wave; every lane returns the sum), in the order of k_predict_gate
 template <typename T, int NI>
 __device__ __forceinline__ double column_dot(const typename Vec<T>::type (&a)[NI], const typename Vec<T>::type (&xr)[NI]) {
     double acc = 0.0;
@@ -141,22 +150,25 @@ __device__ __forceinline__ void load_vec(typename Vec<T>::type (&v)[NI], const T
 
 // The same sum straight from memory, for the rare case that a wait ran out: few registers instead of loads in flight
 template <typename T>
-__device__ __forceinline__ double column_dot_slow(const T* col, const T* x, int nvec, int lane) {
+__device__ __forceinline__ double column_dot_slow(const T* col, const T* x, int first, int end, int lane) {
     using V = typename Vec<T>::type;
     double acc = 0.0;
 #pragma unroll 1
-    for (int idx = lane; idx < nvec; idx += 64)
+    for (int idx = first + lane; idx < end; idx += 64)
         acc = dot_f64(reinterpret_cast<const V*>(col)[idx], reinterpret_cast<const V*>(x)[idx], acc);
     return wave_sum(acc);
 }
-// t computed by this workgroup alone (a wait that ran out)
-template <typename T>
+// t computed by this workgroup alone (a wait that ran out), the parts of a column as in ColumnPart
+template <typename T, int NI>
 __device__ __forceinline__ void own_t(const StepArgs& a, PredictLds& L) {
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, nvec = a.d / Vec<T>::N, per = ColumnPart<T, NI>::P * 64;
 #pragma unroll 1
     for (int j = threadIdx.x >> 6; j < a.rank; j += 4) {
-        const double v = column_dot_slow((const T*)a.A + (size_t)j * a.d, (const T*)a.x, a.d / Vec<T>::N, lane);
-        if (lane == 0) L.t[j] = v;
+        double part[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            part[w] = column_dot_slow((const T*)a.A + (size_t)j * a.d, (const T*)a.x, min(w * per, nvec), min((w + 1) * per, nvec), lane);
+        if (lane == 0) L.t[j] = column_total(part);
     }
     __syncthreads();
 }
@@ -169,11 +181,13 @@ struct MaskTile {
     static constexpr int VE = Vec<T>::N, LPB = 8 / VE;
     V bv[kMaskRows][LPB];
     double bd[kMaskRows][8];
-    float cv[8];
+    float cv;                        // offset of neuron 64 * tile + lane
     int n0;
+    bool own_ok;                     // ... which exists
     __device__ __forceinline__ void request(const StepArgs& a, int tile) {
-        const int tid = threadIdx.x, cl = tid & (kMaskCols - 1), jg = tid >> 3;
+        const int tid = threadIdx.x, cl = tid & (kMaskCols - 1), jg = tid >> 3, own = tile * 64 + (tid & 63);
         n0 = (tile * kMaskCols + cl) * 8;
+        own_ok = own < a.F;
         const T* B = (const T*)a.B;
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) {
@@ -182,8 +196,7 @@ struct MaskTile {
             for (int q = 0; q < LPB; ++q)
                 bv[u][q] = (n0 < a.F && j < a.rank) ? reinterpret_cast<const V*>(B + (size_t)j * a.F + n0)[q] : V(0);
         }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) cv[e] = (a.c && tid < kMaskCols && n0 < a.F) ? a.c[n0 + e] : 0.f;
+        cv = (a.c && own_ok) ? a.c[own] : 0.f;
     }
     // widening takes longer than the multiply-adds (64 values per thread, quarter-rate conversions: 0.6 us), so it is done
     // while t is still on its way
@@ -195,10 +208,10 @@ struct MaskTile {
 #pragma unroll
                 for (int e = 0; e < VE; ++e) bd[u][q * VE + e] = (double)bv[u][q][e];
     }
-    // mask byte of neurons n0 .. n0 + 7 in the threads tid < kMaskCols (0 past the last neuron); one barrier
+    // the 64 mask bits of the tile (0 past the last neuron), in every wave; one barrier
     template <bool WIDE>
-    __device__ __forceinline__ unsigned finish(const StepArgs& a, PredictLds& L) {
-        const int tid = threadIdx.x, wave = tid >> 6, cl = tid & (kMaskCols - 1), jg = tid >> 3;
+    __device__ __forceinline__ unsigned long long finish(const StepArgs& a, PredictLds& L) {
+        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid & (kMaskCols - 1), jg = tid >> 3;
         const T* B = (const T*)a.B;
         double v[8];
 #pragma unroll
@@ -221,60 +234,59 @@ struct MaskTile {
                 }
             }
         }
-        // rank groups of a wave sit 8 lanes apart: halving folds, lanes 8 apart first (a DPP rotation)
-        int owner = 0;
-        auto halve = [&](auto half_c, int m) {
-            constexpr int half = decltype(half_c)::value;
-            const bool up = (tid & m) != 0;
+        // Rank groups of a wave sit 8 lanes apart.  Folds that halve what a lane holds, over lanes 8 apart (a rotation in rows
+        // of 16), then rows, then halves of the wave (a lane gives away one value and gets its partner's other): neuron 8 cl +
+        // owner ends up in lane (owner, cl).  In registers throughout, and the 64 decisions become the mask word by one
+        // ballot: 1.3 -> 0.7 us from t to the published word against exchanges through LDS and a byte per lane.
+        int owner;
+        {
+            const bool up = (lane & 8) != 0;
 #pragma unroll
-            for (int i = 0; i < half; ++i) {
-                const double send = up ? v[i] : v[i + half], keep = up ? v[i + half] : v[i];
-                v[i] = keep + (m == 8 ? dpp_from<0x128, 0xf>(send) : __shfl_xor(send, m, kWave));
+            for (int i = 0; i < 4; ++i) {
+                const double send = up ? v[i] : v[i + 4], keep = up ? v[i + 4] : v[i];
+                v[i] = keep + dpp_from<0x128, 0xf>(send);
             }
-            owner = owner * 2 + (up ? 1 : 0);
-        };
-        halve(std::integral_constant<int, 4>{}, 8);
-        halve(std::integral_constant<int, 2>{}, 16);
-        halve(std::integral_constant<int, 1>{}, 32);
-        L.red[wave][cl][owner] = v[0];
-        __syncthreads();
-        unsigned byte = 0;
-        if (tid < kMaskCols && n0 < a.F) {
-            const double th = (double)a.theta;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                double z = ((L.red[0][cl][e] + L.red[1][cl][e]) + L.red[2][cl][e]) + L.red[3][cl][e];
-                z += (double)cv[e];
-                if (z > th) byte |= 1u << e;
-            }
+            owner = up ? 4 : 0;
         }
-        return byte;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) v[i] = swap_add<16>(v[i], v[i + 2]);
+        v[0] = swap_add<32>(v[0], v[1]);
+        owner += ((lane >> 4) & 1) * 2 + (lane >> 5);
+        L.red[wave][cl * 8 + owner] = v[0];
+        __syncthreads();
+        double z = ((L.red[0][lane] + L.red[1][lane]) + L.red[2][lane]) + L.red[3][lane];
+        z += (double)cv;
+        return __ballot(own_ok && z > (double)a.theta);
     }
 };
 
 template <typename T, int NI>
 __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, PredictLds& L) {
-    using V = typename Vec<T>::type;
-    const int tid = threadIdx.x, lane = tid & 63, nvec = a.d / Vec<T>::N;
-    const int j = block * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool producer = j < a.rank;                // uniform over the wave
+    const int tid = threadIdx.x, nvec = a.d / Vec<T>::N;
+    const bool producer = block < a.rank;
     const bool has_tile = block * kMaskCols * 8 < a.F;
-    V col[NI], xr[NI];
+    ColumnPart<T, NI> col;
     if (producer) {
-        load_vec<T, NI>(xr, (const T*)a.x, nvec, lane);
-        load_vec<T, NI>(col, (const T*)a.A + (size_t)j * a.d, nvec, lane);
+        col.load(col.x, (const T*)a.x, nvec);
+        col.load(col.a, (const T*)a.A + (size_t)block * a.d, nvec);
     }
     MaskTile<T> tile;
     if (has_tile) tile.request(a, block);
     const int err = a.st->cur.error;
     const unsigned now = (unsigned)a.st->cur.step + 1u;
     if (err) return;
-    if (producer) {
-        const double v = column_dot<T, NI>(col, xr);
-        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-        if (lane < 2 * kWordReps)
-            word_store(a.t_words + (size_t)(lane >> 1) * a.t_pitch + 2 * j + (lane & 1), now,
-                       (lane & 1) ? (unsigned)(u >> 32) : (unsigned)u);
+    for (int j = block; j < a.rank; j += a.n_pred) {
+        if (j != block) {
+            col.load(col.a, (const T*)a.A + (size_t)j * a.d, nvec);
+            __syncthreads();                         // (the parts of the column before are still read)
+        }
+        const double v = col.sum();
+        if ((tid & 63) == 0) L.part[tid >> 6] = v;
+        __syncthreads();
+        if (tid < 2 * kWordReps) {
+            const unsigned long long u = __builtin_bit_cast(unsigned long long, column_total(L.part));
+            word_store(a.t_words + (size_t)(tid >> 1) * a.t_pitch + 2 * j + (tid & 1), now, (tid & 1) ? (unsigned)(u >> 32) : (unsigned)u);
+        }
     }
     if (!has_tile) return;
     tile.widen();
@@ -289,17 +301,22 @@ __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, Predi
         for (int i = 0; i < 4; ++i)
             if (i < n) t32[i0 + i * 256] = p[i];
     }
-    if (__syncthreads_or(!ok)) own_t<T>(a, L);
-    const unsigned byte = tile.template finish<true>(a, L);
+    const bool missing = __any(!ok);
+    if ((tid & 63) == 0) L.missing[tid >> 6] = missing;
+    __syncthreads();
+    if (__builtin_expect((L.missing[0] | L.missing[1] | L.missing[2] | L.missing[3]) != 0, 0)) {
+        __syncthreads();
+        own_t<T, NI>(a, L);
+    }
+    const unsigned long long word = tile.template finish<true>(a, L);
     if (tid < 64) {
-        unsigned w = byte << (8 * (tid & 3));        // lanes 0..3 and 4..7: the halves of the 64-bit mask word
-        w |= __shfl_xor(w, 1, kWave);
-        w |= __shfl_xor(w, 2, kWave);
-        w = __shfl(w, (tid & 1) * 4, kWave);
-        if (tid < 2 * kWordReps) word_store(a.m_words + (size_t)(tid >> 1) * a.m_pitch + 2 * block + (tid & 1), now, w);
-        if (tid < kMaskCols && tile.n0 < a.F) {
-            a.masks[tile.n0 >> 3] = (uint8_t)byte;
-            a.step_mask[tile.n0 >> 3] = (uint8_t)byte;
+        if (tid < 2 * kWordReps)
+            word_store(a.m_words + (size_t)(tid >> 1) * a.m_pitch + 2 * block + (tid & 1), now,
+                       (tid & 1) ? (unsigned)(word >> 32) : (unsigned)word);
+        const int at = block * kMaskCols + tid;              // mask byte
+        if (tid < kMaskCols && at * 8 < a.F) {
+            a.masks[at] = (uint8_t)(word >> (8 * tid));
+            a.step_mask[at] = (uint8_t)(word >> (8 * tid));
         }
     }
 }
@@ -350,7 +367,7 @@ constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ?
 
 // ---- window, deletion plan, loaders ----------------------------------------------------------------------------
 
-constexpr int kPtrLds = 4096;        // slot owners staged in LDS
+constexpr int kPtrLds = 8192;        // slot owners staged in LDS
 constexpr int kNoDst = 0xffff;       // dead tail slot (a hole lies below n' <= 65535, so it is never slot 65535)
 constexpr int kHoleFew = 2048;       // holes kept in LDS; longer lists go to the global scratch list
 struct PlanLds {
@@ -358,26 +375,28 @@ struct PlanLds {
     union {
         PredictLds predict;                  // only when a wait ran out
         struct {
-            uint16_t ids[kListItems], dst[kListItems];       // work items: new neuron, destination of the tail row (kNoDst)
-            uint16_t hole[kHoleFew];
-            uint16_t blk_h[1024], blk_f[1024];       // per 64-slot block: counts, then exclusive prefixes
+            uint16_t ids[kListItems];        // loaders: the new neurons of the work items
+            uint16_t hole[kHoleFew];         // bookkeeping: the deletion plan
+            uint16_t fill_before[1024];      // fillers below the granule
+            uint16_t ptr[kPtrLds];           // owners (neurons are numbers below 65536)
+            unsigned long long dead[1024];   // dead slots of the block
         };
     };
-    uint16_t ptr[kPtrLds];                   // (of the slots in use: neurons are numbers below 65536)
     unsigned long long wave_tot[4];
     int cnt_age[264];
     unsigned byte[4];
-    unsigned long long flag_h[64], flag_f[64];       // per block: which slots are holes, fillers (plan_alone)
-    int classified;                          // waves that have written their share of those
-    int planned;                             // wave 1 has written dst
+    int off[64];                             // list positions of the first wave's added neurons
+    unsigned long long first_bits;           // the neuron of the loader's first unit: bit number first_at.y of these that is
+    int2 first_at;                           //  set, from neuron first_at.x on
+    int listed;                              // waves that have written their part of ids
 };
 
 // All mask words computed by this workgroup alone (a wait that ran out): m[i] of the words this thread owns
-template <typename T, bool GATE>
+template <typename T, int NI, bool GATE>
 __device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt, unsigned long long (&m)[4]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nwords = (a.F + 63) >> 6;
-    if constexpr (!GATE) own_t<T>(a, L.predict);
+    if constexpr (!GATE) own_t<T, NI>(a, L.predict);
 #pragma unroll
     for (int i = 0; i < 4; ++i) m[i] = 0ull;
 #pragma unroll 1
@@ -390,7 +409,7 @@ __device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt
 #pragma unroll 1
                 for (int e = 0; e < 8 && grp * 8 < a.F; ++e) {
                     const int i = grp * 8 + e;
-                    const double v = column_dot_slow((const T*)a.A + (size_t)i * a.d, (const T*)a.x, a.d / Vec<T>::N, lane);
+                    const double v = column_dot_slow((const T*)a.A + (size_t)i * a.d, (const T*)a.x, 0, a.d / Vec<T>::N, lane);
                     if (v + (double)a.b[i] > (double)a.theta) byte |= 1u << e;
                 }
                 __syncthreads();
@@ -402,14 +421,9 @@ __device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt
             MaskTile<T> tile;
             tile.request(a, w);
             __syncthreads();
-            const unsigned byte = tile.template finish<false>(a, L.predict);
-            unsigned v = byte << (8 * (tid & 3));
-            v |= __shfl_xor(v, 1, kWave);
-            v |= __shfl_xor(v, 2, kWave);
-            if (tid < kMaskCols && (tid & 3) == 0) L.byte[tid >> 2] = v;
-            __syncthreads();
-            half[0] = L.byte[0];
-            half[1] = L.byte[1];
+            const unsigned long long word = tile.template finish<false>(a, L.predict);
+            half[0] = (unsigned)word;
+            half[1] = (unsigned)(word >> 32);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -431,8 +445,8 @@ __device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt
 //               get as many activation parts as down parts (a counter drawn from by atomics balanced no better, and the
 //               wait for its answer cost 1.5 us per unit; with all activation parts first, rows of 16 KiB loaded a
 //               quarter slower, all reads falling on the same half of every row);
-//   waves 1..3  make the deletion plan meanwhile (LDS only), then move the tail rows that nothing overwrites (more
-//               neurons removed than added; with several tokens one wave does).
+//   waves 1..3  list the added neurons meanwhile, then move the tail rows that nothing overwrites (more neurons removed than
+//               added; with several tokens wave 0 does).
 // Lane l holds the same 16-byte pieces of every vector as in the activation role and sums in the same order.
 //
 // Several tokens (MODE kDots, kMfma): the masks were written by the launch before this one and x lies in LDS.  Wave 0 puts the
@@ -464,7 +478,6 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     constexpr bool PAIRED = NI > 2;
     constexpr int GA = PAIRED ? (GLU ? 2 : 1) : (GLU ? 3 : 2);   // vectors of a unit at most
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned long long lt = (1ull << lane) - 1ull;
     const int F = a.F, d = a.d, capacity = a.capacity, k = a.k;
     const int nwords = (F + 63) >> 6, wpt = (nwords + 255) >> 8;   // mask words per thread (1..4)
     DevState* st = a.st;
@@ -477,7 +490,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
 #pragma unroll
         for (int q = 0; q < kPtrLds / 256; ++q) L.ptr[q * 256 + tid] = (uint16_t)id[q];
     };
-    stage_owners();
+    if (wg == 0) stage_owners();
     const StepCounts cur = st->cur;
     if (cur.error) {
         if (wg == 0 && tid == 0) {
@@ -516,24 +529,41 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     T* matrix = (T*)a.matrix;
     V hv[GA][NI], mv[GA][NI];                                    // the vectors of a unit: host bundle, tail row
     int k_eff = k, off_a = 0, off_r = 0, tot_a = 0, tot_r = 0, n2 = 0, items = 0;
-    auto diff = [&]() {
+    // counts and list positions of the added and removed neurons; returns whether any thread is `missing` its words
+    auto diff = [&](bool missing) -> bool {
         int pa = 0, pr = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             pa += __popcll(now[i] & ~prev[i]);
             pr += __popcll(prev[i] & ~now[i]);
         }
-        block_exclusive_scan2<4, true>(pa, pr, L.wave_tot, &off_a, &off_r, &tot_a, &tot_r);
+        const int v = (pr << 16) | pa, inc = wave_inclusive_scan(v, lane), ex = inc - v;         // (a wave counts at most 16384)
+        const unsigned long long none = __any(missing) ? 1ull << 63 : 0ull;
+        if (lane == kWave - 1) L.wave_tot[wave] = none | ((unsigned long long)(unsigned)(inc >> 16) << 32) | (unsigned)(inc & 0xffff);
+        lds_barrier();
+        unsigned long long before = 0, all = 0, flags = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const unsigned long long t = L.wave_tot[i];
+            flags |= t;
+            if (i < wave) before += t & ~(1ull << 63);
+            all += t & ~(1ull << 63);
+        }
+        off_a = (int)(unsigned)before + (ex & 0xffff);
+        off_r = (int)(unsigned)(before >> 32) + (ex >> 16);
+        tot_a = (int)(unsigned)all;
+        tot_r = (int)(unsigned)(all >> 32);
+        return (flags >> 63) != 0;
     };
     // the added neurons q of [c0, c0 + kListItems) (the words come back from LDS: in registers they would be live through
     // the load loop)
-    auto fill_ids = [&](int c0) {
-        int q = off_a - c0;
+    auto fill_ids = [&](int c0, int of, int at) {                // the words of thread `of`, whose first one has list position `at`
+        int q = at - c0;
 #pragma unroll 1
         for (int i = 0; i < wpt; ++i) {
-            unsigned long long bits = L.add[tid * wpt + i];
+            unsigned long long bits = L.add[of * wpt + i];
             while (bits) {
-                if ((unsigned)q < (unsigned)kListItems) L.ids[q] = (uint16_t)((tid * wpt + i) * 64 + __ffsll((long long)bits) - 1);
+                if ((unsigned)q < (unsigned)kListItems) L.ids[q] = (uint16_t)((of * wpt + i) * 64 + __ffsll((long long)bits) - 1);
                 bits &= bits - 1;
                 ++q;
             }
@@ -591,23 +621,10 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             if (in_part(g, part)) store_pieces(row_vec(s, part * GA + g), v[g]);
     };
     const int nblk = (n + kWave - 1) >> 6;
-    // slot owner of this lane in block b; blocks past the staged ones are read again
-    auto owner = [&](int b) {
-        const int s = b * kWave + lane;
-        int id = L.ptr[min(s, kPtrLds - 1)];
-        if (b >= kPtrLds / kWave) id = s < n ? a.pointers[s] : -1;
-        return id;
-    };
-    auto flags_of = [&](int b, int id, bool& hole, bool& fill) {
-        const int s = b * kWave + lane;
-        const bool dead = (unsigned)id >= (unsigned)F || ((L.rem[id >> 6] >> (id & 63)) & 1ull);
-        hole = s < n2 && dead;
-        fill = s >= n2 && s < n && !dead;
-    };
-
     // ---- masks -> window -> id list -> first host read ----
     const int x_pieces = nvec * a.batch;
     V xs[MODE == kOneToken ? 1 : 16];
+    bool missing = false;
     if constexpr (MODE != kOneToken) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -626,18 +643,27 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     } else {
         unsigned p[8];
         const int w0 = tid * wpt, nw = max(0, min(wpt, nwords - w0));
-        const bool ok = poll_words<8>(a.m_words + (size_t)(wg & (kWordReps - 1)) * a.m_pitch + 2 * w0, 1, 2 * nw, stamp_now,
+        missing = !poll_words<8>(a.m_words + (size_t)(wg & (kWordReps - 1)) * a.m_pitch + 2 * w0, 1, 2 * nw, stamp_now,
                                       a.polls, p);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (i < nw) m[i] = ((unsigned long long)p[2 * i + 1] << 32) | p[2 * i];
-        if (__syncthreads_or(!ok)) own_masks<T, GATE>(a, L, wpt, m);        // (does not touch the staged owners)
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) now[i] = keep[i] | m[i];
-    diff();
+    const bool none = diff(missing);
+    if constexpr (MODE == kOneToken) {
+        if (__builtin_expect(none, 0)) {                         // a wait ran out
+            lds_barrier();
+            own_masks<T, NI, GATE>(a, L, wpt, m);
+            if (wg == 0) stage_owners();                         // (their place has been used)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) now[i] = keep[i] | m[i];
+            diff(false);
+        }
+    }
     bool over = n - tot_r < 0 || n - tot_r + tot_a > capacity;
-    if (over && a.shrink) {
+    if (__builtin_expect(over && a.shrink, 0)) {
         // Dynamic window (see k_window_plan): what this step needs in any case (m) and the ring entries of ages 1 .. j, for the
         // largest j for which they fit.
         auto age_word = [&](int age, int w) -> unsigned long long {
@@ -688,10 +714,10 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             if (i < wpt && w < nwords)
                 for (int age = 1; age <= min(fit, oldest); ++age) now[i] |= age_word(age, w);
         }
-        diff();
+        diff(false);
         over = fit < 0 || n - tot_r < 0 || n - tot_r + tot_a > capacity;
     }
-    if (over) {                                      // uniform: leave everything untouched
+    if (__builtin_expect(over, 0)) {                 // uniform: leave everything untouched
         if (wg == 0 && tid == 0) {
             *a.n_added = 0;
             *a.n_removed = 0;
@@ -704,206 +730,119 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     }
     n2 = n - tot_r;
     items = max(tot_a, tot_r);
+    // The word with the neuron of this loader's first unit is looked up by the thread that holds it (the neuron is its r-th bit); the
+    // list is written while the first host read is on its way.
+    const int unit0 = PAIRED ? lw >> 1 : lw;
+    {
+        int r = unit0 - off_a;
+        bool mine = wg > 0 && r >= 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (i < wpt) {
-            L.rem[tid * wpt + i] = prev[i] & ~now[i];
-            L.add[tid * wpt + i] = now[i] & ~prev[i];
+        for (int i = 0; i < 4; ++i) {
+            if (i < wpt) {
+                const unsigned long long bits = now[i] & ~prev[i];
+                L.rem[tid * wpt + i] = prev[i] & ~now[i];
+                L.add[tid * wpt + i] = bits;
+                const int c = __popcll(bits);
+                if (mine && r < c) {
+                    L.first_bits = bits;
+                    L.first_at = make_int2((tid * wpt + i) * 64, r);
+                    mine = false;
+                }
+                r -= c;
+            }
         }
-    fill_ids(0);                                                 // (reads only what this thread has just written)
-    if (tid == 0) L.planned = L.classified = 0;
+    }
+    if (wave == 0) L.off[lane] = off_a;
+    if (tid == 0) L.listed = 0;
     if constexpr (MODE != kOneToken)
         if (tid == 0) post->seq = post->done = post->arrived = 0;
     lds_barrier();
 
-    // ---- deletion plan (see k_window_plan): holes = dead slots below n', fillers = live slots at or above it ----
-    // Up to 4096 rows waves 1..3 make it while the first host read of wave 0 is on its way (plan_alone).  More rows, and
-    // the bookkeeping workgroup (which needs the number of moves): all waves together, ahead of the host reads.
-    const bool alone = wg > 0 && nblk <= kWave;
-    int H = 0;
-    // destination of the tail slot of this lane in block b (kNoDst: dead) for the items [c0, ...)
-    auto put_dst = [&](int b, bool fill, int c0) {
-        const unsigned long long bf = __ballot(fill);
-        const int q = b * kWave + lane - n2;
-        if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
-            const int r = H - 1 - (L.blk_f[b] + __popcll(bf & lt));
-            int dst = kNoDst;
-            if (fill && r >= 0 && r < H) {
-                if (H <= kHoleFew) dst = L.hole[r];
-                else dst = a.hole_list[r];
-            }
-            L.dst[q - c0] = (uint16_t)dst;
-        }
-    };
-    if (tot_r > 0 && !alone) {                                   // uniform
-        // The dead slots of block b are kept by the wave that classifies it (number i = b / 4 of its blocks) in lane i mod 64 of
-        // dead[i / 64]: looked up again in every pass, the owners past the staged ones cost a memory round trip per block (OPT shape, 4
-        // tokens: 140 -> 125 us a step at 15700 rows, 124 -> 111 at 14300; one token 91 -> 88 at 6600; up to 4096 rows the same).
-        unsigned long long dead[4] = {0ull, 0ull, 0ull, 0ull};
-        auto classify = [&](int b, int id, unsigned long long removed) {         // removed: word id / 64 of L.rem
-            const int i = b >> 2, s = b * kWave + lane;
-            const unsigned long long m = __ballot((unsigned)id >= (unsigned)F || ((removed >> (id & 63)) & 1ull));
+    if (wg == 0) {
+        // ---- deletion plan (see k_window_plan): holes = dead slots below n', fillers = live slots at or above it ----
+        // Made here once and handed to the loaders as stamped words, which arrive before their first bundle does.  (Made by every
+        // loader for itself, by the waves that do not load, it was known 1 us later with few rows; with more than 4096 rows, ahead of
+        // the host reads, it kept them waiting for 14 us: a loader cannot look owners up behind a host read.)
+        // (All of it by a wave and 64 slots at a time took 0.4 us each: 8700 rows 14 us, now 6.)
+        int H = 0;
+        if (tot_r > 0) {                                         // uniform
+            // (Compact on purpose: one workgroup runs this once, so most of its time are instructions on their way to the cache.)
+            constexpr int kRound = 8, kStaged = kPtrLds / kWave; // blocks of a wave at a time; blocks whose owners are staged
+            static_assert(kStaged % (4 * kRound) == 0, "a round is staged as a whole or not at all");
+            int far[kRound];                                     // owners past the staged ones, requested a round ahead
+            auto request = [&](int b0) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dead[r] = (i == r * kWave + lane) ? m : dead[r];
-            const int ch = __popcll(__ballot(s < n2) & m), cf = __popcll(__ballot(s >= n2 && s < n) & ~m);
-            if (lane == 0 && b < nblk) {
-                L.blk_h[b] = (uint16_t)ch;
-                L.blk_f[b] = (uint16_t)cf;
-            }
-        };
-        auto dead_of = [&](int b) -> unsigned long long {            // uniform; never under a condition that differs between lanes
-            const int i = b >> 2;
-            const unsigned long long v = i < 64 ? dead[0] : i < 128 ? dead[1] : i < 192 ? dead[2] : dead[3];
-            return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), i & 63) << 32) |
-                   (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, i & 63);
-        };
-        static_assert(kPtrLds / kWave % 32 == 0, "a round is staged as a whole or not at all");
+                for (int q = 0; q < kRound; ++q) far[q] = a.pointers[min((b0 + q * 4) * kWave + lane, capacity - 1)];
+            };
+            if (nblk > kStaged) request(kStaged + wave);
 #pragma unroll 1
-        for (int b0 = wave; b0 < nblk; b0 += 4 * 8) {
-            int id[8];
-            if (b0 < kPtrLds / kWave) {                          // uniform
+            for (int b0 = wave; b0 < nblk; b0 += 4 * kRound) {
+                int id[kRound];
+                if (b0 < kStaged) {                              // uniform
 #pragma unroll
-                for (int q = 0; q < 8; ++q) id[q] = L.ptr[(b0 + q * 4) * kWave + lane];
-            } else {
+                    for (int q = 0; q < kRound; ++q) id[q] = L.ptr[(b0 + q * 4) * kWave + lane];
+                } else {
 #pragma unroll
-                for (int q = 0; q < 8; ++q) id[q] = a.pointers[min((b0 + q * 4) * kWave + lane, capacity - 1)];
+                    for (int q = 0; q < kRound; ++q) id[q] = far[q];
+                    request(b0 + 4 * kRound);
+                }
+                unsigned long long w[kRound];
+#pragma unroll
+                for (int q = 0; q < kRound; ++q) w[q] = L.rem[min((unsigned)id[q] >> 6, 1023u)];
+                unsigned long long dead = 0ull;                  // of block b0 + 4 * lane
+#pragma unroll
+                for (int q = 0; q < kRound; ++q) {
+                    const unsigned long long m = __ballot((unsigned)id[q] >= (unsigned)F || ((w[q] >> (id[q] & 63)) & 1ull));
+                    dead = lane == q ? m : dead;
+                }
+                if (lane < kRound && b0 + lane * 4 < nblk) L.dead[b0 + lane * 4] = dead;
             }
-#pragma unroll
-            for (int g = 0; g < 8; g += 4) {
-                unsigned long long w[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) w[q] = L.rem[min((unsigned)id[g + q] >> 6, 1023u)];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)                      // (one token: 0.7 us faster with the branch, a batch 0.6 without)
-                    if (MODE != kOneToken || b0 + (g + q) * 4 < nblk) classify(b0 + (g + q) * 4, id[g + q], w[q]);
-            }
-        }
-        lds_barrier();
-        {                                                        // prefix over the blocks, bpt consecutive ones per thread
-            const int bpt = (nblk + 255) >> 8;
-            int vh = 0, vf = 0, fillers;
+            lds_barrier();
+            // A thread counts the holes and fillers of consecutive granules (one, or up to four with more than 16384 rows) and, behind
+            // a prefix sum, lists the holes.  Granules of 16 slots where that many threads are there: a thread takes 0.1 us a hole.
+            const int gl = nblk <= 64 ? 4 : nblk <= 128 ? 5 : 6, g = 1 << gl;            // slots of a granule
+            auto slots_below = [](int k) -> unsigned long long { return k <= 0 ? 0ull : k < 64 ? ~(~0ull << k) : ~0ull; };
+            auto dead_in = [&](int i) -> unsigned long long { return L.dead[(i << gl) >> 6] >> ((i << gl) & 63); };
+            auto holes_in = [&](int i) -> unsigned long long { return dead_in(i) & slots_below(min(n2 - (i << gl), g)); };
+            auto fill_in = [&](int i) -> unsigned long long {
+                return ~dead_in(i) & slots_below(min(n - (i << gl), g)) & ~slots_below(n2 - (i << gl));
+            };
+            const int per = (((n + g - 1) >> gl) + 255) >> 8, i_first = tid * per, i_end = min((n + g - 1) >> gl, i_first + per);
+            int vh = 0, vf = 0, ph, pf, fillers;
 #pragma unroll 1
-            for (int b = tid * bpt; b < min(nblk, tid * bpt + bpt); ++b) {
-                vh += L.blk_h[b];
-                vf += L.blk_f[b];
+            for (int i = i_first; i < i_end; ++i) {
+                vh += __popcll(holes_in(i));
+                vf += __popcll(fill_in(i));
             }
-            int ph, pf;
-            block_exclusive_scan2<4, true>(vh, vf, L.wave_tot, &ph, &pf, &H, &fillers);
+            block_exclusive_scan2<4, false>(vh, vf, L.wave_tot, &ph, &pf, &H, &fillers);
+            const bool in_lds = H <= kHoleFew;                   // (longer lists go through memory)
 #pragma unroll 1
-            for (int b = tid * bpt; b < min(nblk, tid * bpt + bpt); ++b) {
-                const int ch = L.blk_h[b], cf = L.blk_f[b];
-                L.blk_h[b] = (uint16_t)ph;
-                L.blk_f[b] = (uint16_t)pf;
-                ph += ch;
-                pf += cf;
-            }
-        }
-        lds_barrier();
-        if (wg > 0) {
-            const bool in_lds = H <= kHoleFew;                   // longer lists: every workgroup writes the same values to global
-            const int hblk = (n2 + kWave - 1) >> 6;              // blocks with slots below the tail
+            for (int i = i_first; i < i_end; ++i) {
+                L.fill_before[i] = (uint16_t)pf;
+                pf += __popcll(fill_in(i));
 #pragma unroll 1
-            for (int b = wave; b < hblk; b += 4) {
-                const int s = b * kWave + lane;
-                const unsigned long long bh = dead_of(b) & __ballot(s < n2);
-                if ((bh >> lane) & 1ull) {
-                    const int pos = L.blk_h[b] + __popcll(bh & lt);
-                    if (in_lds) L.hole[pos] = (uint16_t)s;
-                    else a.hole_list[pos] = s;
+                for (unsigned long long bits = holes_in(i); bits; bits &= bits - 1) {
+                    const int hole = (i << gl) + __ffsll((long long)bits) - 1;
+                    if (__builtin_expect(in_lds, 1)) L.hole[ph] = (uint16_t)hole;
+                    else a.hole_list[ph] = hole;
+                    ++ph;
                 }
             }
             if (in_lds) lds_barrier();
             else __syncthreads();
-            const int tail = n2 >> 6;                            // first block with slots of the first items
 #pragma unroll 1
-            for (int b = tail + ((wave - tail) & 3); b < nblk; b += 4) {
-                const int s = b * kWave + lane;
-                const unsigned long long m = dead_of(b);         // (by the whole wave)
-                put_dst(b, s >= n2 && s < n && !((m >> lane) & 1ull), 0);
-            }
-        }
-    }
-    auto fill_dst = [&](int c0) {                                // later pieces of the list (`dead` is not kept through the load loop)
-        const int tail = (n2 + c0) >> 6;
-#pragma unroll 1
-        for (int b = tail + ((wave - tail) & 3); b < nblk; b += 4) {
-            bool hole, fill;
-            flags_of(b, owner(b), hole, fill);
-            put_dst(b, fill, c0);
-        }
-    };
-    // The plan for at most 64 blocks, all of them staged, by waves 1..3: they share the classification, wave 1 does the rest.
-    auto plan_alone = [&](int c0) {
-        for (int b0 = (wave - 1) * 4; b0 < nblk; b0 += 12) {
-            int id[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) id[q] = L.ptr[min(b0 + q, kPtrLds / kWave - 1) * kWave + lane];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {                        // (blocks past the last one have no slots in use)
-                bool hole, fill;
-                flags_of(b0 + q, id[q], hole, fill);
-                const unsigned long long bh = __ballot(hole), bf = __ballot(fill);
-                if (lane == 0 && b0 + q < kWave) {
-                    L.flag_h[b0 + q] = bh;
-                    L.flag_f[b0 + q] = bf;
+            for (int q = tid; q < tot_r; q += 256) {
+                const int s = n2 + q;
+                const unsigned long long fill = fill_in(s >> gl), self = 1ull << (s & (g - 1));
+                int dst = kNoDst;
+                if (fill & self) {
+                    const int r = H - 1 - (L.fill_before[s >> gl] + __popcll(fill & (self - 1ull)));
+                    if (r >= 0) dst = in_lds ? (int)L.hole[r] : a.hole_list[r];
                 }
+                word_store(a.plan_words + q, stamp_now, (unsigned)dst);
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        if (lane == 0) __hip_atomic_fetch_add(&L.classified, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (wave != 1) return;
-        while (__hip_atomic_load(&L.classified, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < 3) __builtin_amdgcn_s_sleep(1);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        // lane b keeps the flags of block b, and lists its holes
-        unsigned long long mh = lane < nblk ? L.flag_h[lane] : 0ull;
-        const unsigned long long mf = lane < nblk ? L.flag_f[lane] : 0ull;
-        const int v = __popcll(mh) | (__popcll(mf) << 16), inc = wave_inclusive_scan(v, lane), ex = inc - v;
-        const int holes = __builtin_amdgcn_readlane(inc, kWave - 1) & 0xffff;
-        for (int pos = ex & 0xffff; __any(mh != 0ull); ++pos) {
-            if (mh) L.hole[min(pos, kHoleFew - 1)] = (uint16_t)(lane * kWave + __ffsll((long long)mh) - 1);
-            mh &= mh - 1;
-        }
-        // (at most half of 4096 rows can be holes: kHoleFew)
-        __builtin_amdgcn_wave_barrier();
-        for (int b = (n2 + c0) >> 6; b < nblk; ++b) {
-            const unsigned long long bf = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(mf >> 32), b) << 32) |
-                                          (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mf, b);
-            const int q = b * kWave + lane - n2;
-            if (q >= 0 && q < tot_r && (unsigned)(q - c0) < (unsigned)kListItems) {
-                const int r = holes - 1 - ((int)((unsigned)__builtin_amdgcn_readlane(ex, b) >> 16) + __popcll(bf & lt));
-                L.dst[q - c0] = (((bf >> lane) & 1ull) && r >= 0) ? L.hole[r] : (uint16_t)kNoDst;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        if (lane == 0) __hip_atomic_store(&L.planned, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    if (wg > 0 && !alone) lds_barrier();
-    if (loads && lw < (PAIRED ? 2 * tot_a : tot_a))              // unit lw (below kListItems)
-        request_host(__builtin_amdgcn_readfirstlane((int)L.ids[PAIRED ? lw >> 1 : lw]), PAIRED ? lw & 1 : 0);
 
-    if constexpr (MODE != kOneToken) {
-        if (wg > 0) {
-            int t = tid / nvec, p = tid - t * nvec;
-            const int dt = 256 / nvec, dp = 256 - dt * nvec;
-#pragma unroll
-            for (int g = 0; g < 16; g += 4)
-                if (g * 256 < x_pieces) {
-#pragma unroll
-                    for (int i = g; i < g + 4; ++i) {
-                        if (i * 256 + tid < x_pieces) reinterpret_cast<V*>(lds_x + t * a.x_pitch)[p] = xs[i];
-                        t += dt;
-                        p += dp;
-                        if (p >= nvec) {
-                            p -= nvec;
-                            ++t;
-                        }
-                    }
-                }
-            lds_barrier();
-        }
-    }
-
-    if (wg == 0) {
         // ---- bookkeeping: window state, id lists, counts ----
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -948,13 +887,49 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         return;
     }
 
+    if (loads && lw < (PAIRED ? 2 * tot_a : tot_a)) {            // unit lw (below kListItems)
+        const unsigned long long bits = L.first_bits;
+        const int2 at = L.first_at;
+        const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bits >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bits, 0u));
+        const unsigned long long it = __ballot(((bits >> lane) & 1ull) && before == at.y);
+        request_host(__builtin_amdgcn_readfirstlane(at.x) + __ffsll((long long)it) - 1, PAIRED ? lw & 1 : 0);
+    }
+    if (wave > 0) {
+        if (wave == 1) fill_ids(0, lane, L.off[lane]);           // (for the wave that loads)
+        fill_ids(0, tid, off_a);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) __hip_atomic_fetch_add(&L.listed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+
+    if constexpr (MODE != kOneToken) {
+        {
+            int t = tid / nvec, p = tid - t * nvec;
+            const int dt = 256 / nvec, dp = 256 - dt * nvec;
+#pragma unroll
+            for (int g = 0; g < 16; g += 4)
+                if (g * 256 < x_pieces) {
+#pragma unroll
+                    for (int i = g; i < g + 4; ++i) {
+                        if (i * 256 + tid < x_pieces) reinterpret_cast<V*>(lds_x + t * a.x_pitch)[p] = xs[i];
+                        t += dt;
+                        p += dp;
+                        if (p >= nvec) {
+                            p -= nvec;
+                            ++t;
+                        }
+                    }
+                }
+            lds_barrier();
+        }
+    }
+
     // ---- load and move ----
     const int new_step = cur.step + 1, nw = a.n_load;
     V xr[MODE == kOneToken ? NI : 1];                            // (behind the first host read: needed once that has arrived)
     auto load_x = [&]() {
         if constexpr (MODE == kOneToken) load_pieces(xr, (const char*)a.x);
     };
-    if (wave == 0 || !alone) load_x();                           // (the others have a plan to make first)
+    if (wave == 0) load_x();
     // What a slot becomes: the activation of a row, in the order of operations of the activation role
     constexpr int GV = GLU ? 2 : 1;                              // vectors it needs
     auto partial_dots = [&](const V (&v)[GA][NI], float& pu, float& pg) {
@@ -1130,36 +1105,63 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         if constexpr (MODE != kOneToken && GATE) return a.gact[(size_t)min(lane, a.batch - 1) * F + min(max(id, 0), F - 1)];
         return 0.f;
     };
-    auto old_owner = [&](int s) -> int {
-        int id = L.ptr[min(s, kPtrLds - 1)];
-        if (s >= kPtrLds) id = a.pointers[s];
-        return id;
+    // What was in the cache before this step does not change during the launch and is read through the scalar cache: a vector
+    // load behind host reads takes as long as they do.  (s and id are uniform.)
+    auto owner_of = [&](int s) -> int { return uniform_load(a.pointers + s); };
+    // destination of the tail slot n' + q: its word is asked for behind the host read and arrives with it
+    auto plan_word = [&](int q) -> unsigned long long { return q < tot_r ? word_load(a.plan_words + q) : 0ull; };
+    // ... worked out by this wave alone (a wait that ran out): the place of the slot among the fillers, then the hole
+    auto own_dst = [&](int q) -> int {
+        auto dead_slots = [&](int b) -> unsigned long long {     // of block b
+            const int id = a.pointers[min(b * kWave + lane, capacity - 1)];
+            return __ballot((unsigned)id >= (unsigned)F || ((L.rem[min((unsigned)id >> 6, 1023u)] >> (id & 63)) & 1ull));
+        };
+        auto slots = [&](int b, int from, int to) -> unsigned long long {        // those of block b in [from, to)
+            const int s = b * kWave + lane;
+            return __ballot(s >= from && s < to);
+        };
+        const int s = n2 + q;
+        if ((dead_slots(s >> 6) >> (s & 63)) & 1ull) return kNoDst;
+        int above = 0;                                           // fillers above s: the lowest hole takes the last one
+#pragma unroll 4
+        for (int b = s >> 6; b <= (n - 1) >> 6; ++b) above += __popcll(~dead_slots(b) & slots(b, s + 1, n));
+        for (int b = 0; b * kWave < n2; ++b) {
+            unsigned long long h = dead_slots(b) & slots(b, 0, n2);
+            const int c = __popcll(h);
+            if (above < c) {
+                for (; above > 0; --above) h &= h - 1;
+                return b * kWave + __ffsll((long long)h) - 1;
+            }
+            above -= c;
+        }
+        return kNoDst;
     };
-    auto await_plan = [&]() {
-        while (!__hip_atomic_load(&L.planned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) __builtin_amdgcn_s_sleep(1);
+    auto dst_of = [&](int q, unsigned long long word) -> int {
+        if (q >= tot_r) return kNoDst;
+        for (int tries = 0; (unsigned)(word >> 32) != stamp_now && tries < a.polls; ++tries) word = word_load(a.plan_words + q);
+        if (__builtin_expect((unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(word >> 32)) != stamp_now, 0)) return own_dst(q);
+        return __builtin_amdgcn_readfirstlane((int)(unsigned)word);
+    };
+    if (wave == 0) {                                             // the list of the first piece
+        while (__hip_atomic_load(&L.listed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < 3) __builtin_amdgcn_s_sleep(1);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
+    }
     // Lists longer than kListItems are gone through piece by piece.
     for (int c0 = 0; c0 < items; c0 += kListItems) {
         if (c0 > 0) {
             lds_barrier();
-            fill_ids(c0);
-            if (tid == 0) L.planned = L.classified = 0;
-            if (tot_r > 0 && !alone) fill_dst(c0);
+            fill_ids(c0, tid, off_a);
             lds_barrier();
         }
         const int n_a = min(max(tot_a - c0, 0), kListItems), n_r = min(max(tot_r - c0, 0), kListItems);     // of this piece
         const int units = PAIRED ? 2 * n_a : n_a;
-        if (alone && wave > 0) {
-            if (tot_r > c0) plan_alone(c0);
-            load_x();
-        }
         const int only = max(n_r - n_a, 0);                      // rows that nothing overwrites
         if (MODE != kOneToken && wave > 0) work();
         if (wave == 0) {
             struct Unit {
-                int i, part, nid, dst, old_id;                   // item c0 + i
+                int i, part, nid, old_id;                        // item c0 + i
                 float old_bias, new_bias, old_gate, new_gate;
+                unsigned long long plan;
             };
             auto make_unit = [&](int u, bool ask) {              // its numbers, and the requests for its bundle
                 Unit r;
@@ -1167,31 +1169,30 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                 r.i = PAIRED ? u >> 1 : u;
                 const int s = n2 + c0 + r.i;
                 r.nid = __builtin_amdgcn_readfirstlane((int)L.ids[r.i]);
-                r.dst = r.i < n_r ? __builtin_amdgcn_readfirstlane((int)L.dst[r.i]) : kNoDst;
-                if constexpr (MODE == kOneToken) r.old_id = a.pointers[s];
-                else r.old_id = old_owner(s);
-                r.old_bias = a.bias[s];
-                r.new_bias = a.b[r.nid];
+                r.old_id = owner_of(s);
+                r.old_bias = uniform_load(a.bias + s);
+                r.new_bias = uniform_load(a.b + r.nid);
+                if (ask) request_host(r.nid, r.part);
+                request_row(s, r.part);                          // (also where nothing is moved: no branch around loads)
+                r.plan = plan_word(c0 + r.i);
                 r.old_gate = gate_of(r.old_id);
                 r.new_gate = gate_of(r.nid);
-                if (ask) request_host(r.nid, r.part);
                 return r;
             };
             int place = lw, round = 0;
             if (lw < units) {
-                if (alone && n_r > 0) await_plan();
                 Unit cu = make_unit(lw, c0 > 0);                 // (the bundle of the first piece was requested above)
-                request_row(n2 + c0 + cu.i, cu.part);            // (also where nothing is moved: no branch around loads)
                 for (;;) {
                     const int s = n2 + c0 + cu.i;
-                    const bool act = cu.part == 0, moves = cu.dst != kNoDst;      // uniform over the wave
+                    const int dst = dst_of(c0 + cu.i, cu.plan);
+                    const bool act = cu.part == 0, moves = dst != kNoDst;         // uniform over the wave
                     float mdu = 0.f, mdg = 0.f, hdu = 0.f, hdg = 0.f;
                     if (moves) {
-                        store_row(cu.dst, cu.part, mv);
+                        store_row(dst, cu.part, mv);
                         if (act) partial_dots(mv, mdu, mdg);
                     }
                     store_row(s, cu.part, hv);
-                    const Slot fresh = {s, cu.nid, cu.new_bias}, moved = {cu.dst, cu.old_id, cu.old_bias};
+                    const Slot fresh = {s, cu.nid, cu.new_bias}, moved = {dst, cu.old_id, cu.old_bias};
                     if (act) {
                         partial_dots(hv, hdu, hdg);
                         if (MODE != kOneToken) {
@@ -1210,12 +1211,9 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                     round += nw;
                     const bool more = round + place < units;
                     Unit nu = cu;
-                    if (more) {
-                        nu = make_unit(round + place, true);
-                        request_row(n2 + c0 + nu.i, nu.part);
-                    }
+                    if (more) nu = make_unit(round + place, true);
                     if (MODE == kOneToken && act) {
-                        if (moves) finish_slot(cu.dst, cu.old_id, cu.old_bias, mdu, mdg);
+                        if (moves) finish_slot(dst, cu.old_id, cu.old_bias, mdu, mdg);
                         finish_slot(s, cu.nid, cu.new_bias, hdu, hdg);
                     }
                     if (!more) break;
@@ -1226,14 +1224,14 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         // rows that nothing overwrites: by the waves that do not load, with several tokens by the one that does (whole rows)
         if constexpr (MODE == kOneToken) {
             if (wave > 0 && only > 0) {
-                if (alone) await_plan();
+                load_x();
                 for (int v = lw * 3 + wave - 1; v < (PAIRED ? 2 * only : only); v += 3 * nw) {
                     const int part = (PAIRED && v >= only) ? 1 : 0, i = n_a + v - part * only;
-                    const int dst = __builtin_amdgcn_readfirstlane((int)L.dst[i]), s = n2 + c0 + i;
+                    const int dst = dst_of(c0 + i, plan_word(c0 + i)), s = n2 + c0 + i;
                     if (dst == kNoDst) continue;
                     request_row(s, part);
-                    const int id = a.pointers[s];
-                    const float bs = a.bias[s];
+                    const int id = owner_of(s);
+                    const float bs = uniform_load(a.bias + s);
                     store_row(dst, part, mv);
                     if (part == 0) {
                         float pu, pg;
@@ -1243,14 +1241,13 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                 }
             }
         } else if (wave == 0) {
-            if (only > 0 && alone) await_plan();
             for (int i = n_a + (nw - 1 - lw); i < n_a + only; i += nw) {         // (the last ones have had the fewest units)
-                const int dst = __builtin_amdgcn_readfirstlane((int)L.dst[i]), s = n2 + c0 + i;
+                const int dst = dst_of(c0 + i, plan_word(c0 + i)), s = n2 + c0 + i;
                 if (dst == kNoDst) continue;
                 request_row(s, 0);
                 if (PAIRED) load_pieces(hv[0], row_vec(s, GA));
-                const int id = old_owner(s);
-                const Slot r = {dst, id, a.bias[s]};
+                const int id = owner_of(s);
+                const Slot r = {dst, id, uniform_load(a.bias + s)};
                 const float gb = gate_of(id);
                 store_row(dst, 0, mv);
                 if (PAIRED) store_pieces(row_vec(dst, GA), hv[0]);
@@ -1270,6 +1267,20 @@ constexpr int step1_wgs_per_cu() {
     constexpr int vectors = NI > 2 ? (GLU ? 2 : 1) : (GLU ? 3 : 2);
     return (2 * vectors + 1) * NI * 4 <= 120 ? 2 : 1;
 }
+// The activation role reads megabytes that nothing needs before the down projection; read at once they hold up the predictor, whose few
+// reads the host link waits for (x A published 3.9 to 6.2 us after the launch began instead of 2.2, Falcon and Llama-2 shapes).  So
+// its waves begin when a mask word has been published, or after kActWaits reads of it at the latest.
+constexpr int kActWaits = 64;
+__device__ __forceinline__ void await_predictor(const StepArgs& a, int block) {
+    const int words = 2 * ((a.F + 63) >> 6);
+    const unsigned long long* p = a.m_words + (size_t)(block & (kWordReps - 1)) * a.m_pitch + (unsigned)block % (unsigned)words;
+    if (a.st->cur.error || a.polls == 0) return;
+    const unsigned now = (unsigned)a.st->cur.step + 1u;
+    __builtin_amdgcn_s_sleep(127);
+    for (int tries = min(kActWaits, a.polls); tries > 0 && (unsigned)(word_load(p) >> 32) != now; --tries) __builtin_amdgcn_s_sleep(32);
+    __builtin_amdgcn_s_sleep(40);
+}
+
 template <typename T, int NI, bool GLU, bool GATE>
 __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(const StepArgs a) {
     __shared__ __align__(16) unsigned char lds[sizeof(PlanLds) > sizeof(PredictLds) ? sizeof(PlanLds) : sizeof(PredictLds)];
@@ -1281,6 +1292,7 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
         cache_role<T, NI, GLU, GATE, kOneToken>(a, block - a.n_pred, *reinterpret_cast<PlanLds*>(lds), nullptr, nullptr);
     } else {
         const int first = a.n_pred + a.n_load + 1;
+        await_predictor(a, block);
         ffn_up_role<T, NI, GLU, true>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, 1, a.capacity, a.row_elems, a.spec,
                                       block - first, gridDim.x - first, a.pointers, a.gact, a.F, a.st);
     }

@@ -23,6 +23,10 @@ CASES = {
     "dynamic-window-two-words": ("f16", False, False, 64, 17000, 64, 4, 0.1, 4500, True, 0),
     "slot-of-many-items": ("f16", False, False, 520, 6000, 32, 2, 0.35, 6000, False, 1),
     "most-rows": ("f16", False, False, 16, 65536, 16, 1, 0.85, 65536, False, 0),
+    # the deletion plan where its granules and staged owners change: about 4096, 8192 and 16384 rows in use
+    "plan-64-blocks": ("f16", False, False, 16, 4352, 16, 1, 0.94, 4352, False, 0),
+    "plan-128-blocks": ("f16", False, False, 16, 8704, 16, 1, 0.94, 8704, False, 0),
+    "plan-256-blocks": ("f16", False, False, 16, 17408, 16, 1, 0.94, 17408, False, 0),
     "many-holes": ("f16", False, False, 16, 40000, 64, 1, 0.5, 40000, False, 0),
 }
 
