@@ -158,7 +158,7 @@ struct lif_layer {
     size_t row_elems, row_bytes;
     bool window_pending;
     int expected_rows;          // hint, 0 = none
-    int mask_bt[9];             // tokens per pass of the mask kernel for a batch of b tokens (1, 4 or 8)
+    int mask_tokens;            // tokens per pass of the mask kernel at most
     unsigned char* static_scratch;  // this device's copy of the library's static scratch array (null: lookup failed)
     // event timing
     bool prof_on;
@@ -205,15 +205,14 @@ int launch_predict(lif_layer* L, const void* x, int batch, uint8_t* masks, uint8
     }
     const int grid = (c.d_ffn + kMaskCols * 8 - 1) / (kMaskCols * 8);
     Timed t(L, LIF_K_PREDICT_MASK, s);
-#define LIF_MASK(BT)                                                                                        \
-    hipLaunchKernelGGL((k_predict_mask<T, BT>), dim3(grid), dim3(256), sizeof(double) * BT * c.rank, s,          \
-                       (const T*)L->buf.B, L->buf.c, L->tpart, c.rank, c.d_ffn, batch, c.threshold, masks,         \
+    // tokens per pass over B: chosen at lif_create so that what it keeps of them in LDS fits a workgroup
+    const int tokens = std::min(batch, L->mask_tokens);
+#define LIF_MASK(MANY)                                                                                      \
+    hipLaunchKernelGGL((k_predict_mask<T, MANY>), dim3(grid), dim3(256), MANY ? mask_lds_bytes(c.rank, tokens) : 0, s, \
+                       (const T*)L->buf.B, L->buf.c, L->tpart, c.rank, c.d_ffn, batch, tokens, c.threshold, masks,     \
                        step_mask, L->st)
-    // tokens per pass over B: chosen at lif_create so that t of those tokens and the kernel's own LDS fit a workgroup
-    const int bt = L->mask_bt[batch];
-    if (bt == 1) LIF_MASK(1);
-    else if (bt == 4) LIF_MASK(4);
-    else LIF_MASK(8);
+    if (tokens == 1) LIF_MASK(false);
+    else LIF_MASK(true);
 #undef LIF_MASK
     return LIF_OK;
 }
@@ -328,7 +327,7 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
 #undef LIF_D1
     if (wg_rows > 1)
         hipLaunchKernelGGL((k_ffn_down_finish<T, down1_chunks<SKIP>>), dim3((c.d_model + 255) / 256), dim3(256), 0, s,
-                           ypart, (T*)y, c.d_model, 1, slices, L->st);
+                           ypart, (T*)y, c.d_model, 1, slices, wg_rows, L->st);
 }
 
 // several tokens, fp32
@@ -350,7 +349,7 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
 #undef LIF_DB
     if (wg_rows > 1)
         hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
-                           ypart, (T*)y, c.d_model, batch, slices, L->st);
+                           ypart, (T*)y, c.d_model, batch, slices, wg_rows, L->st);
 }
 
 // several tokens, fp16: the down projection on the matrix cores
@@ -372,7 +371,7 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
 #undef LIF_DM
     if (wg_rows > 1)
         hipLaunchKernelGGL(k_ffn_down_mfma_finish, dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart,
-                           (_Float16*)y, c.d_model, batch, chunk_rows, L->st);
+                           (_Float16*)y, c.d_model, batch, chunk_rows, wg_rows, L->st);
 }
 
 template <typename T>
@@ -499,33 +498,6 @@ void launch_ffn_up_mfma(lif_layer* L, const void* x, int batch, float* h, hipStr
     if (c.glu) LIF_UM(true);
     else LIF_UM(false);
 #undef LIF_UM
-}
-
-// LDS a workgroup of k_predict_mask<T, BT> needs for a predictor of rank r: its static arrays plus BT * r doubles.
-template <typename T, int BT>
-int mask_lds_bytes(int r, size_t* out) {
-    hipFuncAttributes fa;
-    LIF_HIP(hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(&k_predict_mask<T, BT>)));
-    *out = fa.sharedSizeBytes + sizeof(double) * BT * (size_t)r;
-    return LIF_OK;
-}
-
-// For every batch size the largest token tile (8, 4 or 1 tokens per pass over B) whose LDS fits the device limit.
-template <typename T>
-int choose_mask_tiles(lif_layer* L, size_t lds_limit) {
-    size_t need[3];
-    int rc = mask_lds_bytes<T, 1>(L->cfg.rank, &need[0]);
-    if (!rc) rc = mask_lds_bytes<T, 4>(L->cfg.rank, &need[1]);
-    if (!rc) rc = mask_lds_bytes<T, 8>(L->cfg.rank, &need[2]);
-    if (rc) return rc;
-    if (need[0] > lds_limit) return fail(LIF_INVALID_ARG, "rank too large for the LDS of a workgroup on this device");
-    for (int b = 0; b <= 8; ++b) {
-        int bt = 1;
-        if (b > 1 && need[1] <= lds_limit) bt = 4;
-        if (b > 4 && need[2] <= lds_limit) bt = 8;
-        L->mask_bt[b] = bt;
-    }
-    return LIF_OK;
 }
 
 // Bandwidth reference: every 16-byte piece of [src, src + bytes) is read once; the pieces are folded into one word
@@ -703,28 +675,15 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
     L->expected_rows = 0;
     L->prof_on = false;
     L->prof_max = 0;
-    for (int b = 0; b <= 8; ++b) L->mask_bt[b] = 1;
+    // t = x A of the tokens of a pass of the mask kernel lies in LDS (at most 64 KiB without asking, 40 bytes of it static)
+    L->mask_tokens = 8;
+    while (L->mask_tokens > 1 && mask_lds_bytes(std::max(cfg->rank, 0), L->mask_tokens) > 64 * 1024 - 64) --L->mask_tokens;
     {
         // address of the static scratch array on the device that is current now (the layer's device)
         void* p = nullptr;
         hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         L->static_scratch = (e == hipSuccess) ? (unsigned char*)p : nullptr;
         if (e != hipSuccess) (void)hipGetLastError();      // reported by lif_sparse_ffn_static, not by a later launch
-    }
-    if (cfg->predictor == LIF_PRED_LOWRANK) {
-        // the mask kernel keeps t = x A of a tile of tokens in LDS: pick the tile that fits this device
-        int dev = 0, lds_limit = 0;
-        int rc = LIF_OK;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-        if (e != hipSuccess) rc = fail(LIF_HIP_ERROR, "device LDS limit: %s", hipGetErrorString(e));
-        lds_limit = std::min(lds_limit, 64 * 1024);      // (more would have to be allowed for the kernel first)
-        if (!rc) rc = cfg->dtype == LIF_F32 ? choose_mask_tiles<float>(L, (size_t)lds_limit)
-                                            : choose_mask_tiles<_Float16>(L, (size_t)lds_limit);
-        if (rc) {
-            delete L;
-            return rc;
-        }
     }
     if (cfg->max_batch > 1) {
         StepArgs a = {};                                     // (the row width names the kernel form)

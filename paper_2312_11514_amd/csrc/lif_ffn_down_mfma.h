@@ -276,22 +276,16 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
 // more than one workgroup row; does nothing when a single chunk was in use (y is written already).
 // grid = ceil(batch * d / 256), block = 256.
 __global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* __restrict__ ypart, _Float16* __restrict__ y,
-                                                              int d, int batch, int chunk_rows,
+                                                              int d, int batch, int chunk_rows, int ahead,
                                                               const DevState* __restrict__ st) {
+    const int i = blockIdx.x * 256 + threadIdx.x, at = min(i, batch * d - 1);
+    ChunkSum p;
+    p.request(ypart + at, (size_t)batch * d, 0, ahead);
     if (st->cur.error) return;
     const int chunks = down_mfma_chunks(st->cur.num_used, chunk_rows);
     if (chunks == 1) return;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= batch * d) return;
-    // all partials are requested before the first add
-    float v[kDownChunksMax];
-#pragma unroll
-    for (int c = 0; c < kDownChunksMax; ++c) v[c] = (c < chunks) ? ypart[(size_t)c * batch * d + i] : 0.f;
-    float s = 0.f;
-#pragma unroll
-    for (int c = 0; c < kDownChunksMax; ++c)
-        if (c < chunks) s += v[c];
-    y[i] = (_Float16)s;
+    p.request(ypart + at, (size_t)batch * d, ahead, chunks);
+    if (i < batch * d) y[i] = (_Float16)p.sum(chunks);
 }
 
 }  // namespace lif

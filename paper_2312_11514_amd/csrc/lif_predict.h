@@ -80,185 +80,126 @@ __global__ __launch_bounds__(256) void k_predict_xa(const T* __restrict__ x, con
     if (threadIdx.x == 0 && !err) t[(size_t)b * r + j] = column_total(part);
 }
 
-// logits = t B + c, threshold, pack 8 neurons per byte; step mask = OR over the batch.
-// grid = ceil(F / 64), block = 256 = 32 rank groups x 8 column lanes; each column lane owns
-// 8 consecutive neurons = one mask byte.  dynamic LDS: BT * r doubles (t of the tokens of a pass).
-template <typename T, int BT>
-__global__ __launch_bounds__(256) void k_predict_mask(const T* __restrict__ B, const float* __restrict__ c,
-                                                      const double* __restrict__ t, int r, int F, int batch,
+// logits = t B + c, threshold, 64 mask bits at a time; step mask = OR over the batch.
+// grid = ceil(F / 64), block = 256 = 32 rank groups x 8 column lanes; a column lane owns 8 consecutive neurons.  `tokens` of the batch
+// per pass over B; MANY: their t and the sums of the waves lie in LDS (dynamic, mask_lds_bytes), else (tokens = 1) t comes straight
+// from memory with the rows of B.
+// What bounds it: the chain from the launch over one round trip for B and t, 64 fp64 multiply-adds per thread and token, and the
+// sums across the rank groups; a few hundred KB to a few MB are read.  A token at a time, with B widened once: the code is 2 KB
+// instead of 10, and instructions that run once wait for their way into the cache (8 tokens at once, rank 256: 8.1 us).  The sums across a wave go through register
+// exchanges that leave a lane with one neuron, so that a ballot is the mask word.  8 tokens, rank 256: 10.4 -> 7.5 us; 5 tokens, rank 128,
+// 9.5 -> 6.1 us; 3 tokens in fp32, rank 68, 6.6 -> 5.2 us (all tokens at once, exchanges through LDS, sums and bits by 64 threads).
+inline size_t mask_lds_bytes(int r, int tokens) { return sizeof(double) * tokens * ((size_t)r + 4 * 64); }
+template <typename T, bool MANY>
+__global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B, const float* __restrict__ c,
+                                                      const double* __restrict__ t, int r, int F, int batch, int tokens,
                                                       float theta,
                                                       uint8_t* __restrict__ masks, uint8_t* __restrict__ step_mask,
                                                       const DevState* __restrict__ st) {
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N;
     constexpr int LPB = 8 / VE;             // 16-byte loads per group of 8 neurons
-    extern __shared__ __attribute__((aligned(16))) double tl[];          // [BT][r]
-    __shared__ double red[4][kMaskCols][BT][8];
-    __shared__ uint8_t bytes[BT][kMaskCols];
+    constexpr int kChunk = kMaskRows * kMaskJg;      // ranks at a time
+    extern __shared__ __attribute__((aligned(16))) double lds_mask[];
+    __shared__ double red_one[MANY ? 1 : 4 * 64];
+    __shared__ unsigned long long ors[4];
+    double* const red = MANY ? lds_mask : red_one;   // [token][wave][neuron of the tile]
+    double* const tl = lds_mask + tokens * (4 * 64); // [token][r]
 
-    const int tid = threadIdx.x, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cl = tid & (kMaskCols - 1), jg = tid >> 3;
-    const int n0 = (blockIdx.x * kMaskCols + cl) * 8;
+    const int n0 = (blockIdx.x * kMaskCols + cl) * 8, own = blockIdx.x * 64 + lane;
     const bool col_ok = n0 < F;
-    const int mask_stride = F >> 3;
-    const double th = (double)theta;
-    uint8_t or_byte = 0;
-
-    // loads that do not depend on t: the first kMaskRows rows of B of this thread, the offsets, the flag
+    const int mask_stride = F >> 3, byte = blockIdx.x * kMaskCols + lane;                // lanes 0..7: a mask byte each
+    unsigned long long or_word = 0ull;      // of this wave's tokens
     V bv[kMaskRows][LPB];
-#pragma unroll
-    for (int u = 0; u < kMaskRows; ++u) {
-        const int j = jg + u * kMaskJg;
-#pragma unroll
-        for (int q = 0; q < LPB; ++q)
-            bv[u][q] = (col_ok && j < r) ? reinterpret_cast<const V*>(B + (size_t)j * F + n0)[q] : V(0);
-    }
-    float cv[8];
-    {
-        const int c2 = tid & (kMaskCols - 1);
-        const int n2 = (blockIdx.x * kMaskCols + c2) * 8;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) cv[e] = (c && tid < kMaskCols * BT && n2 < F) ? c[n2 + e] : 0.f;
-    }
-    // one token per pass: the kMaskRows values of t this thread multiplies with come straight from global memory,
-    // requested with the rows (no staging in LDS, no barriers in front of the multiply-adds)
-    double tr[BT == 1 ? kMaskRows : 1];
-    if (BT == 1) {
-#pragma unroll
-        for (int u = 0; u < kMaskRows; ++u) tr[u] = t[min(jg + u * kMaskJg, r - 1)];
-    }
-    const int err = st->cur.error;
-
-    for (int b0 = 0; b0 < batch; b0 += BT) {
-        if (BT == 1 && r <= kMaskRows * kMaskJg && b0 > 0) __syncthreads();   // red is still read from the pass before
-        if (BT > 1 || r > kMaskRows * kMaskJg) {
-            __syncthreads();
-            // t of the tokens of a pass is one contiguous run: 16-byte pieces, several of them in flight per thread (one
-            // value at a time, with a division for its token, took 6 of the kernel's 12 us at 8 tokens and rank 256)
-            constexpr int kAhead = 4;
-            const int have = min(BT, batch - b0) * r / 2, pieces = BT * r / 2;      // (r is even)
-            const double2* src = reinterpret_cast<const double2*>(t + (size_t)b0 * r);
-            for (int i0 = tid; i0 < pieces; i0 += 256 * kAhead) {
-                double2 p[kAhead];
-#pragma unroll
-                for (int i = 0; i < kAhead; ++i) p[i] = src[min(i0 + i * 256, have - 1)];
-#pragma unroll
-                for (int i = 0; i < kAhead; ++i) {
-                    const int idx = i0 + i * 256;
-                    if (idx < pieces) reinterpret_cast<double2*>(tl)[idx] = idx < have ? p[i] : make_double2(0.0, 0.0);
-                }
-            }
-            __syncthreads();
-        }
-        if (BT == 1 && b0 > 0) {                     // batches served token by token (large ranks)
-#pragma unroll
-            for (int u = 0; u < kMaskRows; ++u) tr[u] = t[(size_t)b0 * r + min(jg + u * kMaskJg, r - 1)];
-        }
-
-        double v[BT * 8];                    // v[bt * 8 + e]: logit sums of token bt, neuron e of this lane's byte
-#pragma unroll
-        for (int i = 0; i < BT * 8; ++i) v[i] = 0.0;
+    double tr[MANY ? 1 : kMaskRows];
+    auto request = [&](int b0, int j0) {             // the rows j0 + jg + u * kMaskJg of B (0 past the end)
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) {
-            const int j = min(jg + u * kMaskJg, r - 1);           // bv[u] is 0 past the end
+            const int j = j0 + jg + u * kMaskJg;
 #pragma unroll
-            for (int bt = 0; bt < BT; ++bt) {
-                const double tj = (BT == 1) ? tr[u] : tl[bt * r + j];
-#pragma unroll
-                for (int q = 0; q < LPB; ++q)
-#pragma unroll
-                    for (int e = 0; e < VE; ++e)
-                        v[bt * 8 + q * VE + e] = __builtin_fma(tj, (double)bv[u][q][e], v[bt * 8 + q * VE + e]);
-            }
+            for (int q = 0; q < LPB; ++q)
+                bv[u][q] = (col_ok && j < r) ? reinterpret_cast<const V*>(B + (size_t)j * F + n0)[q] : V(0);
+            if constexpr (!MANY) tr[u] = t[(size_t)b0 * r + min(j, r - 1)];
         }
-        if (col_ok) {
-            for (int j = jg + kMaskRows * kMaskJg; j < r; j += kMaskJg) {      // only when rank > 256
-                const V* bp = reinterpret_cast<const V*>(B + (size_t)j * F + n0);
-                V bw[LPB];
+    };
+    request(0, 0);
+    const double cv = (c && own < F) ? (double)c[own] : 0.0;
+    const int err = st->cur.error;
+
+    for (int b0 = 0; b0 < batch; b0 += tokens) {
+        const int nb = min(tokens, batch - b0);
+        if (b0 > 0) {
+            __syncthreads();                         // red and tl are still read from the pass before
+            request(b0, 0);
+        }
+        if constexpr (MANY) {
+            // t of the tokens of a pass is one contiguous run: 16-byte pieces, several of them in flight per thread
+            constexpr int kAhead = 4;
+            typedef double f64x2 __attribute__((ext_vector_type(2)));
+            const int pieces = nb * r / 2;           // (r is even)
+            const f64x2* src = reinterpret_cast<const f64x2*>(t + (size_t)b0 * r);
+            for (int i0 = tid; i0 < pieces; i0 += 256 * kAhead) {
+                f64x2 p[kAhead];
 #pragma unroll
-                for (int q = 0; q < LPB; ++q) bw[q] = bp[q];
+                for (int i = 0; i < kAhead; ++i) p[i] = src[min(i0 + i * 256, pieces - 1)];
 #pragma unroll
-                for (int bt = 0; bt < BT; ++bt) {
-                    const double tj = tl[bt * r + j];
+                for (int i = 0; i < kAhead; ++i)
+                    if (i0 + i * 256 < pieces) reinterpret_cast<f64x2*>(tl)[i0 + i * 256] = p[i];
+            }
+            __syncthreads();
+        }
+        for (int j0 = 0; j0 < r; j0 += kChunk) {
+            double bd[kMaskRows][8], tn[kMaskRows];
 #pragma unroll
-                    for (int q = 0; q < LPB; ++q)
+            for (int u = 0; u < kMaskRows; ++u) {
+                if constexpr (!MANY) tn[u] = tr[u];
 #pragma unroll
-                        for (int e = 0; e < VE; ++e)
-                            v[bt * 8 + q * VE + e] = __builtin_fma(tj, (double)bw[q][e], v[bt * 8 + q * VE + e]);
+                for (int e = 0; e < 8; ++e) bd[u][e] = (double)bv[u][e / VE][e % VE];
+            }
+            if (j0 + kChunk < r) request(b0, j0 + kChunk);
+#pragma unroll 1
+            for (int bt = 0; bt < nb; ++bt) {
+                if constexpr (MANY) {
+#pragma unroll
+                    for (int u = 0; u < kMaskRows; ++u) tn[u] = tl[bt * r + min(j0 + jg + u * kMaskJg, r - 1)];
                 }
+                double v[8];                         // logit sums of the 8 neurons of this lane's byte
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = 0.0;
+#pragma unroll
+                for (int u = 0; u < kMaskRows; ++u)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tn[u], bd[u][e], v[e]);     // (0 past the last rank)
+                // The eight rank groups of a wave sit 8 lanes apart: every exchange leaves a lane with half of its neurons
+                const bool up = (lane & 8) != 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double send = up ? v[e] : v[e + 4], keep = up ? v[e + 4] : v[e];
+                    v[e] = keep + dpp_from<0x128, 0xf>(send);    // lanes 8 apart: a rotation in a row of 16
+                }
+#pragma unroll
+                for (int e = 0; e < 2; ++e) v[e] = swap_add<16>(v[e], v[e + 2]);
+                v[0] = swap_add<32>(v[0], v[1]);
+                double* const to = red + (bt * 4 + wave) * 64 + cl * 8 + (up ? 4 : 0) + ((lane >> 4) & 1) * 2 + (lane >> 5);
+                *to = j0 > 0 ? *to + v[0] : v[0];    // (this lane's alone)
             }
-        }
-        // The eight rank groups of a wave sit 8 lanes apart (lane bits 3..5): butterfly over those bits, then LDS
-        // across the 4 waves.  While a lane still holds the sums of more than one token, a step halves them: the
-        // lane keeps the tokens selected by its own bit and hands the other half to its partner (56 exchanges
-        // instead of 192 for 8 tokens).  Afterwards lane (g, cl), g = lane bits 3..5, holds the 8 sums of token
-        // `owner` (all lanes for BT = 8; even g / g = 0 only for fewer tokens).
-        int owner = 0;
-        auto halve = [&](auto half_c, int m) {       // keep the half selected by this lane's bit m, add the partner's
-            constexpr int half = decltype(half_c)::value;
-            const bool up = (tid & m) != 0;
-#pragma unroll
-            for (int i = 0; i < half; ++i) {
-                const double send = up ? v[i] : v[i + half], keep = up ? v[i + half] : v[i];
-                // lanes 8 apart sit in one row of 16: a rotation by 8 (DPP) instead of a shuffle through LDS
-                v[i] = keep + (m == 8 ? dpp_from<0x128, 0xf>(send) : __shfl_xor(send, m, kWave));
-            }
-            owner = owner * 2 + (up ? 1 : 0);
-        };
-        auto full = [&](int m) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] += (m == 8 ? dpp_from<0x128, 0xf>(v[i]) : __shfl_xor(v[i], m, kWave));
-        };
-        if constexpr (BT == 8) {
-            halve(std::integral_constant<int, 32>{}, 32);
-            halve(std::integral_constant<int, 16>{}, 16);
-            halve(std::integral_constant<int, 8>{}, 8);
-        } else if constexpr (BT == 4) {
-            halve(std::integral_constant<int, 16>{}, 32);
-            halve(std::integral_constant<int, 8>{}, 16);
-            full(8);
-        } else {
-            // one token: the 8 neurons of the byte are halved the same way (7 exchanges instead of 24), the step over
-            // lanes 8 apart first, while a lane still holds all 8: lane (g, cl) ends with neuron `owner`
-            halve(std::integral_constant<int, 4>{}, 8);
-            halve(std::integral_constant<int, 2>{}, 16);
-            halve(std::integral_constant<int, 1>{}, 32);
-        }
-        // which lanes hold a finished token: those whose bits of the non-halving steps are zero
-        constexpr int kHalvings = (BT == 8) ? 3 : (BT == 4) ? 2 : 0;
-        const bool holder = ((tid & 63) & ((64 >> kHalvings) - 8)) == 0;
-        if (BT == 1) {
-            red[wave][cl][0][owner] = v[0];
-        } else if (holder) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) red[wave][cl][owner][e] = v[e];
         }
         __syncthreads();
-        if (tid < kMaskCols * BT) {
-            const int bt = tid / kMaskCols, c2 = tid - bt * kMaskCols;
-            const int n2 = (blockIdx.x * kMaskCols + c2) * 8;
-            uint8_t byte = 0;
-            if (n2 < F && b0 + bt < batch) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    double z = ((red[0][c2][bt][e] + red[1][c2][bt][e]) + red[2][c2][bt][e]) + red[3][c2][bt][e];
-                    z += (double)cv[e];
-                    if (z > th) byte |= (uint8_t)(1u << e);
-                }
-                if (!err) masks[(size_t)(b0 + bt) * mask_stride + (n2 >> 3)] = byte;
-            }
-            if (BT == 1) or_byte |= byte;            // one token per pass: this thread owns column tid of the step mask
-            else bytes[bt][c2] = byte;
-        }
-        if (BT > 1) {
-            __syncthreads();
-            if (tid < kMaskCols) {
-#pragma unroll
-                for (int bt = 0; bt < BT; ++bt) or_byte |= bytes[bt][tid];
-            }
+        for (int bt = wave; bt < nb; bt += 4) {
+            const double* p = red + bt * 256 + lane;
+            double z = ((p[0] + p[64]) + p[128]) + p[192];
+            z += cv;
+            const unsigned long long word = __ballot(own < F && z > (double)theta);
+            or_word |= word;
+            if (lane < kMaskCols && byte < mask_stride && !err) masks[(size_t)(b0 + bt) * mask_stride + byte] = (uint8_t)(word >> (8 * lane));
         }
     }
-    if (tid < kMaskCols && n0 < F && !err) step_mask[n0 >> 3] = or_byte;
+    if (lane == 0) ors[wave] = or_word;
+    __syncthreads();
+    if (tid < kMaskCols && byte < mask_stride && !err)
+        step_mask[byte] = (uint8_t)(((ors[0] | ors[1]) | (ors[2] | ors[3])) >> (8 * lane));
 }
 
 // Gate projection as the predictor (Appendix, Llama 2, "Alternative approaches"): the gate matrix stays

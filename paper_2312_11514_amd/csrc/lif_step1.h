@@ -218,9 +218,11 @@ struct MaskTile {
         for (int i = 0; i < 8; ++i) v[i] = 0.0;
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) {
-            const double tj = L.t[min(jg + u * kMaskJg, a.rank - 1)];            // bd[u] is 0 past the end
+            if (u * kMaskJg < a.rank) {              // (uniform; bd[u] is 0 past the end)
+                const double tj = L.t[min(jg + u * kMaskJg, a.rank - 1)];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tj, WIDE ? bd[u][e] : (double)bv[u][e / VE][e % VE], v[e]);
+                for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tj, WIDE ? bd[u][e] : (double)bv[u][e / VE][e % VE], v[e]);
+            }
         }
         if (n0 < a.F) {
             for (int j = jg + kMaskRows * kMaskJg; j < a.rank; j += kMaskJg) {   // only when rank > 256
