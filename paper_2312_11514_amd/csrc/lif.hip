@@ -337,9 +337,9 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
     constexpr int cols = kDownLanesB * Vec<T>::N;
     // workgroup rows: enough for the chunks of the expected number of rows; fewer than the chunks in use is still
     // correct (a workgroup row then takes several chunks)
-    const int wg_rows = down_chunks(geometry_rows(L));
-    const int down_off = (c.glu ? 2 : 1) * c.d_model;
     const int slices = (c.d_model + cols - 1) / cols;
+    const int wg_rows = down_chunks(geometry_rows(L), slices);
+    const int down_off = (c.glu ? 2 : 1) * c.d_model;
 #define LIF_DB(FUSED)                                                                                        \
     hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(256),  \
                        0, s, (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, c.d_model, batch,          \
@@ -353,17 +353,17 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
 }
 
 // several tokens, fp16: the down projection on the matrix cores
-template <bool SKIP>
-void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
+template <bool SKIP, int ROWS>
+void launch_ffn_down_mfma_rows(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
     const lif_config& c = L->cfg;
     const int slices = (c.d_model + kDmCols - 1) / kDmCols;
-    const int chunk_rows = down_mfma_chunk_rows(c.capacity_rows);
+    const int chunk_rows = down_mfma_chunk_rows(c.capacity_rows, slices);
     // workgroup rows: enough for the chunks of the expected number of rows (with some slack), else of the
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
 #define LIF_DM(FUSED)                                                                                        \
-    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),             \
+    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, ROWS, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),       \
                        dim3(kDmWaves * 64), 0, s, (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y,  \
                        ypart, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
     if (fc.on) LIF_DM(true);
@@ -372,6 +372,13 @@ void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypa
     if (wg_rows > 1)
         hipLaunchKernelGGL(k_ffn_down_mfma_finish, dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart,
                            (_Float16*)y, c.d_model, batch, chunk_rows, wg_rows, L->st);
+}
+
+template <bool SKIP>
+void launch_ffn_down_mfma(lif_layer* L, int batch, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
+    const int slices = (L->cfg.d_model + kDmCols - 1) / kDmCols;
+    if (down_mfma_pass_rows(L->cfg.capacity_rows, slices) == kDmRowsFew) launch_ffn_down_mfma_rows<SKIP, kDmRowsFew>(L, batch, y, h, ypart, s, fc);
+    else launch_ffn_down_mfma_rows<SKIP, kDmRows>(L, batch, y, h, ypart, s, fc);
 }
 
 template <typename T>

@@ -227,14 +227,20 @@ constexpr int kXcds = 8;            // accelerator complex dies of an MI355X, ea
 constexpr int kDownTile = 2048;     // activations (rows x tokens) compacted per pass (at least 512 rows)
 constexpr int kDownChunksMax = 32;  // row chunks of the down projection (partial outputs per chunk)
 constexpr int kDownLanesB = 16;       // lanes per column slice for several tokens
-constexpr int kDownRowsBatch = 512;   // rows per chunk for several tokens
+constexpr int kDownRowsMost = 512, kDownRowsLeast = 128;      // rows per chunk for several tokens
+constexpr int kDownWgs = 512;         // workgroups that chunks of fewer than kDownRowsMost rows are made for
 
-// Row chunks in use for n cached rows and several tokens: their active sets add up, most rows are read, and a chunk is
-// 512 rows so that several hundred workgroups stream at once (column slices alone, d / 64 workgroups, reach only
-// about 3 TB/s).  The host sizes the grid with the same rule.
-__host__ __device__ __forceinline__ int down_chunks(int n, int = 0) {
-    const int c = (n + kDownRowsBatch - 1) / kDownRowsBatch;
-    return c < 1 ? 1 : (c > kDownChunksMax ? kDownChunksMax : c);
+// Row chunks in use for n cached rows, several tokens and `slices` column slices: their active sets add up, most rows are read, and
+// a chunk is at most kDownRowsMost rows: one chunk (no partial sums, no second launch) up to there, beyond it chunks of down to kDownRowsLeast
+// until kDownWgs workgroups stream at once.  With chunks of 512 rows throughout, half of the compute units had nothing to do and a
+// thread went through 32 rows, four at a time.  One FFN call, us, 512 -> now: d = 1288, 3 tokens, 988 rows 14.5 -> 12.3, 2044 rows 16.1 -> 13.4,
+// 4081 rows 18.9 -> 16.4; 8 tokens, 1634 rows 20.6 -> 17.4, 6859 rows 35.1 -> 33.9; d = 4096, 3 tokens, 949 rows 19.5 -> 17.3, 3874 rows
+// the same.  Up to 512 rows one chunk is better where no second launch is needed (3 tokens, d = 1288, 208 rows 8.9 against 11.3).
+// The host sizes the grid with the same rule.
+__host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
+    const int least = (n + kDownRowsMost - 1) / kDownRowsMost, most = (n + kDownRowsLeast - 1) / kDownRowsLeast, fill = kDownWgs / slices;
+    const int c = most < fill ? most : least > fill ? least : fill;
+    return n <= kDownRowsMost ? 1 : (c > kDownChunksMax ? kDownChunksMax : c);
 }
 
 // Down projection  y[t][j] = sum_s H[t][s] * D[s][j]  over the rows in use, for 2..BT tokens (fp32 layers; fp16
@@ -245,7 +251,7 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int = 0) {
 // away with a prefix sum in LDS, in a fixed order).
 // FUSED: the launch after k_step_batch.  One more workgroup commits the step and the activations of fresh rows are picked
 // up; a form of its own because the run-time test cost the plain call 0.2 to 0.6 us of 17 (2 to 5 tokens, d 400 to 2800).
-// The rows are cut into down_chunks(n) chunks - a function of n alone, so the arithmetic does not
+// The rows are cut into down_chunks chunks - a function of n and the width alone, so the arithmetic does not
 // depend on the launch geometry - and workgroup row y takes the chunks y, y + gridDim.y, ...  Every
 // chunk is summed from zero.  With one chunk in use the workgroup writes its columns of y.  With more,
 // a grid of one workgroup row adds its chunk sums in chunk order and writes y; a taller grid writes
@@ -311,15 +317,15 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     const StepCounts* counts = stamp ? &st->next : &st->cur;
     const int err = counts->error, n = counts->num_used, cur_step = counts->step;
     if (err) return;
-    const int chunks = down_chunks(n);
+    const int chunks = down_chunks(n, slices);
     if ((int)blockIdx.y >= chunks) return;           // uniform
     const int per_chunk = (n + chunks - 1) / chunks;
     const int ob = tid / LANES, ol = tid - ob * LANES;            // (token, lane) whose 16-byte piece this thread writes
     const int ocol = slice * (LANES * VE) + ol * VE;
     const bool writer = tid < LANES * BT && ocol < d && ob < batch;
-    float total[VE];
+    double total[VE];
 #pragma unroll
-    for (int e = 0; e < VE; ++e) total[e] = 0.f;
+    for (int e = 0; e < VE; ++e) total[e] = 0.0;
 
     for (int chunk = blockIdx.y; chunk < chunks; chunk += gridDim.y) {
         const int r0 = chunk * per_chunk, r1 = min(n, r0 + per_chunk);
@@ -418,7 +424,7 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
                 for (int e = 0; e < VE; ++e) out[e] = sum[e];
             } else {
 #pragma unroll
-                for (int e = 0; e < VE; ++e) total[e] += sum[e];      // chunk order; 0 + first sum is exact
+                for (int e = 0; e < VE; ++e) total[e] += (double)sum[e];      // as ChunkSum
             }
         }
     }
@@ -448,11 +454,12 @@ struct ChunkSum {
         for (int c = 0; c < kDownChunksMax; ++c)
             if (c >= from && c < to) v[c] = p[(size_t)c * stride];       // (uniform)
     }
-    __device__ __forceinline__ float sum(int chunks) const {
-        float s = 0.f;
+    template <typename A>
+    __device__ __forceinline__ A sum(int chunks) const {
+        A s = 0;
 #pragma unroll
         for (int c = 0; c < kDownChunksMax; ++c)
-            if (c < chunks) s += v[c];
+            if (c < chunks) s += (A)v[c];
         return s;
     }
 };
@@ -460,7 +467,8 @@ struct ChunkSum {
 // y = sum of the chunk partials in chunk order, rounded once to the element type.  Launched after a
 // k_ffn_down grid of more than one workgroup row; does nothing when a single chunk was in use (y is
 // written already).  grid = ceil(batch * d / 256), block = 256.
-// CHUNKS: the chunk rule of the kernel that wrote the partials, for its number of column slices.
+// CHUNKS: the chunk rule of the kernel that wrote the partials, for its number of column slices.  Added in fp64, as in those kernels: every
+// chunk would be another rounding of the whole (3 tokens in fp32, d = 320: 1.43e-7 from the sum in fp64 against 1.60e-7).
 template <typename T, int (*CHUNKS)(int, int)>
 __global__ __launch_bounds__(256) void k_ffn_down_finish(const float* __restrict__ ypart, T* __restrict__ y, int d,
                                                          int batch, int slices, int ahead, const DevState* __restrict__ st) {
@@ -471,7 +479,7 @@ __global__ __launch_bounds__(256) void k_ffn_down_finish(const float* __restrict
     const int chunks = CHUNKS(st->cur.num_used, slices);
     if (chunks == 1) return;
     p.request(ypart + at, (size_t)batch * d, ahead, chunks);
-    if (i < batch * d) y[i] = (T)p.sum(chunks);
+    if (i < batch * d) y[i] = (T)p.sum<double>(chunks);
 }
 
 }  // namespace lif

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
     const int vwaves = down1_waves<SKIP>(n, slices);
     const int stride = vwaves * 64;                  // slots between the groups of a (virtual) wave
     const bool natural = vwaves == WAVES;            // the requests above were for the right slots
-    float total = 0.f;
+    double total = 0.0;
     for (int chunk = blockIdx.y; chunk < chunks; chunk += gridDim.y) {
         const int r0 = chunk * per_chunk, r1 = min(n, r0 + per_chunk);
         for (int vw = wv; vw < vwaves; vw += WAVES) {
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
             if (chunks > 1 && gridDim.y > 1) {
                 if (oc < d) ypart[(size_t)chunk * d + oc] = sum;
             } else {
-                total += sum;                        // chunk order; 0 + first sum is exact
+                total += (double)sum;                // as ChunkSum; 0 + first sum is exact
             }
         }
         __syncthreads();                             // red is written again by the next chunk

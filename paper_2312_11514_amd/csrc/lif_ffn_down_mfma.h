@@ -19,20 +19,29 @@ namespace lif {
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kDmRows = 512;             // rows compacted per pass
-constexpr int kDmPitch = kDmRows + 8;    // fp16 values per token slot in LDS (16 bytes of padding: lanes of one
-                                         // row block read 16 different slots at the same offset)
+constexpr int kDmRowsFew = 256;          // ... where the whole cache in such pieces fits the chip at once
+constexpr int kDmWgsAtOnce = 3 * 256;    // workgroups that do: three to a compute unit
+constexpr int kDmSmall = 1280;           // capacity up to which passes are 512 rows all the same
 constexpr int kDmCols = 128;             // columns per workgroup: 16 lanes x 16 bytes
 constexpr int kDmWaves = 4;              // waves per workgroup: 8 are a little faster below 5000 rows (196 against 197 us for a
                                          // step of 4 tokens at 1250 rows) but leave two workgroups per compute unit and so a
                                          // second, nearly empty round of them above (24 against 19 us at 8600 rows)
 
-// Rows per chunk (one partial output per chunk): a multiple of kDmRows that depends on the capacity alone, so a
-// workgroup row knows where its first chunk starts before the row count arrives, and at most kDownChunksMax
-// chunks are ever in use.
-__host__ __device__ __forceinline__ int down_mfma_chunk_rows(int capacity) {
-    const int per = kDmRows * kDownChunksMax;
+// Rows per pass and per chunk (one partial output per chunk): functions of the capacity and the width alone, so a workgroup row knows
+// where its first chunk starts before the row count arrives; a chunk is whole passes, and at most kDownChunksMax chunks are ever in
+// use.  Passes of 256 rows have half the activations to wait for and twice the workgroups: one FFN call, us, 512 -> 256 rows: d = 512, 3
+// tokens, 1835 rows 15.6 -> 13.3; d = 1024, 8 tokens, 6948 rows 19.8 -> 17.7; d = 4096, 8 tokens, 1674 rows 19.8 -> 17.2.  But where
+// 256-row workgroups would need a second round on the chip 512 are better: d = 4096, 8 tokens, 8177 of 8192 rows 33.9 against 37.2.
+// (Chunks of 256 rows in passes made for 512 gain a third of it.)  And small caches are likely to hold the 257 to 450 rows that one
+// chunk of 512 takes without a second launch: d = 512, 2 tokens, 299 rows 12.1 against 12.9.
+__host__ __device__ __forceinline__ int down_mfma_pass_rows(int capacity, int slices) {
+    const int few = (capacity + kDmRowsFew - 1) / kDmRowsFew;
+    return capacity > kDmSmall && few <= kDownChunksMax && few * slices <= kDmWgsAtOnce ? kDmRowsFew : kDmRows;
+}
+__host__ __device__ __forceinline__ int down_mfma_chunk_rows(int capacity, int slices) {
+    const int rows = down_mfma_pass_rows(capacity, slices), per = rows * kDownChunksMax;
     const int passes = (capacity + per - 1) / per;
-    return kDmRows * (passes < 1 ? 1 : passes);
+    return rows * (passes < 1 ? 1 : passes);
 }
 __host__ __device__ __forceinline__ int down_mfma_chunks(int n, int chunk_rows) {
     const int c = (n + chunk_rows - 1) / chunk_rows;
@@ -51,23 +60,25 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // quarter of the rows: 10976 rows, 8 tokens, d = 4096, gated, activations and down projection 63.3 -> 60.2 us.
 // grid = (ceil(d / 128) column slices, row-chunk workgroups), block = WAVES waves; lane l of a wave: column
 // group n16 = l mod 16 (8 columns) and token slot n16, row block q = l div 16 (8 of the 32 rows of an instruction).
-// A pass compacts the contributing rows of 512 slots (SKIP: rows with some activation; else all rows in use) in a
+// A pass compacts the contributing rows of ROWS slots (SKIP: rows with some activation; else all rows in use) in a
 // fixed order (thread-major over slots p * threads + tid); the waves take groups of 32 compacted rows in turn.
 // A chunk's passes are added in order, the waves in wave order, the chunks in chunk order (by this kernel when
 // one workgroup row is launched, else by k_ffn_down_mfma_finish from ypart[chunk][token][d]).  Nothing depends on
 // the launch geometry.
-template <bool SKIP, int WAVES, bool FUSED>
+template <bool SKIP, int WAVES, int ROWS, bool FUSED>
 __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16* __restrict__ matrix,
                                                               const float* __restrict__ h, const FusedRows fused,
                                                               _Float16* __restrict__ y, float* __restrict__ ypart, int d,
                                                               int batch, int capacity, size_t row_elems, int down_off,
                                                               int chunk_rows, int slices, DevState* __restrict__ st) {
     constexpr int BT = 8, T = WAVES * 64;
-    constexpr int PER = kDmRows / T;                 // slots per thread in the compaction
+    constexpr int PER = ROWS / T;                    // slots per thread in the compaction
+    constexpr int kPitch = ROWS + 8;                 // fp16 values per token slot in LDS (16 bytes of padding: lanes of one
+                                                     // row block read 16 different slots at the same offset)
     constexpr int OUTS = BT * kDmCols / T;           // outputs per thread
-    static_assert(kDmRows % T == 0 && (BT * kDmCols) % T == 0, "whole slots and outputs per thread");
-    __shared__ int list[kDmRows];
-    __shared__ __attribute__((aligned(16))) _Float16 hv[16][kDmPitch];
+    static_assert(ROWS % T == 0 && (BT * kDmCols) % T == 0, "whole slots and outputs per thread");
+    __shared__ int list[ROWS];
+    __shared__ __attribute__((aligned(16))) _Float16 hv[16][kPitch];
     __shared__ int wave_tot[WAVES];
     __shared__ float wave_max[WAVES];
     __shared__ float red[WAVES][32][33];             // per wave and lane with q < 2: 32 sums, padded
@@ -113,7 +124,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
             }
         }
         asm volatile("" ::: "memory");       // (behind the activations: loads return in order)
-        if constexpr (!SKIP) load(w, kDmRows, [&](int i) { return min(s_base + i, capacity - 1); });
+        if constexpr (!SKIP) load(w, ROWS, [&](int i) { return min(s_base + i, capacity - 1); });
     };
     request(blockIdx.y * chunk_rows);
     const StepCounts* counts = stamp ? &st->next : &st->cur;
@@ -133,7 +144,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
 #pragma unroll
             for (int i = 0; i < 32; ++i) red[w][lane][i] = 0.f;
         }
-        for (int s_base = r0; s_base < r1; s_base += kDmRows) {
+        for (int s_base = r0; s_base < r1; s_base += ROWS) {
             // compaction of the rows that contribute and the largest |activation| of the pass
             unsigned flags = 0, nonzero = 0;
             float amax = 0.f;
@@ -157,7 +168,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
             for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, kWave));
             if (lane == 0) wave_max[w] = amax;       // (the barriers of the scan order this write and the reads below,
                                                      //  and keep the previous pass's readers of list / hv ahead of the writes)
-            int cnt = min(r1 - s_base, kDmRows), off = 0;
+            int cnt = min(r1 - s_base, ROWS), off = 0;
             if constexpr (SKIP) off = block_exclusive_scan<WAVES>(__popc(flags), wave_tot, &cnt);
             else __syncthreads();
             float smax = wave_max[0];
@@ -232,7 +243,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
                         if (q < 2) red[w][lane][j * 4 + r] += (acc[j][r] + lo) * inv_scale;
                     }
             }
-            const int next = s_base + kDmRows < r1 ? s_base + kDmRows
+            const int next = s_base + ROWS < r1 ? s_base + ROWS
                                                    : chunk + (int)gridDim.y < chunks ? (chunk + (int)gridDim.y) * chunk_rows : -1;
             if (next >= 0) request(next);
         }
@@ -285,7 +296,7 @@ __global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* __res
     const int chunks = down_mfma_chunks(st->cur.num_used, chunk_rows);
     if (chunks == 1) return;
     p.request(ypart + at, (size_t)batch * d, ahead, chunks);
-    if (i < batch * d) y[i] = (_Float16)p.sum(chunks);
+    if (i < batch * d) y[i] = (_Float16)p.sum<float>(chunks);
 }
 
 }  // namespace lif

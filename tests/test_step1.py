@@ -339,3 +339,38 @@ def test_down_projection_of_one_token_by_row_chunks(d, F, rows, full):
         assert all(torch.equal(y, got[0]) for y in got[1:]), n
         want = h[:n] @ lay.matrix[:n, d:].double()
         assert rel_l2(got[0].double().cpu().numpy(), want.cpu().numpy()) <= REL_L2_TOL, n
+
+
+@pytest.mark.parametrize("dtype,d,F,rows", [("f32", 1288, 13000, (512, 513, 3073, 4097, 12300, 13000)), ("f32", 4096, 1100, (512, 513, 1100)),
+                                            ("f16", 136, 1280, (256, 512, 513, 1280)), ("f16", 136, 1281, (256, 257, 513, 1281)),
+                                            ("f16", 512, 8193, (512, 8193)), ("f16", 4096, 6145, (513, 6145)), ("f16", 4096, 6144, (257, 6144))])
+@pytest.mark.parametrize("full", [False, True])
+def test_down_projection_of_a_batch_by_row_chunks(dtype, d, F, rows, full):
+    """The same for three tokens: fp32 chunks by rows and width, fp16 chunks and passes by capacity and width."""
+    import paper_2312_11514_amd as lif
+    from tests.harness import REL_L2_TOL, rel_l2, require_gpu
+    require_gpu()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + full)
+    dt = torch.float32 if dtype == "f32" else torch.float16
+    zeros = lambda *s, dt=dt: torch.zeros(s, dtype=dt, device="cuda")
+    lay = lif.Layer(d_model=d, d_ffn=(F + 7) // 8 * 8, rank=8, window_k=2, capacity_rows=F, max_batch=3, dtype=dtype,
+                    ffn_mode=lif.FFN_FULL_BUNDLE if full else lif.FFN_SKIP_DEAD, A=zeros(8, d), B=zeros(8, (F + 7) // 8 * 8), c=None,
+                    b=zeros((F + 7) // 8 * 8, dt=torch.float32),
+                    host_bundles=torch.zeros(((F + 7) // 8 * 8, 2 * d), dtype=dt).pin_memory())
+    lay.matrix.copy_(torch.randn((F, 2 * d), generator=g, device="cuda").div_(d ** 0.5))
+    lay.bias.fill_(-0.7)
+    x = torch.randn((3, d), generator=g, device="cuda").to(dt)
+    h = torch.relu(x.double() @ lay.matrix[:, :d].double().t().contiguous() - 0.7)
+    for n in rows:
+        lay.workspace[:4] = torch.tensor([n], dtype=torch.int32).view(torch.uint8).cuda()
+        got = []
+        for hint in (0, 1, n // 2, n, F):
+            print(f"three tokens, {dtype}, d {d}, full {full}: {n} rows, hint {hint}", flush=True)
+            lay.set_expected_rows(hint)
+            y = torch.full_like(x, 9.0)
+            lay.sparse_ffn(x, y, batch=3)
+            got.append(y)
+        assert all(torch.equal(y, got[0]) for y in got[1:]), n
+        want = h[:, :n].contiguous() @ lay.matrix[:n, d:].double()
+        assert rel_l2(got[0].cpu().numpy().astype(np.float64), want.cpu().numpy()) <= (1e-5 if dtype == "f32" else REL_L2_TOL), n
