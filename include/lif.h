@@ -140,7 +140,7 @@ enum lif_kernel_id {
     LIF_K_WINDOW = 2,       /* window diff, added / removed ids, deletion plan            */
     LIF_K_LOAD = 3,         /* row moves + host-to-device bundle append                   */
     LIF_K_FFN_UP = 4,       /* activations of all cached rows                             */
-    LIF_K_FFN_DOWN = 5,     /* y = sum of activation x down column                        */
+    LIF_K_FFN_DOWN = 5,     /* y = sum of activation x down column; a call of one launch  */
     LIF_K_COUNT = 6
 };
 
@@ -251,7 +251,7 @@ int lif_sparse_ffn(lif_layer* layer, const void* x_dev, int32_t batch, void* y_d
  * lif_sparse_ffn for callers that cannot allocate and want no scratch of their own in the call: code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation.  Same arguments, same arithmetic
  * and bit-identical results; the activations and the partial outputs of the call (the scratch that
- * lif_sparse_ffn keeps in the layer's workspace) live in a static device array inside the library instead, of
+ * lif_sparse_ffn keeps in the layer's workspace if it takes more than one launch) live in a static device array inside the library instead, of
  * lif_static_scratch_bytes() = 5 MiB, which every GPU the library runs on holds until the process ends.  The call
  * allocates nothing and frees nothing.
  *   limit   256-byte-rounded 4 * batch * capacity_rows  +  4 * 32 * batch * d_model  <=  lif_static_scratch_bytes()
@@ -312,8 +312,8 @@ int lif_set_expected_rows(lif_layer* layer, int32_t rows);
 int lif_set_loader_pairs(lif_layer* layer, int32_t pairs);
 
 /*
- * Performance knob of the single-token lif_step: workgroups of one launch hand values over to each other, and a
- * workgroup that has polled for a value this often without success computes it itself (0: it never waits).  Results
+ * Performance knob of the single-token lif_step and lif_sparse_ffn: workgroups of one launch hand values over to each
+ * other, and a workgroup that has polled for a value this often without success computes it itself (0: it never waits).  Results
  * never depend on it.
  */
 int lif_set_handoff_polls(lif_layer* layer, int32_t polls);

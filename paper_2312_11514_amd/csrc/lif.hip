@@ -13,6 +13,7 @@
 #include "lif_common.h"
 #include "lif_ffn.h"
 #include "lif_ffn_down1.h"
+#include "lif_ffn_one.h"
 #include "lif_ffn_mfma.h"
 #include "lif_ffn_down_mfma.h"
 #include "lif_predict.h"
@@ -66,7 +67,7 @@ constexpr int kDefaultPolls = 4096;      // a failed poll takes about 0.7 us: 3 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Layout {
-    size_t state, words, ring, tpart, move_dst, hole_list, h, ypart, h_new, stamp, ptr_new, bias_new, gact, total;
+    size_t state, words, one, ring, tpart, move_dst, hole_list, h, ypart, h_new, stamp, ptr_new, bias_new, gact, total;
     int reset_words;                   // 64-bit words from `words` on that a reset clears
 };
 
@@ -104,7 +105,9 @@ Layout make_layout(const lif_config& c) {
     off = align_up(off + sizeof(DevState), 256);
     L.words = off;                     // words handed over inside a fused step: t = x A, the mask words
     off = off + sizeof(uint64_t) * kWordReps * ((size_t)words_pitch(2 * std::max(c.rank, 0)) + words_pitch(2 * ring_words(c)));
-    off = off + sizeof(uint64_t) * c.capacity_rows;               // ... and the deletion plan
+    off = off + sizeof(uint64_t) * c.capacity_rows;               // ... and the deletion plan;
+    L.one = off;                       // inside a single-launch FFN, and its launch number
+    if (c.capacity_rows <= kOneCapacity) off = off + sizeof(uint64_t) * kOneReps * one_pitch(c.capacity_rows) + sizeof(OneState);
     L.ring = off;                      // window_k step masks, each padded to whole 64-bit words
     off = off + (size_t)(c.window_k + 2) * ring_words(c) * 8;     // ... directly followed by the two bitmaps of the cached set
     L.reset_words = (int)((off - L.words) / 8);
@@ -153,6 +156,8 @@ struct lif_layer {
     int32_t* ptr_new;
     float* bias_new;
     unsigned long long* words;
+    unsigned long long* one_words;  // of k_ffn_one, null where the cache has too many slots
+    OneState* one;
     int polls;                  // failed polls of a hand-over word before a workgroup computes the value itself
     float* gact;                // null unless the gate projection is the predictor
     size_t row_elems, row_bytes;
@@ -295,12 +300,17 @@ FusedRows fused_rows(const lif_layer* L, const FusedCall& f) {
     return r;
 }
 
+// column slices of the down projection of one token: whole runs of them per XCD
+int down1_slices(const lif_config& c) {
+    const int cols = kDown1Lanes * vec_elems(c);
+    return ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;
+}
+
 // one token
 template <typename T, bool SKIP>
 void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
     const lif_config& c = L->cfg;
-    constexpr int cols = kDown1Lanes * Vec<T>::N;
-    const int slices = ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;     // whole runs of slices per XCD
+    const int slices = down1_slices(c);
     const int rows = geometry_rows(L);
     // fewer workgroup rows than chunks are still correct; one, and no second launch, where the hint itself needs one chunk
     const bool one = L->expected_rows > 0 && down1_chunks<SKIP>(std::min(L->expected_rows, c.capacity_rows), slices) == 1;
@@ -399,6 +409,37 @@ void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, h
         if (skip) launch_ffn_down_batch<T, 8, true>(L, batch, y, h, ypart, s, fc);
         else launch_ffn_down_batch<T, 8, false>(L, batch, y, h, ypart, s, fc);
     }
+}
+
+// One token in one launch, where few workgroups wait for few words.  What the waiting costs grows with slices x rows (every word is read
+// by every slice), what the second launch costs does not: fp16 in a graph, rows in use / us in two launches -> in one (all sizes in one):
+// 16 slices 871: 6.2 -> 5.7, 32 slices 480: 6.0 -> 6.0, 983: 6.3 -> 6.6, 64 slices 264: 6.1 -> 5.8, 723: 6.3 -> 6.5, 80 slices 703:
+// 6.2 -> 7.4, 128 slices 337: 6.6 -> 7.8; from the host 7.6 -> 5.4 to 6.5, 128 slices 7.7 -> 7.6.  96 slices and more gain from the host
+// alone, so they stay with two.
+bool ffn_one(const lif_layer* L, int batch) {
+    const int rows = geometry_rows(L), slices = down1_slices(L->cfg);
+    return batch == 1 && L->one_words && slices <= kOneSlices && rows <= kOneRows && slices * rows <= kOneWords;
+}
+template <typename T, bool GLU, bool SKIP>
+void launch_ffn_one(lif_layer* L, const void* x, void* y, hipStream_t s) {
+    const lif_config& c = L->cfg;
+    const int ni = (c.d_model / Vec<T>::N + 63) / 64, slices = down1_slices(c), spec = L->expected_rows > 0 ? 1 : 0;
+    const int rows = spec ? std::min(L->expected_rows, c.capacity_rows) : c.capacity_rows;
+    const int n_up = std::max(1, (rows + kOneUpWaves - 1) / kOneUpWaves);
+#define LIF_ONE(NI)                                                                                          \
+    hipLaunchKernelGGL((k_ffn_one<T, NI, GLU, SKIP>), dim3(n_up + slices), dim3(kOneWaves * 64), 0, s,              \
+                       (const T*)L->buf.matrix, L->buf.bias, (const T*)x, (T*)y, c.d_model, c.capacity_rows, L->row_elems, \
+                       spec, n_up, slices, L->one_words, L->one, L->polls, L->buf.pointers, L->gact, c.d_ffn, L->st)
+    if (ni <= 1) LIF_ONE(1);
+    else if (ni <= 2) LIF_ONE(2);
+    else LIF_ONE(4);                   // d <= kOneSlices slices
+#undef LIF_ONE
+}
+template <typename T>
+void launch_ffn_one(lif_layer* L, const void* x, void* y, hipStream_t s) {
+    const bool skip = L->cfg.ffn_mode == LIF_FFN_SKIP_DEAD;
+    if (L->cfg.glu) skip ? launch_ffn_one<T, true, true>(L, x, y, s) : launch_ffn_one<T, true, false>(L, x, y, s);
+    else skip ? launch_ffn_one<T, false, true>(L, x, y, s) : launch_ffn_one<T, false, false>(L, x, y, s);
 }
 
 // bundles of host reads kept in flight
@@ -674,6 +715,8 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
     L->ptr_new = (int32_t*)(ws + lay.ptr_new);
     L->bias_new = (float*)(ws + lay.bias_new);
     L->words = (unsigned long long*)(ws + lay.words);
+    L->one_words = cfg->capacity_rows <= kOneCapacity ? (unsigned long long*)(ws + lay.one) : nullptr;
+    L->one = L->one_words ? (OneState*)(L->one_words + kOneReps * one_pitch(cfg->capacity_rows)) : nullptr;
     L->polls = kDefaultPolls;
     L->gact = cfg->predictor == LIF_PRED_GATE ? (float*)(ws + lay.gact) : nullptr;
     L->row_elems = (size_t)(cfg->glu ? 3 : 2) * cfg->d_model;
@@ -834,6 +877,12 @@ static int check_ffn(lif_layer* L, const void* x_dev, int32_t batch, void* y_dev
 static int ffn_launches(lif_layer* L, const void* x_dev, int32_t batch, void* y_dev, float* h, float* ypart,
                         hipStream_t s) {
     const lif_config& c = L->cfg;
+    if (ffn_one(L, batch)) {
+        Timed t(L, LIF_K_FFN_DOWN, s);
+        if (c.dtype == LIF_F32) launch_ffn_one<float>(L, x_dev, y_dev, s);
+        else launch_ffn_one<_Float16>(L, x_dev, y_dev, s);
+        return check_launch();
+    }
     if (mfma_path(c, batch)) {
         // batched tokens: the activation stage is a dense contraction -> matrix cores
         Timed t(L, LIF_K_FFN_UP, s);

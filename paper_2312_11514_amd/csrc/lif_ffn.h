@@ -13,6 +13,8 @@
 //             k_ffn_down below for several tokens in fp32.
 #pragma once
 
+#include <type_traits>
+
 #include "lif_common.h"
 #include "lif_window_bits.h"
 
@@ -33,13 +35,14 @@ namespace lif {
 // the activation of slot s for token t is then gact[t][pointers[s]] * (up_s . x_t), gact [batch x gact_n];
 // gact_n = d_ffn bounds the lookup.  A single token (XREG) leaves up_s . x and k_ffn_down1 multiplies: a fused step
 // computes both in the same launch.
-template <typename T, int NI, bool GLU, bool XREG, int WAVES = 4>
+// `put(slot, activation)`, by the whole wave, takes the activations of a single token; without it they go to h.
+template <typename T, int NI, bool GLU, bool XREG, int WAVES = 4, typename Put = int>
 __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const float* __restrict__ bias,
                                             const T* __restrict__ x, float* __restrict__ h, int d, int batch,
                                             int capacity, size_t row_elems, int spec, int block, int nblocks,
                                             const int32_t* __restrict__ pointers,
                                             const float* __restrict__ gact, int gact_n,
-                                            const DevState* __restrict__ st) {
+                                            const DevState* __restrict__ st, Put put = Put()) {
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -147,7 +150,8 @@ __device__ __forceinline__ void ffn_up_role(const T* __restrict__ matrix, const 
             } else {
                 act = fmaxf(du + bs, 0.f);
             }
-            if (lane == 0) h[(size_t)b * capacity + s] = act;
+            if constexpr (!std::is_same<Put, int>::value) put(s, act);
+            else if (lane == 0) h[(size_t)b * capacity + s] = act;
         }
         if (sn < n) {
 #pragma unroll

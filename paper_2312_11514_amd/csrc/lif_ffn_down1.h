@@ -11,6 +11,8 @@
 // Slices of 32 or 128 bytes were slower at most sizes (half a line wasted per piece; too few workgroups).
 #pragma once
 
+#include <type_traits>
+
 #include "lif_common.h"
 #include "lif_ffn.h"
 
@@ -65,14 +67,17 @@ __host__ __device__ __forceinline__ int down1_waves(int n, int slices) {
 // capacity, so the addresses are valid; values past the count are masked).
 // Workgroup row y takes the chunks y, y + gridDim.y, ...; with several chunks and several workgroup rows the sums go to
 // ypart[chunk][d] (fp32) and k_ffn_down_finish adds them, else this kernel adds them in the same order.  No atomics.
-template <typename T, bool SKIP, int WAVES, bool FUSED>
-__global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ matrix, const float* __restrict__ h,
-                                                          const FusedRows fused, T* __restrict__ y,
-                                                          float* __restrict__ ypart, int d, int capacity,
-                                                          size_t row_elems, int down_off, int spec, int slices,
-                                                          const int32_t* __restrict__ pointers,
-                                                          const float* __restrict__ gact, int gact_n,
-                                                          DevState* __restrict__ st) {
+// The same as a role of a larger launch (k_ffn_one): bx, by, rows_by take the place of blockIdx.x, blockIdx.y, gridDim.y, and WORDS is where
+// the activations come from: `activations(s0, stride, count, v)` fills v[q] with those of the slots s0 + q * stride (q < count, different
+// for every lane).
+struct NoWords {};
+template <typename T, bool SKIP, int WAVES, bool FUSED, typename Words>
+__device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, const float* __restrict__ h, const FusedRows& fused,
+                                               T* __restrict__ y, float* __restrict__ ypart, int d, int capacity,
+                                               size_t row_elems, int down_off, int spec, int slices,
+                                               const int32_t* __restrict__ pointers, const float* __restrict__ gact, int gact_n,
+                                               DevState* __restrict__ st, int bx, int by, int rows_by, Words activations) {
+    constexpr bool WORDS = !std::is_same<Words, NoWords>::value;
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N, LANES = kDown1Lanes, PER = kDown1Per, THREADS = WAVES * 64;
     constexpr int WL = PER * 64;                     // list entries per wave and pass
@@ -84,14 +89,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l = lane & (LANES - 1), rg = lane / LANES;
     // XCD-aware slice order: workgroups are dealt round-robin to the 8 XCDs, each with its own L2; giving every XCD a
     // contiguous run of slices makes the two halves of a 128-byte line meet in one L2 instead of being fetched twice
-    if (FUSED && (int)blockIdx.x == slices) {
-        if (blockIdx.y == 0) commit_step<THREADS>(fused, capacity, st);
+    if (FUSED && bx == slices) {
+        if (by == 0) commit_step<THREADS>(fused, capacity, st);
         return;
     }
     const float* __restrict__ h_new = fused.h_new;
     const int32_t* __restrict__ stamp = FUSED ? fused.stamp : nullptr;
     const int per_xcd = slices / kXcds;
-    const int slice = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    const int slice = (bx % kXcds) * per_xcd + bx / kXcds;
     const int col = slice * (LANES * VE) + l * VE;
     const bool col_ok = col < d;
     const T* base = matrix + down_off + (col_ok ? col : 0);
@@ -104,8 +109,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
         sfirst[q] = -1;
         ofirst[q] = onfirst[q] = 0;
     }
-    const bool first_row = blockIdx.y == 0;
-    if (first_row) {                                 // (uniform branches around loads from clamped slots)
+    const bool first_row = by == 0;
+    if (!WORDS && first_row) {                               // (uniform branches around loads from clamped slots)
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             if (q < spec) hfirst[q] = h[min(q * THREADS + tid, capacity - 1)];
@@ -130,13 +135,13 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
     const int err = counts->error, n = counts->num_used, cur_step = counts->step;
     if (err) return;
     const int chunks = down1_chunks<SKIP>(n, slices);
-    if ((int)blockIdx.y >= chunks) return;           // uniform
+    if (by >= chunks) return;                        // uniform
     const int per_chunk = chunks == 1 ? n : (n + chunks - 1) / chunks;      // (no division on the shortest path)
     const int vwaves = down1_waves<SKIP>(n, slices);
     const int stride = vwaves * 64;                  // slots between the groups of a (virtual) wave
     const bool natural = vwaves == WAVES;            // the requests above were for the right slots
     double total = 0.0;
-    for (int chunk = blockIdx.y; chunk < chunks; chunk += gridDim.y) {
+    for (int chunk = by; chunk < chunks; chunk += rows_by) {
         const int r0 = chunk * per_chunk, r1 = min(n, r0 + per_chunk);
         for (int vw = wv; vw < vwaves; vw += WAVES) {
             float acc[VE];
@@ -157,7 +162,16 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
                     hval[q] = fresh ? hnfirst[q] : hfirst[q];
                     owner[q] = fresh ? onfirst[q] : ofirst[q];
                 }
-                if (need > have) {
+                if constexpr (WORDS) {
+                    if (gact) {
+#pragma unroll
+                        for (int q = 0; q < PER; ++q) owner[q] = pointers[min(s0 + q * stride, capacity - 1)];
+                    }
+                    int count = 0;
+#pragma unroll
+                    for (int q = 0; q < PER; ++q) count += s0 + q * stride < r1;
+                    activations(s0, stride, count, hval);
+                } else if (need > have) {
 #pragma unroll
                     for (int q = 0; q < PER; ++q)
                         if (q >= have && q < need) {
@@ -249,7 +263,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
             for (int w = 0; w < VWMAX; ++w)
                 if (w < vwaves) sum += red[w][tid / VE][tid % VE];
             const int oc = slice * (LANES * VE) + tid;
-            if (chunks > 1 && gridDim.y > 1) {
+            if (chunks > 1 && rows_by > 1) {
                 if (oc < d) ypart[(size_t)chunk * d + oc] = sum;
             } else {
                 total += (double)sum;                // as ChunkSum; 0 + first sum is exact
@@ -261,10 +275,22 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
         atomicAdd(&st->c_ffn_calls, 1ull);
         atomicAdd(&st->c_ffn_rows, (unsigned long long)n);
     }
-    if (chunks == 1 || gridDim.y == 1) {
+    if (chunks == 1 || rows_by == 1) {
         const int oc = slice * (LANES * VE) + tid;
         if (tid < LANES * VE && oc < d) y[oc] = (T)total;
     }
+}
+
+template <typename T, bool SKIP, int WAVES, bool FUSED>
+__global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ matrix, const float* __restrict__ h,
+                                                          const FusedRows fused, T* __restrict__ y,
+                                                          float* __restrict__ ypart, int d, int capacity,
+                                                          size_t row_elems, int down_off, int spec, int slices,
+                                                          const int32_t* __restrict__ pointers,
+                                                          const float* __restrict__ gact, int gact_n,
+                                                          DevState* __restrict__ st) {
+    ffn_down1_role<T, SKIP, WAVES, FUSED>(matrix, h, fused, y, ypart, d, capacity, row_elems, down_off, spec, slices, pointers, gact,
+                                          gact_n, st, blockIdx.x, blockIdx.y, gridDim.y, NoWords());
 }
 
 }  // namespace lif
