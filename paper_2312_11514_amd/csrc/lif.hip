@@ -335,9 +335,11 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     else if (fc.on) LIF_D1(16, true);
     else LIF_D1(16, false);
 #undef LIF_D1
-    if (wg_rows > 1)
-        hipLaunchKernelGGL((k_ffn_down_finish<T, down1_chunks<SKIP>>), dim3((c.d_model + 255) / 256), dim3(256), 0, s,
-                           ypart, (T*)y, c.d_model, 1, slices, wg_rows, L->st);
+#define LIF_D1F(MOST)                                                                                        \
+    hipLaunchKernelGGL((k_ffn_down_finish<T, down1_chunks<SKIP>, MOST>), dim3((c.d_model + 255) / 256), dim3(256), 0, s,    \
+                       ypart, (T*)y, c.d_model, 1, slices, wg_rows, L->st)
+    if (wg_rows > 1) LIF_FINISH(wg_rows, LIF_D1F);
+#undef LIF_D1F
 }
 
 // several tokens, fp32
@@ -357,9 +359,11 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
     if (fc.on) LIF_DB(true);
     else LIF_DB(false);
 #undef LIF_DB
-    if (wg_rows > 1)
-        hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
-                           ypart, (T*)y, c.d_model, batch, slices, wg_rows, L->st);
+#define LIF_DBF(MOST)                                                                                        \
+    hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks, MOST>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,   \
+                       ypart, (T*)y, c.d_model, batch, slices, wg_rows, L->st)
+    if (wg_rows > 1) LIF_FINISH(wg_rows, LIF_DBF);
+#undef LIF_DBF
 }
 
 // several tokens, fp16: the down projection on the matrix cores
@@ -379,9 +383,11 @@ void launch_ffn_down_mfma_rows(lif_layer* L, int batch, void* y, float* h, float
     if (fc.on) LIF_DM(true);
     else LIF_DM(false);
 #undef LIF_DM
-    if (wg_rows > 1)
-        hipLaunchKernelGGL(k_ffn_down_mfma_finish, dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart,
-                           (_Float16*)y, c.d_model, batch, chunk_rows, wg_rows, L->st);
+#define LIF_DMF(MOST)                                                                                        \
+    hipLaunchKernelGGL((k_ffn_down_mfma_finish<MOST>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart,       \
+                       (_Float16*)y, c.d_model, batch, chunk_rows, wg_rows, L->st)
+    if (wg_rows > 1) LIF_FINISH(wg_rows, LIF_DMF);
+#undef LIF_DMF
 }
 
 template <bool SKIP>

@@ -286,17 +286,21 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
 // y = sum of the chunk partials in chunk order, rounded once to fp16.  Launched after a k_ffn_down_mfma grid of
 // more than one workgroup row; does nothing when a single chunk was in use (y is written already).
 // grid = ceil(batch * d / 256), block = 256.
-__global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* __restrict__ ypart, _Float16* __restrict__ y,
+template <int MOST>
+__global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* ypart, _Float16* __restrict__ y,
                                                               int d, int batch, int chunk_rows, int ahead,
-                                                              const DevState* __restrict__ st) {
-    const int i = blockIdx.x * 256 + threadIdx.x, at = min(i, batch * d - 1);
-    ChunkSum p;
-    p.request(ypart + at, (size_t)batch * d, 0, ahead);
-    if (st->cur.error) return;
-    const int chunks = down_mfma_chunks(st->cur.num_used, chunk_rows);
+                                                              const DevState* st) {
+    const int i = blockIdx.x * 256 + threadIdx.x, stride = batch * d;
+    const float* p = ypart + min(i, stride - 1);
+    const int err = st->cur.error, n = st->cur.num_used;
+    ChunkSum<MOST> part;
+    part.request(p, stride, ahead);
+    asm volatile("" ::: "memory");                   // (the compiler would ask for them, and for the count, where they are used)
+    if (err) return;
+    const int chunks = down_mfma_chunks(n, chunk_rows);
     if (chunks == 1) return;
-    p.request(ypart + at, (size_t)batch * d, ahead, chunks);
-    if (i < batch * d) y[i] = (_Float16)p.sum<float>(chunks);
+    const float sum = part.template sum<float>(p, stride, ahead, chunks);
+    if (i < stride) y[i] = (_Float16)sum;
 }
 
 }  // namespace lif
