@@ -163,7 +163,6 @@ struct lif_layer {
     size_t row_elems, row_bytes;
     bool window_pending;
     int expected_rows;          // hint, 0 = none
-    int mask_tokens;            // tokens per pass of the mask kernel at most
     unsigned char* static_scratch;  // this device's copy of the library's static scratch array (null: lookup failed)
     // event timing
     bool prof_on;
@@ -210,14 +209,14 @@ int launch_predict(lif_layer* L, const void* x, int batch, uint8_t* masks, uint8
     }
     const int grid = (c.d_ffn + kMaskCols * 8 - 1) / (kMaskCols * 8);
     Timed t(L, LIF_K_PREDICT_MASK, s);
-    // tokens per pass over B: chosen at lif_create so that what it keeps of them in LDS fits a workgroup
-    const int tokens = std::min(batch, L->mask_tokens);
-#define LIF_MASK(MANY)                                                                                      \
-    hipLaunchKernelGGL((k_predict_mask<T, MANY>), dim3(grid), dim3(256), MANY ? mask_lds_bytes(c.rank, tokens) : 0, s, \
-                       (const T*)L->buf.B, L->buf.c, L->tpart, c.rank, c.d_ffn, batch, tokens, c.threshold, masks,     \
-                       step_mask, L->st)
-    if (tokens == 1) LIF_MASK(false);
-    else LIF_MASK(true);
+#define LIF_MASK(KERNEL, LDS)                                                                               \
+    hipLaunchKernelGGL((KERNEL), dim3(grid), dim3(256), LDS, s, (const T*)L->buf.B, L->buf.c, L->tpart, c.rank, c.d_ffn,   \
+                       batch, c.threshold, masks, step_mask, L->st)
+    if (batch == 1) LIF_MASK((k_predict_mask<T, false>), 0);
+    else if (c.rank <= kMaskChunk) LIF_MASK((k_predict_mask<T, true>), mask_lds_bytes(c.rank, batch));
+    else if (batch <= 2) LIF_MASK((k_predict_mask_long<T, 2>), 0);
+    else if (batch <= 4) LIF_MASK((k_predict_mask_long<T, 4>), 0);
+    else LIF_MASK((k_predict_mask_long<T, 8>), 0);
 #undef LIF_MASK
     return LIF_OK;
 }
@@ -731,9 +730,6 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
     L->expected_rows = 0;
     L->prof_on = false;
     L->prof_max = 0;
-    // t = x A of the tokens of a pass of the mask kernel lies in LDS (at most 64 KiB without asking, 40 bytes of it static)
-    L->mask_tokens = 8;
-    while (L->mask_tokens > 1 && mask_lds_bytes(std::max(cfg->rank, 0), L->mask_tokens) > 64 * 1024 - 64) --L->mask_tokens;
     {
         // address of the static scratch array on the device that is current now (the layer's device)
         void* p = nullptr;

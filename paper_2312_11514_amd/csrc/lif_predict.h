@@ -80,121 +80,227 @@ __global__ __launch_bounds__(256) void k_predict_xa(const T* __restrict__ x, con
     if (threadIdx.x == 0 && !err) t[(size_t)b * r + j] = column_total(part);
 }
 
+// The sums v[e] of neurons 8 cl + e over a thread's ranks -> the sum over the eight rank groups of the wave, which sit 8 lanes apart:
+// every exchange leaves a lane with half of its neurons, in the end with neuron 8 cl + fold_owner(lane).
+__device__ __forceinline__ double fold_groups(double (&v)[8], int lane) {
+    const bool up = (lane & 8) != 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double send = up ? v[e] : v[e + 4], keep = up ? v[e + 4] : v[e];
+        v[e] = keep + dpp_from<0x128, 0xf>(send);    // lanes 8 apart: a rotation in a row of 16
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) v[e] = swap_add<16>(v[e], v[e + 2]);
+    return swap_add<32>(v[0], v[1]);
+}
+__device__ __forceinline__ int fold_owner(int lane) { return ((lane >> 3) & 1) * 4 + ((lane >> 4) & 1) * 2 + (lane >> 5); }
+
 // logits = t B + c, threshold, 64 mask bits at a time; step mask = OR over the batch.
-// grid = ceil(F / 64), block = 256 = 32 rank groups x 8 column lanes; a column lane owns 8 consecutive neurons.  `tokens` of the batch
-// per pass over B; MANY: their t and the sums of the waves lie in LDS (dynamic, mask_lds_bytes), else (tokens = 1) t comes straight
-// from memory with the rows of B.
+// grid = ceil(F / 64), block = 256 = 32 rank groups x 8 column lanes; a column lane owns 8 consecutive neurons.  A thread adds its ranks
+// jg, jg + 32, ... in that order, then come the rank groups of a wave (fold_groups), then the waves: the one order of a logit, which
+// MaskTile in k_step1 keeps too.
+// MANY: several tokens at a rank of one chunk; their t and the sums of the waves lie in LDS (dynamic, mask_lds_bytes).  Else one token, and
+// t comes straight from memory with the rows of B.  (Several tokens and more chunks: k_predict_mask_long.)
 // What bounds it: the chain from the launch over one round trip for B and t, 64 fp64 multiply-adds per thread and token, and the
 // sums across the rank groups; a few hundred KB to a few MB are read.  A token at a time, with B widened once: the code is 2 KB
-// instead of 10, and instructions that run once wait for their way into the cache (8 tokens at once, rank 256: 8.1 us).  The sums across a wave go through register
-// exchanges that leave a lane with one neuron, so that a ballot is the mask word.  8 tokens, rank 256: 10.4 -> 7.5 us; 5 tokens, rank 128,
-// 9.5 -> 6.1 us; 3 tokens in fp32, rank 68, 6.6 -> 5.2 us (all tokens at once, exchanges through LDS, sums and bits by 64 threads).
+// instead of 10, and instructions that run once wait for their way into the cache (8 tokens at once, rank 256: 8.1 us).  The sums
+// across a wave go through register exchanges that leave a lane with one neuron, so that a ballot is the mask word.  8 tokens,
+// rank 256: 10.4 -> 7.5 us; 5 tokens, rank 128, 9.5 -> 6.1 us; 3 tokens in fp32, rank 68, 6.6 -> 5.2 us (all tokens at once, exchanges
+// through LDS, sums and bits by 64 threads).
+constexpr int kMaskChunk = kMaskRows * kMaskJg;      // ranks at a time
 inline size_t mask_lds_bytes(int r, int tokens) { return sizeof(double) * tokens * ((size_t)r + 4 * 64); }
 template <typename T, bool MANY>
 __global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B, const float* __restrict__ c,
-                                                      const double* __restrict__ t, int r, int F, int batch, int tokens,
-                                                      float theta,
+                                                      const double* __restrict__ t, int r, int F, int batch, float theta,
                                                       uint8_t* __restrict__ masks, uint8_t* __restrict__ step_mask,
                                                       const DevState* __restrict__ st) {
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N;
     constexpr int LPB = 8 / VE;             // 16-byte loads per group of 8 neurons
-    constexpr int kChunk = kMaskRows * kMaskJg;      // ranks at a time
     extern __shared__ __attribute__((aligned(16))) double lds_mask[];
     __shared__ double red_one[MANY ? 1 : 4 * 64];
     __shared__ unsigned long long ors[4];
     double* const red = MANY ? lds_mask : red_one;   // [token][wave][neuron of the tile]
-    double* const tl = lds_mask + tokens * (4 * 64); // [token][r]
+    double* const tl = lds_mask + batch * (4 * 64);  // [token][r]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cl = tid & (kMaskCols - 1), jg = tid >> 3;
     const int n0 = (blockIdx.x * kMaskCols + cl) * 8, own = blockIdx.x * 64 + lane;
     const bool col_ok = n0 < F;
     const int mask_stride = F >> 3, byte = blockIdx.x * kMaskCols + lane;                // lanes 0..7: a mask byte each
-    unsigned long long or_word = 0ull;      // of this wave's tokens
+    const int nb = MANY ? batch : 1;
     V bv[kMaskRows][LPB];
     double tr[MANY ? 1 : kMaskRows];
-    auto request = [&](int b0, int j0) {             // the rows j0 + jg + u * kMaskJg of B (0 past the end)
+    auto request = [&](int j0) {                     // the rows j0 + jg + u * kMaskJg of B (0 past the end)
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) {
             const int j = j0 + jg + u * kMaskJg;
 #pragma unroll
             for (int q = 0; q < LPB; ++q)
                 bv[u][q] = (col_ok && j < r) ? reinterpret_cast<const V*>(B + (size_t)j * F + n0)[q] : V(0);
-            if constexpr (!MANY) tr[u] = t[(size_t)b0 * r + min(j, r - 1)];
+            if constexpr (!MANY) tr[u] = t[min(j, r - 1)];
         }
     };
-    request(0, 0);
-    const double cv = (c && own < F) ? (double)c[own] : 0.0;
+    request(0);
+    const float cv = (c && own < F) ? c[own] : 0.f;      // (widened where it is used: here that would wait for it)
     const int err = st->cur.error;
 
-    for (int b0 = 0; b0 < batch; b0 += tokens) {
-        const int nb = min(tokens, batch - b0);
-        if (b0 > 0) {
-            __syncthreads();                         // red and tl are still read from the pass before
-            request(b0, 0);
-        }
-        if constexpr (MANY) {
-            // t of the tokens of a pass is one contiguous run: 16-byte pieces, several of them in flight per thread
-            constexpr int kAhead = 4;
-            typedef double f64x2 __attribute__((ext_vector_type(2)));
-            const int pieces = nb * r / 2;           // (r is even)
-            const f64x2* src = reinterpret_cast<const f64x2*>(t + (size_t)b0 * r);
-            for (int i0 = tid; i0 < pieces; i0 += 256 * kAhead) {
-                f64x2 p[kAhead];
+    if constexpr (MANY) {
+        // t of the tokens is one contiguous run: 16-byte pieces, several of them in flight per thread
+        constexpr int kAhead = 4;
+        typedef double f64x2 __attribute__((ext_vector_type(2)));
+        const int pieces = nb * r / 2;               // (r is even)
+        const f64x2* src = reinterpret_cast<const f64x2*>(t);
+        for (int i0 = tid; i0 < pieces; i0 += 256 * kAhead) {
+            f64x2 p[kAhead];
 #pragma unroll
-                for (int i = 0; i < kAhead; ++i) p[i] = src[min(i0 + i * 256, pieces - 1)];
+            for (int i = 0; i < kAhead; ++i) p[i] = src[min(i0 + i * 256, pieces - 1)];
 #pragma unroll
-                for (int i = 0; i < kAhead; ++i)
-                    if (i0 + i * 256 < pieces) reinterpret_cast<f64x2*>(tl)[i0 + i * 256] = p[i];
-            }
-            __syncthreads();
-        }
-        for (int j0 = 0; j0 < r; j0 += kChunk) {
-            double bd[kMaskRows][8], tn[kMaskRows];
-#pragma unroll
-            for (int u = 0; u < kMaskRows; ++u) {
-                if constexpr (!MANY) tn[u] = tr[u];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) bd[u][e] = (double)bv[u][e / VE][e % VE];
-            }
-            if (j0 + kChunk < r) request(b0, j0 + kChunk);
-#pragma unroll 1
-            for (int bt = 0; bt < nb; ++bt) {
-                if constexpr (MANY) {
-#pragma unroll
-                    for (int u = 0; u < kMaskRows; ++u) tn[u] = tl[bt * r + min(j0 + jg + u * kMaskJg, r - 1)];
-                }
-                double v[8];                         // logit sums of the 8 neurons of this lane's byte
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = 0.0;
-#pragma unroll
-                for (int u = 0; u < kMaskRows; ++u)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tn[u], bd[u][e], v[e]);     // (0 past the last rank)
-                // The eight rank groups of a wave sit 8 lanes apart: every exchange leaves a lane with half of its neurons
-                const bool up = (lane & 8) != 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const double send = up ? v[e] : v[e + 4], keep = up ? v[e + 4] : v[e];
-                    v[e] = keep + dpp_from<0x128, 0xf>(send);    // lanes 8 apart: a rotation in a row of 16
-                }
-#pragma unroll
-                for (int e = 0; e < 2; ++e) v[e] = swap_add<16>(v[e], v[e + 2]);
-                v[0] = swap_add<32>(v[0], v[1]);
-                double* const to = red + (bt * 4 + wave) * 64 + cl * 8 + (up ? 4 : 0) + ((lane >> 4) & 1) * 2 + (lane >> 5);
-                *to = j0 > 0 ? *to + v[0] : v[0];    // (this lane's alone)
-            }
+            for (int i = 0; i < kAhead; ++i)
+                if (i0 + i * 256 < pieces) reinterpret_cast<f64x2*>(tl)[i0 + i * 256] = p[i];
         }
         __syncthreads();
-        for (int bt = wave; bt < nb; bt += 4) {
-            const double* p = red + bt * 256 + lane;
-            double z = ((p[0] + p[64]) + p[128]) + p[192];
-            z += cv;
-            const unsigned long long word = __ballot(own < F && z > (double)theta);
-            or_word |= word;
-            if (lane < kMaskCols && byte < mask_stride && !err) masks[(size_t)(b0 + bt) * mask_stride + byte] = (uint8_t)(word >> (8 * lane));
+    }
+    double bd[kMaskRows][8];
+    auto widen = [&]() {
+#pragma unroll
+        for (int u = 0; u < kMaskRows; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bd[u][e] = (double)bv[u][e / VE][e % VE];
+    };
+    double v[8];                                     // logit sums of the 8 neurons of this lane's byte
+    auto multiply = [&](const double (&tn)[kMaskRows]) {
+#pragma unroll
+        for (int u = 0; u < kMaskRows; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tn[u], bd[u][e], v[e]);         // (0 past the last rank)
+    };
+    const int at = wave * 64 + cl * 8 + fold_owner(lane);
+    if constexpr (MANY) {
+        widen();
+        double ahead[kMaskRows];                     // of the next token
+        auto read_t = [&](int bt) {
+#pragma unroll
+            for (int u = 0; u < kMaskRows; ++u) ahead[u] = tl[bt * r + min(jg + u * kMaskJg, r - 1)];
+        };
+        read_t(0);
+#pragma unroll 1
+        for (int bt = 0; bt < nb; ++bt) {
+            double tn[kMaskRows];
+#pragma unroll
+            for (int u = 0; u < kMaskRows; ++u) tn[u] = ahead[u];
+            read_t(min(bt + 1, nb - 1));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = 0.0;
+            multiply(tn);
+            red[bt * 256 + at] = fold_groups(v, lane);
         }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = 0.0;
+        for (int j0 = 0; j0 < r; j0 += kMaskChunk) {
+            double tn[kMaskRows];
+            widen();
+#pragma unroll
+            for (int u = 0; u < kMaskRows; ++u) tn[u] = tr[u];
+            if (j0 + kMaskChunk < r) request(j0 + kMaskChunk);
+            multiply(tn);
+        }
+        red[at] = fold_groups(v, lane);
+    }
+    __syncthreads();
+    unsigned long long or_word = 0ull;               // of this wave's tokens
+    for (int bt = wave; bt < nb; bt += 4) {
+        const double* p = red + bt * 256 + lane;
+        double z = ((p[0] + p[64]) + p[128]) + p[192];
+        z += (double)cv;
+        const unsigned long long word = __ballot(own < F && z > (double)theta);
+        or_word |= word;
+        if (lane < kMaskCols && byte < mask_stride && !err) masks[(size_t)bt * mask_stride + byte] = (uint8_t)(word >> (8 * lane));
+    }
+    if (lane == 0) ors[wave] = or_word;
+    __syncthreads();
+    if (tid < kMaskCols && byte < mask_stride && !err)
+        step_mask[byte] = (uint8_t)(((ors[0] | ors[1]) | (ors[2] | ors[3])) >> (8 * lane));
+}
+
+// The same for several tokens at more than kMaskChunk ranks.  A thread's sums have to stay apart from the other rank groups' until its last
+// rank, so they stay in registers for NT tokens at a time (the batch at most; tokens past it are worked for and left out).  A row of B is
+// widened once for all of them and asked for again, a chunk on, as soon as it is used; t goes through LDS a chunk ahead.
+// lif_predict, us, d = 4096, F = 16384, against folding every chunk and adding the folded sums (another order): fp16, 8 tokens, rank 512
+// 16.5 -> 13.8, 768 25.3 -> 18.3, 2048 64.8 -> 41.5; 2 tokens, rank 2048 22.8 -> 23.1; fp32, 3 tokens, rank 512 14.8 -> 14.6.
+template <typename T, int NT>
+__global__ __launch_bounds__(256, 1) void k_predict_mask_long(const T* __restrict__ B, const float* __restrict__ c,
+                                                              const double* __restrict__ t, int r, int F, int batch, float theta,
+                                                              uint8_t* __restrict__ masks, uint8_t* __restrict__ step_mask,
+                                                              const DevState* __restrict__ st) {
+    using V = typename Vec<T>::type;
+    constexpr int VE = Vec<T>::N, LPB = 8 / VE;
+    __shared__ double tl[2][NT][kMaskChunk];
+    __shared__ double red[NT][4][64];
+    __shared__ unsigned long long ors[4];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int cl = tid & (kMaskCols - 1), jg = tid >> 3;
+    const int n0 = (blockIdx.x * kMaskCols + cl) * 8, own = blockIdx.x * 64 + lane;
+    const bool col_ok = n0 < F;
+    const int mask_stride = F >> 3, byte = blockIdx.x * kMaskCols + lane;
+    V bv[kMaskRows][LPB];
+    double td[NT];
+    auto request_row = [&](int u, int j0) {
+        const int j = j0 + jg + u * kMaskJg;
+#pragma unroll
+        for (int q = 0; q < LPB; ++q)
+            bv[u][q] = (col_ok && j < r) ? reinterpret_cast<const V*>(B + (size_t)j * F + n0)[q] : V(0);
+    };
+    auto request_t = [&](int j0) {                   // (0 past the end, and for the tokens past the last one)
+#pragma unroll
+        for (int bt = 0; bt < NT; ++bt) td[bt] = (bt < batch && j0 + tid < r) ? t[(size_t)bt * r + j0 + tid] : 0.0;
+    };
+    auto stage_t = [&](int buf) {
+#pragma unroll
+        for (int bt = 0; bt < NT; ++bt) tl[buf][bt][tid] = td[bt];
+    };
+    request_t(0);
+#pragma unroll
+    for (int u = 0; u < kMaskRows; ++u) request_row(u, 0);
+    const float cv = (c && own < F) ? c[own] : 0.f;      // (widened where it is used: here that would wait for it)
+    const int err = st->cur.error;
+    double v[NT][8];
+#pragma unroll
+    for (int bt = 0; bt < NT; ++bt)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[bt][e] = 0.0;
+    stage_t(0);
+    for (int j0 = 0, buf = 0; j0 < r; j0 += kMaskChunk, buf ^= 1) {
+        __syncthreads();                             // (also: nobody reads the other half of tl any more)
+        const bool more = j0 + kMaskChunk < r;       // uniform
+        if (more) request_t(j0 + kMaskChunk);
+#pragma unroll
+        for (int u = 0; u < kMaskRows; ++u) {
+            double bd[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bd[e] = (double)bv[u][e / VE][e % VE];
+            if (more) request_row(u, j0 + kMaskChunk);
+#pragma unroll
+            for (int bt = 0; bt < NT; ++bt) {
+                const double tj = tl[buf][bt][jg + u * kMaskJg];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[bt][e] = __builtin_fma(tj, bd[e], v[bt][e]);
+            }
+        }
+        if (more) stage_t(buf ^ 1);
+    }
+#pragma unroll
+    for (int bt = 0; bt < NT; ++bt) red[bt][wave][cl * 8 + fold_owner(lane)] = fold_groups(v[bt], lane);
+    __syncthreads();
+    unsigned long long or_word = 0ull;
+    for (int bt = wave; bt < batch; bt += 4) {
+        double z = ((red[bt][0][lane] + red[bt][1][lane]) + red[bt][2][lane]) + red[bt][3][lane];
+        z += (double)cv;
+        const unsigned long long word = __ballot(own < F && z > (double)theta);
+        or_word |= word;
+        if (lane < kMaskCols && byte < mask_stride && !err) masks[(size_t)bt * mask_stride + byte] = (uint8_t)(word >> (8 * lane));
     }
     if (lane == 0) ors[wave] = or_word;
     __syncthreads();

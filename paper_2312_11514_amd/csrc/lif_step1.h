@@ -206,25 +206,9 @@ struct MaskTile {
                 }
             }
         }
-        // Rank groups of a wave sit 8 lanes apart.  Folds that halve what a lane holds, over lanes 8 apart (a rotation in rows
-        // of 16), then rows, then halves of the wave (a lane gives away one value and gets its partner's other): neuron 8 cl +
-        // owner ends up in lane (owner, cl).  In registers throughout, and the 64 decisions become the mask word by one
-        // ballot: 1.3 -> 0.7 us from t to the published word against exchanges through LDS and a byte per lane.
-        int owner;
-        {
-            const bool up = (lane & 8) != 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const double send = up ? v[i] : v[i + 4], keep = up ? v[i + 4] : v[i];
-                v[i] = keep + dpp_from<0x128, 0xf>(send);
-            }
-            owner = up ? 4 : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) v[i] = swap_add<16>(v[i], v[i + 2]);
-        v[0] = swap_add<32>(v[0], v[1]);
-        owner += ((lane >> 4) & 1) * 2 + (lane >> 5);
-        L.red[wave][cl * 8 + owner] = v[0];
+        // (In registers throughout, and the 64 decisions become the mask word by one ballot: 1.3 -> 0.7 us from t to the published
+        // word against exchanges through LDS and a byte per lane.)
+        L.red[wave][cl * 8 + fold_owner(lane)] = fold_groups(v, lane);
         __syncthreads();
         double z = ((L.red[0][lane] + L.red[1][lane]) + L.red[2][lane]) + L.red[3][lane];
         z += (double)cv;
