@@ -18,8 +18,9 @@
 // A value handed over is a 64-bit word: 32 bits of payload and the number of the step as a stamp, written by a relaxed
 // device-scope atomic store and polled with relaxed device-scope atomic loads, so no fence (a device-scope release
 // writes back the L2: 6 us) and no clearing is needed.  Stamps are unique between two resets, which clear the words.
-// A workgroup waits only for workgroups with smaller numbers, and never without bound: after `polls` failed polls it
-// computes what it is missing itself, with the same arithmetic (polls = 0: never waits at all).
+// A workgroup waits for workgroups with smaller numbers or, a tile of neurons for the columns of x A, for workgroups that
+// fit the chip at the same time (kStepColumns); and never without bound: after `polls` failed polls it computes what it is
+// missing itself, with the same arithmetic (polls = 0: never waits at all).
 // What other workgroups may still read is not overwritten: the new counts are left in st->next and the slot owners and
 // biases of the rows a loader writes in ptr_new / bias_new; the down projection, which runs after all of them, commits
 // them.  A matrix row that the activation role reads while a loader overwrites it gives a value that is never used: the
@@ -45,7 +46,16 @@
 namespace lif {
 
 constexpr int kListItems = 2048;     // work items listed at a time
-constexpr int kStepColumns = 256;    // predictor workgroups that only compute columns of x A: at most as many as there are compute units
+// Two workgroups per compute unit as long as a loader's bundle piece, row piece and x fit the registers of half a SIMD.
+template <int NI, bool GLU>
+constexpr int step1_wgs_per_cu() {
+    constexpr int vectors = NI > 2 ? (GLU ? 2 : 1) : (GLU ? 3 : 2);
+    return (2 * vectors + 1) * NI * 4 <= 120 ? 2 : 1;
+}
+// Columns of x A are dealt to the first kStepColumns x step1_wgs_per_cu predictor workgroups: every tile of neurons waits for all columns,
+// so these have to run at the same time, and that many fit the chip.  Dealt over all of them, one token at d = 5120, gated, F = 17000,
+// rank 512 (266 predictor workgroups, one to a compute unit) took 1484 us, every wait running out; so 81.
+constexpr int kStepColumns = 256;
 
 struct StepArgs {
     // predictor
@@ -216,10 +226,11 @@ struct MaskTile {
     }
 };
 
-template <typename T, int NI>
+template <typename T, int NI, int WGS>
 __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, PredictLds& L) {
     const int tid = threadIdx.x, nvec = a.d / Vec<T>::N;
-    const bool producer = block < a.rank;
+    const int dealt = min(a.n_pred, kStepColumns * WGS);
+    const bool producer = block < min(a.rank, dealt);
     const bool has_tile = block * kMaskCols * 8 < a.F;
     ColumnPart<T, NI> col;
     if (producer) {
@@ -231,12 +242,10 @@ __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, Predi
     const int err = a.st->cur.error;
     const unsigned now = (unsigned)a.st->cur.step + 1u;
     if (err) return;
-    for (int j = block; j < a.rank; j += a.n_pred) {
-        if (j != block) {
-            col.load(col.a, (const T*)a.A + (size_t)j * a.d, nvec);
-            __syncthreads();                         // (the parts of the column before are still read)
-        }
+    for (int j = block; producer && j < a.rank; j += dealt) {
+        if (j != block) __syncthreads();             // (the parts of the column before are still read)
         const double v = col.sum();
+        if (j + dealt < a.rank) col.load(col.a, (const T*)a.A + (size_t)(j + dealt) * a.d, nvec);
         if ((tid & 63) == 0) L.part[tid >> 6] = v;
         __syncthreads();
         if (tid < 2 * kWordReps) {
@@ -1217,12 +1226,6 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     }
 }
 
-// Two workgroups per compute unit as long as a loader's bundle piece, row piece and x fit the registers of half a SIMD.
-template <int NI, bool GLU>
-constexpr int step1_wgs_per_cu() {
-    constexpr int vectors = NI > 2 ? (GLU ? 2 : 1) : (GLU ? 3 : 2);
-    return (2 * vectors + 1) * NI * 4 <= 120 ? 2 : 1;
-}
 // The activation role reads megabytes that nothing needs before the down projection; read at once they hold up the predictor, whose few
 // reads the host link waits for (x A published 3.9 to 6.2 us after the launch began instead of 2.2, Falcon and Llama-2 shapes).  So
 // its waves begin when a mask word has been published, or after kActWaits reads of it at the latest.
@@ -1243,7 +1246,7 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
     const int block = blockIdx.x;
     if (block < a.n_pred) {
         if constexpr (GATE) gate_role<T, NI>(a, block, reinterpret_cast<unsigned*>(lds));
-        else lowrank_role<T, NI>(a, block, *reinterpret_cast<PredictLds*>(lds));
+        else lowrank_role<T, NI, step1_wgs_per_cu<NI, GLU>()>(a, block, *reinterpret_cast<PredictLds*>(lds));
     } else if (block <= a.n_pred + a.n_load) {
         cache_role<T, NI, GLU, GATE, kOneToken>(a, block - a.n_pred, *reinterpret_cast<PlanLds*>(lds), nullptr, nullptr);
     } else {

@@ -374,3 +374,33 @@ def test_down_projection_of_a_batch_by_row_chunks(dtype, d, F, rows, full):
         assert all(torch.equal(y, got[0]) for y in got[1:]), n
         want = h[:, :n].contiguous() @ lay.matrix[:n, d:].double()
         assert rel_l2(got[0].cpu().numpy().astype(np.float64), want.cpu().numpy()) <= (1e-5 if dtype == "f32" else REL_L2_TOL), n
+
+
+def test_columns_of_x_a_come_from_workgroups_that_run_together():
+    """More predictor workgroups (266) than fit the chip with the widest gated rows: none of those that run first may wait for columns
+    of those that start when they end.  At rank 512 a step then took 1484 us, each wait until it runs out; now 81.  At rank 256 the columns
+    were never dealt that far, so a step of that rank is the measure."""
+    import paper_2312_11514_amd as lif
+    from tests.harness import require_gpu
+    require_gpu()
+    d, F, cap = 5120, 17000, 512
+    zeros = lambda *s, dt=torch.float16: torch.zeros(s, dtype=dt, device="cuda")
+    host = torch.empty((F, 3 * d), dtype=torch.float16, pin_memory=True)     # (zeros predict no neuron: nothing is loaded)
+    x, y = zeros(1, d), zeros(1, d)
+    us = {}
+    for rank in (256, 512):
+        lay = lif.Layer(d_model=d, d_ffn=F, rank=rank, window_k=2, capacity_rows=cap, glu=True, dtype="f16", A=zeros(rank, d),
+                        B=zeros(rank, F), c=None, b=zeros(F, dt=torch.float32), host_bundles=host)
+        lay.step(x, y)
+        us[rank] = []
+        for _ in range(7):
+            print(f"rank {rank}", flush=True)
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(4):
+                lay.step(x, y)
+            end.record()
+            end.synchronize()
+            us[rank].append(250.0 * begin.elapsed_time(end))
+        assert lay.state()["error"] == 0 and not y.any()
+    assert sorted(us[512])[3] < 5 * sorted(us[256])[3], us
