@@ -37,6 +37,8 @@
 // gate resident 112.8 -> 108.5.
 #pragma once
 
+#include <cstddef>
+
 #include "lif_ffn.h"
 #include "lif_ffn_mfma.h"
 #include "lif_predict.h"
@@ -337,16 +339,6 @@ constexpr int kNoDst = 0xffff;       // dead tail slot (a hole lies below n' <= 
 constexpr int kHoleFew = 2048;       // holes kept in LDS; longer lists go to the global scratch list
 struct PlanLds {
     unsigned long long rem[1024], add[1024]; // removed and added neurons, one bit each
-    union {
-        PredictLds predict;                  // only when a wait ran out
-        struct {
-            uint16_t ids[kListItems];        // loaders: the new neurons of the work items
-            uint16_t hole[kHoleFew];         // bookkeeping: the deletion plan
-            uint16_t fill_before[1024];      // fillers below the granule
-            uint16_t ptr[kPtrLds];           // owners (neurons are numbers below 65536)
-            unsigned long long dead[1024];   // dead slots of the block
-        };
-    };
     unsigned long long wave_tot[4];
     int cnt_age[264];
     unsigned byte[4];
@@ -354,7 +346,21 @@ struct PlanLds {
     unsigned long long first_bits;           // the neuron of the loader's first unit: bit number first_at.y of these that is
     int2 first_at;                           //  set, from neuron first_at.x on
     int listed;                              // waves that have written their part of ids
+    union {
+        PredictLds predict;                  // only when a wait ran out
+        uint16_t ids[kListItems];            // loaders: the new neurons of the work items
+        struct {                             // bookkeeping: the deletion plan
+            uint16_t hole[kHoleFew];
+            uint16_t fill_before[1024];      // fillers below the granule
+            uint16_t ptr[kPtrLds];           // owners (neurons are numbers below 65536)
+            unsigned long long dead[1024];   // dead slots of the block
+        };
+    };
 };
+// What a loader uses of it in a batched step.  The rest of a loader's LDS (PostLds, x, rows) lies where the deletion plan of the bookkeeping
+// workgroup does: all workgroups of the launch carry the same LDS, and behind the whole plan x left room for one of them
+// per compute unit instead of two.
+constexpr size_t kLoaderPlanLds = (offsetof(PlanLds, ids) + sizeof(uint16_t) * kListItems + 15) / 16 * 16;
 
 // All mask words computed by this workgroup alone (a wait that ran out): m[i] of the words this thread owns
 template <typename T, int NI, bool GATE>
@@ -421,7 +427,7 @@ __device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt
 // range are dealt to the waves).  One wave alone took 6 us per bundle of 24 KiB and 8 tokens, as long as the link.
 enum StepMode { kOneToken = 0, kDots = 1, kMfma = 2 };
 
-// LDS behind PlanLds: PostLds, x of the tokens, the activation vectors of `stage_rows` rows
+// LDS of a loader behind its part of PlanLds: PostLds, x of the tokens, the activation vectors of `stage_rows` rows
 struct Slot {                                                // a row that was written
     int s, id;
     float bias;
@@ -433,7 +439,7 @@ struct PostLds {
     float gate[2][8];                                        // resident gate activations, per token
     alignas(16) float sums[8][16][4];                        // kMfma: sums of parts 2 g and 2 g + 1, per token and vector
 };
-constexpr int kStepXOff = (int)((sizeof(PlanLds) + 15) / 16 * 16 + (sizeof(PostLds) + 15) / 16 * 16);
+constexpr int kStepXOff = (int)(kLoaderPlanLds + (sizeof(PostLds) + 15) / 16 * 16);
 __host__ __device__ __forceinline__ int step_x_pitch(int d, int elem) { return d * elem + 16; }     // (16: the reads of 16 tokens
                                                                                                      //  fall on different banks)
 template <typename T, int NI, bool GLU, bool GATE, int MODE>
@@ -720,7 +726,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     if (wave == 0) L.off[lane] = off_a;
     if (tid == 0) L.listed = 0;
     if constexpr (MODE != kOneToken)
-        if (tid == 0) post->seq = post->done = post->arrived = 0;
+        if (wg > 0 && tid == 0) post->seq = post->done = post->arrived = 0;
     lds_barrier();
 
     if (wg == 0) {
@@ -1271,7 +1277,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_step_batch(const StepArgs a) 
     if (block <= a.n_load) {
         if (WAVES > 4 && threadIdx.x >= 256) return;             // (a barrier waits for the waves that are left)
         PlanLds& plan = *reinterpret_cast<PlanLds*>(smem_step);
-        PostLds* post = reinterpret_cast<PostLds*>(smem_step + (sizeof(PlanLds) + 15) / 16 * 16);
+        PostLds* post = reinterpret_cast<PostLds*>(smem_step + kLoaderPlanLds);
         cache_role<T, NI, GLU, GATE, MFMA ? kMfma : kDots>(a, block, plan, post, smem_step + kStepXOff);
     } else if constexpr (MFMA) {
         const int tile = block - a.n_load - 1;
@@ -1289,7 +1295,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_step_batch(const StepArgs a) 
 inline size_t step_batch_lds(int batch, int d, int elem, bool glu, bool mfma, int rows) {
     const size_t loader = kStepXOff + (size_t)batch * step_x_pitch(d, elem) + (size_t)rows * (glu ? 2 : 1) * step_x_pitch(d, elem);
     const size_t up = mfma ? (size_t)mfma_staged_lds(glu, kMfmaWaves) : (size_t)batch * d * elem;
-    return loader > up ? loader : up;
+    const size_t most = loader > up ? loader : up;
+    return most > sizeof(PlanLds) ? most : sizeof(PlanLds);          // (the bookkeeping workgroup)
 }
 constexpr size_t kStepLdsLimit = 160 * 1024;
 
@@ -1309,16 +1316,17 @@ inline void launch_step1_as(const StepArgs& a, int grid, hipStream_t s) {
     else LIF_S1(16);
 #undef LIF_S1
 }
-// Waves of a workgroup of k_step_batch: 4, or 8 where the LDS of a loader (x of the tokens and staged rows) leaves room for one
-// workgroup per compute unit.  The activation workgroups of the launch carry the same LDS, and four waves that read a row each
+// Waves of a workgroup of k_step_batch: 4, or 8 where the LDS of a loader (x of the tokens and staged rows) leaves room for fewer than
+// three of them per compute unit.  The activation workgroups of the launch carry the same LDS, and four waves that read a row each
 // reach a fraction of the bandwidth, which shows where few rows are added and the load does not cover them.  fp32 rows, us a
 // step with 4 -> 8 waves (rows in use, rows added): d = 1288, 8 tokens: (9277, 0) 77.7 -> 57.0, (9578, 47) 88.3 -> 71.2, (13408,
 // 477) 157.8 -> 156.9; d = 2048, gated, 8 tokens: (4699, 0) 71.8 -> 55.1, (6444, 304) 187.8 -> 187.1; d = 2048, 4 tokens: (6221,
-// 0) 51.9 -> 43.2.  With room for two workgroups four waves are better (d = 1288, 3 tokens, (929, 0): 25.7 against 26.6).
+// 0) 51.9 -> 43.2.  With room for three workgroups four waves are better (d = 1288, 3 tokens, (929, 0): 25.7 against 26.6),
+// with room for two eight in one (d = 1288, 8 tokens, (8614, 0): 60.9 against 62.5; d = 2048, 4 tokens, (7235, 0): 49.8 against 50.7).
 // The matrix-core stage keeps 4: it is at least as fast as in a launch of its own.  Gated rows of more than 12 KiB a vector
 // would spill registers at 8 waves.
 constexpr int step_batch_most_waves(int ni, bool glu, bool mfma) { return mfma || ni <= 2 || (glu && ni > 12) ? 4 : 8; }
-inline int step_batch_waves(int ni, bool glu, bool mfma, size_t lds) { return lds > kStepLdsLimit / 2 ? step_batch_most_waves(ni, glu, mfma) : 4; }
+inline int step_batch_waves(int ni, bool glu, bool mfma, size_t lds) { return lds > kStepLdsLimit / 3 ? step_batch_most_waves(ni, glu, mfma) : 4; }
 
 // (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that, for the kernels of a.d)
 template <typename T, bool GLU, bool GATE, bool MFMA>

@@ -93,6 +93,19 @@ def child_step_mask(lib):
     return got
 
 
+def child_step_lds(lib):
+    """Dynamic LDS of the batched step, by shape"""
+    got = {}
+    for d, batch, glu, f16 in ((4096, 2, 0, True), (2048, 5, 0, True), (2048, 6, 0, True), (2560, 4, 0, True), (1536, 7, 0, True),
+                               (1536, 8, 0, True), (4096, 1, 1, True), (1024, 2, 0, False)):
+        h = lib.layer(d, max_batch=max(batch, 2), glu=glu, f16=f16)
+        rc, seen = lib.step(h, max(batch, 2))
+        assert rc == 0
+        got["d %d, %d tokens%s" % (d, max(batch, 2), ", gated" if glu else "")] = max(k[3] for k in seen if "k_step_batch" in k[0])
+        lib.lib.lif_destroy(h)
+    return got
+
+
 def _run(tmp_path_factory, what):
     stub = str(tmp_path_factory.getbasetemp() / "hip_host_stub.so")
     if not os.path.exists(stub):
@@ -114,6 +127,13 @@ def child(tmp_path_factory):
 def test_lds_of_every_launch_is_allowed(child):
     """A launch with more than 64 KiB of LDS needs the limit of its own kernel form raised (lif_create)."""
     assert child("lds") > 0
+
+
+def test_two_workgroups_of_a_batched_step_per_compute_unit(child):
+    """Every workgroup of the launch carries the same LDS: what the bookkeeping workgroup needs for the deletion plan must not come on
+    top of the x and rows of a loader."""
+    for shape, lds in child("step_lds").items():
+        assert 0 < lds <= LDS_MOST // 2, (shape, lds)
 
 
 def test_step_mask_of_a_pass_may_have_any_address(child):
