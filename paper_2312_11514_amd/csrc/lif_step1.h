@@ -14,7 +14,8 @@
 //                                 waiting for one that does), gather bundles from pinned host memory, move the rows they
 //                                 overwrite where the plan says and compute the activations of the rows they write (h_new,
 //                                 stamped with the step)
-//   the rest                      activations of the rows that were already in use; they begin when the predictor is done
+//   the rest                      activations of the rows that were already in use; behind the predictor where a load is
+//                                 likely to hide them (await_predictor), else at once
 // A value handed over is a 64-bit word: 32 bits of payload and the number of the step as a stamp, written by a relaxed
 // device-scope atomic store and polled with relaxed device-scope atomic loads, so no fence (a device-scope release
 // writes back the L2: 6 us) and no clearing is needed.  Stamps are unique between two resets, which clear the words.
@@ -1236,11 +1237,21 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
 // reads the host link waits for (x A published 3.9 to 6.2 us after the launch began instead of 2.2, Falcon and Llama-2 shapes).  So
 // its waves begin when a mask word has been published, or after kActWaits reads of it at the latest.
 constexpr int kActWaits = 64;
+// ... but only where the load that follows is likely to take longer than they do, which the last step tells: bundles of `vectors` vectors at
+// the rate of the link against all but the down vector of the rows in use at kLinkSlower times that rate.  (Else a step that adds
+// nothing waits for nothing and reads then.)  d = 4096, us a step at once / behind the predictor, (rows in use, added): (3414, 0)
+// 31.2 / 37.0, (3504, 13) 36.1 / 37.7, (3617, 16) 41.1 / 39.4, (3812, 40) 48.3 / 44.1; gated (3217, 0) 33.9 / 41.0, (3343, 8) 39.3 / 42.8.
+constexpr int kLinkSlower = 128;
+__host__ __device__ __forceinline__ bool load_hides_activations(int added, int in_use, int vectors) {
+    return added * vectors * kLinkSlower >= in_use * (vectors - 1);
+}
+template <int VECTORS>
 __device__ __forceinline__ void await_predictor(const StepArgs& a, int block) {
     const int words = 2 * ((a.F + 63) >> 6);
     const unsigned long long* p = a.m_words + (size_t)(block & (kWordReps - 1)) * a.m_pitch + (unsigned)block % (unsigned)words;
-    if (a.st->cur.error || a.polls == 0) return;
-    const unsigned now = (unsigned)a.st->cur.step + 1u;
+    const StepCounts& cur = a.st->cur;
+    if (cur.error || a.polls == 0 || !load_hides_activations(cur.n_added, cur.num_used, VECTORS)) return;
+    const unsigned now = (unsigned)cur.step + 1u;
     __builtin_amdgcn_s_sleep(127);
     for (int tries = min(kActWaits, a.polls); tries > 0 && (unsigned)(word_load(p) >> 32) != now; --tries) __builtin_amdgcn_s_sleep(32);
     __builtin_amdgcn_s_sleep(40);
@@ -1257,7 +1268,7 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
         cache_role<T, NI, GLU, GATE, kOneToken>(a, block - a.n_pred, *reinterpret_cast<PlanLds*>(lds), nullptr, nullptr);
     } else {
         const int first = a.n_pred + a.n_load + 1;
-        await_predictor(a, block);
+        await_predictor<GLU ? 3 : 2>(a, block);
         ffn_up_role<T, NI, GLU, true>((const T*)a.matrix, a.bias, (const T*)a.x, a.h, a.d, 1, a.capacity, a.row_elems, a.spec,
                                       block - first, gridDim.x - first, a.pointers, a.gact, a.F, a.st);
     }
