@@ -98,6 +98,15 @@ bool config_ok(const lif_config* c, const char** why) {
     return true;
 }
 
+// column slices of the down projection of one token: whole runs of them per XCD
+int down1_slices(const lif_config& c) {
+    const int cols = kDown1Lanes * vec_elems(c);
+    return ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;
+}
+
+// whether calls on the layer can take the single-launch FFN (ffn_one), so that it has words to hand over
+bool ffn_one_possible(const lif_config& c) { return c.capacity_rows <= kOneCapacity && down1_slices(c) <= kOneSlices; }
+
 Layout make_layout(const lif_config& c) {
     Layout L;
     size_t off = 0;
@@ -107,7 +116,7 @@ Layout make_layout(const lif_config& c) {
     off = off + sizeof(uint64_t) * kWordReps * ((size_t)words_pitch(2 * std::max(c.rank, 0)) + words_pitch(2 * ring_words(c)));
     off = off + sizeof(uint64_t) * c.capacity_rows;               // ... and the deletion plan;
     L.one = off;                       // inside a single-launch FFN, and its launch number
-    if (c.capacity_rows <= kOneCapacity) off = off + sizeof(uint64_t) * kOneReps * one_pitch(c.capacity_rows) + sizeof(OneState);
+    if (ffn_one_possible(c)) off = off + sizeof(uint64_t) * kOneReps * one_pitch(c.capacity_rows) + sizeof(OneState);
     L.ring = off;                      // window_k step masks, each padded to whole 64-bit words
     off = off + (size_t)(c.window_k + 2) * ring_words(c) * 8;     // ... directly followed by the two bitmaps of the cached set
     L.reset_words = (int)((off - L.words) / 8);
@@ -156,7 +165,7 @@ struct lif_layer {
     int32_t* ptr_new;
     float* bias_new;
     unsigned long long* words;
-    unsigned long long* one_words;  // of k_ffn_one, null where the cache has too many slots
+    unsigned long long* one_words;  // of k_ffn_one, null where it is never launched
     OneState* one;
     int polls;                  // failed polls of a hand-over word before a workgroup computes the value itself
     float* gact;                // null unless the gate projection is the predictor
@@ -299,12 +308,6 @@ FusedRows fused_rows(const lif_layer* L, const FusedCall& f) {
     return r;
 }
 
-// column slices of the down projection of one token: whole runs of them per XCD
-int down1_slices(const lif_config& c) {
-    const int cols = kDown1Lanes * vec_elems(c);
-    return ((c.d_model + cols - 1) / cols + kXcds - 1) / kXcds * kXcds;
-}
-
 // one token
 template <typename T, bool SKIP>
 void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t s, const FusedCall& fc) {
@@ -423,7 +426,7 @@ void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, h
 // alone, so they stay with two.
 bool ffn_one(const lif_layer* L, int batch) {
     const int rows = geometry_rows(L), slices = down1_slices(L->cfg);
-    return batch == 1 && L->one_words && slices <= kOneSlices && rows <= kOneRows && slices * rows <= kOneWords;
+    return batch == 1 && L->one_words && rows <= kOneRows && slices * rows <= kOneWords;
 }
 template <typename T, bool GLU, bool SKIP>
 void launch_ffn_one(lif_layer* L, const void* x, void* y, hipStream_t s) {
@@ -720,7 +723,7 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
     L->ptr_new = (int32_t*)(ws + lay.ptr_new);
     L->bias_new = (float*)(ws + lay.bias_new);
     L->words = (unsigned long long*)(ws + lay.words);
-    L->one_words = cfg->capacity_rows <= kOneCapacity ? (unsigned long long*)(ws + lay.one) : nullptr;
+    L->one_words = ffn_one_possible(*cfg) ? (unsigned long long*)(ws + lay.one) : nullptr;
     L->one = L->one_words ? (OneState*)(L->one_words + kOneReps * one_pitch(cfg->capacity_rows)) : nullptr;
     L->polls = kDefaultPolls;
     L->gact = cfg->predictor == LIF_PRED_GATE ? (float*)(ws + lay.gact) : nullptr;

@@ -106,6 +106,20 @@ def child_step_lds(lib):
     return got
 
 
+def child_one_words(lib):
+    """Bytes of workspace and workgroups of a reset, by width and capacity"""
+    got = {}
+    for d in (2048, 2056, 4096):
+        for capacity in (8192, 16384, 24576):
+            h = lib.layer(d, capacity=capacity)
+            cfg = lib.b.LifConfig(d, 1024, 16, 3, capacity, 1, 0, lib.b.LIF_F16, 0, 0, 0, 0.0)
+            rc, seen = lib.launches(lambda: lib.lib.lif_reset(h, None))
+            assert rc == 0 and len(seen) == 1
+            got["%d %d" % (d, capacity)] = [lib.lib.lif_workspace_bytes(C.byref(cfg)), seen[0][1]]
+            lib.lib.lif_destroy(h)
+    return got
+
+
 def _run(tmp_path_factory, what):
     stub = str(tmp_path_factory.getbasetemp() / "hip_host_stub.so")
     if not os.path.exists(stub):
@@ -143,6 +157,18 @@ def test_step_mask_of_a_pass_may_have_any_address(child):
         by_words = any("k_step_batch" in k for k in kernels)
         assert by_words == (int(case.split()[0]) % 8 == 0), (case, kernels)
         assert by_words or [n for n in ("window_plan", "k_load", "ffn_up", "ffn_down") if not any(n in k for k in kernels)] == []
+
+
+def test_words_of_the_single_launch_ffn_only_where_it_is_launched(child):
+    """Four copies of a word for every slot, cleared by every reset: for at most 64 column slices (d = 2048 in fp16) and 16384 slots."""
+    got = child("one_words")
+    for d in (2048, 2056, 4096):
+        (less, _), (most, reset), (more, _) = (got["%d %d" % (d, c)] for c in (8192, 16384, 24576))
+        extra = (most - less) - (more - most)       # over what grows with every slot
+        if d <= 2048:
+            assert extra >= 4 * 8 * 16384
+        else:
+            assert abs(extra) < 4096 and reset <= (16384 + 8192) // 256, (d, extra, reset)
 
 
 if __name__ == "__main__":
