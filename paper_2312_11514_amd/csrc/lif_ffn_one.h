@@ -24,8 +24,16 @@ constexpr int kOneReps = 4;                          // copies of every word
 constexpr int kOneSlices = 64, kOneWords = 16384;    // column slices, and words read by all of them, up to which this form is taken
 constexpr int kOneRows = kDown1FewRows;              // ... and rows: one pass of 8 waves
 constexpr int kOneCapacity = 16384;                  // (there is a word for every slot)
-constexpr int kOneWaits = 1 << 20;                   // reads before a launch whose waits ran out is given up: about a second
+constexpr int kOneWaits = 1 << 20;                   // reads of a thread before a launch whose waits ran out is given up: about a second
 __host__ __device__ __forceinline__ size_t one_pitch(int capacity) { return (size_t)words_pitch(capacity); }
+// Looks at the slots first, first + stride, ... below n until each is there, or for `waits` failed looks in all; returns whether all are.
+template <typename There>
+__host__ __device__ __forceinline__ bool await_slots(int first, int n, int stride, int waits, There there) {
+    for (int s = first; s < n; s += stride)
+        while (!there(s))
+            if (--waits <= 0) return false;
+    return true;
+}
 struct OneState {
     unsigned number, counted;                        // of the last launch; down workgroups of this one so far
 };
@@ -93,13 +101,12 @@ __global__ __launch_bounds__(kOneWaves * 64, 2) void k_ffn_one(const T* __restri
     __syncthreads();
     if (!last) return;                               // uniform
     // (the activation role must have read the number before it changes; every wave of it that has rows has published a word)
-    bool there = true;
     if (__builtin_expect(lost, 0)) {
-        for (int s = tid; s < st->cur.num_used; s += kOneWaves * 64) {
-            int tries = 0;
-            while ((unsigned)(word_load(mine + s) >> 32) != now && ++tries < kOneWaits) __builtin_amdgcn_s_sleep(8);
-            there = there && tries < kOneWaits;
-        }
+        const bool there = await_slots(tid, st->cur.num_used, kOneWaves * 64, kOneWaits, [&](int s) {
+            const bool ok = (unsigned)(word_load(mine + s) >> 32) == now;
+            if (!ok) __builtin_amdgcn_s_sleep(8);
+            return ok;
+        });
         if (!there) st->cur.error = 4;               // LIF_HIP_ERROR
         __syncthreads();
     }

@@ -1,4 +1,4 @@
-"""Rules of the single-launch step that decide how fast it is and nothing else, as the header has them: compiled for the host."""
+"""Rules and bounds of the single launches that run on the device, as the headers have them: compiled for the host."""
 import os
 import shutil
 import subprocess
@@ -15,22 +15,39 @@ def rule(tmp_path_factory):
         pytest.skip("no hipcc")
     at = tmp_path_factory.mktemp("rules")
     (at / "rules.hip").write_text("""#include "lif_step1.h"
+#include "lif_ffn_one.h"
 #include <cstdio>
+#include <cstring>
 int main() {
-    int a, n, v;
-    while (scanf("%d %d %d", &a, &n, &v) == 3) printf("%d\\n", (int)lif::load_hides_activations(a, n, v));
+    char what[16];
+    int a, b, c;
+    while (scanf("%15s %d %d %d", what, &a, &b, &c) == 4) {
+        if (!strcmp(what, "hides")) printf("%d\\n", (int)lif::load_hides_activations(a, b, c));
+        if (!strcmp(what, "await")) {           // b slots, the first c of them there, by thread a of 512: looks, and the answer
+            int looks = 0;
+            const bool all = lif::await_slots(a, b, 512, 1000, [&](int s) { ++looks; return s < c; });
+            printf("%d\\n", all ? looks : -looks);
+        }
+    }
 }
 """)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-I", CSRC, "-o", str(at / "rules"), str(at / "rules.hip")], check=True,
                    capture_output=True)
 
-    def run(*cases):
-        text = "\n".join("%d %d %d" % c for c in cases)
+    def run(what, *cases):
+        text = "\n".join("%s %d %d %d" % ((what,) + c) for c in cases)
         return [int(l) for l in subprocess.run([str(at / "rules")], input=text, capture_output=True, text=True, check=True).stdout.split()]
     return run
 
 
 def test_activations_wait_for_the_predictor_only_behind_a_load(rule):
     """(rows added by the last step, rows in use, vectors of a bundle)"""
-    assert rule((0, 3414, 2), (0, 3217, 3), (0, 1, 2), (13, 3504, 2), (8, 3343, 3), (1, 65536, 2)) == [0] * 6      # begin at once
-    assert rule((0, 0, 2), (143, 975, 2), (489, 3246, 2), (210, 1961, 3), (40, 3812, 2), (19, 3524, 3), (65536, 65536, 3)) == [1] * 7
+    assert rule("hides", (0, 3414, 2), (0, 3217, 3), (0, 1, 2), (13, 3504, 2), (8, 3343, 3), (1, 65536, 2)) == [0] * 6      # begin at once
+    assert rule("hides", (0, 0, 2), (143, 975, 2), (489, 3246, 2), (210, 1961, 3), (40, 3812, 2), (19, 3524, 3), (65536, 65536, 3)) == [1] * 7
+
+
+def test_a_lost_wait_is_bounded_over_all_slots_of_a_thread(rule):
+    """The last workgroup of a single-launch FFN looks for the words of all slots, up to 32 of them a thread, before it gives the launch up:
+    the bound is one for the thread, not one a slot."""
+    assert rule("await", (0, 16384, 16384), (5, 0, 0), (511, 513, 0)) == [32, 0, -1000]      # all there; none to look for; the first is missing
+    assert rule("await", (0, 16384, 8192), (3, 16384, 15000), (3, 16384, 0)) == [-1016, -1030, -1000]
