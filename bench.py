@@ -91,6 +91,13 @@ def cpu_baseline(w, L, X, budget_s=20.0):
     return out
 
 
+def ffn_kernels(lay, x, y, batch):
+    """What one lif_sparse_ffn call on the layer launches: two stages, or (few narrow rows, one token) one launch."""
+    lay.profile_begin(4)
+    lay.sparse_ffn(x, y, batch)
+    return "%s (one lif_sparse_ffn call)" % ("ffn_up + ffn_down" if lay.profile_collect()["ffn_up"][1] else "ffn_one")
+
+
 def pmc_traffic(pmc_dir):
     """HBM-side bytes per lif_sparse_ffn call from two rocprofv3 --pmc runs of this script (FETCH_SIZE, WRITE_SIZE),
     each scaled by what the same counter reported for the 256 MiB device copy of --pmc-copy.  Expects
@@ -107,14 +114,14 @@ def pmc_traffic(pmc_dir):
         if not copies or max(copies) <= 0:
             return None
         scale = 262144.0 / max(copies)                       # reported KiB -> true KiB (the copy moves 256 MiB each way)
-        # one lif_sparse_ffn call = a k_ffn_up dispatch and the k_ffn_down (+ finish) dispatches right after it
-        # (lif_step never launches k_ffn_up on its own, so these are exactly the FFN-only calls)
+        # one lif_sparse_ffn call = a k_ffn_one dispatch, or a k_ffn_up dispatch and the k_ffn_down (+ finish) dispatches right
+        # after it (lif_step never launches k_ffn_one or k_ffn_up, so these are exactly the FFN-only calls)
         rows.sort(key=lambda r: int(r["Dispatch_Id"]))
         calls, total, open_call = 0, 0.0, False
         for r in rows:
             name = r["Kernel_Name"]
-            if "k_ffn_up" in name:
-                calls, open_call = calls + 1, True
+            if "k_ffn_up" in name or "k_ffn_one" in name:
+                calls, open_call = calls + 1, "k_ffn_up" in name
                 total += float(r["Counter_Value"])
             elif open_call and "k_ffn_down" in name:
                 total += float(r["Counter_Value"])
@@ -562,6 +569,7 @@ def bench_stacked(w, base, mode, steps, warmup, no_graph=False, hint=True, ffn_r
         ms = _timed_replays(g2, 5)
         c1 = [lay.counters() for lay in layers]
         calls = sum(b["ffn_calls"] - a["ffn_calls"] for a, b in zip(c0, c1))
+        res["ffn_kernels"] = ffn_kernels(layers[0], x_last, y_stage[0], w.batch)
         res["ffn"] = {"us": ms * 1e3 / calls,
                       "rows": sum(b["ffn_rows"] - a["ffn_rows"] for a, b in zip(c0, c1)) / calls,
                       "active": sum(b["ffn_active"] - a["ffn_active"] for a, b in zip(c0, c1)) / calls}
@@ -651,7 +659,7 @@ def main():
         X = np.stack([X[p * w.spec_keep:p * w.spec_keep + w.batch] for p in range(n_pass)])
     T = len(X)
 
-    steady = ffn_states = ffn_cold = floor = breakdown = None
+    steady = ffn_states = ffn_cold = floor = breakdown = kernel_name = None
     kern, kern_load = {}, None
     ffn = None
     if NL > 1:
@@ -660,6 +668,7 @@ def main():
         ms_per_step, us_per_token_layer = r["ms_per_step"], r["us_per_token_layer"]
         rows_per_call, active_per_call, added_per_call = r["rows_per_call"], r["active_per_call"], r["added_per_call"]
         window_len_end, launch, ffn, kern = r["window_len_end"], r["launch"], r["ffn"], r["kern"]
+        kernel_name = r.get("ffn_kernels")
         h2d_ref = None
     else:
         progress("uploading layer 0")
@@ -767,6 +776,7 @@ def main():
             # stream around every kernel (these include ~2 us of event/dispatch overhead per launch); first the
             # lif_step path that `value` times, then the four separate calls for the paper's three cost columns
             progress("event-timed passes")
+            kernel_name = ffn_kernels(lay0, xd[0], gpu0.y, w.batch)
             for calls in (False, True):
                 lay0.profile_begin(7 * T + 8)
                 lay0.reset()
@@ -810,7 +820,6 @@ def main():
         "end_to_end_us_per_token": us_per_token_layer * NL,
         "h2d_bytes_per_token": added_per_call * w.bundle_bytes * NL,
     }
-    kernel_name = "ffn_up + ffn_down (one lif_sparse_ffn call)"
     if ffn_states:
         us = [f["avg_launch_us"] for f in ffn_states]
         tot_b = sum(f["algorithmic_bytes_per_launch"] for f in ffn_states)

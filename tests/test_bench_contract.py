@@ -25,3 +25,23 @@ def test_bench_never_reaches_the_oracle_outside_its_cpu_baseline_leg():
         if name.endswith(".py"):
             text = open(os.path.join(ROOT, "workloads", name)).read()
             assert "import oracle" not in text and "from oracle" not in text, name
+
+
+def test_traffic_counts_every_form_of_an_ffn_call(tmp_path):
+    """The counter files of a run that has FFN calls of two stages, with and without the finish kernel, and of a single launch, between
+    steps: the copy of 256 MiB is reported as half, so everything counts double."""
+    sys.path.insert(0, ROOT)
+    import bench
+    kernels = ["__amd_rocclr_copyBuffer", "k_step1", "k_ffn_down1", "k_ffn_up", "k_ffn_down1", "k_ffn_one", "k_ffn_up", "k_ffn_down",
+               "k_ffn_down_finish", "k_ffn_one", "k_ffn_one", "k_predict_xa", "k_ffn_down1"]
+    kib = [131072, 1000, 1000, 8, 2, 5, 16, 3, 1, 6, 9, 1000, 1000]
+    for counter in ("FETCH_SIZE", "WRITE_SIZE"):
+        d = tmp_path / ("pmc_" + counter)
+        d.mkdir()
+        lines = ["Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value"]
+        lines += ["%d,void lif::%s(args),%s,%d" % (i, k, counter, v) for i, (k, v) in enumerate(zip(kernels, kib))]
+        (d / "run_counter_collection.csv").write_text("\n".join(lines) + "\n")
+    got = bench.pmc_traffic(str(tmp_path))
+    for counter in ("FETCH_SIZE", "WRITE_SIZE"):
+        assert got[counter]["calls"] == 5
+        assert got[counter]["bytes_per_call"] == 2 * 1024 * (8 + 2 + 5 + 16 + 3 + 1 + 6 + 9) / 5
