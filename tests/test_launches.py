@@ -120,11 +120,26 @@ def child_one_words(lib):
     return got
 
 
-def _run(tmp_path_factory, what):
+def child_ffn_one(lib, cases):
+    """Kernels of one lif_sparse_ffn call of one token, by row-count hint"""
+    got = {}
+    for name, (dtype, glu, gate, full, d, F, _, capacity, hints) in cases.items():
+        h = lib.layer(d, F=F, rank=8, k=2, capacity=capacity, glu=glu, f16=dtype == "f16", gate=gate, full=full)
+        for hint in [0] + hints:
+            assert lib.lib.lif_set_expected_rows(h, hint) == 0
+            for call in (lib.lib.lif_sparse_ffn, lib.lib.lif_sparse_ffn_static):
+                rc, seen = lib.launches(lambda: call(h, lib.p, 1, lib.p, None))
+                assert rc == 0
+                got["%s %d %s" % (name, hint, call.__name__)] = [k[0] for k in seen]
+        lib.lib.lif_destroy(h)
+    return got
+
+
+def _run(tmp_path_factory, what, *args):
     stub = str(tmp_path_factory.getbasetemp() / "hip_host_stub.so")
     if not os.path.exists(stub):
         subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", stub, os.path.join(HERE, "hip_host_stub.cpp")], check=True)
-    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, what], capture_output=True, text=True, timeout=300)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, what] + [json.dumps(a) for a in args], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
     return json.loads(r.stdout.splitlines()[-1])
 
@@ -135,7 +150,7 @@ def child(tmp_path_factory):
     if not os.path.exists(binding.LIB_PATH):
         from paper_2312_11514_amd.build import build_library
         build_library()
-    return lambda what: _run(tmp_path_factory, what)
+    return lambda what, *args: _run(tmp_path_factory, what, *args)
 
 
 def test_lds_of_every_launch_is_allowed(child):
@@ -171,5 +186,17 @@ def test_words_of_the_single_launch_ffn_only_where_it_is_launched(child):
             assert abs(extra) < 4096 and reset <= (16384 + 8192) // 256, (d, extra, reset)
 
 
+def test_single_launch_ffn_is_compared_with_two_launches(child):
+    """tests/test_ffn_one.py compares what it says: its hints take the single launch, and no hint (the capacity) two."""
+    from tests.test_ffn_one import CASES
+    got = child("ffn_one", CASES)
+    assert len(got) == sum(2 + 2 * len(c[-1]) for c in CASES.values())
+    for case, kernels in got.items():
+        if case.split()[1] == "0":
+            assert "k_ffn_up" in kernels[0] and "k_ffn_down" in kernels[1], (case, kernels)
+        else:
+            assert len(kernels) == 1 and "k_ffn_one" in kernels[0], (case, kernels)
+
+
 if __name__ == "__main__":
-    print(json.dumps(globals()["child_" + sys.argv[2]](Library(sys.argv[1]))))
+    print(json.dumps(globals()["child_" + sys.argv[2]](Library(sys.argv[1]), *map(json.loads, sys.argv[3:]))))
