@@ -23,8 +23,9 @@
  *     bundle (up row | down column), G = 3 for gated layers (gate row | up row | down column).
  *   - Shape limits: d_model, rank multiples of 8 (fp16) or 4 (fp32); d_ffn a multiple
  *     of 8 and at most 65536; rank at most 2048; max_batch at most 8; window_k at most 256.
- *   - A device-detected error (capacity overflow) sets a sticky flag: until lif_reset
- *     every hot call becomes a no-op on the device; lif_get_state reports the flag.
+ *   - A device-detected error (capacity overflow, or a lost launch: see lif_state.error) sets a
+ *     sticky flag: until lif_reset every hot call becomes a no-op on the device; lif_get_state
+ *     reports the flag.
  *   - Calls on one handle must not overlap (one stream at a time).
  */
 #ifndef LIF_H
@@ -44,7 +45,7 @@ enum lif_status {
     LIF_INVALID_ARG = 1,   /* null pointer, unsupported shape, batch > max_batch */
     LIF_BAD_STATE = 2,     /* calls out of order (see lif_update_window / lif_load_bundles) */
     LIF_CAPACITY = 3,      /* reported by lif_get_state: active set exceeded capacity_rows */
-    LIF_HIP_ERROR = 4      /* a HIP runtime call failed; see lif_last_error_string */
+    LIF_HIP_ERROR = 4      /* a HIP runtime call failed; see lif_last_error_string (lif_state.error: a lost launch) */
 };
 
 enum lif_dtype { LIF_F32 = 0, LIF_F16 = 1 };
@@ -115,7 +116,9 @@ typedef struct lif_buffers {
 typedef struct lif_state {
     int32_t num_used;       /* rows of the cache in use                                   */
     int32_t step;           /* number of completed lif_update_window calls since reset    */
-    int32_t error;          /* LIF_OK or LIF_CAPACITY (sticky until lif_reset)            */
+    int32_t error;          /* LIF_OK, LIF_CAPACITY or LIF_HIP_ERROR, sticky until lif_reset.  LIF_HIP_ERROR: workgroups of
+                             * a lif_sparse_ffn call of one launch did not run for about a second while others of it
+                             * waited for them.  That call's y is complete; later calls do nothing                */
     int32_t last_added;     /* |added| of the last lif_update_window                      */
     int32_t last_removed;   /* |removed| of the last lif_update_window                    */
     int32_t last_moved;     /* rows moved by the last deletion                            */
@@ -251,9 +254,9 @@ int lif_sparse_ffn(lif_layer* layer, const void* x_dev, int32_t batch, void* y_d
  * lif_sparse_ffn for callers that cannot allocate and want no scratch of their own in the call: code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation.  Same arguments, same arithmetic
  * and bit-identical results; the activations and the partial outputs of the call (the scratch that
- * lif_sparse_ffn keeps in the layer's workspace if it takes more than one launch) live in a static device array inside the library instead, of
- * lif_static_scratch_bytes() = 5 MiB, which every GPU the library runs on holds until the process ends.  The call
- * allocates nothing and frees nothing.
+ * lif_sparse_ffn keeps in the layer's workspace if it takes more than one launch) live in a static device array
+ * inside the library instead, of lif_static_scratch_bytes() = 5 MiB, which every GPU the library runs on holds until
+ * the process ends.  The call allocates nothing and frees nothing.
  *   limit   256-byte-rounded 4 * batch * capacity_rows  +  4 * 32 * batch * d_model  <=  lif_static_scratch_bytes()
  *           (batch 8 at d_model 4096 fits up to 32768 rows, a single token at any shape); beyond it LIF_INVALID_ARG,
  *           nothing is launched
@@ -313,8 +316,8 @@ int lif_set_loader_pairs(lif_layer* layer, int32_t pairs);
 
 /*
  * Performance knob of the single-token lif_step and lif_sparse_ffn: workgroups of one launch hand values over to each
- * other, and a workgroup that has polled for a value this often without success computes it itself (0: it never waits).  Results
- * never depend on it.
+ * other, and a workgroup that has polled for a value this often without success computes it itself (0: it never
+ * waits).  Results never depend on it.
  */
 int lif_set_handoff_polls(lif_layer* layer, int32_t polls);
 

@@ -13,7 +13,7 @@ struct StepCounts {
     int32_t num_used;     // rows of the cache in use (Section 3.3 "num_used")
     int32_t n_base;       // rows kept after the pending deletion (n' = num_used - c)
     int32_t step;         // completed window updates
-    int32_t error;        // sticky lif_status (0 or LIF_CAPACITY)
+    int32_t error;        // sticky lif_status (0, LIF_CAPACITY, or LIF_HIP_ERROR: k_ffn_one)
     int32_t n_added;      // |added| of the pending / last update
     int32_t n_removed;    // |removed| of the pending / last update
     int32_t n_moved;      // rows moved by the last deletion
