@@ -98,7 +98,7 @@ __device__ __forceinline__ int fold_owner(int lane) { return ((lane >> 3) & 1) *
 // logits = t B + c, threshold, 64 mask bits at a time; step mask = OR over the batch.
 // grid = ceil(F / 64), block = 256 = 32 rank groups x 8 column lanes; a column lane owns 8 consecutive neurons.  A thread adds its ranks
 // jg, jg + 32, ... in that order, then come the rank groups of a wave (fold_groups), then the waves: the one order of a logit, which
-// MaskTile in k_step1 keeps too.
+// MaskTile in k_step1 keeps too.  Past the last rank both t and B are 0 (t may be infinite, and 0 x infinity is no number).
 // MANY: several tokens at a rank of one chunk; their t and the sums of the waves lie in LDS (dynamic, mask_lds_bytes).  Else one token, and
 // t comes straight from memory with the rows of B.  (Several tokens and more chunks: k_predict_mask_long.)
 // What bounds it: the chain from the launch over one round trip for B and t, 64 fp64 multiply-adds per thread and token, and the
@@ -108,7 +108,7 @@ __device__ __forceinline__ int fold_owner(int lane) { return ((lane >> 3) & 1) *
 // rank 256: 10.4 -> 7.5 us; 5 tokens, rank 128, 9.5 -> 6.1 us; 3 tokens in fp32, rank 68, 6.6 -> 5.2 us (all tokens at once, exchanges
 // through LDS, sums and bits by 64 threads).
 constexpr int kMaskChunk = kMaskRows * kMaskJg;      // ranks at a time
-inline size_t mask_lds_bytes(int r, int tokens) { return sizeof(double) * tokens * ((size_t)r + 4 * 64); }
+inline size_t mask_lds_bytes(int r, int tokens) { return sizeof(double) * (tokens * ((size_t)r + 4 * 64) + 1); }
 template <typename T, bool MANY>
 __global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B, const float* __restrict__ c,
                                                       const double* __restrict__ t, int r, int F, int batch, float theta,
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B
     __shared__ double red_one[MANY ? 1 : 4 * 64];
     __shared__ unsigned long long ors[4];
     double* const red = MANY ? lds_mask : red_one;   // [token][wave][neuron of the tile]
-    double* const tl = lds_mask + batch * (4 * 64);  // [token][r]
+    double* const tl = lds_mask + batch * (4 * 64);  // [token][r], then a 0
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cl = tid & (kMaskCols - 1), jg = tid >> 3;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B
 #pragma unroll
             for (int q = 0; q < LPB; ++q)
                 bv[u][q] = (col_ok && j < r) ? reinterpret_cast<const V*>(B + (size_t)j * F + n0)[q] : V(0);
-            if constexpr (!MANY) tr[u] = t[min(j, r - 1)];
+            if constexpr (!MANY) tr[u] = j < r ? t[j] : 0.0;
         }
     };
     request(0);
@@ -159,6 +159,7 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B
             for (int i = 0; i < kAhead; ++i)
                 if (i0 + i * 256 < pieces) reinterpret_cast<f64x2*>(tl)[i0 + i * 256] = p[i];
         }
+        if (tid == 0) tl[nb * r] = 0.0;
         __syncthreads();
     }
     double bd[kMaskRows][8];
@@ -179,17 +180,23 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B
     if constexpr (MANY) {
         widen();
         double ahead[kMaskRows];                     // of the next token
-        auto read_t = [&](int bt) {
+        int from[kMaskRows];                         // where they lie (past the last rank: at the 0 behind all tokens)
 #pragma unroll
-            for (int u = 0; u < kMaskRows; ++u) ahead[u] = tl[bt * r + min(jg + u * kMaskJg, r - 1)];
+        for (int u = 0; u < kMaskRows; ++u) from[u] = jg + u * kMaskJg < r ? jg + u * kMaskJg : nb * r;
+        auto read_t = [&]() {
+#pragma unroll
+            for (int u = 0; u < kMaskRows; ++u) {
+                ahead[u] = tl[from[u]];
+                from[u] += jg + u * kMaskJg < r ? r : 0;
+            }
         };
-        read_t(0);
+        read_t();
 #pragma unroll 1
         for (int bt = 0; bt < nb; ++bt) {
             double tn[kMaskRows];
 #pragma unroll
             for (int u = 0; u < kMaskRows; ++u) tn[u] = ahead[u];
-            read_t(min(bt + 1, nb - 1));
+            if (bt + 1 < nb) read_t();
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = 0.0;
             multiply(tn);

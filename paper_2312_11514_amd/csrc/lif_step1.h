@@ -107,7 +107,7 @@ struct StepArgs {
 // ---- predictor -------------------------------------------------------------------------------------------------
 
 struct PredictLds {
-    double t[2048];                  // t = x A
+    double t[2048 + 1];              // t = x A, then a 0
     double red[4][64];               // per wave and neuron of the tile
     double part[4];                  // parts of a column
     int missing[4];                  // per wave: a word did not arrive
@@ -145,6 +145,7 @@ __device__ __forceinline__ double column_dot_slow(const T* col, const T* x, int 
 template <typename T, int NI>
 __device__ __forceinline__ void own_t(const StepArgs& a, PredictLds& L) {
     const int lane = threadIdx.x & 63, nvec = a.d / Vec<T>::N, per = ColumnPart<T, NI>::P * 64;
+    if (threadIdx.x == 0) L.t[a.rank] = 0.0;
 #pragma unroll 1
     for (int j = threadIdx.x >> 6; j < a.rank; j += 4) {
         double part[4];
@@ -202,7 +203,7 @@ struct MaskTile {
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) {
             if (u * kMaskJg < a.rank) {              // (uniform; bd[u] is 0 past the end)
-                const double tj = L.t[min(jg + u * kMaskJg, a.rank - 1)];
+                const double tj = L.t[min(jg + u * kMaskJg, a.rank)];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tj, WIDE ? bd[u][e] : (double)bv[u][e / VE][e % VE], v[e]);
             }
@@ -261,13 +262,13 @@ __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, Predi
     unsigned* t32 = reinterpret_cast<unsigned*>(L.t);
     const unsigned long long* src = a.t_words + (size_t)(block & (kWordReps - 1)) * a.t_pitch;
     bool ok = true;
-    for (int i0 = tid; i0 < 2 * a.rank; i0 += 4 * 256) {
+    for (int i0 = tid; i0 < 2 * a.rank + 2; i0 += 4 * 256) {     // (with the 0 behind them)
         unsigned p[4];
         const int n = min(4, (2 * a.rank - i0 + 255) >> 8);
         ok = poll_words<4>(src + i0, 256, n, now, a.polls, p) && ok;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (i < n) t32[i0 + i * 256] = p[i];
+            if (i0 + i * 256 < 2 * a.rank + 2) t32[i0 + i * 256] = p[i];         // (0 from n on)
     }
     const bool missing = __any(!ok);
     if ((tid & 63) == 0) L.missing[tid >> 6] = missing;

@@ -76,3 +76,34 @@ def test_one_order_of_summation(dtype, rank, batch):
     for b in range(batch):                          # each token by itself: the same decisions
         lay.predict(x[b:b + 1], 1)
         assert (lay.masks[0].cpu().numpy() == want[b]).all(), b
+
+
+@pytest.mark.parametrize("dtype,rank", [("f32", 4), ("f16", 8), ("f16", 32), ("f16", 40), ("f32", 128), ("f16", 264), ("f32", 320)])
+def test_infinite_activations(dtype, rank):
+    """An x that has overflowed: every x A is infinite, of one sign with positive weights, and so is every logit - in all kernels, whatever
+    lies past the last rank."""
+    import paper_2312_11514_amd as lif
+    from tests.harness import require_gpu
+    require_gpu()
+    d, F, dt = 16, 200, torch.float16 if dtype == "f16" else torch.float32
+    rng = np.random.default_rng(rank)
+    up = lambda *s: torch.from_numpy(rng.uniform(0.1, 1.0, s)).to(dt).cuda()
+    lay = lif.Layer(d_model=d, d_ffn=F, rank=rank, window_k=2, capacity_rows=F, max_batch=3, dtype=dtype, A=up(rank, d), B=up(rank, F), c=None,
+                    b=torch.zeros(F, device="cuda"), host_bundles=torch.zeros((F, 2 * d), dtype=dt).pin_memory())
+    x, y = up(3, d), torch.zeros((3, d), dtype=dt, device="cuda")
+    x[0, 3], x[2, 5] = float("inf"), float("-inf")
+    want = [255, 255, 0]
+    for batch in (1, 2, 3):
+        for polls in (None, 0):
+            if polls is not None:
+                lay.set_handoff_polls(polls)
+            for call in (lambda: lay.predict(x, batch), lambda: lay.step(x, y, batch)):
+                print(f"{dtype} rank {rank}, {batch} tokens, polls {polls}", flush=True)
+                lay.reset()
+                lay.masks.zero_()
+                call()
+                for b in range(batch):
+                    assert (lay.masks[b] == want[b]).all(), (batch, b, polls)
+    for b in range(3):
+        lay.predict(x[b:b + 1], 1)
+        assert (lay.masks[0] == want[b]).all(), b
