@@ -1340,6 +1340,14 @@ inline void launch_step1_as(const StepArgs& a, int grid, hipStream_t s) {
 constexpr int step_batch_most_waves(int ni, bool glu, bool mfma) { return mfma || ni <= 2 || (glu && ni > 12) ? 4 : 8; }
 inline int step_batch_waves(int ni, bool glu, bool mfma, size_t lds) { return lds > kStepLdsLimit / 3 ? step_batch_most_waves(ni, glu, mfma) : 4; }
 
+// A workgroup of eight waves keeps its compute unit to itself: beside another one of its activation workgroups a loader, and the
+// bookkeeping workgroup that makes the deletion plan, are slower.  fp32, us a step with the LDS for one / for two per compute unit (rows in
+// use, rows added): d = 836, gated, 6 tokens, (21805, 291) 115.9 / 121.1; fp16 d = 2664, 6 tokens, (4398, 61) 46.0 / 46.8; but d = 1288,
+// 8 tokens, (9585, 48) 70.7 / 67.6.
+inline size_t step_batch_lds_launched(int waves, size_t lds) {
+    return waves == 8 && lds <= kStepLdsLimit / 2 ? kStepLdsLimit / 2 + 1024 : lds;
+}
+
 // (more than 64 KiB of LDS has to be allowed once per kernel and device: `allow` does only that, for the kernels of a.d)
 template <typename T, bool GLU, bool GATE, bool MFMA>
 inline hipError_t launch_step_batch_as(const StepArgs& a, int grid, size_t lds, bool allow, hipStream_t s) {
@@ -1355,7 +1363,7 @@ inline hipError_t launch_step_batch_as(const StepArgs& a, int grid, size_t lds, 
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepLdsLimit); \
         }                                                                                                                \
         const int waves = step_batch_waves(NI, GLU, MFMA, lds);                                                          \
-        hipLaunchKernelGGL(waves == 4 ? few : many, dim3(grid), dim3(waves * 64), lds, s, a);                            \
+        hipLaunchKernelGGL(waves == 4 ? few : many, dim3(grid), dim3(waves * 64), step_batch_lds_launched(waves, lds), s, a);                            \
         return hipSuccess;                                                                                               \
     } while (0)
     if (ni <= 1) LIF_SB(1);
