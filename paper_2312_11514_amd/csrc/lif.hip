@@ -43,21 +43,22 @@ int fail(int code, const char* fmt, const char* detail = "") {
     } while (0)
 
 // Bytes of host reads that lif_step keeps outstanding: pairs of loader workgroups (one bundle in flight per pair) =
-// kStepInflightBytes / bundle bytes, within 5..kStepPairs.  The link needs about 128 KiB (56 GB/s at 1.5 to 2.4 us); the rest covers
-// the time in which a loader writes a bundle out and asks for the next.  One token with 144 / 192 / 256 / 320 / 384 KiB:
-// OPT shape 60.4 / 59.4 / 58.2 / 58.4 / 60.0 us, Falcon shape 188 / 159 / 143 / 141 / 140 us, gated Llama-2 shape 147 / 138 /
-// 137 / 138 / 143 us.
+// kStepInflightBytes / bundle bytes, within 5..kStepPairs.  The link needs about 128 KiB (56 GB/s at 1.5 to 2.4 us); the rest
+// covers the time in which a loader writes a bundle out and asks for the next.  One token with 144 / 192 / 256 / 320 / 384 KiB:
+// OPT shape 60.4 / 59.4 / 58.2 / 58.4 / 60.0 us, Falcon shape 188 / 159 / 143 / 141 / 140 us, gated Llama-2 shape 147 / 138 / 137
+// / 138 / 143 us.
 // For rows of at most 10 KiB the number of loaders is what limits (kStepPairs).
 // Where a vector is at most 2 KiB a loader takes whole bundles, a pair has two in flight, and 256 KiB of them are asked for by
 // at most kStepPairsWhole pairs: bundles of 1 KiB, 1278 and 395 added, with 32 / 48 / 64 pairs 77.1 / 65.1 / 62.1 and 43.8 / 40.5 /
 // 39.5 us (five separate launches: 70.2 and 43.6); of 2 KiB, 783 and 198 added, 57.0 / 55.7 / 55.3 and 28.9 / 27.6 / 26.8; of
 // 4 KiB, 455 and 136 added, with 32 / 40 / 64 54.0 / 53.5 / 54.3 and 29.3 / 29.4 / 30.1.
 // Vectors of more than 12 KiB: a loader takes so long with each (16 pieces a lane) that kStepPairsWide pairs are needed; d = 8192,
-// with 10 / 14 / 20 / 32 pairs: plain 75.0 / 63.3 / 60.2 / 61.6 us (five separate launches: 67.1), gated 92.1 / 87.5 / 83.9 / 84.7, with
-// the gate resident 91.1 / 79.6 / 76.0 / 78.0; d = 7168 59.4 / 53.8 / 53.0 / 55.1; but d = 6144 44.0 / 44.6 / 45.9 / 46.2.
-// Several tokens: more loaders, a bundle takes longer to deal with; 20 / 32 / 48 / 64 pairs of 16 KiB rows: 205 / 207 / 200 / 200 us a
-// pass, of 24 KiB: 262 / 252 / 249 / 250; but every loader workgroup costs a compute unit of the activation stage (11 KiB rows, 60
-// loaded: 52 / 52 / 53 / 56).
+// with 10 / 14 / 20 / 32 pairs: plain 75.0 / 63.3 / 60.2 / 61.6 us (five separate launches: 67.1), gated 92.1 / 87.5 / 83.9 /
+// 84.7, with the gate resident 91.1 / 79.6 / 76.0 / 78.0; d = 7168 59.4 / 53.8 / 53.0 / 55.1; but d = 6144 44.0 / 44.6 / 45.9 /
+// 46.2.
+// Several tokens: more loaders, a bundle takes longer to deal with; 20 / 32 / 48 / 64 pairs of 16 KiB rows: 205 / 207 / 200 / 200
+// us a pass, of 24 KiB: 262 / 252 / 249 / 250; but every loader workgroup costs a compute unit of the activation stage (11 KiB
+// rows, 60 loaded: 52 / 52 / 53 / 56).
 constexpr size_t kStepInflightBytes = 320 * 1024, kStepInflightBytesWhole = 256 * 1024, kStepInflightBytesB = 768 * 1024;
 constexpr int kStepPairs = 32, kStepPairsWhole = 64, kStepPairsWide = 20, kStepPairsB = 48;
 // lif_load_bundles by itself: with 320 / 640 KiB rows of 25 and 30 KiB took 121 / 117 and 110 / 105 us (all four calls).
@@ -419,11 +420,11 @@ void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, h
     }
 }
 
-// One token in one launch, where few workgroups wait for few words.  What the waiting costs grows with slices x rows (every word is read
-// by every slice), what the second launch costs does not: fp16 in a graph, rows in use / us in two launches -> in one (all sizes in one):
-// 16 slices 871: 6.2 -> 5.7, 32 slices 480: 6.0 -> 6.0, 983: 6.3 -> 6.6, 64 slices 264: 6.1 -> 5.8, 723: 6.3 -> 6.5, 80 slices 703:
-// 6.2 -> 7.4, 128 slices 337: 6.6 -> 7.8; from the host 7.6 -> 5.4 to 6.5, 128 slices 7.7 -> 7.6.  96 slices and more gain from the host
-// alone, so they stay with two.
+// One token in one launch, where few workgroups wait for few words.  What the waiting costs grows with slices x rows (every word
+// is read by every slice), what the second launch costs does not: fp16 in a graph, rows in use / us in two launches -> in one
+// (all sizes in one): 16 slices 871: 6.2 -> 5.7, 32 slices 480: 6.0 -> 6.0, 983: 6.3 -> 6.6, 64 slices 264: 6.1 -> 5.8, 723:
+// 6.3 -> 6.5, 80 slices 703: 6.2 -> 7.4, 128 slices 337: 6.6 -> 7.8, 927: 6.0 -> 7.2; from the host 7.6 -> 5.4 to 6.5, 128 slices
+// 927: 7.0 -> 7.2 where the host is fast.  So 96 slices and more stay with two.
 bool ffn_one(const lif_layer* L, int batch) {
     const int rows = geometry_rows(L), slices = down1_slices(L->cfg);
     return batch == 1 && L->one_words && rows <= kOneRows && slices * rows <= kOneWords;

@@ -174,8 +174,8 @@ __global__ __launch_bounds__(256) void k_ffn_up(const T* __restrict__ matrix, co
                                   pointers, gact, gact_n, st);
 }
 
-// After a fused step (k_step1, k_step_batch): the activations, slot owners and biases of the rows that it wrote, valid for the slots
-// whose stamp is the number of that step.  All null otherwise.
+// After a fused step (k_step1, k_step_batch): the activations, slot owners and biases of the rows that it wrote, valid for the
+// slots whose stamp is the number of that step.  All null otherwise.
 struct FusedRows {
     const float* h_new;
     const int32_t* stamp;
@@ -235,11 +235,12 @@ constexpr int kDownRowsMost = 512, kDownRowsLeast = 128;      // rows per chunk 
 constexpr int kDownWgs = 512;         // workgroups that chunks of fewer than kDownRowsMost rows are made for
 
 // Row chunks in use for n cached rows, several tokens and `slices` column slices: their active sets add up, most rows are read, and
-// a chunk is at most kDownRowsMost rows: one chunk (no partial sums, no second launch) up to there, beyond it chunks of down to kDownRowsLeast
-// until kDownWgs workgroups stream at once.  With chunks of 512 rows throughout, half of the compute units had nothing to do and a
-// thread went through 32 rows, four at a time.  One FFN call, us, 512 -> now: d = 1288, 3 tokens, 988 rows 14.5 -> 12.3, 2044 rows 16.1 -> 13.4,
-// 4081 rows 18.9 -> 16.4; 8 tokens, 1634 rows 20.6 -> 17.4, 6859 rows 35.1 -> 33.9; d = 4096, 3 tokens, 949 rows 19.5 -> 17.3, 3874 rows
-// the same.  Up to 512 rows one chunk is better where no second launch is needed (3 tokens, d = 1288, 208 rows 8.9 against 11.3).
+// a chunk is at most kDownRowsMost rows: one chunk (no partial sums, no second launch) up to there, beyond it chunks of down to
+// kDownRowsLeast until kDownWgs workgroups stream at once.  With chunks of 512 rows throughout, half of the compute units had
+// nothing to do and a thread went through 32 rows, four at a time.  One FFN call, us, 512 -> now: d = 1288, 3 tokens, 988 rows
+// 14.5 -> 12.3, 2044 rows 16.1 -> 13.4, 4081 rows 18.9 -> 16.4; 8 tokens, 1634 rows 20.6 -> 17.4, 6859 rows 35.1 -> 33.9; d =
+// 4096, 3 tokens, 949 rows 19.5 -> 17.3, 3874 rows the same.  Up to 512 rows one chunk is better where no second launch is needed
+// (3 tokens, d = 1288, 208 rows 8.9 against 11.3).
 // The host sizes the grid with the same rule.
 __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
     const int least = (n + kDownRowsMost - 1) / kDownRowsMost, most = (n + kDownRowsLeast - 1) / kDownRowsLeast, fill = kDownWgs / slices;
@@ -449,9 +450,9 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
 
 // Sum of the partial outputs of `chunks` chunks, stride floats apart, in chunk order.  The first `ahead` of them (at most MOST) are
 // requested before the row count (and so `chunks`) is known: the launch that wrote them had that many workgroup rows, and the array
-// always has room for kDownChunksMax.  Behind the row count they cost another round trip.  MOST is a compile-time number so that the
-// requests and the adds are straight code: with a branch for each of kDownChunksMax the kernel spent 0.5 us on instructions that run
-// once (one FFN call: 5 tokens, d = 4096, 1365 rows, 16.1 -> 15.4 us; one token, d = 1024, 13000 rows, 16.6 -> 15.8).
+// always has room for kDownChunksMax.  Behind the row count they cost another round trip.  MOST is a compile-time number so that
+// the requests and the adds are straight code: with a branch for each of kDownChunksMax the kernel spent 0.5 us on instructions
+// that run once (one FFN call: 5 tokens, d = 4096, 1365 rows, 16.1 -> 15.4 us; one token, d = 1024, 13000 rows, 16.6 -> 15.8).
 template <int MOST>
 struct ChunkSum {
     float v[MOST];
@@ -488,8 +489,9 @@ struct ChunkSum {
 // y = sum of the chunk partials in chunk order, rounded once to the element type.  Launched after a
 // k_ffn_down grid of more than one workgroup row; does nothing when a single chunk was in use (y is
 // written already).  grid = ceil(batch * d / 256), block = 256.
-// CHUNKS: the chunk rule of the kernel that wrote the partials, for its number of column slices.  Added in fp64, as in those kernels: every
-// chunk would be another rounding of the whole (3 tokens in fp32, d = 320: 1.43e-7 from the sum in fp64 against 1.60e-7).
+// CHUNKS: the chunk rule of the kernel that wrote the partials, for its number of column slices.  Added in fp64, as in those
+// kernels: every chunk would be another rounding of the whole (3 tokens in fp32, d = 320: 1.43e-7 from the sum in fp64 against
+// 1.60e-7).
 template <typename T, int (*CHUNKS)(int, int), int MOST>
 __global__ __launch_bounds__(256) void k_ffn_down_finish(const float* ypart, T* __restrict__ y, int d,
                                                          int batch, int slices, int ahead, const DevState* st) {

@@ -31,10 +31,10 @@ constexpr int kDown1RowsFull = 1024;
 // chunks and a second launch; reading every row (one whole call, OPT shape) 3072 rows 15.7 against 16.8, 3584 rows 17.3 either
 // way, 4096 rows 18.7 in four chunks.
 // Beyond, workgroups of 8 waves, several to a compute unit (with 16 waves one workgroup fills it, and what is left of the
-// workgroups after 256 of them runs almost alone): us a call, 16 waves -> 8 waves, every row read: OPT shape 5120 rows 23.1 -> 21.7,
-// 10240 rows 36.0 -> 32.7; Falcon shape 16384 rows 64.8 -> 56.7; skipping rows, Falcon shape, 10240 rows 27.5 -> 24.1.  Skipping
-// rows in two chunks, where workgroups of 16 waves just fill the compute units (down1_rows16), they are better: OPT shape, half of
-// 10240 rows active, 27.5 against 28.7.
+// workgroups after 256 of them runs almost alone): us a call, 16 waves -> 8 waves, every row read: OPT shape 5120 rows 23.1 ->
+// 21.7, 10240 rows 36.0 -> 32.7; Falcon shape 16384 rows 64.8 -> 56.7; skipping rows, Falcon shape, 10240 rows 27.5 -> 24.1.
+// Skipping rows in two chunks, where workgroups of 16 waves just fill the compute units (down1_rows16), they are better: OPT
+// shape, half of 10240 rows active, 27.5 against 28.7.
 // rows up to which workgroups have 16 waves (from kDown1FewRows on): known before the row count is
 template <bool SKIP>
 __host__ __device__ __forceinline__ int down1_rows16(int slices) {
@@ -67,9 +67,9 @@ __host__ __device__ __forceinline__ int down1_waves(int n, int slices) {
 // capacity, so the addresses are valid; values past the count are masked).
 // Workgroup row y takes the chunks y, y + gridDim.y, ...; with several chunks and several workgroup rows the sums go to
 // ypart[chunk][d] (fp32) and k_ffn_down_finish adds them, else this kernel adds them in the same order.  No atomics.
-// The same as a role of a larger launch (k_ffn_one): bx, by, rows_by take the place of blockIdx.x, blockIdx.y, gridDim.y, and WORDS is where
-// the activations come from: `activations(s0, stride, count, v)` fills v[q] with those of the slots s0 + q * stride (q < count, different
-// for every lane).
+// The same as a role of a larger launch (k_ffn_one): bx, by, rows_by take the place of blockIdx.x, blockIdx.y, gridDim.y, and
+// WORDS is where the activations come from: `activations(s0, stride, count, v)` fills v[q] with those of the slots s0 + q *
+// stride (q < count, different for every lane).
 struct NoWords {};
 template <typename T, bool SKIP, int WAVES, bool FUSED, typename Words>
 __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, const float* __restrict__ h, const FusedRows& fused,

@@ -27,13 +27,13 @@ constexpr int kDmWaves = 4;              // waves per workgroup: 8 are a little 
                                          // step of 4 tokens at 1250 rows) but leave two workgroups per compute unit and so a
                                          // second, nearly empty round of them above (24 against 19 us at 8600 rows)
 
-// Rows per pass and per chunk (one partial output per chunk): functions of the capacity and the width alone, so a workgroup row knows
-// where its first chunk starts before the row count arrives; a chunk is whole passes, and at most kDownChunksMax chunks are ever in
-// use.  Passes of 256 rows have half the activations to wait for and twice the workgroups: one FFN call, us, 512 -> 256 rows: d = 512, 3
-// tokens, 1835 rows 15.6 -> 13.3; d = 1024, 8 tokens, 6948 rows 19.8 -> 17.7; d = 4096, 8 tokens, 1674 rows 19.8 -> 17.2.  But where
-// 256-row workgroups would need a second round on the chip 512 are better: d = 4096, 8 tokens, 8177 of 8192 rows 33.9 against 37.2.
-// (Chunks of 256 rows in passes made for 512 gain a third of it.)  And small caches are likely to hold the 257 to 450 rows that one
-// chunk of 512 takes without a second launch: d = 512, 2 tokens, 299 rows 12.1 against 12.9.
+// Rows per pass and per chunk (one partial output per chunk): functions of the capacity and the width alone, so a workgroup row
+// knows where its first chunk starts before the row count arrives; a chunk is whole passes, and at most kDownChunksMax chunks are
+// ever in use.  Passes of 256 rows have half the activations to wait for and twice the workgroups: one FFN call, us, 512 -> 256
+// rows: d = 512, 3 tokens, 1835 rows 15.6 -> 13.3; d = 1024, 8 tokens, 6948 rows 19.8 -> 17.7; d = 4096, 8 tokens, 1674 rows 19.8
+// -> 17.2. But where 256-row workgroups would need a second round on the chip 512 are better: d = 4096, 8 tokens, 8177 of 8192
+// rows 33.9 against 37.2. (Chunks of 256 rows in passes made for 512 gain a third of it.) And small caches are likely to hold the
+// 257 to 450 rows that one chunk of 512 takes without a second launch: d = 512, 2 tokens, 299 rows 12.1 against 12.9.
 __host__ __device__ __forceinline__ int down_mfma_pass_rows(int capacity, int slices) {
     const int few = (capacity + kDmRowsFew - 1) / kDmRowsFew;
     return capacity > kDmSmall && few <= kDownChunksMax && few * slices <= kDmWgsAtOnce ? kDmRowsFew : kDmRows;

@@ -1,16 +1,17 @@
-// Step 4 for one token in one launch: the first workgroups are the activation stage (a wave per row) and publish every activation as a
-// stamped word, the last ones are the down projection (a column slice each) and wait for the words of their slots.
+// Step 4 for one token in one launch: the first workgroups are the activation stage (a wave per row) and publish every activation
+// as a stamped word, the last ones are the down projection (a column slice each) and wait for the words of their slots.
 //
-// The sums are those of k_ffn_up and k_ffn_down1.  What it saves is a launch: from the host a call was as slow as two launches could be
-// submitted, and behind one another they have a gap and a round trip for the counts.  us a call, two launches -> one, every call from
-// the host / in a graph: fp16 d = 256, 321 rows 7.60 -> 5.14 / 5.72 -> 5.27; d = 1024, 117 rows 7.61 -> 5.24 / 5.56 -> 5.43; d = 2048, gated,
-// 85 rows 7.52 -> 5.29 / 5.83 -> 5.46; fp32 d = 256, 79 rows 7.61 -> 4.86 / 5.97 -> 5.04; d = 1024, 117 rows 7.72 -> 5.33 / 6.36 -> 5.47.
-// Workgroups of the activation stage leave four of their eight waves idle: with a row for each wave, half as many workgroups, it was
-// mostly slower (graph, fp16 d = 512, 312 rows 5.56 -> 5.91, d = 2048, 85 rows gated 5.55 -> 5.86; fp32 d = 256, 79 rows 5.19 -> 4.85).
-// Eight copies of a word instead of four are no faster.
+// The sums are those of k_ffn_up and k_ffn_down1. What it saves is a launch: from the host a call was as slow as two launches
+// could be submitted, and behind one another they have a gap and a round trip for the counts.  us a call, two launches -> one,
+// every call from the host / in a graph: fp16 d = 256, 321 rows 7.60 -> 5.14 / 5.72 -> 5.27; d = 1024, 117 rows 7.61 -> 5.24 /
+// 5.56 -> 5.43; d = 2048, gated, 85 rows 7.52 -> 5.29 / 5.83 -> 5.46; fp32 d = 256, 79 rows 7.61 -> 4.86 / 5.97 -> 5.04; d =
+// 1024, 117 rows 7.72 -> 5.33 / 6.36 -> 5.47.
+// Workgroups of the activation stage leave four of their eight waves idle: with a row for each wave, half as many workgroups, it
+// was mostly slower (graph, fp16 d = 512, 312 rows 5.56 -> 5.91, d = 2048, 85 rows gated 5.55 -> 5.86; fp32 d = 256, 79 rows 5.19
+// -> 4.85). Eight copies of a word instead of four are no faster.
 // A word waits for workgroups with smaller numbers only, and at most `polls` reads: then the wave computes the activation itself.
-// The stamp is a number of the layer that is counted on by the launch itself once nobody reads it any more: the down workgroups count
-// themselves in behind their read of it, the last one to do so sets the next number when it has seen all activations.
+// The stamp is a number of the layer that is counted on by the launch itself once nobody reads it any more: the down workgroups
+// count themselves in behind their read of it, the last one to do so sets the next number when it has seen all activations.
 #pragma once
 
 #include "lif_ffn.h"
@@ -24,9 +25,11 @@ constexpr int kOneReps = 4;                          // copies of every word
 constexpr int kOneSlices = 64, kOneWords = 16384;    // column slices, and words read by all of them, up to which this form is taken
 constexpr int kOneRows = kDown1FewRows;              // ... and rows: one pass of 8 waves
 constexpr int kOneCapacity = 16384;                  // (there is a word for every slot)
-constexpr int kOneWaits = 1 << 20;                   // reads of a thread before a launch whose waits ran out is given up: about a second
+constexpr int kOneWaits = 1 << 20;                   // failed reads of a thread before a launch whose waits ran out is given up:
+                                                     // about a second
 __host__ __device__ __forceinline__ size_t one_pitch(int capacity) { return (size_t)words_pitch(capacity); }
-// Looks at the slots first, first + stride, ... below n until each is there, or for `waits` failed looks in all; returns whether all are.
+// Looks at the slots first, first + stride, ... below n until each is there, or for `waits` failed looks in all; returns whether
+// all are.
 template <typename There>
 __host__ __device__ __forceinline__ bool await_slots(int first, int n, int stride, int waits, There there) {
     for (int s = first; s < n; s += stride)

@@ -34,10 +34,10 @@ constexpr int kMaskCols = 8;       // mask bytes (groups of 8 neurons) per workg
 constexpr int kMaskJg = 32;        // rank groups per workgroup of predict_mask
 constexpr int kMaskRows = 8;       // rows of B a thread keeps in flight
 
-// t[j] = x . row j of At (the first predictor matrix with the contraction dimension contiguous, [r x d]) by a workgroup of four waves:
-// wave w takes the 1 KiB pieces [w * P, w * P + P), P = ceil(NI / 4) of NI = ceil(d / (64 * VE)), in fp64, and the four sums are
-// added in wave order.  A whole row per wave took 1.8 us from the last load to the sum at d = 4096 in fp16: a conversion and a
-// dependent fp64 add for each of 64 products, one wave to a SIMD (k_step1, x A known after 3.1 us instead of 2.3).
+// t[j] = x . row j of At (the first predictor matrix with the contraction dimension contiguous, [r x d]) by a workgroup of four
+// waves: wave w takes the 1 KiB pieces [w * P, w * P + P), P = ceil(NI / 4) of NI = ceil(d / (64 * VE)), in fp64, and the four
+// sums are added in wave order.  A whole row per wave took 1.8 us from the last load to the sum at d = 4096 in fp16: a conversion
+// and a dependent fp64 add for each of 64 products, one wave to a SIMD (k_step1, x A known after 3.1 us instead of 2.3).
 template <typename T, int NI>
 struct ColumnPart {
     using V = typename Vec<T>::type;
@@ -80,8 +80,8 @@ __global__ __launch_bounds__(256) void k_predict_xa(const T* __restrict__ x, con
     if (threadIdx.x == 0 && !err) t[(size_t)b * r + j] = column_total(part);
 }
 
-// The sums v[e] of neurons 8 cl + e over a thread's ranks -> the sum over the eight rank groups of the wave, which sit 8 lanes apart:
-// every exchange leaves a lane with half of its neurons, in the end with neuron 8 cl + fold_owner(lane).
+// The sums v[e] of neurons 8 cl + e over a thread's ranks -> the sum over the eight rank groups of the wave, which sit 8 lanes
+// apart: every exchange leaves a lane with half of its neurons, in the end with neuron 8 cl + fold_owner(lane).
 __device__ __forceinline__ double fold_groups(double (&v)[8], int lane) {
     const bool up = (lane & 8) != 0;
 #pragma unroll
@@ -96,17 +96,18 @@ __device__ __forceinline__ double fold_groups(double (&v)[8], int lane) {
 __device__ __forceinline__ int fold_owner(int lane) { return ((lane >> 3) & 1) * 4 + ((lane >> 4) & 1) * 2 + (lane >> 5); }
 
 // logits = t B + c, threshold, 64 mask bits at a time; step mask = OR over the batch.
-// grid = ceil(F / 64), block = 256 = 32 rank groups x 8 column lanes; a column lane owns 8 consecutive neurons.  A thread adds its ranks
-// jg, jg + 32, ... in that order, then come the rank groups of a wave (fold_groups), then the waves: the one order of a logit, which
-// MaskTile in k_step1 keeps too.  Past the last rank both t and B are 0 (t may be infinite, and 0 x infinity is no number).
-// MANY: several tokens at a rank of one chunk; their t and the sums of the waves lie in LDS (dynamic, mask_lds_bytes).  Else one token, and
-// t comes straight from memory with the rows of B.  (Several tokens and more chunks: k_predict_mask_long.)
+// grid = ceil(F / 64), block = 256 = 32 rank groups x 8 column lanes; a column lane owns 8 consecutive neurons.  A thread adds
+// its ranks jg, jg + 32, ... in that order, then come the rank groups of a wave (fold_groups), then the waves: the one order of a
+// logit, which MaskTile in k_step1 keeps too.  Past the last rank both t and B are 0 (t may be infinite, and 0 x infinity is no
+// number).
+// MANY: several tokens at a rank of one chunk; their t and the sums of the waves lie in LDS (dynamic, mask_lds_bytes). Else one
+// token, and t comes straight from memory with the rows of B. (Several tokens and more chunks: k_predict_mask_long.)
 // What bounds it: the chain from the launch over one round trip for B and t, 64 fp64 multiply-adds per thread and token, and the
 // sums across the rank groups; a few hundred KB to a few MB are read.  A token at a time, with B widened once: the code is 2 KB
 // instead of 10, and instructions that run once wait for their way into the cache (8 tokens at once, rank 256: 8.1 us).  The sums
 // across a wave go through register exchanges that leave a lane with one neuron, so that a ballot is the mask word.  8 tokens,
-// rank 256: 10.4 -> 7.5 us; 5 tokens, rank 128, 9.5 -> 6.1 us; 3 tokens in fp32, rank 68, 6.6 -> 5.2 us (all tokens at once, exchanges
-// through LDS, sums and bits by 64 threads).
+// rank 256: 10.4 -> 7.5 us; 5 tokens, rank 128, 9.5 -> 6.1 us; 3 tokens in fp32, rank 68, 6.6 -> 5.2 us (all tokens at once,
+// exchanges through LDS, sums and bits by 64 threads).
 constexpr int kMaskChunk = kMaskRows * kMaskJg;      // ranks at a time
 inline size_t mask_lds_bytes(int r, int tokens) { return sizeof(double) * (tokens * ((size_t)r + 4 * 64) + 1); }
 template <typename T, bool MANY>
@@ -231,11 +232,13 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask(const T* __restrict__ B
         step_mask[byte] = (uint8_t)(((ors[0] | ors[1]) | (ors[2] | ors[3])) >> (8 * lane));
 }
 
-// The same for several tokens at more than kMaskChunk ranks.  A thread's sums have to stay apart from the other rank groups' until its last
-// rank, so they stay in registers for NT tokens at a time (the batch at most; tokens past it are worked for and left out).  A row of B is
-// widened once for all of them and asked for again, a chunk on, as soon as it is used; t goes through LDS a chunk ahead.
-// lif_predict, us, d = 4096, F = 16384, against folding every chunk and adding the folded sums (another order): fp16, 8 tokens, rank 512
-// 16.5 -> 13.8, 768 25.3 -> 18.3, 2048 64.8 -> 41.5; 2 tokens, rank 2048 22.8 -> 23.1; fp32, 3 tokens, rank 512 14.8 -> 14.6.
+// The same for several tokens at more than kMaskChunk ranks.  A thread's sums have to stay apart from the other rank groups'
+// until its last rank, so they stay in registers for NT tokens at a time (the batch at most; tokens past it are worked for and
+// left out). A row of B is widened once for all of them and asked for again, a chunk on, as soon as it is used; t goes through
+// LDS a chunk ahead.
+// lif_predict, us, d = 4096, F = 16384, against folding every chunk and adding the folded sums (another order): fp16, 8 tokens,
+// rank 512 16.5 -> 13.8, 768 25.3 -> 18.3, 2048 64.8 -> 41.5; 2 tokens, rank 2048 22.8 -> 23.1; fp32, 3 tokens, rank 512 14.8 ->
+// 14.6.
 template <typename T, int NT>
 __global__ __launch_bounds__(256, 1) void k_predict_mask_long(const T* __restrict__ B, const float* __restrict__ c,
                                                               const double* __restrict__ t, int r, int F, int batch, float theta,

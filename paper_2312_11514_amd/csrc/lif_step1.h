@@ -34,8 +34,8 @@
 // (7.5); behind the last bundle is the down projection.  A compute unit has about 5 KiB of host reads under way, whatever its
 // waves ask for, so some 30 loaders fill the link.
 // Measured on gfx950, one decode token, with five launches -> with this kernel and the down projection: fp32 d = 256, F = 1024:
-// 23.4 -> 14.1 us; OPT-6.7B shape 65.3 -> 57; Falcon-7B shape 149.5 -> 136; Llama-2 shape gated, from a graph, 148.7 -> 132, with the
-// gate resident 112.8 -> 108.5.
+// 23.4 -> 14.1 us; OPT-6.7B shape 65.3 -> 57; Falcon-7B shape 149.5 -> 136; Llama-2 shape gated, from a graph, 148.7 -> 132, with
+// the gate resident 112.8 -> 108.5.
 #pragma once
 
 #include <cstddef>
@@ -55,9 +55,9 @@ constexpr int step1_wgs_per_cu() {
     constexpr int vectors = NI > 2 ? (GLU ? 2 : 1) : (GLU ? 3 : 2);
     return (2 * vectors + 1) * NI * 4 <= 120 ? 2 : 1;
 }
-// Columns of x A are dealt to the first kStepColumns x step1_wgs_per_cu predictor workgroups: every tile of neurons waits for all columns,
-// so these have to run at the same time, and that many fit the chip.  Dealt over all of them, one token at d = 5120, gated, F = 17000,
-// rank 512 (266 predictor workgroups, one to a compute unit) took 1484 us, every wait running out; so 81.
+// Columns of x A are dealt to the first kStepColumns x step1_wgs_per_cu predictor workgroups: every tile of neurons waits for all
+// columns, so these have to run at the same time, and that many fit the chip.  Dealt over all of them, one token at d = 5120,
+// gated, F = 17000, rank 512 (266 predictor workgroups, one to a compute unit) took 1484 us, every wait running out; so 81.
 constexpr int kStepColumns = 256;
 
 struct StepArgs {
@@ -359,9 +359,9 @@ struct PlanLds {
         };
     };
 };
-// What a loader uses of it in a batched step.  The rest of a loader's LDS (PostLds, x, rows) lies where the deletion plan of the bookkeeping
-// workgroup does: all workgroups of the launch carry the same LDS, and behind the whole plan x left room for one of them
-// per compute unit instead of two.
+// What a loader uses of it in a batched step.  The rest of a loader's LDS (PostLds, x, rows) lies where the deletion plan of the
+// bookkeeping workgroup does: all workgroups of the launch carry the same LDS, and behind the whole plan x left room for one of
+// them per compute unit instead of two.
 constexpr size_t kLoaderPlanLds = (offsetof(PlanLds, ids) + sizeof(uint16_t) * kListItems + 15) / 16 * 16;
 
 // All mask words computed by this workgroup alone (a wait that ran out): m[i] of the words this thread owns
@@ -414,10 +414,11 @@ __device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt
 //               of a compute unit returns loads in order over all its waves, so a load of device memory behind host
 //               reads takes as long as they do (2 to 5 us): the tail row is requested just behind the bundle (ahead of
 //               it, it would hold back the host read), and the loaders are spread over compute units (four
-//               loading waves per workgroup moved 35 GB/s where one moves 50).  The units of a round are dealt to the workgroups one place further each round, so that all
-//               get as many activation parts as down parts (a counter drawn from by atomics balanced no better, and the
-//               wait for its answer cost 1.5 us per unit; with all activation parts first, rows of 16 KiB loaded a
-//               quarter slower, all reads falling on the same half of every row);
+//               loading waves per workgroup moved 35 GB/s where one moves 50).  The units of a round are dealt to the
+//               workgroups one place further each round, so that all get as many activation parts as down parts (a counter
+//               drawn from by atomics balanced no better, and the wait for its answer cost 1.5 us per unit; with all
+//               activation parts first, rows of 16 KiB loaded a quarter slower, all reads falling on the same half of every
+//               row);
 //   waves 1..3  list the added neurons meanwhile, then move the tail rows that nothing overwrites (more neurons removed than
 //               added; with several tokens wave 0 does).
 // Lane l holds the same 16-byte pieces of every vector as in the activation role and sums in the same order.
@@ -703,8 +704,8 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     }
     n2 = n - tot_r;
     items = max(tot_a, tot_r);
-    // The word with the neuron of this loader's first unit is looked up by the thread that holds it (the neuron is its r-th bit); the
-    // list is written while the first host read is on its way.
+    // The word with the neuron of this loader's first unit is looked up by the thread that holds it (the neuron is its r-th bit);
+    // the list is written while the first host read is on its way.
     const int unit0 = PAIRED ? lw >> 1 : lw;
     {
         int r = unit0 - off_a;
@@ -734,8 +735,8 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     if (wg == 0) {
         // ---- deletion plan (see k_window_plan): holes = dead slots below n', fillers = live slots at or above it ----
         // Made here once and handed to the loaders as stamped words, which arrive before their first bundle does.  (Made by every
-        // loader for itself, by the waves that do not load, it was known 1 us later with few rows; with more than 4096 rows, ahead of
-        // the host reads, it kept them waiting for 14 us: a loader cannot look owners up behind a host read.)
+        // loader for itself, by the waves that do not load, it was known 1 us later with few rows; with more than 4096 rows,
+        // ahead of the host reads, it kept them waiting for 14 us: a loader cannot look owners up behind a host read.)
         // (All of it by a wave and 64 slots at a time took 0.4 us each: 8700 rows 14 us, now 6.)
         int H = 0;
         if (tot_r > 0) {                                         // uniform
@@ -771,8 +772,9 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                 if (lane < kRound && b0 + lane * 4 < nblk) L.dead[b0 + lane * 4] = dead;
             }
             lds_barrier();
-            // A thread counts the holes and fillers of consecutive granules (one, or up to four with more than 16384 rows) and, behind
-            // a prefix sum, lists the holes.  Granules of 16 slots where that many threads are there: a thread takes 0.1 us a hole.
+            // A thread counts the holes and fillers of consecutive granules (one, or up to four with more than 16384 rows) and,
+            // behind a prefix sum, lists the holes.  Granules of 16 slots where that many threads are there: a thread takes 0.1
+            // us a hole.
             const int gl = nblk <= 64 ? 4 : nblk <= 128 ? 5 : 6, g = 1 << gl;            // slots of a granule
             auto slots_below = [](int k) -> unsigned long long { return k <= 0 ? 0ull : k < 64 ? ~(~0ull << k) : ~0ull; };
             auto dead_in = [&](int i) -> unsigned long long { return L.dead[(i << gl) >> 6] >> ((i << gl) & 63); };
@@ -1234,14 +1236,15 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     }
 }
 
-// The activation role reads megabytes that nothing needs before the down projection; read at once they hold up the predictor, whose few
-// reads the host link waits for (x A published 3.9 to 6.2 us after the launch began instead of 2.2, Falcon and Llama-2 shapes).  So
-// its waves begin when a mask word has been published, or after kActWaits reads of it at the latest.
+// The activation role reads megabytes that nothing needs before the down projection; read at once they hold up the predictor,
+// whose few reads the host link waits for (x A published 3.9 to 6.2 us after the launch began instead of 2.2, Falcon and Llama-2
+// shapes). So its waves begin when a mask word has been published, or after kActWaits reads of it at the latest.
 constexpr int kActWaits = 64;
-// ... but only where the load that follows is likely to take longer than they do, which the last step tells: bundles of `vectors` vectors at
-// the rate of the link against all but the down vector of the rows in use at kLinkSlower times that rate.  (Else a step that adds
-// nothing waits for nothing and reads then.)  d = 4096, us a step at once / behind the predictor, (rows in use, added): (3414, 0)
-// 31.2 / 37.0, (3504, 13) 36.1 / 37.7, (3617, 16) 41.1 / 39.4, (3812, 40) 48.3 / 44.1; gated (3217, 0) 33.9 / 41.0, (3343, 8) 39.3 / 42.8.
+// ... but only where the load that follows is likely to take longer than they do, which the last step tells: bundles of `vectors`
+// vectors at the rate of the link against all but the down vector of the rows in use at kLinkSlower times that rate.  (Else a
+// step that adds nothing waits for nothing and reads then.) d = 4096, us a step at once / behind the predictor, (rows in use,
+// added): (3414, 0) 31.2 / 37.0, (3504, 13) 36.1 / 37.7, (3617, 16) 41.1 / 39.4, (3812, 40) 48.3 / 44.1; gated (3217, 0) 33.9 /
+// 41.0, (3343, 8) 39.3 / 42.8.
 constexpr int kLinkSlower = 128;
 __host__ __device__ __forceinline__ bool load_hides_activations(int added, int in_use, int vectors) {
     return added * vectors * kLinkSlower >= in_use * (vectors - 1);
@@ -1279,9 +1282,10 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
 // loaders, and the activation stage over the rows in use - on the matrix cores (MFMA: fp16, d a multiple of 32), else one
 // wave per row.  Dynamic LDS: step_batch_lds bytes.
 // Registers (gfx950, as the compiler reports them): the loader role has more uniform values than the 106 scalar registers hold,
-// 97 to 148 of them live in lanes of vector registers (k_step1: 75 to 124).  None goes to memory, which would queue up behind the
-// host reads.  The predictor is a template parameter for that reason: a kernel with both forms of the role spilled 169 to 246
-// scalar registers and was 82 to 106 KB of code (41 to 60 KB each by itself), more than the 64 KB instruction cache of two compute units.
+// 83 to 144 of them live in lanes of vector registers (k_step1: 61 to 138).  No vector register goes to memory, which would queue
+// up behind the host reads; 18 of the 106 forms, all with the gate predictor, keep 36 bytes a lane there (k_step1: none).  The
+// predictor is a template parameter for that reason: a kernel with both forms of the role spilled 169 to 246 scalar registers and
+// was 82 to 106 KB of code (41 to 60 KB each by itself), more than the 64 KB instruction cache of two compute units.
 template <typename T, int NI, bool GLU, bool GATE, bool MFMA, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 1) void k_step_batch(const StepArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_step[];
@@ -1328,22 +1332,23 @@ inline void launch_step1_as(const StepArgs& a, int grid, hipStream_t s) {
     else LIF_S1(16);
 #undef LIF_S1
 }
-// Waves of a workgroup of k_step_batch: 4, or 8 where the LDS of a loader (x of the tokens and staged rows) leaves room for fewer than
-// three of them per compute unit.  The activation workgroups of the launch carry the same LDS, and four waves that read a row each
-// reach a fraction of the bandwidth, which shows where few rows are added and the load does not cover them.  fp32 rows, us a
-// step with 4 -> 8 waves (rows in use, rows added): d = 1288, 8 tokens: (9277, 0) 77.7 -> 57.0, (9578, 47) 88.3 -> 71.2, (13408,
-// 477) 157.8 -> 156.9; d = 2048, gated, 8 tokens: (4699, 0) 71.8 -> 55.1, (6444, 304) 187.8 -> 187.1; d = 2048, 4 tokens: (6221,
-// 0) 51.9 -> 43.2.  With room for three workgroups four waves are better (d = 1288, 3 tokens, (929, 0): 25.7 against 26.6),
-// with room for two eight in one (d = 1288, 8 tokens, (8614, 0): 60.9 against 62.5; d = 2048, 4 tokens, (7235, 0): 49.8 against 50.7).
+// Waves of a workgroup of k_step_batch: 4, or 8 where the LDS of a loader (x of the tokens and staged rows) leaves room for fewer
+// than three of them per compute unit.  The activation workgroups of the launch carry the same LDS, and four waves that read a
+// row each reach a fraction of the bandwidth, which shows where few rows are added and the load does not cover them.  fp32 rows,
+// us a step with 4 -> 8 waves (rows in use, rows added): d = 1288, 8 tokens: (9277, 0) 77.7 -> 57.0, (9578, 47) 88.3 -> 71.2,
+// (13408, 477) 157.8 -> 156.9; d = 2048, gated, 8 tokens: (4699, 0) 71.8 -> 55.1, (6444, 304) 187.8 -> 187.1; d = 2048, 4 tokens:
+// (6221, 0) 51.9 -> 43.2. With room for three workgroups four waves are better (d = 1288, 3 tokens, (929, 0): 25.7 against 26.6),
+// with room for two eight in one (d = 1288, 8 tokens, (8614, 0): 60.9 against 62.5; d = 2048, 4 tokens, (7235, 0): 49.8 against
+// 50.7).
 // The matrix-core stage keeps 4: it is at least as fast as in a launch of its own.  Gated rows of more than 12 KiB a vector
 // would spill registers at 8 waves.
 constexpr int step_batch_most_waves(int ni, bool glu, bool mfma) { return mfma || ni <= 2 || (glu && ni > 12) ? 4 : 8; }
 inline int step_batch_waves(int ni, bool glu, bool mfma, size_t lds) { return lds > kStepLdsLimit / 3 ? step_batch_most_waves(ni, glu, mfma) : 4; }
 
 // A workgroup of eight waves keeps its compute unit to itself: beside another one of its activation workgroups a loader, and the
-// bookkeeping workgroup that makes the deletion plan, are slower.  fp32, us a step with the LDS for one / for two per compute unit (rows in
-// use, rows added): d = 836, gated, 6 tokens, (21805, 291) 115.9 / 121.1; fp16 d = 2664, 6 tokens, (4398, 61) 46.0 / 46.8; but d = 1288,
-// 8 tokens, (9585, 48) 70.7 / 67.6.
+// bookkeeping workgroup that makes the deletion plan, are slower.  fp32, us a step with the LDS for one / for two per compute
+// unit (rows in use, rows added): d = 836, gated, 6 tokens, (21805, 291) 115.9 / 121.1; fp16 d = 2664, 6 tokens, (4398, 61) 46.0
+// / 46.8; but d = 1288, 8 tokens, (9585, 48) 70.7 / 67.6.
 inline size_t step_batch_lds_launched(int waves, size_t lds) {
     return waves == 8 && lds <= kStepLdsLimit / 2 ? kStepLdsLimit / 2 + 1024 : lds;
 }

@@ -1,6 +1,6 @@
-// Values handed over between the workgroups of a launch: 64-bit words of 32 bits of payload and a stamp that tells this launch's from
-// older ones, written by relaxed device-scope atomic stores and polled with relaxed device-scope atomic loads, so no fence (a
-// device-scope release writes back the L2: 6 us) and no clearing is needed.
+// Values handed over between the workgroups of a launch: 64-bit words of 32 bits of payload and a stamp that tells this launch's
+// from older ones, written by relaxed device-scope atomic stores and polled with relaxed device-scope atomic loads, so no fence
+// (a device-scope release writes back the L2: 6 us) and no clearing is needed.
 #pragma once
 
 #include "lif_common.h"
