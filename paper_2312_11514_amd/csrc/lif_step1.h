@@ -617,7 +617,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     } else {
         unsigned p[8];
         const int w0 = tid * wpt, nw = max(0, min(wpt, nwords - w0));
-        missing = !poll_words<8>(a.m_words + (size_t)(wg & (kWordReps - 1)) * a.m_pitch + 2 * w0, 1, 2 * nw, stamp_now,
+        missing = !poll_words<8, !GATE>(a.m_words + (size_t)(wg & (kWordReps - 1)) * a.m_pitch + 2 * w0, 1, 2 * nw, stamp_now,
                                       a.polls, p);
 #pragma unroll
         for (int i = 0; i < 4; ++i)

@@ -17,25 +17,37 @@ __device__ __forceinline__ unsigned long long word_load(const unsigned long long
 __device__ __forceinline__ void word_store(unsigned long long* p, unsigned stamp, unsigned payload) {
     __hip_atomic_store(p, ((unsigned long long)stamp << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Reads N words p[i * step] (i < n) of this stamp by the whole wave: all are requested before the first is looked at, and
-// again as a whole until every lane has its words or `polls` more reads have failed (read again one after the other, a
-// lane's second word cost a round trip of its own).  Returns whether all words of this lane have arrived.
-template <int N>
+// Reads N words p[i * step] (i < n) of this stamp by the whole wave: all are requested before the first is looked at, the missing
+// ones again until they have come or `polls` more reads have failed.  Returns whether all words of this lane have arrived.
+// TOGETHER: again as a whole until every lane has its words (one after the other, a lane's second word cost a round trip of its
+// own).  Else each word for itself: where words come over many microseconds, as those of the gate predictor do, reading all of
+// them again and again stands in the way of the reads they are waiting for (one token, d = 2376, gate resident, 542 rows, 41
+// added, 19 steps of a sequence 541.6 -> 537.5 us; Llama-2 shape, no rows added, 39.6 -> 39.2).
+template <int N, bool TOGETHER = true>
 __device__ __forceinline__ bool poll_words(const unsigned long long* p, int step, int n, unsigned stamp, int polls,
                                            unsigned (&out)[N]) {
+    unsigned long long w[N];
     bool all;
     for (int tries = 0;; ++tries) {
-        unsigned long long w[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) w[i] = (i < n) ? word_load(p + (size_t)i * step) : 0ull;
+        if (!TOGETHER) break;
         all = true;
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            all = all && (i >= n || (unsigned)(w[i] >> 32) == stamp);
-            out[i] = (unsigned)w[i];
-        }
+        for (int i = 0; i < N; ++i) all = all && (i >= n || (unsigned)(w[i] >> 32) == stamp);
         if (!__any(!all) || tries >= polls) break;
     }
+    if (!TOGETHER) {
+        all = true;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (i < n) {
+                for (int tries = 0; (unsigned)(w[i] >> 32) != stamp && tries < polls; ++tries) w[i] = word_load(p + (size_t)i * step);
+                all = all && (unsigned)(w[i] >> 32) == stamp;
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = (unsigned)w[i];
     return all;
 }
 
