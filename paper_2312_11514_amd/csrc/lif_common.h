@@ -143,6 +143,25 @@ __device__ __forceinline__ U uniform_load(const U* p) {
     return *reinterpret_cast<const __attribute__((address_space(4))) U*>(q);
 }
 
+// v to the 16 bytes at base + off, written through the L2 to memory; base is the same for the whole wave and off + 16 <= bytes.
+// A launch ends when every L2 has written back what it holds changed: the rows that a fused step has loaded and moved, a few MB, stood
+// in front of the down projection.  us a step, plain stores -> these: OPT shape 56.9 -> 56.2, Falcon shape 137.6 -> 136.4, Llama-2
+// shape from a graph 130.5 -> 129.4, gate resident 108.8 -> 106.6, 8 tokens 233.6 -> 232.5.  lif_load_bundles keeps plain stores: the
+// activation stage behind it finds the rows in the L2 (fp32 d = 1288, 3 tokens, four calls 68.6 against 69.2).  Partial outputs and
+// activations written through were no faster.
+template <typename V>
+__device__ __forceinline__ void store_through(char* base, unsigned off, unsigned bytes, V v) {
+    static_assert(sizeof(V) == 16, "four dwords");
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    constexpr int kFlags = 0x00027000, kWriteThrough = 1 << 4;    // a raw buffer of dwords; the cache policy bit sc1
+    const unsigned long long u = reinterpret_cast<unsigned long long>(base);
+    const unsigned long long q = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32)) << 32) |
+                                 (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v),
+                                           __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(q), 0, (int)bytes, kFlags), (int)off, 0,
+                                           kWriteThrough);
+}
+
 // Workgroup barrier that orders LDS accesses only: unlike __syncthreads() it does not wait for the global
 // stores a wave has in flight (their acknowledgement from the L2 costs several hundred nanoseconds).  Use it
 // where the data handed over lives in LDS and no thread reads global memory that another one has just written.

@@ -575,7 +575,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         const unsigned off = lane_bytes();
 #pragma unroll
         for (int it = 0; it < NI; ++it)
-            if (it < full_pieces(NI) || off + it * 1024u < (unsigned)vec_bytes) *reinterpret_cast<V*>(p + (off + it * 1024u)) = v[it];
+            if (it < full_pieces(NI) || off + it * 1024u < (unsigned)vec_bytes) store_through(p, off + it * 1024u, (unsigned)vec_bytes, v[it]);
     };
     // (the second vector of a unit exists only in its activation part, a third one only in unsplit gated bundles)
     auto in_part = [&](int g, int part) { return part ? g == 0 : true; };
