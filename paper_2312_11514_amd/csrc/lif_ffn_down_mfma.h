@@ -58,11 +58,14 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // reductions.  All workgroups are resident at once (three per compute unit need at most 168 registers, which the launch
 // bound asks for), so the prologue is not hidden by other workgroups; where every row is read it overlaps with the first
 // quarter of the rows: 10976 rows, 8 tokens, d = 4096, gated, activations and down projection 63.3 -> 60.2 us.
+// The sums of the waves and the two halves of the token slots meet in LDS as 16-byte pieces: by 32 lane exchanges and as many
+// read-add-writes of 4 bytes per lane it took 2.0 us from the last row to the last sum, twelve waves sharing the LDS of a unit; now
+// 0.7.  us a pass: d = 4096, gated, 8 tokens, 10976 rows, both stages 59.2 -> 57.9; 12 passes of 5 tokens, OPT shape, 2339 -> 2313.
 // grid = (ceil(d / 128) column slices, row-chunk workgroups), block = WAVES waves; lane l of a wave: column
 // group n16 = l mod 16 (8 columns) and token slot n16, row block q = l div 16 (8 of the 32 rows of an instruction).
 // A pass compacts the contributing rows of ROWS slots (SKIP: rows with some activation; else all rows in use) in a
 // fixed order (thread-major over slots p * threads + tid); the waves take groups of 32 compacted rows in turn.
-// A chunk's passes are added in order, the waves in wave order, the chunks in chunk order (by this kernel when
+// The waves of a pass are added in wave order, a chunk's passes in order, the chunks in chunk order (by this kernel when
 // one workgroup row is launched, else by k_ffn_down_mfma_finish from ypart[chunk][token][d]).  Nothing depends on
 // the launch geometry.
 template <bool SKIP, int WAVES, int ROWS, bool FUSED>
@@ -75,13 +78,12 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
     constexpr int PER = ROWS / T;                    // slots per thread in the compaction
     constexpr int kPitch = ROWS + 8;                 // fp16 values per token slot in LDS (16 bytes of padding: lanes of one
                                                      // row block read 16 different slots at the same offset)
-    constexpr int OUTS = BT * kDmCols / T;           // outputs per thread
-    static_assert(ROWS % T == 0 && (BT * kDmCols) % T == 0, "whole slots and outputs per thread");
+    static_assert(ROWS % T == 0 && BT * kDmCols == 4 * T, "whole slots and one column of four tokens per thread");
     __shared__ int list[ROWS];
     __shared__ __attribute__((aligned(16))) _Float16 hv[16][kPitch];
     __shared__ int wave_tot[WAVES];
     __shared__ float wave_max[WAVES];
-    __shared__ float red[WAVES][32][33];             // per wave and lane with q < 2: 32 sums, padded
+    __shared__ f32x4 red[WAVES][8][64];              // per wave, column of a lane's 8, and lane: sums of four token slots
     __shared__ int n_active;
 
     if (FUSED && (int)blockIdx.x == slices) {
@@ -133,17 +135,12 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
     const int chunks = down_mfma_chunks(n, chunk_rows);
     if ((int)blockIdx.y >= chunks) return;           // uniform
 
-    float total[OUTS];                               // thread tid finishes outputs tid + k * T of the 8 tokens x 128 columns
-#pragma unroll
-    for (int k = 0; k < OUTS; ++k) total[k] = 0.f;
+    const int oc = tid & (kDmCols - 1), og = tid / kDmCols, ocol = blockIdx.x * kDmCols + oc;     // this thread finishes column oc
+    f32x4 total = {0.f, 0.f, 0.f, 0.f};                                                           //  of tokens 4 og .. 4 og + 3
 
     for (int chunk = blockIdx.y; chunk < chunks; chunk += gridDim.y) {
         const int r0 = chunk * chunk_rows, r1 = min(n, r0 + chunk_rows);
-        // red[w][lane with q < 2][j * 4 + r]: this wave's sum for tokens 4q + r, column j of the lane's 8
-        if (q < 2) {
-#pragma unroll
-            for (int i = 0; i < 32; ++i) red[w][lane][i] = 0.f;
-        }
+        f32x4 part = {0.f, 0.f, 0.f, 0.f};
         for (int s_base = r0; s_base < r1; s_base += ROWS) {
             // compaction of the rows that contribute and the largest |activation| of the pass
             unsigned flags = 0, nonzero = 0;
@@ -233,38 +230,34 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
                     g += WAVES;
                     if (g * 32 < cnt) load(g, cnt, row);
                 }
-                // token slots 8..15 (lanes with q >= 2) hold the low-part products of tokens 0..7: add them; the
-                // passes of a chunk add up in the wave's own LDS entries (0 + first pass is exact)
+                // The waves took different rows, and token slots 8..15 (lanes with q >= 2) hold the low-part products of tokens 0..7:
+                // all of them are added through LDS, the waves in wave order.  (The 16-byte places of odd columns are swapped by
+                // eight, so that the columns that a wave reads side by side fall on different banks.)
+                auto place = [](int j, int l) { return l ^ ((j & 1) << 3); };
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
+                for (int j = 0; j < 8; ++j) red[w][j][place(j, lane)] = acc[j];
+                lds_barrier();
+                f32x4 sum;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float lo = __shfl_down(acc[j][r], 32, kWave);
-                        if (q < 2) red[w][lane][j * 4 + r] += (acc[j][r] + lo) * inv_scale;
-                    }
+                for (int ww = 0; ww < WAVES; ++ww) {
+                    const f32x4* from = red[ww][oc & 7];
+                    const int l = og * 16 + (oc >> 3);
+                    const f32x4 v = (from[place(oc, l)] + from[place(oc, l + 32)]) * inv_scale;
+                    sum = ww ? sum + v : v;
+                }
+                part += sum;                         // (0 + first pass is exact)
             }
             const int next = s_base + ROWS < r1 ? s_base + ROWS
                                                    : chunk + (int)gridDim.y < chunks ? (chunk + (int)gridDim.y) * chunk_rows : -1;
             if (next >= 0) request(next);
         }
-        // the waves took different rows: add in wave order
-        __syncthreads();
+        if (chunks > 1 && gridDim.y > 1) {
 #pragma unroll
-        for (int k = 0; k < OUTS; ++k) {
-            const int o = tid + k * T;               // token o / 128, column o % 128 of the slice
-            const int t = o >> 7, c = o & 127;
-            const int src_lane = (t >> 2) * 16 + (c >> 3), src = (c & 7) * 4 + (t & 3);
-            float sum = red[0][src_lane][src];
-#pragma unroll
-            for (int ww = 1; ww < WAVES; ++ww) sum += red[ww][src_lane][src];
-            const int ocol = blockIdx.x * kDmCols + c;
-            if (chunks > 1 && gridDim.y > 1) {
-                if (t < batch && ocol < d) ypart[((size_t)chunk * batch + t) * d + ocol] = sum;
-            } else {
-                total[k] += sum;                     // chunk order; 0 + first sum is exact
-            }
+            for (int r = 0; r < 4; ++r)
+                if (og * 4 + r < batch && ocol < d) ypart[((size_t)chunk * batch + og * 4 + r) * d + ocol] = part[r];
+        } else {
+            total += part;                           // chunk order; 0 + first sum is exact
         }
-        __syncthreads();                             // red is written again by the next chunk
     }
     if (blockIdx.x == 0 && tid == 0) {
         if (blockIdx.y == 0) {
@@ -275,11 +268,8 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
     }
     if (chunks == 1 || gridDim.y == 1) {
 #pragma unroll
-        for (int k = 0; k < OUTS; ++k) {
-            const int o = tid + k * T;
-            const int t = o >> 7, ocol = blockIdx.x * kDmCols + (o & 127);
-            if (t < batch && ocol < d) y[(size_t)t * d + ocol] = (_Float16)total[k];
-        }
+        for (int r = 0; r < 4; ++r)
+            if (og * 4 + r < batch && ocol < d) y[(size_t)(og * 4 + r) * d + ocol] = (_Float16)total[r];
     }
 }
 
