@@ -543,17 +543,19 @@ hipError_t launch_step_batch(lif_layer* L, StepArgs a, bool allow, hipStream_t s
 
 void launch_ffn_up_mfma(lif_layer* L, const void* x, int batch, float* h, hipStream_t s) {
     const lif_config& c = L->cfg;
-    constexpr int W = kMfmaWavesAll;
     // with a row-count hint the grid is sized to it (a workgroup strides on if more rows are in use) and every
     // workgroup asks for its first rows before the count arrives
     const int spec = L->expected_rows > 0 ? 1 : 0;
     const int grid = spec ? mfma_hint_tiles(L) : (c.capacity_rows + 15) / 16;
-#define LIF_UM(GLU)                                                                                          \
+    const bool few = spec && up_mfma_waves(grid, c.d_model) == kMfmaWavesFew;      // (without a hint most tiles are likely not in use)
+#define LIF_UM(GLU, W)                                                                                       \
     hipLaunchKernelGGL((k_ffn_up_mfma<GLU, W>), dim3(grid), dim3(W * 64), 0, s, (const _Float16*)L->buf.matrix,  \
                        L->buf.bias, (const _Float16*)x, h, c.d_model, batch, c.capacity_rows, L->row_elems,        \
                        L->buf.pointers, L->gact, c.d_ffn, spec, L->st)
-    if (c.glu) LIF_UM(true);
-    else LIF_UM(false);
+    if (c.glu && few) LIF_UM(true, kMfmaWavesFew);
+    else if (c.glu) LIF_UM(true, kMfmaWavesAll);
+    else if (few) LIF_UM(false, kMfmaWavesFew);
+    else LIF_UM(false, kMfmaWavesAll);
 #undef LIF_UM
 }
 

@@ -51,13 +51,23 @@ __device__ __forceinline__ float tree_sum(float (&v)[WAVES]) {
 // that way, passes the up rows and then the gate rows through its own LDS area (rows padded by 16 bytes: the
 // b128 reads of 16 lanes then fall on 16 distinct bank groups) and reads the fragments back from there; the
 // registers are refilled with the next stage as soon as they are written out, across part boundaries too.
-// Every number of waves gives the same bits.  With 8 waves a tile takes
-// half the dependent stages per wave: 7.7 us against 10 us at 1400 rows, 26 us against 27 us at 8700.
+// Every number of waves gives the same bits (up_mfma_waves chooses).
 // `spec`: the first stage is requested before the row count arrives (the addresses of slots [0, capacity) are
 // always valid); the host sets it for the tiles a row-count hint covers.
 constexpr int kStageSteps = 4;                           // k-steps per stage: 256 bytes of a row
 constexpr int kStagePitch = kStageSteps * 64 + 16;       // bytes between the staged rows of a wave
-constexpr int kMfmaWavesAll = 8;                         // waves per tile of the stand-alone pass over all rows
+
+// Waves per tile of the stand-alone pass over all rows.  With 8 a tile takes half the dependent stages per wave (7.7 us against 10
+// us at 1400 rows) but two workgroups fill a compute unit: more than 512 tiles take a second round on the chip, in which most of it
+// is idle.  Of 4 waves three workgroups and more are resident.  One FFN call of 8 tokens, us, 8 -> 4 waves: d = 4096 11803 rows 49.4
+// -> 43.2, 16290 rows 73.6 -> 69.9, gated, 10989 rows, all read, 57.9 -> 56.7; d = 1024 10422 rows 21.4 -> 18.7; d = 2048 16294 rows
+// 42.9 -> 41.6, gated 9414 rows 30.7 -> 29.9; d = 512 13195 rows 19.6 -> 18.2; up to 512 tiles mostly the other way round: d = 4096
+// 2545 rows 15.4 against 17.4, d = 3072 5447 rows 19.0 against 19.5 (but 7828 rows 27.8 against 25.9).  Rows of more than 16 parts of
+// two stages are slower with 4 at any number (d = 5120, gated, 6 tokens, 8775 rows 61.5 against 62.4).
+constexpr int kMfmaWavesFew = 4, kMfmaWavesAll = 8, kMfmaTilesAll = 2 * 256;
+inline int up_mfma_waves(int likely_tiles, int d) {
+    return likely_tiles > kMfmaTilesAll && d <= kMfmaParts * 2 * kStageSteps * 32 ? kMfmaWavesFew : kMfmaWavesAll;
+}
 
 // LDS of ffn_up_mfma_tile_staged
 constexpr int mfma_staged_lds(bool glu, int waves) { return waves * 16 * kStagePitch + (glu ? 2 : 1) * waves * 64 * 4 * 4; }
@@ -210,7 +220,7 @@ __device__ __forceinline__ bool ffn_up_mfma_tile_staged(const _Float16* __restri
 }
 
 template <bool GLU, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void k_ffn_up_mfma(const _Float16* __restrict__ matrix,
+__global__ __launch_bounds__(WAVES * 64, WAVES == kMfmaWavesFew ? 3 : 4) void k_ffn_up_mfma(const _Float16* __restrict__ matrix,
                                                                  const float* __restrict__ bias,
                                                                  const _Float16* __restrict__ x, float* __restrict__ h,
                                                                  int d, int batch, int capacity, size_t row_elems,
