@@ -247,6 +247,7 @@ void launch_predict_gate(lif_layer* L, const void* x, int batch, uint8_t* masks,
     if (ni <= 1) LIF_PG(1);
     else if (ni <= 2) LIF_PG(2);
     else if (ni <= 4) LIF_PG(4);
+    else if (ni <= 6) LIF_PG(6);           // (full_pieces)
     else if (ni <= 8) LIF_PG(8);
     else if (ni <= 9) LIF_PG(9);
     else if (ni <= 12) LIF_PG(12);

@@ -16,18 +16,60 @@
 
 namespace lif {
 
-// acc + sum_q a[q] * b[q] with every product and sum in fp64.  A product of two fp16 values is exact in fp32
-// (22 significant bits, exponents far inside the fp32 range), so for fp16 it is formed there and widened once:
-// the same bits as widening both factors, at half the conversions.
-__device__ __forceinline__ double dot_f64(f16x8 a, f16x8 b, double acc) {
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+
+// acc[r] + sum_q a[r][q] * b[q] with every product and sum in fp64, for R rows at a time.  A product of two fp16 values is exact in
+// fp32 (22 significant bits, exponents far inside the fp32 range), so for fp16 it is formed there and widened once: the same bits
+// as widening both factors, at half the conversions.  One instruction forms it, which the compiler does not use by itself (a
+// product of -0 becomes +0, which changes no sum that begins with +0).
+// The compiler is held to the order products, conversions, sums: left to itself it has every sum wait for its own conversion.
+__device__ __forceinline__ void in_order() { __builtin_amdgcn_sched_barrier(0x94); }      // (scalar, memory and LDS operations may pass)
+template <int R>
+__device__ __forceinline__ void dot_f64(const f16x8 (&a)[R], f16x8 b, double (&acc)[R]) {
+    float p[R][8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc += (double)((float)a[q] * (float)b[q]);
-    return acc;
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < 8; q += 2) {
+            const f16x2 ap = {a[r][q], a[r][q + 1]}, bp = {b[q], b[q + 1]};
+            asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,1,0]" : "=v"(p[r][q]) : "v"(ap), "v"(bp));
+            asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,1,0] op_sel_hi:[1,1,0]" : "=v"(p[r][q + 1]) : "v"(ap), "v"(bp));
+        }
+    in_order();
+    double w[R][8];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[r][q] = (double)p[r][q];
+    in_order();
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] += w[r][q];
+    in_order();
 }
-__device__ __forceinline__ double dot_f64(f32x4 a, f32x4 b, double acc) {
+template <int R>
+__device__ __forceinline__ void dot_f64(const f32x4 (&a)[R], f32x4 b, double (&acc)[R]) {
+    double w[R][4], x[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc = __builtin_fma((double)a[q], (double)b[q], acc);
-    return acc;
+    for (int q = 0; q < 4; ++q) {
+        x[q] = (double)b[q];
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[r][q] = (double)a[r][q];
+    }
+    in_order();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = __builtin_fma(w[r][q], x[q], acc[r]);
+    in_order();
+}
+template <typename V>
+__device__ __forceinline__ double dot_f64(V a, V b, double acc) {
+    const V row[1] = {a};
+    double sum[1] = {acc};
+    dot_f64<1>(row, b, sum);
+    return sum[0];
 }
 
 constexpr int kMaskCols = 8;       // mask bytes (groups of 8 neurons) per workgroup of predict_mask
@@ -318,6 +360,83 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask_long(const T* __restric
         step_mask[byte] = (uint8_t)(((ors[0] | ors[1]) | (ors[2] | ors[3])) >> (8 * lane));
 }
 
+// pieces of 1 KiB that every vector served by this NI has in full (NI in 1, 2, 4, 6, 8, 9, 12, 16: the least that covers a vector)
+constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ? 2 : ni <= 6 ? 4 : ni <= 8 ? 6 : ni <= 9 ? 8 : ni <= 12 ? 9 : 12; }
+
+// relu(gate_i . x + b_i) and the mask bits of the 8 neurons of a mask byte by one wave, x in registers (0 past the end).
+// R rows at a time are worked on, each register set asked for again, for the row R further, as soon as its row is done. The sums of
+// the R rows cross the wave together, in the tree of wave_sum: lanes 1, 2, 4 apart, then 8, 16, 32; from 8 on every exchange halves
+// the rows of a lane, as far as it has several.
+// What bounds it: HBM, and next to it 64 conversions to fp64 a lane and row, each as long as four multiply-adds; in a wave of its own
+// on a SIMD every wait shows.  With sums that wait for their own conversion and one row at a time a step of the gated shape d = 4096,
+// F = 11008 took 114.7 us, with two rows interleaved by the compiler and no row on its way meanwhile 107.1, now 105.7.  Tokens of a
+// batch (one row at a time from LDS, the same order): four calls, d = 1496, F = 19864, 8 tokens 182.7 -> 174.4; d = 1232, F = 11728, 6
+// tokens 107.3 -> 101.3.
+template <typename T, int NI>
+__device__ __forceinline__ unsigned gate_byte(const T* __restrict__ Wg, const float* __restrict__ b, float* __restrict__ gact, int grp,
+                                              int nvec, const typename Vec<T>::type (&xr)[NI], double th) {
+    using V = typename Vec<T>::type;
+    constexpr int R = NI <= 9 ? 4 : 2;
+    const int lane = threadIdx.x & 63, owner = R == 4 ? ((lane >> 3) & 1) * 2 + ((lane >> 4) & 1) : (lane >> 3) & 1;
+    const V* rows = reinterpret_cast<const V*>(Wg) + (size_t)grp * 8 * nvec;
+    float bias[8 / R];
+#pragma unroll
+    for (int r = 0; r < 8 / R; ++r) bias[r] = b[grp * 8 + r * R + owner];
+    V g[R][NI];
+    auto request = [&](V (&v)[NI], int e) {
+#pragma unroll
+        for (int it = 0; it < NI; ++it) v[it] = rows[(size_t)e * nvec + (it < full_pieces(NI) ? it * 64 + lane : min(it * 64 + lane, nvec - 1))];
+    };
+#pragma unroll
+    for (int u = 0; u < R; ++u) request(g[u], u);
+    unsigned byte = 0;
+    auto round = [&](int e0, auto more) {
+        double v[R];
+#pragma unroll
+        for (int u = 0; u < R; u += 2) {
+            double sum[2] = {0.0, 0.0};
+#pragma unroll
+            for (int it = 0; it < NI; ++it) {
+                const bool in = it < full_pieces(NI) || it * 64 + lane < nvec;
+                const V pair[2] = {in ? g[u][it] : V(0), in ? g[u + 1][it] : V(0)};
+                dot_f64<2>(pair, xr[it], sum);
+            }
+            v[u] = sum[0];
+            v[u + 1] = sum[1];
+            if constexpr (decltype(more)::value) {
+                request(g[u], e0 + R + u);
+                request(g[u + 1], e0 + R + u + 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);       // (the products of a row need the registers that those of the one before had)
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) v[u] += dpp_from<0xB1, 0xf>(v[u]);       // quad_perm 1 0 3 2
+#pragma unroll
+        for (int u = 0; u < R; ++u) v[u] += dpp_from<0x4E, 0xf>(v[u]);       // quad_perm 2 3 0 1
+#pragma unroll
+        for (int u = 0; u < R; ++u) v[u] += dpp_from<0x141, 0xf>(v[u]);      // half row mirrored: the other quad, all of whose lanes are alike
+        const bool up = (lane & 8) != 0;
+#pragma unroll
+        for (int u = 0; u < R / 2; ++u) {
+            const double send = up ? v[u] : v[u + R / 2], keep = up ? v[u + R / 2] : v[u];
+            v[u] = keep + dpp_from<0x128, 0xf>(send);
+        }
+        double a = swap_add<16>(v[0], v[R == 4 ? 1 : 0]);
+        float bi = bias[0];
+#pragma unroll
+        for (int r = 1; r < 8 / R; ++r) bi = e0 == r * R ? bias[r] : bi;
+        a = swap_add<32>(a, a) + (double)bi;
+        const unsigned long long fires = __ballot(a > th);
+#pragma unroll
+        for (int u = 0; u < R; ++u) byte |= (unsigned)(fires >> (R == 4 ? (u >> 1) * 8 + (u & 1) * 16 : u * 8) & 1u) << (e0 + u);
+        if ((lane & (R == 4 ? 0x27 : 0x37)) == 0) gact[grp * 8 + e0 + owner] = (float)(a > 0.0 ? a : 0.0);
+    };
+#pragma unroll 1
+    for (int e0 = 0; e0 < 8 - R; e0 += R) round(e0, std::true_type());
+    round(8 - R, std::false_type());
+    return byte;
+}
+
 // Gate projection as the predictor (Appendix, Llama 2, "Alternative approaches"): the gate matrix stays
 // resident and  a_i = gate_i . x + b_i  decides exactly which neurons fire (mask bit = a_i > theta); the same
 // pass leaves relu(a_i) per token and neuron for the FFN, so bundles hold only up row | down column.
@@ -354,6 +473,14 @@ __global__ __launch_bounds__(256) void k_predict_gate(const T* __restrict__ Wg, 
     const double th = (double)theta;
     const int mask_stride = F >> 3;
     for (int grp = gw; grp * 8 < F; grp += nw) {
+        if constexpr (XREG) {
+            const unsigned byte = gate_byte<T, NI>(Wg, b, gact, __builtin_amdgcn_readfirstlane(grp), nvec, xr, th);
+            if (lane == 0) {
+                mask[grp] = (uint8_t)byte;
+                if (step_mask != mask) step_mask[grp] = (uint8_t)byte;   // one token: the step mask is the mask
+            }
+            continue;
+        }
         unsigned long long bits = 0;                 // bit 8 * token + e: neuron grp * 8 + e fires for that token
 #pragma unroll 2
         for (int e = 0; e < 8; ++e) {
@@ -366,13 +493,12 @@ __global__ __launch_bounds__(256) void k_predict_gate(const T* __restrict__ Wg, 
                 g[it] = (idx < nvec) ? row[idx] : V(0);
             }
             const double bi = (double)b[i];
-            for (int t = 0; t < (XREG ? 1 : batch); ++t) {
+            for (int t = 0; t < batch; ++t) {
                 double acc = 0.0;
 #pragma unroll
                 for (int it = 0; it < NI; ++it) {
                     const int idx = it * 64 + lane;
-                    if (XREG) acc = dot_f64(g[it], xr[it], acc);          // both are 0 past the end of the vector
-                    else if (idx < nvec) acc = dot_f64(g[it], xs[t * nvec + idx], acc);
+                    if (idx < nvec) acc = dot_f64(g[it], xs[t * nvec + idx], acc);
                 }
                 acc = wave_sum(acc);
                 const double a = acc + bi;
@@ -380,19 +506,12 @@ __global__ __launch_bounds__(256) void k_predict_gate(const T* __restrict__ Wg, 
                 if (lane == 0) gact[(size_t)t * F + i] = (float)(a > 0.0 ? a : 0.0);
             }
         }
-        if (XREG) {
-            if (lane == 0) {
-                mask[grp] = (uint8_t)bits;
-                if (step_mask != mask) step_mask[grp] = (uint8_t)bits;   // one token: the step mask is the mask
-            }
-        } else {
-            if (lane < batch) mask[(size_t)lane * mask_stride + grp] = (uint8_t)(bits >> (8 * lane));
-            if (lane == 0) {
-                unsigned long long o = bits | (bits >> 32);
-                o |= o >> 16;
-                o |= o >> 8;
-                step_mask[grp] = (uint8_t)o;
-            }
+        if (lane < batch) mask[(size_t)lane * mask_stride + grp] = (uint8_t)(bits >> (8 * lane));
+        if (lane == 0) {
+            unsigned long long o = bits | (bits >> 32);
+            o |= o >> 16;
+            o |= o >> 8;
+            step_mask[grp] = (uint8_t)o;
         }
     }
 }

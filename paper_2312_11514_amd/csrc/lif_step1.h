@@ -113,14 +113,6 @@ struct PredictLds {
     int missing[4];                  // per wave: a word did not arrive
 };
 
-// x . row of the gate projection (the whole wave; every lane returns the sum), in the order of k_predict_gate
-template <typename T, int NI>
-__device__ __forceinline__ double column_dot(const typename Vec<T>::type (&a)[NI], const typename Vec<T>::type (&xr)[NI]) {
-    double acc = 0.0;
-#pragma unroll
-    for (int it = 0; it < NI; ++it) acc = dot_f64(a[it], xr[it], acc);
-    return wave_sum(acc);
-}
 template <typename T, int NI>
 __device__ __forceinline__ void load_vec(typename Vec<T>::type (&v)[NI], const T* p, int nvec, int lane) {
     using V = typename Vec<T>::type;
@@ -131,7 +123,7 @@ __device__ __forceinline__ void load_vec(typename Vec<T>::type (&v)[NI], const T
     }
 }
 
-// The same sum straight from memory, for the rare case that a wait ran out: few registers instead of loads in flight
+// x . column straight from memory, for the rare case that a wait ran out: few registers instead of loads in flight
 template <typename T>
 __device__ __forceinline__ double column_dot_slow(const T* col, const T* x, int first, int end, int lane) {
     using V = typename Vec<T>::type;
@@ -292,23 +284,6 @@ __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, Predi
 
 // Gate predictor: relu(gate_i . x + b_i) and the mask bit of 8 neurons per wave, as k_predict_gate for one token.
 template <typename T, int NI>
-__device__ __forceinline__ unsigned gate_byte(const StepArgs& a, int grp, const typename Vec<T>::type (&xr)[NI]) {
-    using V = typename Vec<T>::type;
-    const int lane = threadIdx.x & 63, nvec = a.d / Vec<T>::N;
-    const double th = (double)a.theta;
-    unsigned bits = 0;
-#pragma unroll 2
-    for (int e = 0; e < 8; ++e) {
-        const int i = grp * 8 + e;
-        V g[NI];
-        load_vec<T, NI>(g, (const T*)a.A + (size_t)i * a.d, nvec, lane);
-        const double v = column_dot<T, NI>(g, xr) + (double)a.b[i];
-        if (v > th) bits |= 1u << e;
-        if (lane == 0) a.gact[i] = (float)(v > 0.0 ? v : 0.0);
-    }
-    return bits;
-}
-template <typename T, int NI>
 __device__ __forceinline__ void gate_role(const StepArgs& a, int block, unsigned* lds) {
     using V = typename Vec<T>::type;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -320,7 +295,7 @@ __device__ __forceinline__ void gate_role(const StepArgs& a, int block, unsigned
     const int grp = block * 4 + wave;
     unsigned byte = 0;
     if (grp * 8 < a.F) {
-        byte = gate_byte<T, NI>(a, grp, xr);
+        byte = gate_byte<T, NI>((const T*)a.A, a.b, a.gact, grp, a.d / Vec<T>::N, xr, (double)a.theta);
         if (lane == 0) {
             a.masks[grp] = (uint8_t)byte;
             a.step_mask[grp] = (uint8_t)byte;
@@ -330,9 +305,6 @@ __device__ __forceinline__ void gate_role(const StepArgs& a, int block, unsigned
     __syncthreads();
     if (tid < kWordReps) word_store(a.m_words + (size_t)tid * a.m_pitch + block, now, lds[0] | lds[1] | lds[2] | lds[3]);
 }
-
-// pieces of 1 KiB that every vector served by this NI has in full (launch_step1_as)
-constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ? 2 : ni <= 6 ? 4 : ni <= 8 ? 6 : ni <= 9 ? 8 : ni <= 12 ? 9 : 12; }
 
 // ---- window, deletion plan, loaders ----------------------------------------------------------------------------
 
