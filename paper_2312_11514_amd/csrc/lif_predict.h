@@ -364,24 +364,24 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask_long(const T* __restric
 constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ? 2 : ni <= 6 ? 4 : ni <= 8 ? 6 : ni <= 9 ? 8 : ni <= 12 ? 9 : 12; }
 
 // relu(gate_i . x + b_i) and the mask bits of the 8 neurons of a mask byte by one wave, x in registers (0 past the end).
-// R rows at a time are worked on, each register set asked for again, for the row R further, as soon as its row is done. The sums of
-// the R rows cross the wave together, in the tree of wave_sum: lanes 1, 2, 4 apart, then 8, 16, 32; from 8 on every exchange halves
-// the rows of a lane, as far as it has several.
+// Four rows at a time are worked on, two of them side by side, whose registers are asked for again, for the rows four further, as soon
+// as they are done. The sums of the four cross the wave together, in the tree of wave_sum: lanes 1, 2, 4 apart, then 8, 16, 32; at 8
+// and 16 the rows of a lane are halved.
 // What bounds it: HBM, and next to it 64 conversions to fp64 a lane and row, each as long as four multiply-adds; in a wave of its own
 // on a SIMD every wait shows.  With sums that wait for their own conversion and one row at a time a step of the gated shape d = 4096,
-// F = 11008 took 114.7 us, with two rows interleaved by the compiler and no row on its way meanwhile 107.1, now 105.7.  Tokens of a
+// F = 11008 took 114.7 us, with two rows interleaved by the compiler and no row on its way meanwhile 107.1, now 105.7; d = 2048,
+// F = 8192 44.3 -> 41.1, d = 4544, F = 6000 61.5 -> 57.2.  With two rows at a time the widest have none on their way while two are worked
+// on: d = 5120, F = 8192 77.7 -> 84.4, with four 74.7; fp32 d = 2600, F = 6000 62.8 -> 68.1, with four 59.5.  Tokens of a
 // batch (one row at a time from LDS, the same order): four calls, d = 1496, F = 19864, 8 tokens 182.7 -> 174.4; d = 1232, F = 11728, 6
 // tokens 107.3 -> 101.3.
 template <typename T, int NI>
 __device__ __forceinline__ unsigned gate_byte(const T* __restrict__ Wg, const float* __restrict__ b, float* __restrict__ gact, int grp,
-                                              int nvec, const typename Vec<T>::type (&xr)[NI], double th) {
+                                              int nvec, typename Vec<T>::type (&xr)[NI], double th) {
     using V = typename Vec<T>::type;
-    constexpr int R = NI <= 9 ? 4 : 2;
-    const int lane = threadIdx.x & 63, owner = R == 4 ? ((lane >> 3) & 1) * 2 + ((lane >> 4) & 1) : (lane >> 3) & 1;
+    constexpr int R = 4;
+    const int lane = threadIdx.x & 63, owner = ((lane >> 3) & 1) * 2 + ((lane >> 4) & 1);
     const V* rows = reinterpret_cast<const V*>(Wg) + (size_t)grp * 8 * nvec;
-    float bias[8 / R];
-#pragma unroll
-    for (int r = 0; r < 8 / R; ++r) bias[r] = b[grp * 8 + r * R + owner];
+    const float bias0 = b[grp * 8 + owner], bias1 = b[grp * 8 + R + owner];
     V g[R][NI];
     auto request = [&](V (&v)[NI], int e) {
 #pragma unroll
@@ -391,6 +391,8 @@ __device__ __forceinline__ unsigned gate_byte(const T* __restrict__ Wg, const fl
     for (int u = 0; u < R; ++u) request(g[u], u);
     unsigned byte = 0;
     auto round = [&](int e0, auto more) {
+#pragma unroll
+        for (int it = 0; it < NI; ++it) asm volatile("" : "+v"(xr[it]));      // (else x is widened once, and twice as many registers kept)
         double v[R];
 #pragma unroll
         for (int u = 0; u < R; u += 2) {
@@ -421,19 +423,15 @@ __device__ __forceinline__ unsigned gate_byte(const T* __restrict__ Wg, const fl
             const double send = up ? v[u] : v[u + R / 2], keep = up ? v[u + R / 2] : v[u];
             v[u] = keep + dpp_from<0x128, 0xf>(send);
         }
-        double a = swap_add<16>(v[0], v[R == 4 ? 1 : 0]);
-        float bi = bias[0];
-#pragma unroll
-        for (int r = 1; r < 8 / R; ++r) bi = e0 == r * R ? bias[r] : bi;
-        a = swap_add<32>(a, a) + (double)bi;
+        double a = swap_add<16>(v[0], v[1]);
+        a = swap_add<32>(a, a) + (double)(e0 ? bias1 : bias0);
         const unsigned long long fires = __ballot(a > th);
 #pragma unroll
-        for (int u = 0; u < R; ++u) byte |= (unsigned)(fires >> (R == 4 ? (u >> 1) * 8 + (u & 1) * 16 : u * 8) & 1u) << (e0 + u);
-        if ((lane & (R == 4 ? 0x27 : 0x37)) == 0) gact[grp * 8 + e0 + owner] = (float)(a > 0.0 ? a : 0.0);
+        for (int u = 0; u < R; ++u) byte |= (unsigned)(fires >> ((u >> 1) * 8 + (u & 1) * 16) & 1u) << (e0 + u);
+        if ((lane & 0x27) == 0) gact[grp * 8 + e0 + owner] = (float)(a > 0.0 ? a : 0.0);
     };
-#pragma unroll 1
-    for (int e0 = 0; e0 < 8 - R; e0 += R) round(e0, std::true_type());
-    round(8 - R, std::false_type());
+    round(0, std::true_type());
+    round(R, std::false_type());
     return byte;
 }
 
