@@ -364,52 +364,59 @@ __global__ __launch_bounds__(256, 1) void k_predict_mask_long(const T* __restric
 constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ? 2 : ni <= 6 ? 4 : ni <= 8 ? 6 : ni <= 9 ? 8 : ni <= 12 ? 9 : 12; }
 
 // relu(gate_i . x + b_i) and the mask bits of the 8 neurons of a mask byte by one wave, x in registers (0 past the end).
-// Four rows at a time are worked on, two of them side by side, whose registers are asked for again, for the rows four further, as soon
-// as they are done. The sums of the four cross the wave together, in the tree of wave_sum: lanes 1, 2, 4 apart, then 8, 16, 32; at 8
-// and 16 the rows of a lane are halved.
-// What bounds it: HBM, and next to it 64 conversions to fp64 a lane and row, each as long as four multiply-adds; in a wave of its own
-// on a SIMD every wait shows.  With sums that wait for their own conversion and one row at a time a step of the gated shape d = 4096,
-// F = 11008 took 114.7 us, with two rows interleaved by the compiler and no row on its way meanwhile 107.1, now 105.7; d = 2048,
-// F = 8192 44.3 -> 41.1, d = 4544, F = 6000 61.5 -> 57.2.  With two rows at a time the widest have none on their way while two are worked
-// on: d = 5120, F = 8192 77.7 -> 84.4, with four 74.7; fp32 d = 2600, F = 6000 62.8 -> 68.1, with four 59.5.  Tokens of a
-// batch (one row at a time from LDS, the same order): four calls, d = 1496, F = 19864, 8 tokens 182.7 -> 174.4; d = 1232, F = 11728, 6
-// tokens 107.3 -> 101.3.
+// Two rows are worked on side by side, piece by piece; the registers of a piece are asked for again, for the piece kGateAhead further
+// (of these rows or the next two), as soon as its products are formed.  The sums of four rows cross the wave together, in the tree of
+// wave_sum: lanes 1, 2, 4 apart, then 8, 16, 32; at 8 and 16 the rows of a lane are halved.
+// What bounds it: HBM, and next to it 64 conversions to fp64 a lane and row, each as long as four multiply-adds.
+// A wave that holds whole rows takes the registers of others: four of them, asked for again two at a time, were 200 to 350 registers a
+// lane at rows of 8 KiB and more, one workgroup per compute unit from 9 KiB on (and registers in memory in the fp32 step of 9 KiB), so
+// that layers of many neurons went over the chip twice.  us a step from a graph (2 % of the neurons fire), two rows interleaved by
+// the compiler and none on its way meanwhile / four whole rows / now: d = 5120, F = 4096 44.5 / 40.8 / 38.4, F = 8192 57.6 / 54.5 /
+// 53.0, F = 13824 75.7 / 78.6 / 74.5, F = 17000 98.6 / 98.7 / 92.4; d = 8192, F = 12288 103.8 / 108.0 / 104.4; d = 4096, F = 11008
+// 60.5 / 59.8 / 58.9; fp32 d = 2304, F = 6000 43.9 / 44.5 / 41.1, F = 20000 90.1 / 95.9 / 88.6.
+// The same piece of four rows side by side falls on too few channels of the memory where a row is a power of two: lif_predict, two
+// / four rows, d = 4096, F = 20000 27.1 / 30.6, fp32 d = 4096, F = 12000 31.1 / 36.2 (d = 5120, F = 8192 14.6 / 14.8).  Pieces ahead,
+// 6 / 8 / 10 / 16: d = 5120, F = 13824 21.8 / 21.8 / 22.2 / 23.3, fp32 d = 4096, F = 8000 22.0 / 21.2 / 21.8 / 23.1.
+// Tokens of a batch (one row at a time from LDS, the same order), four calls with sums that wait for their own conversion / that do
+// not: d = 1496, F = 19864, 8 tokens 182.7 / 174.4; d = 1232, F = 11728, 6 tokens 107.3 / 101.3.
+constexpr int kGateAhead = 8;
 template <typename T, int NI>
 __device__ __forceinline__ unsigned gate_byte(const T* __restrict__ Wg, const float* __restrict__ b, float* __restrict__ gact, int grp,
                                               int nvec, typename Vec<T>::type (&xr)[NI], double th) {
     using V = typename Vec<T>::type;
-    constexpr int R = 4;
+    constexpr int R = 4, W = NI < kGateAhead / 2 ? 2 * NI : kGateAhead;
     const int lane = threadIdx.x & 63, owner = ((lane >> 3) & 1) * 2 + ((lane >> 4) & 1);
     const V* rows = reinterpret_cast<const V*>(Wg) + (size_t)grp * 8 * nvec;
     const float bias0 = b[grp * 8 + owner], bias1 = b[grp * 8 + R + owner];
-    V g[R][NI];
-    auto request = [&](V (&v)[NI], int e) {
+    V g[W][2];
+    auto request = [&](int k) {                      // piece k mod NI of row 2 (k / NI) and of the row behind it
+        const int e = k / NI * 2, it = k % NI;
 #pragma unroll
-        for (int it = 0; it < NI; ++it) v[it] = rows[(size_t)e * nvec + (it < full_pieces(NI) ? it * 64 + lane : min(it * 64 + lane, nvec - 1))];
+        for (int u = 0; u < 2; ++u)
+            g[k % W][u] = rows[(size_t)(e + u) * nvec + (it < full_pieces(NI) ? it * 64 + lane : min(it * 64 + lane, nvec - 1))];
     };
 #pragma unroll
-    for (int u = 0; u < R; ++u) request(g[u], u);
+    for (int k = 0; k < W; ++k) request(k);
     unsigned byte = 0;
-    auto round = [&](int e0, auto more) {
 #pragma unroll
-        for (int it = 0; it < NI; ++it) asm volatile("" : "+v"(xr[it]));      // (else x is widened once, and twice as many registers kept)
+    for (int e0 = 0; e0 < 8; e0 += R) {
         double v[R];
 #pragma unroll
         for (int u = 0; u < R; u += 2) {
+#pragma unroll
+            for (int it = 0; it < NI; ++it) asm volatile("" : "+v"(xr[it]));  // (else x is widened once, and twice as many registers kept)
             double sum[2] = {0.0, 0.0};
 #pragma unroll
             for (int it = 0; it < NI; ++it) {
+                const int k = (e0 + u) / 2 * NI + it;
                 const bool in = it < full_pieces(NI) || it * 64 + lane < nvec;
-                const V pair[2] = {in ? g[u][it] : V(0), in ? g[u + 1][it] : V(0)};
+                const V pair[2] = {in ? g[k % W][0] : V(0), in ? g[k % W][1] : V(0)};
                 dot_f64<2>(pair, xr[it], sum);
+                if (k + W < 4 * NI) request(k + W);
+                __builtin_amdgcn_sched_barrier(0);   // (the requests go out in turn, each as soon as its registers are free)
             }
             v[u] = sum[0];
             v[u + 1] = sum[1];
-            if constexpr (decltype(more)::value) {
-                request(g[u], e0 + R + u);
-                request(g[u + 1], e0 + R + u + 1);
-            }
-            __builtin_amdgcn_sched_barrier(0);       // (the products of a row need the registers that those of the one before had)
         }
 #pragma unroll
         for (int u = 0; u < R; ++u) v[u] += dpp_from<0xB1, 0xf>(v[u]);       // quad_perm 1 0 3 2
@@ -429,9 +436,7 @@ __device__ __forceinline__ unsigned gate_byte(const T* __restrict__ Wg, const fl
 #pragma unroll
         for (int u = 0; u < R; ++u) byte |= (unsigned)(fires >> ((u >> 1) * 8 + (u & 1) * 16) & 1u) << (e0 + u);
         if ((lane & 0x27) == 0) gact[grp * 8 + e0 + owner] = (float)(a > 0.0 ? a : 0.0);
-    };
-    round(0, std::true_type());
-    round(R, std::false_type());
+    }
     return byte;
 }
 

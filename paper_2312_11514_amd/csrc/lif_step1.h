@@ -1233,9 +1233,16 @@ __device__ __forceinline__ void await_predictor(const StepArgs& a, int block) {
     __builtin_amdgcn_s_sleep(40);
 }
 
+// The gate form stays at two workgroups per compute unit (LDS): rows of more than 4 KiB would leave room for three, whose
+// predictors, all at once, hold up the loaders.  us a step from a graph, three / two: fp32 d = 1400, F = 18000 60.7 / 59.5, d = 2048,
+// F = 18000 78.7 / 78.0; d = 4544, F = 18000 84.9 / 84.1; d = 4096, F = 11008 58.2 / 57.8; but fp32 d = 2304, F = 16000, where two have
+// one round of predictors just full, 74.6 / 75.8.
+constexpr int kGatePairNi = 6;
+constexpr size_t kGatePairLds = 56 * 1024;           // more than a third of the 160 KiB of a compute unit
 template <typename T, int NI, bool GLU, bool GATE>
 __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(const StepArgs a) {
-    __shared__ __align__(16) unsigned char lds[sizeof(PlanLds) > sizeof(PredictLds) ? sizeof(PlanLds) : sizeof(PredictLds)];
+    constexpr size_t kRoles = sizeof(PlanLds) > sizeof(PredictLds) ? sizeof(PlanLds) : sizeof(PredictLds);
+    __shared__ __align__(16) unsigned char lds[GATE && NI >= kGatePairNi && kRoles < kGatePairLds ? kGatePairLds : kRoles];
     const int block = blockIdx.x;
     if (block < a.n_pred) {
         if constexpr (GATE) gate_role<T, NI>(a, block, reinterpret_cast<unsigned*>(lds));
@@ -1254,8 +1261,8 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
 // loaders, and the activation stage over the rows in use - on the matrix cores (MFMA: fp16, d a multiple of 32), else one
 // wave per row.  Dynamic LDS: step_batch_lds bytes.
 // Registers (gfx950, as the compiler reports them): the loader role has more uniform values than the 106 scalar registers hold,
-// 83 to 144 of them live in lanes of vector registers (k_step1: 61 to 138).  No vector register goes to memory, which would queue
-// up behind the host reads; 18 of the 106 forms, all with the gate predictor, keep 36 bytes a lane there (k_step1: none).  The
+// 85 to 146 of them live in lanes of vector registers (k_step1: 77 to 136).  No vector register goes to memory, which would queue
+// up behind the host reads; 17 of the 106 forms, all with the gate predictor, keep 36 bytes a lane there (k_step1: none).  The
 // predictor is a template parameter for that reason: a kernel with both forms of the role spilled 169 to 246 scalar registers and
 // was 82 to 106 KB of code (41 to 60 KB each by itself), more than the 64 KB instruction cache of two compute units.
 template <typename T, int NI, bool GLU, bool GATE, bool MFMA, int WAVES>
