@@ -548,7 +548,7 @@ void launch_ffn_up_mfma(lif_layer* L, const void* x, int batch, float* h, hipStr
     // workgroup asks for its first rows before the count arrives
     const int spec = L->expected_rows > 0 ? 1 : 0;
     const int grid = spec ? mfma_hint_tiles(L) : (c.capacity_rows + 15) / 16;
-    const bool few = spec && up_mfma_waves(grid, c.d_model) == kMfmaWavesFew;      // (without a hint most tiles are likely not in use)
+    const bool few = spec && up_mfma_waves(grid, c.d_model, c.glu != 0) == kMfmaWavesFew;      // (without a hint most tiles are likely not in use)
 #define LIF_UM(GLU, W)                                                                                       \
     hipLaunchKernelGGL((k_ffn_up_mfma<GLU, W>), dim3(grid), dim3(W * 64), 0, s, (const _Float16*)L->buf.matrix,  \
                        L->buf.bias, (const _Float16*)x, h, c.d_model, batch, c.capacity_rows, L->row_elems,        \

@@ -58,15 +58,22 @@ constexpr int kStageSteps = 4;                           // k-steps per stage: 2
 constexpr int kStagePitch = kStageSteps * 64 + 16;       // bytes between the staged rows of a wave
 
 // Waves per tile of the stand-alone pass over all rows.  With 8 a tile takes half the dependent stages per wave (7.7 us against 10
-// us at 1400 rows) but two workgroups fill a compute unit: more than 512 tiles take a second round on the chip, in which most of it
-// is idle.  Of 4 waves three workgroups and more are resident.  One FFN call of 8 tokens, us, 8 -> 4 waves: d = 4096 11803 rows 49.4
-// -> 43.2, 16290 rows 73.6 -> 69.9, gated, 10989 rows, all read, 57.9 -> 56.7; d = 1024 10422 rows 21.4 -> 18.7; d = 2048 16294 rows
-// 42.9 -> 41.6, gated 9414 rows 30.7 -> 29.9; d = 512 13195 rows 19.6 -> 18.2; up to 512 tiles mostly the other way round: d = 4096
-// 2545 rows 15.4 against 17.4, d = 3072 5447 rows 19.0 against 19.5 (but 7828 rows 27.8 against 25.9).  Rows of more than 16 parts of
-// two stages are slower with 4 at any number (d = 5120, gated, 6 tokens, 8775 rows 61.5 against 62.4).
+// us at 1400 rows) but two workgroups fill a compute unit, 512 tiles a round on the chip.  Of 4 waves four workgroups are resident,
+// three where rows are gated (registers), and 1024 and 768 tiles go in one round; where both need two rounds, gated rows between 768
+// and 1024 tiles, 8 are faster again.  A hint lies above the rows in use, by an eighth or so: the lines are at 7/6 of these.
+// One FFN call of 8 tokens from a graph, us, 8 -> 4 waves, the hint the rows in use: d = 1024 10223 rows 24.7 -> 22.8, d = 2048 10987
+// rows 28.3 -> 25.8, d = 4096 11486 rows 35.6 -> 33.3, 14980 rows 46.8 -> 44.6; up to 512 tiles mostly the other way round: d = 3072
+// 6598 rows 26.5 against 26.9, 2 tokens 7084 rows 25.6 against 27.1.  Gated, the hint 1.15 times the rows in use, up to 896 tiles: d =
+// 1792 4 % faster, d = 4096 1 to 2 %, 2048 to 3840 the same within 3 %; 896 to 1194 tiles: d = 1792 and below 0 to 2 % faster, but d =
+// 2304 2 to 4 % slower, d = 3072 16124 rows 52.9 against 54.6; above: d = 4096 2 % faster, the others the same within 1 %.
+// Rows of more than 16 parts of two stages: plain ones gain 5 to 10 % up to 896 tiles, but lose once the cache behind the L2 no
+// longer holds them all (d = 8192 from 13500 rows on 10 to 19 %); gated ones lose up to 4 %.  They keep 8 throughout.
 constexpr int kMfmaWavesFew = 4, kMfmaWavesAll = 8, kMfmaTilesAll = 2 * 256;
-inline int up_mfma_waves(int likely_tiles, int d) {
-    return likely_tiles > kMfmaTilesAll && d <= kMfmaParts * 2 * kStageSteps * 32 ? kMfmaWavesFew : kMfmaWavesAll;
+constexpr int kGluTilesFew = 3 * 256 * 7 / 6, kGluTilesAll = 4 * 256 * 7 / 6;
+inline int up_mfma_waves(int likely_tiles, int d, bool glu) {
+    const int stage = kStageSteps * 32;              // columns
+    if (likely_tiles <= kMfmaTilesAll || d > kMfmaParts * 2 * stage) return kMfmaWavesAll;
+    return glu && d >= kMfmaParts * stage && likely_tiles > kGluTilesFew && likely_tiles <= kGluTilesAll ? kMfmaWavesAll : kMfmaWavesFew;
 }
 
 // LDS of ffn_up_mfma_tile_staged

@@ -23,6 +23,7 @@ int main() {
     int a, b, c;
     while (scanf("%15s %d %d %d", what, &a, &b, &c) == 4) {
         if (!strcmp(what, "hides")) printf("%d\\n", (int)lif::load_hides_activations(a, b, c));
+        if (!strcmp(what, "waves")) printf("%d\\n", lif::up_mfma_waves(a, b, c != 0));
         if (!strcmp(what, "await")) {           // b slots, the first c of them there, by thread a of 512: looks, and the answer
             int looks = 0;
             const bool all = lif::await_slots(a, b, 512, 1000, [&](int s) { ++looks; return s < c; });
@@ -51,3 +52,11 @@ def test_a_lost_wait_is_bounded_over_all_slots_of_a_thread(rule):
     the bound is one for the thread, not one a slot."""
     assert rule("await", (0, 16384, 16384), (5, 0, 0), (511, 513, 0)) == [32, 0, -1000]      # all there; none to look for; the first is missing
     assert rule("await", (0, 16384, 8192), (3, 16384, 15000), (3, 16384, 0)) == [-1016, -1030, -1000]
+
+
+def test_waves_per_tile_by_rounds_on_the_chip(rule):
+    """(16-row tiles that a hint covers, columns, gated).  Plain rows: one line.  Gated rows of 2048 columns and more: 8 waves again where
+    4 take two rounds as well.  Rows of more than 4096 columns and few tiles: always 8."""
+    assert rule("waves", (512, 4096, 0), (513, 4096, 0), (513, 4128, 0), (897, 4096, 0), (4096, 32, 0)) == [8, 4, 8, 4, 4]
+    assert rule("waves", (512, 2048, 1), (513, 2048, 1), (896, 4096, 1), (897, 4096, 1), (897, 2016, 1), (1194, 2048, 1), (1195, 2048, 1),
+                (600, 4128, 1)) == [8, 4, 4, 8, 4, 8, 4, 8]
