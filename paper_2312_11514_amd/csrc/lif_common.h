@@ -145,8 +145,10 @@ __device__ __forceinline__ U uniform_load(const U* p) {
 
 // v to the 16 bytes at base + off, written through the L2 to memory; base is the same for the whole wave and off + 16 <= bytes.
 // A launch ends when every L2 has written back what it holds changed: the rows that a fused step has loaded and moved, a few MB, stood
-// in front of the down projection.  us a step, plain stores -> these: OPT shape 56.9 -> 56.2, Falcon shape 137.6 -> 136.4, Llama-2
-// shape from a graph 130.5 -> 129.4, gate resident 108.8 -> 106.6, 8 tokens 233.6 -> 232.5.  lif_load_bundles keeps plain stores: the
+// in front of the down projection.  us a step, plain stores -> these, two timings in turn: OPT shape 57.9 -> 57.3 and 58.2 -> 57.7, eight
+// stacked layers of it from a graph 467.5 -> 465.2 and 476.4 -> 471.3, Falcon shape 134.6 -> 133.3 and 135.9 -> 134.8, Llama-2 shape from
+// a graph 132.1 -> 130.5 and 132.0 -> 130.8, gate resident 105.1 -> 104.1 and 105.8 -> 104.8, 8 tokens 230.6 -> 229.5 and 231.0 -> 230.4
+// (two runs of one build differ by up to 0.4 %).  lif_load_bundles keeps plain stores: the
 // activation stage behind it finds the rows in the L2 (fp32 d = 1288, 3 tokens, four calls 68.6 against 69.2).  Partial outputs and
 // activations written through were no faster.
 template <typename V>

@@ -60,7 +60,8 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // quarter of the rows: 10976 rows, 8 tokens, d = 4096, gated, activations and down projection 63.3 -> 60.2 us.
 // The sums of the waves and the two halves of the token slots meet in LDS as 16-byte pieces: by 32 lane exchanges and as many
 // read-add-writes of 4 bytes per lane it took 2.0 us from the last row to the last sum, twelve waves sharing the LDS of a unit; now
-// 0.7.  us a pass: d = 4096, gated, 8 tokens, 10976 rows, both stages 59.2 -> 57.9; 12 passes of 5 tokens, OPT shape, 2339 -> 2313.
+// 0.7.  us, two timings in turn: d = 4096, gated, 8 tokens, 10989 rows, all read, both stages 58.0 -> 56.7 and 58.0 -> 56.8; 12 passes of
+// 5 tokens, OPT shape, 2435 -> 2409 and 2349 -> 2327.
 // grid = (ceil(d / 128) column slices, row-chunk workgroups), block = WAVES waves; lane l of a wave: column
 // group n16 = l mod 16 (8 columns) and token slot n16, row block q = l div 16 (8 of the 32 rows of an instruction).
 // A pass compacts the contributing rows of ROWS slots (SKIP: rows with some activation; else all rows in use) in a

@@ -35,7 +35,7 @@
 // waves ask for, so some 30 loaders fill the link.
 // Measured on gfx950, one decode token, with five launches -> with this kernel and the down projection: fp32 d = 256, F = 1024:
 // 23.4 -> 14.1 us; OPT-6.7B shape 65.3 -> 57; Falcon-7B shape 149.5 -> 136; Llama-2 shape gated, from a graph, 148.7 -> 132, with
-// the gate resident 112.8 -> 108.5.
+// the gate resident 112.8 -> 105.
 #pragma once
 
 #include <cstddef>
