@@ -368,7 +368,7 @@ constexpr int full_pieces(int ni) { return ni <= 1 ? 0 : ni <= 2 ? 1 : ni <= 4 ?
 // (of these rows or the next two), as soon as its products are formed.  The sums of four rows cross the wave together, in the tree of
 // wave_sum: lanes 1, 2, 4 apart, then 8, 16, 32; at 8 and 16 the rows of a lane are halved.
 // What bounds it: HBM, and next to it 64 conversions to fp64 a lane and row, each as long as four multiply-adds.
-// A wave that holds whole rows takes the registers of others: four of them, asked for again two at a time, were 200 to 350 registers a
+// A wave that holds whole rows takes the registers of others: four of them, asked for again two at a time, were 200 to 500 registers a
 // lane at rows of 8 KiB and more, one workgroup per compute unit from 9 KiB on (and registers in memory in the fp32 step of 9 KiB), so
 // that layers of many neurons went over the chip twice.  us a step from a graph (2 % of the neurons fire), two rows interleaved by
 // the compiler and none on its way meanwhile / four whole rows / now: d = 5120, F = 4096 44.5 / 40.8 / 38.4, F = 8192 57.6 / 54.5 /
