@@ -324,8 +324,9 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     // workgroup of 8 goes twice through the work of 16 (Falcon shape, 5120 rows, skipping: 16.9 -> 19.3 us), while one of 16 leaves
     // half of its waves idle where 8 are in use, so without a hint 8 are taken only where every row is read and most layers of
     // this capacity hold more than one chunk (OPT shape, 8192 rows: 29.9 -> 28.3 us).
-    const int likely = L->expected_rows > 0 ? L->expected_rows / 6 * 5 : SKIP ? kDown1OneSkip : c.capacity_rows / 2;
-    const int waves = rows <= kDown1FewRows ? 8 : down1_waves<SKIP>(std::max(kDown1FewRows + 1, likely), slices);
+    const int likely = L->expected_rows > 0 ? L->expected_rows - L->expected_rows / 8
+                       : rows <= kDown1FewRows ? rows : std::max(kDown1FewRows + 1, SKIP ? kDown1OneSkip : c.capacity_rows / 2);
+    const int waves = down1_waves<SKIP>(likely, slices);
     // groups of slots whose activations are asked for ahead of the row count: those the hint covers; without a hint 2048
     // slots if that many rows make one pass (else the order of the slots is not known yet)
     const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;

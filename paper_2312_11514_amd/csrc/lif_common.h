@@ -231,6 +231,27 @@ constexpr int wave_fold_dup_mask() {
     }
     return mask;
 }
+// The exchanges are register moves (lanes 4 and 8 apart: permutations in a row of 16; 16 and 32 apart: swaps of rows and halves):
+// through the LDS crossbar each of them is a round trip that the next one waits for.
+template <int M>
+__device__ __forceinline__ float from_xor(float v) {                 // v of the lane whose number differs in bit M
+    static_assert(M == 4 || M == 8, "inside a row of 16 lanes");
+    if constexpr (M == 4) return dpp_from<0x1b, 0xf>(dpp_from<0x141, 0xf>(v));      // mirrored in 8 lanes (^7), then in 4 (^3)
+    else return dpp_from<0x128, 0xf>(v);                             // a rotation by 8
+}
+// a + b where lanes M apart trade first, as the fp64 form above
+template <int M>
+__device__ __forceinline__ float swap_add(float a, float b) {
+    static_assert(M == 16 || M == 32, "rows or halves of the wave");
+    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
+    if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+        return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(ua, ub, false, false);
+        return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+    }
+}
 template <int HELD, int M, int N>
 __device__ __forceinline__ void wave_fold_step(float (&v)[N], int& first, int lane) {
     if constexpr (M < kWave) {
@@ -239,13 +260,18 @@ __device__ __forceinline__ void wave_fold_step(float (&v)[N], int& first, int la
             const bool up = (lane & M) != 0;
 #pragma unroll
             for (int i = 0; i < half; ++i) {
-                const float send = up ? v[i] : v[i + half], keep = up ? v[i + half] : v[i];
-                v[i] = keep + __shfl_xor(send, M, kWave);
+                if constexpr (M >= 16) {
+                    v[i] = swap_add<M>(v[i], v[i + half]);
+                } else {
+                    const float send = up ? v[i] : v[i + half], keep = up ? v[i + half] : v[i];
+                    v[i] = keep + from_xor<M>(send);
+                }
             }
             first += up ? half : 0;
             wave_fold_step<half, M * 2, N>(v, first, lane);
         } else {
-            v[0] += __shfl_xor(v[0], M, kWave);
+            if constexpr (M >= 16) v[0] = swap_add<M>(v[0], v[0]);
+            else v[0] += from_xor<M>(v[0]);
             wave_fold_step<1, M * 2, N>(v, first, lane);
         }
     }
