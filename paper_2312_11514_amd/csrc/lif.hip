@@ -68,7 +68,7 @@ constexpr int kDefaultPolls = 4096;      // a failed poll takes about 0.7 us: 3 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Layout {
-    size_t state, words, one, ring, tpart, move_dst, hole_list, h, ypart, h_new, stamp, ptr_new, bias_new, gact, total;
+    size_t state, words, one, arrived, ring, tpart, move_dst, hole_list, h, ypart, h_new, stamp, ptr_new, bias_new, gact, total;
     int reset_words;                   // 64-bit words from `words` on that a reset clears
 };
 
@@ -118,6 +118,8 @@ Layout make_layout(const lif_config& c) {
     off = off + sizeof(uint64_t) * c.capacity_rows;               // ... and the deletion plan;
     L.one = off;                       // inside a single-launch FFN, and its launch number
     if (ffn_one_possible(c)) off = off + sizeof(uint64_t) * kOneReps * one_pitch(c.capacity_rows) + sizeof(OneState);
+    L.arrived = off;                   // per column slice: workgroups whose partial outputs are written
+    off = off + sizeof(unsigned) * kArrivedPitch * down1_slices(c);      // (no down projection has more slices)
     L.ring = off;                      // window_k step masks, each padded to whole 64-bit words
     off = off + (size_t)(c.window_k + 2) * ring_words(c) * 8;     // ... directly followed by the two bitmaps of the cached set
     L.reset_words = (int)((off - L.words) / 8);
@@ -168,6 +170,7 @@ struct lif_layer {
     unsigned long long* words;
     unsigned long long* one_words;  // of k_ffn_one, null where it is never launched
     OneState* one;
+    unsigned* arrived;
     int polls;                  // failed polls of a hand-over word before a workgroup computes the value itself
     float* gact;                // null unless the gate projection is the predictor
     size_t row_elems, row_bytes;
@@ -333,18 +336,13 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     const FusedRows f = fused_rows(L, fc);
 #define LIF_D1(W, FUSED)                                                                                     \
     hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W, FUSED>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(W * 64), 0, s,     \
-                       (const T*)L->buf.matrix, h, f, (T*)y, ypart, c.d_model, c.capacity_rows, L->row_elems,        \
+                       (const T*)L->buf.matrix, h, f, (T*)y, ypart, L->arrived, c.d_model, c.capacity_rows, L->row_elems,        \
                        down_off, spec, slices, L->buf.pointers, L->gact, c.d_ffn, L->st)
     if (waves == 8 && fc.on) LIF_D1(8, true);
     else if (waves == 8) LIF_D1(8, false);
     else if (fc.on) LIF_D1(16, true);
     else LIF_D1(16, false);
 #undef LIF_D1
-#define LIF_D1F(MOST)                                                                                        \
-    hipLaunchKernelGGL((k_ffn_down_finish<T, down1_chunks<SKIP>, MOST>), dim3((c.d_model + 255) / 256), dim3(256), 0, s,    \
-                       ypart, (T*)y, c.d_model, 1, slices, wg_rows, L->st)
-    if (wg_rows > 1) LIF_FINISH(wg_rows, LIF_D1F);
-#undef LIF_D1F
 }
 
 // several tokens, fp32
@@ -359,16 +357,11 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
 #define LIF_DB(FUSED)                                                                                        \
     hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(256),  \
-                       0, s, (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, c.d_model, batch,          \
+                       0, s, (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, L->arrived, c.d_model, batch,          \
                        c.capacity_rows, L->row_elems, down_off, slices, L->st)
     if (fc.on) LIF_DB(true);
     else LIF_DB(false);
 #undef LIF_DB
-#define LIF_DBF(MOST)                                                                                        \
-    hipLaunchKernelGGL((k_ffn_down_finish<T, down_chunks, MOST>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,   \
-                       ypart, (T*)y, c.d_model, batch, slices, wg_rows, L->st)
-    if (wg_rows > 1) LIF_FINISH(wg_rows, LIF_DBF);
-#undef LIF_DBF
 }
 
 // several tokens, fp16: the down projection on the matrix cores
@@ -384,15 +377,10 @@ void launch_ffn_down_mfma_rows(lif_layer* L, int batch, void* y, float* h, float
 #define LIF_DM(FUSED)                                                                                        \
     hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, ROWS, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),       \
                        dim3(kDmWaves * 64), 0, s, (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y,  \
-                       ypart, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
+                       ypart, L->arrived, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
     if (fc.on) LIF_DM(true);
     else LIF_DM(false);
 #undef LIF_DM
-#define LIF_DMF(MOST)                                                                                        \
-    hipLaunchKernelGGL((k_ffn_down_mfma_finish<MOST>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart,       \
-                       (_Float16*)y, c.d_model, batch, chunk_rows, wg_rows, L->st)
-    if (wg_rows > 1) LIF_FINISH(wg_rows, LIF_DMF);
-#undef LIF_DMF
 }
 
 template <bool SKIP>
@@ -730,6 +718,7 @@ int lif_create(const lif_config* cfg, const lif_buffers* buf, lif_layer** out) {
     L->words = (unsigned long long*)(ws + lay.words);
     L->one_words = ffn_one_possible(*cfg) ? (unsigned long long*)(ws + lay.one) : nullptr;
     L->one = L->one_words ? (OneState*)(L->one_words + kOneReps * one_pitch(cfg->capacity_rows)) : nullptr;
+    L->arrived = (unsigned*)(ws + lay.arrived);
     L->polls = kDefaultPolls;
     L->gact = cfg->predictor == LIF_PRED_GATE ? (float*)(ws + lay.gact) : nullptr;
     L->row_elems = (size_t)(cfg->glu ? 3 : 2) * cfg->d_model;

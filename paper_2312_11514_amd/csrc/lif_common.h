@@ -164,6 +164,14 @@ __device__ __forceinline__ void store_through(char* base, unsigned off, unsigned
                                            kWriteThrough);
 }
 
+// 16 bytes at base + off past the caches, so what another workgroup of the launch has written with store_through; base is the same
+// for the whole wave and off + 16 <= bytes
+__device__ __forceinline__ f32x4 load_through(const float* base, unsigned off, unsigned bytes) {
+    constexpr int kFlags = 0x00027000, kPast = 1 << 4;           // a raw buffer of dwords; the cache policy bit sc1
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)bytes, kFlags), (int)off, 0, kPast));
+}
+
 // Workgroup barrier that orders LDS accesses only: unlike __syncthreads() it does not wait for the global
 // stores a wave has in flight (their acknowledgement from the L2 costs several hundred nanoseconds).  Use it
 // where the data handed over lives in LDS and no thread reads global memory that another one has just written.

@@ -248,6 +248,49 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
     return n <= kDownRowsMost ? 1 : (c > kDownChunksMax ? kDownChunksMax : c);
 }
 
+// Where several workgroup rows of a down projection share the row chunks, their sums meet in the launch that forms them: each
+// writes the sums of its chunks to ypart[chunk][token][d] and counts itself in at its column slice, and the last one to do so adds the
+// slice's sums in chunk order.  Nobody waits.  The sums are written and read past the caches, so that an acknowledged store is
+// where every XCD reads it and no fence is needed (the last workgroup behind __threadfence(), which writes back and invalidates
+// the L2, was twice as slow as a launch that adds them).  The count wraps to 0 by itself, whatever launches have been before.
+// us a pass, a launch of its own for these sums -> here, two timings in turn: 8 tokens of the Llama-2 shape 229.7 -> 226.8 (the launch
+// took 4.6, the down projection now 0.5 more), 12 passes of 5 tokens 2300 -> 2286, fp32 d = 1288, 3 tokens, four calls 68.6 -> 67.4;
+// 10989 rows all read, 8 tokens, d = 4096, 22 chunks, both stages 56.8 -> 56.6.  With 16 chunks asked for at a time the last was 56.65.
+constexpr int kArrivedPitch = 32;     // counters of two slices are this many words apart: a cache line
+__device__ __forceinline__ void store_part(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Whether this workgroup is the last of `parts` whose sums of a slice are written (uniform; `flag` is in LDS)
+__device__ __forceinline__ bool last_part(unsigned* arrived, int parts, int* flag) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this wave's stores are acknowledged,
+    __syncthreads();                                             // and those of the others
+    if (threadIdx.x == 0) *flag = (int)atomicInc(arrived, (unsigned)parts - 1u) == parts - 1;
+    __syncthreads();
+    return *flag != 0;
+}
+// sum[e] = the four floats from ypart[at + c * stride + e] on (at and stride multiples of 4), added over the chunks c in order
+template <typename A>
+__device__ __forceinline__ void sum_parts(const float* ypart, unsigned at, unsigned stride, int chunks, A (&sum)[4]) {
+    constexpr int PER = 8;                                       // asked for at a time, the next ones ahead of the adds
+    const unsigned bytes = stride * (unsigned)chunks * 4u;
+    auto request = [&](f32x4 (&v)[PER], int c0) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] = load_through(ypart, (at + (unsigned)min(c0 + i, chunks - 1) * stride) * 4u, bytes);
+    };
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum[e] = 0;
+    f32x4 now[PER], next[PER];
+    request(now, 0);
+#pragma unroll 1
+    for (int c0 = 0; c0 < chunks; c0 += PER) {
+        if (c0 + PER < chunks) request(next, c0 + PER);
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] = c0 + i < chunks ? sum[e] + (A)now[i][e] : sum[e];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) now[i] = next[i];
+    }
+}
+
 // Down projection  y[t][j] = sum_s H[t][s] * D[s][j]  over the rows in use, for 2..BT tokens (fp32 layers; fp16
 // batches run on the matrix cores, single tokens in k_ffn_down1).
 // grid = (column slices, row-chunk workgroups), block = 256 = (256 / LANES) row groups x LANES lanes; a
@@ -259,13 +302,15 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
 // The rows are cut into down_chunks chunks - a function of n and the width alone, so the arithmetic does not
 // depend on the launch geometry - and workgroup row y takes the chunks y, y + gridDim.y, ...  Every
 // chunk is summed from zero.  With one chunk in use the workgroup writes its columns of y.  With more,
-// a grid of one workgroup row adds its chunk sums in chunk order and writes y; a taller grid writes
-// them to ypart[chunk][token][d] (fp32) and k_ffn_down_finish adds them in the same order.  No atomics.
+// a grid of one workgroup row adds its chunk sums in chunk order and writes y; of a taller grid the last workgroup of a slice
+// adds them in the same order (last_part), in fp64: every chunk would be another rounding of the whole (3 tokens in fp32, d =
+// 320: 1.43e-7 from the sum in fp64 against 1.60e-7).
 template <typename T, int BT, bool SKIP, int LANES, bool FUSED>
 __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, const float* __restrict__ h,
                                                   const FusedRows fused, T* __restrict__ y,
-                                                  float* __restrict__ ypart, int d, int batch, int capacity,
-                                                  size_t row_elems, int down_off, int slices, DevState* __restrict__ st) {
+                                                  float* ypart, unsigned* __restrict__ arrived, int d, int batch,
+                                                  int capacity, size_t row_elems, int down_off, int slices,
+                                                  DevState* __restrict__ st) {
     static_assert(BT > 1, "single tokens: k_ffn_down1");
     using V = typename Vec<T>::type;
     constexpr int VE = Vec<T>::N;
@@ -277,7 +322,7 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     __shared__ float hv[BT][TS];
     __shared__ int wave_tot[4];
     __shared__ float red[4][LANES][BT * VE];
-    __shared__ int n_active;
+    __shared__ int n_active, last;
 
     if (FUSED && (int)blockIdx.x == slices) {
         if (blockIdx.y == 0) commit_step<256>(fused, capacity, st);
@@ -424,12 +469,12 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
                 sum[e] = ((red[0][ol][ob * VE + e] + red[1][ol][ob * VE + e]) + red[2][ol][ob * VE + e]) +
                          red[3][ol][ob * VE + e];
             if (chunks > 1 && gridDim.y > 1) {
-                float* out = ypart + ((size_t)chunk * batch + ob) * d + ocol;
+                const unsigned at = ((unsigned)chunk * batch + ob) * d + ocol;
 #pragma unroll
-                for (int e = 0; e < VE; ++e) out[e] = sum[e];
+                for (int e = 0; e < VE; ++e) store_part(ypart + at + e, sum[e]);
             } else {
 #pragma unroll
-                for (int e = 0; e < VE; ++e) total[e] += (double)sum[e];      // as ChunkSum
+                for (int e = 0; e < VE; ++e) total[e] += (double)sum[e];
             }
         }
     }
@@ -440,72 +485,16 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
         }
         if (n_active) atomicAdd(&st->c_ffn_active, (unsigned long long)n_active);
     }
-    if (writer && (chunks == 1 || gridDim.y == 1)) {
+    if (chunks > 1 && gridDim.y > 1) {
+        if (!last_part(arrived + slice * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
+        if (writer) sum_parts(ypart, (unsigned)(ob * d + ocol), (unsigned)(batch * d), chunks, total);
+    }
+    if (writer) {
         V out;
 #pragma unroll
         for (int e = 0; e < VE; ++e) out[e] = (T)total[e];
         *reinterpret_cast<V*>(y + (size_t)ob * d + ocol) = out;
     }
-}
-
-// Sum of the partial outputs of `chunks` chunks, stride floats apart, in chunk order.  The first `ahead` of them (at most MOST) are
-// requested before the row count (and so `chunks`) is known: the launch that wrote them had that many workgroup rows, and the array
-// always has room for kDownChunksMax.  Behind the row count they cost another round trip.  MOST is a compile-time number so that
-// the requests and the adds are straight code: with a branch for each of kDownChunksMax the kernel spent 0.5 us on instructions
-// that run once (one FFN call: 5 tokens, d = 4096, 1365 rows, 16.1 -> 15.4 us; one token, d = 1024, 13000 rows, 16.6 -> 15.8).
-template <int MOST>
-struct ChunkSum {
-    float v[MOST];
-    __device__ __forceinline__ void request(const float* p, int stride, int ahead) {
-#pragma unroll
-        for (int c = 0; c < MOST; ++c) v[c] = p[min(c, ahead - 1) * stride];       // (beyond: lines that are on their way already)
-    }
-    template <typename A>
-    __device__ __forceinline__ A sum(const float* p, int stride, int ahead, int chunks) const {
-        A s = 0;
-        const int here = min(ahead, chunks);
-#pragma unroll
-        for (int c = 0; c < MOST; ++c) s = c < here ? s + (A)v[c] : s;
-#pragma unroll 1
-        for (int c = ahead; c < chunks; c += 4) {    // more rows in use than the hint let expect
-            float w[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) w[q] = p[min(c + q, chunks - 1) * stride];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) s = c + q < chunks ? s + (A)w[q] : s;
-        }
-        return s;
-    }
-};
-// The launch with the least MOST that takes `ahead` partial outputs
-#define LIF_FINISH(AHEAD, LAUNCH)            \
-    do {                                     \
-        if ((AHEAD) <= 4) LAUNCH(4);         \
-        else if ((AHEAD) <= 8) LAUNCH(8);    \
-        else if ((AHEAD) <= 16) LAUNCH(16);  \
-        else LAUNCH(kDownChunksMax);         \
-    } while (0)
-
-// y = sum of the chunk partials in chunk order, rounded once to the element type.  Launched after a
-// k_ffn_down grid of more than one workgroup row; does nothing when a single chunk was in use (y is
-// written already).  grid = ceil(batch * d / 256), block = 256.
-// CHUNKS: the chunk rule of the kernel that wrote the partials, for its number of column slices.  Added in fp64, as in those
-// kernels: every chunk would be another rounding of the whole (3 tokens in fp32, d = 320: 1.43e-7 from the sum in fp64 against
-// 1.60e-7).
-template <typename T, int (*CHUNKS)(int, int), int MOST>
-__global__ __launch_bounds__(256) void k_ffn_down_finish(const float* ypart, T* __restrict__ y, int d,
-                                                         int batch, int slices, int ahead, const DevState* st) {
-    const int i = blockIdx.x * 256 + threadIdx.x, stride = batch * d;
-    const float* p = ypart + min(i, stride - 1);
-    const int err = st->cur.error, n = st->cur.num_used;
-    ChunkSum<MOST> part;
-    part.request(p, stride, ahead);
-    asm volatile("" ::: "memory");                   // (the compiler would ask for them, and for the count, where they are used)
-    if (err) return;
-    const int chunks = CHUNKS(n, slices);
-    if (chunks == 1) return;
-    const double sum = part.template sum<double>(p, stride, ahead, chunks);
-    if (i < stride) y[i] = (T)sum;
 }
 
 }  // namespace lif

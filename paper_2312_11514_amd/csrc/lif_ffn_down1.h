@@ -66,15 +66,15 @@ __host__ __device__ __forceinline__ int down1_waves(int n, int slices) {
 // spec: groups of WAVES * 64 slots whose activations are requested before the row count is known (the arrays span the
 // capacity, so the addresses are valid; values past the count are masked).
 // Workgroup row y takes the chunks y, y + gridDim.y, ...; with several chunks and several workgroup rows the sums go to
-// ypart[chunk][d] (fp32) and k_ffn_down_finish adds them, else this kernel adds them in the same order.  No atomics.
+// ypart[chunk][d] (fp32) and the last workgroup of a slice adds them (last_part), else every workgroup its own, in the same order.
 // The same as a role of a larger launch (k_ffn_one): bx, by, rows_by take the place of blockIdx.x, blockIdx.y, gridDim.y, and
 // WORDS is where the activations come from: `activations(s0, stride, count, v)` fills v[q] with those of the slots s0 + q *
 // stride (q < count, different for every lane).
 struct NoWords {};
 template <typename T, bool SKIP, int WAVES, bool FUSED, typename Words>
 __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, const float* __restrict__ h, const FusedRows& fused,
-                                               T* __restrict__ y, float* __restrict__ ypart, int d, int capacity,
-                                               size_t row_elems, int down_off, int spec, int slices,
+                                               T* __restrict__ y, float* ypart, unsigned* __restrict__ arrived, int d,
+                                               int capacity, size_t row_elems, int down_off, int spec, int slices,
                                                const int32_t* __restrict__ pointers, const float* __restrict__ gact, int gact_n,
                                                DevState* __restrict__ st, int bx, int by, int rows_by, Words activations) {
     constexpr bool WORDS = !std::is_same<Words, NoWords>::value;
@@ -86,6 +86,7 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
     __shared__ int list[WAVES][WL];
     __shared__ float hv[WAVES][WL];
     __shared__ float red[VWMAX][LANES][VE + 1];
+    __shared__ int last;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l = lane & (LANES - 1), rg = lane / LANES;
     // XCD-aware slice order: workgroups are dealt round-robin to the 8 XCDs, each with its own L2; giving every XCD a
     // contiguous run of slices makes the two halves of a 128-byte line meet in one L2 instead of being fetched twice
@@ -265,9 +266,9 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
             for (int w = 0; w < VWMAX; ++w) sum = w < vwaves ? sum + part[w] : sum;
             const int oc = slice * (LANES * VE) + tid;
             if (chunks > 1 && rows_by > 1) {
-                if (oc < d) ypart[(size_t)chunk * d + oc] = sum;
+                if (oc < d) store_part(ypart + (size_t)chunk * d + oc, sum);
             } else {
-                total += (double)sum;                // as ChunkSum; 0 + first sum is exact
+                total += (double)sum;                // 0 + first sum is exact
                 if (chunk + rows_by >= chunks && oc < d) y[oc] = (T)total;
             }
         }
@@ -277,17 +278,27 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
         atomicAdd(&st->c_ffn_calls, 1ull);
         atomicAdd(&st->c_ffn_rows, (unsigned long long)n);
     }
+    if (chunks > 1 && rows_by > 1) {
+        if (!last_part(arrived + slice * kArrivedPitch, min(chunks, rows_by), &last)) return;
+        const int oc = slice * (LANES * VE) + tid * 4;
+        if (tid < LANES * VE / 4 && oc < d) {        // four columns per thread
+            double sum[4];
+            sum_parts(ypart, (unsigned)oc, (unsigned)d, chunks, sum);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[oc + e] = (T)sum[e];
+        }
+    }
 }
 
 template <typename T, bool SKIP, int WAVES, bool FUSED>
 __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ matrix, const float* __restrict__ h,
                                                           const FusedRows fused, T* __restrict__ y,
-                                                          float* __restrict__ ypart, int d, int capacity,
+                                                          float* ypart, unsigned* __restrict__ arrived, int d, int capacity,
                                                           size_t row_elems, int down_off, int spec, int slices,
                                                           const int32_t* __restrict__ pointers,
                                                           const float* __restrict__ gact, int gact_n,
                                                           DevState* __restrict__ st) {
-    ffn_down1_role<T, SKIP, WAVES, FUSED>(matrix, h, fused, y, ypart, d, capacity, row_elems, down_off, spec, slices, pointers, gact,
+    ffn_down1_role<T, SKIP, WAVES, FUSED>(matrix, h, fused, y, ypart, arrived, d, capacity, row_elems, down_off, spec, slices, pointers, gact,
                                           gact_n, st, blockIdx.x, blockIdx.y, gridDim.y, NoWords());
 }
 

@@ -67,13 +67,13 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // A pass compacts the contributing rows of ROWS slots (SKIP: rows with some activation; else all rows in use) in a
 // fixed order (thread-major over slots p * threads + tid); the waves take groups of 32 compacted rows in turn.
 // The waves of a pass are added in wave order, a chunk's passes in order, the chunks in chunk order (by this kernel when
-// one workgroup row is launched, else by k_ffn_down_mfma_finish from ypart[chunk][token][d]).  Nothing depends on
-// the launch geometry.
+// one workgroup row is launched, else by the last workgroup of a slice from ypart[chunk][token][d], see last_part).  Nothing
+// depends on the launch geometry.
 template <bool SKIP, int WAVES, int ROWS, bool FUSED>
 __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16* __restrict__ matrix,
                                                               const float* __restrict__ h, const FusedRows fused,
-                                                              _Float16* __restrict__ y, float* __restrict__ ypart, int d,
-                                                              int batch, int capacity, size_t row_elems, int down_off,
+                                                              _Float16* __restrict__ y, float* ypart,
+                                                              unsigned* __restrict__ arrived, int d, int batch, int capacity, size_t row_elems, int down_off,
                                                               int chunk_rows, int slices, DevState* __restrict__ st) {
     constexpr int BT = 8, T = WAVES * 64;
     constexpr int PER = ROWS / T;                    // slots per thread in the compaction
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
     __shared__ int wave_tot[WAVES];
     __shared__ float wave_max[WAVES];
     __shared__ f32x4 red[WAVES][8][64];              // per wave, column of a lane's 8, and lane: sums of four token slots
-    __shared__ int n_active;
+    __shared__ int n_active, last;
 
     if (FUSED && (int)blockIdx.x == slices) {
         if (blockIdx.y == 0) commit_step<WAVES * 64>(fused, capacity, st);
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
         if (chunks > 1 && gridDim.y > 1) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (og * 4 + r < batch && ocol < d) ypart[((size_t)chunk * batch + og * 4 + r) * d + ocol] = part[r];
+                if (og * 4 + r < batch && ocol < d) store_part(ypart + ((size_t)chunk * batch + og * 4 + r) * d + ocol, part[r]);
         } else {
             total += part;                           // chunk order; 0 + first sum is exact
         }
@@ -271,27 +271,18 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (og * 4 + r < batch && ocol < d) y[(size_t)(og * 4 + r) * d + ocol] = (_Float16)total[r];
+        return;
     }
-}
-
-// y = sum of the chunk partials in chunk order, rounded once to fp16.  Launched after a k_ffn_down_mfma grid of
-// more than one workgroup row; does nothing when a single chunk was in use (y is written already).
-// grid = ceil(batch * d / 256), block = 256.
-template <int MOST>
-__global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* ypart, _Float16* __restrict__ y,
-                                                              int d, int batch, int chunk_rows, int ahead,
-                                                              const DevState* st) {
-    const int i = blockIdx.x * 256 + threadIdx.x, stride = batch * d;
-    const float* p = ypart + min(i, stride - 1);
-    const int err = st->cur.error, n = st->cur.num_used;
-    ChunkSum<MOST> part;
-    part.request(p, stride, ahead);
-    asm volatile("" ::: "memory");                   // (the compiler would ask for them, and for the count, where they are used)
-    if (err) return;
-    const int chunks = down_mfma_chunks(n, chunk_rows);
-    if (chunks == 1) return;
-    const float sum = part.template sum<float>(p, stride, ahead, chunks);
-    if (i < stride) y[i] = (_Float16)sum;
+    if (!last_part(arrived + blockIdx.x * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
+    // four columns of a token per thread
+    static_assert(BT * kDmCols == 4 * T, "one piece of every token and four columns");
+    const int pt = tid / (kDmCols / 4), pc = blockIdx.x * kDmCols + tid % (kDmCols / 4) * 4;
+    if (pt < batch && pc < d) {
+        float sum[4];
+        sum_parts(ypart, (unsigned)(pt * d + pc), (unsigned)(batch * d), chunks, sum);
+        typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<f16x4*>(y + (size_t)pt * d + pc) = f16x4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
+    }
 }
 
 }  // namespace lif
