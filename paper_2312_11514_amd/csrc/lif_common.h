@@ -133,6 +133,12 @@ __device__ __forceinline__ double wave_sum(double v) {
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// a value that is the same in all lanes, as one of the whole wave
+__device__ __forceinline__ unsigned long long uniform(unsigned long long v) {
+    return ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32)) << 32) |
+           (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+}
+
 // *p at an address that is the same for the whole wave, through the scalar cache: of memory that nothing writes during the launch
 template <typename U>
 __device__ __forceinline__ U uniform_load(const U* p) {

@@ -31,7 +31,7 @@
 // What bounds it: the host link.  From the first request to the last bundle it moves 55 to 57 GB/s (a copy of 256 MiB by the
 // runtime: 57.5).  In front of the first request are a launch and two hand-overs, OPT-6.7B shape (Falcon-7B shape), us from the
 // start of the first workgroup: x A published 2.4 (2.5), masks published 4.7 (5.0), known to the loaders 6.2 (6.6), first request 7
-// (7.5); behind the last bundle is the down projection.  A compute unit has about 5 KiB of host reads under way, whatever its
+// (7.5), of an early bundle 5; behind the last bundle is the down projection.  A compute unit has about 5 KiB of host reads under way, whatever its
 // waves ask for, so some 30 loaders fill the link.
 // Measured on gfx950, one decode token, with five launches -> with this kernel and the down projection: fp32 d = 256, F = 1024:
 // 23.4 -> 14.1 us; OPT-6.7B shape 65.3 -> 57; Falcon-7B shape 149.5 -> 136; Llama-2 shape gated, from a graph, 148.7 -> 132, with
@@ -151,12 +151,13 @@ __device__ __forceinline__ void own_t(const StepArgs& a, PredictLds& L) {
 
 // The 64 mask bits of a tile of neurons: as k_predict_mask for one token.  The weights and offsets are requested by
 // the constructor, before t is there.
-template <typename T>
+// WIDE: the weights are widened (`widen`) ahead of t.
+template <typename T, bool WIDE = true>
 struct MaskTile {
     using V = typename Vec<T>::type;
     static constexpr int VE = Vec<T>::N, LPB = 8 / VE;
     V bv[kMaskRows][LPB];
-    double bd[kMaskRows][8];
+    double bd[WIDE ? kMaskRows : 1][8];
     float cv;                        // offset of neuron 64 * tile + lane
     int n0;
     bool own_ok;                     // ... which exists
@@ -185,7 +186,6 @@ struct MaskTile {
                 for (int e = 0; e < VE; ++e) bd[u][q * VE + e] = (double)bv[u][q][e];
     }
     // the 64 mask bits of the tile (0 past the last neuron), in every wave; one barrier
-    template <bool WIDE>
     __device__ __forceinline__ unsigned long long finish(const StepArgs& a, PredictLds& L) {
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid & (kMaskCols - 1), jg = tid >> 3;
         const T* B = (const T*)a.B;
@@ -197,7 +197,7 @@ struct MaskTile {
             if (u * kMaskJg < a.rank) {              // (uniform; bd[u] is 0 past the end)
                 const double tj = L.t[min(jg + u * kMaskJg, a.rank)];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tj, WIDE ? bd[u][e] : (double)bv[u][e / VE][e % VE], v[e]);
+                for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(tj, WIDE ? bd[WIDE ? u : 0][e] : (double)bv[u][e / VE][e % VE], v[e]);
             }
         }
         if (n0 < a.F) {
@@ -221,6 +221,26 @@ struct MaskTile {
         return __ballot(own_ok && z > (double)a.theta);
     }
 };
+
+// t of this step into LDS (with the 0 behind it), from copy `rep` of its words; one barrier.  Returns whether all of it has come.
+__device__ __forceinline__ bool await_t(const StepArgs& a, PredictLds& L, int rep, unsigned now) {
+    const int tid = threadIdx.x;
+    unsigned* t32 = reinterpret_cast<unsigned*>(L.t);
+    const unsigned long long* src = a.t_words + (size_t)(rep & (kWordReps - 1)) * a.t_pitch;
+    bool ok = true;
+    for (int i0 = tid; i0 < 2 * a.rank + 2; i0 += 4 * 256) {
+        unsigned p[4];
+        const int n = min(4, (2 * a.rank - i0 + 255) >> 8);
+        ok = poll_words<4>(src + i0, 256, n, now, a.polls, p) && ok;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i0 + i * 256 < 2 * a.rank + 2) t32[i0 + i * 256] = p[i];         // (0 from n on)
+    }
+    const bool missing = __any(!ok);
+    if ((tid & 63) == 0) L.missing[tid >> 6] = missing;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(L.missing[0] | L.missing[1] | L.missing[2] | L.missing[3]) == 0;
+}
 
 template <typename T, int NI, int WGS>
 __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, PredictLds& L) {
@@ -251,25 +271,11 @@ __device__ __forceinline__ void lowrank_role(const StepArgs& a, int block, Predi
     }
     if (!has_tile) return;
     tile.widen();
-    unsigned* t32 = reinterpret_cast<unsigned*>(L.t);
-    const unsigned long long* src = a.t_words + (size_t)(block & (kWordReps - 1)) * a.t_pitch;
-    bool ok = true;
-    for (int i0 = tid; i0 < 2 * a.rank + 2; i0 += 4 * 256) {     // (with the 0 behind them)
-        unsigned p[4];
-        const int n = min(4, (2 * a.rank - i0 + 255) >> 8);
-        ok = poll_words<4>(src + i0, 256, n, now, a.polls, p) && ok;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (i0 + i * 256 < 2 * a.rank + 2) t32[i0 + i * 256] = p[i];         // (0 from n on)
-    }
-    const bool missing = __any(!ok);
-    if ((tid & 63) == 0) L.missing[tid >> 6] = missing;
-    __syncthreads();
-    if (__builtin_expect((L.missing[0] | L.missing[1] | L.missing[2] | L.missing[3]) != 0, 0)) {
+    if (__builtin_expect(!await_t(a, L, block, now), 0)) {
         __syncthreads();
         own_t<T, NI>(a, L);
     }
-    const unsigned long long word = tile.template finish<true>(a, L);
+    const unsigned long long word = tile.finish(a, L);
     if (tid < 64) {
         if (tid < 2 * kWordReps)
             word_store(a.m_words + (size_t)(tid >> 1) * a.m_pitch + 2 * block + (tid & 1), now,
@@ -320,6 +326,7 @@ struct PlanLds {
     unsigned long long first_bits;           // the neuron of the loader's first unit: bit number first_at.y of these that is
     int2 first_at;                           //  set, from neuron first_at.x on
     int listed;                              // waves that have written their part of ids
+    unsigned long long early;                // early tiles with added neurons, one bit each
     union {
         PredictLds predict;                  // only when a wait ran out
         uint16_t ids[kListItems];            // loaders: the new neurons of the work items
@@ -363,10 +370,10 @@ __device__ __forceinline__ void own_masks(const StepArgs& a, PlanLds& L, int wpt
                 half[hf] = L.byte[0] | L.byte[1] | L.byte[2] | L.byte[3];
             }
         } else {
-            MaskTile<T> tile;
+            MaskTile<T, false> tile;
             tile.request(a, w);
             __syncthreads();
-            const unsigned long long word = tile.template finish<false>(a, L.predict);
+            const unsigned long long word = tile.finish(a, L.predict);
             half[0] = (unsigned)word;
             half[1] = (unsigned)(word >> 32);
         }
@@ -448,6 +455,21 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         }
         return;
     }
+    // Early bundles (one token, low-rank predictor).  A loader decides the mask word of an early tile for itself, as soon as t is
+    // there, and asks for the first neuron it adds: that is 2 us before all masks are known and its place in the list with them,
+    // time in which the link did nothing.  The early tiles are the first words of the first threads' runs, one per loader (per pair
+    // of them, who take a part each); which neurons they add follows from the masks, so every loader knows what the others have
+    // taken.  What is read early holds up what the loader reads next, the masks, until it has arrived, so it is done where the
+    // last step kept every loader busy.  us a step, without -> with, two timings in turn: OPT shape 55.9 -> 53.7 and 54.3 -> 52.4, eight
+    // stacked layers from a graph 464 -> 450, Falcon shape 134.9 -> 134.4, 24 steps with the dynamic window 2816 -> 2781; d = 1024, F =
+    // 8192 21.1 -> 20.4; d = 2048, F = 8192, gated, 40.9 -> 38.9; fp32 d = 1288, F = 5000 28.9 -> 27.5; Llama-2 shape the same (half as
+    // many loaders, twice the bytes).  Rows of one KiB have 128 loaders and hardly ever as much to load; there the code alone costs
+    // 0.15 of 13 us.
+    constexpr bool EARLY = MODE == kOneToken && !GATE && NI > 1;
+    constexpr int PARTS = PAIRED ? 2 : 1;                         // loaders of a bundle
+    const int early_tiles = EARLY && cur.n_added * PARTS >= a.n_load ? min(min(a.n_load / PARTS, kWave), (nwords + wpt - 1) / wpt) : 0;
+    const int mine = (wg - 1) / PARTS;                            // (wg >= 1)
+    const bool has_early = wg > 0 && mine < early_tiles;
     const unsigned stamp_now = (unsigned)cur.step + 1u;
     const int n = cur.num_used, slot_now = cur.ring_pos % k, oldest = min(cur.window_len, k - a.keep);      // largest age that stays in the window
     unsigned long long prev[4], keep[4], m[4], now[4];
@@ -475,6 +497,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     T* matrix = (T*)a.matrix;
     V hv[GA][NI], mv[GA][NI];                                    // the vectors of a unit: host bundle, tail row
     int k_eff = k, off_a = 0, off_r = 0, tot_a = 0, tot_r = 0, n2 = 0, items = 0;
+    unsigned long long adding = 0ull;                             // early tiles with added neurons
     // counts and list positions of the added and removed neurons; returns whether any thread is `missing` its words
     auto diff = [&](bool missing) -> bool {
         int pa = 0, pr = 0;
@@ -485,8 +508,13 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         }
         const int v = (pr << 16) | pa, inc = wave_inclusive_scan(v, lane), ex = inc - v;         // (a wave counts at most 16384)
         const unsigned long long none = __any(missing) ? 1ull << 63 : 0ull;
+        if constexpr (EARLY) {
+            const unsigned long long adds = __ballot(lane < early_tiles && (now[0] & ~prev[0]) != 0ull);
+            if (tid == 0) L.early = adds;
+        }
         if (lane == kWave - 1) L.wave_tot[wave] = none | ((unsigned long long)(unsigned)(inc >> 16) << 32) | (unsigned)(inc & 0xffff);
         lds_barrier();
+        if constexpr (EARLY) adding = L.early;
         unsigned long long before = 0, all = 0, flags = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -571,6 +599,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     const int x_pieces = nvec * a.batch;
     V xs[MODE == kOneToken ? 1 : 16];
     bool missing = false;
+    int asked = -1;                                              // neuron whose part is on its way already
     if constexpr (MODE != kOneToken) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -587,6 +616,21 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                 }
         }
     } else {
+        if constexpr (EARLY) {
+            if (has_early) {                                     // uniform
+                MaskTile<T> tile;
+                tile.request(a, mine * wpt);
+                const unsigned long long held = a.cur_set[(size_t)cur.set_par * a.ring_words + mine * wpt];
+                tile.widen();
+                if (await_t(a, L.predict, wg, stamp_now)) {
+                    const unsigned long long bits = tile.finish(a, L.predict) & ~uniform(held);
+                    if (bits) {
+                        asked = __builtin_amdgcn_readfirstlane(mine * wpt * 64 + __ffsll((long long)bits) - 1);
+                        if (wave == 0) request_host(asked, PAIRED ? lw & 1 : 0);
+                    }
+                }
+            }
+        }
         unsigned p[8];
         const int w0 = tid * wpt, nw = max(0, min(wpt, nwords - w0));
         missing = !poll_words<8, !GATE>(a.m_words + (size_t)(wg & (kWordReps - 1)) * a.m_pitch + 2 * w0, 1, 2 * nw, stamp_now,
@@ -676,23 +720,32 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     }
     n2 = n - tot_r;
     items = max(tot_a, tot_r);
+    // Early tiles with added neurons; the first neuron of each is taken, the others are dealt to the loaders in turn, in the first
+    // round to those that have no early one.  (Nothing is taken early where the list does not go in one piece.)
+    const unsigned long long early = EARLY && __builtin_amdgcn_readfirstlane(tot_a) <= kListItems ? uniform(adding) : 0ull;
+    const int n_early = __popcll(early);
+    const bool is_early = has_early && ((early >> mine) & 1ull);
+    const int unit_first = lw - PARTS * (mine < early_tiles ? __popcll(early & ((1ull << (mine & 63)) - 1ull)) : n_early);
+    auto early_before = [&]() {                                   // ... of the threads below this one
+        return wave == 0 ? (int)__builtin_amdgcn_mbcnt_hi((unsigned)(early >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)early, 0u)) : n_early;
+    };
     // The word with the neuron of this loader's first unit is looked up by the thread that holds it (the neuron is its r-th bit);
     // the list is written while the first host read is on its way.
-    const int unit0 = PAIRED ? lw >> 1 : lw;
     {
-        int r = unit0 - off_a;
-        bool mine = wg > 0 && r >= 0;
+        int r = unit_first / PARTS - (off_a - early_before());
+        bool open = wg > 0 && r >= 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (i < wpt) {
                 const unsigned long long bits = now[i] & ~prev[i];
                 L.rem[tid * wpt + i] = prev[i] & ~now[i];
                 L.add[tid * wpt + i] = bits;
-                const int c = __popcll(bits);
-                if (mine && r < c) {
-                    L.first_bits = bits;
+                const unsigned long long dealt = i == 0 && wave == 0 && ((early >> lane) & 1ull) ? bits & (bits - 1ull) : bits;
+                const int c = __popcll(dealt);
+                if (open && r < c) {
+                    L.first_bits = dealt;
                     L.first_at = make_int2((tid * wpt + i) * 64, r);
-                    mine = false;
+                    open = false;
                 }
                 r -= c;
             }
@@ -834,12 +887,15 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         return;
     }
 
-    if (loads && lw < (PAIRED ? 2 * tot_a : tot_a)) {            // unit lw (below kListItems)
+    if (loads && is_early) {
+        const int w = mine * wpt, id = w * 64 + __ffsll((long long)uniform(L.add[w])) - 1;
+        if (__builtin_expect(id != asked, 0)) request_host(id, PAIRED ? lw & 1 : 0); // (t did not come in time)
+    } else if (loads && unit_first < PARTS * (tot_a - n_early)) {        // (below kListItems)
         const unsigned long long bits = L.first_bits;
         const int2 at = L.first_at;
         const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bits >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bits, 0u));
         const unsigned long long it = __ballot(((bits >> lane) & 1ull) && before == at.y);
-        request_host(__builtin_amdgcn_readfirstlane(at.x) + __ffsll((long long)it) - 1, PAIRED ? lw & 1 : 0);
+        request_host(__builtin_amdgcn_readfirstlane(at.x) + __ffsll((long long)it) - 1, PAIRED ? unit_first & 1 : 0);
     }
     if (wave > 0) {
         if (wave == 1) fill_ids(0, lane, L.off[lane]);           // (for the wave that loads)
@@ -1101,7 +1157,8 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             lds_barrier();
         }
         const int n_a = min(max(tot_a - c0, 0), kListItems), n_r = min(max(tot_r - c0, 0), kListItems);     // of this piece
-        const int units = PAIRED ? 2 * n_a : n_a;
+        const bool early_first = c0 == 0 && is_early;
+        const int taken = c0 == 0 ? PARTS * n_early : 0, units = PARTS * n_a - taken;        // units dealt in turn
         const int only = max(n_r - n_a, 0);                      // rows that nothing overwrites
         if (MODE != kOneToken && wave > 0) work();
         if (wave == 0) {
@@ -1110,10 +1167,12 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                 float old_bias, new_bias, old_gate, new_gate;
                 unsigned long long plan;
             };
-            auto make_unit = [&](int u, bool ask) {              // its numbers, and the requests for its bundle
+            // (item of the dealt bundle j: behind it in the list are the early ones below)
+            const int early_at = EARLY && ((early >> lane) & 1ull) ? L.off[lane] - early_before() : 0x7fffffff;
+            auto make_item = [&](int i, int part, bool ask) {    // its numbers, and the requests for its bundle
                 Unit r;
-                r.part = PAIRED ? u & 1 : 0;
-                r.i = PAIRED ? u >> 1 : u;
+                r.part = part;
+                r.i = i;
                 const int s = n2 + c0 + r.i;
                 r.nid = __builtin_amdgcn_readfirstlane((int)L.ids[r.i]);
                 r.old_id = owner_of(s);
@@ -1126,9 +1185,11 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                 r.new_gate = gate_of(r.nid);
                 return r;
             };
-            int place = lw, round = 0;
-            if (lw < units) {
-                Unit cu = make_unit(lw, c0 > 0);                 // (the bundle of the first piece was requested above)
+            auto item_of = [&](int u) { return EARLY ? u / PARTS + __popcll(__ballot(early_at <= u / PARTS)) : u / PARTS; };
+            int place = lw, round = -taken;
+            if (early_first || unit_first < units) {             // (the bundle of the first piece was requested above)
+                Unit cu = make_item(early_first ? __builtin_amdgcn_readfirstlane(L.off[mine]) : item_of(unit_first),
+                                    (early_first ? lw : unit_first) & (PARTS - 1), c0 > 0);
                 for (;;) {
                     const int s = n2 + c0 + cu.i;
                     const int dst = dst_of(c0 + cu.i, cu.plan);
@@ -1158,7 +1219,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                     round += nw;
                     const bool more = round + place < units;
                     Unit nu = cu;
-                    if (more) nu = make_unit(round + place, true);
+                    if (more) nu = make_item(item_of(round + place), (round + place) & (PARTS - 1), true);
                     if (MODE == kOneToken && act) {
                         if (moves) finish_slot(dst, cu.old_id, cu.old_bias, mdu, mdg);
                         finish_slot(s, cu.nid, cu.new_bias, hdu, hdg);
