@@ -411,13 +411,16 @@ void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, h
 }
 
 // One token in one launch, where few workgroups wait for few words.  What the waiting costs grows with slices x rows (every word
-// is read by every slice), what the second launch costs does not: fp16 in a graph, rows in use / us in two launches -> in one
-// (all sizes in one): 16 slices 871: 6.2 -> 5.7, 32 slices 480: 6.0 -> 6.0, 983: 6.3 -> 6.6, 64 slices 264: 6.1 -> 5.8, 723:
-// 6.3 -> 6.5, 80 slices 703: 6.2 -> 7.4, 128 slices 337: 6.6 -> 7.8, 927: 6.0 -> 7.2; from the host 7.6 -> 5.4 to 6.5, 128 slices
-// 927: 7.0 -> 7.2 where the host is fast.  So 96 slices and more stay with two.
+// is read by every slice), what the second launch costs does not.  us a call, two launches -> one, twenty calls in a graph / from the
+// host (rows in use, the hint 1.15 times as many): 64 slices, d = 2048 341: 5.9 -> 5.4 / 6.8 -> 5.5, 685: 6.0 -> 5.8 / 6.8 -> 5.8 (8.8 -> 6.4 where
+// the host is slow), 1111: 6.1 -> 6.1 / 6.7 -> 6.3; 48 slices 685: 6.0 -> 5.9 / 6.8 -> 5.7, 1111: 6.1 -> 6.0 / 6.8 -> 6.0; 32 slices 1111:
+// 6.0 -> 5.8 / 6.8 -> 5.7; fp32, 64 slices, d = 1024 685: 6.4 -> 5.6 / 6.9 -> 5.6.  Rows gated or read in full are longer on their way:
+// 64 slices 685: gated 6.15 -> 6.27 / 6.8 -> 6.3, in full 6.45 -> 6.55 / 6.8 -> 6.4, so half as many words there.  128 slices (OPT shape),
+// 927: 6.5 -> 7.2 / 8.8 -> 7.7, 7.4 -> 7.9 where the host is fast: two launches.
 bool ffn_one(const lif_layer* L, int batch) {
     const int rows = geometry_rows(L), slices = down1_slices(L->cfg);
-    return batch == 1 && L->one_words && rows <= kOneRows && slices * rows <= kOneWords;
+    const int most = L->cfg.glu || L->cfg.ffn_mode == LIF_FFN_FULL_BUNDLE ? kOneWords / 2 : kOneWords;
+    return batch == 1 && L->one_words && rows <= kOneRows && slices * rows <= most;
 }
 template <typename T, bool GLU, bool SKIP>
 void launch_ffn_one(lif_layer* L, const void* x, void* y, hipStream_t s) {

@@ -22,7 +22,7 @@ namespace lif {
 
 constexpr int kOneWaves = 8, kOneUpWaves = 4;        // waves of a workgroup; those of the activation stage that have rows
 constexpr int kOneReps = 4;                          // copies of every word
-constexpr int kOneSlices = 64, kOneWords = 16384;    // column slices, and words read by all of them, up to which this form is taken
+constexpr int kOneSlices = 64, kOneWords = 65536;    // column slices, and words read by all of them, up to which this form is taken
 constexpr int kOneRows = kDown1FewRows;              // ... and rows: one pass of 8 waves
 constexpr int kOneCapacity = 16384;                  // (there is a word for every slot)
 constexpr int kOneWaits = 1 << 20;                   // failed reads of a thread before a launch whose waits ran out is given up:
