@@ -114,7 +114,7 @@ def pmc_traffic(pmc_dir):
         if not copies or max(copies) <= 0:
             return None
         scale = 262144.0 / max(copies)                       # reported KiB -> true KiB (the copy moves 256 MiB each way)
-        # one lif_sparse_ffn call = a k_ffn_one dispatch, or a k_ffn_up dispatch and the k_ffn_down dispatch right
+        # one lif_sparse_ffn call = a k_ffn_one dispatch, or a k_ffn_up dispatch and the k_ffn_down (+ finish) dispatches right
         # after it (lif_step never launches k_ffn_one or k_ffn_up, so these are exactly the FFN-only calls)
         rows.sort(key=lambda r: int(r["Dispatch_Id"]))
         calls, total, open_call = 0, 0.0, False

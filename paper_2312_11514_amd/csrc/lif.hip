@@ -374,13 +374,17 @@ void launch_ffn_down_mfma_rows(lif_layer* L, int batch, void* y, float* h, float
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
+    const bool finish = wg_rows > 1 && slices * wg_rows > kDmWgsAtOnce;        // the chunk sums are added by a launch of its own
 #define LIF_DM(FUSED)                                                                                        \
     hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, ROWS, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),       \
                        dim3(kDmWaves * 64), 0, s, (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y,  \
-                       ypart, L->arrived, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
+                       ypart, finish ? nullptr : L->arrived, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
     if (fc.on) LIF_DM(true);
     else LIF_DM(false);
 #undef LIF_DM
+    if (finish)
+        hipLaunchKernelGGL(k_ffn_down_mfma_finish, dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart, (_Float16*)y,
+                           c.d_model, batch, chunk_rows, wg_rows, L->st);
 }
 
 template <bool SKIP>

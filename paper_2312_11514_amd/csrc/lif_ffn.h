@@ -255,7 +255,8 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
 // the L2, was twice as slow as a launch that adds them).  The count wraps to 0 by itself, whatever launches have been before.
 // us a pass, a launch of its own for these sums -> here, two timings in turn: 8 tokens of the Llama-2 shape 229.7 -> 226.8 (the launch
 // took 4.6, the down projection now 0.5 more), 12 passes of 5 tokens 2300 -> 2286, fp32 d = 1288, 3 tokens, four calls 68.6 -> 67.4;
-// 10989 rows all read, 8 tokens, d = 4096, 22 chunks, both stages 56.8 -> 56.6.  With 16 chunks asked for at a time the last was 56.65.
+// 10989 rows all read, 8 tokens, d = 4096, 22 chunks, both stages 56.8 -> 56.5.  16 chunks asked for at a time are better from 25 on
+// (4 tokens, d = 2560, 40.1 -> 39.4; a launch 39.8), 8 below (the 22 chunks 56.6).
 constexpr int kArrivedPitch = 32;     // counters of two slices are this many words apart: a cache line
 __device__ __forceinline__ void store_part(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // Whether this workgroup is the last of `parts` whose sums of a slice are written (uniform; `flag` is in LDS)
@@ -266,10 +267,10 @@ __device__ __forceinline__ bool last_part(unsigned* arrived, int parts, int* fla
     __syncthreads();
     return *flag != 0;
 }
-// sum[e] = the four floats from ypart[at + c * stride + e] on (at and stride multiples of 4), added over the chunks c in order
-template <typename A>
+// sum[e] = the four floats from ypart[at + c * stride + e] on (at and stride multiples of 4), added over the chunks c in order; PER of
+// them are asked for at a time, the next ones ahead of the adds
+template <int PER, typename A>
 __device__ __forceinline__ void sum_parts(const float* ypart, unsigned at, unsigned stride, int chunks, A (&sum)[4]) {
-    constexpr int PER = 8;                                       // asked for at a time, the next ones ahead of the adds
     const unsigned bytes = stride * (unsigned)chunks * 4u;
     auto request = [&](f32x4 (&v)[PER], int c0) {
 #pragma unroll
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
     }
     if (chunks > 1 && gridDim.y > 1) {
         if (!last_part(arrived + slice * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
-        if (writer) sum_parts(ypart, (unsigned)(ob * d + ocol), (unsigned)(batch * d), chunks, total);
+        if (writer) sum_parts<8>(ypart, (unsigned)(ob * d + ocol), (unsigned)(batch * d), chunks, total);
     }
     if (writer) {
         V out;

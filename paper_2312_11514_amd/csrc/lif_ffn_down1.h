@@ -283,7 +283,7 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
         const int oc = slice * (LANES * VE) + tid * 4;
         if (tid < LANES * VE / 4 && oc < d) {        // four columns per thread
             double sum[4];
-            sum_parts(ypart, (unsigned)oc, (unsigned)d, chunks, sum);
+            sum_parts<8>(ypart, (unsigned)oc, (unsigned)d, chunks, sum);
 #pragma unroll
             for (int e = 0; e < 4; ++e) y[oc + e] = (T)sum[e];
         }

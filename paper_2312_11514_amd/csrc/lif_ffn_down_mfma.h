@@ -67,8 +67,8 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // A pass compacts the contributing rows of ROWS slots (SKIP: rows with some activation; else all rows in use) in a
 // fixed order (thread-major over slots p * threads + tid); the waves take groups of 32 compacted rows in turn.
 // The waves of a pass are added in wave order, a chunk's passes in order, the chunks in chunk order (by this kernel when
-// one workgroup row is launched, else by the last workgroup of a slice from ypart[chunk][token][d], see last_part).  Nothing
-// depends on the launch geometry.
+// one workgroup row is launched, else by the last workgroup of a slice from ypart[chunk][token][d], see last_part; `arrived` null: by
+// k_ffn_down_mfma_finish).  No sum depends on the launch geometry.
 template <bool SKIP, int WAVES, int ROWS, bool FUSED>
 __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16* __restrict__ matrix,
                                                               const float* __restrict__ h, const FusedRows fused,
@@ -273,16 +273,44 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
             if (og * 4 + r < batch && ocol < d) y[(size_t)(og * 4 + r) * d + ocol] = (_Float16)total[r];
         return;
     }
+    if (!arrived) return;                            // (k_ffn_down_mfma_finish)
     if (!last_part(arrived + blockIdx.x * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
     // four columns of a token per thread
     static_assert(BT * kDmCols == 4 * T, "one piece of every token and four columns");
     const int pt = tid / (kDmCols / 4), pc = blockIdx.x * kDmCols + tid % (kDmCols / 4) * 4;
     if (pt < batch && pc < d) {
         float sum[4];
-        sum_parts(ypart, (unsigned)(pt * d + pc), (unsigned)(batch * d), chunks, sum);
+        if (chunks > 24) sum_parts<16>(ypart, (unsigned)(pt * d + pc), (unsigned)(batch * d), chunks, sum);
+        else sum_parts<8>(ypart, (unsigned)(pt * d + pc), (unsigned)(batch * d), chunks, sum);
         typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
         *reinterpret_cast<f16x4*>(y + (size_t)pt * d + pc) = f16x4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
     }
+}
+
+// y = sum of the chunk partials in chunk order, rounded once to fp16: the launch behind a k_ffn_down_mfma grid of more workgroups than
+// the chip holds at once (kDmWgsAtOnce).  There a workgroup that waits for its stores and its count keeps the next one out: d = 5120,
+// gated, 6 tokens, 27 chunks, both stages 79.1 us with this launch, 80.1 to 80.4 with the last workgroup of a slice adding.  Does
+// nothing when a single chunk was in use (y is written already).  The partials of the first `ahead` chunks, which that grid had
+// workgroup rows for, are requested before the row count is known; behind it they cost another round trip.  (Straight code: branches
+// for each of them were 0.5 us of instructions that run once.)  grid = ceil(batch * d / 256), block = 256.
+__global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* ypart, _Float16* __restrict__ y, int d, int batch, int chunk_rows,
+                                                              int ahead, const DevState* st) {
+    const int i = blockIdx.x * 256 + threadIdx.x, stride = batch * d;
+    const float* p = ypart + min(i, stride - 1);
+    const int err = st->cur.error, n = st->cur.num_used;
+    float v[kDownChunksMax];
+#pragma unroll
+    for (int c = 0; c < kDownChunksMax; ++c) v[c] = p[min(c, ahead - 1) * stride];         // (beyond: lines that are on their way already)
+    asm volatile("" ::: "memory");                   // (the compiler would ask for them, and for the count, where they are used)
+    if (err) return;
+    const int chunks = down_mfma_chunks(n, chunk_rows), here = min(ahead, chunks);
+    if (chunks == 1) return;
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < kDownChunksMax; ++c) sum = c < here ? sum + v[c] : sum;
+#pragma unroll 1
+    for (int c = ahead; c < chunks; ++c) sum += p[c * stride];                             // more rows in use than the hint let expect
+    if (i < stride) y[i] = (_Float16)sum;
 }
 
 }  // namespace lif

@@ -1,7 +1,7 @@
 """Row chunks of the down projection, whose sums the last workgroup of a column slice adds: the bits do not depend on how many
 workgroup rows share the chunks (a row-count hint that is far too small leaves one, which adds its own), nor on the call, and are
-those of the oracle's FFN over the cached rows within the tolerance of one FFN call.  2 to more than 16 chunks (those asked for
-at a time), ragged last slices, every kernel."""
+those of the oracle's FFN over the cached rows within the tolerance of one FFN call.  2 to more than 24 chunks (asked for 8 at a
+time, then 16), ragged last slices, every kernel, and more workgroups than the chip holds, where a launch of its own adds them."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype,batch,full,d,F", [
     ("f16", 1, False, 136, 16384), ("f16", 1, True, 72, 8000), ("f32", 1, True, 68, 16384),
-    ("f16", 5, False, 160, 4800), ("f16", 8, True, 264, 9000), ("f16", 3, False, 4104, 1480),
+    ("f16", 5, False, 160, 4800), ("f16", 8, True, 264, 15000), ("f16", 3, False, 4104, 1480), ("f16", 2, False, 4104, 12304),
     ("f32", 3, False, 132, 1400), ("f32", 8, True, 68, 9000)])
 def test_chunks_shared_or_not(dtype, batch, full, d, F):
     from oracle import lif_oracle as O
