@@ -235,11 +235,11 @@ constexpr int kDownRowsMost = 512, kDownRowsLeast = 128;      // rows per chunk 
 constexpr int kDownWgs = 512;         // workgroups that chunks of fewer than kDownRowsMost rows are made for
 
 // Row chunks in use for n cached rows, several tokens and `slices` column slices: their active sets add up, most rows are read, and
-// a chunk is at most kDownRowsMost rows: one chunk (no partial sums, no second launch) up to there, beyond it chunks of down to
+// a chunk is at most kDownRowsMost rows: one chunk (no partial sums) up to there, beyond it chunks of down to
 // kDownRowsLeast until kDownWgs workgroups stream at once.  With chunks of 512 rows throughout, half of the compute units had
 // nothing to do and a thread went through 32 rows, four at a time.  One FFN call, us, 512 -> now: d = 1288, 3 tokens, 988 rows
 // 14.5 -> 12.3, 2044 rows 16.1 -> 13.4, 4081 rows 18.9 -> 16.4; 8 tokens, 1634 rows 20.6 -> 17.4, 6859 rows 35.1 -> 33.9; d =
-// 4096, 3 tokens, 949 rows 19.5 -> 17.3, 3874 rows the same.  Up to 512 rows one chunk is better where no second launch is needed
+// 4096, 3 tokens, 949 rows 19.5 -> 17.3, 3874 rows the same.  Up to 512 rows one chunk is better
 // (3 tokens, d = 1288, 208 rows 8.9 against 11.3).
 // The host sizes the grid with the same rule.
 __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {

@@ -26,9 +26,9 @@ constexpr int kDown1OneFull = 3584;      // ... when every row is read
 constexpr int kDown1RowsSkip = 4096;     // rows per chunk beyond, for workgroups of 8 waves
 constexpr int kDown1RowsFull = 1024;
 
-// Row chunks in use for n cached rows and `slices` column slices.  One chunk (no partial sums, no second launch) as long as
+// Row chunks in use for n cached rows and `slices` column slices.  One chunk (no partial sums) as long as
 // d / 32 workgroups of 16 waves keep up with the rows: skipping rows, 8000 rows take 8.6 us in one chunk against 11.5 us in two
-// chunks and a second launch; reading every row (one whole call, OPT shape) 3072 rows 15.7 against 16.8, 3584 rows 17.3 either
+// chunks and the launch that added their sums then; reading every row (one whole call, OPT shape) 3072 rows 15.7 against 16.8, 3584 rows 17.3 either
 // way, 4096 rows 18.7 in four chunks.
 // Beyond, workgroups of 8 waves, several to a compute unit (with 16 waves one workgroup fills it, and what is left of the
 // workgroups after 256 of them runs almost alone): us a call, 16 waves -> 8 waves, every row read: OPT shape 5120 rows 23.1 ->

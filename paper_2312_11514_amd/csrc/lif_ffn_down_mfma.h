@@ -33,7 +33,7 @@ constexpr int kDmWaves = 4;              // waves per workgroup: 8 are a little 
 // rows: d = 512, 3 tokens, 1835 rows 15.6 -> 13.3; d = 1024, 8 tokens, 6948 rows 19.8 -> 17.7; d = 4096, 8 tokens, 1674 rows 19.8
 // -> 17.2. But where 256-row workgroups would need a second round on the chip 512 are better: d = 4096, 8 tokens, 8177 of 8192
 // rows 33.9 against 37.2. (Chunks of 256 rows in passes made for 512 gain a third of it.) And small caches are likely to hold the
-// 257 to 450 rows that one chunk of 512 takes without a second launch: d = 512, 2 tokens, 299 rows 12.1 against 12.9.
+// 257 to 450 rows that one chunk of 512 takes without partial sums: d = 512, 2 tokens, 299 rows 12.1 against 12.9.
 __host__ __device__ __forceinline__ int down_mfma_pass_rows(int capacity, int slices) {
     const int few = (capacity + kDmRowsFew - 1) / kDmRowsFew;
     return capacity > kDmSmall && few <= kDownChunksMax && few * slices <= kDmWgsAtOnce ? kDmRowsFew : kDmRows;

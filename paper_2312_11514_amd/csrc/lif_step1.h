@@ -461,11 +461,11 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     // of them, who take a part each); which neurons they add follows from the masks, so every loader knows what the others have
     // taken.  What is read early holds up what the loader reads next, the masks, until it has arrived, so it is done where the
     // last step kept every loader busy.  us a step, without -> with, two timings in turn: OPT shape 55.9 -> 53.7 and 54.3 -> 52.4, eight
-    // stacked layers from a graph 464 -> 450, Falcon shape 134.9 -> 134.4, 24 steps with the dynamic window 2816 -> 2781; d = 1024, F =
-    // 8192 21.1 -> 20.4; d = 2048, F = 8192, gated, 40.9 -> 38.9; fp32 d = 1288, F = 5000 28.9 -> 27.5; Llama-2 shape the same (half as
-    // many loaders, twice the bytes).  Rows of one KiB have 128 loaders and hardly ever as much to load; there the code alone costs
-    // 0.15 of 13 us.
-    constexpr bool EARLY = MODE == kOneToken && !GATE && NI > 1;
+    // stacked layers from a graph 464 -> 450, Falcon shape 134.9 -> 134.4, 24 steps with the dynamic window 2816 -> 2781; d = 2048, F = 8192,
+    // gated, 40.9 -> 38.9; fp32 d = 1288, F = 5000 28.9 -> 27.5; Llama-2 shape the same (half as many loaders, twice the bytes).  Rows of
+    // up to 2 KiB have 64 to 128 loaders and seldom as much to load, and there the code alone costs more than it gives: d = 736, 18
+    // added 13.7 -> 14.9 (d = 1024, F = 8192, many added 21.1 -> 20.4).
+    constexpr bool EARLY = MODE == kOneToken && !GATE && PAIRED;
     constexpr int PARTS = PAIRED ? 2 : 1;                         // loaders of a bundle
     const int early_tiles = EARLY && cur.n_added * PARTS >= a.n_load ? min(min(a.n_load / PARTS, kWave), (nwords + wpt - 1) / wpt) : 0;
     const int mine = (wg - 1) / PARTS;                            // (wg >= 1)

@@ -12,15 +12,15 @@ from tests.test_step1 import _make, _snapshot
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    # name: (dtype, glu, gate, d, F, rank, k, p, capacity, shrink, pairs), rows of more than 1 KiB
+    # name: (dtype, glu, gate, d, F, rank, k, p, capacity, shrink, pairs), "whole": on the other side of the rule (rows of up to 2 KiB have none)
     "whole": ("f16", False, False, 1024, 1960, 32, 3, 0.15, 1960, False, 1),
     "whole-most-loaders": ("f16", True, False, 768, 6000, 24, 2, 0.1, 6000, False, 64),
     "parts": ("f16", False, False, 2064, 3000, 40, 3, 0.1, 3000, False, 5),
     "parts-f32-gated": ("f32", True, False, 772, 1600, 20, 2, 0.2, 1600, False, 2),
     "two-words-a-thread": ("f16", False, False, 1032, 17000, 16, 2, 0.02, 4000, False, 40),
-    "four-words-a-thread": ("f16", False, False, 520, 50000, 16, 2, 0.01, 5000, False, 64),
+    "four-words-a-thread": ("f16", False, False, 1032, 50000, 16, 2, 0.01, 5000, False, 64),
     "many-ranks": ("f16", False, False, 1096, 2000, 320, 3, 0.1, 2000, False, 3),
-    "pieces": ("f16", False, False, 520, 12000, 16, 1, 0.35, 12000, False, 3),
+    "pieces": ("f16", False, False, 1040, 12000, 16, 1, 0.35, 12000, False, 3),
     "dynamic-window": ("f16", False, False, 1040, 4160, 16, 9, 0.1, 900, True, 4),
 }
 
