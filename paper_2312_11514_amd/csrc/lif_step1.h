@@ -10,10 +10,11 @@
 //                                 are requested before the wait).  Gate predictor: 32 neurons per workgroup, nothing to wait for.
 //   workgroup n_pred              bookkeeping: waits for the masks, makes the deletion plan and publishes it, writes the window
 //                                 state, id lists and counts
-//   the next n_load workgroups    loaders: wait for the masks, work out the added ids (every workgroup for itself: cheaper than
-//                                 waiting for one that does), gather bundles from pinned host memory, move the rows they
-//                                 overwrite where the plan says and compute the activations of the rows they write (h_new,
-//                                 stamped with the step)
+//   the next n_load workgroups    loaders: after a step that kept them all busy, wait for t, decide a tile of neurons each (each
+//                                 pair) and ask for the first bundle it adds; wait for the masks, work out the added ids (every
+//                                 workgroup for itself: cheaper than waiting for one that does), gather bundles from pinned host
+//                                 memory, move the rows they overwrite where the plan says and compute the activations of the
+//                                 rows they write (h_new, stamped with the step)
 //   the rest                      activations of the rows that were already in use; behind the predictor where a load is
 //                                 likely to hide them (await_predictor), else at once
 // A value handed over is a 64-bit word: 32 bits of payload and the number of the step as a stamp, written by a relaxed
@@ -328,7 +329,7 @@ struct PlanLds {
     int listed;                              // waves that have written their part of ids
     unsigned long long early;                // early tiles with added neurons, one bit each
     union {
-        PredictLds predict;                  // only when a wait ran out
+        PredictLds predict;                  // an early tile; when a wait ran out
         uint16_t ids[kListItems];            // loaders: the new neurons of the work items
         struct {                             // bookkeeping: the deletion plan
             uint16_t hole[kHoleFew];
@@ -460,11 +461,18 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     // time in which the link did nothing.  The early tiles are the first words of the first threads' runs, one per loader (per pair
     // of them, who take a part each); which neurons they add follows from the masks, so every loader knows what the others have
     // taken.  What is read early holds up what the loader reads next, the masks, until it has arrived, so it is done where the
-    // last step kept every loader busy.  us a step, without -> with, two timings in turn: OPT shape 55.9 -> 53.7 and 54.3 -> 52.4, eight
-    // stacked layers from a graph 464 -> 450, Falcon shape 134.9 -> 134.4, 24 steps with the dynamic window 2816 -> 2781; d = 2048, F = 8192,
-    // gated, 40.9 -> 38.9; fp32 d = 1288, F = 5000 28.9 -> 27.5; Llama-2 shape the same (half as many loaders, twice the bytes).  Rows of
-    // up to 2 KiB have 64 to 128 loaders and seldom as much to load, and there the code alone costs more than it gives: d = 736, 18
-    // added 13.7 -> 14.9 (d = 1024, F = 8192, many added 21.1 -> 20.4).
+    // last step kept every loader busy.  us a step, without -> with, two timings in turn: OPT shape 55.9 -> 53.7 and 54.3 -> 52.5, eight
+    // stacked layers from a graph 463 -> 448, Llama-2 shape from a graph 131.4 -> 130.8, 24 steps with the dynamic window 2816 -> 2781;
+    // gated d = 4544 110.9 -> 109.1; fp32 gated d = 2048, F = 8192 74.7 -> 72.8, d = 4096 112.8 -> 110.4.  Rows of up to 2 KiB have 64
+    // to 128 loaders and seldom as much to load, and there the code alone costs more than it gives: d = 736, 18 added 13.7 -> 14.9
+    // (d = 1024, F = 8192, many added 21.1 -> 20.4).
+    // Where a wait for the masks runs out the early bundle is given up.  Kept in registers through own_masks it cost most fp32 forms
+    // and some gated ones a workgroup per compute unit, which shows where the predictor fills the chip or little is loaded: fp32,
+    // without early bundles / kept / given up: gated d = 2048, F = 16384 96.2 / 98.4 / 94.2, with 3 added 39.0 / 42.1 / 38.4; plain
+    // F = 32768 d = 640 44.6 / 46.8 / 44.3, d = 1288 59.1 / 59.4 / 55.9, d = 2304 79.4 / 80.7 / 77.0.
+    // The gated forms are 67 to 86 KB of code, more than the 64 KB instruction cache of two compute units.  With the tile decided by
+    // the predictor's own code (53 to 75 KB), which leaves the window's words to be read behind the bundle, most were slower all the
+    // same: OPT shape 52.6 -> 53.0, Llama-2 shape 130.0 -> 131.2, fp32 d = 4096 80.3 -> 81.1.
     constexpr bool EARLY = MODE == kOneToken && !GATE && PAIRED;
     constexpr int PARTS = PAIRED ? 2 : 1;                         // loaders of a bundle
     const int early_tiles = EARLY && cur.n_added * PARTS >= a.n_load ? min(min(a.n_load / PARTS, kWave), (nwords + wpt - 1) / wpt) : 0;
@@ -626,7 +634,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
                     const unsigned long long bits = tile.finish(a, L.predict) & ~uniform(held);
                     if (bits) {
                         asked = __builtin_amdgcn_readfirstlane(mine * wpt * 64 + __ffsll((long long)bits) - 1);
-                        if (wave == 0) request_host(asked, PAIRED ? lw & 1 : 0);
+                        if (wave == 0) request_host(asked, lw & 1);
                     }
                 }
             }
@@ -645,6 +653,13 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     if constexpr (MODE == kOneToken) {
         if (__builtin_expect(none, 0)) {                         // a wait ran out
             lds_barrier();
+            if constexpr (EARLY) {                               // what was asked for early is given up: no register is held through this
+                asked = -1;
+#pragma unroll
+                for (int g = 0; g < GA; ++g)
+#pragma unroll
+                    for (int it = 0; it < NI; ++it) hv[g][it] = V(0);
+            }
             own_masks<T, NI, GATE>(a, L, wpt, m);
             if (wg == 0) stage_owners();                         // (their place has been used)
 #pragma unroll
@@ -725,6 +740,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     const unsigned long long early = EARLY && __builtin_amdgcn_readfirstlane(tot_a) <= kListItems ? uniform(adding) : 0ull;
     const int n_early = __popcll(early);
     const bool is_early = has_early && ((early >> mine) & 1ull);
+    // (a whole number of bundles before lw: the part of a bundle that this loader takes first is lw % PARTS)
     const int unit_first = lw - PARTS * (mine < early_tiles ? __popcll(early & ((1ull << (mine & 63)) - 1ull)) : n_early);
     auto early_before = [&]() {                                   // ... of the threads below this one
         return wave == 0 ? (int)__builtin_amdgcn_mbcnt_hi((unsigned)(early >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)early, 0u)) : n_early;
@@ -889,13 +905,13 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
 
     if (loads && is_early) {
         const int w = mine * wpt, id = w * 64 + __ffsll((long long)uniform(L.add[w])) - 1;
-        if (__builtin_expect(id != asked, 0)) request_host(id, PAIRED ? lw & 1 : 0); // (t did not come in time)
+        if (__builtin_expect(id != asked, 0)) request_host(id, lw & 1);              // (t did not come in time)
     } else if (loads && unit_first < PARTS * (tot_a - n_early)) {        // (below kListItems)
         const unsigned long long bits = L.first_bits;
         const int2 at = L.first_at;
         const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bits >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bits, 0u));
         const unsigned long long it = __ballot(((bits >> lane) & 1ull) && before == at.y);
-        request_host(__builtin_amdgcn_readfirstlane(at.x) + __ffsll((long long)it) - 1, PAIRED ? unit_first & 1 : 0);
+        request_host(__builtin_amdgcn_readfirstlane(at.x) + __ffsll((long long)it) - 1, lw & (PARTS - 1));
     }
     if (wave > 0) {
         if (wave == 1) fill_ids(0, lane, L.off[lane]);           // (for the wave that loads)
@@ -1189,7 +1205,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
             int place = lw, round = -taken;
             if (early_first || unit_first < units) {             // (the bundle of the first piece was requested above)
                 Unit cu = make_item(early_first ? __builtin_amdgcn_readfirstlane(L.off[mine]) : item_of(unit_first),
-                                    (early_first ? lw : unit_first) & (PARTS - 1), c0 > 0);
+                                    lw & (PARTS - 1), c0 > 0);
                 for (;;) {
                     const int s = n2 + c0 + cu.i;
                     const int dst = dst_of(c0 + cu.i, cu.plan);
@@ -1322,10 +1338,10 @@ __global__ __launch_bounds__(256, (step1_wgs_per_cu<NI, GLU>())) void k_step1(co
 // loaders, and the activation stage over the rows in use - on the matrix cores (MFMA: fp16, d a multiple of 32), else one
 // wave per row.  Dynamic LDS: step_batch_lds bytes.
 // Registers (gfx950, as the compiler reports them): the loader role has more uniform values than the 106 scalar registers hold,
-// 85 to 146 of them live in lanes of vector registers (k_step1: 77 to 136).  No vector register goes to memory, which would queue
+// 85 to 146 of them live in lanes of vector registers (k_step1: 76 to 171).  No vector register goes to memory, which would queue
 // up behind the host reads; 17 of the 106 forms, all with the gate predictor, keep 36 bytes a lane there (k_step1: none).  The
 // predictor is a template parameter for that reason: a kernel with both forms of the role spilled 169 to 246 scalar registers and
-// was 82 to 106 KB of code (41 to 60 KB each by itself), more than the 64 KB instruction cache of two compute units.
+// was 82 to 106 KB of code (43 to 61 KB each by itself), more than the 64 KB instruction cache of two compute units.
 template <typename T, int NI, bool GLU, bool GATE, bool MFMA, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 1) void k_step_batch(const StepArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_step[];
