@@ -319,7 +319,7 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     const lif_config& c = L->cfg;
     const int slices = down1_slices(c);
     const int rows = geometry_rows(L);
-    // fewer workgroup rows than chunks are still correct; one, and no second launch, where the hint itself needs one chunk
+    // fewer workgroup rows than chunks are still correct; one, and no partial sums, where the hint itself needs one chunk
     const bool one = L->expected_rows > 0 && down1_chunks<SKIP>(std::min(L->expected_rows, c.capacity_rows), slices) == 1;
     const int wg_rows = one ? 1 : down1_chunks<SKIP>(rows, slices);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
@@ -334,15 +334,23 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     // slots if that many rows make one pass (else the order of the slots is not known yet)
     const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;
     const FusedRows f = fused_rows(L, fc);
-#define LIF_D1(W, FUSED)                                                                                     \
-    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W, FUSED>), dim3(slices + (fc.on ? 1 : 0), wg_rows), dim3(W * 64), 0, s,     \
+    const bool finish = L->expected_rows > 0 && down1_finish(wg_rows, slices);
+#define LIF_D1(W, FUSED, SHARED)                                                                             \
+    hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(W * 64), 0, s, \
                        (const T*)L->buf.matrix, h, f, (T*)y, ypart, L->arrived, c.d_model, c.capacity_rows, L->row_elems,        \
                        down_off, spec, slices, L->buf.pointers, L->gact, c.d_ffn, L->st)
-    if (waves == 8 && fc.on) LIF_D1(8, true);
-    else if (waves == 8) LIF_D1(8, false);
-    else if (fc.on) LIF_D1(16, true);
-    else LIF_D1(16, false);
+#define LIF_D1W(W)                                                                                           \
+    do {                                                                                                     \
+        if (wg_rows == 1 || finish) { if (fc.on) LIF_D1(W, true, false); else LIF_D1(W, false, false); }     \
+        else { if (fc.on) LIF_D1(W, true, true); else LIF_D1(W, false, true); }                              \
+    } while (0)
+    if (waves == 8) LIF_D1W(8);
+    else LIF_D1W(16);
+#undef LIF_D1W
 #undef LIF_D1
+    if (finish)
+        hipLaunchKernelGGL((k_ffn_down_finish<T, double, down1_chunks<SKIP>>), dim3((c.d_model + 255) / 256), dim3(256), 0, s, ypart, (T*)y,
+                           c.d_model, 1, slices, wg_rows, L->st);
 }
 
 // several tokens, fp32
@@ -355,13 +363,17 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
     const int slices = (c.d_model + cols - 1) / cols;
     const int wg_rows = down_chunks(geometry_rows(L), slices);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-#define LIF_DB(FUSED)                                                                                        \
-    hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(256),  \
+    const bool finish = L->expected_rows > 0 && down_finish(wg_rows, slices, batch);
+#define LIF_DB(FUSED, SHARED)                                                                                \
+    hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(256),  \
                        0, s, (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, L->arrived, c.d_model, batch,          \
                        c.capacity_rows, L->row_elems, down_off, slices, L->st)
-    if (fc.on) LIF_DB(true);
-    else LIF_DB(false);
+    if (wg_rows == 1 || finish) { if (fc.on) LIF_DB(true, false); else LIF_DB(false, false); }
+    else { if (fc.on) LIF_DB(true, true); else LIF_DB(false, true); }
 #undef LIF_DB
+    if (finish)
+        hipLaunchKernelGGL((k_ffn_down_finish<T, double, down_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart, (T*)y,
+                           c.d_model, batch, slices, wg_rows, L->st);
 }
 
 // several tokens, fp16: the down projection on the matrix cores
@@ -374,17 +386,17 @@ void launch_ffn_down_mfma_rows(lif_layer* L, int batch, void* y, float* h, float
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    const bool finish = wg_rows > 1 && slices * wg_rows > kDmWgsAtOnce;        // the chunk sums are added by a launch of its own
-#define LIF_DM(FUSED)                                                                                        \
-    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, ROWS, FUSED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),       \
+    const bool finish = down_mfma_finish(wg_rows, slices, batch, ROWS, L->expected_rows > 0);
+#define LIF_DM(FUSED, SHARED)                                                                                \
+    hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, ROWS, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),       \
                        dim3(kDmWaves * 64), 0, s, (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y,  \
-                       ypart, finish ? nullptr : L->arrived, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
-    if (fc.on) LIF_DM(true);
-    else LIF_DM(false);
+                       ypart, L->arrived, c.d_model, batch, c.capacity_rows, L->row_elems, down_off, chunk_rows, slices, L->st)
+    if (wg_rows == 1 || finish) { if (fc.on) LIF_DM(true, false); else LIF_DM(false, false); }
+    else { if (fc.on) LIF_DM(true, true); else LIF_DM(false, true); }
 #undef LIF_DM
     if (finish)
-        hipLaunchKernelGGL(k_ffn_down_mfma_finish, dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s, ypart, (_Float16*)y,
-                           c.d_model, batch, chunk_rows, wg_rows, L->st);
+        hipLaunchKernelGGL((k_ffn_down_finish<_Float16, float, down_mfma_chunks>), dim3((batch * c.d_model + 255) / 256), dim3(256), 0, s,
+                           ypart, (_Float16*)y, c.d_model, batch, chunk_rows, wg_rows, L->st);
 }
 
 template <bool SKIP>

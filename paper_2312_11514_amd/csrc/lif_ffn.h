@@ -248,6 +248,15 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
     return n <= kDownRowsMost ? 1 : (c > kDownChunksMax ? kDownChunksMax : c);
 }
 
+// Whether the chunk sums of that grid are added by a launch of its own: the last workgroup of a slice goes through more than 24 of
+// them in four round trips, and many workgroups that wait keep others out.  us a call in a graph, the last workgroup -> a launch, 32
+// chunks: 8 tokens, d = 1024, 4096 rows 20.0 -> 19.4, 8192 rows 30.1 -> 29.4, d = 2048 91.1 -> 90.8; 3 tokens, d = 4096 124.8 ->
+// 123.4, 4 tokens 135.4 -> 133.8; but 3 tokens, d = 1024 22.9 -> 22.9 and 37.8 -> 38.1, d = 2048 60.7 -> 60.8, d = 512 12.8 -> 13.1;
+// 16 chunks 0.5 to 0.9 better with the last workgroup at every width.
+__host__ __device__ __forceinline__ bool down_finish(int wg_rows, int slices, int batch) {
+    return wg_rows > 24 && slices * wg_rows > (batch > 4 ? 256 : 1024);
+}
+
 // Where several workgroup rows of a down projection share the row chunks, their sums meet in the launch that forms them: each
 // writes the sums of its chunks to ypart[chunk][token][d] and counts itself in at its column slice, and the last one to do so adds the
 // slice's sums in chunk order.  Nobody waits.  The sums are written and read past the caches, so that an acknowledged store is
@@ -255,8 +264,14 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
 // the L2, was twice as slow as a launch that adds them).  The count wraps to 0 by itself, whatever launches have been before.
 // us a pass, a launch of its own for these sums -> here, two timings in turn: 8 tokens of the Llama-2 shape 229.7 -> 226.8 (the launch
 // took 4.6, the down projection now 0.5 more), 12 passes of 5 tokens 2300 -> 2286, fp32 d = 1288, 3 tokens, four calls 68.6 -> 67.4;
-// 10989 rows all read, 8 tokens, d = 4096, 22 chunks, both stages 56.8 -> 56.5.  16 chunks asked for at a time are better from 25 on
-// (4 tokens, d = 2560, 40.1 -> 39.4; a launch 39.8), 8 below (the 22 chunks 56.6).
+// 10989 rows all read, 8 tokens, d = 4096, 22 chunks, both stages 56.8 -> 56.5; one FFN call of few chunks 0.5 to 0.9 (2 tokens, d =
+// 2048, 8 chunks 11.7 -> 10.8; fp32, 3 tokens, d = 1024, 16 chunks 12.8 -> 11.8).  16 chunks asked for at a time are better from 25
+// on (4 tokens, d = 2560, 40.1 -> 39.4), 8 below (the 22 chunks 56.6).
+// SHARED: the kernel form that does so.  A grid of one workgroup row has nothing to add, and where a launch of its own is better
+// (down1_finish, down_finish, down_mfma_finish) k_ffn_down_finish adds: there the form without the code and its registers is taken.
+// These rules go by the rows that a hint tells.  Without one the grid is made for the capacity, of which few rows may be in use, and
+// then a third launch costs more than it gives: us a call, the last workgroup / a launch, 8 tokens, d = 1024, 1203 of 8192 rows 10.6 /
+// 12.7, in a graph 9.6 / 10.8, fp32 14.1 / 15.8; one token, d = 4096, 283 of 20000 rows, every row read, 8.9 / 12.3.
 constexpr int kArrivedPitch = 32;     // counters of two slices are this many words apart: a cache line
 __device__ __forceinline__ void store_part(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // Whether this workgroup is the last of `parts` whose sums of a slice are written (uniform; `flag` is in LDS)
@@ -304,9 +319,9 @@ __device__ __forceinline__ void sum_parts(const float* ypart, unsigned at, unsig
 // depend on the launch geometry - and workgroup row y takes the chunks y, y + gridDim.y, ...  Every
 // chunk is summed from zero.  With one chunk in use the workgroup writes its columns of y.  With more,
 // a grid of one workgroup row adds its chunk sums in chunk order and writes y; of a taller grid the last workgroup of a slice
-// adds them in the same order (last_part), in fp64: every chunk would be another rounding of the whole (3 tokens in fp32, d =
-// 320: 1.43e-7 from the sum in fp64 against 1.60e-7).
-template <typename T, int BT, bool SKIP, int LANES, bool FUSED>
+// (SHARED, last_part) or k_ffn_down_finish adds them in the same order, in fp64: every chunk would be another rounding of the whole
+// (3 tokens in fp32, d = 320: 1.43e-7 from the sum in fp64 against 1.60e-7).
+template <typename T, int BT, bool SKIP, int LANES, bool FUSED, bool SHARED>
 __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, const float* __restrict__ h,
                                                   const FusedRows fused, T* __restrict__ y,
                                                   float* ypart, unsigned* __restrict__ arrived, int d, int batch,
@@ -487,7 +502,7 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
         if (n_active) atomicAdd(&st->c_ffn_active, (unsigned long long)n_active);
     }
     if (chunks > 1 && gridDim.y > 1) {
-        if (!last_part(arrived + slice * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
+        if (!SHARED || !last_part(arrived + slice * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
         if (writer) sum_parts<8>(ypart, (unsigned)(ob * d + ocol), (unsigned)(batch * d), chunks, total);
     }
     if (writer) {
@@ -496,6 +511,32 @@ __global__ __launch_bounds__(256) void k_ffn_down(const T* __restrict__ matrix, 
         for (int e = 0; e < VE; ++e) out[e] = (T)total[e];
         *reinterpret_cast<V*>(y + (size_t)ob * d + ocol) = out;
     }
+}
+
+// y = sum of the chunk partials in chunk order, rounded once to the element type: the launch behind a down projection whose
+// workgroups do not add them themselves.  Does nothing when a single chunk was in use (y is written already).  CHUNKS(n, by) is the
+// chunk rule of that kernel; A: the type it adds in.  The partials of the first `ahead` chunks, which its grid had workgroup rows for,
+// are requested before the row count is known; behind it they cost another round trip.  (Straight code: branches for each of them
+// were 0.5 us of instructions that run once.)  grid = ceil(batch * d / 256), block = 256.
+template <typename T, typename A, int (*CHUNKS)(int, int)>
+__global__ __launch_bounds__(256) void k_ffn_down_finish(const float* ypart, T* __restrict__ y, int d, int batch, int by, int ahead,
+                                                         const DevState* st) {
+    const int i = blockIdx.x * 256 + threadIdx.x, stride = batch * d;
+    const float* p = ypart + min(i, stride - 1);
+    const int err = st->cur.error, n = st->cur.num_used;
+    float v[kDownChunksMax];
+#pragma unroll
+    for (int c = 0; c < kDownChunksMax; ++c) v[c] = p[min(c, ahead - 1) * stride];         // (beyond: lines that are on their way already)
+    asm volatile("" ::: "memory");                   // (the compiler would ask for them, and for the count, where they are used)
+    if (err) return;
+    const int chunks = CHUNKS(n, by), here = min(ahead, chunks);
+    if (chunks == 1) return;
+    A sum = 0;
+#pragma unroll
+    for (int c = 0; c < kDownChunksMax; ++c) sum = c < here ? sum + (A)v[c] : sum;
+#pragma unroll 1
+    for (int c = ahead; c < chunks; ++c) sum += (A)p[c * stride];                          // more rows in use than the hint let expect
+    if (i < stride) y[i] = (T)sum;
 }
 
 }  // namespace lif

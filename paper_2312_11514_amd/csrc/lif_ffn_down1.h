@@ -49,6 +49,13 @@ __host__ __device__ __forceinline__ int down1_chunks(int n, int slices) {
     return c < kDownChunksMax ? c : kDownChunksMax;
 }
 
+// Whether the chunk sums of that grid are added by a launch of its own (see last_part): a workgroup that waits for its stores and its
+// count keeps the next one out where there are many rounds of them.  us a call in a graph, the last workgroup of a slice -> a launch,
+// every row read: d = 8192, 20 x 256 workgroups 121.6 -> 117.7, 16 x 256 100.4 -> 98.0, 8 x 256 44.45 -> 44.98; d = 5120, 20 x 160
+// 86.4 -> 83.9, 16 x 160 69.2 -> 68.5, 8 x 160 31.8 against 32.1; d = 4096, 20 x 128 66.4 -> 64.3, 16 x 128 44.9 -> 44.7, 8 x 128 26.1
+// against 26.4; skipping rows, d = 8192, 9 x 256 144.1 -> 142.9.
+__host__ __device__ __forceinline__ bool down1_finish(int wg_rows, int slices) { return slices * wg_rows > 2048; }
+
 // Waves of the summation order for n rows: a function of n and the width alone.  The slots are dealt to that many (virtual) waves,
 // 64 consecutive slots at a time; every wave compacts its own slots with ballots into its own list, takes the list
 // positions i with i mod 16 = row group in ascending order, folds its row groups, and the waves are added in order.  A
@@ -66,12 +73,13 @@ __host__ __device__ __forceinline__ int down1_waves(int n, int slices) {
 // spec: groups of WAVES * 64 slots whose activations are requested before the row count is known (the arrays span the
 // capacity, so the addresses are valid; values past the count are masked).
 // Workgroup row y takes the chunks y, y + gridDim.y, ...; with several chunks and several workgroup rows the sums go to
-// ypart[chunk][d] (fp32) and the last workgroup of a slice adds them (last_part), else every workgroup its own, in the same order.
+// ypart[chunk][d] (fp32) and the last workgroup of a slice (SHARED, last_part) or k_ffn_down_finish adds them, else every workgroup its
+// own, in the same order.
 // The same as a role of a larger launch (k_ffn_one): bx, by, rows_by take the place of blockIdx.x, blockIdx.y, gridDim.y, and
 // WORDS is where the activations come from: `activations(s0, stride, count, v)` fills v[q] with those of the slots s0 + q *
 // stride (q < count, different for every lane).
 struct NoWords {};
-template <typename T, bool SKIP, int WAVES, bool FUSED, typename Words>
+template <typename T, bool SKIP, int WAVES, bool FUSED, bool SHARED, typename Words>
 __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, const float* __restrict__ h, const FusedRows& fused,
                                                T* __restrict__ y, float* ypart, unsigned* __restrict__ arrived, int d,
                                                int capacity, size_t row_elems, int down_off, int spec, int slices,
@@ -279,7 +287,7 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
         atomicAdd(&st->c_ffn_rows, (unsigned long long)n);
     }
     if (chunks > 1 && rows_by > 1) {
-        if (!last_part(arrived + slice * kArrivedPitch, min(chunks, rows_by), &last)) return;
+        if (!SHARED || !last_part(arrived + slice * kArrivedPitch, min(chunks, rows_by), &last)) return;
         const int oc = slice * (LANES * VE) + tid * 4;
         if (tid < LANES * VE / 4 && oc < d) {        // four columns per thread
             double sum[4];
@@ -290,7 +298,7 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
     }
 }
 
-template <typename T, bool SKIP, int WAVES, bool FUSED>
+template <typename T, bool SKIP, int WAVES, bool FUSED, bool SHARED>
 __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ matrix, const float* __restrict__ h,
                                                           const FusedRows fused, T* __restrict__ y,
                                                           float* ypart, unsigned* __restrict__ arrived, int d, int capacity,
@@ -298,7 +306,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_ffn_down1(const T* __restrict__ 
                                                           const int32_t* __restrict__ pointers,
                                                           const float* __restrict__ gact, int gact_n,
                                                           DevState* __restrict__ st) {
-    ffn_down1_role<T, SKIP, WAVES, FUSED>(matrix, h, fused, y, ypart, arrived, d, capacity, row_elems, down_off, spec, slices, pointers, gact,
+    ffn_down1_role<T, SKIP, WAVES, FUSED, SHARED>(matrix, h, fused, y, ypart, arrived, d, capacity, row_elems, down_off, spec, slices, pointers, gact,
                                           gact_n, st, blockIdx.x, blockIdx.y, gridDim.y, NoWords());
 }
 

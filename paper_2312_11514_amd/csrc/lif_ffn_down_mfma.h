@@ -48,6 +48,19 @@ __host__ __device__ __forceinline__ int down_mfma_chunks(int n, int chunk_rows) 
     return c < 1 ? 1 : c;
 }
 
+// Whether the chunk sums of that grid are added by a launch of its own (see last_part).  Of more workgroups than the chip holds at
+// once one that waits for its stores and its count keeps the next one out: d = 5120, gated, 6 tokens, 27 chunks, both stages 79.1 us
+// with the launch, 80.1 to 80.4 with the last workgroup of a slice.  Where passes are of 256 rows all workgroups end at the same
+// time, and what the last one of a slice then reads by itself, a sum per chunk and token, nothing hides: us a call, the last workgroup ->
+// a launch, d = 1024, 8 tokens, in a graph 32 / 24 / 18 / 12 chunks 15.9 -> 15.1 / 14.4 -> 14.0 / 13.6 -> 13.3 / 11.6 -> 11.9, from the host,
+// which submits a launch more, 32 / 18 chunks 15.8 -> 15.6 / 14.0 -> 14.5; d = 2048, 8 tokens, in a graph 32 / 24 / 18 chunks 21.7 ->
+// 21.3 / 18.6 -> 18.4 / 16.9 -> 16.7, from the host 18 chunks 17.2 -> 17.5; 5 tokens, 32 chunks 20.45 -> 20.3 and 20.9 -> 21.0; 2
+// tokens, d = 1024, 32 chunks 14.6 -> 14.7.  Chunks of 512 rows and more are better off with the last workgroup (8 tokens, 32
+// chunks, in a graph: d = 1024 a launch 21.2, the last workgroup 21.1, d = 2048 32.2, 32.1).
+__host__ __device__ __forceinline__ bool down_mfma_finish(int wg_rows, int slices, int batch, int pass_rows, bool hint) {
+    return wg_rows > 1 && (slices * wg_rows > kDmWgsAtOnce || (hint && pass_rows == kDmRowsFew && wg_rows * batch > 200));
+}
+
 // Two fp16 values (one from each source register) packed into one: the low halves or the high halves.
 // v_perm_b32 picks bytes out of {s0 = bytes 7..4, s1 = bytes 3..0}.
 __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first, bool high) {
@@ -67,14 +80,15 @@ __device__ __forceinline__ unsigned pack_halves(unsigned second, unsigned first,
 // A pass compacts the contributing rows of ROWS slots (SKIP: rows with some activation; else all rows in use) in a
 // fixed order (thread-major over slots p * threads + tid); the waves take groups of 32 compacted rows in turn.
 // The waves of a pass are added in wave order, a chunk's passes in order, the chunks in chunk order (by this kernel when
-// one workgroup row is launched, else by the last workgroup of a slice from ypart[chunk][token][d], see last_part; `arrived` null: by
-// k_ffn_down_mfma_finish).  No sum depends on the launch geometry.
-template <bool SKIP, int WAVES, int ROWS, bool FUSED>
+// one workgroup row is launched, else by the last workgroup of a slice from ypart[chunk][token][d] (SHARED, last_part), or by
+// k_ffn_down_finish).  No sum depends on the launch geometry.
+template <bool SKIP, int WAVES, int ROWS, bool FUSED, bool SHARED>
 __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16* __restrict__ matrix,
                                                               const float* __restrict__ h, const FusedRows fused,
                                                               _Float16* __restrict__ y, float* ypart,
-                                                              unsigned* __restrict__ arrived, int d, int batch, int capacity, size_t row_elems, int down_off,
-                                                              int chunk_rows, int slices, DevState* __restrict__ st) {
+                                                              unsigned* __restrict__ arrived, int d, int batch, int capacity,
+                                                              size_t row_elems, int down_off, int chunk_rows, int slices,
+                                                              DevState* __restrict__ st) {
     constexpr int BT = 8, T = WAVES * 64;
     constexpr int PER = ROWS / T;                    // slots per thread in the compaction
     constexpr int kPitch = ROWS + 8;                 // fp16 values per token slot in LDS (16 bytes of padding: lanes of one
@@ -273,8 +287,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
             if (og * 4 + r < batch && ocol < d) y[(size_t)(og * 4 + r) * d + ocol] = (_Float16)total[r];
         return;
     }
-    if (!arrived) return;                            // (k_ffn_down_mfma_finish)
-    if (!last_part(arrived + blockIdx.x * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
+    if (!SHARED || !last_part(arrived + blockIdx.x * kArrivedPitch, min(chunks, (int)gridDim.y), &last)) return;
     // four columns of a token per thread
     static_assert(BT * kDmCols == 4 * T, "one piece of every token and four columns");
     const int pt = tid / (kDmCols / 4), pc = blockIdx.x * kDmCols + tid % (kDmCols / 4) * 4;
@@ -285,32 +298,6 @@ __global__ __launch_bounds__(WAVES * 64, 3) void k_ffn_down_mfma(const _Float16*
         typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
         *reinterpret_cast<f16x4*>(y + (size_t)pt * d + pc) = f16x4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
     }
-}
-
-// y = sum of the chunk partials in chunk order, rounded once to fp16: the launch behind a k_ffn_down_mfma grid of more workgroups than
-// the chip holds at once (kDmWgsAtOnce).  There a workgroup that waits for its stores and its count keeps the next one out: d = 5120,
-// gated, 6 tokens, 27 chunks, both stages 79.1 us with this launch, 80.1 to 80.4 with the last workgroup of a slice adding.  Does
-// nothing when a single chunk was in use (y is written already).  The partials of the first `ahead` chunks, which that grid had
-// workgroup rows for, are requested before the row count is known; behind it they cost another round trip.  (Straight code: branches
-// for each of them were 0.5 us of instructions that run once.)  grid = ceil(batch * d / 256), block = 256.
-__global__ __launch_bounds__(256) void k_ffn_down_mfma_finish(const float* ypart, _Float16* __restrict__ y, int d, int batch, int chunk_rows,
-                                                              int ahead, const DevState* st) {
-    const int i = blockIdx.x * 256 + threadIdx.x, stride = batch * d;
-    const float* p = ypart + min(i, stride - 1);
-    const int err = st->cur.error, n = st->cur.num_used;
-    float v[kDownChunksMax];
-#pragma unroll
-    for (int c = 0; c < kDownChunksMax; ++c) v[c] = p[min(c, ahead - 1) * stride];         // (beyond: lines that are on their way already)
-    asm volatile("" ::: "memory");                   // (the compiler would ask for them, and for the count, where they are used)
-    if (err) return;
-    const int chunks = down_mfma_chunks(n, chunk_rows), here = min(ahead, chunks);
-    if (chunks == 1) return;
-    float sum = 0.f;
-#pragma unroll
-    for (int c = 0; c < kDownChunksMax; ++c) sum = c < here ? sum + v[c] : sum;
-#pragma unroll 1
-    for (int c = ahead; c < chunks; ++c) sum += p[c * stride];                             // more rows in use than the hint let expect
-    if (i < stride) y[i] = (_Float16)sum;
 }
 
 }  // namespace lif

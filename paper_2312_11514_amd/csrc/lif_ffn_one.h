@@ -69,8 +69,8 @@ __global__ __launch_bounds__(kOneWaves * 64, 2) void k_ffn_one(const T* __restri
     if (tid == 0)
         last = st->cur.error == 0 && (int)atomicInc(&one->counted, (unsigned)slices - 1u) == slices - 1;
     const unsigned long long* mine = words + (slice & (kOneReps - 1)) * pitch;
-    ffn_down1_role<T, SKIP, kOneWaves, false>(matrix, (const float*)nullptr, FusedRows{}, y, (float*)nullptr, (unsigned*)nullptr, d, capacity, row_elems, down_off, 0,
-                                              slices, pointers, gact, gact_n, st, slice, 0, 1,
+    ffn_down1_role<T, SKIP, kOneWaves, false, false>(matrix, (const float*)nullptr, FusedRows{}, y, (float*)nullptr, (unsigned*)nullptr,
+                                              d, capacity, row_elems, down_off, 0, slices, pointers, gact, gact_n, st, slice, 0, 1,
                                               [&](int s0, int stride, int count, float (&v)[kDown1Per]) {
         unsigned p[kDown1Per];
         const bool ok = poll_words<kDown1Per>(mine + s0, stride, count, now, polls, p);

@@ -135,6 +135,20 @@ def child_ffn_one(lib, cases):
     return got
 
 
+def child_ffn_down(lib, cases):
+    """[kernel, workgroups, threads] of the launches of one lif_sparse_ffn call behind the activations, by case and row-count hint"""
+    got = {}
+    for name, (dtype, batch, full, d, capacity, hints) in cases.items():
+        h = lib.layer(d, F=65536, rank=8, k=2, capacity=capacity, max_batch=batch, f16=dtype == "f16", full=full)
+        for hint in hints:
+            assert lib.lib.lif_set_expected_rows(h, hint) == 0
+            rc, seen = lib.launches(lambda: lib.lib.lif_sparse_ffn(h, lib.p, batch, lib.p, None))
+            assert rc == 0
+            got["%s %d" % (name, hint)] = [k[:3] for k in seen[1:]]
+        lib.lib.lif_destroy(h)
+    return got
+
+
 def _run(tmp_path_factory, what, *args):
     stub = str(tmp_path_factory.getbasetemp() / "hip_host_stub.so")
     if not os.path.exists(stub):
