@@ -175,7 +175,7 @@ struct lif_layer {
     float* gact;                // null unless the gate projection is the predictor
     size_t row_elems, row_bytes;
     bool window_pending;
-    int expected_rows;          // hint, 0 = none
+    int expected_rows;          // hint, at most the capacity; 0 = none
     unsigned char* static_scratch;  // this device's copy of the library's static scratch array (null: lookup failed)
     // event timing
     bool prof_on;
@@ -268,7 +268,7 @@ void launch_ffn_up(lif_layer* L, const void* x, int batch, float* h, hipStream_t
     const int ni = (nvec + 63) / 64;
     // one wave per row; with a row-count hint the grid is sized to it and the first pass is speculative
     const int spec = L->expected_rows > 0 ? 1 : 0;
-    const int grid = spec ? std::min(kUpMaxWgs, std::max(1, std::min(L->expected_rows, c.capacity_rows) / 4))
+    const int grid = spec ? std::min(kUpMaxWgs, std::max(1, L->expected_rows / 4))
                           : std::min((c.capacity_rows + 3) / 4, 512);
     const size_t shm = batch == 1 ? 0 : (size_t)batch * c.d_model * sizeof(T);
 #define LIF_UP_X(NI, XREG)                                                                                   \
@@ -320,7 +320,7 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     const int slices = down1_slices(c);
     const int rows = geometry_rows(L);
     // fewer workgroup rows than chunks are still correct; one, and no partial sums, where the hint itself needs one chunk
-    const bool one = L->expected_rows > 0 && down1_chunks<SKIP>(std::min(L->expected_rows, c.capacity_rows), slices) == 1;
+    const bool one = L->expected_rows > 0 && down1_chunks<SKIP>(L->expected_rows, slices) == 1;
     const int wg_rows = one ? 1 : down1_chunks<SKIP>(rows, slices);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
     // Waves of a workgroup: what the rows likely in use need, a little less than the hint says.  Any choice is correct, but a
@@ -442,7 +442,7 @@ template <typename T, bool GLU, bool SKIP>
 void launch_ffn_one(lif_layer* L, const void* x, void* y, hipStream_t s) {
     const lif_config& c = L->cfg;
     const int ni = (c.d_model / Vec<T>::N + 63) / 64, slices = down1_slices(c), spec = L->expected_rows > 0 ? 1 : 0;
-    const int rows = spec ? std::min(L->expected_rows, c.capacity_rows) : c.capacity_rows;
+    const int rows = spec ? L->expected_rows : c.capacity_rows;
     const int n_up = std::max(1, (rows + kOneUpWaves - 1) / kOneUpWaves);
 #define LIF_ONE(NI)                                                                                          \
     hipLaunchKernelGGL((k_ffn_one<T, NI, GLU, SKIP>), dim3(n_up + slices), dim3(kOneWaves * 64), 0, s,              \
@@ -494,7 +494,7 @@ StepArgs step_args(lif_layer* L, const void* x, uint8_t* masks, uint8_t* step_ma
 }
 // workgroups of the activation role with one wave per row; with a row-count hint the grid is sized to it
 int up_blocks(const lif_layer* L) {
-    return L->expected_rows > 0 ? std::min(kUpMaxWgs, std::max(1, std::min(L->expected_rows, L->cfg.capacity_rows) / 4))
+    return L->expected_rows > 0 ? std::min(kUpMaxWgs, std::max(1, L->expected_rows / 4))
                                 : std::min((L->cfg.capacity_rows + 3) / 4, 512);
 }
 
@@ -514,11 +514,8 @@ bool mfma_path(const lif_config& c, int batch) {
     return c.dtype == LIF_F16 && batch > 1 && c.d_model % 32 == 0;
 }
 
-// 16-row tiles a row-count hint covers (at least one, at most all)
-int mfma_hint_tiles(const lif_layer* L) {
-    const int tiles = (L->cfg.capacity_rows + 15) / 16;
-    return std::max(1, std::min(tiles, (L->expected_rows + 15) / 16));
-}
+// 16-row tiles a row-count hint covers (at least one)
+int mfma_hint_tiles(const lif_layer* L) { return std::max(1, (L->expected_rows + 15) / 16); }
 
 // several tokens, the predictor's launches done: window, load and activations (allow: see launch_step_batch_as)
 hipError_t launch_step_batch(lif_layer* L, StepArgs a, bool allow, hipStream_t s) {
@@ -1022,7 +1019,7 @@ int lif_set_handoff_polls(lif_layer* L, int32_t polls) {
 
 int lif_set_expected_rows(lif_layer* L, int32_t rows) {
     if (!L || rows < 0) return fail(LIF_INVALID_ARG, "bad row hint");
-    L->expected_rows = rows;
+    L->expected_rows = std::min(rows, L->cfg.capacity_rows);       // (more are never in use)
     return LIF_OK;
 }
 

@@ -212,5 +212,16 @@ def test_single_launch_ffn_is_compared_with_two_launches(child):
             assert len(kernels) == 1 and "k_ffn_one" in kernels[0], (case, kernels)
 
 
+def test_waves_of_a_layer_whose_capacity_the_hint_exceeds(child):
+    """Rows past the capacity are never in use: a hint beyond it counts as the capacity.  Eight waves (512 threads) for at most 2048 rows of
+    one token, whatever the hint says."""
+    cases = {"%s%d %d" % (dtype, full, capacity): (dtype, 1, bool(full), 4096, capacity, [0, capacity, capacity + 1, 2400, 5000, 2**31 - 1])
+             for dtype in ("f16", "f32") for full in (0, 1) for capacity in (900, 2048)}
+    got = child("ffn_down", cases)
+    assert len(got) == 8 * 6
+    for case, kernels in got.items():
+        assert len(kernels) == 1 and "k_ffn_down1" in kernels[0][0] and kernels[0][2] == 512, (case, kernels)
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()["child_" + sys.argv[2]](Library(sys.argv[1]), *map(json.loads, sys.argv[3:]))))
