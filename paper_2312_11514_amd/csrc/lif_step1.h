@@ -425,6 +425,18 @@ struct PostLds {
 constexpr int kStepXOff = (int)(kLoaderPlanLds + (sizeof(PostLds) + 15) / 16 * 16);
 __host__ __device__ __forceinline__ int step_x_pitch(int d, int elem) { return d * elem + 16; }     // (16: the reads of 16 tokens
                                                                                                      //  fall on different banks)
+// Early bundles (see cache_role): the forms that have them, the tiles of neurons whose first added one is asked for early (the first
+// words of `firsts` threads, one tile per pair of loaders), and the first of the units dealt in turn that loader lw takes if it has
+// none of the `early` tiles: a whole number of bundles before lw, so its part is lw % parts.
+constexpr bool early_form(int ni, bool gate) { return ni > 2 && !gate; }
+__host__ __device__ __forceinline__ int early_tiles(int added, int loaders, int firsts) {
+    const int pairs = loaders / 2 < kWave ? loaders / 2 : kWave;
+    return added * 2 >= loaders ? (pairs < firsts ? pairs : firsts) : 0;
+}
+__host__ __device__ __forceinline__ int first_unit(int lw, int parts, int tiles, unsigned long long early) {
+    const int pair = lw / parts;
+    return lw - parts * __builtin_popcountll(pair < tiles ? early & ((1ull << (pair & 63)) - 1ull) : early);
+}
 template <typename T, int NI, bool GLU, bool GATE, int MODE>
 __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L, PostLds* post, unsigned char* lds_x) {
     using V = typename Vec<T>::type;
@@ -473,11 +485,11 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     // The gated forms are 67 to 86 KB of code, more than the 64 KB instruction cache of two compute units.  With the tile decided by
     // the predictor's own code (53 to 75 KB), which leaves the window's words to be read behind the bundle, most were slower all the
     // same: OPT shape 52.6 -> 53.0, Llama-2 shape 130.0 -> 131.2, fp32 d = 4096 80.3 -> 81.1.
-    constexpr bool EARLY = MODE == kOneToken && !GATE && PAIRED;
+    constexpr bool EARLY = MODE == kOneToken && early_form(NI, GATE);
     constexpr int PARTS = PAIRED ? 2 : 1;                         // loaders of a bundle
-    const int early_tiles = EARLY && cur.n_added * PARTS >= a.n_load ? min(min(a.n_load / PARTS, kWave), (nwords + wpt - 1) / wpt) : 0;
+    const int tiles = EARLY ? early_tiles(cur.n_added, a.n_load, (nwords + wpt - 1) / wpt) : 0;
     const int mine = (wg - 1) / PARTS;                            // (wg >= 1)
-    const bool has_early = wg > 0 && mine < early_tiles;
+    const bool has_early = wg > 0 && mine < tiles;
     const unsigned stamp_now = (unsigned)cur.step + 1u;
     const int n = cur.num_used, slot_now = cur.ring_pos % k, oldest = min(cur.window_len, k - a.keep);      // largest age that stays in the window
     unsigned long long prev[4], keep[4], m[4], now[4];
@@ -517,7 +529,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
         const int v = (pr << 16) | pa, inc = wave_inclusive_scan(v, lane), ex = inc - v;         // (a wave counts at most 16384)
         const unsigned long long none = __any(missing) ? 1ull << 63 : 0ull;
         if constexpr (EARLY) {
-            const unsigned long long adds = __ballot(lane < early_tiles && (now[0] & ~prev[0]) != 0ull);
+            const unsigned long long adds = __ballot(lane < tiles && (now[0] & ~prev[0]) != 0ull);
             if (tid == 0) L.early = adds;
         }
         if (lane == kWave - 1) L.wave_tot[wave] = none | ((unsigned long long)(unsigned)(inc >> 16) << 32) | (unsigned)(inc & 0xffff);
@@ -740,8 +752,7 @@ __device__ __forceinline__ void cache_role(const StepArgs& a, int wg, PlanLds& L
     const unsigned long long early = EARLY && __builtin_amdgcn_readfirstlane(tot_a) <= kListItems ? uniform(adding) : 0ull;
     const int n_early = __popcll(early);
     const bool is_early = has_early && ((early >> mine) & 1ull);
-    // (a whole number of bundles before lw: the part of a bundle that this loader takes first is lw % PARTS)
-    const int unit_first = lw - PARTS * (mine < early_tiles ? __popcll(early & ((1ull << (mine & 63)) - 1ull)) : n_early);
+    const int unit_first = first_unit(lw, PARTS, tiles, early);
     auto early_before = [&]() {                                   // ... of the threads below this one
         return wave == 0 ? (int)__builtin_amdgcn_mbcnt_hi((unsigned)(early >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)early, 0u)) : n_early;
     };

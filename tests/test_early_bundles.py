@@ -1,7 +1,9 @@
 """Bundles that the loaders of a one-token step ask for ahead of the list of all added neurons (many were added the step before): the
 step against the four calls, bit for bit, with few loaders and with more than 64, whole bundles and bundles in two parts, several mask
 words per thread, lists of more than one piece on either side, the dynamic window, passes of tokens in between (whose rejected
-tokens leave neurons in the cache that are in no mask of the window), and polls = 0, where no loader knows its own tile in time."""
+tokens leave neurons in the cache that are in no mask of the window), and polls = 0, where no loader knows its own tile in time.
+Which steps have early bundles is the rule that tests/test_step_rules.py looks at; results cannot tell which request a bundle came
+with."""
 import numpy as np
 import pytest
 import torch
@@ -46,7 +48,7 @@ def test_early_bundles_equal_four_calls(name, polls):
         fused.layer.set_loader_pairs(pairs)
         fused.layer.set_handoff_polls(polls)
         if tokens == 1:
-            early += fused.layer.state()["last_added"] * parts >= 2 * pairs
+            early += parts == 2 and fused.layer.state()["last_added"] >= pairs
             fused.layer.step(xf, fused.y, 1)
             calls.layer.step_calls(xc, calls.y, 1)
         else:
@@ -58,4 +60,4 @@ def test_early_bundles_equal_four_calls(name, polls):
         assert a[0]["error"] == 0 and a[0] == b[0], (name, at, a[0], b[0])
         for i, (u, v) in enumerate(zip(a[2:], b[2:])):
             assert u == v, (name, at, i)
-    assert early >= 2
+    assert early >= 2 if parts == 2 else early == 0

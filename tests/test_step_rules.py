@@ -23,6 +23,9 @@ int main() {
     int a, b, c;
     while (scanf("%15s %d %d %d", what, &a, &b, &c) == 4) {
         if (!strcmp(what, "hides")) printf("%d\\n", (int)lif::load_hides_activations(a, b, c));
+        if (!strcmp(what, "form")) printf("%d\\n", (int)lif::early_form(a, b != 0));
+        if (!strcmp(what, "tiles")) printf("%d\\n", lif::early_tiles(a, b, c));
+        if (!strcmp(what, "unit")) printf("%d\\n", lif::first_unit(a, 2, b, (unsigned long long)c << (b > 31 ? b - 31 : 0)));
         if (!strcmp(what, "waves")) printf("%d\\n", lif::up_mfma_waves(a, b, c != 0));
         if (!strcmp(what, "await")) {           // b slots, the first c of them there, by thread a of 512: looks, and the answer
             int looks = 0;
@@ -60,3 +63,24 @@ def test_waves_per_tile_by_rounds_on_the_chip(rule):
     assert rule("waves", (512, 4096, 0), (513, 4096, 0), (513, 4128, 0), (897, 4096, 0), (4096, 32, 0)) == [8, 4, 8, 4, 4]
     assert rule("waves", (512, 2048, 1), (513, 2048, 1), (896, 4096, 1), (897, 4096, 1), (897, 2016, 1), (1194, 2048, 1), (1195, 2048, 1),
                 (600, 4128, 1)) == [8, 4, 4, 8, 4, 8, 4, 8]
+
+
+def test_early_bundles_where_the_last_step_kept_every_loader_busy(rule):
+    """Rows of more than 2 KiB and the low-rank predictor; (neurons added by the last step, loaders, threads with a first word) -> tiles decided
+    early: one per pair of loaders, at most as many as there are."""
+    assert rule("form", (1, 0, 0), (2, 0, 0), (4, 0, 0), (16, 0, 0), (4, 1, 0), (16, 1, 0)) == [0, 0, 1, 1, 0, 0]
+    assert rule("tiles", (0, 40, 256), (19, 40, 256), (20, 40, 256), (65536, 40, 256), (500, 128, 256), (500, 128, 31), (500, 10, 3),
+                (1, 2, 256)) == [0, 0, 20, 20, 64, 31, 3, 1]
+
+
+def test_first_units_of_the_loaders_without_an_early_bundle(rule):
+    """Every unit that is dealt in turn has one loader in the first round, and is the part of a bundle that its number says; some of `tiles` pairs
+    have an early bundle (a mask of 31 bits, those of the last tiles)."""
+    for loaders, tiles in ((40, 20), (128, 64), (128, 31), (10, 3), (2, 1), (26, 13)):
+        for mask in (0, 1, 2, 0x155, 0x7fffffff, 0x40080001):
+            mask &= (1 << min(tiles, 31)) - 1
+            early = mask << max(tiles - 31, 0)
+            others = [lw for lw in range(loaders) if lw // 2 >= tiles or not early >> (lw // 2) & 1]
+            units = rule("unit", *[(lw, tiles, mask) for lw in others]) if others else []
+            assert units == list(range(len(others))), (loaders, tiles, mask)
+            assert all(u % 2 == lw % 2 for u, lw in zip(units, others))
