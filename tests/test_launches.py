@@ -226,11 +226,11 @@ def test_waves_of_a_layer_whose_capacity_the_hint_exceeds(child):
 def test_waves_of_a_hint_around_the_rows_of_eight(child):
     """The hint is the mean number of rows in use: 16 waves (1024 threads) where a sixteenth more than that is beyond what eight waves take in
     one go (2048), eight up to there, and again where every row is read and the rows make several chunks."""
-    hints = {"f16": (1, 1900, 1927, 1928, 2048, 2100, 2340, 3000, 9000), "f32": (1927, 1928, 2100)}
+    hints = {"f16": (1, 1900, 1928, 1929, 2048, 2100, 2340, 3000, 9000), "f32": (1928, 1929, 2100)}
     got = child("ffn_down", {dtype: (dtype, 1, False, 4096, 9000, h) for dtype, h in hints.items()})
     for case, kernels in got.items():
-        assert len(kernels) == 1 and kernels[0][2] == (512 if int(case.split()[1]) <= 1927 else 1024), (case, kernels)
-    got = child("ffn_down", {"full": ("f16", 1, True, 4096, 9000, (1927, 1928, 4000, 4200))})
+        assert len(kernels) == 1 and kernels[0][2] == (512 if int(case.split()[1]) <= 1928 else 1024), (case, kernels)
+    got = child("ffn_down", {"full": ("f16", 1, True, 4096, 9000, (1928, 1929, 4000, 4200))})
     assert [k[0][2] for k in got.values()] == [512, 1024, 1024, 512]
 
 
