@@ -437,6 +437,10 @@ void launch_ffn_down(lif_layer* L, int batch, void* y, float* h, float* ypart, h
 // 6.0 -> 5.8 / 6.8 -> 5.7; fp32, 64 slices, d = 1024 685: 6.4 -> 5.6 / 6.9 -> 5.6.  Rows gated or read in full are longer on their way:
 // 64 slices 685: gated 6.15 -> 6.27 / 6.8 -> 6.3, in full 6.45 -> 6.55 / 6.8 -> 6.4, so half as many words there.  128 slices (OPT shape),
 // 927: 6.5 -> 7.2 / 8.8 -> 7.7, 7.4 -> 7.9 where the host is fast: two launches.
+// Without a hint the capacity counts, and every slot of it has a wave in the launch (rows in use of capacity): 64 slices 174 of 500: 5.8 ->
+// 5.45 / 8.6 -> 5.6, gated 194 of 500 5.9 -> 5.55 / 8.8 -> 5.8, in full 174 of 500 5.9 -> 5.6 / 8.7 -> 5.7, 174 of 1000 5.7 -> 6.0 / 8.7 ->
+// 6.2, 552 of 1000 6.0 -> 6.5 / 8.7 -> 6.6; 32 slices 164 of 2000 5.5 -> 5.1 / 8.7 -> 5.3, 970 of 2000 5.9 -> 5.4 / 8.5 -> 5.8; fp32, 64
+// slices 369 of 1000 6.0 -> 6.0 / 8.7 -> 6.3: what a graph loses at the end of the range is a fifth of what the host gains.
 bool ffn_one(const lif_layer* L, int batch) {
     const int rows = geometry_rows(L), slices = down1_slices(L->cfg);
     const int most = L->cfg.glu || L->cfg.ffn_mode == LIF_FFN_FULL_BUNDLE ? kOneWords / 2 : kOneWords;

@@ -266,7 +266,10 @@ __host__ __device__ __forceinline__ bool down_finish(int wg_rows, int slices, in
 // took 4.6, the down projection now 0.5 more), 12 passes of 5 tokens 2300 -> 2286, fp32 d = 1288, 3 tokens, four calls 68.6 -> 67.4;
 // 10989 rows all read, 8 tokens, d = 4096, 22 chunks, both stages 56.8 -> 56.5; one FFN call of few chunks 0.5 to 0.9 (2 tokens, d =
 // 2048, 8 chunks 11.7 -> 10.8; fp32, 3 tokens, d = 1024, 16 chunks 12.8 -> 11.8).  16 chunks asked for at a time are better from 25
-// on (4 tokens, d = 2560, 40.1 -> 39.4), 8 below (the 22 chunks 56.6).
+// on (8 at a time -> 16, fp16: 26 chunks, 2 tokens, d = 1024 14.4 -> 13.6, d = 2048 17.8 -> 17.05, d = 3072 22.4 -> 21.6; 27 chunks, 2
+// tokens, d = 1024 19.9 -> 19.1; 32 chunks, 8 tokens, d = 1024 21.7 -> 21.1, d = 3072 39.6 -> 39.0; 4 tokens, d = 2560 40.1 -> 39.4), 8
+// below (18 and 24 chunks, d = 1024, 8 tokens 13.65 -> 13.9 and 14.4 -> 14.65, 5 tokens 13.2 -> 13.1 and 13.8 -> 14.05, 2 tokens 0.1 to
+// 0.3 better with 16; the 22 chunks above 56.6 -> 56.9).  In fp32 16 at a time cost a resident wave: 8 always.
 // SHARED: the kernel form that does so.  A grid of one workgroup row has nothing to add, and where a launch of its own is better
 // (down1_finish, down_finish, down_mfma_finish) k_ffn_down_finish adds: there the form without the code and its registers is taken.
 // These rules go by the rows that a hint tells.  Without one the grid is made for the capacity, of which few rows may be in use, and
