@@ -1,9 +1,7 @@
 """Bundles that the loaders of a one-token step ask for ahead of the list of all added neurons (many were added the step before): the
 step against the four calls, bit for bit, with few loaders and with more than 64, whole bundles and bundles in two parts, several mask
 words per thread, lists of more than one piece on either side, the dynamic window, passes of tokens in between (whose rejected
-tokens leave neurons in the cache that are in no mask of the window), and polls = 0, where no loader knows its own tile in time.
-Which steps have early bundles is the rule that tests/test_step_rules.py looks at; results cannot tell which request a bundle came
-with."""
+tokens leave neurons in the cache that are in no mask of the window), and polls = 0, where no loader knows its own tile in time."""
 import numpy as np
 import pytest
 import torch
@@ -48,7 +46,7 @@ def test_early_bundles_equal_four_calls(name, polls):
         fused.layer.set_loader_pairs(pairs)
         fused.layer.set_handoff_polls(polls)
         if tokens == 1:
-            early += parts == 2 and fused.layer.state()["last_added"] >= pairs
+            early += fused.layer.state()["last_added"] * parts >= 2 * pairs
             fused.layer.step(xf, fused.y, 1)
             calls.layer.step_calls(xc, calls.y, 1)
         else:
@@ -60,4 +58,20 @@ def test_early_bundles_equal_four_calls(name, polls):
         assert a[0]["error"] == 0 and a[0] == b[0], (name, at, a[0], b[0])
         for i, (u, v) in enumerate(zip(a[2:], b[2:])):
             assert u == v, (name, at, i)
-    assert early >= 2 if parts == 2 else early == 0
+    assert early >= 2
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_cases_have_early_bundles_where_the_form_has_them(name):
+    """By the rule that tests/test_step_rules.py looks at: rows of more than 2 KiB, and a last step that added as many neurons as there are pairs
+    of loaders.  (Results cannot tell which request a bundle came with.)"""
+    from tests.harness import GpuLayer
+    w, L, X, pairs = _make(name, CASES[name])
+    g = GpuLayer(w, L, shrink=w.shrink)
+    g.layer.set_loader_pairs(pairs)
+    early = 0
+    for x in X[:5]:
+        early += w.d_model * w.elem_bytes > 2048 and g.layer.state()["last_added"] >= pairs
+        g.layer.step(g.upload_x(x), g.y, 1)
+    print(f"{name}: {early} steps with early bundles", flush=True)
+    assert g.layer.state()["error"] == 0 and (early >= 2 if not name.startswith("whole") else early == 0)

@@ -1,5 +1,5 @@
-"""Registers of the single-launch step, as the compiler reports them: how many workgroups fit a compute unit at every width (two with the
-gate predictor), and no register goes to memory, which would queue up behind the host reads."""
+"""Registers of the single-launch step with the gate predictor, as the compiler reports them: two workgroups fit a compute unit at every
+width, and no register goes to memory, which would queue up behind the host reads."""
 import os
 import re
 import shutil
