@@ -328,8 +328,9 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     // half of its waves idle where 8 are in use, so without a hint 8 are taken only where every row is read and most layers of
     // this capacity hold more than one chunk (OPT shape, 8192 rows: 29.9 -> 28.3 us).
     // Few rows: 8 waves as long as a sixteenth more than the hint says are still few.  One FFN call in a graph, us, launched with 8 / 16
-    // waves: d = 4096 2000 rows 6.8 / 7.0, 2060 rows 8.6 / 7.2; fp32 d = 2048 2000 rows 7.05 / 7.15, 2060 rows 8.75 / 7.3: to be wrong
-    // with 8 costs seven times as much as with 16, and the hint is a mean that the rows in use are around.
+    // waves: d = 4096 2000 rows 6.8 / 7.0, 2060 rows 8.6 / 7.2; fp32 d = 2048 2000 rows 7.05 / 7.0, 2060 rows 8.75 / 7.3; a step with the
+    // gate resident, d = 4096, rows around 1992 98.9 / 99.15, around 2255 107.5 / 104.7: to be wrong with 8 costs several times as much as
+    // with 16, and the hint is a mean that the rows in use are around.
     const int told = L->expected_rows;
     const int likely = told > 0 ? (std::min(c.capacity_rows, told + told / 16) <= kDown1FewRows ? told : std::max(kDown1FewRows + 1, told - told / 8))
                        : rows <= kDown1FewRows ? rows : std::max(kDown1FewRows + 1, SKIP ? kDown1OneSkip : c.capacity_rows / 2);

@@ -148,7 +148,38 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
     const int per_chunk = chunks == 1 ? n : (n + chunks - 1) / chunks;      // (no division on the shortest path)
     const int vwaves = down1_waves<SKIP>(n, slices);
     const int stride = vwaves * 64;                  // slots between the groups of a (virtual) wave
-    const bool natural = vwaves == WAVES;            // the requests above were for the right slots
+    int asked = vwaves == WAVES ? spec : 0;          // groups of these waves that the requests above were for
+    if constexpr (WAVES == 16 && !WORDS) {
+        // Few rows, which 8 of the waves take (one chunk): the others hold every second group of theirs, and hand it over in LDS.  Asked for
+        // again it was another round trip behind the row count.  us, 16 waves launched, asked again -> handed over / 8 waves launched: a step
+        // with the gate resident, d = 4096, 1992 rows 99.5 -> 99.15 / 98.9; low-rank, OPT shape, 1994 rows 80.9 -> 80.6 / 80.8; an FFN call
+        // in a graph fp32 d = 2048, 1600 rows 7.2 -> 7.0 / 7.1, fp16 d = 4096 the same.
+        if (n <= kDown1FewRows && spec > 0) {        // uniform
+            constexpr int HALF = PER / 2;            // (groups of 1024 slots that hold 2048)
+            float hq[HALF];
+            int oq[HALF];
+#pragma unroll
+            for (int q = 0; q < HALF; ++q) {
+                const bool fresh = stamp && sfirst[q] == cur_step;
+                hq[q] = fresh ? hnfirst[q] : hfirst[q];
+                oq[q] = fresh ? onfirst[q] : ofirst[q];
+                if (wv >= 8) {
+                    hv[wv][q * 64 + lane] = hq[q];
+                    if (gact) list[wv][q * 64 + lane] = oq[q];
+                }
+            }
+            lds_barrier();
+#pragma unroll
+            for (int q = 0; q < HALF; ++q) {
+                hfirst[2 * q] = hq[q];
+                hfirst[2 * q + 1] = hv[8 + (wv & 7)][q * 64 + lane];
+                ofirst[2 * q] = oq[q];
+                if (gact) ofirst[2 * q + 1] = list[8 + (wv & 7)][q * 64 + lane];
+                sfirst[2 * q] = sfirst[2 * q + 1] = -1;
+            }
+            asked = min(PER, 2 * spec);
+        }
+    }
     double total = 0.0;
     for (int chunk = by; chunk < chunks; chunk += rows_by) {
         const int r0 = chunk * per_chunk, r1 = min(n, r0 + per_chunk);
@@ -162,7 +193,7 @@ __device__ __forceinline__ void ffn_down1_role(const T* __restrict__ matrix, con
                 const int s0 = s_base + vw * 64 + lane;
                 const int start = cnt;               // list position of the first entry of this pass
                 const int need = min(PER, (r1 - s_base - vw * 64 + stride - 1) / stride);       // groups with rows in them
-                const int have = (natural && first_row && s_base == 0) ? spec : 0;              // ... requested at the start
+                const int have = first_row && s_base == 0 ? asked : 0;                          // ... requested at the start
                 float hval[PER];
                 int owner[PER];
 #pragma unroll
