@@ -339,7 +339,7 @@ void launch_ffn_down1(lif_layer* L, void* y, float* h, float* ypart, hipStream_t
     // slots if that many rows make one pass (else the order of the slots is not known yet)
     const int spec = L->expected_rows > 0 || waves == 8 ? std::min(kDown1Per, (rows + waves * 64 - 1) / (waves * 64)) : 0;
     const FusedRows f = fused_rows(L, fc);
-    const bool finish = L->expected_rows > 0 && down1_finish(wg_rows, slices);
+    const bool finish = told > 0 && wg_rows > 1 && down1_finish(down1_chunks<SKIP>(told, slices), slices);
 #define LIF_D1(W, FUSED, SHARED)                                                                             \
     hipLaunchKernelGGL((k_ffn_down1<T, SKIP, W, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(W * 64), 0, s, \
                        (const T*)L->buf.matrix, h, f, (T*)y, ypart, L->arrived, c.d_model, c.capacity_rows, L->row_elems,        \
@@ -368,7 +368,7 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
     const int slices = (c.d_model + cols - 1) / cols;
     const int wg_rows = down_chunks(geometry_rows(L), slices);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    const bool finish = L->expected_rows > 0 && down_finish(wg_rows, slices, batch);
+    const bool finish = L->expected_rows > 0 && wg_rows > 1 && down_finish(down_chunks(L->expected_rows, slices), slices, batch);
 #define LIF_DB(FUSED, SHARED)                                                                                \
     hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(256),  \
                        0, s, (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, L->arrived, c.d_model, batch,          \
@@ -391,7 +391,8 @@ void launch_ffn_down_mfma_rows(lif_layer* L, int batch, void* y, float* h, float
     // capacity; fewer than the chunks in use is still correct (a workgroup row then takes several chunks)
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    const bool finish = down_mfma_finish(wg_rows, slices, batch, ROWS, L->expected_rows > 0);
+    const int told = L->expected_rows > 0 ? down_mfma_chunks(L->expected_rows, chunk_rows) : 0;       // chunks of the hint
+    const bool finish = wg_rows > 1 && down_mfma_finish(wg_rows, told, slices, batch);
 #define LIF_DM(FUSED, SHARED)                                                                                \
     hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, ROWS, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),       \
                        dim3(kDmWaves * 64), 0, s, (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y,  \

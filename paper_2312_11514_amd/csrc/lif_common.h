@@ -155,8 +155,8 @@ __device__ __forceinline__ U uniform_load(const U* p) {
 // stacked layers of it from a graph 467.5 -> 465.2 and 476.4 -> 471.3, Falcon shape 134.6 -> 133.3 and 135.9 -> 134.8, Llama-2 shape from
 // a graph 132.1 -> 130.5 and 132.0 -> 130.8, gate resident 105.1 -> 104.1 and 105.8 -> 104.8, 8 tokens 230.6 -> 229.5 and 231.0 -> 230.4
 // (two runs of one build differ by up to 0.4 %).  lif_load_bundles keeps plain stores: the
-// activation stage behind it finds the rows in the L2 (fp32 d = 1288, 3 tokens, four calls 68.6 against 69.2).  Activations, and partial
-// outputs that only a later launch reads, were no faster written through; partial outputs that the same launch reads have to be (store_part).
+// activation stage behind it finds the rows in the L2 (fp32 d = 1288, 3 tokens, four calls 68.6 against 69.2).  Activations
+// were no faster written through; partial outputs are (store_part), and have to be where the same launch reads them.
 template <typename V>
 __device__ __forceinline__ void store_through(char* base, unsigned off, unsigned bytes, V v) {
     static_assert(sizeof(V) == 16, "four dwords");

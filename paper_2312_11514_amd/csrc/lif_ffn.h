@@ -248,13 +248,13 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
     return n <= kDownRowsMost ? 1 : (c > kDownChunksMax ? kDownChunksMax : c);
 }
 
-// Whether the chunk sums of that grid are added by a launch of its own: the last workgroup of a slice goes through more than 24 of
-// them in four round trips, and many workgroups that wait keep others out.  us a call in a graph, the last workgroup -> a launch, 32
-// chunks: 8 tokens, d = 1024, 4096 rows 20.0 -> 19.4, 8192 rows 30.1 -> 29.4, d = 2048 91.1 -> 90.8; 3 tokens, d = 4096 124.8 ->
-// 123.4, 4 tokens 135.4 -> 133.8; but 3 tokens, d = 1024 22.9 -> 22.9 and 37.8 -> 38.1, d = 2048 60.7 -> 60.8, d = 512 12.8 -> 13.1;
-// 16 chunks 0.5 to 0.9 better with the last workgroup at every width.
-__host__ __device__ __forceinline__ bool down_finish(int wg_rows, int slices, int batch) {
-    return wg_rows > 24 && slices * wg_rows > (batch > 4 ? 256 : 1024);
+// Whether the sums of so many chunks are added by a launch of its own: the last workgroup of a slice goes through more than 24 of
+// them in four round trips, the longer the more tokens there are, and many workgroups that wait keep others out.  us a call in a
+// graph, skipping, the last workgroup -> a launch, means over 2048 to 16384 rows and, if not said, d = 256 to 2048: 32 chunks 5, 6, 8 tokens
+// 0.95, 0.86, 0.80 better (d = 512, 8 tokens, 4096 rows 16.2 -> 15.3; submitted by the host 0.5 better), 3 and 4 tokens 0.2 worse, d = 4096 1.4
+// better; 21 to 24 chunks 5 to 8 tokens the same, 2 to 4 tokens 0.5 to 0.9 worse; 16 chunks 0.6 to 1.5 worse.
+__host__ __device__ __forceinline__ bool down_finish(int chunks, int slices, int batch) {
+    return chunks > 24 && (batch > 4 || slices * chunks > 1024);
 }
 
 // Where several workgroup rows of a down projection share the row chunks, their sums meet in the launch that forms them: each
@@ -276,6 +276,7 @@ __host__ __device__ __forceinline__ bool down_finish(int wg_rows, int slices, in
 // then a third launch costs more than it gives: us a call, the last workgroup / a launch, 8 tokens, d = 1024, 1203 of 8192 rows 10.6 /
 // 12.7, in a graph 9.6 / 10.8, fp32 14.1 / 15.8; one token, d = 4096, 283 of 20000 rows, every row read, 8.9 / 12.3.
 constexpr int kArrivedPitch = 32;     // counters of two slices are this many words apart: a cache line
+// (Also where a later launch reads them: with plain stores there 8 tokens, d = 1024, 16384 rows took 22.3 us instead of 21.4.)
 __device__ __forceinline__ void store_part(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // Whether this workgroup is the last of `parts` whose sums of a slice are written (uniform; `flag` is in LDS)
 __device__ __forceinline__ bool last_part(unsigned* arrived, int parts, int* flag) {

@@ -49,7 +49,7 @@ __host__ __device__ __forceinline__ int down1_chunks(int n, int slices) {
     return c < kDownChunksMax ? c : kDownChunksMax;
 }
 
-// Whether the chunk sums of that grid are added by a launch of its own (see last_part): a workgroup that waits for its stores and its
+// Whether the sums of so many chunks are added by a launch of its own (see last_part): a workgroup that waits for its stores and its
 // count keeps the next one out where there are many rounds of them, and beyond 16 sums the last workgroup of a slice goes through a third
 // round trip.  us a call in a graph, the last workgroup of a slice -> a launch, every row read, fp16 unless it says fp32: d = 1024, 16 x 32
 // workgroups 18.9 -> 19.2, 18 x 32 22.0 -> 21.55, 20 x 32 22.9 -> 22.5; d = 2048, 18 x 64 30.3 -> 30.2; d = 3072, 16 x 96 36.95 -> 37.05,
@@ -57,7 +57,7 @@ __host__ __device__ __forceinline__ int down1_chunks(int n, int slices) {
 // -> 46.2), 18 x 128 59.4 -> 57.9; d = 5120, 10 x 160 39.9 -> 39.6, 12 x 160 45.4 either way, 14 x 160 61.4 -> 60.0, 20 x 160 93.1 -> 90.1;
 // d = 8192, 8 x 256 46.8 -> 47.5, 10 x 256 68.7 -> 67.7, 20 x 256 127.9 -> 124.4.  Up to 8 chunks the last workgroup is 0.6 to 1.5 better at
 // every width, every row read or not.
-__host__ __device__ __forceinline__ bool down1_finish(int wg_rows, int slices) { return wg_rows > 16 || slices * wg_rows > 2048; }
+__host__ __device__ __forceinline__ bool down1_finish(int chunks, int slices) { return chunks > 16 || slices * chunks > 2048; }
 
 // Waves of the summation order for n rows: a function of n and the width alone.  The slots are dealt to that many (virtual) waves,
 // 64 consecutive slots at a time; every wave compacts its own slots with ballots into its own list, takes the list

@@ -48,17 +48,15 @@ __host__ __device__ __forceinline__ int down_mfma_chunks(int n, int chunk_rows) 
     return c < 1 ? 1 : c;
 }
 
-// Whether the chunk sums of that grid are added by a launch of its own (see last_part).  Of more workgroups than the chip holds at
-// once one that waits for its stores and its count keeps the next one out: d = 5120, gated, 6 tokens, 27 chunks, both stages 79.1 us
-// with the launch, 80.1 to 80.4 with the last workgroup of a slice.  Where passes are of 256 rows all workgroups end at the same
-// time, and what the last one of a slice then reads by itself, a sum per chunk and token, nothing hides: us a call, the last workgroup ->
-// a launch, d = 1024, 8 tokens, in a graph 32 / 24 / 18 / 12 chunks 15.9 -> 15.1 / 14.4 -> 14.0 / 13.6 -> 13.3 / 11.6 -> 11.9, from the host,
-// which submits a launch more, 32 / 18 chunks 15.8 -> 15.6 / 14.0 -> 14.5; d = 2048, 8 tokens, in a graph 32 / 24 / 18 chunks 21.7 ->
-// 21.3 / 18.6 -> 18.4 / 16.9 -> 16.7, from the host 18 chunks 17.2 -> 17.5; 5 tokens, 32 chunks 20.45 -> 20.3 and 20.9 -> 21.0; 2
-// tokens, d = 1024, 32 chunks 14.6 -> 14.7.  Chunks of 512 rows and more are better off with the last workgroup (8 tokens, 32
-// chunks, in a graph: d = 1024 a launch 21.2, the last workgroup 21.1, d = 2048 32.2, 32.1).
-__host__ __device__ __forceinline__ bool down_mfma_finish(int wg_rows, int slices, int batch, int pass_rows, bool hint) {
-    return wg_rows > 1 && (slices * wg_rows > kDmWgsAtOnce || (hint && pass_rows == kDmRowsFew && wg_rows * batch > 200));
+// Whether the chunk sums of that grid are added by a launch of its own (see last_part); told: chunks of the row-count hint, 0 without one.
+// Of more workgroups than the chip holds at once one that waits for its stores and its count keeps the next one out: d = 5120, gated, 6
+// tokens, 27 chunks, both stages 79.1 us with the launch, 80.1 to 80.4 with the last workgroup of a slice.  Else all workgroups end at about
+// the same time, and what the last one of a slice then reads by itself, a sum per chunk and token, nothing hides: us a call, skipping, a launch
+// against the last workgroup, means over d = 512 to 3072 and chunks of 256 and 512 rows, in a graph / submitted by the host: 8 tokens 32 chunks 0.7
+// / 0.4 better (d = 1024, 16384 rows 22.4 -> 21.4), 17 to 24 chunks 0.45 / 0.15 better, 16 chunks 0.2 / 0.5 worse; 5 tokens 0.3 to 0.4 / 0.05 better
+// from 17 on, 0.3 / 0.7 worse with 16; 4 tokens 0.15 to 0.3 better / 0.05 worse; 2 tokens the same / 0.35 worse.
+__host__ __device__ __forceinline__ bool down_mfma_finish(int wg_rows, int told, int slices, int batch) {
+    return slices * wg_rows > kDmWgsAtOnce || (told > 16 && batch > 4);
 }
 
 // Two fp16 values (one from each source register) packed into one: the low halves or the high halves.

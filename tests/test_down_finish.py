@@ -12,9 +12,9 @@ from tests.test_launches import _run
 MANY_WORKGROUPS = ("f16", 2, False, 4104, 12304, (19, 24), True)
 CASES = [("f16", 1, False, 136, 16384, (2, 4), False), ("f16", 1, True, 72, 8000, (5, 6), False), ("f32", 1, True, 68, 16384, (9, 13), False),
          ("f16", 1, True, 8192, 9304, (5, 7), True), ("f16", 1, True, 136, 30000, (17, 24), True),
-         ("f16", 5, False, 160, 4800, (18, 19), False), ("f16", 8, False, 136, 7000, (27, 28), True), ("f16", 8, True, 264, 15000, (29, 30), False),
+         ("f16", 5, False, 160, 4800, (18, 19), True), ("f16", 8, False, 136, 7000, (27, 28), True), ("f16", 8, True, 264, 15000, (29, 30), True),
          ("f16", 3, False, 4104, 1480, (5, 6), False), MANY_WORKGROUPS,
-         ("f32", 3, False, 132, 1400, (10, 11), False), ("f32", 8, True, 68, 9000, (32, 32), False), ("f32", 5, False, 1020, 4200, (30, 32), True)]
+         ("f32", 3, False, 132, 1400, (10, 11), False), ("f32", 8, True, 68, 9000, (32, 32), True), ("f32", 5, False, 1020, 4200, (30, 32), True)]
 # (those of tests/test_down_chunks.py)
 BESIDE = [("f16", 1, False, 136, 16384), ("f16", 1, True, 72, 8000), ("f32", 1, True, 68, 16384), ("f16", 5, False, 160, 4800),
           ("f16", 8, True, 264, 15000), ("f16", 3, False, 4104, 1480), MANY_WORKGROUPS[:5], ("f32", 3, False, 132, 1400),
@@ -22,16 +22,16 @@ BESIDE = [("f16", 1, False, 136, 16384), ("f16", 1, True, 72, 8000), ("f32", 1, 
 
 
 def test_launch_that_adds_the_chunk_sums(tmp_path_factory):
-    """A launch of its own behind many workgroups of one token or of fp16 rows, behind more than 16 chunks of one token, behind many sums of fp16 rows of several tokens in passes of
-    256 rows, behind more than 24 chunks of fp32 rows of several tokens: on either side of each line.  A hint of one chunk: none.  No
-    hint, and so a grid for the capacity: only behind more workgroups of fp16 rows than the chip holds."""
+    """A launch of its own where a hint makes more than 16 chunks of one token, or many workgroups; more than 16 chunks of fp16 rows of five tokens
+    and more; more than 24 chunks of fp32 rows of as many tokens, or of wide rows: on either side of each line.  A hint of one chunk:
+    none.  No hint, and so a grid for the capacity: only behind more workgroups of fp16 rows than the chip holds."""
     lines = {
         # hints on either side of the line, then one of a single chunk
         "one": ("f16", 1, True, 8192, 20480, (8190 * 8 // 9, 9300 * 8 // 9, 900)), "one-skip": ("f32", 1, False, 4096, 50000, (29000, 36000, 900)),
-        "one-many-sums": ("f16", 1, True, 1024, 20480, (14563, 14700, 900)), "one-many-sums-f32": ("f32", 1, True, 512, 65536, (14563, 14700, 900)),
+        "one-many-sums": ("f16", 1, True, 1024, 20480, (16384, 16385, 900)), "one-many-sums-f32": ("f32", 1, True, 512, 65536, (16384, 16385, 900)),
         "many-workgroups": ("f16", 2, False, 4104, 16384, (10400, 11000, 200)),
-        "many-sums": ("f16", 8, False, 1024, 8192, (5688, 5700, 200)), "few-tokens": ("f16", 4, False, 1024, 8192, (4000, 8192, 200)),
-        "f32": ("f32", 5, False, 1024, 20000, (2720, 4096, 200)), "f32-few-tokens": ("f32", 4, False, 2048, 20000, (4096, 16384, 200)),
+        "many-sums": ("f16", 8, False, 1024, 8192, (4096, 4097, 200)), "many-sums-512": ("f16", 5, True, 1024, 16384, (8192, 8193, 200)), "few-tokens": ("f16", 4, False, 1024, 8192, (4000, 8192, 200)),
+        "f32": ("f32", 5, False, 1024, 20000, (3072, 3073, 200)), "f32-narrow": ("f32", 8, True, 256, 9000, (3072, 3073, 200)), "f32-few-tokens": ("f32", 4, False, 2048, 20000, (4096, 16384, 200)),
         "f32-wide": ("f32", 4, False, 4096, 20000, (9000, 16384, 200)),
     }
     got = _run(tmp_path_factory, "ffn_down", lines)
