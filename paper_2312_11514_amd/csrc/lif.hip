@@ -392,7 +392,7 @@ void launch_ffn_down_mfma_rows(lif_layer* L, int batch, void* y, float* h, float
     const int wg_rows = down_mfma_chunks(geometry_rows(L), chunk_rows);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
     const int told = L->expected_rows > 0 ? down_mfma_chunks(L->expected_rows, chunk_rows) : 0;       // chunks of the hint
-    const bool finish = wg_rows > 1 && down_mfma_finish(wg_rows, told, slices, batch);
+    const bool finish = wg_rows > 1 && down_mfma_finish(wg_rows, fc.on ? 0 : told, slices, batch);
 #define LIF_DM(FUSED, SHARED)                                                                                \
     hipLaunchKernelGGL((k_ffn_down_mfma<SKIP, kDmWaves, ROWS, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows),       \
                        dim3(kDmWaves * 64), 0, s, (const _Float16*)L->buf.matrix, h, fused_rows(L, fc), (_Float16*)y,  \

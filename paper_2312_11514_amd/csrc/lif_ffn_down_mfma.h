@@ -48,15 +48,18 @@ __host__ __device__ __forceinline__ int down_mfma_chunks(int n, int chunk_rows) 
     return c < 1 ? 1 : c;
 }
 
-// Whether the chunk sums of that grid are added by a launch of its own (see last_part); told: chunks of the row-count hint, 0 without one.
+// Whether the chunk sums of that grid are added by a launch of its own (see last_part); told: chunks of the row-count hint, 0 without one
+// and in a fused step.
 // Of more workgroups than the chip holds at once one that waits for its stores and its count keeps the next one out: d = 5120, gated, 6
 // tokens, 27 chunks, both stages 79.1 us with the launch, 80.1 to 80.4 with the last workgroup of a slice.  Else all workgroups end at about
 // the same time, and what the last one of a slice then reads by itself, a sum per chunk and token, nothing hides: us a call, skipping, a launch
 // against the last workgroup, means over d = 512 to 3072 and chunks of 256 and 512 rows, in a graph / submitted by the host: 8 tokens 32 chunks 0.7
 // / 0.4 better (d = 1024, 16384 rows 22.4 -> 21.4), 17 to 24 chunks 0.45 / 0.15 better, 16 chunks 0.2 / 0.5 worse; 5 tokens 0.3 to 0.4 / 0.05 better
-// from 17 on, 0.3 / 0.7 worse with 16; 4 tokens 0.15 to 0.3 better / 0.05 worse; 2 tokens the same / 0.35 worse.
+// from 17 on, 0.3 / 0.7 worse with 16; 4 tokens 0.15 to 0.3 better / 0.05 worse; 2 tokens the same / 0.35 worse.  d = 3584, 17 to 32 chunks
+// 0.4 better in a graph; d = 4096 0.2 better skipping, the same with every row read, gated 0.3 worse (56.2 -> 56.5).  In a fused step the last
+// workgroup is better: 8 tokens d = 1024, 22 chunks 74.75 against 75.8 us, d = 2048 74.45 against 75.5, the Llama-2 shape 226.1 against 228.7.
 __host__ __device__ __forceinline__ bool down_mfma_finish(int wg_rows, int told, int slices, int batch) {
-    return slices * wg_rows > kDmWgsAtOnce || (told > 16 && batch > 4);
+    return slices * wg_rows > kDmWgsAtOnce || (told > 16 && batch > 4 && slices < 32);
 }
 
 // Two fp16 values (one from each source register) packed into one: the low halves or the high halves.

@@ -23,21 +23,24 @@ BESIDE = [("f16", 1, False, 136, 16384), ("f16", 1, True, 72, 8000), ("f32", 1, 
 
 def test_launch_that_adds_the_chunk_sums(tmp_path_factory):
     """A launch of its own where a hint makes more than 16 chunks of one token, or many workgroups; more than 16 chunks of fp16 rows of five tokens
-    and more; more than 24 chunks of fp32 rows of as many tokens, or of wide rows: on either side of each line.  A hint of one chunk:
+    and more, below 4096 columns; more than 24 chunks of fp32 rows of as many tokens, or of wide rows: on either side of each line.  A hint of one chunk:
     none.  No hint, and so a grid for the capacity: only behind more workgroups of fp16 rows than the chip holds."""
     lines = {
         # hints on either side of the line, then one of a single chunk
         "one": ("f16", 1, True, 8192, 20480, (8190 * 8 // 9, 9300 * 8 // 9, 900)), "one-skip": ("f32", 1, False, 4096, 50000, (29000, 36000, 900)),
         "one-many-sums": ("f16", 1, True, 1024, 20480, (16384, 16385, 900)), "one-many-sums-f32": ("f32", 1, True, 512, 65536, (16384, 16385, 900)),
         "many-workgroups": ("f16", 2, False, 4104, 16384, (10400, 11000, 200)),
-        "many-sums": ("f16", 8, False, 1024, 8192, (4096, 4097, 200)), "many-sums-512": ("f16", 5, True, 1024, 16384, (8192, 8193, 200)), "few-tokens": ("f16", 4, False, 1024, 8192, (4000, 8192, 200)),
-        "f32": ("f32", 5, False, 1024, 20000, (3072, 3073, 200)), "f32-narrow": ("f32", 8, True, 256, 9000, (3072, 3073, 200)), "f32-few-tokens": ("f32", 4, False, 2048, 20000, (4096, 16384, 200)),
+        "many-sums": ("f16", 8, False, 1024, 8192, (4096, 4097, 200)), "many-sums-512": ("f16", 5, True, 3968, 16384, (8192, 8193, 200)),
+        "4096-columns": ("f16", 8, True, 4096, 11008, (8192, 10000, 200)), "few-tokens": ("f16", 4, False, 1024, 8192, (4000, 8192, 200)),
+        "f32": ("f32", 5, False, 1024, 20000, (3072, 3073, 200)), "f32-narrow": ("f32", 8, True, 256, 9000, (3072, 3073, 200)),
+        "f32-few-tokens": ("f32", 4, False, 2048, 20000, (4096, 16384, 200)),
         "f32-wide": ("f32", 4, False, 4096, 20000, (9000, 16384, 200)),
     }
+    last = ("4096-columns", "few-tokens", "f32-few-tokens")            # never a launch
     got = _run(tmp_path_factory, "ffn_down", lines)
     for name, case in lines.items():
         few, many, none = (got["%s %d" % (name, h)] for h in case[-1])
-        assert [len(v) for v in (few, many, none)] == [1, 1 if "few-tokens" in name else 2, 1], (name, few, many, none)
+        assert [len(v) for v in (few, many, none)] == [1, 1 if name in last else 2, 1], (name, few, many, none)
         assert len(many) == 1 or "k_ffn_down_finish" in many[1][0]
     cases = {str(i): (dtype, batch, full, d, F, (0, F)) for i, (dtype, batch, full, d, F, _, _) in enumerate(CASES)}
     got = _run(tmp_path_factory, "ffn_down", cases)
