@@ -368,7 +368,7 @@ void launch_ffn_down_batch(lif_layer* L, int batch, void* y, float* h, float* yp
     const int slices = (c.d_model + cols - 1) / cols;
     const int wg_rows = down_chunks(geometry_rows(L), slices);
     const int down_off = (c.glu ? 2 : 1) * c.d_model;
-    const bool finish = L->expected_rows > 0 && wg_rows > 1 && down_finish(down_chunks(L->expected_rows, slices), slices, batch);
+    const bool finish = !fc.on && L->expected_rows > 0 && wg_rows > 1 && down_finish(down_chunks(L->expected_rows, slices), slices, batch);
 #define LIF_DB(FUSED, SHARED)                                                                                \
     hipLaunchKernelGGL((k_ffn_down<T, BT, SKIP, kDownLanesB, FUSED, SHARED>), dim3(slices + (FUSED ? 1 : 0), wg_rows), dim3(256),  \
                        0, s, (const T*)L->buf.matrix, h, fused_rows(L, fc), (T*)y, ypart, L->arrived, c.d_model, batch,          \

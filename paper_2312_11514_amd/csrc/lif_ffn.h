@@ -253,6 +253,9 @@ __host__ __device__ __forceinline__ int down_chunks(int n, int slices) {
 // graph, skipping, the last workgroup -> a launch, means over 2048 to 16384 rows and, if not said, d = 256 to 2048: 32 chunks 5, 6, 8 tokens
 // 0.95, 0.86, 0.80 better (d = 512, 8 tokens, 4096 rows 16.2 -> 15.3; submitted by the host 0.5 better), 3 and 4 tokens 0.2 worse, d = 4096 1.4
 // better; 21 to 24 chunks 5 to 8 tokens the same, 2 to 4 tokens 0.5 to 0.9 worse; 16 chunks 0.6 to 1.5 worse.
+// In a fused step the last workgroup adds them always: us a step, against a launch, 5 tokens, d = 1288, 27 chunks 151.4 / 153.65, 6 tokens, d =
+// 1536, 31 chunks 162.1 / 164.8, 8 tokens, d = 1024, 32 chunks of 419 rows 93.8 / 94.4, of 219 rows 64.9 / 64.4, d = 256 45.3 / 44.8, 4 tokens, d =
+// 4096 270.7 / 270.1.
 __host__ __device__ __forceinline__ bool down_finish(int chunks, int slices, int batch) {
     return chunks > 24 && (batch > 4 || slices * chunks > 1024);
 }
